@@ -103,6 +103,12 @@ struct LiveArgs {
     uint32_t bits[MAX_POOL / 32];
 };
 
+// one launch's worth of chunks on their way to the host (kernel argument): chunk i = frames[i] rows from row row[i] of the mel
+// ring, to row to[i] of the pinned staging buffer
+struct StageArgs {
+    int row[MAX_POOL], frames[MAX_POOL], to[MAX_POOL];
+};
+
 // one launch's worth of slot moves (kernel argument): request i goes from slot from[i] to slot to[i]; L = its encoder
 // length, t = frames it has produced so far (an upper bound is fine)
 constexpr int MOVE_BATCH = 32;

@@ -45,6 +45,8 @@ constexpr int N_STEP_KERNELS = 4;
 hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int cur, hipStream_t s, hipEvent_t* ev = nullptr);
 
 hipError_t launch_set_live(const DevPtrs& d, const LiveArgs& args, hipStream_t s);
+// chunks of `n` (<= MAX_POOL) requests from the mel ring to pinned host memory (its device address; 16-byte aligned)
+hipError_t launch_stage_chunks(const DevPtrs& d, const StageArgs& sa, int n, int most_frames, float* dst, hipStream_t s);
 // the whole per-slot state of `n` (<= MOVE_BATCH) running requests, each from its slot to a free one; the slots moved
 // from and the slots moved to are disjoint
 hipError_t launch_move_slots(const DevPtrs& d, int wdtype, int mdtype, const MoveArgs& mv, int n, hipStream_t s);

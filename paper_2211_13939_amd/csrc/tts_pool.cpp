@@ -233,6 +233,8 @@ extern "C" size_t tts_pool_workspace_bytes(const tts_config* cfg)
 }
 
 // ------------------------------------------------------------------ pool
+static const size_t STAGE_BYTES = 16u << 20;
+
 struct tts_pool {
     tts_config cfg;
     DevPtrs d;
@@ -248,9 +250,15 @@ struct tts_pool {
     std::map<int, hipGraphExec_t> graphs;   // key = ((steps * 1024 + bucket) * 2 + parity
     std::vector<hipGraph_t> graph_defs;
     int* h_fault = nullptr;       // pinned, mapped: non-zero once a kernel's bounded wait has run out
-    float* h_chunk = nullptr;     // pinned staging for one chunk on its way to the caller's (pageable) buffer: a copy from
-                                  // the device into pinned memory is a plain DMA, one into pageable memory is staged by the
-                                  // runtime at three times the cost
+    // Pinned staging of chunks on their way to the caller's (pageable) buffers.  The first drain after some steps copies every
+    // chunk that is ready, one launch and one wait for all of them; the drains that follow find theirs here.  stage_regions
+    // regions of stage_frames frames: one per slot, or a single one where chunks are so long that this would be more than
+    // STAGE_BYTES (then each drain copies its own).
+    float* h_stage = nullptr;
+    float* d_stage = nullptr;     // its device address
+    int stage_regions = 0, stage_frames = 0;
+    struct Staged { int64_t id = -1; int first = 0, count = 0; };
+    std::vector<Staged> staged;   // per region: which frames of which request it holds (frames never change once made)
     int n_slots_padded = 0;       // slots the arena holds (max_pool rounded up to whole tiles)
     std::vector<int64_t> lost_ids; // requests the device ended early that tts_pool_sync has not reported yet
 };
@@ -421,9 +429,18 @@ extern "C" int tts_pool_create(const tts_config* cfg, const tts_weights* w, void
             return rc0;
         }
     }
-    if (hipHostMalloc(reinterpret_cast<void**>(&p->h_chunk), (size_t)cfg->chunk_frames * N_MEL * 4, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        p->h_chunk = nullptr;     // drains then copy straight into the caller's buffer
+    {
+        p->stage_frames = std::min(cfg->chunk_frames, cfg->max_steps);
+        const size_t region = (size_t)p->stage_frames * N_MEL * 4;
+        p->stage_regions = region * cfg->max_pool <= STAGE_BYTES ? cfg->max_pool : 1;
+        hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&p->h_stage), region * p->stage_regions, hipHostMallocMapped);
+        if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&p->d_stage), p->h_stage, 0);
+        if (e != hipSuccess) {
+            const int rc0 = fail(TTS_E_HIP, "pinned staging buffer: %s", hipGetErrorString(e));
+            tts_pool_destroy(p);
+            return rc0;
+        }
+        p->staged.resize(p->stage_regions);
     }
     d.WmemT = (const float*)(base + l.WmemT);
     d.lsa_kfrag = base + l.lsa_kfrag;
@@ -488,7 +505,7 @@ extern "C" void tts_pool_destroy(tts_pool* p)
     if (p->ev0) (void)hipEventDestroy(p->ev0);
     if (p->ev1) (void)hipEventDestroy(p->ev1);
     if (p->h_fault) (void)hipHostFree(p->h_fault);
-    if (p->h_chunk) (void)hipHostFree(p->h_chunk);
+    if (p->h_stage) (void)hipHostFree(p->h_stage);
     delete p;
 }
 
@@ -831,6 +848,45 @@ static int refresh_slot(tts_pool* p, int slot)
     return TTS_OK;
 }
 
+// where slot's planned chunk lies in the staging buffer, or null
+static const float* find_staged(const tts_pool* p, int slot, int first, int count)
+{
+    if (slot >= p->stage_regions) return nullptr;
+    const tts_pool::Staged& st = p->staged[slot];
+    return st.id == p->book->slot(slot).id && st.first == first && st.count == count ? p->h_stage + (size_t)slot * p->stage_frames * N_MEL : nullptr;
+}
+
+// Copies the chunk of `slot` to the staging buffer, and with it (a region per slot) every other chunk that the next drains
+// could hand out and that is not there yet; waits for the stream.
+static int stage_chunks(tts_pool* p, int slot)
+{
+    StageArgs sa;
+    int n = 0, most = 0;
+    const bool all = p->stage_regions > 1;
+    for (int k = all ? 0 : slot; k < (all ? p->cfg.max_pool : slot + 1); ++k) {
+        const SlotInfo& si = p->book->slot(k);
+        if (si.state == SlotState::Free) continue;
+        int first, count, fin;
+        p->book->drain_plan(k, &first, &count, &fin);
+        if (count == 0 || (all && find_staged(p, k, first, count))) continue;
+        const int region = all ? k : 0;
+        p->staged[region].id = all ? si.id : -1;
+        p->staged[region].first = first;
+        p->staged[region].count = count;
+        sa.row[n] = k * p->cfg.max_steps + first;
+        sa.frames[n] = count;
+        sa.to[n] = region * p->stage_frames;
+        most = std::max(most, count);
+        ++n;
+    }
+    if (n == 0) return TTS_OK;
+    hipError_t e = launch_stage_chunks(p->d, sa, n, most, p->d_stage, p->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
+    if (e == hipSuccess) return TTS_OK;
+    for (tts_pool::Staged& st : p->staged) st.id = -1;
+    return fail(TTS_E_HIP, "copying chunks to the host: %s", hipGetErrorString(e));
+}
+
 extern "C" int tts_pool_drain_chunk(tts_pool* p, int64_t id, float* dst, int* out_frames, int* out_finished)
 {
     if (!p || !dst || !out_frames || !out_finished) return fail(TTS_E_INVAL, "null argument");
@@ -841,22 +897,20 @@ extern "C" int tts_pool_drain_chunk(tts_pool* p, int64_t id, float* dst, int* ou
     int first, count, fin;
     p->book->drain_plan(slot, &first, &count, &fin);
     if (count > 0) {
-        float* via = p->h_chunk ? p->h_chunk : dst;      // count <= chunk_frames: the staging buffer holds it
-        const float* src = p->d.mel_ring + ((size_t)slot * p->cfg.max_steps + first) * N_MEL;
-        HIP_TRY(hipMemcpyAsync(via, src, (size_t)count * N_MEL * 4, hipMemcpyDeviceToHost, p->stream));
-        HIP_TRY(hipStreamSynchronize(p->stream));
-        if (*p->h_fault) {
-            // some request was frozen since the last look: if it is this one, the plan above counted frames that were
-            // never made; plan again from what the device holds (the copy above is then repeated for the right range)
-            if ((rc = absorb_failures(p))) return rc;
-            p->book->drain_plan(slot, &first, &count, &fin);
-            if (count > 0) {
-                src = p->d.mel_ring + ((size_t)slot * p->cfg.max_steps + first) * N_MEL;
-                HIP_TRY(hipMemcpyAsync(via, src, (size_t)count * N_MEL * 4, hipMemcpyDeviceToHost, p->stream));
-                HIP_TRY(hipStreamSynchronize(p->stream));
+        const float* from = find_staged(p, slot, first, count);
+        if (!from) {
+            if ((rc = stage_chunks(p, slot))) return rc;
+            if (*p->h_fault) {
+                // some request was frozen since the last look: if it is this one, the plan above counted frames that were
+                // never made; plan again from what the device holds (the copy is then repeated for the right range)
+                if ((rc = absorb_failures(p))) return rc;
+                p->book->drain_plan(slot, &first, &count, &fin);
+                if (count > 0 && (p->stage_regions == 1 || !find_staged(p, slot, first, count)))
+                    if ((rc = stage_chunks(p, slot))) return rc;
             }
+            from = p->h_stage + (size_t)(p->stage_regions > 1 ? slot : 0) * p->stage_frames * N_MEL;
         }
-        if (via != dst && count > 0) memcpy(dst, via, (size_t)count * N_MEL * 4);
+        if (count > 0) memcpy(dst, from, (size_t)count * N_MEL * 4);
         p->book->drain_commit(slot, count);
     }
     *out_frames = count;

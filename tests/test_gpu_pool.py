@@ -815,3 +815,35 @@ def test_steps_of_a_pool_above_64_slots_beside_other_work_on_the_gpu(weights_bf1
     quiet, busy = decode(False), decode(True)
     for a, b in zip(quiet, busy):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("chunk,max_steps", [(8, 24), (1, 24), (4000, 4000)])
+def test_chunks_staged_together(chunk, max_steps, wl8, weights_fp32, solo_frames):
+    """A drain brings every chunk that is ready to the host; what it brought is handed out later, after further steps, also
+    when a slot has gone to another request meanwhile.  (4000: chunks too long for a staging region per slot.)"""
+    say(f"case: staged chunks, chunk_frames {chunk}")
+    pool = make_pool(wl8, weights_fp32, max_pool=16, max_enc_len=90, max_steps=max_steps, chunk_frames=chunk)
+    ids = pool.add_requests([wl8.encoder_outputs(i) for i in range(6)], [24, 24, 17, 9, 24, 5])
+    got = {i: [] for i in range(8)}
+
+    def drain(i, rid):
+        frames, fin = pool.drain_chunk(rid)
+        got[i].append(frames)
+        return fin
+
+    pool.step_n(8)
+    drain(0, ids[0])                                  # brings the others' chunks along
+    drain(5, ids[5])
+    pool.retire(ids[5])
+    late = pool.add_request(wl8.encoder_outputs(7), 16)       # takes the slot of a request whose chunk was staged
+    pool.step_n(5)
+    for i in (4, 3, 2, 1):
+        drain(i, ids[i])
+    pool.step_n(24)
+    for i, rid in [(i, ids[i]) for i in range(5)] + [(7, late)]:
+        while not drain(i, rid):
+            pass
+    for i, n in ((0, 24), (1, 24), (2, 17), (3, 9), (4, 24), (7, 16)):
+        np.testing.assert_array_equal(np.concatenate(got[i]), solo_frames[i][:n])
+    np.testing.assert_array_equal(np.concatenate(got[5])[:1], solo_frames[5][:1])
+    pool.close()
