@@ -19,8 +19,8 @@
  * The output is fp32 [tokens][512] in device memory, ready to be handed to
  * tts_pool_add_request as a device pointer.  All kernels are queued on the
  * stream given at creation; device memory comes from the caller's arena;
- * nothing is allocated on the device (creation allocates one pinned host
- * buffer, through which the ids travel).  Conventions as in tts_pool.h: 0 on
+ * nothing is allocated on the device (creation allocates pinned host memory:
+ * two buffers through which the ids travel, in turn, and a status word).  Conventions as in tts_pool.h: 0 on
  * success, negative tts_status otherwise, text in tts_last_error(); one owner
  * thread per object.
  */
@@ -77,7 +77,10 @@ int tts_encoder_create(const tts_encoder_config *cfg, const tts_encoder_weights 
  *   d_out   DEVICE fp32 [total][2 * hid]: F_enc of the requests back to back.
  * Asynchronous on the stream (ids and lens are consumed before the call returns).
  * Errors: TTS_E_INVAL for null pointers, n outside 1 .. TTS_ENCODER_MAX_BATCH, bad lengths, more than
- * max_tokens tokens, or an id outside its table.
+ * max_tokens tokens, or an id outside its table.  With fp32 weights the workgroups of the recurrence hand h to each
+ * other and wait for it, a bounded time; if such a wait ran out (never seen: it takes a device that keeps a workgroup
+ * from starting for a quarter of a second), the next tts_encoder_run or tts_encoder_elapsed_ms returns TTS_E_LOST once:
+ * the results of the call before it are not valid.
  */
 int tts_encoder_run(tts_encoder *enc, const int *ids, const int *lens, int n, float *d_out);
 

@@ -8,6 +8,7 @@
 #include <new>
 #include <vector>
 
+#include "dev.h"
 #include "encoder_kernels.h"
 #include "hostutil.h"
 
@@ -31,7 +32,7 @@ int check(const tts_encoder_config* c)
 
 struct EncLayout {
     size_t tables[ENC_TABLES], conv_w[ENC_CONVS], conv_b[ENC_CONVS], w_ih[2], w_hh[2], b[2];
-    size_t act[2], cmeta, orow, ids, xproj, total;
+    size_t act[2], cmeta, hx, xproj, total;
     size_t scratch_begin;      // everything from here on is cleared at creation
 };
 
@@ -54,8 +55,7 @@ EncLayout layout_of(const tts_encoder_config& c)
     l.scratch_begin = a.off;
     for (int i = 0; i < 2; ++i) l.act[i] = a.take(cols * ENC_DIM * ws);
     l.cmeta = a.take(cols * 4);
-    l.orow = a.take(cols * 4);
-    l.ids = a.take((size_t)ENC_TABLES * c.max_tokens * 4);
+    l.hx = a.take(ws == 4 ? (size_t)2 * ENC_MAX_BATCH * 2 * ENC_HID * 4 : 0);
     l.xproj = a.take((size_t)2 * c.max_tokens * ENC_GATES * 4);
     l.total = a.off;
     return l;
@@ -63,6 +63,8 @@ EncLayout layout_of(const tts_encoder_config& c)
 
 // gate row r of the permuted matrices = (unit r / 4, gate r % 4); the caller's rows are gate * hid + unit
 inline int source_row(int r) { return (r % 4) * ENC_HID + r / 4; }
+// two-byte W_hh: row tile t = gate t % 4 of the units 16 (t / 4) ..
+inline int source_row_by_gate(int r) { return (r / 16 % 4) * ENC_HID + 16 * (r / 64) + r % 16; }
 
 }  // namespace
 
@@ -70,12 +72,26 @@ struct tts_encoder {
     tts_encoder_config cfg;
     EncoderPtrs d;
     hipStream_t stream = nullptr;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    bool ev_valid = false;
-    int* h_ids = nullptr;            // pinned staging buffer [tables][max_tokens]: the caller's ids leave its memory at once
-    hipEvent_t ev_copied = nullptr;  // the staging buffer has been read by the last call's copies
-    bool copy_pending = false;
+    // Two pinned staging buffers, taken in turn: what a call hands over leaves the caller's memory at once, the device reads it
+    // from here, and a buffer is free again when the call before last has ended.
+    struct Staging {
+        int4* ids = nullptr;
+        int* meta = nullptr;
+        EncStaged dev;                   // the same, device addresses
+        hipEvent_t ev0 = nullptr, ev1 = nullptr;
+        bool used = false;
+    } st[2];
+    int last = -1;                       // staging buffer of the last call
+    int* h_fault = nullptr;              // pinned, mapped: non-zero once a kernel's bounded wait has run out
 };
+
+// a workgroup of an earlier call gave up waiting for its partners: that call's results are not valid
+static int check_fault(tts_encoder* e)
+{
+    if (!e->h_fault || !*e->h_fault) return TTS_OK;
+    *e->h_fault = 0;
+    return fail(TTS_E_LOST, "a bounded wait of an earlier tts_encoder_run ran out: its results are not valid");
+}
 
 extern "C" size_t tts_encoder_workspace_bytes(const tts_encoder_config* cfg)
 {
@@ -125,7 +141,7 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
         const float *ih = w->w_ih[d], *hh = w->w_hh[d], *bb = w->b[d];
         rc = upload(base + lay.w_ih[d], pack_fragments(ENC_GATES, ENC_DIM, bf, [&](int r, int k) { return ih[(size_t)source_row(r) * ENC_DIM + k]; }), bf);
         if (rc == TTS_OK)
-            rc = upload(base + lay.w_hh[d], pack_fragments(ENC_GATES, ENC_HID, bf, [&](int r, int k) { return hh[(size_t)source_row(r) * ENC_HID + k]; }), bf);
+            rc = upload(base + lay.w_hh[d], pack_fragments(ENC_GATES, ENC_HID, bf, [&](int r, int k) { return hh[(size_t)(bf ? source_row_by_gate(r) : source_row(r)) * ENC_HID + k]; }), bf);
         if (rc == TTS_OK) {
             std::vector<float> bp(ENC_GATES);
             for (int r = 0; r < ENC_GATES; ++r) bp[r] = bb[source_row(r)];
@@ -134,11 +150,28 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
     }
     if (rc == TTS_OK && hipMemset(base + lay.scratch_begin, 0, lay.total - lay.scratch_begin) != hipSuccess)
         rc = fail(TTS_E_HIP, "clearing the activation buffers failed");
-    if (rc == TTS_OK && (hipEventCreate(&e->ev0) != hipSuccess || hipEventCreate(&e->ev1) != hipSuccess ||
-                         hipEventCreate(&e->ev_copied) != hipSuccess))
-        rc = fail(TTS_E_HIP, "hipEventCreate failed");
-    if (rc == TTS_OK && hipHostMalloc((void**)&e->h_ids, (size_t)ENC_TABLES * cfg->max_tokens * 4, hipHostMallocDefault) != hipSuccess)
-        rc = fail(TTS_E_HIP, "hipHostMalloc of the id staging buffer failed");
+    const size_t n_tok = cfg->max_tokens;
+    for (tts_encoder::Staging& st : e->st) {
+        if (rc == TTS_OK && (hipEventCreate(&st.ev0) != hipSuccess || hipEventCreate(&st.ev1) != hipSuccess))
+            rc = fail(TTS_E_HIP, "hipEventCreate failed");
+        void* dev = nullptr;
+        if (rc == TTS_OK && (hipHostMalloc((void**)&st.ids, n_tok * (sizeof(int4) + sizeof(int)), hipHostMallocMapped) != hipSuccess ||
+                             hipHostGetDevicePointer(&dev, st.ids, 0) != hipSuccess))
+            rc = fail(TTS_E_HIP, "hipHostMalloc of an id staging buffer failed");
+        if (rc) break;
+        st.meta = reinterpret_cast<int*>(st.ids + n_tok);
+        st.dev.ids = static_cast<const int4*>(dev);
+        st.dev.meta = reinterpret_cast<const int*>(st.dev.ids + n_tok);
+    }
+    if (rc == TTS_OK) {
+        if (hipHostMalloc((void**)&e->h_fault, sizeof(int), hipHostMallocMapped) != hipSuccess ||
+            hipHostGetDevicePointer((void**)&e->d.fault, e->h_fault, 0) != hipSuccess)
+            rc = fail(TTS_E_HIP, "hipHostMalloc of the status word failed");
+        else
+            *e->h_fault = 0;
+    }
+    if (rc == TTS_OK && hipDeviceGetAttribute(&e->d.n_cu, hipDeviceAttributeMultiprocessorCount, attr.device) != hipSuccess)
+        rc = fail(TTS_E_HIP, "the number of compute units is not known");
     if (rc) {
         tts_encoder_destroy(e);
         return rc;
@@ -157,8 +190,8 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
     p.act[0] = base + lay.act[0];
     p.act[1] = base + lay.act[1];
     p.cmeta = (int*)(base + lay.cmeta);
-    p.orow = (int*)(base + lay.orow);
-    p.ids = (int*)(base + lay.ids);
+    p.hx = (uint32_t*)(base + lay.hx);
+    p.wait_polls = DEFAULT_WAIT_POLLS;
     p.xproj = (float*)(base + lay.xproj);
     p.max_tokens = cfg->max_tokens;
     *out = e;
@@ -168,6 +201,8 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
 extern "C" int tts_encoder_run(tts_encoder* e, const int* ids, const int* lens, int n, float* d_out)
 {
     if (!e || !ids || !lens || !d_out) return fail(TTS_E_INVAL, "null argument");
+    int rc = check_fault(e);
+    if (rc) return rc;
     if (n < 1 || n > ENC_MAX_BATCH) return fail(TTS_E_INVAL, "n = %d requests, at most %d per call", n, ENC_MAX_BATCH);
     PnWindows w;
     w.n = n;
@@ -188,35 +223,42 @@ extern "C" int tts_encoder_run(tts_encoder* e, const int* ids, const int* lens, 
             const int id = ids[(size_t)t * n_col + c];
             if (id < 0 || id >= e->cfg.vocab[t]) return fail(TTS_E_INVAL, "table %d, token %d: id %d outside [0, %d)", t, c, id, e->cfg.vocab[t]);
         }
-    if (e->copy_pending) HIP_TRY(hipEventSynchronize(e->ev_copied));      // the previous call's copies have read the staging buffer
-    for (int t = 0; t < ENC_TABLES; ++t) memcpy(e->h_ids + (size_t)t * e->cfg.max_tokens, ids + (size_t)t * n_col, (size_t)n_col * 4);
-    HIP_TRY(hipEventRecord(e->ev0, e->stream));
-    for (int t = 0; t < ENC_TABLES; ++t)
-        HIP_TRY(hipMemcpyAsync(e->d.ids + (size_t)t * e->cfg.max_tokens, e->h_ids + (size_t)t * e->cfg.max_tokens, (size_t)n_col * 4,
-                               hipMemcpyHostToDevice, e->stream));
-    HIP_TRY(hipEventRecord(e->ev_copied, e->stream));
-    e->copy_pending = true;
-    HIP_TRY(launch_encoder(e->d, e->cfg.weight_dtype, w, n_col, d_out, e->stream));
-    HIP_TRY(hipEventRecord(e->ev1, e->stream));
-    e->ev_valid = true;
+    const int turn = e->last == 0 ? 1 : 0;
+    tts_encoder::Staging& st = e->st[turn];
+    if (st.used) HIP_TRY(hipEventSynchronize(st.ev1));      // the call before last has read this buffer
+    for (int i = 0; i < n; ++i)
+        for (int k = 0; k < lens[i]; ++k) {
+            const int c = w.col0[i] + k;
+            st.ids[c] = make_int4(ids[c], ids[n_col + c], ids[2 * (size_t)n_col + c], ids[3 * (size_t)n_col + c]);
+            st.meta[c] = (lens[i] << 16) | k;
+        }
+    HIP_TRY(hipEventRecord(st.ev0, e->stream));
+    HIP_TRY(launch_encoder(e->d, e->cfg.weight_dtype, w, n_col, st.dev, d_out, e->stream));
+    HIP_TRY(hipEventRecord(st.ev1, e->stream));
+    st.used = true;
+    e->last = turn;
     return TTS_OK;
 }
 
 extern "C" int tts_encoder_elapsed_ms(tts_encoder* e, float* out_ms)
 {
     if (!e || !out_ms) return fail(TTS_E_INVAL, "null argument");
-    if (!e->ev_valid) return fail(TTS_E_INVAL, "nothing has run yet");
-    HIP_TRY(hipEventSynchronize(e->ev1));
-    HIP_TRY(hipEventElapsedTime(out_ms, e->ev0, e->ev1));
-    return TTS_OK;
+    if (e->last < 0) return fail(TTS_E_INVAL, "nothing has run yet");
+    const tts_encoder::Staging& st = e->st[e->last];
+    HIP_TRY(hipEventSynchronize(st.ev1));
+    HIP_TRY(hipEventElapsedTime(out_ms, st.ev0, st.ev1));
+    return check_fault(e);
 }
 
 extern "C" void tts_encoder_destroy(tts_encoder* e)
 {
     if (!e) return;
-    if (e->ev0) (void)hipEventDestroy(e->ev0);
-    if (e->ev1) (void)hipEventDestroy(e->ev1);
-    if (e->ev_copied) (void)hipEventDestroy(e->ev_copied);
-    if (e->h_ids) (void)hipHostFree(e->h_ids);
+    for (tts_encoder::Staging& st : e->st) {
+        if (st.used) (void)hipEventSynchronize(st.ev1);     // the device may still read what the last calls staged
+        if (st.ev0) (void)hipEventDestroy(st.ev0);
+        if (st.ev1) (void)hipEventDestroy(st.ev1);
+        if (st.ids) (void)hipHostFree(st.ids);
+    }
+    if (e->h_fault) (void)hipHostFree(e->h_fault);
     delete e;
 }

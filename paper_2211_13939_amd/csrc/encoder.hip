@@ -2,15 +2,11 @@
 //   k_enc_embed   E_all = sum of the four embedding rows of every token, stored as the first convolution's input
 //   (conv5_kernels.h: three kernel-5 convolutions with ReLU, "same" padding inside each request)
 //   k_enc_xproj   W_ih x + b for every token and both directions: the part of the LSTM that has no recurrence
-//   k_enc_lstm    the recurrence, one workgroup per direction and group of 16 requests (fp32 weights);
-//                 k_enc_lstm_dot: two-byte weights, one workgroup per direction and request
-//
-// The recurrence is a chain of L dependent steps of a 1024 x 256 matrix-vector product: latency, not bandwidth.
-// With two-byte weights the matrix of one direction (512 KB) is resident in ONE compute unit per request -- registers
-// and LDS of k_enc_lstm_dot's workgroup -- so a step touches no memory beyond the request's precomputed input projection.
-// fp32 matrices (1 MB) do not fit a compute unit: they stream from L2 every step through MFMAs whose 16 columns are 16
-// requests, the hidden state going round through LDS in B-fragment order.  Gate rows are stored unit-major / gate-minor,
-// so the four gate sums of a unit are contiguous.
+//   the recurrence, a chain of L dependent steps of a 1024 x 256 matrix-vector product (latency, not bandwidth):
+//   k_enc_lstm_sp      two-byte weights, one workgroup per direction and request, the matrix resident in its CU
+//   k_enc_lstm_shared  fp32 weights, several workgroups per direction and request(s), the matrix spread over their registers
+// The gate rows of W_ih, the biases and the fp32 W_hh are stored unit-major / gate-minor, so the four gate sums of a unit
+// are contiguous; the two-byte W_hh has one gate of 16 units per row tile.
 #include "encoder_kernels.h"
 
 #include "conv5_kernels.h"
@@ -19,22 +15,40 @@ namespace tts {
 namespace {
 
 struct EncTables { const float* t[ENC_TABLES]; };
-constexpr int ENC_COMPACT_UP_TO = 2;       // requests per call up to which the recurrence compacts its cell update
 
+// One wave per column, eight channels a lane.  The ids and the per-column table of the convolutions (staged.meta: request
+// length << 16 | position inside the request) come straight from the call's pinned staging buffer: one trip over the host link
+// in place of four copies and a kernel that expanded the table.  The words through which k_enc_lstm_shared's workgroups
+// exchange h are cleared here as well (n_words of them; none in the two-byte mode).
 template <typename XT>
-__global__ __launch_bounds__(256) void k_enc_embed(EncTables tb, const int* __restrict__ ids, int max_tokens, int n_col,
-                                                   int n_col_pad, XT* __restrict__ X)
+__global__ __launch_bounds__(256) void k_enc_embed(EncTables tb, EncStaged staged, int n_col, int n_col_pad, XT* __restrict__ X,
+                                                   int* __restrict__ cmeta, uint32_t* __restrict__ hx, int n_words)
 {
-    constexpr int KB = Frag<XT>::KB;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    const int col = idx / ENC_DIM, ch = idx - col * ENC_DIM;
+    constexpr int KB = Frag<XT>::KB, EPL = Frag<XT>::EPL;
+    const int col = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n_words; i += gridDim.x * 256) hx[i] = 0;
     if (col >= n_col_pad) return;
-    float v = 0.f;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    int meta = 0;
     if (col < n_col) {
+        const int4 id = staged.ids[col];
+        meta = staged.meta[col];
+        const int row[ENC_TABLES] = {id.x, id.y, id.z, id.w};
 #pragma unroll
-        for (int t = 0; t < ENC_TABLES; ++t) v += tb.t[t][(size_t)ids[(size_t)t * max_tokens + col] * ENC_DIM + ch];
+        for (int t = 0; t < ENC_TABLES; ++t) {
+            const float4* e = reinterpret_cast<const float4*>(tb.t[t] + (size_t)row[t] * ENC_DIM) + 2 * lane;
+            const float4 lo = e[0], hi = e[1];
+            v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
+            v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;
+        }
     }
-    X[xoff<XT>(ENC_DIM / KB, col, ch)] = from_float<XT>(v);
+#pragma unroll
+    for (int i = 0; i < 8; i += EPL) {
+        XT* dst = X + xoff<XT>(ENC_DIM / KB, col, 8 * lane + i);
+        if constexpr (sizeof(XT) == 2) *reinterpret_cast<uint4*>(dst) = make_uint4(pack2<XT>(v[0], v[1]), pack2<XT>(v[2], v[3]), pack2<XT>(v[4], v[5]), pack2<XT>(v[6], v[7]));
+        else *reinterpret_cast<float4*>(dst) = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
+    }
+    if (lane == 0) cmeta[col] = meta;
 }
 
 // grid = (row tiles / 4, column tiles, 2 directions); a wave = one 16-row tile x one 16-column tile, K = dim
@@ -55,316 +69,369 @@ __global__ __launch_bounds__(256) void k_enc_xproj(const uint4* __restrict__ W0,
     if (col < n_col) *reinterpret_cast<floatx4*>(Y + ((size_t)dir * max_tokens + col) * ENC_GATES + rt * 16 + 4 * g) = acc;
 }
 
-template <typename XT> struct EncLstmGeom {
-    static constexpr int KB = Frag<XT>::KB, EPL = Frag<XT>::EPL;
-    static constexpr int NK = ENC_HID / KB;                       // k fragments of W_hh (it streams from L2 every step)
-    static constexpr int ROW_TILES = ENC_GATES / 16;              // 64
-    static constexpr int TILES_PER_WAVE = ROW_TILES / 4;          // 16: a wave owns 64 units
-    static constexpr int GCOLS = 2;                               // requests whose gate sums pass through LDS: the most a call may have
-    static_assert(GCOLS >= ENC_COMPACT_UP_TO, "the compacting kernel serves calls of up to ENC_COMPACT_UP_TO requests");
-    static constexpr int H_VECS = NK * 64;                        // h of the 16 requests, B-fragment order
-    static constexpr int C_VECS = ENC_HID * 16 / 4;               // the cell state of 256 units x 16 requests, fp32
-    static constexpr int G_VECS = GCOLS * ENC_GATES / 4;          // W_hh h of GCOLS requests, fp32
-    static constexpr int LDS_BYTES = (H_VECS + C_VECS + G_VECS) * 16;
-};
+// The recurrence with two-byte weights: one workgroup per direction and REQUEST, the direction's whole matrix (512 KB)
+// resident in its CU, so a step touches no memory beyond the request's precomputed input projection.  A request's steps are a
+// chain, and a chain is as fast alone on a CU as it gets; it does not depend on its companions in the call.
+//
+// The matrix-vector product of a step runs on the SPARSE matrix instruction: v_smfmac_f32_16x16x64_f16 contracts 64 k of a
+// dense 64 x 16 operand in the 16 cycles in which the dense instruction contracts 32, its other operand holding two of every
+// four k per row.  Here the dense operand is the weights (16 gate rows as its columns) and the sparse one is h: even rows
+// carry k 0, 1 of every four and odd rows k 2, 3, so that the sum of two rows is the whole product - 1024 weights per
+// instruction, 64 a cycle and SIMD, twice what a dense MFMA with one request in its sixteen columns, or a dot-product
+// instruction of the vector units (v_dot2_f32_f16), consumes.  fp16 products, fp32 accumulation, like those.
+// Four waves, one per SIMD, 64 units each.  A tile = one gate of 16 units, so the lane group q of a wave finds the four gate
+// sums of its unit in the tiles 4 q .. 4 q + 3 (all four groups of a tile's rows hold the same sums: a select, no exchange)
+// and updates the cell where they are.  Of a group's 16 fragments (8 registers a lane each) three are read from LDS every
+// step, the others live in registers: 512 KB of registers and 160 KB of LDS are all a CU has, and LDS reads are not free (a
+// fragment of every wave takes 64 cycles).  The floor of a step is 64 x 16 cycles of the matrix pipe, 0.43 us; the cell
+// update, the barrier and the read of h from LDS follow it.
+// Measured: one request of 165 tokens 236 us (1.41 us a step) as chains of v_dot2_f32_f16 with two threads a unit -> 117 us
+// (0.70 us a step); 16 requests of 30 .. 300 tokens 419 -> 207 us.  With the instructions scheduled by the compiler: 165 us.
+// grid = (2 directions, requests), 256 threads.
+constexpr int ENC_SP_THREADS = 256;
+constexpr int ENC_SP_LDS_TILES = 3;                                        // of a group's four tiles, those whose last piece lives in LDS
+constexpr int ENC_SP_W_VECS = 4 * 4 * ENC_SP_LDS_TILES * 2 * 64;           // waves x groups x tiles x 2 x lanes
+constexpr int ENC_SP_LDS_BYTES = ENC_SP_W_VECS * 16 + 2 * ENC_HID * 2;
+constexpr int ENC_SP_AHEAD = 2;                                            // steps between the request for an input projection and its use
 
-// grid = (2 directions, 1), 256 threads; for calls of at most GCOLS requests.
-// One step:  (1) every wave: its 16 row tiles of W_hh h on MFMA, the requests as the first of the 16 columns;
-//            (2) the lanes that hold those columns put the sums into LDS;
-//            (3) thread u = hidden unit u takes the four gate sums of its unit, adds the precomputed input
-//                projection, updates the cell and writes h (B-fragment order in LDS for the next step, fp32 to F_enc).
-// The cell update runs on compacted data: with one request in flight the MFMA columns are 1/16 full, and so would
-// every vector instruction be that worked on the accumulators where they are.
-template <typename XT>
-__global__ __launch_bounds__(256) void k_enc_lstm(const uint4* __restrict__ Whh0, const uint4* __restrict__ Whh1,
-                                                  const float* __restrict__ xproj, PnWindows w, int max_tokens, float* __restrict__ out)
+// The products of one step as one run of instructions.  Left to itself the compiler moves accumulators between the two halves
+// of the register file around every chain, and every move waits for the matrix pipe; here nothing does:
+//   * the four chains of a group (one per gate) are interleaved, a sum is fed again after three other instructions;
+//   * the groups use two sets of accumulators in turn (v[224:239], v[240:255]); a group adds up the previous group's sums and
+//     clears them between its own instructions, while the vector units have nothing else to do (two of a lane's four rows
+//     are enough: the other two repeat them and are never read);
+//   * one piece of three of a group's tiles lives in LDS, at different places of the run; each is requested a whole group
+//     (256 cycles) before its use, into the registers (v[200:223]) its predecessor has just left; h arrives piece by piece.
+// The hardware does not check these distances: a sum is read at least 7 wait states (4 passes + 3) after the instruction that
+// completed it - four others of 4 passes each lie between, at the end the s_nops -, and an operand of a matrix instruction
+// is written at least two wait states before.  LDS returns in order: the counts are those of the reads issued since.
+#define SP_STR2(x) #x
+#define SP_STR(x) SP_STR2(x)
+#define SP_MM(acc, f, w) "v_smfmac_f32_16x16x64_f16 " acc ", %[h" #f "], " w ", %[ix]\n\t"
+#define SP_I(U, g, f, acc) SP_MM(acc, f, "%[w" #U #f #g "]")
+#define SP_WAIT(n) "s_waitcnt lgkmcnt(" #n ")\n\t"
+#define SP_READ(lo, hi, next, g) "ds_read_b128 " lo ", %[la] offset:(" #next "*3+" #g ")*2048\n\tds_read_b128 " hi ", %[la] offset:(" #next "*3+" #g ")*2048+1024\n\t"
+#define SP_L0(next, acc, wait) wait SP_MM(acc, 1, "v[200:207]") SP_READ("v[200:203]", "v[204:207]", next, 0)
+#define SP_L1(next, acc, wait) wait SP_MM(acc, 2, "v[208:215]") SP_READ("v[208:211]", "v[212:215]", next, 1)
+#define SP_L2(next, acc, wait) wait SP_MM(acc, 3, "v[216:223]") SP_READ("v[216:219]", "v[220:223]", next, 2)
+#define SP_P0 "v[224:227]"
+#define SP_P1 "v[228:231]"
+#define SP_P2 "v[232:235]"
+#define SP_P3 "v[236:239]"
+#define SP_Q0 "v[240:243]"
+#define SP_Q1 "v[244:247]"
+#define SP_Q2 "v[248:251]"
+#define SP_Q3 "v[252:255]"
+#define SP_TAKE(g, r0, r1, m) "v_add_f32 %[t], v" #r0 ", v" #r1 "\n\tv_cndmask_b32 %[s" #g "], %[s" #g "], %[t], %[" m "]\n\t"
+#define SP_CLEAR(r0, r1) "v_mov_b32 v" #r0 ", 0\n\tv_mov_b32 v" #r1 ", 0\n\t"
+#define SP_TAKE_P0(m) SP_TAKE(0, 224, 225, m)
+#define SP_TAKE_P1(m) SP_TAKE(1, 228, 229, m)
+#define SP_TAKE_P2(m) SP_TAKE(2, 232, 233, m)
+#define SP_TAKE_P3(m) SP_TAKE(3, 236, 237, m)
+#define SP_TAKE_Q0(m) SP_TAKE(0, 240, 241, m)
+#define SP_TAKE_Q1(m) SP_TAKE(1, 244, 245, m)
+#define SP_TAKE_Q2(m) SP_TAKE(2, 248, 249, m)
+#define SP_TAKE_Q3(m) SP_TAKE(3, 252, 253, m)
+#define SP_NO_TAKE0(m)
+#define SP_NO_TAKE1(m)
+#define SP_NO_TAKE2(m)
+#define SP_NO_TAKE3(m)
+#define SP_CLEAR_P0 SP_CLEAR(224, 225)
+#define SP_CLEAR_P1 SP_CLEAR(228, 229)
+#define SP_CLEAR_P2 SP_CLEAR(232, 233)
+#define SP_CLEAR_P3 SP_CLEAR(236, 237)
+#define SP_CLEAR_Q0 SP_CLEAR(240, 241)
+#define SP_CLEAR_Q1 SP_CLEAR(244, 245)
+#define SP_CLEAR_Q2 SP_CLEAR(248, 249)
+#define SP_CLEAR_Q3 SP_CLEAR(252, 253)
+// U: group, N: the group behind it, C: its accumulators (P or Q), O: the previous group's, TAKE, m: how the previous group's
+// sums are taken; W0 .. W3: waits for the pieces of h, WL: wait for a piece of the LDS-resident weights
+#define SP_GROUP(U, N, C, O, TAKE, m, W0, W1, W2, W3, WL)                                                                                \
+    W0 SP_I(U, 0, 0, SP_##C##0) SP_I(U, 1, 0, SP_##C##1) SP_I(U, 2, 0, SP_##C##2) SP_I(U, 3, 0, SP_##C##3)                               \
+    W1 SP_L0(N, SP_##C##0, WL) TAKE##0(m) SP_I(U, 1, 1, SP_##C##1) TAKE##1(m) SP_I(U, 2, 1, SP_##C##2) TAKE##2(m)                        \
+    SP_I(U, 3, 1, SP_##C##3) TAKE##3(m)                                                                                                  \
+    W2 SP_I(U, 0, 2, SP_##C##0) SP_CLEAR_##O##0 SP_L1(N, SP_##C##1, WL) SP_CLEAR_##O##1 SP_I(U, 2, 2, SP_##C##2) SP_CLEAR_##O##2          \
+    SP_I(U, 3, 2, SP_##C##3) SP_CLEAR_##O##3                                                                                             \
+    W3 SP_I(U, 0, 3, SP_##C##0) SP_I(U, 1, 3, SP_##C##1) SP_L2(N, SP_##C##2, WL) SP_I(U, 3, 3, SP_##C##3)
+#define SP_STEP(hoff)                                                                                                                    \
+    "ds_read_b128 %[h0], %[ha] offset:" SP_STR(hoff) "\n\tds_read_b128 %[h1], %[ha] offset:" SP_STR(hoff) "+128\n\t"                    \
+    "ds_read_b128 %[h2], %[ha] offset:" SP_STR(hoff) "+256\n\tds_read_b128 %[h3], %[ha] offset:" SP_STR(hoff) "+384\n\t"                \
+    SP_GROUP(0, 1, P, Q, SP_NO_TAKE, "", SP_WAIT(3), SP_WAIT(2), SP_WAIT(3), SP_WAIT(4), )                                                \
+    SP_GROUP(1, 2, Q, P, SP_TAKE_P, "m0", , , , , SP_WAIT(4))                                                                            \
+    SP_GROUP(2, 3, P, Q, SP_TAKE_Q, "m1", , , , , SP_WAIT(4))                                                                            \
+    SP_GROUP(3, 0, Q, P, SP_TAKE_P, "m2", , , , , SP_WAIT(4))                                                                            \
+    SP_TAKE_Q0("m3") SP_TAKE_Q1("m3") "s_nop 1\n\t" SP_TAKE_Q2("m3") "s_nop 3\n\t" SP_TAKE_Q3("m3")
+#define SP_W(c, U, f, g) [w##U##f##g] c(wr[U][f][g])
+#define SP_WROW(c, U, f) SP_W(c, U, f, 0), SP_W(c, U, f, 1), SP_W(c, U, f, 2), SP_W(c, U, f, 3)
+#define SP_WGROUP(c, U)                                                                                                                  \
+    SP_WROW(c, U, 0), SP_W(c, U, 1, 1), SP_W(c, U, 1, 2), SP_W(c, U, 1, 3), SP_W(c, U, 2, 0), SP_W(c, U, 2, 2), SP_W(c, U, 2, 3),           \
+        SP_W(c, U, 3, 0), SP_W(c, U, 3, 1), SP_W(c, U, 3, 3)
+#define SP_RUN(hoff)                                                                                                                     \
+    asm volatile(SP_STEP(hoff)                                                                                                           \
+                 : [h0] "=&v"(hv[0]), [h1] "=&v"(hv[1]), [h2] "=&v"(hv[2]), [h3] "=&v"(hv[3]), [s0] "+v"(gs[0]), [s1] "+v"(gs[1]),         \
+                   [s2] "+v"(gs[2]), [s3] "+v"(gs[3]), [t] "=&v"(tmp), "+{v[200:207]}"(wv[0]), "+{v[208:215]}"(wv[1]),                    \
+                   "+{v[216:223]}"(wv[2]), "+{v[224:227]}"(accp[0]), "+{v[228:231]}"(accp[1]), "+{v[232:235]}"(accp[2]),                  \
+                   "+{v[236:239]}"(accp[3]), "+{v[240:243]}"(accq[0]), "+{v[244:247]}"(accq[1]), "+{v[248:251]}"(accq[2]),                \
+                   "+{v[252:255]}"(accq[3])                                                                                               \
+                 : [ha] "v"(h_at), [la] "v"(w_at), [ix] "v"(idx), [m0] "s"(lanes_of(0)), [m1] "s"(lanes_of(1)), [m2] "s"(lanes_of(2)),     \
+                   [m3] "s"(lanes_of(3)), SP_WGROUP("a", 0), SP_WGROUP("a", 1), SP_WROW("a", 2, 0), SP_W("a", 2, 1, 1),                  \
+                   SP_W("a", 2, 1, 2), SP_W("v", 2, 1, 3), SP_W("v", 2, 2, 0), SP_W("v", 2, 2, 2), SP_W("v", 2, 2, 3),                     \
+                   SP_W("v", 2, 3, 0), SP_W("v", 2, 3, 1), SP_W("v", 2, 3, 3), SP_WGROUP("v", 3)                                         \
+                 : "memory")
+
+typedef uint32_t u32x8_t __attribute__((ext_vector_type(8)));
+
+__global__ __launch_bounds__(ENC_SP_THREADS) void k_enc_lstm_sp(const uint4* __restrict__ Whh0, const uint4* __restrict__ Whh1,
+                                                                const float* __restrict__ xproj, PnWindows w, int max_tokens, float* __restrict__ out)
 {
-    using G = EncLstmGeom<XT>;
-    constexpr int NK = G::NK, TPW = G::TILES_PER_WAVE, GCOLS = G::GCOLS;
+    constexpr int NK = ENC_HID / 32, NF = ENC_HID / 64;                    // dense fragments of the stored matrix, k pieces of 64
+    static_assert(NF == 4, "the instruction runs are written for four pieces of k");
     extern __shared__ uint4 lds_enc[];
-    uint4* hb = lds_enc;                                          // [NK][64 lanes]
-    float* cl = reinterpret_cast<float*>(hb + G::H_VECS);         // [unit][request]
-    float* gl = cl + ENC_HID * 16;                                // [GCOLS][gate row]
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, g = lane >> 4;
-    const int dir = blockIdx.x, req0 = blockIdx.y * 16;
-    const int nact = min(GCOLS, w.n - req0);                      // requests of this call
-    // lengths and first tokens once, into registers: the request table is a kernel argument, and indexing it inside
-    // the step loop would cost a memory round trip per use
-    int len_of[GCOLS], col0_of[GCOLS], lmax = 0;
+    uint4* wl = lds_enc;
+    uint16_t* hs = reinterpret_cast<uint16_t*>(lds_enc + ENC_SP_W_VECS);   // h as halves, [buffer][unit in operand order]
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, q = lane >> 4;
+    const int dir = blockIdx.x, req = blockIdx.y;
+    const int len = __builtin_amdgcn_readfirstlane((int)w.len[req]), col0 = __builtin_amdgcn_readfirstlane(w.col0[req]);
+    const uint4* Wl = (dir ? Whh1 : Whh0) + lane;
+    uint4* wlw = wl + wave * 4 * ENC_SP_LDS_TILES * 2 * 64 + lane;
+    // tile 4 (4 wave + U) + g = gate g of the units 16 (4 wave + U) ..; its k piece f = the dense fragments 2 f and 2 f + 1
+    u32x8_t wr[4][NF][4];
 #pragma unroll
-    for (int j = 0; j < GCOLS; ++j) {
-        const int jj = min(j, nact - 1);
-        len_of[j] = w.len[req0 + jj];
-        col0_of[j] = w.col0[req0 + jj];
-        if (j < nact) lmax = max(lmax, len_of[j]);
-    }
-    const uint4* Whh = dir ? Whh1 : Whh0;
-
-    for (int idx = tid; idx < G::H_VECS + G::C_VECS; idx += 256) hb[idx] = make_uint4(0, 0, 0, 0);    // h = 0, c = 0
-
-    // token of request j at step s: forwards from 0, backwards from the request's own last token
-    auto token = [&](int j, int s) { return dir ? len_of[j] - 1 - s : s; };
-    // this thread's unit: four gate sums of a request are 16 contiguous bytes of the input projection
-    const float* xp = xproj + (size_t)dir * max_tokens * ENC_GATES + 4 * tid;
-    // the first two requests' input projections are requested a step ahead (a batch at join time is that small)
-    floatx4 xnext[GCOLS];
+    for (int U = 0; U < 4; ++U)
 #pragma unroll
-    for (int j = 0; j < GCOLS; ++j) {
-        const int t0 = min(max(token(j, 0), 0), len_of[j] - 1);
-        xnext[j] = *reinterpret_cast<const floatx4*>(xp + (size_t)(col0_of[j] + t0) * ENC_GATES);
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const size_t at = ((size_t)(4 * (4 * wave + U) + g) * NK + 2 * f) * 64;
+                const uint4 lo = Wl[at], hi = Wl[at + 64];
+                if (g < ENC_SP_LDS_TILES && f == g + 1) {        // (the LDS-resident pieces)
+                    wlw[((U * ENC_SP_LDS_TILES + g) * 2) * 64] = lo;
+                    wlw[((U * ENC_SP_LDS_TILES + g) * 2 + 1) * 64] = hi;
+                } else {
+                    wr[U][f][g] = u32x8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                }
+            }
+    reinterpret_cast<uint32_t*>(hs)[tid] = 0;                              // h = 0, both buffers
+
+    // this lane's unit, and where its h lies in the sparse operand: k = 64 f + 16 q' + 4 j + 2 p + e sits in piece (f, q', p),
+    // half 2 j + e; a lane of row r reads the pieces of parity p = r % 2
+    const int unit = 16 * (4 * wave + q) + n;
+    const int hpos = ((unit >> 4) * 2 + ((n >> 1) & 1)) * 8 + 2 * (n >> 2) + (n & 1);
+    const int idx = (n & 1) ? (int)0xEEEEEEEEu : 0x44444444;
+    // Input projections and F_enc through bounds-checked descriptors: steps past the request's end (the loop below takes
+    // ENC_SP_AHEAD at a time) read zeros and store nothing.
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xproj) + ((size_t)dir * max_tokens + col0) * ENC_GATES, 0,
+                                                                        len * ENC_GATES * 4, BUFFER_RSRC_RAW);
+    const __amdgpu_buffer_rsrc_t outr = __builtin_amdgcn_make_buffer_rsrc(out + (size_t)col0 * (2 * ENC_HID), 0, len * 2 * ENC_HID * 4, BUFFER_RSRC_RAW);
+    const int step = dir ? -1 : 1;
+    int tok = dir ? len - 1 : 0;                                           // of the next step; leaves 0 .. len - 1 at the request's end
+    auto load_x = [&](int t) { return __builtin_bit_cast(floatx4, buffer_load16(xr, (t * ENC_GATES + 4 * unit) * 4)); };
+    floatx4 x[ENC_SP_AHEAD];
+#pragma unroll
+    for (int j = 0; j < ENC_SP_AHEAD; ++j) x[j] = load_x(tok + j * step);
+    float c = 0.f;
+    floatx4 accp[4], accq[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) accp[g] = accq[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto lanes_of = [](int group) { return 0xFFFFull << (16 * group); };
+    typedef __attribute__((address_space(3))) void lds_void;
+    const uint32_t w_at = (uint32_t)(uintptr_t)(lds_void*)wlw, h_at = (uint32_t)(uintptr_t)(lds_void*)(hs + (q * 2 + (n & 1)) * 8);
+    u32x8_t wv[ENC_SP_LDS_TILES];
+#pragma unroll
+    for (int g = 0; g < ENC_SP_LDS_TILES; ++g) {
+        const uint4 lo = wlw[g * 2 * 64], hi = wlw[(g * 2 + 1) * 64];      // (this wave's own writes)
+        wv[g] = u32x8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
     }
+    // every weight has arrived before the loop, and so have the first projections: the loop's waits count its own requests only
+#pragma unroll
+    for (int U = 0; U < 4; ++U)
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                if (g >= ENC_SP_LDS_TILES || f != g + 1) {
+                    if (U < 2 || (U == 2 && (f == 0 || (f == 1 && g < 3)))) asm volatile("" : "+a"(wr[U][f][g]));
+                    else asm volatile("" : "+v"(wr[U][f][g]));
+                }
+    vm_in_flight_at_most<0>();
     __syncthreads();
 
-    for (int s = 0; s < lmax; ++s) {
-        // ---- (1) W_hh h: the matrix streams from L2, one k fragment of the wave's row tiles at a time;
-        //      (2) the sums of this call's (at most GCOLS) requests into LDS
-        float* dst = gl + (n % GCOLS) * ENC_GATES + (TPW * wave) * 16 + 4 * g;
-        floatx4 acc[TPW];
+    for (int s0 = 0; s0 < len; s0 += ENC_SP_AHEAD) {
 #pragma unroll
-        for (int i = 0; i < TPW; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-        for (int kf = 0; kf < NK; ++kf) {
-            const uint4 bv = hb[kf * 64 + lane];
-#pragma unroll
-            for (int i = 0; i < TPW; ++i) acc[i] = mfma_frag<XT>(Whh[xfrag(NK, TPW * wave + i, kf, lane)], bv, acc[i]);
-        }
-        if (n < GCOLS) {
-#pragma unroll
-            for (int i = 0; i < TPW; ++i) *reinterpret_cast<floatx4*>(dst + i * 16) = acc[i];
-        }
-        __syncthreads();                                   // the sums are in LDS and every wave has read h
-        // ---- (3) thread = hidden unit
-#pragma unroll
-        for (int j = 0; j < GCOLS; ++j) {
-            if (j >= nact) break;                          // uniform over the workgroup
-            const int len = len_of[j], col0 = col0_of[j];
-            if (s >= len) continue;                        // this request has ended
-            const int t = token(j, s);
-            const floatx4 gs = *reinterpret_cast<const floatx4*>(gl + j * ENC_GATES + 4 * tid) + xnext[j];
+        for (int j = 0; j < ENC_SP_AHEAD; ++j) {
+            u32x4_t hv[NF];
+            floatx4 gs = {0.f, 0.f, 0.f, 0.f};
+            float tmp;
+            if (j & 1) SP_RUN(512);
+            else SP_RUN(0);
+            gs += x[j];
             const float gi = sigmoidf_(gs[0]), gf = sigmoidf_(gs[1]), gg = tanhf_(gs[2]), go = sigmoidf_(gs[3]);
-            const float cn = gf * cl[tid * 16 + j] + gi * gg;
-            cl[tid * 16 + j] = cn;
-            const float h = go * tanhf_(cn);
-            reinterpret_cast<XT*>(hb)[(((tid / G::KB) * 64 + j + 16 * ((tid % G::KB) / G::EPL)) * G::EPL) + (tid % G::EPL)] = from_float<XT>(h);
-            out[(size_t)(col0 + t) * (2 * ENC_HID) + dir * ENC_HID + tid] = h;
-            const int tn = min(max(token(j, s + 1), 0), len - 1);      // next step's input projection, clamped to the request
-            xnext[j] = *reinterpret_cast<const floatx4*>(xp + (size_t)(col0 + tn) * ENC_GATES);
+            c = gf * c + gi * gg;
+            const float h = go * tanhf_(c);
+            hs[((j + 1) & 1) * ENC_HID + hpos] = from_float<h16_t>(h).bits;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(h), outr, (tok * 2 * ENC_HID + dir * ENC_HID + unit) * 4, 0, 0);
+            x[j] = load_x(tok + ENC_SP_AHEAD * step);
+            tok += step;
+            __syncthreads();                              // h is complete (the other buffer is free for the next step)
         }
-        __syncthreads();                                   // h is complete and the gate buffer free for the next step
     }
 }
+#undef SP_STR
+#undef SP_MM
+#undef SP_I
+#undef SP_WAIT
+#undef SP_READ
+#undef SP_TAKE
+#undef SP_CLEAR
+#undef SP_GROUP
+#undef SP_STEP
+#undef SP_RUN
+#undef SP_W
 
-// The recurrence with two-byte weights, on the vector units: one workgroup per direction and REQUEST (a call has at most
-// ENC_MAX_BATCH = 256 requests, so at most two workgroups per CU's worth of the chip, and the usual call at join time
-// has one).  A request's steps are a chain, and a chain is as fast alone on a CU as it gets: sixteen requests side by
-// side as the columns of one workgroup's MFMAs take 6 us per step, sixteen workgroups 1.9 us.  Every workgroup reads
-// the direction's 512 KB of W_hh once, from L2 after the first.  The recurrence of a request does not depend on its
-// companions in the call.
-// 512 threads: a pair of threads is one hidden unit, each holding one half of k of the unit's four gate rows - the even
-// one the even pieces of eight consecutive k, the odd one the odd pieces - (512 halves a thread: 192 registers' worth and
-// 64 LDS words, the same split of k as above, straight from the fragment-ordered matrix; at two waves per SIMD a lane has
-// 256 registers, all of them operands of vector instructions).  A thread forms its half of the four gate sums as chains
-// of two-element dot products (v_dot2_f32_f16, fp32 accumulation) over its half of h, which it reads from LDS as a
-// broadcast (a wave reads two neighbouring pieces at a time: no bank is asked twice); the pair adds its halves and both
-// update the cell.  With one request in flight an MFMA's sixteen columns are 1/16 full - 32 cycles of the matrix
-// pipe for 512 useful products - while a dot-product instruction does 128 useful products in 4 cycles, and the gate sums
-// never pass through LDS.
-// grid = (2 directions, requests), 512 threads.  LDS: [16][512] uint4 of weights, h as halves [2 buffers][256].
-constexpr int ENC_DOT_THREADS = 2 * ENC_HID;
-constexpr int ENC_DOT_W_VECS = 16 * ENC_DOT_THREADS;
-constexpr int ENC_DOT_LDS_BYTES = ENC_DOT_W_VECS * 16 + 2 * ENC_HID * 2;
+// The recurrence with fp32 weights: a direction's matrix (1 MB) does not fit a CU, and streaming it from L2 takes 40 us a step
+// (one CU's load path).  So G workgroups share a direction of R requests: each keeps the gate rows of 256 / G units in
+// registers (64 a thread), forms those units' gate sums from the whole h, updates their cells, and hands their h to its
+// partners through memory.  h needs no separate flag: |h| <= 1 leaves bit 30 of its fp32 word free, which carries the round
+// of the word's reuse (two buffers per request, the bit flips each time a buffer comes round; k_enc_embed clears the words
+// of a call).  A partner can be at most one step behind: nobody finishes step s + 1 without all of its words of step s.
+// A step is bound by that exchange (a store becoming visible plus a trip of the poll, about 1 us); the products take 0.1 us
+// (16 threads per unit, each 16 k of its four gate rows: 64 FMAs) to 0.4 us (16 waves a workgroup).  Measured: one request of
+// 165 tokens 6.56 -> 0.22 ms (1.3 us a step), 8 requests of 30 .. 300 tokens 5.8 -> 0.45 ms, 60 of them 1.0 ms.  G is as large as the
+// number of workgroups allows: all of them (2 directions x groups x G <= one per CU) must be resident at once, because they
+// wait for each other.  Every wait is bounded; one that runs out raises *fault and ends the workgroup.
+// A unit's sum is taken in the same order whatever G and R are, so a request's result does not depend on its companions.
+// grid = (G, groups of R requests, 2 directions), 4096 / G threads (<= 1024).
+constexpr int ENC_X_PARTS = 16;                                            // threads per unit: thread p owns k = 64 i + 4 p .. + 3
+constexpr uint32_t ENC_X_ROUND = 1u << 30;
 
-__device__ __forceinline__ float dot8(uint4 w, uint4 h, float acc)
+template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
 {
-    acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(halfx2, w.x), __builtin_bit_cast(halfx2, h.x), acc, false);
-    acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(halfx2, w.y), __builtin_bit_cast(halfx2, h.y), acc, false);
-    acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(halfx2, w.z), __builtin_bit_cast(halfx2, h.z), acc, false);
-    return __builtin_amdgcn_fdot2(__builtin_bit_cast(halfx2, w.w), __builtin_bit_cast(halfx2, h.w), acc, false);
+    return x + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+// the sum over the 16 lanes of a row, the same bits in all of them (partners add the same two values at every level)
+__device__ __forceinline__ float row16_sum(float x)
+{
+    x = dpp_add<0xB1>(x);          // quad_perm 1 0 3 2
+    x = dpp_add<0x4E>(x);          // quad_perm 2 3 0 1
+    x = dpp_add<0x141>(x);         // row_half_mirror
+    return dpp_add<0x140>(x);      // row_mirror
 }
 
-__global__ __launch_bounds__(ENC_DOT_THREADS) void k_enc_lstm_dot(const uint4* __restrict__ Whh0, const uint4* __restrict__ Whh1,
-                                                                  const float* __restrict__ xproj, PnWindows w, int max_tokens, float* __restrict__ out)
+template <int R>
+__global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restrict__ Whh0, const uint4* __restrict__ Whh1,
+                                                          const float* __restrict__ xproj, uint32_t* hx, PnWindows w, int max_tokens,
+                                                          float* __restrict__ out, int wait_polls, int* fault)
 {
-    typedef h16_t XT;
-    constexpr int KB = Frag<XT>::KB, NK = ENC_HID / KB;
-    static_assert(KB == 32 && NK == 8, "k = 32 kf + 8 q + e: a lane's 16 bytes are 8 consecutive k");
-    extern __shared__ uint4 lds_enc[];
-    uint4* wl = lds_enc;                                                        // [gate * 4 + piece / 4][thread]
-    uint16_t* hs = reinterpret_cast<uint16_t*>(lds_enc + ENC_DOT_W_VECS);       // [buffer][unit]
-    const int tid = threadIdx.x, dir = blockIdx.x, req = blockIdx.y, unit = tid >> 1, half = tid & 1;
-    const int len = w.len[req], col0 = w.col0[req];
+    constexpr int NK = ENC_HID / 16, NI = ENC_HID / (4 * ENC_X_PARTS);
+    __shared__ __attribute__((aligned(16))) float hs[2][R][ENC_HID];
+    __shared__ int gave_up;
+    const int tid = threadIdx.x, nthr = blockDim.x, p = tid & (ENC_X_PARTS - 1);
+    const int dir = blockIdx.z, req0 = blockIdx.y * R, unit = blockIdx.x * (nthr / ENC_X_PARTS) + tid / ENC_X_PARTS;
+    // lengths and first tokens once, into registers: the request table is a kernel argument
+    int len[R], col0[R], lmax = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int rq = min(req0 + r, w.n - 1);
+        len[r] = req0 + r < w.n ? (int)w.len[rq] : 0;
+        col0[r] = w.col0[rq];
+        lmax = max(lmax, len[r]);
+    }
     const uint4* Whh = dir ? Whh1 : Whh0;
-    // gate row 4 u + g lies in row tile u / 4 at row 4 (u % 4) + g; its k = 32 kf + 8 q .. + 7 in lane row + 16 q;
-    // this thread's pieces are q = half and half + 2
-    const int rt = unit >> 2, r0 = 4 * (unit & 3);
-    // of its 16 pieces (piece i: kf = i / 2, q = half + 2 (i % 2)) every fourth lives in LDS, the others in registers: the
-    // LDS reads are spread evenly over a step
-    constexpr int NP = 2 * NK, NP_LDS = NP / 4, NP_REG = NP - NP_LDS;
-    static_assert(NP_LDS * 4 * ENC_DOT_THREADS == ENC_DOT_W_VECS, "the LDS share of the weights");
-    uint4 wr[4][NP_REG];
+    float4 wr[4][NI];
 #pragma unroll
     for (int g = 0; g < 4; ++g)
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const uint4 v = Whh[xfrag(NK, rt, i >> 1, r0 + g + 16 * (half + 2 * (i & 1)))];
-            if ((i & 3) == 3) wl[(g * NP_LDS + (i >> 2)) * ENC_DOT_THREADS + tid] = v;
-            else wr[g][i - (i >> 2)] = v;
-        }
-    hs[tid] = 0;                                                                // h = 0, both buffers
+        for (int i = 0; i < NI; ++i)
+            wr[g][i] = __builtin_bit_cast(float4, Whh[xfrag(NK, unit >> 2, 4 * i + (p >> 2), 4 * (unit & 3) + g + 16 * (p & 3))]);
+    for (int i = tid; i < 2 * R * ENC_HID; i += nthr) (&hs[0][0][0])[i] = 0.f;
+    if (tid == 0) gave_up = 0;
 
-    auto token = [&](int s) { return dir ? len - 1 - s : s; };
-    const float* xp = xproj + ((size_t)dir * max_tokens + col0) * ENC_GATES + 4 * unit;
-    floatx4 xnext = *reinterpret_cast<const floatx4*>(xp + (size_t)min(max(token(0), 0), len - 1) * ENC_GATES);
-    float c = 0.f;
-    __syncthreads();
-
-    for (int s = 0; s < len; ++s) {
-        const uint4* hr = reinterpret_cast<const uint4*>(hs + (s & 1) * ENC_HID);               // 32 pieces of 8 halves
-        uint16_t* hx = hs + ((s + 1) & 1) * ENC_HID;
-        asm volatile("" ::: "memory");                    // (the LDS-resident weights are read again every step, not kept in registers)
-        // one chain per gate over this thread's half of k, a piece of eight k at a time; the next piece's LDS words (h, and
-        // the weights that live there) are requested before the current piece's products, and no further ahead: few live
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
-        uint4 hv = hr[half], wv[4];
+    auto token = [&](int r, int s) { return min(max(dir ? len[r] - 1 - s : s, 0), max(len[r] - 1, 0)); };
+    const float* xp = xproj + (size_t)dir * max_tokens * ENC_GATES + 4 * unit;
+    uint32_t* words = hx + ((size_t)dir * w.n + req0) * 2 * ENC_HID;       // [request][buffer][unit]
+    floatx4 x[R];
+    float c[R];
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            uint4 hn = hv, wn[4];
-            if (i + 1 < NP) {
-                hn = hr[((i + 1) >> 1) * 4 + half + 2 * ((i + 1) & 1)];
-                if (((i + 1) & 3) == 3) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) wn[g] = wl[(g * NP_LDS + ((i + 1) >> 2)) * ENC_DOT_THREADS + tid];
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < 4; ++g) acc[g] = dot8((i & 3) == 3 ? wv[g] : wr[g][(i & 3) == 3 ? 0 : i - (i >> 2)], hv, acc[g]);
-            hv = hn;
-            if (i + 1 < NP && ((i + 1) & 3) == 3) {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) wv[g] = wn[g];
-            }
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // the pair adds its halves: both threads hold all four gate sums, bit for bit the same
-        const int t = token(s);
-        floatx4 gs;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) gs[g] = acc[g] + __shfl_xor(acc[g], 1, 64);
-        gs += xnext;
-        const float gi = sigmoidf_(gs[0]), gf = sigmoidf_(gs[1]), gg = tanhf_(gs[2]), go = sigmoidf_(gs[3]);
-        c = gf * c + gi * gg;
-        const float h = go * tanhf_(c);
-        if (half == 0) {
-            hx[unit] = from_float<XT>(h).bits;
-            out[(size_t)(col0 + t) * (2 * ENC_HID) + dir * ENC_HID + unit] = h;
-        }
-        const int tn = min(max(token(s + 1), 0), len - 1);             // next step's input projection, clamped to the request
-        xnext = *reinterpret_cast<const floatx4*>(xp + (size_t)tn * ENC_GATES);
-        __syncthreads();                                   // h is complete (the other buffer is free for the next step)
-    }
-}
-
-template <typename XT> struct EncLstmWideGeom {
-    static constexpr int KB = Frag<XT>::KB, EPL = Frag<XT>::EPL;
-    static constexpr int NK = ENC_HID / KB;                       // k fragments of W_hh (it streams from L2 every step)
-    static constexpr int ROW_TILES = ENC_GATES / 16;              // 64
-    static constexpr int TILES_PER_WAVE = ROW_TILES / 4;          // 16: a wave owns 64 units
-    static constexpr int H_VECS = NK * 64;                        // one copy of h; there are two (read one, write the other)
-    static constexpr int C_VECS = ENC_HID * 16 / 4;              // the cell state of 256 units x 16 requests, fp32
-    static constexpr int LDS_BYTES = (2 * H_VECS + C_VECS) * 16;
-};
-
-// The recurrence for well-filled groups (more than ENC_COMPACT_UP_TO requests in the call): the cell update runs where
-// the accumulators are -- a lane owns the four gates of one unit for its request's column -- so nothing passes through
-// LDS but h, and the next step's input projection lands in the accumulators half a step ahead.
-// grid = (2 directions, groups of 16 requests), 256 threads
-template <typename XT>
-__global__ __launch_bounds__(256) void k_enc_lstm_wide(const uint4* __restrict__ Whh0, const uint4* __restrict__ Whh1,
-                                                  const float* __restrict__ xproj, PnWindows w, int max_tokens, float* __restrict__ out)
-{
-    using G = EncLstmWideGeom<XT>;
-    constexpr int NK = G::NK, TPW = G::TILES_PER_WAVE;
-    extern __shared__ uint4 lds_enc[];
-    uint4* hb = lds_enc;                     // h of the 16 requests, B-fragment order, [NK][64 lanes]
-    float* cl = reinterpret_cast<float*>(hb + 2 * G::H_VECS); // cell state [unit][request]: only its owner lane touches an entry
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, g = lane >> 4;
-    const int dir = blockIdx.x, req = blockIdx.y * 16 + n;
-    const bool active = req < w.n;
-    const int len = active ? (int)w.len[req] : 0, col0 = active ? w.col0[req] : 0;
-    int lmax = len;
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) lmax = max(lmax, __shfl_xor(lmax, o, 64));
-    const uint4* Whh = dir ? Whh1 : Whh0;
-
-    for (int idx = tid; idx < 2 * G::H_VECS; idx += 256) hb[idx] = make_uint4(0, 0, 0, 0);
-
-    // token of this lane's request at step s: forwards from 0, backwards from its own last token; clamped so that
-    // a request that has ended keeps reading (and computing on) valid memory -- its results are not stored
-    auto token = [&](int s) { return min(max(dir ? len - 1 - s : s, 0), max(len - 1, 0)); };
-    const float* xp = xproj + ((size_t)dir * max_tokens + col0) * ENC_GATES + (TPW * wave) * 16 + 4 * g;
-    floatx4 acc[TPW];
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-        acc[i] = *reinterpret_cast<const floatx4*>(xp + (size_t)token(0) * ENC_GATES + i * 16);
-        cl[(4 * (TPW * wave + i) + g) * 16 + n] = 0.f;
+    for (int r = 0; r < R; ++r) {
+        x[r] = *reinterpret_cast<const floatx4*>(xp + (size_t)(col0[r] + token(r, 0)) * ENC_GATES);
+        c[r] = 0.f;
     }
     __syncthreads();
 
-    // A step in two halves of eight row tiles.  h is read from one buffer and written to the other, so a half's cell
-    // update can follow its MFMAs at once (and overlap the other half's MFMAs); when a half's accumulators have been
-    // consumed, the next step's input projection for those tiles is requested into them: half a step ahead of its use.
-    constexpr int HALF = TPW / 2;
     for (int s = 0; s < lmax; ++s) {
-        const uint4* hr = hb + (s & 1) * G::H_VECS;
-        XT* hx = reinterpret_cast<XT*>(hb + ((s + 1) & 1) * G::H_VECS);
-        const int t_cur = dir ? len - 1 - s : s;
-        const bool store = active && s < len;
-        const int tn = token(s + 1);
+        const int buf = s & 1;
+        const uint32_t round = ((s >> 1) & 1) ? 0u : ENC_X_ROUND;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            // the matrix streams from L2, one k fragment of the half's row tiles at a time
-#pragma unroll 1
-            for (int kf = 0; kf < NK; ++kf) {
-                const uint4 bv = hr[kf * 64 + lane];
+        for (int r = 0; r < R; ++r) {
+            if (s >= len[r]) continue;                                     // uniform over the workgroup and its partners
+            const float4* h4 = reinterpret_cast<const float4*>(&hs[buf][r][0]);
+            floatx4 gs = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int j = 0; j < HALF; ++j)
-                    acc[half * HALF + j] = mfma_frag<XT>(Whh[xfrag(NK, TPW * wave + half * HALF + j, kf, lane)], bv, acc[half * HALF + j]);
+            for (int i = 0; i < NI; ++i) {
+                const float4 hv = h4[i * ENC_X_PARTS + p];
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    gs[g] = fmaf(wr[g][i].w, hv.w, fmaf(wr[g][i].z, hv.z, fmaf(wr[g][i].y, hv.y, fmaf(wr[g][i].x, hv.x, gs[g]))));
             }
 #pragma unroll
-            for (int j = 0; j < HALF; ++j) {
-                const int i = half * HALF + j;
-                const float gi = sigmoidf_(acc[i][0]), gf = sigmoidf_(acc[i][1]), gg = tanhf_(acc[i][2]), go = sigmoidf_(acc[i][3]);
-                const int u = 4 * (TPW * wave + i) + g;           // this lane's unit of tile i
-                const float cn = gf * cl[u * 16 + n] + gi * gg;
-                cl[u * 16 + n] = cn;
-                const float h = go * tanhf_(cn);
-                hx[(((u / G::KB) * 64 + n + 16 * ((u % G::KB) / G::EPL)) * G::EPL) + (u % G::EPL)] = from_float<XT>(h);
-                if (store) out[(size_t)(col0 + t_cur) * (2 * ENC_HID) + dir * ENC_HID + u] = h;
-                acc[i] = *reinterpret_cast<const floatx4*>(xp + (size_t)tn * ENC_GATES + i * 16);
+            for (int g = 0; g < 4; ++g) gs[g] = row16_sum(gs[g]);
+            gs += x[r];
+            const float gi = sigmoidf_(gs[0]), gf = sigmoidf_(gs[1]), gg = tanhf_(gs[2]), go = sigmoidf_(gs[3]);
+            c[r] = gf * c[r] + gi * gg;
+            const float h = go * tanhf_(c[r]);
+            if (p == 0) {
+                if (s + 1 < len[r])
+                    __hip_atomic_store(&words[(r * 2 + buf) * ENC_HID + unit], (__float_as_uint(h) & ~ENC_X_ROUND) | round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                out[(size_t)(col0[r] + token(r, s)) * (2 * ENC_HID) + dir * ENC_HID + unit] = h;
             }
+            x[r] = *reinterpret_cast<const floatx4*>(xp + (size_t)(col0[r] + token(r, s + 1)) * ENC_GATES);
         }
-        __syncthreads();                       // the new h is complete; the old one is free to be overwritten next step
+        // the whole h of this step, for the next one
+        for (int i = tid; i < R * ENC_HID; i += nthr) {
+            const int r = i / ENC_HID, u = i - r * ENC_HID;
+            int l = len[0];
+#pragma unroll
+            for (int k = 1; k < R; ++k) l = r == k ? len[k] : l;
+            if (s + 1 >= l) continue;
+            uint32_t* at = &words[(r * 2 + buf) * ENC_HID + u];
+            uint32_t v = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int polls = 0; (v & ENC_X_ROUND) != round; ++polls) {
+                if (polls >= wait_polls) {
+                    gave_up = 1;
+                    __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    break;
+                }
+                v = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            v &= ~ENC_X_ROUND;
+            if ((v & 0x7FFFFFFFu) >= 0x3FC00000u) v |= ENC_X_ROUND;        // no h has a magnitude of 1.5: it was a NaN
+            hs[buf ^ 1][r][u] = __uint_as_float(v);
+        }
+        __syncthreads();                               // h is complete (every wave has read the other buffer)
+        if (gave_up) return;
     }
 }
 
+template <int R>
+void lstm_shared(int G, const EncoderPtrs& d, const PnWindows& w, float* out, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_enc_lstm_shared<R>), dim3(G, (w.n + R - 1) / R, 2), dim3(ENC_HID / G * ENC_X_PARTS), 0, s, (const uint4*)d.w_hh[0],
+                       (const uint4*)d.w_hh[1], d.xproj, d.hx, w, d.max_tokens, out, d.wait_polls, d.fault);
+}
+
 template <typename XT>
-hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, float* out, hipStream_t s)
+hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const EncStaged& staged, float* out, hipStream_t s)
 {
     constexpr int C = ENC_DIM;
     const int n_ctiles = (n_col + 15) / 16, n_col_pad = n_ctiles * 16;
     const bool wide = n_ctiles >= PN_WIDE_FROM;
     XT* x0 = reinterpret_cast<XT*>(d.act[0]);
     XT* x1 = reinterpret_cast<XT*>(d.act[1]);
-    PostnetPtrs tables{};                     // the shared per-column table kernel only needs these two
-    tables.cmeta = d.cmeta;
-    tables.orow = d.orow;
-    hipError_t e = launch_postnet_meta(tables, w, n_col, n_col_pad, true, s);
-    if (e != hipSuccess) return e;
     EncTables tb;
     for (int t = 0; t < ENC_TABLES; ++t) tb.t[t] = d.tables[t];
-    hipLaunchKernelGGL((k_enc_embed<XT>), dim3((n_col_pad * C + 255) / 256), dim3(256), 0, s, tb, d.ids, d.max_tokens, n_col, n_col_pad, x0);
-    e = hipGetLastError();
+    hipLaunchKernelGGL((k_enc_embed<XT>), dim3((n_col_pad + 3) / 4), dim3(256), 0, s, tb, staged, n_col, n_col_pad, x0, d.cmeta, d.hx,
+                       sizeof(XT) == 2 ? 0 : w.n * 4 * ENC_HID);
+    hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[0], d.conv_b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[1], d.conv_b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[2], d.conv_b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
@@ -374,38 +441,36 @@ hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, float*
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if constexpr (sizeof(XT) == 2) {
-        // two-byte weights: the recurrence on the vector units, a workgroup per direction and request
-        static bool dot_attr_set = false;
-        if (!dot_attr_set) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_enc_lstm_dot), hipFuncAttributeMaxDynamicSharedMemorySize, ENC_DOT_LDS_BYTES);
+        static bool attr_set = false;               // dynamic LDS above 64 KB has to be allowed once
+        if (!attr_set) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_enc_lstm_sp), hipFuncAttributeMaxDynamicSharedMemorySize, ENC_SP_LDS_BYTES);
             if (e != hipSuccess) return e;
-            dot_attr_set = true;
+            attr_set = true;
         }
-        hipLaunchKernelGGL(k_enc_lstm_dot, dim3(2, w.n), dim3(ENC_DOT_THREADS), ENC_DOT_LDS_BYTES, s, (const uint4*)d.w_hh[0], (const uint4*)d.w_hh[1], d.xproj, w,
+        hipLaunchKernelGGL(k_enc_lstm_sp, dim3(2, w.n), dim3(ENC_SP_THREADS), ENC_SP_LDS_BYTES, s, (const uint4*)d.w_hh[0], (const uint4*)d.w_hh[1], d.xproj, w,
                            d.max_tokens, out);
     } else {
-        // fp32 weights: a call with a few requests takes the kernel that compacts the cell update
-        const bool compact = w.n <= ENC_COMPACT_UP_TO;
-        const int lds = compact ? EncLstmGeom<XT>::LDS_BYTES : EncLstmWideGeom<XT>::LDS_BYTES;
-        auto kern = compact ? k_enc_lstm<XT> : k_enc_lstm_wide<XT>;
-        static bool attr_set[2] = {false, false};   // dynamic LDS above 64 KB has to be allowed once per kernel
-        if (!attr_set[compact]) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            if (e != hipSuccess) return e;
-            attr_set[compact] = true;
-        }
-        hipLaunchKernelGGL(kern, dim3(2, (w.n + 15) / 16), dim3(256), lds, s, (const uint4*)d.w_hh[0], (const uint4*)d.w_hh[1], d.xproj, w,
-                           d.max_tokens, out);
+        // as many workgroups per direction and request as can all be resident, at least 4 (256 KB of weights each); from
+        // there on, several requests per group of workgroups
+        int G = 16, R = 1;
+        auto wgs = [&] { return 2L * G * ((w.n + R - 1) / R); };
+        while (G > 4 && wgs() > d.n_cu) G /= 2;
+        while (R < 8 && wgs() > d.n_cu) R *= 2;
+        if (wgs() > d.n_cu) return hipErrorCooperativeLaunchTooLarge;
+        if (R == 1) lstm_shared<1>(G, d, w, out, s);
+        else if (R == 2) lstm_shared<2>(G, d, w, out, s);
+        else if (R == 4) lstm_shared<4>(G, d, w, out, s);
+        else lstm_shared<8>(G, d, w, out, s);
     }
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_encoder(const EncoderPtrs& d, int wdtype, const PnWindows& w, int n_col, float* out, hipStream_t s)
+hipError_t launch_encoder(const EncoderPtrs& d, int wdtype, const PnWindows& w, int n_col, const EncStaged& staged, float* out, hipStream_t s)
 {
     if (n_col < 1 || w.n < 1) return hipSuccess;
-    return wdtype == 0 ? run_typed<float>(d, w, n_col, out, s) : run_typed<h16_t>(d, w, n_col, out, s);
+    return wdtype == 0 ? run_typed<float>(d, w, n_col, staged, out, s) : run_typed<h16_t>(d, w, n_col, staged, out, s);
 }
 
 }  // namespace tts

@@ -23,13 +23,21 @@ struct EncoderPtrs {
     const float* b[2];                      // permuted like the rows
     void* act[2];                           // activations of the convolution stack, fragment order
     int* cmeta;                             // per column: (request length << 16) | position inside the request
-    int* orow;                              // written by the shared table kernel, unused here
-    int* ids;                               // [tables][max_tokens]
+    uint32_t* hx;                           // fp32: [2][requests][2][ENC_HID] words through which workgroups exchange h
     float* xproj;                           // [2][max_tokens][ENC_GATES]: W_ih x + b of every token, both directions
     int max_tokens;
+    int n_cu;                               // compute units of the device
+    int wait_polls;                         // how often a workgroup polls a partner's word before it gives up
+    int* fault;                             // pinned host word, raised by a workgroup that gave up
 };
 
-// ids are already in d.ids; w lists the requests (PnWindows: col0 = first token, len); out fp32 [n_col][2 hid]
-hipError_t launch_encoder(const EncoderPtrs& d, int wdtype, const PnWindows& w, int n_col, float* out, hipStream_t s);
+// what a call hands over through pinned host memory (device addresses), one entry per token
+struct EncStaged {
+    const int4* ids;                        // the ids of the four tables
+    const int* meta;                        // (request length << 16) | position inside the request
+};
+
+// w lists the requests (PnWindows: col0 = first token, len); out fp32 [n_col][2 hid]
+hipError_t launch_encoder(const EncoderPtrs& d, int wdtype, const PnWindows& w, int n_col, const EncStaged& staged, float* out, hipStream_t s);
 
 }  // namespace tts

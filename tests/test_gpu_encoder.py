@@ -238,3 +238,20 @@ def test_largest_batch_bf16():
     np.testing.assert_array_equal(got[200], enc.run(ids[150:])[50])
     enc.close()
 
+
+
+def test_shared_recurrence_fp32():
+    """fp32 weights: how many workgroups share a direction, and how many requests share them, follows from the number of
+    requests (every boundary of that rule is here); the order of a sum does not, so results equal those of a request alone."""
+    w = synth.make_encoder_weights()
+    lens = [3, 1, 8, 2, 5] + [1 + i % 3 for i in range(124)]
+    ids = [synth.encoder_ids(L, 1500 + i) for i, L in enumerate(lens)]
+    enc = binding.Encoder(binding.make_encoder_config(max_tokens=1024, max_len=16), w)
+    alone = {k: enc.run([ids[k]])[0] for k in (0, 1, 2, 7, 8, 15, 31, 63, 128)}
+    for n in (2, 8, 9, 16, 17, 32, 33, 64, 65, 128, 129):
+        say(f"case encoder, fp32: {n} requests share the recurrence")
+        got = enc.run(ids[:n])
+        for k in alone:
+            if k < n:
+                np.testing.assert_array_equal(got[k], alone[k])
+    enc.close()
