@@ -20,7 +20,7 @@
  * tts_pool_add_request as a device pointer.  All kernels are queued on the
  * stream given at creation; device memory comes from the caller's arena;
  * nothing is allocated on the device (creation allocates pinned host memory:
- * two buffers through which the ids travel, in turn, and a status word).  Conventions as in tts_pool.h: 0 on
+ * two buffers through which the ids travel, in turn).  Conventions as in tts_pool.h: 0 on
  * success, negative tts_status otherwise, text in tts_last_error(); one owner
  * thread per object.
  */
@@ -77,12 +77,16 @@ int tts_encoder_create(const tts_encoder_config *cfg, const tts_encoder_weights 
  *   d_out   DEVICE fp32 [total][2 * hid]: F_enc of the requests back to back.
  * Asynchronous on the stream (ids and lens are consumed before the call returns).
  * Errors: TTS_E_INVAL for null pointers, n outside 1 .. TTS_ENCODER_MAX_BATCH, bad lengths, more than
- * max_tokens tokens, or an id outside its table.  With fp32 weights the workgroups of the recurrence hand h to each
- * other and wait for it, a bounded time; if such a wait ran out (never seen: it takes a device that keeps a workgroup
- * from starting for a quarter of a second), the next tts_encoder_run or tts_encoder_elapsed_ms returns TTS_E_LOST once:
- * the results of the call before it are not valid.
+ * max_tokens tokens, or an id outside its table.
  */
 int tts_encoder_run(tts_encoder *enc, const int *ids, const int *lens, int n, float *d_out);
+
+/*
+ * With fp32 weights the workgroups of the recurrence hand h to each other and poll for it at most `polls` times (some
+ * milliseconds by default); if other work on the GPU keeps one of them from starting for so long, the call's results are
+ * formed again without such hand-overs, bit for bit the same, at some forty times the time.  0 is allowed.
+ */
+int tts_encoder_set_wait_polls(tts_encoder *enc, int polls);
 
 /* Device time of the last tts_encoder_run in milliseconds (HIP events on the stream); waits for the stream. */
 int tts_encoder_elapsed_ms(tts_encoder *enc, float *out_ms);

@@ -43,7 +43,7 @@ EXPORTS = (
     "tts_postnet_destroy",
     "tts_vocoder_workspace_bytes", "tts_vocoder_create", "tts_vocoder_run", "tts_vocoder_elapsed_ms",
     "tts_vocoder_destroy",
-    "tts_encoder_workspace_bytes", "tts_encoder_create", "tts_encoder_run", "tts_encoder_elapsed_ms",
+    "tts_encoder_workspace_bytes", "tts_encoder_create", "tts_encoder_run", "tts_encoder_set_wait_polls", "tts_encoder_elapsed_ms",
     "tts_encoder_destroy",
 )
 
@@ -173,6 +173,7 @@ def lib() -> C.CDLL:
     L.tts_encoder_create.argtypes = [C.POINTER(TtsEncoderConfig), C.POINTER(TtsEncoderWeights), vp, C.c_size_t, vp,
                                      C.POINTER(vp)]
     L.tts_encoder_run.argtypes = [vp, _ip, _ip, C.c_int, vp]
+    L.tts_encoder_set_wait_polls.argtypes = [vp, C.c_int]
     L.tts_encoder_elapsed_ms.argtypes = [vp, _fp]
     L.tts_encoder_destroy.restype = None
     L.tts_encoder_destroy.argtypes = [vp]
@@ -682,6 +683,9 @@ class Encoder:
         _check(lib().tts_encoder_run(self._h, ids.ctypes.data_as(_ip), lens.ctypes.data_as(_ip), int(lens.shape[0]),
                                      C.c_void_p(d_out.data_ptr())))
         return [int(x) for x in np.concatenate([[0], np.cumsum(lens)[:-1]])]
+
+    def set_wait_polls(self, polls: int) -> None:
+        _check(lib().tts_encoder_set_wait_polls(self._h, int(polls)))
 
     def run(self, ids_list) -> list:
         """Returns F_enc of every request as numpy [L_i, 2 hid]."""

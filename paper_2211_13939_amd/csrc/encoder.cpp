@@ -30,9 +30,14 @@ int check(const tts_encoder_config* c)
     return TTS_OK;
 }
 
+// How often a workgroup of the fp32 recurrence polls a partner's word: a few milliseconds, far above a step's exchange (1 us)
+// and far below what a pool's workgroups wait (DEFAULT_WAIT_POLLS), so that where the two keep each other from starting it is
+// the encoder that gives way (its results then come from k_enc_lstm_alone).
+constexpr int ENC_WAIT_POLLS = DEFAULT_WAIT_POLLS / 64;
+
 struct EncLayout {
     size_t tables[ENC_TABLES], conv_w[ENC_CONVS], conv_b[ENC_CONVS], w_ih[2], w_hh[2], b[2];
-    size_t act[2], cmeta, hx, xproj, total;
+    size_t act[2], cmeta, hx, gave_up, xproj, total;
     size_t scratch_begin;      // everything from here on is cleared at creation
 };
 
@@ -56,6 +61,7 @@ EncLayout layout_of(const tts_encoder_config& c)
     for (int i = 0; i < 2; ++i) l.act[i] = a.take(cols * ENC_DIM * ws);
     l.cmeta = a.take(cols * 4);
     l.hx = a.take(ws == 4 ? (size_t)2 * ENC_MAX_BATCH * 2 * ENC_HID * 4 : 0);
+    l.gave_up = a.take(ws == 4 ? 4 : 0);
     l.xproj = a.take((size_t)2 * c.max_tokens * ENC_GATES * 4);
     l.total = a.off;
     return l;
@@ -82,16 +88,7 @@ struct tts_encoder {
         bool used = false;
     } st[2];
     int last = -1;                       // staging buffer of the last call
-    int* h_fault = nullptr;              // pinned, mapped: non-zero once a kernel's bounded wait has run out
 };
-
-// a workgroup of an earlier call gave up waiting for its partners: that call's results are not valid
-static int check_fault(tts_encoder* e)
-{
-    if (!e->h_fault || !*e->h_fault) return TTS_OK;
-    *e->h_fault = 0;
-    return fail(TTS_E_LOST, "a bounded wait of an earlier tts_encoder_run ran out: its results are not valid");
-}
 
 extern "C" size_t tts_encoder_workspace_bytes(const tts_encoder_config* cfg)
 {
@@ -163,13 +160,6 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
         st.dev.ids = static_cast<const int4*>(dev);
         st.dev.meta = reinterpret_cast<const int*>(st.dev.ids + n_tok);
     }
-    if (rc == TTS_OK) {
-        if (hipHostMalloc((void**)&e->h_fault, sizeof(int), hipHostMallocMapped) != hipSuccess ||
-            hipHostGetDevicePointer((void**)&e->d.fault, e->h_fault, 0) != hipSuccess)
-            rc = fail(TTS_E_HIP, "hipHostMalloc of the status word failed");
-        else
-            *e->h_fault = 0;
-    }
     if (rc == TTS_OK && hipDeviceGetAttribute(&e->d.n_cu, hipDeviceAttributeMultiprocessorCount, attr.device) != hipSuccess)
         rc = fail(TTS_E_HIP, "the number of compute units is not known");
     if (rc) {
@@ -191,7 +181,8 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
     p.act[1] = base + lay.act[1];
     p.cmeta = (int*)(base + lay.cmeta);
     p.hx = (uint32_t*)(base + lay.hx);
-    p.wait_polls = DEFAULT_WAIT_POLLS;
+    p.gave_up = (int*)(base + lay.gave_up);
+    p.wait_polls = ENC_WAIT_POLLS;
     p.xproj = (float*)(base + lay.xproj);
     p.max_tokens = cfg->max_tokens;
     *out = e;
@@ -201,8 +192,6 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
 extern "C" int tts_encoder_run(tts_encoder* e, const int* ids, const int* lens, int n, float* d_out)
 {
     if (!e || !ids || !lens || !d_out) return fail(TTS_E_INVAL, "null argument");
-    int rc = check_fault(e);
-    if (rc) return rc;
     if (n < 1 || n > ENC_MAX_BATCH) return fail(TTS_E_INVAL, "n = %d requests, at most %d per call", n, ENC_MAX_BATCH);
     PnWindows w;
     w.n = n;
@@ -240,6 +229,14 @@ extern "C" int tts_encoder_run(tts_encoder* e, const int* ids, const int* lens, 
     return TTS_OK;
 }
 
+extern "C" int tts_encoder_set_wait_polls(tts_encoder* e, int polls)
+{
+    if (!e) return fail(TTS_E_INVAL, "encoder is null");
+    if (polls < 0) return fail(TTS_E_INVAL, "polls = %d is negative", polls);
+    e->d.wait_polls = polls;
+    return TTS_OK;
+}
+
 extern "C" int tts_encoder_elapsed_ms(tts_encoder* e, float* out_ms)
 {
     if (!e || !out_ms) return fail(TTS_E_INVAL, "null argument");
@@ -247,7 +244,7 @@ extern "C" int tts_encoder_elapsed_ms(tts_encoder* e, float* out_ms)
     const tts_encoder::Staging& st = e->st[e->last];
     HIP_TRY(hipEventSynchronize(st.ev1));
     HIP_TRY(hipEventElapsedTime(out_ms, st.ev0, st.ev1));
-    return check_fault(e);
+    return TTS_OK;
 }
 
 extern "C" void tts_encoder_destroy(tts_encoder* e)
@@ -259,6 +256,5 @@ extern "C" void tts_encoder_destroy(tts_encoder* e)
         if (st.ev1) (void)hipEventDestroy(st.ev1);
         if (st.ids) (void)hipHostFree(st.ids);
     }
-    if (e->h_fault) (void)hipHostFree(e->h_fault);
     delete e;
 }

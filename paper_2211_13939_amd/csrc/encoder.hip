@@ -5,6 +5,7 @@
 //   the recurrence, a chain of L dependent steps of a 1024 x 256 matrix-vector product (latency, not bandwidth):
 //   k_enc_lstm_sp      two-byte weights, one workgroup per direction and request, the matrix resident in its CU
 //   k_enc_lstm_shared  fp32 weights, several workgroups per direction and request(s), the matrix spread over their registers
+//   k_enc_lstm_alone   fp32 weights, one workgroup per direction and request: where the former's workgroups did not all start
 // The gate rows of W_ih, the biases and the fp32 W_hh are stored unit-major / gate-minor, so the four gate sums of a unit
 // are contiguous; the two-byte W_hh has one gate of 16 units per row tile.
 #include "encoder_kernels.h"
@@ -19,14 +20,15 @@ struct EncTables { const float* t[ENC_TABLES]; };
 // One wave per column, eight channels a lane.  The ids and the per-column table of the convolutions (staged.meta: request
 // length << 16 | position inside the request) come straight from the call's pinned staging buffer: one trip over the host link
 // in place of four copies and a kernel that expanded the table.  The words through which k_enc_lstm_shared's workgroups
-// exchange h are cleared here as well (n_words of them; none in the two-byte mode).
+// exchange h, and the one that says that it gave up, are cleared here as well (n_words; none in the two-byte mode).
 template <typename XT>
 __global__ __launch_bounds__(256) void k_enc_embed(EncTables tb, EncStaged staged, int n_col, int n_col_pad, XT* __restrict__ X,
-                                                   int* __restrict__ cmeta, uint32_t* __restrict__ hx, int n_words)
+                                                   int* __restrict__ cmeta, uint32_t* __restrict__ hx, int n_words, int* __restrict__ gave_up)
 {
     constexpr int KB = Frag<XT>::KB, EPL = Frag<XT>::EPL;
     const int col = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     for (int i = blockIdx.x * 256 + threadIdx.x; i < n_words; i += gridDim.x * 256) hx[i] = 0;
+    if (n_words > 0 && blockIdx.x == 0 && threadIdx.x == 0) *gave_up = 0;
     if (col >= n_col_pad) return;
     float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     int meta = 0;
@@ -298,7 +300,9 @@ __global__ __launch_bounds__(ENC_SP_THREADS) void k_enc_lstm_sp(const uint4* __r
 // (16 threads per unit, each 16 k of its four gate rows: 64 FMAs) to 0.4 us (16 waves a workgroup).  Measured: one request of
 // 165 tokens 6.56 -> 0.22 ms (1.3 us a step), 8 requests of 30 .. 300 tokens 5.8 -> 0.45 ms, 60 of them 1.0 ms.  G is as large as the
 // number of workgroups allows: all of them (2 directions x groups x G <= one per CU) must be resident at once, because they
-// wait for each other.  Every wait is bounded; one that runs out raises *fault and ends the workgroup.
+// wait for each other.  Work on other streams may keep some from starting (a second encoder, a pool whose own workgroups
+// wait for each other): every wait is bounded, one that runs out raises *fault and ends the workgroup, and k_enc_lstm_alone
+// behind this kernel then forms the call's results without waiting for anybody.
 // A unit's sum is taken in the same order whatever G and R are, so a request's result does not depend on its companions.
 // grid = (G, groups of R requests, 2 directions), 4096 / G threads (<= 1024).
 constexpr int ENC_X_PARTS = 16;                                            // threads per unit: thread p owns k = 64 i + 4 p .. + 3
@@ -308,6 +312,32 @@ template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
 {
     return x + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, true));
 }
+// The four gate sums of a unit over this lane's 16 k; weights(g, i) = four k of gate g.  One order of the sums and one form of
+// the cell for both kernels, so that they agree bit for bit.
+constexpr int ENC_X_NI = ENC_HID / (4 * ENC_X_PARTS);
+template <typename W>
+__device__ __forceinline__ floatx4 gate_parts(const float* h, int p, W&& weights)
+{
+    const float4* h4 = reinterpret_cast<const float4*>(h);
+    floatx4 gs = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < ENC_X_NI; ++i) {
+        const float4 hv = h4[i * ENC_X_PARTS + p];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 w = weights(g, i);
+            gs[g] = fmaf(w.w, hv.w, fmaf(w.z, hv.z, fmaf(w.y, hv.y, fmaf(w.x, hv.x, gs[g]))));
+        }
+    }
+    return gs;
+}
+__device__ __forceinline__ float cell(floatx4 gs, float& c)
+{
+    const float gi = sigmoidf_(gs[0]), gf = sigmoidf_(gs[1]), gg = tanhf_(gs[2]), go = sigmoidf_(gs[3]);
+    c = fmaf(gf, c, gi * gg);
+    return go * tanhf_(c);
+}
+
 // the sum over the 16 lanes of a row, the same bits in all of them (partners add the same two values at every level)
 __device__ __forceinline__ float row16_sum(float x)
 {
@@ -322,7 +352,7 @@ __global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restric
                                                           const float* __restrict__ xproj, uint32_t* hx, PnWindows w, int max_tokens,
                                                           float* __restrict__ out, int wait_polls, int* fault)
 {
-    constexpr int NK = ENC_HID / 16, NI = ENC_HID / (4 * ENC_X_PARTS);
+    constexpr int NK = ENC_HID / 16, NI = ENC_X_NI;
     __shared__ __attribute__((aligned(16))) float hs[2][R][ENC_HID];
     __shared__ int gave_up;
     const int tid = threadIdx.x, nthr = blockDim.x, p = tid & (ENC_X_PARTS - 1);
@@ -364,21 +394,11 @@ __global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restric
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (s >= len[r]) continue;                                     // uniform over the workgroup and its partners
-            const float4* h4 = reinterpret_cast<const float4*>(&hs[buf][r][0]);
-            floatx4 gs = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const float4 hv = h4[i * ENC_X_PARTS + p];
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    gs[g] = fmaf(wr[g][i].w, hv.w, fmaf(wr[g][i].z, hv.z, fmaf(wr[g][i].y, hv.y, fmaf(wr[g][i].x, hv.x, gs[g]))));
-            }
+            floatx4 gs = gate_parts(&hs[buf][r][0], p, [&](int g, int i) { return wr[g][i]; });
 #pragma unroll
             for (int g = 0; g < 4; ++g) gs[g] = row16_sum(gs[g]);
             gs += x[r];
-            const float gi = sigmoidf_(gs[0]), gf = sigmoidf_(gs[1]), gg = tanhf_(gs[2]), go = sigmoidf_(gs[3]);
-            c[r] = gf * c[r] + gi * gg;
-            const float h = go * tanhf_(c[r]);
+            const float h = cell(gs, c[r]);
             if (p == 0) {
                 if (s + 1 < len[r])
                     __hip_atomic_store(&words[(r * 2 + buf) * ENC_HID + unit], (__float_as_uint(h) & ~ENC_X_ROUND) | round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -398,7 +418,7 @@ __global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restric
             for (int polls = 0; (v & ENC_X_ROUND) != round; ++polls) {
                 if (polls >= wait_polls) {
                     gave_up = 1;
-                    __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;
                 }
                 v = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -412,11 +432,49 @@ __global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restric
     }
 }
 
+// The same recurrence by one workgroup per direction and request, the weights streamed from L2 in every step (40 us a step:
+// one CU's load path).  It ends at once unless k_enc_lstm_shared gave up (given == nullptr: it was not launched, the device has
+// too few compute units for its workgroups).  grid = (2 directions, requests), 1024 threads.
+__global__ __launch_bounds__(1024) void k_enc_lstm_alone(const uint4* __restrict__ Whh0, const uint4* __restrict__ Whh1,
+                                                         const float* __restrict__ xproj, PnWindows w, int max_tokens,
+                                                         float* __restrict__ out, const int* given)
+{
+    constexpr int NK = ENC_HID / 16, PASS = 1024 / ENC_X_PARTS, NP = ENC_HID / PASS;
+    if (given && *given == 0) return;
+    __shared__ __attribute__((aligned(16))) float hs[2][ENC_HID], cs[ENC_HID];
+    const int tid = threadIdx.x, p = tid & (ENC_X_PARTS - 1), dir = blockIdx.x;
+    const int len = (int)w.len[blockIdx.y], col0 = w.col0[blockIdx.y];
+    const uint4* Whh = dir ? Whh1 : Whh0;
+    if (tid < ENC_HID) hs[0][tid] = cs[tid] = 0.f;
+    __syncthreads();
+    for (int s = 0; s < len; ++s) {
+        const size_t col = (size_t)col0 + (dir ? len - 1 - s : s);
+#pragma unroll 1
+        for (int k = 0; k < NP; ++k) {                 // (a pass's weights are all the registers hold)
+            const int unit = k * PASS + tid / ENC_X_PARTS;
+            floatx4 gs = gate_parts(hs[s & 1], p, [&](int g, int i) {
+                return __builtin_bit_cast(float4, Whh[xfrag(NK, unit >> 2, 4 * i + (p >> 2), 4 * (unit & 3) + g + 16 * (p & 3))]);
+            });
+#pragma unroll
+            for (int g = 0; g < 4; ++g) gs[g] = row16_sum(gs[g]);
+            gs += *reinterpret_cast<const floatx4*>(xproj + ((size_t)dir * max_tokens + col) * ENC_GATES + 4 * unit);
+            float c = cs[unit];                        // (read and written by the lanes of one wave)
+            const float h = cell(gs, c);
+            if (p == 0) {
+                cs[unit] = c;
+                hs[(s + 1) & 1][unit] = h;
+                out[col * (2 * ENC_HID) + dir * ENC_HID + unit] = h;
+            }
+        }
+        __syncthreads();                               // h is complete (every wave has read the other buffer)
+    }
+}
+
 template <int R>
 void lstm_shared(int G, const EncoderPtrs& d, const PnWindows& w, float* out, hipStream_t s)
 {
     hipLaunchKernelGGL((k_enc_lstm_shared<R>), dim3(G, (w.n + R - 1) / R, 2), dim3(ENC_HID / G * ENC_X_PARTS), 0, s, (const uint4*)d.w_hh[0],
-                       (const uint4*)d.w_hh[1], d.xproj, d.hx, w, d.max_tokens, out, d.wait_polls, d.fault);
+                       (const uint4*)d.w_hh[1], d.xproj, d.hx, w, d.max_tokens, out, d.wait_polls, d.gave_up);
 }
 
 template <typename XT>
@@ -430,7 +488,7 @@ hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const 
     EncTables tb;
     for (int t = 0; t < ENC_TABLES; ++t) tb.t[t] = d.tables[t];
     hipLaunchKernelGGL((k_enc_embed<XT>), dim3((n_col_pad + 3) / 4), dim3(256), 0, s, tb, staged, n_col, n_col_pad, x0, d.cmeta, d.hx,
-                       sizeof(XT) == 2 ? 0 : w.n * 4 * ENC_HID);
+                       sizeof(XT) == 2 ? 0 : w.n * 4 * ENC_HID, d.gave_up);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[0], d.conv_b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[1], d.conv_b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
@@ -456,11 +514,17 @@ hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const 
         auto wgs = [&] { return 2L * G * ((w.n + R - 1) / R); };
         while (G > 4 && wgs() > d.n_cu) G /= 2;
         while (R < 8 && wgs() > d.n_cu) R *= 2;
-        if (wgs() > d.n_cu) return hipErrorCooperativeLaunchTooLarge;
-        if (R == 1) lstm_shared<1>(G, d, w, out, s);
+        const bool share = wgs() <= d.n_cu;
+        if (!share) {
+            // too few compute units for that many requests: without partners
+        } else if (R == 1) lstm_shared<1>(G, d, w, out, s);
         else if (R == 2) lstm_shared<2>(G, d, w, out, s);
         else if (R == 4) lstm_shared<4>(G, d, w, out, s);
         else lstm_shared<8>(G, d, w, out, s);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_enc_lstm_alone, dim3(2, w.n), dim3(1024), 0, s, (const uint4*)d.w_hh[0], (const uint4*)d.w_hh[1], d.xproj, w,
+                           d.max_tokens, out, share ? d.gave_up : nullptr);
     }
     return hipGetLastError();
 }

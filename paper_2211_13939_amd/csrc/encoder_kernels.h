@@ -28,7 +28,7 @@ struct EncoderPtrs {
     int max_tokens;
     int n_cu;                               // compute units of the device
     int wait_polls;                         // how often a workgroup polls a partner's word before it gives up
-    int* fault;                             // pinned host word, raised by a workgroup that gave up
+    int* gave_up;                           // fp32: device word, raised by a workgroup that gave up
 };
 
 // what a call hands over through pinned host memory (device addresses), one entry per token

@@ -255,3 +255,21 @@ def test_shared_recurrence_fp32():
             if k < n:
                 np.testing.assert_array_equal(got[k], alone[k])
     enc.close()
+
+
+@pytest.mark.parametrize("n", [1, 9, 65])
+def test_shared_recurrence_that_gives_up_fp32(n):
+    """Workgroups whose partners keep them waiting give up (here at once: no polls are allowed); the call's results are the
+    same, bit for bit, and so are those of the call behind it."""
+    w = synth.make_encoder_weights()
+    ids = [synth.encoder_ids(3 + 7 * i % 20, 1700 + i) for i in range(n)]
+    enc = binding.Encoder(binding.make_encoder_config(max_tokens=2048, max_len=32), w)
+    want = enc.run(ids)
+    say(f"case encoder, fp32: {n} requests, no polls")
+    enc.set_wait_polls(0)
+    got = enc.run(ids)
+    enc.set_wait_polls(1 << 12)
+    for a, b, c in zip(want, got, enc.run(ids)):
+        np.testing.assert_array_equal(a, b)
+        np.testing.assert_array_equal(a, c)
+    enc.close()
