@@ -192,7 +192,7 @@ static int run_batch(tts_postnet* p, const PostnetPtrs& d, int max_columns, bool
             c += win_len[i];
             r += win_len[i] - keep_from[i];
         }
-        HIP_TRY(launch_postnet_meta(d, w, n_col, n_pad, i0 == 0, p->stream));
+        HIP_TRY(launch_postnet_pack(d, p->cfg.weight_dtype, w, d_mel, n_col, n_pad, i0 == 0, p->stream));
     }
     HIP_TRY(launch_postnet(d, p->cfg.weight_dtype, d_mel, n_col, d_out, p->stream));
     if (timed) {

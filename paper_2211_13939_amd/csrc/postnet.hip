@@ -5,55 +5,70 @@
 
 namespace tts {
 
-// Per-column tables from the call's window list: one workgroup per window; the first launch of a call
-// also marks the columns that pad the last tile.
-__global__ __launch_bounds__(64) void k_pn_meta(PnWindows w, int n_col, int n_col_pad, int clear_pad, int* __restrict__ cmeta,
-                                                int* __restrict__ orow)
+// Everything the layers need of a call's windows, in one launch: the per-column tables from the window list, and the mel frames
+// in the first layer's operand order, channels zero-padded to CIN.  A thread = 16 bytes of operand (8 or 4 channels of a column),
+// one 16-byte store.  grid = (windows, pieces of 256 threads of the longest window); the call's first launch also clears the
+// columns that pad the last tile.  Latency-bound at every size: as two
+// launches with 2-byte stores a round of 3 windows took 38.3 us and one of 64 86.9 us, like this 36.1 and 83.8 us.
+template <typename XT, int CIN>
+__global__ __launch_bounds__(256) void k_pn_pack(PnWindows w, const float* __restrict__ mel, int n_col, int n_col_pad, int clear_pad,
+                                                 XT* __restrict__ X, int* __restrict__ cmeta, int* __restrict__ orow)
 {
-    const int i = blockIdx.x;
-    if (i < w.n) {
-        const int T = w.len[i], keep = w.keep[i];
-        for (int t = threadIdx.x; t < T; t += 64) {
-            cmeta[w.col0[i] + t] = (T << 16) | t;
-            orow[w.col0[i] + t] = t >= keep ? w.row0[i] + (t - keep) : -1;
+    constexpr int KB = Frag<XT>::KB, EPL = Frag<XT>::EPL, NG = CIN / EPL;
+    static_assert(PN_N_MEL % EPL == 0 && CIN % EPL == 0, "a piece is all mel channels or all padding");
+    const int i = blockIdx.x, first = blockIdx.y * 256 + threadIdx.x;
+    const int T = w.len[i], keep = w.keep[i], col0 = w.col0[i], row0 = w.row0[i];
+    for (int e = first; e < T * NG; e += gridDim.y * 256) {
+        const int t = e / NG, ch = (e - t * NG) * EPL, col = col0 + t;
+        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (ch < PN_N_MEL) {
+#pragma unroll
+            for (int k = 0; k < EPL; k += 4) {
+                const float4 m = *reinterpret_cast<const float4*>(mel + (size_t)col * PN_N_MEL + ch + k);
+                v[k] = m.x; v[k + 1] = m.y; v[k + 2] = m.z; v[k + 3] = m.w;
+            }
+        }
+        XT* dst = X + xoff<XT>(CIN / KB, col, ch);
+        if constexpr (sizeof(XT) == 2) *reinterpret_cast<uint4*>(dst) = make_uint4(pack2<XT>(v[0], v[1]), pack2<XT>(v[2], v[3]), pack2<XT>(v[4], v[5]), pack2<XT>(v[6], v[7]));
+        else *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+        if (ch == 0) {
+            cmeta[col] = (T << 16) | t;
+            orow[col] = t >= keep ? row0 + (t - keep) : -1;
         }
     }
     if (clear_pad && i == 0)
-        for (int c = n_col + threadIdx.x; c < n_col_pad; c += 64) {
-            cmeta[c] = 0;
-            orow[c] = -1;
+        for (int e = first; e < (n_col_pad - n_col) * NG; e += gridDim.y * 256) {
+            const int c = e / NG, ch = (e - c * NG) * EPL, col = n_col + c;
+            *reinterpret_cast<uint4*>(X + xoff<XT>(CIN / KB, col, ch)) = make_uint4(0, 0, 0, 0);
+            if (ch == 0) {
+                cmeta[col] = 0;
+                orow[col] = -1;
+            }
         }
 }
 
-hipError_t launch_postnet_meta(const PostnetPtrs& d, const PnWindows& w, int n_col, int n_col_pad, bool first, hipStream_t s)
+hipError_t launch_postnet_pack(const PostnetPtrs& d, int wdtype, const PnWindows& w, const float* mel, int n_col, int n_col_pad, bool first,
+                               hipStream_t s)
 {
-    hipLaunchKernelGGL(k_pn_meta, dim3(w.n > 0 ? w.n : 1), dim3(64), 0, s, w, n_col, n_col_pad, first ? 1 : 0, d.cmeta, d.orow);
+    int most = 0;
+    for (int i = 0; i < w.n; ++i) most = w.len[i] > most ? w.len[i] : most;
+    if (w.n < 1 || most < 1) return hipSuccess;
+    auto go = [&](auto kern, int per_column, auto* x) {
+        hipLaunchKernelGGL(kern, dim3(w.n, (most * per_column + 255) / 256), dim3(256), 0, s, w, mel, n_col, n_col_pad, first ? 1 : 0, x, d.cmeta, d.orow);
+    };
+    if (wdtype == 0) go(k_pn_pack<float, PN_CIN0>, PN_CIN0 / Frag<float>::EPL, reinterpret_cast<float*>(d.act[0]));
+    else go(k_pn_pack<h16_t, PN_CIN0>, PN_CIN0 / Frag<h16_t>::EPL, reinterpret_cast<h16_t*>(d.act[0]));
     return hipGetLastError();
 }
 
-// mel fp32 [n_col][n_mel] -> layer-1 input in fragment order, channels zero-padded to CIN
-template <typename XT, int CIN>
-__global__ __launch_bounds__(256) void k_pn_pack(const float* __restrict__ mel, int n_mel, int n_col, int n_col_pad, XT* __restrict__ X)
-{
-    constexpr int KB = Frag<XT>::KB;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    const int col = idx / CIN, ch = idx - col * CIN;
-    if (col >= n_col_pad) return;
-    const float v = (col < n_col && ch < n_mel) ? mel[(size_t)col * n_mel + ch] : 0.f;
-    X[xoff<XT>(CIN / KB, col, ch)] = from_float<XT>(v);
-}
-
 template <typename XT>
-static hipError_t run_typed(const PostnetPtrs& d, const float* mel, int n_col, int n_ctiles, float* out, hipStream_t s)
+static hipError_t run_typed(const PostnetPtrs& d, const float* mel, int n_ctiles, float* out, hipStream_t s)
 {
     constexpr int C1 = PN_CIN0, C = PN_CHANNELS, CO = PN_COUT_LAST;
-    const int n_col_pad = n_ctiles * 16;
     const bool wide = n_ctiles >= PN_WIDE_FROM;
     XT* x0 = reinterpret_cast<XT*>(d.act[0]);
     XT* x1 = reinterpret_cast<XT*>(d.act[1]);
-    hipLaunchKernelGGL((k_pn_pack<XT, C1>), dim3((n_col_pad * C1 + 255) / 256), dim3(256), 0, s, mel, d.n_mel, n_col, n_col_pad, x0);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = conv_layer<XT, C1, C, PN_EPI_TANH>(wide, d.W[0], d.b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
+    hipError_t e = conv_layer<XT, C1, C, PN_EPI_TANH>(wide, d.W[0], d.b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(wide, d.W[1], d.b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(wide, d.W[2], d.b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(wide, d.W[3], d.b[3], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
@@ -65,7 +80,7 @@ hipError_t launch_postnet(const PostnetPtrs& d, int wdtype, const float* mel, in
 {
     const int n_ctiles = (n_col + 15) / 16;
     if (n_ctiles < 1) return hipSuccess;
-    return wdtype == 0 ? run_typed<float>(d, mel, n_col, n_ctiles, out, s) : run_typed<h16_t>(d, mel, n_col, n_ctiles, out, s);
+    return wdtype == 0 ? run_typed<float>(d, mel, n_ctiles, out, s) : run_typed<h16_t>(d, mel, n_ctiles, out, s);
 }
 
 }  // namespace tts

@@ -31,10 +31,12 @@ struct PnWindows {
     uint16_t len[PN_META_WINDOWS];    // frames in the window
     uint16_t keep[PN_META_WINDOWS];   // frames of context in front of the chunk
 };
-// n_col_pad: columns rounded up to whole tiles; `first` clears the padding columns too
-hipError_t launch_postnet_meta(const PostnetPtrs& d, const PnWindows& w, int n_col, int n_col_pad, bool first, hipStream_t s);
+// The windows' tables and mel frames where the layers read them.  mel: device fp32 [n_col][n_mel]; n_col_pad: columns rounded up
+// to whole tiles; `first`: the call's first windows (clears the padding columns too)
+hipError_t launch_postnet_pack(const PostnetPtrs& d, int wdtype, const PnWindows& w, const float* mel, int n_col, int n_col_pad, bool first,
+                               hipStream_t s);
 
-// mel: device fp32 [n_col][n_mel]; out: device fp32 [kept rows][n_mel]
+// The five layers behind it; out: device fp32 [kept rows][n_mel]
 hipError_t launch_postnet(const PostnetPtrs& d, int wdtype, const float* mel, int n_col, float* out, hipStream_t s);
 
 }  // namespace tts
