@@ -319,3 +319,21 @@ def test_serving_loop_with_postnet_matches_oracle(weights_fp32):
     assert worst <= 5 * TOL_F32
     pn.close()
     pool.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n", [15, 16, 17, 257])
+def test_packing_of_many_short_windows(bf16, n):
+    """Window list, mel and padding columns reach the layers whatever the number of windows (256 travel per launch) and of
+    columns that pad the last tile, also over what a larger call left behind: results equal those of calls of one window."""
+    ws, bs = synth.make_postnet_weights(bf16=bf16)
+    rng = np.random.default_rng(31)
+    wins = [rng.standard_normal((1 + i % 3 if n > 17 else 1, 80)).astype(np.float32) for i in range(n)]
+    keeps = [min(i % 2, w.shape[0] - 1) for i, w in enumerate(wins)]
+    say(f"case postnet packing: {n} windows, {sum(w.shape[0] for w in wins)} frames, {'bf16' if bf16 else 'fp32'}")
+    pn = binding.Postnet(binding.make_postnet_config(max_columns=1024, bf16=bf16), ws, bs)
+    pn.run([rng.standard_normal((1000, 80)).astype(np.float32)], [0])
+    got = pn.run(wins, keeps)
+    for i in sorted({0, 1, n // 2, n - 2, n - 1}):
+        np.testing.assert_array_equal(got[i], pn.run([wins[i]], [keeps[i]])[0])
+    pn.close()
