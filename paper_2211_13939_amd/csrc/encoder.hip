@@ -354,7 +354,8 @@ __global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restric
 {
     constexpr int NK = ENC_HID / 16, NI = ENC_X_NI;
     __shared__ __attribute__((aligned(16))) float hs[2][R][ENC_HID];
-    __shared__ int gave_up;
+    __shared__ int gave_up[2];                         // by the parity of the step: what a wave reads behind a step's barrier is not
+                                                       // written again before that wave has passed the next one
     const int tid = threadIdx.x, nthr = blockDim.x, p = tid & (ENC_X_PARTS - 1);
     const int dir = blockIdx.z, req0 = blockIdx.y * R, unit = blockIdx.x * (nthr / ENC_X_PARTS) + tid / ENC_X_PARTS;
     // lengths and first tokens once, into registers: the request table is a kernel argument
@@ -374,7 +375,7 @@ __global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restric
         for (int i = 0; i < NI; ++i)
             wr[g][i] = __builtin_bit_cast(float4, Whh[xfrag(NK, unit >> 2, 4 * i + (p >> 2), 4 * (unit & 3) + g + 16 * (p & 3))]);
     for (int i = tid; i < 2 * R * ENC_HID; i += nthr) (&hs[0][0][0])[i] = 0.f;
-    if (tid == 0) gave_up = 0;
+    if (tid < 2) gave_up[tid] = 0;
 
     auto token = [&](int r, int s) { return min(max(dir ? len[r] - 1 - s : s, 0), max(len[r] - 1, 0)); };
     const float* xp = xproj + (size_t)dir * max_tokens * ENC_GATES + 4 * unit;
@@ -417,7 +418,7 @@ __global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restric
             uint32_t v = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             for (int polls = 0; (v & ENC_X_ROUND) != round; ++polls) {
                 if (polls >= wait_polls) {
-                    gave_up = 1;
+                    gave_up[buf] = 1;
                     __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;
                 }
@@ -428,7 +429,7 @@ __global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restric
             hs[buf ^ 1][r][u] = __uint_as_float(v);
         }
         __syncthreads();                               // h is complete (every wave has read the other buffer)
-        if (gave_up) return;
+        if (gave_up[buf]) return;                      // every wave of the workgroup, at the same step
     }
 }
 

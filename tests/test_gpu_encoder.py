@@ -273,3 +273,19 @@ def test_shared_recurrence_that_gives_up_fp32(n):
         np.testing.assert_array_equal(a, b)
         np.testing.assert_array_equal(a, c)
     enc.close()
+
+
+@pytest.mark.parametrize("polls", [1, 2, 3, 4, 6])
+def test_shared_recurrence_that_gives_up_on_the_way_fp32(polls):
+    """A few polls are sometimes enough and sometimes not: workgroups give up in the middle of a chain, at steps of their own,
+    while their waves may be a step apart.  Every wave leaves at the same step, and the results are the same bits."""
+    w = synth.make_encoder_weights()
+    ids = [synth.encoder_ids(L, 2100 + i) for i, L in enumerate([90, 4, 33, 61, 1, 17, 48, 25, 70] * 4)]
+    enc = binding.Encoder(binding.make_encoder_config(max_tokens=2048, max_len=96), w)
+    want = {n: enc.run(ids[:n]) for n in (1, 9, 36)}
+    enc.set_wait_polls(polls)
+    for n in want:
+        say(f"case encoder, fp32: {n} requests, {polls} polls")
+        for a, b in zip(want[n], enc.run(ids[:n])):
+            np.testing.assert_array_equal(a, b)
+    enc.close()
