@@ -222,8 +222,12 @@ extern "C" int tts_encoder_run(tts_encoder* e, const int* ids, const int* lens, 
             st.meta[c] = (lens[i] << 16) | k;
         }
     HIP_TRY(hipEventRecord(st.ev0, e->stream));
-    HIP_TRY(launch_encoder(e->d, e->cfg.weight_dtype, w, n_col, st.dev, d_out, e->stream));
-    HIP_TRY(hipEventRecord(st.ev1, e->stream));
+    hipError_t err = launch_encoder(e->d, e->cfg.weight_dtype, w, n_col, st.dev, d_out, e->stream);
+    if (err == hipSuccess) err = hipEventRecord(st.ev1, e->stream);
+    if (err != hipSuccess) {
+        (void)hipStreamSynchronize(e->stream);              // kernels queued before the failure still read this buffer
+        return fail(TTS_E_HIP, "encoder launch: %s", hipGetErrorString(err));
+    }
     st.used = true;
     e->last = turn;
     return TTS_OK;

@@ -1,0 +1,160 @@
+// A HIP runtime and the kernels' launch wrappers on host memory, for the host side of the library alone: streams run what is
+// queued at once, except that what a kernel still has to read of pinned memory counts as pending until the host has waited for
+// it.  Any call can be made to fail (fake_fail), and a slot can be frozen as a kernel would that gave up (fake_freeze).
+#include <algorithm>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../paper_2211_13939_amd/csrc/encoder_kernels.h"
+#include "../paper_2211_13939_amd/csrc/kernels.h"
+
+namespace {
+
+struct Fail { int in, times; };
+std::map<std::string, int> calls;               // calls so far
+std::map<std::string, Fail> fails;              // the call that fails, counted from the time of fake_fail, and how many from there on
+struct Pending { const void* at; int seq; };
+std::vector<Pending> pending;                   // pinned memory that queued work still reads
+int seq = 0, violations = 0;                    // violations: such memory rewritten or freed
+int freeze_slot = -1, freeze_at = 0;
+struct Event { int seq = 0; };
+
+hipError_t call(const char* what)
+{
+    ++calls[what];
+    auto it = fails.find(what);
+    if (it == fails.end() || --it->second.in > 0) return hipSuccess;
+    if (--it->second.times <= 0) fails.erase(it);
+    return hipErrorUnknown;
+}
+void done_up_to(int s)
+{
+    pending.erase(std::remove_if(pending.begin(), pending.end(), [&](const Pending& p) { return p.seq <= s; }), pending.end());
+}
+bool is_pending(const void* at)
+{
+    return std::any_of(pending.begin(), pending.end(), [&](const Pending& p) { return p.at == at; });
+}
+
+}  // namespace
+
+extern "C" {
+void fake_fail(const char* what, int nth, int times) { fails[what] = {nth, times}; }
+void fake_reset() { fails.clear(); freeze_slot = -1; pending.clear(); violations = 0; }
+int fake_calls(const char* what) { return calls[what]; }
+int fake_violations() { return violations; }
+void fake_freeze(int slot, int at_frame) { freeze_slot = slot; freeze_at = at_frame; }
+
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "injected"; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void*)
+{
+    memset(a, 0, sizeof *a);
+    a->type = hipMemoryTypeDevice;
+    return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipDeviceSynchronize() { done_up_to(seq); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned)
+{
+    if (hipError_t e = call("hipHostMalloc")) return e;
+    *p = malloc(n);
+    return hipSuccess;
+}
+hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return hipSuccess; }
+hipError_t hipHostFree(void* p)
+{
+    violations += is_pending(p);
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t)
+{
+    if (hipError_t e = call("hipMemcpyAsync")) return e;
+    memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t)
+{
+    if (hipError_t e = call("hipStreamSynchronize")) return e;
+    done_up_to(seq);
+    return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) { *e = reinterpret_cast<hipEvent_t>(new Event); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { delete reinterpret_cast<Event*>(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t)
+{
+    if (hipError_t x = call("hipEventRecord")) return x;
+    reinterpret_cast<Event*>(e)->seq = seq;
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) { done_up_to(reinterpret_cast<Event*>(e)->seq); return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t*) { return hipErrorNotSupported; }
+hipError_t hipGraphInstantiate(hipGraphExec_t*, hipGraph_t, hipGraphNode_t*, char*, size_t) { return hipErrorNotSupported; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+}
+
+namespace tts {
+
+hipError_t launch_encoder(const EncoderPtrs&, int, const PnWindows&, int, const EncStaged& staged, float*, hipStream_t)
+{
+    violations += is_pending(staged.ids);       // the host has written the ids by now
+    pending.push_back({staged.ids, ++seq});     // the first kernel is queued whether or not a later launch fails
+    return call("launch_encoder");
+}
+
+// frame f of a request of n frames: all of its values are 1000 n + f
+hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int, hipStream_t, hipEvent_t*)
+{
+    for (int s = 0; s < cfg.n_blocks; ++s) {
+        if (!d.live[s] || d.done[s]) continue;
+        if (s == freeze_slot && d.t[s] >= freeze_at) {
+            d.failed[s] = d.done[s] = 1;
+            *d.fault = 1;
+            continue;
+        }
+        std::fill_n(d.mel_ring + ((size_t)s * d.max_steps + d.t[s]) * N_MEL, N_MEL, 1000.f * d.n_steps[s] + d.t[s]);
+        if (++d.t[s] >= d.n_steps[s]) d.done[s] = 1;
+    }
+    return hipSuccess;
+}
+hipError_t launch_set_live(const DevPtrs& d, const LiveArgs& a, hipStream_t)
+{
+    for (int s = 0; s < MAX_POOL; ++s) d.live[s] = a.bits[s >> 5] >> (s & 31) & 1;
+    return hipSuccess;
+}
+hipError_t launch_join(const DevPtrs& d, int, int, const JoinArgs& ja, int n, hipStream_t)
+{
+    for (int i = 0; i < n; ++i) {
+        const int s = ja.slot[i];
+        d.L[s] = ja.L[i];
+        d.n_steps[s] = ja.n_steps[i];
+        d.t[s] = d.done[s] = d.failed[s] = 0;
+        std::fill_n(d.mel_ring + (size_t)s * d.max_steps * N_MEL, (size_t)d.max_steps * N_MEL, -1.f);   // frames never made
+    }
+    return hipSuccess;
+}
+hipError_t launch_stage_chunks(const DevPtrs& d, const StageArgs& sa, int n, int, float* dst, hipStream_t)
+{
+    if (hipError_t e = call("launch_stage_chunks")) return e;
+    for (int i = 0; i < n; ++i)
+        memcpy(dst + (size_t)sa.to[i] * N_MEL, d.mel_ring + (size_t)sa.row[i] * N_MEL, (size_t)sa.frames[i] * N_MEL * 4);
+    return hipSuccess;
+}
+hipError_t launch_move_slots(const DevPtrs&, int, int, const MoveArgs&, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_presum_tile(const DevPtrs&, int, int, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_prenet_slot(const DevPtrs&, int, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_x_get(int, const void*, int, int, int, int, float*, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_x_set(int, void*, int, int, int, int, const float*, hipStream_t) { return hipErrorNotSupported; }
+
+}  // namespace tts

@@ -1,0 +1,131 @@
+"""Error paths of the library's host code, on the CPU: tts_pool.cpp and encoder.cpp compiled against a HIP runtime on host
+memory (fake_hip.cpp) in which any call can be made to fail."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2211_13939_amd import binding, synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+N_MEL = synth.DIMS["n_mel"]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake") / "libfake.so")
+    csrc = os.path.join(ROOT, "paper_2211_13939_amd", "csrc")
+    # -Bsymbolic: the HIP runtime of this process is not in the way
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-Wno-unused-result", os.path.join(ROOT, "tests", "fake_hip.cpp"), os.path.join(csrc, "tts_pool.cpp"),
+                    os.path.join(csrc, "encoder.cpp"), "-o", out], check=True)
+    L = C.CDLL(out)
+    for f in ("tts_pool_workspace_bytes", "tts_encoder_workspace_bytes"):
+        getattr(L, f).restype = C.c_size_t
+    L.tts_last_error.restype = C.c_char_p
+    for f in ("tts_pool_destroy", "tts_encoder_destroy"):
+        getattr(L, f).restype = None
+        getattr(L, f).argtypes = [C.c_void_p]
+    L.fake_fail.argtypes = [C.c_char_p, C.c_int, C.c_int]
+    L.fake_calls.argtypes = [C.c_char_p]
+    return L
+
+
+@pytest.fixture(autouse=True)
+def _reset(lib):
+    lib.fake_reset()
+
+
+def _arena(nbytes):
+    raw = np.zeros(nbytes + 256, np.uint8)
+    return raw, C.c_void_p(raw.ctypes.data + (-raw.ctypes.data) % 256)
+
+
+class FakePool:
+    def __init__(self, lib, weights, max_pool=4, max_steps=64, chunk=8):
+        self.L, self.chunk = lib, chunk
+        cfg = binding.make_config(synth.DIMS, max_pool=max_pool, max_enc_len=16, max_steps=max_steps, chunk_frames=chunk, use_graph=False)
+        n = int(lib.tts_pool_workspace_bytes(C.byref(cfg)))
+        self._arena, at = _arena(n)
+        w = binding.TtsWeights(*[weights[k].ctypes.data_as(C.POINTER(C.c_float)) for k in binding.WEIGHT_FIELDS])
+        self.h = C.c_void_p()
+        assert lib.tts_pool_create(C.byref(cfg), C.byref(w), at, C.c_size_t(n), C.c_void_p(1), C.byref(self.h)) == 0, lib.tts_last_error()
+
+    def add(self, n_steps):
+        enc, rid = np.zeros((3, synth.DIMS["enc_dim"]), np.float32), C.c_int64()
+        assert self.L.tts_pool_add_request(self.h, enc.ctypes.data_as(C.c_void_p), 3, n_steps, C.byref(rid)) == 0
+        return rid.value
+
+    def step_n(self, n):
+        assert self.L.tts_pool_step_n(self.h, n, None) == 0
+
+    def drain(self, rid):
+        """(status, first value of every frame, finished)"""
+        buf, n, fin = np.full((self.chunk, N_MEL), np.nan, np.float32), C.c_int(-1), C.c_int(-1)
+        rc = self.L.tts_pool_drain_chunk(self.h, C.c_int64(rid), buf.ctypes.data_as(C.c_void_p), C.byref(n), C.byref(fin))
+        if rc:
+            return rc, None, None
+        got = buf[:n.value]
+        assert (got == got[:, :1]).all()
+        return rc, got[:, 0].tolist(), bool(fin.value)
+
+    def close(self):
+        self.L.tts_pool_destroy(self.h)
+
+
+def _frames(n_steps, first, count):
+    return [1000.0 * n_steps + f for f in range(first, first + count)]
+
+
+class FakeEncoder:
+    def __init__(self, lib):
+        self.L = lib
+        cfg = binding.make_encoder_config(max_tokens=64, max_len=64)
+        w = binding.TtsEncoderWeights()
+        src = synth.make_encoder_weights()
+        keep = self._keep = []
+
+        def ptr(a):
+            keep.append(np.ascontiguousarray(a, np.float32))
+            return keep[-1].ctypes.data_as(C.POINTER(C.c_float))
+
+        for t in range(4):
+            w.tables[t] = ptr(src["tables"][t])
+        for i in range(3):
+            w.conv_w[i], w.conv_b[i] = ptr(src["conv_w"][i]), ptr(src["conv_b"][i])
+        for d, k in enumerate("fb"):
+            w.w_ih[d], w.w_hh[d], w.b[d] = ptr(src["w_ih_" + k]), ptr(src["w_hh_" + k]), ptr(src["b_" + k])
+        n = int(lib.tts_encoder_workspace_bytes(C.byref(cfg)))
+        self._arena, at = _arena(n)
+        self.h = C.c_void_p()
+        assert lib.tts_encoder_create(C.byref(cfg), C.byref(w), at, C.c_size_t(n), C.c_void_p(1), C.byref(self.h)) == 0, lib.tts_last_error()
+
+    def run(self):
+        ids, lens = synth.encoder_ids(7, 1).astype(np.int32), np.array([7], np.int32)
+        out = np.zeros((7, 512), np.float32)
+        return self.L.tts_encoder_run(self.h, ids.ctypes.data_as(C.POINTER(C.c_int)), lens.ctypes.data_as(C.POINTER(C.c_int)), 1,
+                                      out.ctypes.data_as(C.c_void_p))
+
+    def close(self):
+        self.L.tts_encoder_destroy(self.h)
+
+
+@pytest.mark.parametrize("before", [0, 1, 2, 3])
+@pytest.mark.parametrize("what,nth", [("launch_encoder", 1), ("hipEventRecord", 2)])
+def test_encoder_call_that_fails_on_the_way_is_through_with_its_ids(lib, before, what, nth):
+    """A call whose launches fail after the first kernel has been queued: that kernel still reads the ids in pinned memory, which
+    neither the next call may rewrite nor the end of the encoder free before the stream has got there."""
+    enc = FakeEncoder(lib)
+    for _ in range(before):
+        assert enc.run() == 0
+    lib.fake_fail(what.encode(), nth, 1)
+    assert enc.run() == binding.TTS_E_HIP
+    for _ in range(3):
+        assert enc.run() == 0
+    assert lib.fake_violations() == 0
+    lib.fake_fail(what.encode(), nth, 1)
+    assert enc.run() == binding.TTS_E_HIP
+    enc.close()
+    assert lib.fake_violations() == 0
