@@ -856,6 +856,11 @@ static const float* find_staged(const tts_pool* p, int slot, int first, int coun
     return st.id == p->book->slot(slot).id && st.first == first && st.count == count ? p->h_stage + (size_t)slot * p->stage_frames * N_MEL : nullptr;
 }
 
+static void forget_staged(tts_pool* p)
+{
+    for (tts_pool::Staged& st : p->staged) st.id = -1;
+}
+
 // Copies the chunk of `slot` to the staging buffer, and with it (a region per slot) every other chunk that the next drains
 // could hand out and that is not there yet; waits for the stream.
 static int stage_chunks(tts_pool* p, int slot)
@@ -883,7 +888,7 @@ static int stage_chunks(tts_pool* p, int slot)
     hipError_t e = launch_stage_chunks(p->d, sa, n, most, p->d_stage, p->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
     if (e == hipSuccess) return TTS_OK;
-    for (tts_pool::Staged& st : p->staged) st.id = -1;
+    forget_staged(p);
     return fail(TTS_E_HIP, "copying chunks to the host: %s", hipGetErrorString(e));
 }
 
@@ -903,7 +908,10 @@ extern "C" int tts_pool_drain_chunk(tts_pool* p, int64_t id, float* dst, int* ou
             if (*p->h_fault) {
                 // some request was frozen since the last look: if it is this one, the plan above counted frames that were
                 // never made; plan again from what the device holds (the copy is then repeated for the right range)
-                if ((rc = absorb_failures(p))) return rc;
+                if ((rc = absorb_failures(p))) {
+                    forget_staged(p);        // any of the chunks may hold frames that were never made
+                    return rc;
+                }
                 p->book->drain_plan(slot, &first, &count, &fin);
                 if (count > 0 && (p->stage_regions == 1 || !find_staged(p, slot, first, count)))
                     if ((rc = stage_chunks(p, slot))) return rc;

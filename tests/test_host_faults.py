@@ -129,3 +129,21 @@ def test_encoder_call_that_fails_on_the_way_is_through_with_its_ids(lib, before,
     assert enc.run() == binding.TTS_E_HIP
     enc.close()
     assert lib.fake_violations() == 0
+
+
+def test_drain_whose_bookkeeping_fails_leaves_no_chunk_behind_that_was_never_made(lib, weights_fp32):
+    """Slot 1 is frozen after 5 frames of a step call of 8.  The drain of request 0 brings both chunks to the host, sees the
+    fault and fails to read what the device lost: request 1's chunk of 8 frames, 3 of them never made, must not be handed out."""
+    pool = FakePool(lib, weights_fp32)
+    a, b = pool.add(24), pool.add(23)
+    lib.fake_freeze(1, 5)
+    pool.step_n(8)
+    lib.fake_fail(b"hipMemcpyAsync", 1, 1)
+    assert pool.drain(a)[0] == binding.TTS_E_HIP
+    assert pool.drain(b) == (0, _frames(23, 0, 5), True)
+    assert pool.drain(a) == (0, _frames(24, 0, 8), False)
+    pool.step_n(16)
+    assert pool.drain(a) == (0, _frames(24, 8, 8), False)
+    assert pool.drain(a) == (0, _frames(24, 16, 8), True)
+    assert pool.drain(b) == (0, [], True)
+    pool.close()
