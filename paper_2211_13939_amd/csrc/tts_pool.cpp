@@ -253,7 +253,8 @@ struct tts_pool {
     // Pinned staging of chunks on their way to the caller's (pageable) buffers.  The first drain after some steps copies every
     // chunk that is ready, one launch and one wait for all of them; the drains that follow find theirs here.  stage_regions
     // regions of stage_frames frames: one per slot, or a single one where chunks are so long that this would be more than
-    // STAGE_BYTES (then each drain copies its own).
+    // STAGE_BYTES, or where so much pinned memory cannot be had (then each drain copies its own); none where there is no pinned
+    // memory at all (then each drain copies straight to the caller's buffer).
     float* h_stage = nullptr;
     float* d_stage = nullptr;     // its device address
     int stage_regions = 0, stage_frames = 0;
@@ -432,13 +433,18 @@ extern "C" int tts_pool_create(const tts_config* cfg, const tts_weights* w, void
     {
         p->stage_frames = std::min(cfg->chunk_frames, cfg->max_steps);
         const size_t region = (size_t)p->stage_frames * N_MEL * 4;
-        p->stage_regions = region * cfg->max_pool <= STAGE_BYTES ? cfg->max_pool : 1;
-        hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&p->h_stage), region * p->stage_regions, hipHostMallocMapped);
-        if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&p->d_stage), p->h_stage, 0);
-        if (e != hipSuccess) {
-            const int rc0 = fail(TTS_E_HIP, "pinned staging buffer: %s", hipGetErrorString(e));
-            tts_pool_destroy(p);
-            return rc0;
+        for (int regions : {region * cfg->max_pool <= STAGE_BYTES ? cfg->max_pool : 1, 1}) {
+            hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&p->h_stage), region * regions, hipHostMallocMapped);
+            if (e == hipSuccess) {
+                e = hipHostGetDevicePointer(reinterpret_cast<void**>(&p->d_stage), p->h_stage, 0);
+                if (e != hipSuccess) (void)hipHostFree(p->h_stage);
+            }
+            if (e == hipSuccess) {
+                p->stage_regions = regions;
+                break;
+            }
+            (void)hipGetLastError();
+            p->h_stage = nullptr;
         }
         p->staged.resize(p->stage_regions);
     }
@@ -892,6 +898,21 @@ static int stage_chunks(tts_pool* p, int slot)
     return fail(TTS_E_HIP, "copying chunks to the host: %s", hipGetErrorString(e));
 }
 
+// Brings the planned chunk of `slot` to the host: *at = where it lies in the staging buffer, or `dst` itself where there is
+// none; waits for the stream.
+static int bring_chunk(tts_pool* p, int slot, int first, int count, float* dst, const float** at)
+{
+    if (p->h_stage) {
+        *at = p->h_stage + (size_t)(p->stage_regions > 1 ? slot : 0) * p->stage_frames * N_MEL;
+        return stage_chunks(p, slot);
+    }
+    *at = dst;
+    const float* src = p->d.mel_ring + ((size_t)slot * p->cfg.max_steps + first) * N_MEL;
+    HIP_TRY(hipMemcpyAsync(dst, src, (size_t)count * N_MEL * 4, hipMemcpyDeviceToHost, p->stream));
+    HIP_TRY(hipStreamSynchronize(p->stream));
+    return TTS_OK;
+}
+
 extern "C" int tts_pool_drain_chunk(tts_pool* p, int64_t id, float* dst, int* out_frames, int* out_finished)
 {
     if (!p || !dst || !out_frames || !out_finished) return fail(TTS_E_INVAL, "null argument");
@@ -902,9 +923,9 @@ extern "C" int tts_pool_drain_chunk(tts_pool* p, int64_t id, float* dst, int* ou
     int first, count, fin;
     p->book->drain_plan(slot, &first, &count, &fin);
     if (count > 0) {
-        const float* from = find_staged(p, slot, first, count);
-        if (!from) {
-            if ((rc = stage_chunks(p, slot))) return rc;
+        const float* at = find_staged(p, slot, first, count);
+        if (!at) {
+            if ((rc = bring_chunk(p, slot, first, count, dst, &at))) return rc;
             if (*p->h_fault) {
                 // some request was frozen since the last look: if it is this one, the plan above counted frames that were
                 // never made; plan again from what the device holds (the copy is then repeated for the right range)
@@ -913,12 +934,11 @@ extern "C" int tts_pool_drain_chunk(tts_pool* p, int64_t id, float* dst, int* ou
                     return rc;
                 }
                 p->book->drain_plan(slot, &first, &count, &fin);
-                if (count > 0 && (p->stage_regions == 1 || !find_staged(p, slot, first, count)))
-                    if ((rc = stage_chunks(p, slot))) return rc;
+                if (count > 0 && !(at = find_staged(p, slot, first, count)))
+                    if ((rc = bring_chunk(p, slot, first, count, dst, &at))) return rc;
             }
-            from = p->h_stage + (size_t)(p->stage_regions > 1 ? slot : 0) * p->stage_frames * N_MEL;
         }
-        if (count > 0) memcpy(dst, from, (size_t)count * N_MEL * 4);
+        if (count > 0 && at != dst) memcpy(dst, at, (size_t)count * N_MEL * 4);
         p->book->drain_commit(slot, count);
     }
     *out_frames = count;

@@ -147,3 +147,25 @@ def test_drain_whose_bookkeeping_fails_leaves_no_chunk_behind_that_was_never_mad
     assert pool.drain(a) == (0, _frames(24, 16, 8), True)
     assert pool.drain(b) == (0, [], True)
     pool.close()
+
+
+@pytest.mark.parametrize("times", [1, 2])
+def test_pool_without_pinned_memory_for_its_chunks(lib, weights_fp32, times):
+    """Where the pinned staging buffer cannot be had (the second pinned allocation; the first is the status word), the pool makes
+    do with less of it, or none: it is created, and its drains hand out the same frames."""
+    lib.fake_fail(b"hipHostMalloc", 2, times)
+    pool = FakePool(lib, weights_fp32)
+    a, b = pool.add(20), pool.add(11)
+    pool.step_n(8)
+    assert pool.drain(a) == (0, _frames(20, 0, 8), False)
+    assert pool.drain(a) == (0, [], False)
+    pool.step_n(12)
+    assert pool.drain(b) == (0, _frames(11, 0, 8), False)
+    assert pool.drain(a) == (0, _frames(20, 8, 8), False)
+    assert pool.drain(b) == (0, _frames(11, 8, 3), True)
+    assert pool.drain(a) == (0, _frames(20, 16, 4), True)
+    c = pool.add(24)
+    lib.fake_freeze(2, 5)
+    pool.step_n(8)
+    assert pool.drain(c) == (0, _frames(24, 0, 5), True)
+    pool.close()
