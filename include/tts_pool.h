@@ -160,9 +160,9 @@ int tts_pool_step_n(tts_pool *pool, int n, int64_t *out_frames);
  * `dst` [chunk_frames, n_mel] fp32.  If fewer than chunk_frames undrained
  * frames exist and the request is unfinished, *out_frames = 0 and TTS_OK.  The
  * last chunk of a finished request may be short.  *out_finished = 1 once the
- * request is finished AND everything has been drained.  Waits for the stream,
- * unless an earlier drain has brought this chunk to the host already: a drain
- * copies every chunk that is ready to pinned memory, for the drains that follow.
+ * request is finished AND everything has been drained.  Waits for the stream
+ * (a drain brings every chunk that is ready to pinned memory with one launch,
+ * for the drains that follow).
  * A request the device ended early (tts_pool_sync, tts_pool_lost) hands out the frames it has like any finished one.
  */
 int tts_pool_drain_chunk(tts_pool *pool, int64_t id, float *dst, int *out_frames, int *out_finished);

@@ -169,3 +169,24 @@ def test_pool_without_pinned_memory_for_its_chunks(lib, weights_fp32, times):
     pool.step_n(8)
     assert pool.drain(c) == (0, _frames(24, 0, 5), True)
     pool.close()
+
+
+def test_every_drain_that_hands_out_frames_waits_for_the_stream(lib, weights_fp32):
+    """A caller may take a drain that handed out frames for a wait, also when an earlier drain had brought the chunk along; and a
+    request that further steps have frozen meanwhile is reported as finished by that drain already."""
+    pool = FakePool(lib, weights_fp32)
+    a, b = pool.add(24), pool.add(23)
+    pool.step_n(8)
+    for rid in (a, b):
+        before = lib.fake_calls(b"hipStreamSynchronize")
+        assert pool.drain(rid)[1] == _frames(24 if rid == a else 23, 0, 8)
+        assert lib.fake_calls(b"hipStreamSynchronize") > before
+    pool.step_n(8)
+    assert pool.drain(a) == (0, _frames(24, 8, 8), False)         # brings b's frames 8 .. 15 along
+    lib.fake_freeze(1, 16)
+    pool.step_n(8)
+    assert pool.drain(b) == (0, _frames(23, 8, 8), True)
+    lib.fake_fail(b"hipStreamSynchronize", 1, 1)
+    assert pool.drain(a)[0] == binding.TTS_E_HIP
+    assert pool.drain(a) == (0, _frames(24, 16, 8), True)
+    pool.close()
