@@ -2308,13 +2308,14 @@ __global__ __launch_bounds__(256) void k_prenet_slot(DevPtrs d, int slot)
     for (int b = 0; b < 2; ++b) reinterpret_cast<XT*>(d.xatt[b])[xoff<XT>(K_ATT / KB, slot, XA_P + o)] = p;
 }
 
-// Chunks from the mel ring straight into pinned host memory, all that are ready in one launch: grid = (chunks, pieces of 256
-// 16-byte words).  Bound by the host link.  One copy and one wait per chunk cost 15 - 18 us each, 64 chunks 1.1 ms beside
-// 0.9 ms of decoder steps; one launch for the 64 takes about 25 us.
+// Chunks from the mel ring straight into pinned host memory, all that are ready in one launch: grid = (pieces of 256 16-byte
+// words, chunks); the pieces come first because a chunk of the longest utterance (2^20 frames) has more of them than a grid may
+// have rows.  Bound by the host link.  One copy and one wait per chunk cost 15 - 18 us each, 64 chunks 1.1 ms beside 0.9 ms of
+// decoder steps; one launch for the 64 takes about 25 us.
 __global__ __launch_bounds__(256) void k_stage_chunks(StageArgs a, const floatx4* __restrict__ ring, floatx4* __restrict__ dst)
 {
     constexpr int VEC = N_MEL / 4;
-    const int i = blockIdx.x, e = blockIdx.y * 256 + threadIdx.x;
+    const int i = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
     if (e < a.frames[i] * VEC) __builtin_nontemporal_store(ring[(size_t)a.row[i] * VEC + e], dst + (size_t)a.to[i] * VEC + e);
 }
 
@@ -2681,7 +2682,7 @@ hipError_t launch_set_live(const DevPtrs& d, const LiveArgs& args, hipStream_t s
 hipError_t launch_stage_chunks(const DevPtrs& d, const StageArgs& sa, int n, int most_frames, float* dst, hipStream_t s)
 {
     if (n < 1 || n > MAX_POOL || most_frames < 1 || !dst) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_stage_chunks, dim3(n, (most_frames * (N_MEL / 4) + 255) / 256), dim3(256), 0, s, sa,
+    hipLaunchKernelGGL(k_stage_chunks, dim3((most_frames * (N_MEL / 4) + 255) / 256, n), dim3(256), 0, s, sa,
                        reinterpret_cast<const floatx4*>(d.mel_ring), reinterpret_cast<floatx4*>(dst));
     return hipGetLastError();
 }
