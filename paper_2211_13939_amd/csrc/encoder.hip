@@ -91,8 +91,8 @@ __global__ __launch_bounds__(256) void k_enc_xproj(const uint4* __restrict__ W0,
 // (0.70 us a step); 16 requests of 30 .. 300 tokens 419 -> 207 us.  With the instructions scheduled by the compiler: 165 us.
 // grid = (2 directions, requests), 256 threads.
 constexpr int ENC_SP_THREADS = 256;
-constexpr int ENC_SP_LDS_TILES = 3;                                        // of a group's four tiles, those whose last piece lives in LDS
-constexpr int ENC_SP_W_VECS = 4 * 4 * ENC_SP_LDS_TILES * 2 * 64;           // waves x groups x tiles x 2 x lanes
+constexpr int ENC_SP_LDS_TILES = 3;                                        // of a group's sixteen fragments, those that live in LDS
+constexpr int ENC_SP_W_VECS = 4 * 4 * ENC_SP_LDS_TILES * 2 * 64;           // waves x groups x fragments x 2 x lanes
 constexpr int ENC_SP_LDS_BYTES = ENC_SP_W_VECS * 16 + 2 * ENC_HID * 2;
 constexpr int ENC_SP_AHEAD = 2;                                            // steps between the request for an input projection and its use
 
@@ -102,20 +102,26 @@ constexpr int ENC_SP_AHEAD = 2;                                            // st
 //   * the groups use two sets of accumulators in turn (v[224:239], v[240:255]); a group adds up the previous group's sums and
 //     clears them between its own instructions, while the vector units have nothing else to do (two of a lane's four rows
 //     are enough: the other two repeat them and are never read);
-//   * one piece of three of a group's tiles lives in LDS, at different places of the run; each is requested a whole group
-//     (256 cycles) before its use, into the registers (v[200:223]) its predecessor has just left; h arrives piece by piece.
-// The hardware does not check these distances: a sum is read at least 7 wait states (4 passes + 3) after the instruction that
-// completed it - four others of 4 passes each lie between, at the end the s_nops -, and an operand of a matrix instruction
-// is written at least two wait states before.  LDS returns in order: the counts are those of the reads issued since.
+//   * three of a group's sixteen fragments live in LDS; each is requested some thirteen matrix instructions (208 cycles) before
+//     its use, into the registers (v[200:223]) its predecessor has just left.  In the later groups they come earlier
+//     (enc_sp_piece), so that the last request of a step, for the next step's first group, is seven instructions from the
+//     step's end; h arrives piece by piece.
+// The hardware does not check these distances: a sum is read at least 8 wait states (gfx950: 4 passes + 4; every instruction
+// in between counted as one) after the instruction that completed it, and an operand of a matrix instruction is written at
+// least two wait states before.  LDS returns in order: the counts are those of the reads issued since.  Every read is waited
+// for inside the run: the compiler takes its outputs as written, and may copy or spill them behind it.
 #define SP_STR2(x) #x
 #define SP_STR(x) SP_STR2(x)
 #define SP_MM(acc, f, w) "v_smfmac_f32_16x16x64_f16 " acc ", %[h" #f "], " w ", %[ix]\n\t"
 #define SP_I(U, g, f, acc) SP_MM(acc, f, "%[w" #U #f #g "]")
 #define SP_WAIT(n) "s_waitcnt lgkmcnt(" #n ")\n\t"
 #define SP_READ(lo, hi, next, g) "ds_read_b128 " lo ", %[la] offset:(" #next "*3+" #g ")*2048\n\tds_read_b128 " hi ", %[la] offset:(" #next "*3+" #g ")*2048+1024\n\t"
-#define SP_L0(next, acc, wait) wait SP_MM(acc, 1, "v[200:207]") SP_READ("v[200:203]", "v[204:207]", next, 0)
-#define SP_L1(next, acc, wait) wait SP_MM(acc, 2, "v[208:215]") SP_READ("v[208:211]", "v[212:215]", next, 1)
-#define SP_L2(next, acc, wait) wait SP_MM(acc, 3, "v[216:223]") SP_READ("v[216:219]", "v[220:223]", next, 2)
+// one instruction of group U, k piece f, gate g: weights in registers (R) or the LDS-resident piece 0, 1, 2 (L0, L1, L2), whose
+// successor, group N's, is requested behind it
+#define SP_DO_R(U, N, f, g, acc, wait) SP_I(U, g, f, acc)
+#define SP_DO_L0(U, N, f, g, acc, wait) wait SP_MM(acc, f, "v[200:207]") SP_READ("v[200:203]", "v[204:207]", N, 0)
+#define SP_DO_L1(U, N, f, g, acc, wait) wait SP_MM(acc, f, "v[208:215]") SP_READ("v[208:211]", "v[212:215]", N, 1)
+#define SP_DO_L2(U, N, f, g, acc, wait) wait SP_MM(acc, f, "v[216:223]") SP_READ("v[216:219]", "v[220:223]", N, 2)
 #define SP_P0 "v[224:227]"
 #define SP_P1 "v[228:231]"
 #define SP_P2 "v[232:235]"
@@ -147,27 +153,48 @@ constexpr int ENC_SP_AHEAD = 2;                                            // st
 #define SP_CLEAR_Q2 SP_CLEAR(248, 249)
 #define SP_CLEAR_Q3 SP_CLEAR(252, 253)
 // U: group, N: the group behind it, C: its accumulators (P or Q), O: the previous group's, TAKE, m: how the previous group's
-// sums are taken; W0 .. W3: waits for the pieces of h, WL: wait for a piece of the LDS-resident weights
-#define SP_GROUP(U, N, C, O, TAKE, m, W0, W1, W2, W3, WL)                                                                                \
-    W0 SP_I(U, 0, 0, SP_##C##0) SP_I(U, 1, 0, SP_##C##1) SP_I(U, 2, 0, SP_##C##2) SP_I(U, 3, 0, SP_##C##3)                               \
-    W1 SP_L0(N, SP_##C##0, WL) TAKE##0(m) SP_I(U, 1, 1, SP_##C##1) TAKE##1(m) SP_I(U, 2, 1, SP_##C##2) TAKE##2(m)                        \
-    SP_I(U, 3, 1, SP_##C##3) TAKE##3(m)                                                                                                  \
-    W2 SP_I(U, 0, 2, SP_##C##0) SP_CLEAR_##O##0 SP_L1(N, SP_##C##1, WL) SP_CLEAR_##O##1 SP_I(U, 2, 2, SP_##C##2) SP_CLEAR_##O##2          \
-    SP_I(U, 3, 2, SP_##C##3) SP_CLEAR_##O##3                                                                                             \
-    W3 SP_I(U, 0, 3, SP_##C##0) SP_I(U, 1, 3, SP_##C##1) SP_L2(N, SP_##C##2, WL) SP_I(U, 3, 3, SP_##C##3)
+// sums are taken; W0 .. W3: waits for the pieces of h, WL: wait for an LDS-resident piece; Xfg: where the weights of k piece f,
+// gate g are
+#define SP_GROUP(U, N, C, O, TAKE, m, W0, W1, W2, W3, WL, X00, X01, X02, X03, X10, X11, X12, X13, X20, X21, X22, X23, X30, X31, X32, X33) \
+    W0 SP_DO_##X00(U, N, 0, 0, SP_##C##0, WL) SP_DO_##X01(U, N, 0, 1, SP_##C##1, WL) SP_DO_##X02(U, N, 0, 2, SP_##C##2, WL)              \
+    SP_DO_##X03(U, N, 0, 3, SP_##C##3, WL)                                                                                               \
+    W1 SP_DO_##X10(U, N, 1, 0, SP_##C##0, WL) TAKE##0(m) SP_DO_##X11(U, N, 1, 1, SP_##C##1, WL) TAKE##1(m)                               \
+    SP_DO_##X12(U, N, 1, 2, SP_##C##2, WL) TAKE##2(m) SP_DO_##X13(U, N, 1, 3, SP_##C##3, WL) TAKE##3(m)                                  \
+    W2 SP_DO_##X20(U, N, 2, 0, SP_##C##0, WL) SP_CLEAR_##O##0 SP_DO_##X21(U, N, 2, 1, SP_##C##1, WL) SP_CLEAR_##O##1                     \
+    SP_DO_##X22(U, N, 2, 2, SP_##C##2, WL) SP_CLEAR_##O##2 SP_DO_##X23(U, N, 2, 3, SP_##C##3, WL) SP_CLEAR_##O##3                        \
+    W3 SP_DO_##X30(U, N, 3, 0, SP_##C##0, WL) SP_DO_##X31(U, N, 3, 1, SP_##C##1, WL) SP_DO_##X32(U, N, 3, 2, SP_##C##2, WL)              \
+    SP_DO_##X33(U, N, 3, 3, SP_##C##3, WL)
 #define SP_STEP(hoff)                                                                                                                    \
+    SP_WAIT(0)                                                                                                                           \
     "ds_read_b128 %[h0], %[ha] offset:" SP_STR(hoff) "\n\tds_read_b128 %[h1], %[ha] offset:" SP_STR(hoff) "+128\n\t"                    \
     "ds_read_b128 %[h2], %[ha] offset:" SP_STR(hoff) "+256\n\tds_read_b128 %[h3], %[ha] offset:" SP_STR(hoff) "+384\n\t"                \
-    SP_GROUP(0, 1, P, Q, SP_NO_TAKE, "", SP_WAIT(3), SP_WAIT(2), SP_WAIT(3), SP_WAIT(4), )                                                \
-    SP_GROUP(1, 2, Q, P, SP_TAKE_P, "m0", , , , , SP_WAIT(4))                                                                            \
-    SP_GROUP(2, 3, P, Q, SP_TAKE_Q, "m1", , , , , SP_WAIT(4))                                                                            \
-    SP_GROUP(3, 0, Q, P, SP_TAKE_P, "m2", , , , , SP_WAIT(4))                                                                            \
-    SP_TAKE_Q0("m3") SP_TAKE_Q1("m3") "s_nop 1\n\t" SP_TAKE_Q2("m3") "s_nop 3\n\t" SP_TAKE_Q3("m3")
+    SP_GROUP(0, 1, P, Q, SP_NO_TAKE, "", SP_WAIT(3), SP_WAIT(2), SP_WAIT(3), SP_WAIT(4), , R, R, R, R, L0, R, R, R, R, L1, R, R, R, R, L2, R) \
+    SP_GROUP(1, 2, Q, P, SP_TAKE_P, "m0", , , , , SP_WAIT(4), R, R, R, R, L0, R, R, R, R, L1, R, R, R, R, L2, R)                          \
+    SP_GROUP(2, 3, P, Q, SP_TAKE_Q, "m1", , , , , SP_WAIT(4), R, R, L0, R, R, R, R, L1, R, R, R, L2, R, R, R, R)                          \
+    SP_GROUP(3, 0, Q, P, SP_TAKE_P, "m2", , , , , SP_WAIT(4), L0, R, R, R, L1, R, R, R, L2, R, R, R, R, R, R, R)                          \
+    "s_nop 4\n\t" SP_TAKE_Q0("m3") SP_TAKE_Q1("m3") SP_TAKE_Q2("m3") SP_TAKE_Q3("m3") SP_WAIT(0)
+// the LDS-resident pieces, as the groups above have them: the number of k piece f of gate g in group U, or -1
+__device__ constexpr int enc_sp_piece(int U, int f, int g)
+{
+    constexpr int at[4][ENC_SP_LDS_TILES] = {{4, 9, 14}, {4, 9, 14}, {2, 7, 11}, {0, 4, 8}};      // 4 f + g
+    for (int i = 0; i < ENC_SP_LDS_TILES; ++i)
+        if (at[U][i] == 4 * f + g) return i;
+    return -1;
+}
+// register operands: %[wUfg] = k piece f of gate g in group U; the first 32 fragments in the accumulation half of the file
 #define SP_W(c, U, f, g) [w##U##f##g] c(wr[U][f][g])
-#define SP_WROW(c, U, f) SP_W(c, U, f, 0), SP_W(c, U, f, 1), SP_W(c, U, f, 2), SP_W(c, U, f, 3)
-#define SP_WGROUP(c, U)                                                                                                                  \
-    SP_WROW(c, U, 0), SP_W(c, U, 1, 1), SP_W(c, U, 1, 2), SP_W(c, U, 1, 3), SP_W(c, U, 2, 0), SP_W(c, U, 2, 2), SP_W(c, U, 2, 3),           \
-        SP_W(c, U, 3, 0), SP_W(c, U, 3, 1), SP_W(c, U, 3, 3)
+#define SP_WGROUP01(U)                                                                                                                   \
+    SP_W("a", U, 0, 0), SP_W("a", U, 0, 1), SP_W("a", U, 0, 2), SP_W("a", U, 0, 3), SP_W("a", U, 1, 1), SP_W("a", U, 1, 2),               \
+        SP_W("a", U, 1, 3), SP_W("a", U, 2, 0), SP_W("a", U, 2, 2), SP_W("a", U, 2, 3), SP_W("a", U, 3, 0), SP_W("a", U, 3, 1),           \
+        SP_W("a", U, 3, 3)
+#define SP_WGROUP2                                                                                                                       \
+    SP_W("a", 2, 0, 0), SP_W("a", 2, 0, 1), SP_W("a", 2, 0, 3), SP_W("a", 2, 1, 0), SP_W("a", 2, 1, 1), SP_W("a", 2, 1, 2),               \
+        SP_W("v", 2, 2, 0), SP_W("v", 2, 2, 1), SP_W("v", 2, 2, 2), SP_W("v", 2, 3, 0), SP_W("v", 2, 3, 1), SP_W("v", 2, 3, 2),           \
+        SP_W("v", 2, 3, 3)
+#define SP_WGROUP3                                                                                                                       \
+    SP_W("v", 3, 0, 1), SP_W("v", 3, 0, 2), SP_W("v", 3, 0, 3), SP_W("v", 3, 1, 1), SP_W("v", 3, 1, 2), SP_W("v", 3, 1, 3),               \
+        SP_W("v", 3, 2, 1), SP_W("v", 3, 2, 2), SP_W("v", 3, 2, 3), SP_W("v", 3, 3, 0), SP_W("v", 3, 3, 1), SP_W("v", 3, 3, 2),           \
+        SP_W("v", 3, 3, 3)
 #define SP_RUN(hoff)                                                                                                                     \
     asm volatile(SP_STEP(hoff)                                                                                                           \
                  : [h0] "=&v"(hv[0]), [h1] "=&v"(hv[1]), [h2] "=&v"(hv[2]), [h3] "=&v"(hv[3]), [s0] "+v"(gs[0]), [s1] "+v"(gs[1]),         \
@@ -176,9 +203,7 @@ constexpr int ENC_SP_AHEAD = 2;                                            // st
                    "+{v[236:239]}"(accp[3]), "+{v[240:243]}"(accq[0]), "+{v[244:247]}"(accq[1]), "+{v[248:251]}"(accq[2]),                \
                    "+{v[252:255]}"(accq[3])                                                                                               \
                  : [ha] "v"(h_at), [la] "v"(w_at), [ix] "v"(idx), [m0] "s"(lanes_of(0)), [m1] "s"(lanes_of(1)), [m2] "s"(lanes_of(2)),     \
-                   [m3] "s"(lanes_of(3)), SP_WGROUP("a", 0), SP_WGROUP("a", 1), SP_WROW("a", 2, 0), SP_W("a", 2, 1, 1),                  \
-                   SP_W("a", 2, 1, 2), SP_W("v", 2, 1, 3), SP_W("v", 2, 2, 0), SP_W("v", 2, 2, 2), SP_W("v", 2, 2, 3),                     \
-                   SP_W("v", 2, 3, 0), SP_W("v", 2, 3, 1), SP_W("v", 2, 3, 3), SP_WGROUP("v", 3)                                         \
+                   [m3] "s"(lanes_of(3)), SP_WGROUP01(0), SP_WGROUP01(1), SP_WGROUP2, SP_WGROUP3                                          \
                  : "memory")
 
 typedef uint32_t u32x8_t __attribute__((ext_vector_type(8)));
@@ -206,9 +231,10 @@ __global__ __launch_bounds__(ENC_SP_THREADS) void k_enc_lstm_sp(const uint4* __r
             for (int g = 0; g < 4; ++g) {
                 const size_t at = ((size_t)(4 * (4 * wave + U) + g) * NK + 2 * f) * 64;
                 const uint4 lo = Wl[at], hi = Wl[at + 64];
-                if (g < ENC_SP_LDS_TILES && f == g + 1) {        // (the LDS-resident pieces)
-                    wlw[((U * ENC_SP_LDS_TILES + g) * 2) * 64] = lo;
-                    wlw[((U * ENC_SP_LDS_TILES + g) * 2 + 1) * 64] = hi;
+                const int piece = enc_sp_piece(U, f, g);
+                if (piece >= 0) {                                  // (lives in LDS)
+                    wlw[((U * ENC_SP_LDS_TILES + piece) * 2) * 64] = lo;
+                    wlw[((U * ENC_SP_LDS_TILES + piece) * 2 + 1) * 64] = hi;
                 } else {
                     wr[U][f][g] = u32x8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
                 }
@@ -251,8 +277,8 @@ __global__ __launch_bounds__(ENC_SP_THREADS) void k_enc_lstm_sp(const uint4* __r
         for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                if (g >= ENC_SP_LDS_TILES || f != g + 1) {
-                    if (U < 2 || (U == 2 && (f == 0 || (f == 1 && g < 3)))) asm volatile("" : "+a"(wr[U][f][g]));
+                if (enc_sp_piece(U, f, g) < 0) {
+                    if (U < 2 || (U == 2 && f < 2)) asm volatile("" : "+a"(wr[U][f][g]));
                     else asm volatile("" : "+v"(wr[U][f][g]));
                 }
     vm_in_flight_at_most<0>();
