@@ -32,8 +32,8 @@ def test_ragged_batch_matches_oracle(bf16):
 
 @pytest.mark.parametrize("n_tokens", [1, 2, 33, 300])
 def test_a_call_of_one_request_matches_oracle_bf16(n_tokens):
-    """The usual call at join time: one request (in the two-byte mode the recurrence runs on the vector units, a kernel of
-    its own): one token, two tokens and a request that feeds h back 300 times."""
+    """The usual call at join time: one request (one column of a column tile of the convolutions, two workgroups of the
+    recurrence): one token, two tokens and a request that feeds h back 300 times."""
     from oracle import oracle as orc
     w = synth.make_encoder_weights(bf16=True)
     ids = synth.encoder_ids(n_tokens, 500 + n_tokens)
@@ -70,9 +70,9 @@ def test_more_requests_than_mfma_columns_and_long_request():
 @pytest.mark.parametrize("bf16", [True, False])
 def test_result_does_not_depend_on_batch_composition(bf16):
     """Bitwise, among calls that take the same kernels (the convolutions have one kernel for calls below 80 column tiles
-    of tokens - all calls here - and one for larger calls, which differ in summation order only).  In the two-byte mode
-    every request has workgroups of its own in the recurrence; with fp32 weights calls of up to two requests compact the
-    cell update and larger calls do not, again a difference in summation order."""
+    of tokens - all calls here - and one for larger calls, which differ in summation order only).  The recurrence sums in
+    one order whatever the call: with two-byte weights every request has workgroups of its own, with fp32 weights a unit's
+    sum does not depend on how many workgroups share a direction and how many requests share them."""
     w = synth.make_encoder_weights(bf16=bf16)
     ids = [synth.encoder_ids(L, 300 + i) for i, L in enumerate((40, 9, 23, 61, 5, 33))]
     enc = binding.Encoder(binding.make_encoder_config(max_tokens=512, max_len=100, bf16=bf16), w)
@@ -85,10 +85,7 @@ def test_result_does_not_depend_on_batch_composition(bf16):
     four = enc.run([ids[0], ids[1], ids[2], ids[3]])[2]
     np.testing.assert_array_equal(four, enc.run(ids)[2])
     np.testing.assert_array_equal(four, enc.run([ids[2], ids[5], ids[4]])[0])
-    if bf16:
-        np.testing.assert_array_equal(four, alone)
-    else:
-        assert np.abs(four - alone).max() <= 1e-5       # (the two kernels agree to rounding)
+    np.testing.assert_array_equal(four, alone)
     enc.close()
 
 
@@ -193,8 +190,8 @@ def test_serving_loop_with_encoder_at_join_matches_oracle(weights_fp32):
 
 
 def test_largest_batch_and_a_very_long_request():
-    """256 requests in one call (16 groups of MFMA columns per direction) and, in another call, one request of 1000
-    tokens (the recurrence runs 1000 dependent steps), fp32."""
+    """256 requests in one call (eight of them share a group of workgroups of the recurrence) and, in another call, one request
+    of 1000 tokens (the recurrence runs 1000 dependent steps), fp32."""
     from oracle import oracle as orc
     w = synth.make_encoder_weights()
     W = orc.EncoderWeights(w)
@@ -237,7 +234,6 @@ def test_largest_batch_bf16():
     # bit for bit what a smaller call gives that takes the same convolution kernel (from 80 column tiles up)
     np.testing.assert_array_equal(got[200], enc.run(ids[150:])[50])
     enc.close()
-
 
 
 def test_shared_recurrence_fp32():
@@ -288,4 +284,26 @@ def test_shared_recurrence_that_gives_up_on_the_way_fp32(polls):
         say(f"case encoder, fp32: {n} requests, {polls} polls")
         for a, b in zip(want[n], enc.run(ids[:n])):
             np.testing.assert_array_equal(a, b)
+    enc.close()
+
+
+@pytest.mark.parametrize("n,at", [(20, 7), (40, 6), (40, 39), (100, 41), (160, 83), (160, 159)])
+def test_shared_recurrence_of_a_long_request_among_short_ones_fp32(n, at):
+    """A request of 300 tokens whose companions - alone in its group of workgroups (20 requests), or one, three and seven others
+    (40, 100, 160) - end hundreds of steps before it, while the words through which h travels are reused 150 times: the same
+    bits as alone, and the oracle's values."""
+    from oracle import oracle as orc
+    w = synth.make_encoder_weights()
+    lens = [1 + (5 * i) % 8 for i in range(n)]
+    lens[at] = 300
+    assert sum(lens) <= 79 * 16                # (the convolutions' kernel is that of a call of one request)
+    ids = [synth.encoder_ids(L, 2300 + i) for i, L in enumerate(lens)]
+    enc = binding.Encoder(binding.make_encoder_config(max_tokens=1280, max_len=300), w)
+    say(f"case encoder, fp32: request {at} of {n} has 300 tokens, the others up to 8")
+    got = enc.run(ids)
+    for k in sorted({0, at - 1, at, min(at + 1, n - 1), n - 1}):
+        np.testing.assert_array_equal(got[k], enc.run([ids[k]])[0])
+    err = float(np.abs(got[at] - orc.encoder(orc.EncoderWeights(w), ids[at])).max())
+    say(f"  max abs err {err:.3e}")
+    assert err <= TOL_F32
     enc.close()
