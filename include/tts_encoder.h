@@ -20,7 +20,8 @@
  * tts_pool_add_request as a device pointer.  All kernels are queued on the
  * stream given at creation; device memory comes from the caller's arena;
  * nothing is allocated on the device (creation allocates pinned host memory:
- * two buffers through which the ids travel, in turn).  Conventions as in tts_pool.h: 0 on
+ * two buffers through which the ids travel, in turn, 40 bytes a token of
+ * max_tokens in all).  Conventions as in tts_pool.h: 0 on
  * success, negative tts_status otherwise, text in tts_last_error(); one owner
  * thread per object.
  */
@@ -84,7 +85,7 @@ int tts_encoder_run(tts_encoder *enc, const int *ids, const int *lens, int n, fl
 /*
  * With fp32 weights the workgroups of the recurrence hand h to each other and poll for it at most `polls` times (some
  * milliseconds by default); if other work on the GPU keeps one of them from starting for so long, the call's results are
- * formed again without such hand-overs, bit for bit the same, at some forty times the time.  0 is allowed.
+ * formed again without such hand-overs, bit for bit the same, at about twenty times a step's time.  0 is allowed.
  */
 int tts_encoder_set_wait_polls(tts_encoder *enc, int polls);
 

@@ -1,6 +1,6 @@
 // Host side of the tts_encoder C ABI: argument checks, arena carve-up, weight re-layout (LSTM gate rows permuted
-// to unit-major / gate-minor), the per-call request table and the upload of the id sequences.  All arithmetic is
-// in encoder.hip and conv5_kernels.h.
+// to unit-major / gate-minor), the per-call request table and the pinned memory in which a call's id sequences lie for the
+// device.  All arithmetic is in encoder.hip and conv5_kernels.h.
 #include "../../include/tts_encoder.h"
 
 #include <hip/hip_runtime.h>
@@ -199,9 +199,7 @@ extern "C" int tts_encoder_run(tts_encoder* e, const int* ids, const int* lens, 
     for (int i = 0; i < n; ++i) {
         if (lens[i] < 1 || lens[i] > e->cfg.max_len) return fail(TTS_E_INVAL, "request %d has %d tokens, max_len = %d", i, lens[i], e->cfg.max_len);
         w.col0[i] = (int)total;
-        w.row0[i] = (int)total;
         w.len[i] = (uint16_t)lens[i];
-        w.keep[i] = 0;
         total += lens[i];
         if (total > e->cfg.max_tokens) return fail(TTS_E_INVAL, "more than max_tokens = %d tokens in one call", e->cfg.max_tokens);
     }

@@ -88,7 +88,8 @@ __global__ __launch_bounds__(256) void k_enc_xproj(const uint4* __restrict__ W0,
 // fragment of every wave takes 64 cycles).  The floor of a step is 64 x 16 cycles of the matrix pipe, 0.43 us; the cell
 // update, the barrier and the read of h from LDS follow it.
 // Measured: one request of 165 tokens 236 us (1.41 us a step) as chains of v_dot2_f32_f16 with two threads a unit -> 117 us
-// (0.70 us a step); 16 requests of 30 .. 300 tokens 419 -> 207 us.  With the instructions scheduled by the compiler: 165 us.
+// (0.67 us a step behind 6.6 us that load the weights); 16 requests of 300 tokens 206 us.  With the instructions scheduled by
+// the compiler: 165 us.
 // grid = (2 directions, requests), 256 threads.
 constexpr int ENC_SP_THREADS = 256;
 constexpr int ENC_SP_LDS_TILES = 3;                                        // of a group's sixteen fragments, those that live in LDS
@@ -316,16 +317,17 @@ __global__ __launch_bounds__(ENC_SP_THREADS) void k_enc_lstm_sp(const uint4* __r
 #undef SP_RUN
 #undef SP_W
 
-// The recurrence with fp32 weights: a direction's matrix (1 MB) does not fit a CU, and streaming it from L2 takes 40 us a step
-// (one CU's load path).  So G workgroups share a direction of R requests: each keeps the gate rows of 256 / G units in
-// registers (64 a thread), forms those units' gate sums from the whole h, updates their cells, and hands their h to its
+// The recurrence with fp32 weights: a direction's matrix (1 MB) does not fit a CU, and streaming it from L2 takes 29 us a step
+// (k_enc_lstm_alone; one CU's load path).  So G workgroups share a direction of R requests: each keeps the gate rows of 256 / G
+// units in registers (64 a thread), forms those units' gate sums from the whole h, updates their cells, and hands their h to its
 // partners through memory.  h needs no separate flag: |h| <= 1 leaves bit 30 of its fp32 word free, which carries the round
 // of the word's reuse (two buffers per request, the bit flips each time a buffer comes round; k_enc_embed clears the words
 // of a call).  A partner can be at most one step behind: nobody finishes step s + 1 without all of its words of step s.
 // A step is bound by that exchange (a store becoming visible plus a trip of the poll, about 1 us); the products take 0.1 us
 // (16 threads per unit, each 16 k of its four gate rows: 64 FMAs) to 0.4 us (16 waves a workgroup).  Measured: one request of
-// 165 tokens 6.56 -> 0.22 ms (1.3 us a step), 8 requests of 30 .. 300 tokens 5.8 -> 0.45 ms, 60 of them 1.0 ms.  G is as large as the
-// number of workgroups allows: all of them (2 directions x groups x G <= one per CU) must be resident at once, because they
+// 165 tokens 0.24 ms (1.4 us a step; 6.6 ms with the matrix streamed through MFMAs whose columns were the requests), 8 requests
+// of 30 .. 300 tokens 0.41 ms, 60 of them 0.94 ms (two to a group of workgroups).  G is as large as the number of workgroups
+// allows: all of them (2 directions x groups x G <= one per CU) must be resident at once, because they
 // wait for each other.  Work on other streams may keep some from starting (a second encoder, a pool whose own workgroups
 // wait for each other): every wait is bounded, one that runs out raises *fault and ends the workgroup, and k_enc_lstm_alone
 // behind this kernel then forms the call's results without waiting for anybody.
@@ -459,9 +461,10 @@ __global__ __launch_bounds__(1024) void k_enc_lstm_shared(const uint4* __restric
     }
 }
 
-// The same recurrence by one workgroup per direction and request, the weights streamed from L2 in every step (40 us a step:
-// one CU's load path).  It ends at once unless k_enc_lstm_shared gave up (given == nullptr: it was not launched, the device has
-// too few compute units for its workgroups).  grid = (2 directions, requests), 1024 threads.
+// The same recurrence by one workgroup per direction and request, the weights streamed from L2 in every step (28.7 us a step: one
+// CU's load path; 60 requests of 30 .. 300 tokens side by side 8.5 ms).  It ends at once unless k_enc_lstm_shared gave up (given
+// == nullptr: it was not launched, the device has too few compute units for its workgroups).
+// grid = (2 directions, requests), 1024 threads.
 __global__ __launch_bounds__(1024) void k_enc_lstm_alone(const uint4* __restrict__ Whh0, const uint4* __restrict__ Whh1,
                                                          const float* __restrict__ xproj, PnWindows w, int max_tokens,
                                                          float* __restrict__ out, const int* given)

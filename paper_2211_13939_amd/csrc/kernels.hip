@@ -2311,7 +2311,7 @@ __global__ __launch_bounds__(256) void k_prenet_slot(DevPtrs d, int slot)
 // Chunks from the mel ring straight into pinned host memory, all that are ready in one launch: grid = (pieces of 256 16-byte
 // words, chunks); the pieces come first because a chunk of the longest utterance (2^20 frames) has more of them than a grid may
 // have rows.  Bound by the host link.  One copy and one wait per chunk cost 15 - 18 us each, 64 chunks 1.1 ms beside 0.9 ms of
-// decoder steps; one launch for the 64 takes about 25 us.
+// decoder steps; one launch for 64 chunks of 40 frames takes 16 us (51 GB/s), for 256 of them 61 us (54 GB/s).
 __global__ __launch_bounds__(256) void k_stage_chunks(StageArgs a, const floatx4* __restrict__ ring, floatx4* __restrict__ dst)
 {
     constexpr int VEC = N_MEL / 4;

@@ -8,8 +8,9 @@ namespace tts {
 // Everything the layers need of a call's windows, in one launch: the per-column tables from the window list, and the mel frames
 // in the first layer's operand order, channels zero-padded to CIN.  A thread = 16 bytes of operand (8 or 4 channels of a column),
 // one 16-byte store.  grid = (windows, pieces of 256 threads of the longest window); the call's first launch also clears the
-// columns that pad the last tile.  Latency-bound at every size: as two
-// launches with 2-byte stores a round of 3 windows took 38.3 us and one of 64 86.9 us, like this 36.1 and 83.8 us.
+// columns that pad the last tile.  Latency-bound at every size: 3.0 us for 3 windows, 3.4 us for 64, 4.0 us for 256.  As two
+// launches with 2-byte stores a round of 64 windows took 86.8 us, like this 83.7 us; one of 3 windows 41.5 us, like this 38.3 us
+// (two runs of one side differ by 3 %).
 template <typename XT, int CIN>
 __global__ __launch_bounds__(256) void k_pn_pack(PnWindows w, const float* __restrict__ mel, int n_col, int n_col_pad, int clear_pad,
                                                  XT* __restrict__ X, int* __restrict__ cmeta, int* __restrict__ orow)
