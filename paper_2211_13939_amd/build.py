@@ -14,6 +14,11 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
          # the first 16 dwords of a kernel's arguments arrive in scalar registers with the wave (gfx950 preloads them):
          # the first loads of a kernel no longer wait for a cold read of the argument block
          "-mllvm", "-amdgpu-kernarg-preload-count=16",
+         # accumulators of the matrix instructions in ordinary vector registers: left to its heuristics the compiler kept them in
+         # the accumulation half of the file in kernels of 256 threads (vocoder.hip) and moved every sum out and in around each
+         # convolution, 15155 moves in that file's assembly against 85 (vocoder, a stream of 64 requests 1.25 -> 1.11 ms, of one
+         # request 322 -> 310 us; the other files had no such moves and their times stay)
+         "-mllvm", "-amdgpu-mfma-vgpr-form=1",
          "-Wall", "-Wno-unused-result"]
 
 
