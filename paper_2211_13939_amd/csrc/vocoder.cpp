@@ -44,12 +44,16 @@ size_t bytes_of(const ConvShape& s, bool bf) { return (size_t)s.rows_pad * s.k_p
 
 ConvShape pre_shape(bool bf) { return shape_of(VOC_C0, VOC_N_MEL, VOC_K_PRE, bf); }
 ConvShape up_shape(int s, bool bf) { return shape_of(voc_rate(s) * voc_channels(s), 2 * voc_channels(s), 3, bf); }
-ConvShape res_shape(int s, int b, bool bf) { return shape_of(voc_channels(s), voc_channels(s), voc_block_k(b), bf); }
+ConvShape res_shape(int s, int b, bool bf)
+{
+    const int c = voc_channels(s), k = voc_block_k(b);
+    return voc_paired(c) ? shape_of(2 * c, c, k + 1, bf) : shape_of(c, c, k, bf);
+}
 ConvShape post_shape(bool bf) { return shape_of(1, voc_channels(VOC_STAGES - 1), VOC_K_POST, bf); }
 
 struct VocLayout {
     size_t pre_w, pre_b, up_w[VOC_STAGES], up_b[VOC_STAGES];
-    size_t res_w[VOC_STAGES][VOC_BLOCKS][2 * VOC_PAIRS], res_b[VOC_STAGES][VOC_BLOCKS][2 * VOC_PAIRS];
+    size_t res_w[VOC_STAGES][VOC_BLOCKS], res_b[VOC_STAGES][VOC_BLOCKS];
     size_t post_w, post_b, alpha, beta, m_tail, s_tail, len, x_mel, x0, y, r[VOC_BLOCKS], audio, total;
     size_t state_begin;   // everything from here on is cleared at creation
 };
@@ -67,11 +71,10 @@ VocLayout layout_of(const tts_vocoder_config& c)
     for (int s = 0; s < VOC_STAGES; ++s) {
         l.up_w[s] = a.take(bytes_of(up_shape(s, bf), bf));
         l.up_b[s] = a.take(voc_channels(s) * 4);
-        for (int b = 0; b < VOC_BLOCKS; ++b)
-            for (int i = 0; i < 2 * VOC_PAIRS; ++i) {
-                l.res_w[s][b][i] = a.take(bytes_of(res_shape(s, b, bf), bf));
-                l.res_b[s][b][i] = a.take(voc_channels(s) * 4);
-            }
+        for (int b = 0; b < VOC_BLOCKS; ++b) {
+            l.res_w[s][b] = a.take(2 * VOC_PAIRS * bytes_of(res_shape(s, b, bf), bf));
+            l.res_b[s][b] = a.take(2 * VOC_PAIRS * voc_channels(s) * 4);
+        }
     }
     l.post_w = a.take(bytes_of(post_shape(bf), bf));
     l.post_b = a.take(16);
@@ -160,6 +163,16 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
                           return (j >= 0 && j < 2 * u) ? src[((size_t)c * c_out + co) * (2 * u) + j] : 0.f;
                       }), bf);
     };
+    // a convolution of the residual blocks: where positions are formed in pairs, GEMM row = position of the pair * c_out + channel,
+    // and the second position meets the same taps one further on
+    auto put_res = [&](size_t off, int s, int b, const float* src) {
+        const ConvShape sh = res_shape(s, b, bf);
+        const int c_out = voc_channels(s), taps = voc_block_k(b);
+        return upload(base + off, pack_fragments(sh.rows_pad, sh.k_pad, bf, [&](int r, int k) {
+                          const int co = r % c_out, tap = k / sh.c_in - r / c_out, c = k % sh.c_in;
+                          return (r < sh.rows && tap >= 0 && tap < taps) ? src[((size_t)co * sh.c_in + c) * taps + tap] : 0.f;
+                      }), bf);
+    };
     auto put_bias = [&](size_t off, const float* src, int n) { return upload(base + off, std::vector<float>(src, src + n), false); };
 
     rc = put_conv(lay.pre_w, pre_shape(bf), w->pre_w);
@@ -169,8 +182,8 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
         if (rc == TTS_OK) rc = put_bias(lay.up_b[s], w->up_b[s], voc_channels(s));
         for (int b = 0; b < VOC_BLOCKS && rc == TTS_OK; ++b)
             for (int i = 0; i < 2 * VOC_PAIRS && rc == TTS_OK; ++i) {
-                rc = put_conv(lay.res_w[s][b][i], res_shape(s, b, bf), w->res_w[s][b][i]);
-                if (rc == TTS_OK) rc = put_bias(lay.res_b[s][b][i], w->res_b[s][b][i], voc_channels(s));
+                rc = put_res(lay.res_w[s][b] + i * bytes_of(res_shape(s, b, bf), bf), s, b, w->res_w[s][b][i]);
+                if (rc == TTS_OK) rc = put_bias(lay.res_b[s][b] + i * voc_channels(s) * 4, w->res_b[s][b][i], voc_channels(s));
             }
     }
     if (rc == TTS_OK) rc = put_conv(lay.post_w, post_shape(bf), w->post_w);
@@ -201,11 +214,10 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
     for (int s = 0; s < VOC_STAGES; ++s) {
         d.up_w[s] = base + lay.up_w[s];
         d.up_b[s] = (const float*)(base + lay.up_b[s]);
-        for (int b = 0; b < VOC_BLOCKS; ++b)
-            for (int i = 0; i < 2 * VOC_PAIRS; ++i) {
-                d.res_w[s][b][i] = base + lay.res_w[s][b][i];
-                d.res_b[s][b][i] = (const float*)(base + lay.res_b[s][b][i]);
-            }
+        for (int b = 0; b < VOC_BLOCKS; ++b) {
+            d.res_w[s][b] = base + lay.res_w[s][b];
+            d.res_b[s][b] = (const float*)(base + lay.res_b[s][b]);
+        }
     }
     d.post_w = base + lay.post_w;
     d.post_b = (const float*)(base + lay.post_b);

@@ -8,8 +8,8 @@
 //                     a 3-tap convolution with rows = (phase r, output channel) and one zero tap per phase
 // Activations live in HBM as fp32 [position][channel]; a workgroup stages the positions of its tile plus the halo
 // in LDS (leaky ReLU and the conversion to the MFMA operand type happen there, once per element), so that a lane's
-// B operand -- consecutive channels of one tap at one position -- is one 16-byte LDS read.  Rows of LDS are padded
-// to an odd number of 16-byte pieces.  The weights are stored in A-fragment order and stream from L2.
+// B operand -- consecutive channels of one tap at one position -- is one 16-byte LDS read.  LDS holds a plane per 16
+// bytes of channels.  The weights are stored in A-fragment order and stream from L2.
 // Windows of different requests lie at a fixed stride; positions outside a window's own length read as zero, which
 // is the zero padding of every layer.
 #include "vocoder_kernels.h"
@@ -30,8 +30,6 @@ enum { EPI_PLAIN = 0, EPI_UP = 2, EPI_POST = 3 };
 template <typename XT, int CIN> struct VcGeom {
     static constexpr int EPL = Frag<XT>::EPL;
     static constexpr int GP = CIN / EPL;         // 16-byte pieces per position
-    static constexpr int GPP = GP | 1;           // ... padded to an odd count
-    static constexpr int CINP = GPP * EPL;
     static_assert(CIN % EPL == 0, "channels must fill whole 16-byte pieces");
 };
 
@@ -40,9 +38,11 @@ template <typename XT, int CIN, int ROWS, int HALO, bool SHORT = false> constexp
 {
     constexpr int RT = ROWS / 16, RG = RT < 4 ? RT : 4;
     int tp = SHORT ? 64 : 1024 / RG;
-    while (tp > 64 && (tp + 2 * HALO) * VcGeom<XT, CIN>::GPP * 16 > VC_LDS_BYTES) tp /= 2;
+    while (tp > 64 && (tp + 2 * HALO) * VcGeom<XT, CIN>::GP * 16 > VC_LDS_BYTES) tp /= 2;
     return tp;
 }
+// rows of the operand buffer: a plane per 16 bytes of channels, a multiple of 16 rows apart (see VrGeom::STRIDE)
+constexpr int vc_stride(int rows) { return (rows + 15) / 16 * 16; }
 
 struct VcArgs {
     const float* in0;     // input activations [position][C_in]
@@ -51,11 +51,10 @@ struct VcArgs {
     float* out;
     const uint4* W;
     const float* bias;
-    int dil;
 };
 
-// slope < 1: the larger of x and slope * x
-__device__ __forceinline__ float lrelu(float x) { return fmaxf(x, VC_SLOPE * x); }
+// slope < 1: the larger of x and slope * x.  (fmaxf costs a third instruction that quiets x first; maximum has NaN for NaN too.)
+__device__ __forceinline__ float lrelu(float x) { return __builtin_elementwise_maximum(x, VC_SLOPE * x); }
 
 template <typename XT> __device__ __forceinline__ void lds_put4(uint4* lds, int elem, float4 v);
 template <> __device__ __forceinline__ void lds_put4<float>(uint4* lds, int elem, float4 v)
@@ -85,27 +84,38 @@ __device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wba
     static_assert(ROWS % 16 == 0 && RT % RG == 0 && TP % (16 * VC_WAVES) == 0, "tile shape");
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
-    const int halo = (KS - 1) / 2 * a.dil;
-    const int nrows = TP + 2 * halo;
+    constexpr int halo = (KS - 1) / 2, nrows = TP + 2 * halo, STRIDE = vc_stride(nrows);
 
-    // ---- stage positions [p0 - halo, p0 + TP + halo): activation and operand type applied once per element
-    for (int idx = tid; idx < nrows * C4; idx += VC_THREADS) {
-        const int row = idx / C4, c4 = idx - row * C4;
-        const int p = p0 - halo + row;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (p >= 0 && p < valid) {
-            const size_t off = (wbase + p) * CIN + 4 * c4;
-            v = *reinterpret_cast<const float4*>(a.in0 + off);
+    // ---- stage positions [p0 - halo, p0 + TP + halo): activation and operand type applied once per element; a few pieces of every
+    // thread are requested together, from clamped positions
+    constexpr int N_STAGE = nrows * C4, AT_ONCE = SRC3 ? 4 : 8;
+    for (int i0 = 0; i0 < N_STAGE; i0 += AT_ONCE * VC_THREADS) {
+        float4 v[AT_ONCE], v1[SRC3 ? AT_ONCE : 1], v2[SRC3 ? AT_ONCE : 1];
+#pragma unroll
+        for (int i = 0; i < AT_ONCE; ++i) {
+            const int idx = min(i0 + i * VC_THREADS + tid, N_STAGE - 1), row = idx / C4, c4 = idx - row * C4;
+            const unsigned off = (unsigned)(min(max(p0 - halo + row, 0), valid - 1) * CIN + 4 * c4) * 4u;     // bytes from the window's first position
+            v[i] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.in0 + wbase * CIN) + off);
             if constexpr (SRC3) {
-                const float4 v1 = *reinterpret_cast<const float4*>(a.in1 + off);
-                const float4 v2 = *reinterpret_cast<const float4*>(a.in2 + off);
-                constexpr float third = 1.0f / 3.0f;
-                v.x = ((v.x + v1.x) + v2.x) * third; v.y = ((v.y + v1.y) + v2.y) * third;
-                v.z = ((v.z + v1.z) + v2.z) * third; v.w = ((v.w + v1.w) + v2.w) * third;
+                v1[i] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.in1 + wbase * CIN) + off);
+                v2[i] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.in2 + wbase * CIN) + off);
             }
-            if constexpr (PRE_ACT) { v.x = lrelu(v.x); v.y = lrelu(v.y); v.z = lrelu(v.z); v.w = lrelu(v.w); }
         }
-        lds_put4<XT>(lds, row * G::CINP + 4 * c4, v);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < AT_ONCE; ++i) {
+            const int idx = i0 + i * VC_THREADS + tid, row = idx / C4, c4 = idx - row * C4;
+            if (idx >= N_STAGE) break;
+            float4 u = v[i];
+            if constexpr (SRC3) {
+                constexpr float third = 1.0f / 3.0f;
+                u.x = ((u.x + v1[i].x) + v2[i].x) * third; u.y = ((u.y + v1[i].y) + v2[i].y) * third;
+                u.z = ((u.z + v1[i].z) + v2[i].z) * third; u.w = ((u.w + v1[i].w) + v2[i].w) * third;
+            }
+            if constexpr (PRE_ACT) { u.x = lrelu(u.x); u.y = lrelu(u.y); u.z = lrelu(u.z); u.w = lrelu(u.w); }
+            if ((unsigned)(p0 - halo + row) >= (unsigned)valid) u = make_float4(0.f, 0.f, 0.f, 0.f);
+            lds_put4<XT>(lds, ((4 * c4 / G::EPL) * STRIDE + row) * G::EPL + 4 * c4 % G::EPL, u);
+        }
     }
     __syncthreads();
 
@@ -137,10 +147,10 @@ __device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wba
             // this lane's 16 bytes of k: piece q = (tap, channel group); pieces past the end meet zero weights
             const int q = min(kf * 4 + g, NQ - 1);
             const int tap = q / G::GP, cg = q - tap * G::GP;
-            const uint4* bl = lds + (colbase + n + tap * a.dil) * G::GPP + cg;
+            const uint4* bl = lds + cg * STRIDE + colbase + n + tap;
             uint4 bv[CT];
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) bv[ct] = bl[ct * 16 * G::GPP];
+            for (int ct = 0; ct < CT; ++ct) bv[ct] = bl[ct * 16];
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
@@ -182,7 +192,7 @@ template <typename XT, int CIN, int ROWS, int COUT, int KS, int EPI, bool PRE_AC
 __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __restrict__ len, int rate, int window)
 {
     constexpr int TP = vc_tp<XT, CIN, ROWS, (KS - 1) / 2, SHORT>();
-    __shared__ uint4 lds[(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GPP];
+    __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
     const int w = blockIdx.y, valid = len[w] * rate, p0 = blockIdx.x * TP;
     if (p0 >= valid) return;
     conv_tile<XT, CIN, ROWS, COUT, KS, TP, EPI, PRE_ACT, SRC3, U>(a, valid, (size_t)w * window * rate, p0, lds);
@@ -192,217 +202,313 @@ __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __res
 // One residual block, all three convolution pairs, on one tile of positions without leaving the CU:
 //   for d in (1, 3, 5):  x += conv_{k,1}(lrelu(conv_{k,d}(lrelu(x))))
 // The residual stream x of the tile -- TP positions plus the halo H = (k-1)/2 * 12 that the six convolutions
-// eat on each side -- stays in registers in the MFMA accumulator layout (lane = one position, four channels
-// per row tile), so the second convolution of a pair accumulates straight onto it.  The operand of the next
-// convolution (leaky ReLU applied, operand type, zero outside the request's window) goes through one LDS
-// buffer: written by the lanes that own the values, read as B fragments by every wave.  Values near the
-// edge of the region are wrong after a convolution (their neighbours were not staged); the error front moves
-// inwards by one halo per convolution and stops exactly at the TP positions that are written out.
+// eat on each side -- stays in registers in the MFMA accumulator layout, so the second convolution of a pair
+// accumulates straight onto it.  The operand of the next convolution (leaky ReLU applied, operand type, zero outside
+// the request's window) goes through one LDS buffer: written by the lanes that own the values, read as B fragments by
+// every wave.  Values near the edge of the region are wrong after a convolution (their neighbours were not staged); the
+// error front moves inwards by one halo per convolution and stops exactly at the TP positions that are written out.
+// Without HALO the region is a whole window and has no such edge.
+//
+// A column of the GEMM is a position, and its rows are the channels, where there are 32 or 64 of them.  With 8 or 16
+// channels a column is a PAIR of positions, 2 P and 2 P + d for a convolution with dilation d (odd: every position is in
+// one pair), and its rows are (position of the pair, channel): the pair shares all but one of its taps at either end, so
+// k + 1 taps feed 2 C rows.  Eight channels fill a 16-row tile (half of it was padding), and with sixteen a B fragment
+// read from LDS feeds two MFMAs -- k + 1 taps of 16 channels are whole fragments, where k were padded to the same count.
+// The operand buffer holds even and odd positions in planes of their own, so the columns of a tap are still consecutive
+// rows: 2 P + m d lies in plane m & 1 at row P + (m d - (m & 1)) / 2.
+//
+// Measured (two-byte mode, windows of 48 frames, one launch): 1 window, 64 / 32 / 16 / 8 channels 34.0 / 13.9 / 9.5 / 9.0 us -> 22.3 / 11.1 /
+// 7.8 / 5.5; 64 windows 93.4 / 107 / 70.4 / 119 -> 42.8 / 92 / 69 / 42.5.  With 16 and 32 channels the matrix pipes are busy 36 % of the
+// time and the vector units 30 %: the two waves of a SIMD run in step, so that products (16 cycles each) and the work on their
+// sums (two and a half instructions a value, half as much time) follow each other more than they overlap.  One workgroup for
+// a stage's three blocks, with their mean stored for the next layer, took as long (352 against 353 us a round of 64).
 // ---------------------------------------------------------------------------
 struct VrArgs {
     const float* in;                         // the stage's upsampled activations
     float* out;                              // the block's output
-    const uint4* W[2 * VOC_PAIRS];           // [2 pair + {0: dilated, 1: plain}]
-    const float* bias[2 * VOC_PAIRS];
+    const uint4* W;                          // the six convolutions one after the other, [2 pair + {0: dilated, 1: plain}]
+    const float* bias;                       // [2 * VOC_PAIRS][C]
 };
 struct VrArgs3 { VrArgs b[VOC_BLOCKS]; };
 
 constexpr int VR_LDS_MAX = 160 * 1024;
 
-template <typename XT, int C, int KS, int TP> struct VrGeom {
+// The weights stream from L1 / L2 into a ring of registers, VR_AHEAD fragments ahead of the products; the first ones of a
+// convolution are requested before the operand is put in LDS.  (Through LDS, as a first version had them, they were a quarter
+// to a half of its traffic, and a convolution's 88 KB at 64 channels went through the CU in one burst.)  Two operand buffers,
+// where LDS holds them, so that one barrier per convolution is enough and a wave that is done prepares the next operand
+// while others still read this one.
+constexpr int VR_AHEAD = 4;
+
+template <typename XT, int C, int KS, int TP, bool HALO> struct VrGeom {
+    using G = VcGeom<XT, C>;
+    static constexpr bool PAIR = voc_paired(C);
+    static constexpr int RGROUPS = C == 64 ? 2 : 1;           // groups of rows, a quarter of the columns per wave in each
+    static constexpr int THREADS = RGROUPS * 256;
     static constexpr int HALF = (KS - 1) / 2;
-    static constexpr int H = HALF * 12;                       // sum over d = 1, 3, 5 of (d + 1) * HALF
-    static constexpr int NCOL = (TP + 2 * H + 63) / 64;       // column tiles per wave
-    static constexpr int W = 64 * NCOL;                       // positions of the region
-    static constexpr int PADR = HALF * 5;                     // zero rows on each side: the widest tap offset
-    static constexpr int OPERAND_VECS = (W + 2 * PADR) * VcGeom<XT, C>::GPP;     // 16-byte pieces of the operand buffer
-    // one convolution's weights (A-fragment order) as 16-byte pieces; they go through LDS when both fit
-    static constexpr int W_VECS = ((C < 16 ? 16 : C) / 16) * ((KS * C + Frag<XT>::KB - 1) / Frag<XT>::KB) * 64;
-    static constexpr bool W_LDS = (OPERAND_VECS + W_VECS) * 16 <= VR_LDS_MAX;
-    static constexpr int BYTES = (OPERAND_VECS + (W_LDS ? W_VECS : 0)) * 16;
+    static constexpr int H = HALO ? HALF * 12 : 0;            // sum over d = 1, 3, 5 of (d + 1) * HALF
+    static constexpr int PW = PAIR ? 32 : 16;                 // positions per column tile
+    static constexpr int NCOL = (TP + 2 * H + 4 * PW - 1) / (4 * PW);     // column tiles per wave
+    static constexpr int W = 4 * PW * NCOL;                   // positions of the region
+    static constexpr int RT = (PAIR ? 2 * C : C) / 16 / RGROUPS;          // row tiles per wave
+    static constexpr int TAPS = PAIR ? KS + 1 : KS;
+    static constexpr int NK = TAPS * C / Frag<XT>::KB;
+    static constexpr int AHEAD = NK < VR_AHEAD ? NK : VR_AHEAD;
+    // zero rows on each side: the widest tap offset
+    static constexpr int PAD = PAIR ? (5 * (HALF + 1) + 1) / 2 : 5 * HALF;
+    static constexpr int PLANE = (PAIR ? W / 2 : W) + 2 * PAD;            // rows of a plane
+    // 16-byte pieces: a plane per 16 bytes of channels, and of even and odd positions.  Lanes l and l + 16 of a B fragment read
+    // the same rows (or, with 8 channels, rows of even and odd positions up to three apart) of different planes: LDS gives 256
+    // bytes a cycle where their distance is a multiple of 16 pieces, half of that otherwise (4.4 and 8.0 cycles a wave's read)
+    static constexpr int EVEN = PAIR ? (PLANE + 2 + 15) / 16 * 16 : 0;    // where the even positions begin, up to a shift
+    static constexpr int STRIDE = (EVEN + PLANE + 15) / 16 * 16;          // between channel planes
+    static constexpr int OPERAND_VECS = STRIDE * G::GP;
+    static constexpr bool TWO = 2 * OPERAND_VECS * 16 + 2 * VOC_PAIRS * C * 4 <= VR_LDS_MAX;
+    static constexpr int BIAS_AT = (TWO ? 2 : 1) * OPERAND_VECS;         // the six biases
+    static constexpr int BYTES = BIAS_AT * 16 + 2 * VOC_PAIRS * C * 4;
+    static constexpr int W_BYTES = RT * RGROUPS * NK * 1024;             // weights of one convolution
+    static_assert(RT * RGROUPS * 16 == (PAIR ? 2 * C : C) && NK * Frag<XT>::KB == TAPS * C, "whole tiles and fragments");
+    // first piece of the plane of position parity s.  With 8 channels neighbouring taps of a dilation d lie (d + 1) / 2 rows apart in the
+    // odd and the even plane: the shift is that of d = 1 in the second buffer and of d = 3 in the first, which has d = 1, 3, 5 in turn
+    __device__ static constexpr int plane(int s, int buf) { return !PAIR || s ? 0 : EVEN - (TWO && buf == 0 ? 2 : 1); }
+    static_assert(HALO || !PAIR, "a pair's second position is missing at the region's first positions: they have to lie in a halo");
 };
 
-// Positions per workgroup of the fused kernel.  Up to 32 channels the region's accumulators (x and one convolution's
-// output) and the operand buffer are small enough for two workgroups to share a CU: while one is in a convolution
-// (MFMA) the other can be preparing an operand (VALU).  Small batches take half of that, a request or two a quarter:
-// more workgroups, each with a shorter chain (and a larger share of halo: the sum of their work grows).
-template <int C, int LEVEL> constexpr int vr_tp() { return (C >= 32 ? 256 : 512) >> LEVEL; }
-constexpr int VR_SMALL_BELOW = 1024;             // workgroups of the large tiling below which the half tiles are used
-constexpr int VR_TINY_BELOW = 128;               // ... and the quarter tiles
+// every LDS access of this wave is done, then all waves are here; loads from memory stay on their way
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// acc[rt][ct] += W (rows rt, all k) * operand(columns of tile ct shifted by the taps)
-template <typename XT, int C, int KS, int NCOL, int PADR>
-__device__ __forceinline__ void conv_regs(const uint4* __restrict__ Wf, int dil, const uint4* lds, int col0, int lane,
-                                          floatx4 (&acc)[(C < 16 ? 16 : C) / 16][NCOL])
+// The weights of a block's six convolutions in A-fragment order: a fragment's place is a scalar offset, so all of them share one
+// address register, and no pointer has to be loaded before a convolution's first fragment can be requested.
+template <typename R> struct VrWeights {
+    __amdgpu_buffer_rsrc_t rsrc;
+    int rt0, lane;
+    __device__ __forceinline__ VrWeights(const uint4* W, int rt0, int lane)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(W), 0, 2 * VOC_PAIRS * R::W_BYTES, BUFFER_RSRC_RAW)), rt0(rt0), lane(lane) {}
+    __device__ __forceinline__ uint4 at(int conv, int rt, int kf) const
+    {
+        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, conv * R::W_BYTES + ((rt0 + rt) * R::NK + kf) * 1024, 0);
+        return make_uint4(v.x, v.y, v.z, v.w);
+    }
+};
+template <typename R> using VrRing = uint4[R::AHEAD][R::RT];
+template <typename R> __device__ __forceinline__ void ring_fill(VrRing<R>& ring, const VrWeights<R>& W, int conv)
 {
-    using G = VcGeom<XT, C>;
-    constexpr int KB = Frag<XT>::KB;
-    constexpr int RT = (C < 16 ? 16 : C) / 16;
-    constexpr int NK = (KS * C + KB - 1) / KB;
-    constexpr int NQ = KS * G::GP;
+#pragma unroll
+    for (int kf = 0; kf < R::AHEAD; ++kf)
+#pragma unroll
+        for (int rt = 0; rt < R::RT; ++rt) ring[kf][rt] = W.at(conv, rt, kf);
+}
+
+// acc += W * operand, or bias + W * operand (INIT).  A k step's B fragments are requested before the products of the step before.
+template <typename XT, typename R, bool INIT>
+__device__ __forceinline__ void conv_regs(const VrWeights<R>& W, int conv, VrRing<R>& ring, int dil, const uint4* lds, int buf, int col0, int lane,
+                                          const floatx4 (&bias)[R::RT], floatx4 (&acc)[R::RT][R::NCOL])
+{
+    using G = typename R::G;
+    constexpr int NK = R::NK, RT = R::RT, NCOL = R::NCOL, GP = G::GP;
     const int n = lane & 15, g = lane >> 4;
-    const uint4* Wl = Wf + lane;
-#pragma unroll 2
+    // this lane's 16 bytes of k in fragment kf: piece 4 kf + g = (tap, channel group)
+    auto b_at = [&](int kf) __attribute__((always_inline)) {
+        constexpr int STEP = GP < 4 ? 4 / GP : 1;             // taps per fragment
+        if constexpr (R::PAIR && STEP % 2 == 0) {             // the parity of a lane's tap does not change from fragment to fragment
+            const int m = g / GP - R::HALF, pl = m & 1;
+            return (g % GP) * R::STRIDE + R::plane(pl, buf) + R::PAD + col0 + n + ((m * dil - pl) >> 1) + kf * (STEP / 2) * dil;
+        } else {
+            const int q = 4 * kf + g, m = q / GP - R::HALF;
+            if constexpr (R::PAIR) return (q % GP) * R::STRIDE + R::plane(m & 1, buf) + R::PAD + col0 + n + ((m * dil - (m & 1)) >> 1);
+            else return (q % GP) * R::STRIDE + R::PAD + col0 + n + m * dil;
+        }
+    };
+    uint4 bv[2][NCOL];
+    auto request = [&](int kf) __attribute__((always_inline)) {
+        const uint4* bl = lds + b_at(kf);
+#pragma unroll
+        for (int ct = 0; ct < NCOL; ++ct) bv[kf & 1][ct] = bl[ct * 16];
+    };
+    request(0);
+#pragma unroll
     for (int kf = 0; kf < NK; ++kf) {
         uint4 af[RT];
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) af[rt] = Wl[((size_t)rt * NK + kf) * 64];
-        const int q = min(kf * 4 + g, NQ - 1);
-        const int tap = q / G::GP, cg = q - tap * G::GP;
-        const uint4* bl = lds + (col0 + n + PADR + (tap - (KS - 1) / 2) * dil) * G::GPP + cg;
-        // all B fragments of this k step are requested before the first MFMA waits for one
-        uint4 bv[NCOL];
-#pragma unroll
-        for (int ct = 0; ct < NCOL; ++ct) bv[ct] = bl[ct * 16 * G::GPP];
+        for (int rt = 0; rt < RT; ++rt) {
+            af[rt] = ring[kf % R::AHEAD][rt];
+            if (kf + R::AHEAD < NK) ring[kf % R::AHEAD][rt] = W.at(conv, rt, kf + R::AHEAD);
+        }
+        if (kf + 1 < NK) request(kf + 1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int ct = 0; ct < NCOL; ++ct)
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) acc[rt][ct] = mfma_frag<XT>(af[rt], bv[ct], acc[rt][ct]);
+            for (int rt = 0; rt < RT; ++rt) acc[rt][ct] = mfma_frag<XT>(af[rt], bv[kf & 1][ct], INIT && kf == 0 ? bias[rt] : acc[rt][ct]);
     }
 }
 
-template <typename XT, int C, int KS, int TP>
+template <typename XT, int C, int KS, int TP, bool HALO>
 __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t wbase, int p0, uint4* lds)
 {
-    using G = VcGeom<XT, C>;
-    using R = VrGeom<XT, C, KS, TP>;
-    constexpr int RT = (C < 16 ? 16 : C) / 16, NCOL = R::NCOL;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    using R = VrGeom<XT, C, KS, TP, HALO>;
+    using G = typename R::G;
+    constexpr int RT = R::RT, NCOL = R::NCOL;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
-    const int col0 = wave * 16 * NCOL;           // this wave's first position of the region
+    const int col0 = (wave & 3) * 16 * NCOL;     // this wave's first column of the region
+    const int rt0 = (wave >> 2) * RT;            // ... and its first row tile
     const int pbase = p0 - R::H;                 // the region's first position inside the window
-    const bool rows_ok = 4 * g < C;              // C = 8: the upper half of the 16-row tile is padding
+    // the lane's four rows of row tile rt: position s of the pair, channels ch .. ch + 3
+    auto part = [&](int rt) __attribute__((always_inline)) { return !R::PAIR ? 0 : C == 8 ? g >> 1 : rt; };
+    auto chan = [&](int rt) __attribute__((always_inline)) { return R::PAIR ? (C == 8 ? 4 * (g & 1) : 4 * g) : (rt0 + rt) * 16 + 4 * g; };
+    // position inside the region of row tile rt, column tile ct, in a layout whose pairs are d apart.  c = this lane's column of
+    // column tile 0, made anew by its users: positions kept from one phase to the next would cost more registers than the sums
+    auto column = [&]() __attribute__((always_inline)) {
+        int c = col0 + n;
+        asm volatile("" : "+v"(c));
+        return c;
+    };
+    auto pos = [&](int c, int rt, int ct, int d) __attribute__((always_inline)) {
+        const int col = c + ct * 16;
+        return R::PAIR ? 2 * col + part(rt) * d : col;
+    };
+    // byte offsets of 32 bits from the window's first position: a window is at most (4096 + 16) * 2048 values
+    const char* in = reinterpret_cast<const char*>(a.in + wbase * C);
+    char* out = reinterpret_cast<char*>(a.out + wbase * C);
+    auto byte_at = [&](int p, int rt) __attribute__((always_inline)) { return (unsigned)(p * C + chan(rt)) * 4u; };
 
-    // zero rows in front of and behind the region: never written again
-    for (int idx = tid; idx < 2 * R::PADR * G::GPP; idx += VC_THREADS) {
-        const int r = idx / G::GPP, c = idx - r * G::GPP;
-        lds[(r < R::PADR ? r : R::W + r) * G::GPP + c] = make_uint4(0, 0, 0, 0);
-    }
-    // The weights of the next convolution are fetched into registers while the current one computes and
-    // handed to LDS together with its operand, so no MFMA loop waits for L2 (where they fit beside the operand).
-    constexpr int W_PER = (R::W_VECS + VC_THREADS - 1) / VC_THREADS;
-    uint4* wbuf = lds + R::OPERAND_VECS;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 wreg[R::W_LDS ? W_PER : 1];
-    auto fetch = [&](const uint4* __restrict__ Wg) __attribute__((always_inline)) {
-        if constexpr (R::W_LDS) {
-#pragma unroll
-            for (int i = 0; i < W_PER; ++i) wreg[i] = reinterpret_cast<const u32x4*>(Wg)[min(tid + i * VC_THREADS, R::W_VECS - 1)];
-        }
-    };
-    auto stash = [&]() __attribute__((always_inline)) {
-        if constexpr (R::W_LDS) {
-#pragma unroll
-            for (int i = 0; i < W_PER; ++i)
-                if (tid + i * VC_THREADS < R::W_VECS) reinterpret_cast<u32x4*>(wbuf)[tid + i * VC_THREADS] = wreg[i];
-        }
-    };
-    fetch(a.W[0]);
+    const VrWeights<R> weights(a.W, rt0, lane);
+    VrRing<R> ring;
+    float* const lds_bias = reinterpret_cast<float*>(lds + R::BIAS_AT);
     floatx4 x[RT][NCOL];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int ct = 0; ct < NCOL; ++ct) {
-            const int p = pbase + col0 + ct * 16 + n;
-            floatx4 v = {0.f, 0.f, 0.f, 0.f};
-            if (p >= 0 && p < valid && rows_ok) v = *reinterpret_cast<const floatx4*>(a.in + (wbase + p) * C + rt * 16 + 4 * g);
-            x[rt][ct] = v;
-        }
-    // operand of the next convolution: lrelu, zero outside the window, operand type
-    const bool edge = pbase < 0 || pbase + R::W > valid;        // only tiles at a window's ends need the mask
-    auto put = [&](const floatx4 (&v)[RT][NCOL]) __attribute__((always_inline)) {
-        if (!rows_ok) return;
+    {
+        const int c = column();
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int ct = 0; ct < NCOL; ++ct) {
-                const int j = col0 + ct * 16 + n, p = pbase + j;
-                const bool in = !edge || (p >= 0 && p < valid);
-                const float4 o = make_float4(in ? lrelu(v[rt][ct][0]) : 0.f, in ? lrelu(v[rt][ct][1]) : 0.f,
-                                             in ? lrelu(v[rt][ct][2]) : 0.f, in ? lrelu(v[rt][ct][3]) : 0.f);
-                lds_put4<XT>(lds, (j + R::PADR) * G::CINP + rt * 16 + 4 * g, o);
+            for (int ct = 0; ct < NCOL; ++ct) {                 // clamped: what lies outside the window is never put in the buffer
+                const int p = min(max(pbase + pos(c, rt, ct, 1), 0), valid - 1);
+                x[rt][ct] = *reinterpret_cast<const floatx4*>(in + byte_at(p, rt));
             }
+    }
+    ring_fill<R>(ring, weights, 0);
+    for (int i = tid; i < 2 * VOC_PAIRS * C; i += R::THREADS) lds_bias[i] = a.bias[i];
+    // Rows in front of and behind the region, and those of positions outside the window, are zero: nothing but a pair's second
+    // position a little past the region's end is ever stored there.
+    const int r0 = max(-pbase, 0), r1 = min(valid - pbase, R::W);         // positions r0 .. r1 - 1 of the region exist
+    const bool edge = r0 > 0 || r1 < R::W;
+    auto zero_rows = [&](uint4* plane, int from, int to) __attribute__((always_inline)) {
+        for (int row = from + tid; row < to; row += R::THREADS)
+#pragma unroll
+            for (int cg = 0; cg < G::GP; ++cg) plane[cg * R::STRIDE + row] = make_uint4(0, 0, 0, 0);
     };
-    auto bias_of = [&](const float* b, int rt) __attribute__((always_inline)) {
-        floatx4 v = {0.f, 0.f, 0.f, 0.f};
-        if (rows_ok) v = *reinterpret_cast<const floatx4*>(b + rt * 16 + 4 * g);
-        return v;
+#pragma unroll
+    for (int buf = 0; buf < (R::TWO ? 2 : 1); ++buf)
+#pragma unroll
+        for (int pl = 0; pl < (R::PAIR ? 2 : 1); ++pl) {       // row PAD + i of plane pl: position 2 i + pl, or i
+            uint4* plane = lds + buf * R::OPERAND_VECS + R::plane(pl, buf);
+            zero_rows(plane, 0, R::PAD + (R::PAIR ? (r0 - pl + 1) >> 1 : r0));
+            zero_rows(plane, R::PAD + (R::PAIR ? (r1 - pl + 1) >> 1 : r1), R::PLANE);
+        }
+    // operand of the next convolution: lrelu, operand type, positions of the window only; v in the layout of pairs d apart
+    auto put = [&](uint4* at, int buf, const floatx4 (&v)[RT][NCOL], int d) __attribute__((always_inline)) {
+        const int c = column();
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const int ch = chan(rt), s = part(rt);
+            const int e = ((ch / G::EPL) * R::STRIDE + (s ? R::plane(1, buf) : R::plane(0, buf)) + s * ((d - 1) >> 1) + R::PAD + c) * G::EPL + ch % G::EPL;
+            auto store = [&](int ct) __attribute__((always_inline)) {
+                const floatx4 f = v[rt][ct];
+                lds_put4<XT>(at, e + ct * 16 * G::EPL, make_float4(lrelu(f[0]), lrelu(f[1]), lrelu(f[2]), lrelu(f[3])));
+            };
+            if (edge) {
+#pragma unroll
+                for (int ct = 0; ct < NCOL; ++ct)
+                    if ((unsigned)(pbase + pos(c, rt, ct, d)) < (unsigned)valid) store(ct);
+            } else {
+#pragma unroll
+                for (int ct = 0; ct < NCOL; ++ct) store(ct);
+            }
+        }
     };
-    put(x);
-    stash();
-    __syncthreads();
+    auto biases = [&](int conv, floatx4 (&v)[RT]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) v[rt] = *reinterpret_cast<const floatx4*>(lds_bias + conv * C + chan(rt));
+    };
+    uint4* const lds1 = lds + (R::TWO ? R::OPERAND_VECS : 0);
+    put(lds, 0, x, 1);
+    lds_barrier();
 #pragma unroll 1
     for (int pair = 0; pair < VOC_PAIRS; ++pair) {
-        fetch(a.W[2 * pair + 1]);
-        floatx4 t[RT][NCOL];
+        const int d = 2 * pair + 1;
+        floatx4 t[RT][NCOL], b[RT];
+        biases(2 * pair, b);
+        conv_regs<XT, R, true>(weights, 2 * pair, ring, d, lds, 0, col0, lane, b, t);
+        ring_fill<R>(ring, weights, 2 * pair + 1);
+        if constexpr (!R::TWO) lds_barrier();     // every wave has read the old operand
+        __builtin_amdgcn_s_setprio(2);            // vector work goes ahead of the products of the wave it shares a SIMD with
+        put(lds1, 1, t, d);
+        __builtin_amdgcn_s_setprio(0);
+        biases(2 * pair + 1, b);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const floatx4 b1 = bias_of(a.bias[2 * pair], rt);
+        for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int ct = 0; ct < NCOL; ++ct) t[rt][ct] = b1;
-        }
-        conv_regs<XT, C, KS, NCOL, R::PADR>(R::W_LDS ? wbuf : a.W[2 * pair], 2 * pair + 1, lds, col0, lane, t);
-        __syncthreads();                          // every wave has read the old operand and the old weights
-        put(t);
-        stash();
-        __syncthreads();
-        if (pair + 1 < VOC_PAIRS) fetch(a.W[2 * pair + 2]);
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const floatx4 b2 = bias_of(a.bias[2 * pair + 1], rt);
-#pragma unroll
-            for (int ct = 0; ct < NCOL; ++ct) x[rt][ct] += b2;
-        }
-        conv_regs<XT, C, KS, NCOL, R::PADR>(R::W_LDS ? wbuf : a.W[2 * pair + 1], 1, lds, col0, lane, x);
+            for (int ct = 0; ct < NCOL; ++ct) x[rt][ct] += b[rt];
+        lds_barrier();
+        conv_regs<XT, R, false>(weights, 2 * pair + 1, ring, 1, lds1, 1, col0, lane, b, x);
         if (pair + 1 < VOC_PAIRS) {
-            __syncthreads();
-            put(x);
-            stash();
-            __syncthreads();
+            ring_fill<R>(ring, weights, 2 * pair + 2);
+            if constexpr (!R::TWO) lds_barrier();
+            __builtin_amdgcn_s_setprio(2);
+            put(lds, 0, x, 1);
+            __builtin_amdgcn_s_setprio(0);
+            lds_barrier();
         }
     }
-    if (!rows_ok) return;
+    const int o0 = R::H, o1 = min(R::H + TP, valid - pbase);  // positions of the region that are this tile's output
+    const int c = column();
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int ct = 0; ct < NCOL; ++ct) {
-            const int j = col0 + ct * 16 + n, p = pbase + j;
-            if (j >= R::H && j < R::H + TP && p < valid)
-                *reinterpret_cast<floatx4*>(a.out + (wbase + p) * C + rt * 16 + 4 * g) = x[rt][ct];
+            const int j = pos(c, rt, ct, 1);
+            if (j >= o0 && j < o1) *reinterpret_cast<floatx4*>(out + byte_at(pbase + j, rt)) = x[rt][ct];
         }
 }
 
-// grid = (tiles, windows, 3): the three residual blocks (kernels 3, 7, 11) of a stage
-template <typename XT, int C, int TP>
-__global__ __launch_bounds__(VC_THREADS) void k_vres(VrArgs3 a3, const int* __restrict__ len, int rate, int window)
+// The three residual blocks (kernels 3, 7, 11) of a stage: grid = (tiles, windows, 3), the longest first.
+template <typename XT, int C, int TP, bool HALO>
+__global__ __launch_bounds__((VrGeom<XT, C, 3, TP, HALO>::THREADS), C == 8 ? (sizeof(XT) == 2 ? 4 : 3) : 2) void k_vres(VrArgs3 a3, const int* __restrict__ len, int rate, int window)
 {
     extern __shared__ uint4 lds_dyn[];
     const int w = blockIdx.y, valid = len[w] * rate, p0 = blockIdx.x * TP;
     if (p0 >= valid) return;
     const size_t wbase = (size_t)w * window * rate;
-    if (blockIdx.z == 0) resblock_tile<XT, C, 3, TP>(a3.b[0], valid, wbase, p0, lds_dyn);
-    else if (blockIdx.z == 1) resblock_tile<XT, C, 7, TP>(a3.b[1], valid, wbase, p0, lds_dyn);
-    else resblock_tile<XT, C, 11, TP>(a3.b[2], valid, wbase, p0, lds_dyn);
+    if (blockIdx.z == 2) resblock_tile<XT, C, 3, TP, HALO>(a3.b[0], valid, wbase, p0, lds_dyn);
+    else if (blockIdx.z == 1) resblock_tile<XT, C, 7, TP, HALO>(a3.b[1], valid, wbase, p0, lds_dyn);
+    else resblock_tile<XT, C, 11, TP, HALO>(a3.b[2], valid, wbase, p0, lds_dyn);
 }
 
-// One workgroup per window: rows [0, ov) <- tail(M_pre) of the slot (if the request has a previous chunk), then M_cur;
-// the slot's tail becomes M_cur's last ov frames (Eq. 4) unless this was the request's last chunk.
+// Rows [0, ov) of a window <- tail(M_pre) of the slot (if the request has a previous chunk), then M_cur; the slot's tail becomes
+// M_cur's last ov frames (Eq. 4) unless this was the request's last chunk.  grid = (windows, pieces of 256 threads of a window),
+// four channels of a frame per thread, requested as four words (the caller's frames need only be aligned to them); the thread that
+// copies a piece of the old tail writes the new one.  One workgroup per window took 5.1 us for one window and 7.1 us for 64.
 __global__ __launch_bounds__(256) void k_voc_splice(VocBatch b, const float* __restrict__ d_mel, float* __restrict__ x_mel,
                                                     float* __restrict__ m_tail, int* __restrict__ len, int ov, int window)
 {
-    const int w = blockIdx.x, tid = threadIdx.x;
+    const int w = blockIdx.x, e = (blockIdx.y * 256 + threadIdx.x) * 4;
     const int nf = b.n_frames[w], hp = b.has_prev[w], last = b.last[w];
-    const float* src = d_mel + (size_t)b.src_row[w] * VOC_N_MEL;
-    float* dst = x_mel + (size_t)w * window * VOC_N_MEL;
-    float* tail = m_tail + (size_t)b.slot[w] * ov * VOC_N_MEL;
     const int ovw = hp ? ov : 0;
-    for (int e = tid; e < ov * VOC_N_MEL; e += 256) {
-        if (hp) dst[e] = tail[e];
-        if (!last) tail[e] = src[(size_t)(nf - ov) * VOC_N_MEL + e];
+    if (e == 0) len[w] = ovw + nf;
+    const float* src = d_mel + (size_t)b.src_row[w] * VOC_N_MEL;
+    float* tail = m_tail + (size_t)b.slot[w] * ov * VOC_N_MEL;
+    float4 v;
+    if (e < ovw * VOC_N_MEL) v = *reinterpret_cast<const float4*>(tail + e);
+    else {
+        const float* p = src + min(e, (ovw + nf) * VOC_N_MEL - 4) - ovw * VOC_N_MEL;
+        v = make_float4(p[0], p[1], p[2], p[3]);
     }
-    for (int e = tid; e < nf * VOC_N_MEL; e += 256) dst[(size_t)ovw * VOC_N_MEL + e] = src[e];
-    if (tid == 0) len[w] = ovw + nf;
+    if (e < ov * VOC_N_MEL && !last) {                          // nf >= ov here
+        const float* p = src + (nf - ov) * VOC_N_MEL + e;
+        *reinterpret_cast<float4*>(tail + e) = make_float4(p[0], p[1], p[2], p[3]);
+    }
+    if (e < (ovw + nf) * VOC_N_MEL) *reinterpret_cast<float4*>(x_mel + (size_t)w * window * VOC_N_MEL + e) = v;
 }
 
 // grid = (frames of a window, windows), one sample per thread.  The thread that owns sample i of the overlap
@@ -446,31 +552,43 @@ void conv_launch(const VcArgs& a, const int* len, int rate, int window, int n_wi
     hipLaunchKernelGGL((k_vconv<XT, CIN, ROWS, COUT, KS, EPI, PRE_ACT, SRC3, U, SHORT>), grid, dim3(VC_THREADS), 0, s, a, len, rate, window);
 }
 
-template <typename XT, int C, int LEVEL>
+template <typename XT, int C, int TP, bool HALO>
 hipError_t blocks_launch_tp(const VrArgs3& a, const int* len, int rate, int window, int n_windows, hipStream_t s)
 {
-    constexpr int TP = vr_tp<C, LEVEL>();
-    constexpr int L3 = VrGeom<XT, C, 3, TP>::BYTES, L7 = VrGeom<XT, C, 7, TP>::BYTES, L11 = VrGeom<XT, C, 11, TP>::BYTES;
+    constexpr int L3 = VrGeom<XT, C, 3, TP, HALO>::BYTES, L7 = VrGeom<XT, C, 7, TP, HALO>::BYTES, L11 = VrGeom<XT, C, 11, TP, HALO>::BYTES;
     constexpr int LDS = L3 > L7 ? (L3 > L11 ? L3 : L11) : (L7 > L11 ? L7 : L11);      // the three kernels share a launch
-    auto kern = k_vres<XT, C, TP>;
+    auto kern = k_vres<XT, C, TP, HALO>;
     static bool attr_set = false;                            // dynamic LDS above 64 KB has to be allowed once per kernel
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const dim3 grid((window * rate + TP - 1) / TP, n_windows, VOC_BLOCKS);
-    hipLaunchKernelGGL(kern, grid, dim3(VC_THREADS), LDS, s, a, len, rate, window);
+    const dim3 grid(HALO ? (window * rate + TP - 1) / TP : 1, n_windows, VOC_BLOCKS);
+    hipLaunchKernelGGL(kern, grid, dim3(VrGeom<XT, C, 3, TP, HALO>::THREADS), LDS, s, a, len, rate, window);
     return hipSuccess;
 }
+
+// Positions per workgroup of the three tilings: small batches take half of the large tiles, a request or two a quarter -- more
+// workgroups, each with a shorter chain, and a larger share of halo.
+template <int C, int LEVEL> constexpr int vr_tp() { return (C >= 32 ? 256 : 512) >> LEVEL; }
+// With 64 channels (8 positions a frame) the halo of a tile of 128 doubles its work.  A window of up to 384 positions fits a
+// workgroup's registers and LDS and needs none: a CU per window and block, which pays from a few dozen windows on
+// (64 windows: 58 us a launch in tiles of 128, 43 whole).
+constexpr int VR_WHOLE = 384;
+constexpr int VR_WHOLE_FROM = 48;                // windows from which it is used
+constexpr int VR_SMALL_BELOW = 1024;             // workgroups of the large tiling below which the half tiles are used
+constexpr int VR_TINY_BELOW = 128;               // ... and the quarter tiles
 
 template <typename XT, int C>
 hipError_t blocks_launch(const VrArgs3& a, const int* len, int rate, int window, int n_windows, hipStream_t s)
 {
+    if constexpr (C == 64)
+        if (window * rate <= VR_WHOLE && n_windows >= VR_WHOLE_FROM) return blocks_launch_tp<XT, C, VR_WHOLE, false>(a, len, rate, window, n_windows, s);
     const long wgs = (long)((window * rate + vr_tp<C, 0>() - 1) / vr_tp<C, 0>()) * n_windows * VOC_BLOCKS;
-    return wgs < VR_TINY_BELOW    ? blocks_launch_tp<XT, C, 2>(a, len, rate, window, n_windows, s)
-           : wgs < VR_SMALL_BELOW ? blocks_launch_tp<XT, C, 1>(a, len, rate, window, n_windows, s)
-                                  : blocks_launch_tp<XT, C, 0>(a, len, rate, window, n_windows, s);
+    return wgs < VR_TINY_BELOW    ? blocks_launch_tp<XT, C, vr_tp<C, 2>(), true>(a, len, rate, window, n_windows, s)
+           : wgs < VR_SMALL_BELOW ? blocks_launch_tp<XT, C, vr_tp<C, 1>(), true>(a, len, rate, window, n_windows, s)
+                                  : blocks_launch_tp<XT, C, vr_tp<C, 0>(), true>(a, len, rate, window, n_windows, s);
 }
 
 template <typename XT, int S>
@@ -485,16 +603,13 @@ hipError_t stage_launch(const VocoderPtrs& d, int n_windows, hipStream_t s)
     up.out = d.y;
     up.W = reinterpret_cast<const uint4*>(d.up_w[S]);
     up.bias = d.up_b[S];
-    up.dil = 1;
     conv_launch<XT, CIN, U * C, C, 3, EPI_UP, true, (S > 0), U, (S == 0)>(up, d.len, rate_in, d.window, n_windows, s);
     VrArgs3 rb{};
     for (int b = 0; b < VOC_BLOCKS; ++b) {
         rb.b[b].in = d.y;
         rb.b[b].out = d.r[b];
-        for (int i = 0; i < 2 * VOC_PAIRS; ++i) {
-            rb.b[b].W[i] = reinterpret_cast<const uint4*>(d.res_w[S][b][i]);
-            rb.b[b].bias[i] = d.res_b[S][b][i];
-        }
+        rb.b[b].W = reinterpret_cast<const uint4*>(d.res_w[S][b]);
+        rb.b[b].bias = d.res_b[S][b];
     }
     return blocks_launch<XT, C>(rb, d.len, rate, d.window, n_windows, s);
 }
@@ -507,7 +622,6 @@ hipError_t generator_typed(const VocoderPtrs& d, int n_windows, hipStream_t s)
     pre.out = d.x0;
     pre.W = reinterpret_cast<const uint4*>(d.pre_w);
     pre.bias = d.pre_b;
-    pre.dil = 1;
     conv_launch<XT, VOC_N_MEL, VOC_C0, VOC_C0, VOC_K_PRE, EPI_PLAIN, false, false, 1, true>(pre, d.len, 1, d.window, n_windows, s);
     hipError_t e = stage_launch<XT, 0>(d, n_windows, s);
     if (e == hipSuccess) e = stage_launch<XT, 1>(d, n_windows, s);
@@ -521,7 +635,6 @@ hipError_t generator_typed(const VocoderPtrs& d, int n_windows, hipStream_t s)
     post.out = d.audio;
     post.W = reinterpret_cast<const uint4*>(d.post_w);
     post.bias = d.post_b;
-    post.dil = 1;
     conv_launch<XT, voc_channels(VOC_STAGES - 1), 16, 1, VOC_K_POST, EPI_POST, true, true, 1, false>(post, d.len, VOC_HOP, d.window, n_windows, s);
     return hipGetLastError();
 }
@@ -530,7 +643,7 @@ hipError_t generator_typed(const VocoderPtrs& d, int n_windows, hipStream_t s)
 
 hipError_t launch_vocoder_splice(const VocoderPtrs& d, const VocBatch& b, const float* d_mel, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_voc_splice, dim3(b.n), dim3(256), 0, s, b, d_mel, d.x_mel, d.m_tail, d.len, d.overlap, d.window);
+    hipLaunchKernelGGL(k_voc_splice, dim3(b.n, (d.window * VOC_N_MEL + 1023) / 1024), dim3(256), 0, s, b, d_mel, d.x_mel, d.m_tail, d.len, d.overlap, d.window);
     return hipGetLastError();
 }
 

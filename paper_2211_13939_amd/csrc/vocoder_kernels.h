@@ -19,14 +19,16 @@ constexpr int voc_rate(int s) { return s < 2 ? 8 : 2; }
 constexpr int voc_block_k(int b) { return b == 0 ? 3 : (b == 1 ? 7 : 11); }
 constexpr int voc_dil(int p) { return 2 * p + 1; }
 constexpr int voc_channels(int s) { return VOC_C0 >> (s + 1); }              // channels after stage s
+// residual blocks of this many channels form pairs of positions: 2 C GEMM rows = (position of the pair, channel), k + 1 taps
+constexpr bool voc_paired(int channels) { return channels <= 16; }
 constexpr int voc_cum_rate(int s) { return s == 0 ? 8 : (s == 1 ? 64 : (s == 2 ? 128 : 256)); }   // positions per frame after stage s
 
 struct VocoderPtrs {
     // weights in MFMA A-fragment order (weight dtype), k = tap * C_in + channel; biases fp32
     const void* pre_w;  const float* pre_b;
     const void* up_w[VOC_STAGES];  const float* up_b[VOC_STAGES];     // rows = phase * C_out + channel, taps = input offsets -1, 0, +1
-    const void* res_w[VOC_STAGES][VOC_BLOCKS][2 * VOC_PAIRS];
-    const float* res_b[VOC_STAGES][VOC_BLOCKS][2 * VOC_PAIRS];
+    const void* res_w[VOC_STAGES][VOC_BLOCKS];      // a block's six convolutions one after the other, [2 pair + {0: dilated, 1: plain}]
+    const float* res_b[VOC_STAGES][VOC_BLOCKS];     // [2 * VOC_PAIRS][channels]
     const void* post_w; const float* post_b;
     const float* alpha; const float* beta;    // [overlap * 256] fade-in / fade-out
     float* m_tail;      // [max_requests][overlap][n_mel]   tail(M_pre) of every state slot

@@ -276,3 +276,28 @@ def test_largest_batch_of_short_chunks():
     with pytest.raises(binding.TtsError):
         voc.run([a[0]] * 257, list(range(256)) + [0], [FIRST] * 257)
     voc.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n,window", [(48, 48), (48, 49), (47, 48), (11, 67)])
+def test_windows_around_the_tiles_of_the_residual_blocks(bf16, n, window):
+    """Windows whose ends fall next to the ends of tiles and regions (whole windows of up to 48 frames from 48 windows on, tiles
+    with a halo otherwise; 32, 64 and 128 positions a column tile): every response equals, bit for bit, the same chunk's alone,
+    and the oracle's for the shortest, two odd ones and the longest."""
+    from oracle import oracle as orc
+    w = synth.make_vocoder_weights(bf16=bf16)
+    rng = np.random.default_rng(29)
+    lens = [1, 2, 3, window - 1, window] + [int(k) for k in rng.integers(1, window + 1, size=n - 5)]
+    mels = [_mel(rng, k) for k in lens]
+    say(f"case vocoder tiles: {n} windows of up to {window} frames, {'bf16' if bf16 else 'fp32'}")
+    cfg = dict(overlap=0, max_chunk=window, bf16=bf16)
+    voc = binding.Vocoder(binding.make_vocoder_config(max_requests=n, max_batch=n, **cfg), w)
+    got = voc.run(mels, list(range(n)), [FIRST | LAST] * n)
+    voc.close()
+    solo = binding.Vocoder(binding.make_vocoder_config(max_requests=1, max_batch=1, **cfg), w)
+    for k in range(0, n, 5 if n > 20 else 1):
+        np.testing.assert_array_equal(solo.run([mels[k]], [0], [FIRST | LAST])[0], got[k])
+    solo.close()
+    W = orc.VocoderWeights(w)
+    for k in (0, 2, 3, 4):
+        assert np.abs(got[k] - orc.generator(W, mels[k])).max() <= (TOL_BF16 if bf16 else TOL_F32)
