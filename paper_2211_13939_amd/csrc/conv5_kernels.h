@@ -129,123 +129,251 @@ __global__ __launch_bounds__(PN_THREADS) void k_pn_conv(
     }
 }
 
-// The same layer for large batches.  The kernel above spreads a small batch over many workgroups (one
-// row tile each, K split over the waves) but pulls 80 KB of weights per 160 MFMAs; here a workgroup owns
-// 8 row tiles (one per wave, no K split, no reduction) and PN_WCT column tiles, whose staged columns in LDS
-// serve all eight waves: 8 x 80 KB of weights for 8 x 80 x PN_WCT MFMAs.
-constexpr int PN_WCT = 4;
-template <typename XT, int CIN, int COUT, int EPI>
-__global__ __launch_bounds__(PN_THREADS) void k_pn_conv_wide(
-    const uint4* __restrict__ Wfrag, const float* __restrict__ bias, const uint4* __restrict__ Xin, XT* __restrict__ Xout,
-    const int* __restrict__ cmeta, int n_ctiles, const float* __restrict__ mel, int n_mel, const int* __restrict__ orow,
-    float* __restrict__ out)
+// The same layer for large batches, and (TAPS = 1) the encoder's input projection: a workgroup owns WR x RPW row tiles and WC x CTW
+// column tiles, RPW x CTW of them per wave.  K is not split, so nothing is reduced.  The columns are staged a few channel
+// fragments at a time, the next ones on their way while the present ones are in use, all taps of a chunk before the next chunk.
+//   * What a compute unit can take decides the shape.  Per k step (64 bytes of k) a wave fetches RPW KB of weights (16 cycles of
+//     the unit's L1 a KB), reads CTW KB of operands from LDS (4.4 cycles a KB where nothing conflicts) and spends 17 RPW CTW
+//     cycles in products: 2 x 2 waves of 2 x 4 tiles each take 128, 70 and 136 cycles of the unit.
+//   * LDS holds a plane per 16 bytes of channels, rows = columns, planes a multiple of 16 pieces apart: the lanes of a B fragment
+//     (16 columns x 4 pieces) then meet every bank once.  Operands are requested two steps ahead.
+//   * A tap that leaves its window reads a row of zeros: an address chosen once per tap and chunk, not a mask on every operand
+//     (a vector instruction beside a product costs it two to four cycles).
+// The sums are the same whatever the tile: k in the order chunk, tap, fragment, on top of the bias.
+constexpr int CC_BUFS = 2, CC_AHEAD = 2;
+template <typename XT, int CIN, int TAPS, int CT, int WAVES> struct ColGeom {
+    static constexpr int NKF = CIN / Frag<XT>::KB, NKT = TAPS * NKF;
+    static constexpr int CF = NKF % 4 == 0 ? 4 : 3;            // channel fragments per chunk
+    static constexpr int NCH = NKF / CF;
+    static constexpr int NK = TAPS * CF;                       // k steps per chunk
+    static constexpr int THREADS = WAVES * 64;
+    static constexpr int HALO = TAPS / 2;
+    static constexpr int ROWS = CT * 16 + 2 * HALO;            // staged columns; row ROWS is zero
+    static constexpr int PLANE = (ROWS + 1 + 15) / 16 * 16;
+    static constexpr int BUF_VECS = CF * 4 * PLANE;
+    static constexpr int PIECES = CF * 4 * ROWS;
+    static constexpr int PER = (PIECES + THREADS - 1) / THREADS;
+    static constexpr int LDS = CC_BUFS * BUF_VECS * 16;
+    static constexpr int AHEAD = NK % 5 == 0 ? 5 : NK;         // weight fragments in flight (divides NK: the ring is static)
+    static_assert(NKF % CF == 0 && NK % AHEAD == 0, "whole chunks");
+};
+
+enum { CC_TANH = PN_EPI_TANH, CC_LAST = PN_EPI_LAST, CC_RELU = PN_EPI_RELU, CC_XPROJ = 3 };
+
+struct ColArgs {
+    const uint4* W;           // A-fragment order, k = tap * CIN + channel
+    const uint4* W1;          // CC_XPROJ: the second half of the rows
+    const float* bias;
+    const float* bias1;
+    const uint4* Xin;
+    void* Xout;
+    const int* cmeta;
+    int n_ctiles;
+    const float* mel;         // CC_LAST
+    int n_mel;
+    const int* orow;
+    float* out;               // CC_LAST: [rows][n_mel]; CC_XPROJ: [2][max_cols][COUT / 2]
+    int n_col, max_cols;      // CC_XPROJ
+};
+
+// grid = (row groups, ceil(column tiles / CT))
+template <typename XT, int CIN, int COUT, int TAPS, int EPI, int WR, int WC, int RPW, int CTW>
+__global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
 {
-    constexpr int KB = Frag<XT>::KB, EPL = Frag<XT>::EPL;
-    constexpr int NKF = CIN / KB, NKT = PN_TAPS * NKF;
-    constexpr int ROWS = PN_WCT * 16 + 2 * PN_HALO;
-    constexpr int LD = CIN * (int)sizeof(XT) + 16;
-    constexpr int NRT = COUT / 16;
-    extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // ROWS * LD bytes
-    unsigned char* s_x = s_dyn;
+    constexpr int CT = WC * CTW;
+    using R = ColGeom<XT, CIN, TAPS, CT, WR * WC>;
+    constexpr int NKF = R::NKF, CF = R::CF, NK = R::NK, AHEAD = R::AHEAD;
+    extern __shared__ uint4 s_cols[];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int n = lane & 15, g = lane >> 4;
+    const int rt_all = (blockIdx.x * WR + wave % WR) * RPW, cw = wave / WR * CTW;      // the wave's first row and column tile
+    const bool half = EPI == CC_XPROJ && rt_all >= COUT / 32;
+    const int rt0 = half ? rt_all - COUT / 32 : rt_all;
+    const int ct0 = blockIdx.y * CT, n_col_pad = p.n_ctiles * 16, col_first = ct0 * 16 - R::HALO;
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int jl = lane & 15, g = lane >> 4;
-    const int rt = blockIdx.x * PN_WAVES + wave;           // this wave's row tile (may lie beyond the last one)
-    const bool row_on = rt < NRT;
-    const int rtc = row_on ? rt : NRT - 1;
-    const int ct0 = blockIdx.y * PN_WCT;
-    const int n_col_pad = n_ctiles * 16;
-    const int col_first = ct0 * 16 - PN_HALO;
-
-    for (int p = tid; p < ROWS * NKF * 4; p += PN_THREADS) {
-        const int row = p / (NKF * 4), rem = p - row * (NKF * 4);
-        const int cf = rem >> 2, gg = rem & 3;
-        const int col = col_first + row;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (col >= 0 && col < n_col_pad) v = Xin[xfrag(NKF, col >> 4, cf, (col & 15) + 16 * gg)];
-        *reinterpret_cast<uint4*>(&s_x[row * LD + (cf * KB + gg * EPL) * (int)sizeof(XT)]) = v;
-    }
-    int tapmask[PN_WCT];
+    // a fragment's place is a scalar offset: all weight loads share one address register
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(half ? p.W1 : p.W), 0, COUT / (EPI == CC_XPROJ ? 32 : 16) * R::NKT * 1024, BUFFER_RSRC_RAW);
+    auto weight = [&](int chunk, int i, int r) __attribute__((always_inline)) {       // k step i of a chunk
+        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, ((rt0 + r) * R::NKT + i / CF * NKF + chunk * CF + i % CF) * 1024, 0);
+        return make_uint4(v.x, v.y, v.z, v.w);
+    };
+    // This thread's pieces of a chunk: piece = (plane, column).  The activations are read through a descriptor that begins at the tile
+    // in front of the workgroup's (byte offsets stay small); a column outside them has an offset past its end, and reads zeros.
+    const int tile0 = max(ct0 - 1, 0);
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(p.Xin + xfrag(NKF, tile0, 0, 0)), 0,
+                                                                       min(p.n_ctiles - tile0, CT + 2) * NKF * 1024, BUFFER_RSRC_RAW);
+    unsigned from[R::PER];
 #pragma unroll
-    for (int c = 0; c < PN_WCT; ++c) {
-        const int col = min((ct0 + c) * 16 + jl, n_col_pad - 1);
-        const int m = cmeta[col];
-        const int t = m & 0xFFFF, T = m >> 16;
-        int bits = 0;
-#pragma unroll
-        for (int d = -PN_HALO; d <= PN_HALO; ++d) bits |= (t + d >= 0 && t + d < T) ? (1 << (d + PN_HALO)) : 0;
-        tapmask[c] = bits;
+    for (int i = 0; i < R::PER; ++i) {
+        const int idx = min(i * R::THREADS + tid, R::PIECES - 1), plane = idx / R::ROWS, col = col_first + idx - plane * R::ROWS;
+        const bool in = col >= 0 && col < n_col_pad;
+        from[i] = in ? (unsigned)xfrag(NKF, (col >> 4) - tile0, plane >> 2, (col & 15) + 16 * (plane & 3)) * 16u : 0x80000000u;
     }
-    const floatx4 bias4 = *reinterpret_cast<const floatx4*>(bias + rtc * 16 + 4 * g);
+    uint4 st[R::PER];
+    auto request = [&](int chunk) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < R::PER; ++i) {
+            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)from[i], chunk * CF * 1024, 0);
+            st[i] = make_uint4(v.x, v.y, v.z, v.w);
+        }
+    };
+    auto stash = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < R::PER; ++i) {
+            const int idx = i * R::THREADS + tid, plane = idx / R::ROWS;
+            if ((i + 1) * R::THREADS <= R::PIECES || idx < R::PIECES) s_cols[buf * R::BUF_VECS + plane * R::PLANE + idx - plane * R::ROWS] = st[i];
+        }
+    };
+    request(0);
+    uint4 ring[AHEAD][RPW];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) ring[i][r] = weight(0, i, r);
+    for (int i = tid; i < CC_BUFS * CF * 4; i += R::THREADS) s_cols[i * R::PLANE + R::ROWS] = make_uint4(0, 0, 0, 0);
+    // which taps stay inside the column's own window (bit d + HALO for column offset d)
+    int taps[CTW];
+    if constexpr (TAPS > 1) {
+#pragma unroll
+        for (int c = 0; c < CTW; ++c) {
+            const int m = p.cmeta[min((ct0 + cw + c) * 16 + n, n_col_pad - 1)];
+            const int t = m & 0xFFFF, T = m >> 16;
+            int bits = 0;
+#pragma unroll
+            for (int d = -R::HALO; d <= R::HALO; ++d) bits |= (t + d >= 0 && t + d < T) ? (1 << (d + R::HALO)) : 0;
+            taps[c] = bits;
+        }
+    }
+    floatx4 acc[RPW][CTW];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+        const floatx4 b = *reinterpret_cast<const floatx4*>((half ? p.bias1 : p.bias) + (rt0 + r) * 16 + 4 * g);
+#pragma unroll
+        for (int c = 0; c < CTW; ++c) acc[r][c] = b;
+    }
+    stash(0);
     __syncthreads();
-
-    floatx4 acc[PN_WCT];
-#pragma unroll
-    for (int c = 0; c < PN_WCT; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // weights of the wave's row tile stream through registers, PF fragments ahead
-    constexpr int PF = 16;
-    uint4 a[PF];
-#pragma unroll
-    for (int i = 0; i < PF; ++i) a[i] = Wfrag[xfrag(NKT, rtc, i < NKT ? i : NKT - 1, lane)];
 #pragma unroll 1
-    for (int f0 = 0; f0 < NKT; f0 += PF) {
+    for (int chunk = 0; chunk < R::NCH; ++chunk) {
+        const int next = min(chunk + 1, R::NCH - 1);           // the last chunk requests its own first weights again, and drops them
+        if (chunk + 1 < R::NCH) request(chunk + 1);
+        const uint4* buf = s_cols + (chunk & 1) * R::BUF_VECS + g * R::PLANE;
+        constexpr int NB = CC_AHEAD + 1;
+        uint4 bv[NB][CTW];
+        int row[CTW];
+        auto operands = [&](int i) __attribute__((always_inline)) {
+            const int tap = i / CF;
+            if (i % CF == 0) {
 #pragma unroll
-        for (int i = 0; i < PF; ++i) {
-            const int f = f0 + i;
-            const uint4 af = a[i];
-            a[i] = Wfrag[xfrag(NKT, rtc, min(f + PF, NKT - 1), lane)];   // unconditional: past the end it re-reads the last one
-            if (f < NKT) {
-                const int tap = f / NKF, cf = f - tap * NKF;
+                for (int c = 0; c < CTW; ++c) row[c] = TAPS == 1 || ((taps[c] >> tap) & 1) ? (cw + c) * 16 + n + tap : R::ROWS;
+            }
 #pragma unroll
-                for (int c = 0; c < PN_WCT; ++c) {
-                    uint4 b = *reinterpret_cast<const uint4*>(&s_x[(c * 16 + jl + tap) * LD + (cf * KB + g * EPL) * (int)sizeof(XT)]);
-                    if (!((tapmask[c] >> tap) & 1)) b = make_uint4(0, 0, 0, 0);
-                    acc[c] = mfma_frag<XT>(af, b, acc[c]);
+            for (int c = 0; c < CTW; ++c) bv[i % NB][c] = buf[(i % CF) * 4 * R::PLANE + row[c]];
+        };
+#pragma unroll
+        for (int i = 0; i < CC_AHEAD; ++i) operands(i);
+#pragma unroll
+        for (int i = 0; i < NK; ++i) {
+            uint4 af[RPW];
+#pragma unroll
+            for (int r = 0; r < RPW; ++r) {
+                af[r] = ring[i % AHEAD][r];
+                ring[i % AHEAD][r] = i + AHEAD < NK ? weight(chunk, i + AHEAD, r) : weight(next, i + AHEAD - NK, r);
+            }
+            if (i + CC_AHEAD < NK) operands(i + CC_AHEAD);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < CTW; ++c)
+#pragma unroll
+                for (int r = 0; r < RPW; ++r) acc[r][c] = mfma_frag<XT>(af[r], bv[i % NB][c], acc[r][c]);
+        }
+        if (chunk + 1 < R::NCH) {
+            stash((chunk + 1) & 1);
+            lds_barrier();
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CTW; ++c) {
+        if (ct0 + cw + c >= p.n_ctiles) break;
+        const int col = (ct0 + cw + c) * 16 + n;
+        const int r_out = EPI == CC_LAST ? p.orow[col] : 0;
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+            const floatx4 y = acc[r][c];
+            const int ch = (rt0 + r) * 16 + 4 * g;
+            if constexpr (EPI == CC_XPROJ) {
+                if (col < p.n_col) *reinterpret_cast<floatx4*>(p.out + ((size_t)(half ? 1 : 0) * p.max_cols + col) * (COUT / 2) + ch) = y;
+            } else if constexpr (EPI == CC_LAST) {
+                if (r_out >= 0 && ch < p.n_mel) {
+                    const float4 m = *reinterpret_cast<const float4*>(p.mel + (size_t)col * p.n_mel + ch);
+                    *reinterpret_cast<float4*>(p.out + (size_t)r_out * p.n_mel + ch) = make_float4(m.x + y[0], m.y + y[1], m.z + y[2], m.w + y[3]);
                 }
+            } else {
+                const float y0 = pn_act<EPI>(y[0]), y1 = pn_act<EPI>(y[1]), y2 = pn_act<EPI>(y[2]), y3 = pn_act<EPI>(y[3]);
+                XT* dst = reinterpret_cast<XT*>(p.Xout) + xoff<XT>(COUT / Frag<XT>::KB, col, ch);
+                if constexpr (sizeof(XT) == 2) *reinterpret_cast<uint2*>(dst) = make_uint2(pack2<XT>(y0, y1), pack2<XT>(y2, y3));
+                else *reinterpret_cast<float4*>(dst) = make_float4(y0, y1, y2, y3);
             }
         }
     }
-    if (!row_on) return;
-#pragma unroll
-    for (int c = 0; c < PN_WCT; ++c) {
-        if (ct0 + c >= n_ctiles) break;
-        const floatx4 y = acc[c] + bias4;
-        const int col = (ct0 + c) * 16 + jl;
-        const int ch = rt * 16 + 4 * g;
-        if constexpr (EPI != PN_EPI_LAST) {
-            const float y0 = pn_act<EPI>(y[0]), y1 = pn_act<EPI>(y[1]), y2 = pn_act<EPI>(y[2]), y3 = pn_act<EPI>(y[3]);
-            XT* dst = Xout + xoff<XT>(COUT / KB, col, ch);
-            if constexpr (sizeof(XT) == 2) *reinterpret_cast<uint2*>(dst) = make_uint2(pack2<XT>(y0, y1), pack2<XT>(y2, y3));
-            else *reinterpret_cast<float4*>(dst) = make_float4(y0, y1, y2, y3);
-        } else {
-            const int r = orow[col];
-            if (r >= 0 && ch < n_mel) {
-                const float4 m = *reinterpret_cast<const float4*>(mel + (size_t)col * n_mel + ch);
-                *reinterpret_cast<float4*>(out + (size_t)r * n_mel + ch) = make_float4(m.x + y[0], m.y + y[1], m.z + y[2], m.w + y[3]);
-            }
-        }
+}
+
+// 2 x 2 waves of two row tiles each; five waves of one where there are five (the PostNet's last layer); four waves of two row
+// tiles each in the input projection, which has few k steps and whose time is its stores (16 requests of 165 tokens 26.8 -> 16.2 us;
+// 2 x 2 waves 16.8, and 50.6 against 42.7 us for 64 requests)
+template <int COUT, int TAPS> struct ColWaves {
+    static constexpr bool FOUR = COUT / 16 % 4 == 0, SQUARE = FOUR && TAPS > 1;
+    static constexpr int WR = SQUARE ? 2 : FOUR ? 4 : COUT / 16, WC = SQUARE ? 2 : 1, RPW = FOUR ? 2 : 1, GROUPS = COUT / 16 / (WR * RPW);
+    static constexpr int CT_MOST = SQUARE ? 8 : FOUR ? 7 : 4;
+};
+
+template <typename XT, int CIN, int COUT, int TAPS, int EPI, int CT>
+inline hipError_t conv_cols_ct(const ColArgs& p, hipStream_t s)
+{
+    using V = ColWaves<COUT, TAPS>;
+    using R = ColGeom<XT, CIN, TAPS, CT, V::WR * V::WC>;
+    static_assert(V::GROUPS * V::WR * V::RPW * 16 == COUT && V::WR * V::WC <= 8 && CT % V::WC == 0, "whole row and column groups");
+    auto kern = k_conv_cols<XT, CIN, COUT, TAPS, EPI, V::WR, V::WC, V::RPW, CT / V::WC>;
+    static bool attr_set = false;                 // dynamic LDS above 64 KB has to be allowed once per kernel
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, R::LDS);
+        if (e != hipSuccess) return e;
+        attr_set = true;
     }
+    hipLaunchKernelGGL(kern, dim3(V::GROUPS, (p.n_ctiles + CT - 1) / CT), dim3(R::THREADS), R::LDS, s, p);
+    return hipGetLastError();
+}
+
+// Column tiles per workgroup: the fewest that leave no more workgroups than there are compute units, CT_MOST at most (up to there
+// the registers hold the sums and two workgroups share a CU's LDS)
+constexpr int CC_CUS = 256;
+template <typename XT, int CIN, int COUT, int TAPS, int EPI>
+inline hipError_t conv_cols(const ColArgs& p, hipStream_t s)
+{
+    using V = ColWaves<COUT, TAPS>;
+    auto fits = [&](int ct) { return V::GROUPS * ((p.n_ctiles + ct - 1) / ct) <= CC_CUS; };
+    if (fits(2)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 2>(p, s);
+    if (V::CT_MOST == 4 || fits(4)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 4>(p, s);
+    return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, V::CT_MOST>(p, s);
 }
 
 template <typename XT, int CIN, int COUT, int EPI>
 inline hipError_t conv_layer(bool wide, const void* W, const float* b, const void* xin, XT* xout, const int* cmeta, int n_ctiles,
                              const float* mel, int n_mel, const int* orow, float* out, hipStream_t s)
 {
-    // fewer row tiles than a wide workgroup has waves (the PostNet's last layer, 512 -> 80): the wide kernel would run on a
-    // few dozen workgroups with idle waves; the narrow one spreads the layer over the chip whatever the batch
-    if (COUT / 16 < PN_WAVES) wide = false;
     if (wide) {
-        constexpr int LDS = (PN_WCT * 16 + 2 * PN_HALO) * (CIN * (int)sizeof(XT) + 16);
-        auto kern = k_pn_conv_wide<XT, CIN, COUT, EPI>;
-        static bool attr_set = false;             // dynamic LDS above 64 KB has to be allowed once per kernel
-        if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-            if (e != hipSuccess) return e;
-            attr_set = true;
-        }
-        const dim3 grid((COUT / 16 + PN_WAVES - 1) / PN_WAVES, (n_ctiles + PN_WCT - 1) / PN_WCT);
-        hipLaunchKernelGGL(kern, grid, dim3(PN_THREADS), LDS, s, (const uint4*)W, b, (const uint4*)xin, xout, cmeta, n_ctiles,
-                           mel, n_mel, orow, out);
+        ColArgs p{};
+        p.W = (const uint4*)W;
+        p.bias = b;
+        p.Xin = (const uint4*)xin;
+        p.Xout = xout;
+        p.cmeta = cmeta;
+        p.n_ctiles = n_ctiles;
+        p.mel = mel;
+        p.n_mel = n_mel;
+        p.orow = orow;
+        p.out = out;
+        return conv_cols<XT, CIN, COUT, PN_TAPS, EPI>(p, s);
     } else {
         constexpr int CT = PnCT<XT>::value;
         const dim3 grid(COUT / 16, (n_ctiles + CT - 1) / CT);
@@ -255,8 +383,10 @@ inline hipError_t conv_layer(bool wide, const void* W, const float* b, const voi
     return hipGetLastError();
 }
 
-// batches of at least this many column tiles take the wide kernel (measured with 50-column windows, two-byte mode: the narrow
-// kernel is the faster one up to 75 column tiles - 25 tiles 43 against 71 us per PostNet round -, the wide one from 100)
-constexpr int PN_WIDE_FROM = 80;
+// Calls of at least this many column tiles take the kernel above.  It is the faster one from about 30 on (two-byte mode, 512 -> 512
+// layers, 75 tiles: 14.5 us in the narrow kernel, 10.7 in this one); the lines lie higher so that calls of a few short windows and a
+// window alone, which the narrow kernel serves, give the same bits up to there: the kernels differ in the order of their sums.
+constexpr int PN_WIDE_FROM = 40;
+template <typename XT> constexpr int enc_wide_from() { return sizeof(XT) == 2 ? 40 : 80; }
 
 }  // namespace tts

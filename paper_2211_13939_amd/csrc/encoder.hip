@@ -512,7 +512,7 @@ hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const 
 {
     constexpr int C = ENC_DIM;
     const int n_ctiles = (n_col + 15) / 16, n_col_pad = n_ctiles * 16;
-    const bool wide = n_ctiles >= PN_WIDE_FROM;
+    const bool wide = n_ctiles >= enc_wide_from<XT>();
     XT* x0 = reinterpret_cast<XT*>(d.act[0]);
     XT* x1 = reinterpret_cast<XT*>(d.act[1]);
     EncTables tb;
@@ -524,9 +524,23 @@ hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const 
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[1], d.conv_b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[2], d.conv_b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_enc_xproj<XT>), dim3(ENC_GATES / 16 / 4, n_ctiles, 2), dim3(256), 0, s, (const uint4*)d.w_ih[0], (const uint4*)d.w_ih[1],
-                       d.b[0], d.b[1], (const uint4*)x1, n_col, d.max_tokens, d.xproj);
-    e = hipGetLastError();
+    if (wide) {
+        ColArgs p{};
+        p.W = (const uint4*)d.w_ih[0];
+        p.W1 = (const uint4*)d.w_ih[1];
+        p.bias = d.b[0];
+        p.bias1 = d.b[1];
+        p.Xin = (const uint4*)x1;
+        p.n_ctiles = n_ctiles;
+        p.out = d.xproj;
+        p.n_col = n_col;
+        p.max_cols = d.max_tokens;
+        e = conv_cols<XT, C, 2 * ENC_GATES, 1, CC_XPROJ>(p, s);
+    } else {
+        hipLaunchKernelGGL((k_enc_xproj<XT>), dim3(ENC_GATES / 16 / 4, n_ctiles, 2), dim3(256), 0, s, (const uint4*)d.w_ih[0], (const uint4*)d.w_ih[1],
+                           d.b[0], d.b[1], (const uint4*)x1, n_col, d.max_tokens, d.xproj);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess) return e;
     if constexpr (sizeof(XT) == 2) {
         static bool attr_set = false;               // dynamic LDS above 64 KB has to be allowed once

@@ -125,6 +125,9 @@ template <int N> __device__ __forceinline__ void vm_in_flight_at_most()
     asm volatile("" ::: "memory");
 }
 
+// every LDS access of this wave is done, then all waves are here; loads from memory stay on their way
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Fragment geometry for element type T: a fragment is 64 bytes of k per row / column.
 template <typename T> struct Frag {
     static constexpr int KB = 64 / (int)sizeof(T);    // k elements per fragment

@@ -274,9 +274,6 @@ template <typename XT, int C, int KS, int TP, bool HALO> struct VrGeom {
     static_assert(HALO || !PAIR, "a pair's second position is missing at the region's first positions: they have to lie in a halo");
 };
 
-// every LDS access of this wave is done, then all waves are here; loads from memory stay on their way
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // The weights of a block's six convolutions in A-fragment order: a fragment's place is a scalar offset, so all of them share one
 // address register, and no pointer has to be loaded before a convolution's first fragment can be requested.
 template <typename R> struct VrWeights {

@@ -337,3 +337,37 @@ def test_packing_of_many_short_windows(bf16, n):
     for i in sorted({0, 1, n // 2, n - 2, n - 1}):
         np.testing.assert_array_equal(got[i], pn.run([wins[i]], [keeps[i]])[0])
     pn.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_column_tiles_of_the_large_batch_kernel(bf16):
+    """Ragged batches on both sides of every line of the rule that gives a workgroup its column tiles (from 40 tiles on; 64 and 128
+    tiles), with whole and barely begun last tiles: the same windows give the same bits in all of them, and the oracle's values."""
+    from oracle import oracle as orc
+    ws, bs = synth.make_postnet_weights(bf16=bf16)
+    W = orc.PostnetWeights(ws, bs)
+    rng = np.random.default_rng(41)
+    wins, total = [], 0
+    while total < 2049:
+        wins.append(rng.standard_normal((min(int(rng.integers(1, 51)), 2049 - total), 80)).astype(np.float32))
+        total += wins[-1].shape[0]
+    keeps = [min(10, w.shape[0] - 1) if i % 3 else 0 for i, w in enumerate(wins)]
+    pn = binding.Postnet(binding.make_postnet_config(max_columns=2064, bf16=bf16), ws, bs)
+    first = None
+    for columns in (625, 640, 1024, 1025, 2048, 2049):
+        n, left = 0, columns
+        while left >= wins[n].shape[0] and n + 1 < len(wins):
+            left -= wins[n].shape[0]
+            n += 1
+        cut = [w for w in wins[:n]] + ([wins[n][:left]] if left else [])
+        say(f"case postnet column tiles: {columns} columns in {len(cut)} windows, {'bf16' if bf16 else 'fp32'}")
+        got = pn.run(cut, keeps[:n] + ([0] if left else []))
+        if first is None:
+            first = got[:n]
+            for i in (0, 1, n // 2, n - 1):
+                assert np.abs(got[i] - orc.postnet_chunk(W, wins[i].astype(np.float64), keeps[i])).max() <= (TOL_BF16 if bf16 else TOL_F32)
+        for a, b in zip(first, got):
+            np.testing.assert_array_equal(a, b)
+        if left:
+            assert np.abs(got[n] - orc.postnet_chunk(W, cut[n].astype(np.float64), 0)).max() <= (TOL_BF16 if bf16 else TOL_F32)
+    pn.close()
