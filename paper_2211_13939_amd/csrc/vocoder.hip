@@ -69,11 +69,27 @@ template <> __device__ __forceinline__ void lds_put4<h16_t>(uint4* lds, int elem
     *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(lds) + elem) = u;
 }
 
+// Four channels of one position of the input: of one array, or of three whose mean is meant.
+struct Quad1 {
+    float4 v;
+    __device__ __forceinline__ float4 value() const { return v; }
+};
+struct Quad3 {
+    float4 v0, v1, v2;
+    __device__ __forceinline__ float4 value() const
+    {
+        constexpr float third = 1.0f / 3.0f;
+        return make_float4(((v0.x + v1.x) + v2.x) * third, ((v0.y + v1.y) + v2.y) * third, ((v0.z + v1.z) + v2.z) * third, ((v0.w + v1.w) + v2.w) * third);
+    }
+};
+
 // One tile of TP positions of one window, all ROWS output rows.
 //   valid  positions of this window that exist (input side); wbase = first position of the window in the arrays
 //   p0     first position of the tile inside the window
-template <typename XT, int CIN, int ROWS, int COUT, int KS, int TP, int EPI, bool PRE_ACT, bool SRC3, int U>
-__device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wbase, int p0, uint4* lds)
+//   fetch  (position that exists, channel / 4) -> Quad1 or Quad3
+//   emit   (position, sample): EPI_POST, instead of a store
+template <typename XT, int CIN, int ROWS, int COUT, int KS, int TP, int EPI, bool PRE_ACT, int U, typename FETCH, typename EMIT>
+__device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wbase, int p0, uint4* lds, FETCH fetch, EMIT emit)
 {
     using G = VcGeom<XT, CIN>;
     constexpr int KB = Frag<XT>::KB;
@@ -88,30 +104,21 @@ __device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wba
 
     // ---- stage positions [p0 - halo, p0 + TP + halo): activation and operand type applied once per element; a few pieces of every
     // thread are requested together, from clamped positions
-    constexpr int N_STAGE = nrows * C4, AT_ONCE = SRC3 ? 4 : 8;
+    using Quad = decltype(fetch(0, 0));
+    constexpr int N_STAGE = nrows * C4, AT_ONCE = sizeof(Quad) > 16 ? 4 : 8;
     for (int i0 = 0; i0 < N_STAGE; i0 += AT_ONCE * VC_THREADS) {
-        float4 v[AT_ONCE], v1[SRC3 ? AT_ONCE : 1], v2[SRC3 ? AT_ONCE : 1];
+        Quad v[AT_ONCE];
 #pragma unroll
         for (int i = 0; i < AT_ONCE; ++i) {
-            const int idx = min(i0 + i * VC_THREADS + tid, N_STAGE - 1), row = idx / C4, c4 = idx - row * C4;
-            const unsigned off = (unsigned)(min(max(p0 - halo + row, 0), valid - 1) * CIN + 4 * c4) * 4u;     // bytes from the window's first position
-            v[i] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.in0 + wbase * CIN) + off);
-            if constexpr (SRC3) {
-                v1[i] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.in1 + wbase * CIN) + off);
-                v2[i] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.in2 + wbase * CIN) + off);
-            }
+            const int idx = min(i0 + i * VC_THREADS + tid, N_STAGE - 1), row = idx / C4;
+            v[i] = fetch(min(max(p0 - halo + row, 0), valid - 1), idx - row * C4);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < AT_ONCE; ++i) {
             const int idx = i0 + i * VC_THREADS + tid, row = idx / C4, c4 = idx - row * C4;
             if (idx >= N_STAGE) break;
-            float4 u = v[i];
-            if constexpr (SRC3) {
-                constexpr float third = 1.0f / 3.0f;
-                u.x = ((u.x + v1[i].x) + v2[i].x) * third; u.y = ((u.y + v1[i].y) + v2[i].y) * third;
-                u.z = ((u.z + v1[i].z) + v2[i].z) * third; u.w = ((u.w + v1[i].w) + v2[i].w) * third;
-            }
+            float4 u = v[i].value();
             if constexpr (PRE_ACT) { u.x = lrelu(u.x); u.y = lrelu(u.y); u.z = lrelu(u.z); u.w = lrelu(u.w); }
             if ((unsigned)(p0 - halo + row) >= (unsigned)valid) u = make_float4(0.f, 0.f, 0.f, 0.f);
             lds_put4<XT>(lds, ((4 * c4 / G::EPL) * STRIDE + row) * G::EPL + 4 * c4 % G::EPL, u);
@@ -168,7 +175,7 @@ __device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wba
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
                     const int p = p0 + colbase + ct * 16 + n;
-                    if (p < valid) a.out[wbase + p] = tanhf_(acc[rg][ct][0] + b0);
+                    if (p < valid) emit(p, tanhf_(acc[rg][ct][0] + b0));
                 }
             } else {
                 const int co = EPI == EPI_UP ? row0 % COUT : row0;
@@ -187,7 +194,13 @@ __device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wba
     }
 }
 
-// grid = (tiles of a window, windows): one convolution of one kind
+// byte offset of 32 bits from a window's first position: a window is at most (4096 + 16) * 2048 values
+template <int CIN> __device__ __forceinline__ float4 quad_at(const float* window, int p, int c4)
+{
+    return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(window) + (unsigned)(p * CIN + 4 * c4) * 4u);
+}
+
+// grid = (tiles of a window, windows, row groups): one convolution of one kind
 template <typename XT, int CIN, int ROWS, int COUT, int KS, int EPI, bool PRE_ACT, bool SRC3, int U, bool SHORT>
 __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __restrict__ len, int rate, int window)
 {
@@ -195,7 +208,72 @@ __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __res
     __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
     const int w = blockIdx.y, valid = len[w] * rate, p0 = blockIdx.x * TP;
     if (p0 >= valid) return;
-    conv_tile<XT, CIN, ROWS, COUT, KS, TP, EPI, PRE_ACT, SRC3, U>(a, valid, (size_t)w * window * rate, p0, lds);
+    const size_t wbase = (size_t)w * window * rate;
+    const float *in0 = a.in0 + wbase * CIN, *in1 = SRC3 ? a.in1 + wbase * CIN : nullptr, *in2 = SRC3 ? a.in2 + wbase * CIN : nullptr;
+    auto fetch = [&](int p, int c4) __attribute__((always_inline)) {
+        if constexpr (SRC3) return Quad3{quad_at<CIN>(in0, p, c4), quad_at<CIN>(in1, p, c4), quad_at<CIN>(in2, p, c4)};
+        else return Quad1{quad_at<CIN>(in0, p, c4)};
+    };
+    conv_tile<XT, CIN, ROWS, COUT, KS, TP, EPI, PRE_ACT, U>(a, valid, wbase, p0, lds, fetch, [](int, float) {});
+}
+
+// The first layer, on the spliced windows [tail(M_pre), M_cur] (Eq. 3 line 1), which exist nowhere else: frames [0, ov) of a window
+// with a previous chunk come from the slot's tail, the others from the caller's chunk, four words at a time (his frames need only
+// be aligned to them).  Publishes the windows' lengths.  (A launch that wrote the windows to memory first took 2.9 us for one
+// window, 4.4 us for 64.)
+template <typename XT>
+__global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, const float* __restrict__ d_mel, const float* __restrict__ m_tail,
+                                                          int* __restrict__ len, int ov, int window)
+{
+    constexpr int CIN = VOC_N_MEL, KS = VOC_K_PRE, TP = vc_tp<XT, CIN, VOC_C0, (KS - 1) / 2, true>();
+    __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
+    const int w = blockIdx.y, ovw = b.has_prev[w] & VOC_HAS_PREV ? ov : 0, valid = ovw + b.n_frames[w], p0 = blockIdx.x * TP;
+    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) len[w] = valid;
+    if (p0 >= valid) return;
+    const float* mel = d_mel + ((ptrdiff_t)b.src_row[w] - ovw) * CIN;
+    const float* tail = m_tail + (size_t)b.slot[w] * ov * CIN;
+    auto fetch = [&](int p, int c4) __attribute__((always_inline)) {
+        const float* f = (p < ovw ? tail : mel) + p * CIN + 4 * c4;
+        return Quad1{make_float4(f[0], f[1], f[2], f[3])};
+    };
+    conv_tile<XT, CIN, VOC_C0, VOC_C0, KS, TP, EPI_PLAIN, false, 1>(a, valid, (size_t)w * window, p0, lds, fetch, [](int, float) {});
+}
+
+// The last layer, and what becomes of its samples S_cur: the first ov * 256 of a window with a previous chunk are fused with the
+// slot's tail(S_pre) (Eq. 3 line 2), the response goes to the caller, and the slot's tails become those of this chunk (Eq. 4) unless
+// it was the request's last.  Each slot has two tails of audio, which calls read and write in turn: the workgroups of a launch come in any order.
+// (The mel tail is written here because the first layer reads the old one.)  As a launch of its own behind the last layer this took 3.3 us
+// for one window, 4.5 us for 64.
+template <typename XT, bool SHORT>
+__global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, const float* __restrict__ alpha, const float* __restrict__ beta,
+                                                         float* __restrict__ s_tail, size_t s_tail_turn, float* __restrict__ d_audio,
+                                                         const float* __restrict__ d_mel, float* __restrict__ m_tail, int ov, int window)
+{
+    constexpr int CIN = voc_channels(VOC_STAGES - 1), KS = VOC_K_POST, TP = vc_tp<XT, CIN, 16, (KS - 1) / 2, SHORT>();
+    __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
+    const int w = blockIdx.y, flags = b.has_prev[w], nf = b.n_frames[w];
+    const bool hp = flags & VOC_HAS_PREV, last = b.last[w];
+    const int valid = ((hp ? ov : 0) + nf) * VOC_HOP, p0 = blockIdx.x * TP, N = ov * VOC_HOP;
+    if (p0 >= valid) return;
+    if (blockIdx.x == 0 && !last) {                            // nf >= ov here
+        const float* src = d_mel + (size_t)(b.src_row[w] + nf - ov) * VOC_N_MEL;
+        float* dst = m_tail + (size_t)b.slot[w] * ov * VOC_N_MEL;
+        for (int e = threadIdx.x; e < ov * VOC_N_MEL; e += VC_THREADS) dst[e] = src[e];
+    }
+    const size_t turn = flags & VOC_TURN ? s_tail_turn : 0, slot = (size_t)b.slot[w] * N;
+    const float* old_tail = s_tail + turn + slot;
+    float* new_tail = s_tail + (s_tail_turn - turn) + slot;
+    float* out = d_audio + b.out_off[w];
+    const int keep = valid - N, n_out = last ? valid : keep;
+    auto emit = [&](int i, float v) __attribute__((always_inline)) {
+        if (!last && i >= keep) new_tail[i - keep] = v;
+        if (i >= n_out) return;
+        out[i] = hp && i < N ? alpha[i] * v + beta[i] * old_tail[i] : v;
+    };
+    const size_t wbase = (size_t)w * window * VOC_HOP;
+    const float *in0 = a.in0 + wbase * CIN, *in1 = a.in1 + wbase * CIN, *in2 = a.in2 + wbase * CIN;
+    auto fetch = [&](int p, int c4) __attribute__((always_inline)) { return Quad3{quad_at<CIN>(in0, p, c4), quad_at<CIN>(in1, p, c4), quad_at<CIN>(in2, p, c4)}; };
+    conv_tile<XT, CIN, 16, 1, KS, TP, EPI_POST, true, 1>(a, valid, wbase, p0, lds, fetch, emit);
 }
 
 // ---------------------------------------------------------------------------
@@ -243,13 +321,17 @@ constexpr int VR_AHEAD = 4;
 template <typename XT, int C, int KS, int TP, bool HALO> struct VrGeom {
     using G = VcGeom<XT, C>;
     static constexpr bool PAIR = voc_paired(C);
-    static constexpr int RGROUPS = C == 64 ? 2 : 1;           // groups of rows, a quarter of the columns per wave in each
-    static constexpr int THREADS = RGROUPS * 256;
+    // Waves: groups of rows times groups of columns.  Every group of columns fetches the weights of its rows, 16 cycles of the
+    // compute unit's L1 a KB: where a region is small they would cost more than the products (64 channels, 128 positions, four
+    // groups: 352 KB a convolution of 11 taps, 5600 cycles against 3000), so there the waves share out the rows instead.
+    static constexpr int THREADS = C == 64 ? 512 : 256;
+    static constexpr int RGROUPS = C == 64 ? (TP < 128 ? 4 : 2) : C == 32 && TP < 128 ? 2 : 1;
+    static constexpr int CGROUPS = THREADS / 64 / RGROUPS;
     static constexpr int HALF = (KS - 1) / 2;
     static constexpr int H = HALO ? HALF * 12 : 0;            // sum over d = 1, 3, 5 of (d + 1) * HALF
     static constexpr int PW = PAIR ? 32 : 16;                 // positions per column tile
-    static constexpr int NCOL = (TP + 2 * H + 4 * PW - 1) / (4 * PW);     // column tiles per wave
-    static constexpr int W = 4 * PW * NCOL;                   // positions of the region
+    static constexpr int NCOL = (TP + 2 * H + CGROUPS * PW - 1) / (CGROUPS * PW);       // column tiles per wave
+    static constexpr int W = CGROUPS * PW * NCOL;             // positions of the region
     static constexpr int RT = (PAIR ? 2 * C : C) / 16 / RGROUPS;          // row tiles per wave
     static constexpr int TAPS = PAIR ? KS + 1 : KS;
     static constexpr int NK = TAPS * C / Frag<XT>::KB;
@@ -348,8 +430,8 @@ __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t
     constexpr int RT = R::RT, NCOL = R::NCOL;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
-    const int col0 = (wave & 3) * 16 * NCOL;     // this wave's first column of the region
-    const int rt0 = (wave >> 2) * RT;            // ... and its first row tile
+    const int col0 = wave % R::CGROUPS * 16 * NCOL;            // this wave's first column of the region
+    const int rt0 = wave / R::CGROUPS * RT;                    // ... and its first row tile
     const int pbase = p0 - R::H;                 // the region's first position inside the window
     // the lane's four rows of row tile rt: position s of the pair, channels ch .. ch + 3
     auto part = [&](int rt) __attribute__((always_inline)) { return !R::PAIR ? 0 : C == 8 ? g >> 1 : rt; };
@@ -482,54 +564,6 @@ __global__ __launch_bounds__((VrGeom<XT, C, 3, TP, HALO>::THREADS), C == 8 ? (si
     else resblock_tile<XT, C, 11, TP, HALO>(a3.b[2], valid, wbase, p0, lds_dyn);
 }
 
-// Rows [0, ov) of a window <- tail(M_pre) of the slot (if the request has a previous chunk), then M_cur; the slot's tail becomes
-// M_cur's last ov frames (Eq. 4) unless this was the request's last chunk.  grid = (windows, pieces of 256 threads of a window),
-// four channels of a frame per thread, requested as four words (the caller's frames need only be aligned to them); the thread that
-// copies a piece of the old tail writes the new one.  One workgroup per window took 5.1 us for one window and 7.1 us for 64.
-__global__ __launch_bounds__(256) void k_voc_splice(VocBatch b, const float* __restrict__ d_mel, float* __restrict__ x_mel,
-                                                    float* __restrict__ m_tail, int* __restrict__ len, int ov, int window)
-{
-    const int w = blockIdx.x, e = (blockIdx.y * 256 + threadIdx.x) * 4;
-    const int nf = b.n_frames[w], hp = b.has_prev[w], last = b.last[w];
-    const int ovw = hp ? ov : 0;
-    if (e == 0) len[w] = ovw + nf;
-    const float* src = d_mel + (size_t)b.src_row[w] * VOC_N_MEL;
-    float* tail = m_tail + (size_t)b.slot[w] * ov * VOC_N_MEL;
-    float4 v;
-    if (e < ovw * VOC_N_MEL) v = *reinterpret_cast<const float4*>(tail + e);
-    else {
-        const float* p = src + min(e, (ovw + nf) * VOC_N_MEL - 4) - ovw * VOC_N_MEL;
-        v = make_float4(p[0], p[1], p[2], p[3]);
-    }
-    if (e < ov * VOC_N_MEL && !last) {                          // nf >= ov here
-        const float* p = src + (nf - ov) * VOC_N_MEL + e;
-        *reinterpret_cast<float4*>(tail + e) = make_float4(p[0], p[1], p[2], p[3]);
-    }
-    if (e < (ovw + nf) * VOC_N_MEL) *reinterpret_cast<float4*>(x_mel + (size_t)w * window * VOC_N_MEL + e) = v;
-}
-
-// grid = (frames of a window, windows), one sample per thread.  The thread that owns sample i of the overlap
-// region reads the slot's old tail(S_pre)[i] before it writes the new one, so nothing races.
-__global__ __launch_bounds__(VOC_HOP) void k_voc_fade(VocBatch b, const float* __restrict__ audio, const float* __restrict__ alpha,
-                                                      const float* __restrict__ beta, float* __restrict__ s_tail,
-                                                      float* __restrict__ d_audio, int ov, int window)
-{
-    const int w = blockIdx.y, i = blockIdx.x * VOC_HOP + threadIdx.x;
-    const int hp = b.has_prev[w], last = b.last[w];
-    const int N = ov * VOC_HOP;
-    const int L = ((hp ? ov : 0) + b.n_frames[w]) * VOC_HOP;
-    if (i >= L) return;
-    const float* S = audio + (size_t)w * window * VOC_HOP;
-    float v = S[i];
-    if (i < N) {
-        float* tail = s_tail + (size_t)b.slot[w] * N;
-        if (hp) v = alpha[i] * v + beta[i] * tail[i];
-        if (!last) tail[i] = S[L - N + i];
-    }
-    const int emit = last ? L : L - N;
-    if (i < emit) d_audio[(size_t)b.out_off[w] + i] = v;
-}
-
 // grid = (tiles of a window, windows, row groups).  SHORT: tiles of 64 positions - for the layer that runs at one position
 // per frame, where a window is a few dozen positions long, and for every layer of a batch so small that the large tiles
 // would leave most of the chip idle (an output's sum does not depend on the tile it falls in).
@@ -566,9 +600,11 @@ hipError_t blocks_launch_tp(const VrArgs3& a, const int* len, int rate, int wind
     return hipSuccess;
 }
 
-// Positions per workgroup of the three tilings: small batches take half of the large tiles, a request or two a quarter -- more
-// workgroups, each with a shorter chain, and a larger share of halo.
-template <int C, int LEVEL> constexpr int vr_tp() { return (C >= 32 ? 256 : 512) >> LEVEL; }
+// Positions per workgroup of the tilings: small batches take half of the large tiles, a request or two a quarter -- more
+// workgroups, each with a shorter chain, and a larger share of halo.  Behind the longest halo (120) a region is a whole number of
+// column tiles.  With 64 channels, where a window is a few hundred positions and a region's products are the longest, a
+// request alone takes the smallest region there is.
+template <int C, int LEVEL> constexpr int vr_tp() { return LEVEL == 3 ? 8 : ((C >= 32 ? 256 : 512) >> LEVEL) + 8; }
 // With 64 channels (8 positions a frame) the halo of a tile of 128 doubles its work.  A window of up to 384 positions fits a
 // workgroup's registers and LDS and needs none: a CU per window and block, which pays from a few dozen windows on
 // (64 windows: 58 us a launch in tiles of 128, 43 whole).
@@ -576,12 +612,16 @@ constexpr int VR_WHOLE = 384;
 constexpr int VR_WHOLE_FROM = 48;                // windows from which it is used
 constexpr int VR_SMALL_BELOW = 1024;             // workgroups of the large tiling below which the half tiles are used
 constexpr int VR_TINY_BELOW = 128;               // ... and the quarter tiles
+constexpr int VR_LEAST_UPTO = 320;               // most workgroups of the smallest regions
 
 template <typename XT, int C>
 hipError_t blocks_launch(const VrArgs3& a, const int* len, int rate, int window, int n_windows, hipStream_t s)
 {
     if constexpr (C == 64)
         if (window * rate <= VR_WHOLE && n_windows >= VR_WHOLE_FROM) return blocks_launch_tp<XT, C, VR_WHOLE, false>(a, len, rate, window, n_windows, s);
+    if constexpr (C == 64)
+        if ((long)((window * rate + vr_tp<C, 3>() - 1) / vr_tp<C, 3>()) * n_windows * VOC_BLOCKS <= VR_LEAST_UPTO)
+            return blocks_launch_tp<XT, C, vr_tp<C, 3>(), true>(a, len, rate, window, n_windows, s);
     const long wgs = (long)((window * rate + vr_tp<C, 0>() - 1) / vr_tp<C, 0>()) * n_windows * VOC_BLOCKS;
     return wgs < VR_TINY_BELOW    ? blocks_launch_tp<XT, C, vr_tp<C, 2>(), true>(a, len, rate, window, n_windows, s)
            : wgs < VR_SMALL_BELOW ? blocks_launch_tp<XT, C, vr_tp<C, 1>(), true>(a, len, rate, window, n_windows, s)
@@ -612,48 +652,42 @@ hipError_t stage_launch(const VocoderPtrs& d, int n_windows, hipStream_t s)
 }
 
 template <typename XT>
-hipError_t generator_typed(const VocoderPtrs& d, int n_windows, hipStream_t s)
+hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d_mel, float* d_audio, hipStream_t s)
 {
     VcArgs pre{};
-    pre.in0 = d.x_mel;
     pre.out = d.x0;
     pre.W = reinterpret_cast<const uint4*>(d.pre_w);
     pre.bias = d.pre_b;
-    conv_launch<XT, VOC_N_MEL, VOC_C0, VOC_C0, VOC_K_PRE, EPI_PLAIN, false, false, 1, true>(pre, d.len, 1, d.window, n_windows, s);
-    hipError_t e = stage_launch<XT, 0>(d, n_windows, s);
-    if (e == hipSuccess) e = stage_launch<XT, 1>(d, n_windows, s);
-    if (e == hipSuccess) e = stage_launch<XT, 2>(d, n_windows, s);
-    if (e == hipSuccess) e = stage_launch<XT, 3>(d, n_windows, s);
+    constexpr int PRE_TP = vc_tp<XT, VOC_N_MEL, VOC_C0, (VOC_K_PRE - 1) / 2, true>();
+    hipLaunchKernelGGL((k_voc_first<XT>), dim3((d.window + PRE_TP - 1) / PRE_TP, b.n, VOC_C0 / 64), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.len,
+                       d.overlap, d.window);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = stage_launch<XT, 0>(d, b.n, s);
+    if (e == hipSuccess) e = stage_launch<XT, 1>(d, b.n, s);
+    if (e == hipSuccess) e = stage_launch<XT, 2>(d, b.n, s);
+    if (e == hipSuccess) e = stage_launch<XT, 3>(d, b.n, s);
     if (e != hipSuccess) return e;
     VcArgs post{};
     post.in0 = d.r[0];
     post.in1 = d.r[1];
     post.in2 = d.r[2];
-    post.out = d.audio;
     post.W = reinterpret_cast<const uint4*>(d.post_w);
     post.bias = d.post_b;
-    conv_launch<XT, voc_channels(VOC_STAGES - 1), 16, 1, VOC_K_POST, EPI_POST, true, true, 1, false>(post, d.len, VOC_HOP, d.window, n_windows, s);
+    auto last = [&](auto kern, int tp) {
+        hipLaunchKernelGGL(kern, dim3((d.window * VOC_HOP + tp - 1) / tp, b.n), dim3(VC_THREADS), 0, s, b, post, d.alpha, d.beta, d.s_tail, d.s_tail_turn, d_audio,
+                           d_mel, d.m_tail, d.overlap, d.window);
+    };
+    constexpr int CL = voc_channels(VOC_STAGES - 1), LONG_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2>(), SHORT_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2, true>();
+    if ((long)((d.window * VOC_HOP + LONG_TP - 1) / LONG_TP) * b.n < VC_SHORT_BELOW) last(k_voc_last<XT, true>, SHORT_TP);
+    else last(k_voc_last<XT, false>, LONG_TP);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_vocoder_splice(const VocoderPtrs& d, const VocBatch& b, const float* d_mel, hipStream_t s)
+hipError_t launch_vocoder(const VocoderPtrs& d, int wdtype, const VocBatch& b, const float* d_mel, float* d_audio, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_voc_splice, dim3(b.n, (d.window * VOC_N_MEL + 1023) / 1024), dim3(256), 0, s, b, d_mel, d.x_mel, d.m_tail, d.len, d.overlap, d.window);
-    return hipGetLastError();
-}
-
-hipError_t launch_vocoder_generator(const VocoderPtrs& d, int wdtype, int n_windows, hipStream_t s)
-{
-    return wdtype == 0 ? generator_typed<float>(d, n_windows, s) : generator_typed<h16_t>(d, n_windows, s);
-}
-
-hipError_t launch_vocoder_fade(const VocoderPtrs& d, const VocBatch& b, float* d_audio, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_voc_fade, dim3(d.window, b.n), dim3(VOC_HOP), 0, s, b, d.audio, d.alpha, d.beta, d.s_tail, d_audio,
-                       d.overlap, d.window);
-    return hipGetLastError();
+    return wdtype == 0 ? vocoder_typed<float>(d, b, d_mel, d_audio, s) : vocoder_typed<h16_t>(d, b, d_mel, d_audio, s);
 }
 
 }  // namespace tts

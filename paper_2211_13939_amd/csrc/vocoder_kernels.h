@@ -32,16 +32,16 @@ struct VocoderPtrs {
     const void* post_w; const float* post_b;
     const float* alpha; const float* beta;    // [overlap * 256] fade-in / fade-out
     float* m_tail;      // [max_requests][overlap][n_mel]   tail(M_pre) of every state slot
-    float* s_tail;      // [max_requests][overlap * 256]    tail(S_pre)
+    float* s_tail;      // [2][max_requests][overlap * 256] tail(S_pre): a slot's calls read one and write the other in turn
+    size_t s_tail_turn; // elements between the two
     int* len;           // [max_batch] frames in window i of this call (overlap frames in front included)
-    float* x_mel;       // [max_batch * window][n_mel]      the spliced windows
     float* x0;          // [max_batch * window][c0]         conv_pre output
     float* y;           // upsampled activations of the current stage, [positions][channels]
     float* r[VOC_BLOCKS];   // output of every residual block of the current stage
-    float* audio;       // [max_batch * window * 256]       S_cur of every window
     int overlap, window;    // window = overlap + max_chunk frames: the stride between windows, in frames
 };
 
+constexpr uint8_t VOC_HAS_PREV = 1, VOC_TURN = 2;
 // The batch as a kernel argument (no host-to-device copy).
 struct VocBatch {
     int n;
@@ -49,15 +49,12 @@ struct VocBatch {
     int out_off[VOC_MAX_BATCH];      // first sample of the response in d_audio
     uint16_t n_frames[VOC_MAX_BATCH];
     uint16_t slot[VOC_MAX_BATCH];
-    uint8_t has_prev[VOC_MAX_BATCH];
+    uint8_t has_prev[VOC_MAX_BATCH]; // VOC_HAS_PREV: the slot has a previous chunk; VOC_TURN: whose audio tail is the second one
     uint8_t last[VOC_MAX_BATCH];
 };
 
-// splice [tail(M_pre), M_cur] into the windows, write tail(M_cur) back (Eq. 3 line 1, Eq. 4), publish the window lengths
-hipError_t launch_vocoder_splice(const VocoderPtrs& d, const VocBatch& b, const float* d_mel, hipStream_t s);
-// G on every window: x_mel -> audio
-hipError_t launch_vocoder_generator(const VocoderPtrs& d, int wdtype, int n_windows, hipStream_t s);
-// fade the heads against tail(S_pre), write the responses, write tail(S_cur) back (Eq. 3 line 2, Eq. 4)
-hipError_t launch_vocoder_fade(const VocoderPtrs& d, const VocBatch& b, float* d_audio, hipStream_t s);
+// One dynamic batch: splice [tail(M_pre), M_cur] (Eq. 3 line 1), G, fade of the heads against tail(S_pre) (Eq. 3 line 2), responses, both
+// tails written back (Eq. 4)
+hipError_t launch_vocoder(const VocoderPtrs& d, int wdtype, const VocBatch& b, const float* d_mel, float* d_audio, hipStream_t s);
 
 }  // namespace tts
