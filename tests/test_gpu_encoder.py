@@ -322,3 +322,38 @@ def test_input_projection_of_large_calls(bf16, lens):
     for k, got in enumerate(enc.run(ids)):
         assert np.abs(got - orc.encoder(W, ids[k])).max() <= (TOL_BF16 if bf16 else TOL_F32)
     enc.close()
+
+
+@pytest.mark.parametrize("max_tokens", [64, 100, 400])
+def test_requests_that_join_together_are_encoded_together(weights_fp32, max_tokens):
+    """Requests that arrive at one time go through the encoder in as few calls as its token limit and the join's buffer allow
+    (64, 100 and 400 tokens against 45 + 11 + 30 + 1 + 44 + 20), and each one's frames equal those of a join of its own."""
+    from paper_2211_13939_amd import stream
+    lens, steps = [45, 11, 30, 1, 44, 20], [9, 8, 17, 5, 12, 16]
+    ids = [synth.encoder_ids(L, 2800 + i) for i, L in enumerate(lens)]
+    wl = synth.small_workload(len(lens), 8, 45, 5, 17, seed=67)
+    enc_w, got, calls = synth.make_encoder_weights(), [], []
+    for together in (False, True):
+        pool = make_pool(wl, weights_fp32, chunk_frames=8, max_pool=4, max_enc_len=64, max_steps=20)
+        enc = binding.Encoder(binding.make_encoder_config(max_tokens=max_tokens, max_len=45), enc_w, stream=pool.stream)
+        run_device, frames = enc.run_device, {i: [] for i in range(len(lens))}
+        enc.run_device = lambda a, out: calls.append((together, len(a))) or run_device(a, out)
+        join = stream.EncoderAtJoin(enc, lambda i: ids[i], 45)
+        be = stream.GpuBackend(pool, join if together else lambda i: join(i), steps, 8)
+        drain = pool.drain_chunk
+
+        def keep(rid):
+            f, fin = drain(rid)
+            frames[be.live[rid]["index"]].append(f.copy())
+            return f, fin
+        pool.drain_chunk = keep
+        say(f"case encoder, joins {'together' if together else 'one by one'}: {lens} tokens, at most {max_tokens} a call")
+        stream.simulate(be, np.zeros(len(lens)), steps, 8, max_pool=4)
+        got.append([np.concatenate(frames[i]) for i in range(len(lens))])
+        enc.close()
+        pool.close()
+    assert [f.shape[0] for f in got[0]] == steps
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+    assert [n for t, n in calls if not t] == [1] * len(lens)
+    assert sum(n for t, n in calls if t) == len(lens) and max(n for t, n in calls if t) == (2 if max_tokens == 64 else 4)
