@@ -139,8 +139,11 @@ __global__ __launch_bounds__(PN_THREADS) void k_pn_conv(
 //     (16 columns x 4 pieces) then meet every bank once.  Operands are requested two steps ahead.
 //   * A tap that leaves its window reads a row of zeros: an address chosen once per tap and chunk, not a mask on every operand
 //     (a vector instruction beside a product costs it two to four cycles).
-// The sums are the same whatever the tile: k in the order chunk, tap, fragment, on top of the bias.
-constexpr int CC_BUFS = 2, CC_AHEAD = 2;
+// The sums are the same whatever the tile: k in the order chunk, tap, fragment, on top of the bias.  In fp32 a chunk's products are
+// summed by themselves and added to the sum so far: against 64 bits the PostNet was 1.5e-6 .. 1.7e-6 off with one chain over all
+// of k, and is 0.9e-6 off so, as with the eight chains of the kernel above.
+constexpr int CC_BUFS = 2;
+template <typename XT> constexpr int cc_ahead() { return sizeof(XT) == 2 ? 2 : 1; }   // k steps between an operand's request and its use
 template <typename XT, int CIN, int TAPS, int CT, int WAVES> struct ColGeom {
     static constexpr int NKF = CIN / Frag<XT>::KB, NKT = TAPS * NKF;
     static constexpr int CF = NKF % 4 == 0 ? 4 : 3;            // channel fragments per chunk
@@ -183,6 +186,8 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
     constexpr int CT = WC * CTW;
     using R = ColGeom<XT, CIN, TAPS, CT, WR * WC>;
     constexpr int NKF = R::NKF, CF = R::CF, NK = R::NK, AHEAD = R::AHEAD;
+    constexpr bool PARTS = sizeof(XT) == 4 && TAPS > 1;
+    constexpr int SUM_OF = R::NCH > 2 ? NK : CF;               // k steps of a partial sum: a chunk, or (few chunks) a tap of one
     extern __shared__ uint4 s_cols[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
@@ -258,7 +263,8 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
         const int next = min(chunk + 1, R::NCH - 1);           // the last chunk requests its own first weights again, and drops them
         if (chunk + 1 < R::NCH) request(chunk + 1);
         const uint4* buf = s_cols + (chunk & 1) * R::BUF_VECS + g * R::PLANE;
-        constexpr int NB = CC_AHEAD + 1;
+        constexpr int CC_AHEAD = cc_ahead<XT>(), NB = CC_AHEAD + 1;
+        floatx4 part[PARTS ? RPW : 1][PARTS ? CTW : 1];
         uint4 bv[NB][CTW];
         int row[CTW];
         auto operands = [&](int i) __attribute__((always_inline)) {
@@ -285,7 +291,18 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
 #pragma unroll
             for (int c = 0; c < CTW; ++c)
 #pragma unroll
-                for (int r = 0; r < RPW; ++r) acc[r][c] = mfma_frag<XT>(af[r], bv[i % NB][c], acc[r][c]);
+                for (int r = 0; r < RPW; ++r) {
+                    if constexpr (PARTS) part[r][c] = mfma_frag<XT>(af[r], bv[i % NB][c], i % SUM_OF == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : part[r][c]);
+                    else acc[r][c] = mfma_frag<XT>(af[r], bv[i % NB][c], acc[r][c]);
+                }
+            if constexpr (PARTS) {
+                if (i % SUM_OF == SUM_OF - 1) {
+#pragma unroll
+                    for (int r = 0; r < RPW; ++r)
+#pragma unroll
+                        for (int c = 0; c < CTW; ++c) acc[r][c] += part[r][c];
+                }
+            }
         }
         if (chunk + 1 < R::NCH) {
             stash((chunk + 1) & 1);
@@ -353,8 +370,9 @@ inline hipError_t conv_cols(const ColArgs& p, hipStream_t s)
     using V = ColWaves<COUT, TAPS>;
     auto fits = [&](int ct) { return V::GROUPS * ((p.n_ctiles + ct - 1) / ct) <= CC_CUS; };
     if (fits(2)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 2>(p, s);
-    if (V::CT_MOST == 4 || fits(4)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 4>(p, s);
-    return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, V::CT_MOST>(p, s);
+    constexpr int MOST = sizeof(XT) == 4 && CIN < 512 ? 4 : V::CT_MOST;       // (fp32, few channels: eight tiles of partial sums spill)
+    if (MOST == 4 || fits(4)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 4>(p, s);
+    return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, MOST>(p, s);
 }
 
 template <typename XT, int CIN, int COUT, int EPI>
