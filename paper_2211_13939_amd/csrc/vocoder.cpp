@@ -54,7 +54,7 @@ ConvShape post_shape(bool bf) { return shape_of(1, voc_channels(VOC_STAGES - 1),
 struct VocLayout {
     size_t pre_w, pre_b, up_w[VOC_STAGES], up_b[VOC_STAGES];
     size_t res_w[VOC_STAGES][VOC_BLOCKS], res_b[VOC_STAGES][VOC_BLOCKS];
-    size_t post_w, post_b, alpha, beta, m_tail, s_tail, len, x0, y, r[VOC_BLOCKS], total;
+    size_t post_w, post_b, alpha, beta, m_tail, s_tail, turn, len, x0, y, r[VOC_BLOCKS], total;
     size_t state_begin;   // everything from here on is cleared at creation
 };
 
@@ -83,6 +83,7 @@ VocLayout layout_of(const tts_vocoder_config& c)
     l.state_begin = a.off;
     l.m_tail = a.take((size_t)c.max_requests * n_ov * VOC_N_MEL * 4);
     l.s_tail = a.take(2 * (size_t)c.max_requests * n_ov * VOC_HOP * 4);
+    l.turn = a.take((size_t)c.max_requests * 4);
     l.len = a.take(VOC_MAX_BATCH * 4);
     l.x0 = a.take(frames * VOC_C0 * 4);
     // positions x channels per frame: 8 * 64, 64 * 32, 128 * 16, 256 * 8 -- at most 2048
@@ -102,7 +103,6 @@ struct tts_vocoder {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool ev_valid = false;
     std::vector<uint8_t> open;      // per state slot: a chunk went through and was not the last
-    std::vector<uint8_t> turn;      // ... and which of its two audio tails that chunk wrote
 };
 
 extern "C" size_t tts_vocoder_workspace_bytes(const tts_vocoder_config* cfg)
@@ -139,7 +139,6 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
     v->cfg = *cfg;
     v->stream = (hipStream_t)hip_stream;
     v->open.assign(cfg->max_requests, 0);
-    v->turn.assign(cfg->max_requests, 0);
     char* base = (char*)dev_arena;
     const bool bf = cfg->weight_dtype == TTS_DTYPE_BF16;
 
@@ -226,6 +225,7 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
     d.m_tail = (float*)(base + lay.m_tail);
     d.s_tail = (float*)(base + lay.s_tail);
     d.s_tail_turn = (size_t)cfg->max_requests * cfg->overlap * VOC_HOP;
+    d.turn = (int*)(base + lay.turn);
     d.len = (int*)(base + lay.len);
     d.x0 = (float*)(base + lay.x0);
     d.y = (float*)(base + lay.y);
@@ -267,17 +267,14 @@ extern "C" int tts_vocoder_run(tts_vocoder* v, const float* d_mel, const int* n_
         b.out_off[i] = (int)off;
         b.n_frames[i] = (uint16_t)nf;
         b.slot[i] = (uint16_t)slot;
-        b.has_prev[i] = (has_prev ? VOC_HAS_PREV : 0) | (v->turn[slot] ? VOC_TURN : 0);
+        b.has_prev[i] = has_prev ? 1 : 0;
         b.last[i] = last ? 1 : 0;
         out_samples[i] = emit;
         row += nf;
         off += emit;
         if (off > 0x7FFFFFFF) return fail(TTS_E_INVAL, "more than 2^31 samples in one call");
     }
-    for (int i = 0; i < n; ++i) {
-        v->open[state_slot[i]] = (flags[i] & TTS_VOCODER_LAST) ? 0 : 1;
-        v->turn[state_slot[i]] ^= 1;
-    }
+    for (int i = 0; i < n; ++i) v->open[state_slot[i]] = (flags[i] & TTS_VOCODER_LAST) ? 0 : 1;
     HIP_TRY(hipEventRecord(v->ev0, v->stream));
     HIP_TRY(launch_vocoder(v->d, v->cfg.weight_dtype, b, d_mel, d_audio, v->stream));
     HIP_TRY(hipEventRecord(v->ev1, v->stream));

@@ -223,12 +223,15 @@ __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __res
 // window, 4.4 us for 64.)
 template <typename XT>
 __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, const float* __restrict__ d_mel, const float* __restrict__ m_tail,
-                                                          int* __restrict__ len, int ov, int window)
+                                                          int* __restrict__ len, int* __restrict__ turn, int ov, int window)
 {
     constexpr int CIN = VOC_N_MEL, KS = VOC_K_PRE, TP = vc_tp<XT, CIN, VOC_C0, (KS - 1) / 2, true>();
     __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
-    const int w = blockIdx.y, ovw = b.has_prev[w] & VOC_HAS_PREV ? ov : 0, valid = ovw + b.n_frames[w], p0 = blockIdx.x * TP;
-    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) len[w] = valid;
+    const int w = blockIdx.y, ovw = b.has_prev[w] ? ov : 0, valid = ovw + b.n_frames[w], p0 = blockIdx.x * TP;
+    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
+        len[w] = valid;
+        turn[b.slot[w]] ^= 1;
+    }
     if (p0 >= valid) return;
     const float* mel = d_mel + ((ptrdiff_t)b.src_row[w] - ovw) * CIN;
     const float* tail = m_tail + (size_t)b.slot[w] * ov * CIN;
@@ -241,18 +244,20 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, 
 
 // The last layer, and what becomes of its samples S_cur: the first ov * 256 of a window with a previous chunk are fused with the
 // slot's tail(S_pre) (Eq. 3 line 2), the response goes to the caller, and the slot's tails become those of this chunk (Eq. 4) unless
-// it was the request's last.  Each slot has two tails of audio, which calls read and write in turn: the workgroups of a launch come in any order.
+// it was the request's last.  Each slot has two tails of audio, which calls read and write in turn (the workgroups of a launch come in
+// any order); whose turn it is lies in device memory, where the call's first layer has changed it: a call that was captured goes on
+// with the stream at every replay.
 // (The mel tail is written here because the first layer reads the old one.)  As a launch of its own behind the last layer this took 3.3 us
 // for one window, 4.5 us for 64.
 template <typename XT, bool SHORT>
 __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, const float* __restrict__ alpha, const float* __restrict__ beta,
-                                                         float* __restrict__ s_tail, size_t s_tail_turn, float* __restrict__ d_audio,
+                                                         float* __restrict__ s_tail, size_t s_tail_turn, const int* __restrict__ turn, float* __restrict__ d_audio,
                                                          const float* __restrict__ d_mel, float* __restrict__ m_tail, int ov, int window)
 {
     constexpr int CIN = voc_channels(VOC_STAGES - 1), KS = VOC_K_POST, TP = vc_tp<XT, CIN, 16, (KS - 1) / 2, SHORT>();
     __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
-    const int w = blockIdx.y, flags = b.has_prev[w], nf = b.n_frames[w];
-    const bool hp = flags & VOC_HAS_PREV, last = b.last[w];
+    const int w = blockIdx.y, nf = b.n_frames[w], mine = turn[b.slot[w]];
+    const bool hp = b.has_prev[w], last = b.last[w];
     const int valid = ((hp ? ov : 0) + nf) * VOC_HOP, p0 = blockIdx.x * TP, N = ov * VOC_HOP;
     if (p0 >= valid) return;
     if (blockIdx.x == 0 && !last) {                            // nf >= ov here
@@ -260,9 +265,9 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, c
         float* dst = m_tail + (size_t)b.slot[w] * ov * VOC_N_MEL;
         for (int e = threadIdx.x; e < ov * VOC_N_MEL; e += VC_THREADS) dst[e] = src[e];
     }
-    const size_t turn = flags & VOC_TURN ? s_tail_turn : 0, slot = (size_t)b.slot[w] * N;
-    const float* old_tail = s_tail + turn + slot;
-    float* new_tail = s_tail + (s_tail_turn - turn) + slot;
+    const size_t slot = (size_t)b.slot[w] * N;
+    const float* old_tail = s_tail + (mine ? 0 : s_tail_turn) + slot;
+    float* new_tail = s_tail + (mine ? s_tail_turn : 0) + slot;
     float* out = d_audio + b.out_off[w];
     const int keep = valid - N, n_out = last ? valid : keep;
     auto emit = [&](int i, float v) __attribute__((always_inline)) {
@@ -295,11 +300,12 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, c
 // The operand buffer holds even and odd positions in planes of their own, so the columns of a tap are still consecutive
 // rows: 2 P + m d lies in plane m & 1 at row P + (m d - (m & 1)) / 2.
 //
-// Measured (two-byte mode, windows of 48 frames, one launch): 1 window, 64 / 32 / 16 / 8 channels 34.0 / 13.9 / 9.5 / 9.0 us -> 22.3 / 11.1 /
-// 7.8 / 5.5; 64 windows 93.4 / 107 / 70.4 / 119 -> 42.8 / 92 / 69 / 42.5.  With 16 and 32 channels the matrix pipes are busy 36 % of the
-// time and the vector units 30 %: the two waves of a SIMD run in step, so that products (16 cycles each) and the work on their
-// sums (two and a half instructions a value, half as much time) follow each other more than they overlap.  One workgroup for
-// a stage's three blocks, with their mean stored for the next layer, took as long (352 against 353 us a round of 64).
+// Measured (two-byte mode, windows of 48 frames, one launch): 1 window, 64 / 32 / 16 / 8 channels 34.0 / 13.9 / 9.5 / 9.0 us -> 16.4 / 11.0 /
+// 8.4 / 5.7; 64 windows 93.4 / 107 / 70.4 / 119 -> 43.0 / 92 / 67 / 41.  With 32 channels the matrix pipes are busy 36 % of the time and
+// the vector units 30 %: a product takes 17 cycles, a vector instruction beside it two to four more, whichever wave of the SIMD it
+// is of, and a value costs two and a half of them (leaky ReLU, conversion, store).  One workgroup for a stage's three blocks, with
+// their mean stored for the next layer, took as long (352 against 353 us a round of 64); two tiles in a workgroup of eight waves
+// that take turns at products and vector work were slower (32 channels 96 -> 102 us).
 // ---------------------------------------------------------------------------
 struct VrArgs {
     const float* in;                         // the stage's upsampled activations
@@ -311,9 +317,9 @@ struct VrArgs3 { VrArgs b[VOC_BLOCKS]; };
 
 constexpr int VR_LDS_MAX = 160 * 1024;
 
-// The weights stream from L1 / L2 into a ring of registers, VR_AHEAD fragments ahead of the products; the first ones of a
-// convolution are requested before the operand is put in LDS.  (Through LDS, as a first version had them, they were a quarter
-// to a half of its traffic, and a convolution's 88 KB at 64 channels went through the CU in one burst.)  Two operand buffers,
+// The weights stream from L1 / L2 into a ring of registers, VR_AHEAD fragments ahead of the products (6 and 11 ahead: a round of one
+// window 0.6 and 4.5 us longer); the first ones of a convolution are requested before the operand is put in LDS.  (Through LDS, as a
+// first version had them, they were a quarter to a half of its traffic, and a convolution's 88 KB at 64 channels went through the CU in one burst.)  Two operand buffers,
 // where LDS holds them, so that one barrier per convolution is enough and a wave that is done prepares the next operand
 // while others still read this one.
 constexpr int VR_AHEAD = 4;
@@ -660,7 +666,7 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     pre.bias = d.pre_b;
     constexpr int PRE_TP = vc_tp<XT, VOC_N_MEL, VOC_C0, (VOC_K_PRE - 1) / 2, true>();
     hipLaunchKernelGGL((k_voc_first<XT>), dim3((d.window + PRE_TP - 1) / PRE_TP, b.n, VOC_C0 / 64), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.len,
-                       d.overlap, d.window);
+                       d.turn, d.overlap, d.window);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = stage_launch<XT, 0>(d, b.n, s);
     if (e == hipSuccess) e = stage_launch<XT, 1>(d, b.n, s);
@@ -674,7 +680,7 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     post.W = reinterpret_cast<const uint4*>(d.post_w);
     post.bias = d.post_b;
     auto last = [&](auto kern, int tp) {
-        hipLaunchKernelGGL(kern, dim3((d.window * VOC_HOP + tp - 1) / tp, b.n), dim3(VC_THREADS), 0, s, b, post, d.alpha, d.beta, d.s_tail, d.s_tail_turn, d_audio,
+        hipLaunchKernelGGL(kern, dim3((d.window * VOC_HOP + tp - 1) / tp, b.n), dim3(VC_THREADS), 0, s, b, post, d.alpha, d.beta, d.s_tail, d.s_tail_turn, d.turn, d_audio,
                            d_mel, d.m_tail, d.overlap, d.window);
     };
     constexpr int CL = voc_channels(VOC_STAGES - 1), LONG_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2>(), SHORT_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2, true>();

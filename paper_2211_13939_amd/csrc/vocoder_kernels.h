@@ -34,6 +34,7 @@ struct VocoderPtrs {
     float* m_tail;      // [max_requests][overlap][n_mel]   tail(M_pre) of every state slot
     float* s_tail;      // [2][max_requests][overlap * 256] tail(S_pre): a slot's calls read one and write the other in turn
     size_t s_tail_turn; // elements between the two
+    int* turn;          // [max_requests]  which of the two the slot's latest call writes (its calls' first launch changes it)
     int* len;           // [max_batch] frames in window i of this call (overlap frames in front included)
     float* x0;          // [max_batch * window][c0]         conv_pre output
     float* y;           // upsampled activations of the current stage, [positions][channels]
@@ -41,7 +42,6 @@ struct VocoderPtrs {
     int overlap, window;    // window = overlap + max_chunk frames: the stride between windows, in frames
 };
 
-constexpr uint8_t VOC_HAS_PREV = 1, VOC_TURN = 2;
 // The batch as a kernel argument (no host-to-device copy).
 struct VocBatch {
     int n;
@@ -49,7 +49,7 @@ struct VocBatch {
     int out_off[VOC_MAX_BATCH];      // first sample of the response in d_audio
     uint16_t n_frames[VOC_MAX_BATCH];
     uint16_t slot[VOC_MAX_BATCH];
-    uint8_t has_prev[VOC_MAX_BATCH]; // VOC_HAS_PREV: the slot has a previous chunk; VOC_TURN: whose audio tail is the second one
+    uint8_t has_prev[VOC_MAX_BATCH];
     uint8_t last[VOC_MAX_BATCH];
 };
 

@@ -301,3 +301,39 @@ def test_windows_around_the_tiles_of_the_residual_blocks(bf16, n, window):
     W = orc.VocoderWeights(w)
     for k in (0, 2, 3, 4):
         assert np.abs(got[k] - orc.generator(W, mels[k])).max() <= (TOL_BF16 if bf16 else TOL_F32)
+
+
+def test_a_captured_call_goes_on_with_the_stream_at_every_replay():
+    """A middle chunk's call captured once and replayed for the chunks that follow, eager work between the replays: the state of a
+    slot, its tails included, is the device's own, so every response equals the eager stream's, bit for bit."""
+    import torch
+    w = synth.make_vocoder_weights(bf16=True)
+    rng = np.random.default_rng(37)
+    n, chunk, ov = 3, 12, 4
+    chunks = [[_mel(rng, chunk) for _ in range(n)] for _ in range(6)]
+    cfg = binding.make_vocoder_config(overlap=ov, max_chunk=chunk, max_requests=n, max_batch=n, bf16=True)
+    eager = binding.Vocoder(cfg, w)
+    want = [eager.run(c, list(range(n)), [FIRST if r == 0 else 0] * n) for r, c in enumerate(chunks)]
+    eager.close()
+    say(f"case vocoder under capture: {n} requests, one captured call replayed for {len(chunks) - 2} chunks")
+    voc = binding.Vocoder(cfg, w)
+    for r in (0, 1):
+        for a, b in zip(voc.run(chunks[r], list(range(n)), [FIRST if r == 0 else 0] * n), want[r]):
+            np.testing.assert_array_equal(a, b)
+    mel = torch.zeros((n * chunk, 80), device=voc.device)
+    out = torch.zeros(n * (chunk + ov) * HOP, device=voc.device)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=voc.stream):
+        voc.run_device(mel, [chunk] * n, list(range(n)), [0] * n, out)
+    for r in range(2, 6):
+        mel.copy_(torch.from_numpy(np.concatenate(chunks[r])))
+        out.fill_(7.0)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(voc.stream):
+            graph.replay()
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        for i in range(n):
+            np.testing.assert_array_equal(got[i * chunk * HOP:(i + 1) * chunk * HOP], want[r][i])
+    voc.close()
