@@ -137,18 +137,23 @@ __global__ __launch_bounds__(PN_THREADS) void k_pn_conv(
 //     cycles in products: 2 x 2 waves of 2 x 4 tiles each take 128, 70 and 136 cycles of the unit.
 //   * LDS holds a plane per 16 bytes of channels, rows = columns, planes a multiple of 16 pieces apart: the lanes of a B fragment
 //     (16 columns x 4 pieces) then meet every bank once.  Operands are requested two steps ahead.
-//   * A tap that leaves its window reads a row of zeros: an address chosen once per tap and chunk, not a mask on every operand
-//     (a vector instruction beside a product costs it two to four cycles).
-// The sums are the same whatever the tile: k in the order chunk, tap, fragment, on top of the bias.  In fp32 a chunk's products are
-// summed by themselves and added to the sum so far: against 64 bits the PostNet was 1.5e-6 .. 1.7e-6 off with one chain over all
-// of k, and is 0.9e-6 off so, as with the eight chains of the kernel above.
-constexpr int CC_BUFS = 2;
+//   * A tap that leaves its window reads a row of zeros: an address chosen once per tap, not a mask on every operand (a vector
+//     instruction beside a product costs it two to four cycles).  Which of the two buffers is read is a constant in the read's offset.
+// The sums are those of the kernel above, bit for bit: eight partial sums, sum w of the fragments f = w, w + 8, ... (f = tap * NKF +
+// channel fragment), added to the bias in the order of w.  So a request's and a chunk's results are the same alone and in a call of any
+// size, whichever kernel a layer of the call takes.  A chunk holds the channel fragments w, w + 8, .. of one partial sum (fp32) or two
+// (two-byte), or, with a few channels, all there are.  The price is 32 additions a wave and partial sum: with one chain over all of k,
+// which differed from the kernel above by 1.4e-4 (two-byte) and was further off 64 bits in fp32 (1.5e-6 .. 1.7e-6 of the PostNet's output
+// against 0.9e-6), a PostNet round of 64 / 256 requests took 66 / 152 us, like this 68 / 155 us; fp32 316 / 1047 us, like this 307 / 1032.
 template <typename XT> constexpr int cc_ahead() { return sizeof(XT) == 2 ? 2 : 1; }   // k steps between an operand's request and its use
 template <typename XT, int CIN, int TAPS, int CT, int WAVES> struct ColGeom {
     static constexpr int NKF = CIN / Frag<XT>::KB, NKT = TAPS * NKF;
-    static constexpr int CF = NKF % 4 == 0 ? 4 : 3;            // channel fragments per chunk
-    static constexpr int NCH = NKF / CF;
+    static constexpr bool PARTS = TAPS > 1;                    // (the input projection is one chain in its other kernel, too)
+    static constexpr bool CHUNKED = NKF % PN_WAVES == 0;
+    static constexpr int CF = CHUNKED ? 4 : NKF;               // channel fragments per chunk
+    static constexpr int NCH = NKF / CF, BUFS = NCH > 1 ? 2 : 1;
     static constexpr int NK = TAPS * CF;                       // k steps per chunk
+    static constexpr int CSTEP = PARTS && CHUNKED ? PN_WAVES / NCH : CF;   // between the first fragments of two chunks
     static constexpr int THREADS = WAVES * 64;
     static constexpr int HALO = TAPS / 2;
     static constexpr int ROWS = CT * 16 + 2 * HALO;            // staged columns; row ROWS is zero
@@ -156,9 +161,20 @@ template <typename XT, int CIN, int TAPS, int CT, int WAVES> struct ColGeom {
     static constexpr int BUF_VECS = CF * 4 * PLANE;
     static constexpr int PIECES = CF * 4 * ROWS;
     static constexpr int PER = (PIECES + THREADS - 1) / THREADS;
-    static constexpr int LDS = CC_BUFS * BUF_VECS * 16;
-    static constexpr int AHEAD = NK % 5 == 0 ? 5 : NK;         // weight fragments in flight (divides NK: the ring is static)
-    static_assert(NKF % CF == 0 && NK % AHEAD == 0, "whole chunks");
+    static constexpr int LDS = BUFS * BUF_VECS * 16;
+    static constexpr int AHEAD = CHUNKED && PARTS && CT == 8 ? 4 : NK % 5 == 0 ? 5 : NK;    // weight fragments in flight (divides NK: the ring is static)
+    static_assert(NKF % CF == 0 && NCH % BUFS == 0 && NK % AHEAD == 0, "whole chunks");
+    // channel fragment (of the first chunk) that lies in place j of a chunk
+    __device__ static constexpr int frag(int j) { return PARTS && NCH > 1 ? j * PN_WAVES / NKF + j % (NKF / PN_WAVES) * PN_WAVES : j; }
+    // k step i of a chunk: the partial sum it belongs to (of the chunk's), how far in, its tap and its place in the chunk.  Where all
+    // channels are one chunk, the first LONG partial sums have one fragment more than the others
+    static constexpr int LONG = NKT % PN_WAVES, LEN = NKT / PN_WAVES, SPLIT = LONG * (LEN + 1);
+    __device__ static constexpr int part(int i) { return !PARTS ? 0 : i < SPLIT ? i / (LEN + 1) : LONG + (i - SPLIT) / LEN; }
+    __device__ static constexpr int within(int i) { return !PARTS ? i : i < SPLIT ? i % (LEN + 1) : (i - SPLIT) % LEN; }
+    __device__ static constexpr int fragment(int i) { return PARTS ? part(i) + PN_WAVES * within(i) : i; }
+    __device__ static constexpr int tap(int i) { return fragment(i) / NKF; }
+    __device__ static constexpr int place(int i) { return !PARTS || NCH == 1 ? fragment(i) % NKF : part(i) * (NKF / PN_WAVES) + within(i) % (NKF / PN_WAVES); }
+    static_assert(!PARTS || NCH == 1 || (LONG == 0 && NK % LEN == 0), "partial sums end with their chunk");
 };
 
 enum { CC_TANH = PN_EPI_TANH, CC_LAST = PN_EPI_LAST, CC_RELU = PN_EPI_RELU, CC_XPROJ = 3 };
@@ -186,8 +202,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
     constexpr int CT = WC * CTW;
     using R = ColGeom<XT, CIN, TAPS, CT, WR * WC>;
     constexpr int NKF = R::NKF, CF = R::CF, NK = R::NK, AHEAD = R::AHEAD;
-    constexpr bool PARTS = sizeof(XT) == 4 && TAPS > 1;
-    constexpr int SUM_OF = R::NCH > 2 ? NK : CF;               // k steps of a partial sum: a chunk, or (few chunks) a tap of one
+    constexpr bool PARTS = R::PARTS;
     extern __shared__ uint4 s_cols[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
@@ -199,7 +214,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
     // a fragment's place is a scalar offset: all weight loads share one address register
     const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(half ? p.W1 : p.W), 0, COUT / (EPI == CC_XPROJ ? 32 : 16) * R::NKT * 1024, BUFFER_RSRC_RAW);
     auto weight = [&](int chunk, int i, int r) __attribute__((always_inline)) {       // k step i of a chunk
-        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, ((rt0 + r) * R::NKT + i / CF * NKF + chunk * CF + i % CF) * 1024, 0);
+        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, ((rt0 + r) * R::NKT + R::tap(i) * NKF + R::frag(R::place(i)) + chunk * R::CSTEP) * 1024, 0);
         return make_uint4(v.x, v.y, v.z, v.w);
     };
     // This thread's pieces of a chunk: piece = (plane, column).  The activations are read through a descriptor that begins at the tile
@@ -212,13 +227,13 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
     for (int i = 0; i < R::PER; ++i) {
         const int idx = min(i * R::THREADS + tid, R::PIECES - 1), plane = idx / R::ROWS, col = col_first + idx - plane * R::ROWS;
         const bool in = col >= 0 && col < n_col_pad;
-        from[i] = in ? (unsigned)xfrag(NKF, (col >> 4) - tile0, plane >> 2, (col & 15) + 16 * (plane & 3)) * 16u : 0x80000000u;
+        from[i] = in ? (unsigned)xfrag(NKF, (col >> 4) - tile0, R::frag(plane >> 2), (col & 15) + 16 * (plane & 3)) * 16u : 0x80000000u;
     }
     uint4 st[R::PER];
     auto request = [&](int chunk) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < R::PER; ++i) {
-            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)from[i], chunk * CF * 1024, 0);
+            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)from[i], chunk * R::CSTEP * 1024, 0);
             st[i] = make_uint4(v.x, v.y, v.z, v.w);
         }
     };
@@ -235,19 +250,16 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
     for (int i = 0; i < AHEAD; ++i)
 #pragma unroll
         for (int r = 0; r < RPW; ++r) ring[i][r] = weight(0, i, r);
-    for (int i = tid; i < CC_BUFS * CF * 4; i += R::THREADS) s_cols[i * R::PLANE + R::ROWS] = make_uint4(0, 0, 0, 0);
-    // which taps stay inside the column's own window (bit d + HALO for column offset d)
-    int taps[CTW];
-    if constexpr (TAPS > 1) {
+    for (int i = tid; i < R::BUFS * CF * 4; i += R::THREADS) s_cols[i * R::PLANE + R::ROWS] = make_uint4(0, 0, 0, 0);
+    // where every tap's operand lies: the column it meets, or a row of zeros where it leaves the column's own window
+    const uint4* at[TAPS][CTW];
 #pragma unroll
-        for (int c = 0; c < CTW; ++c) {
-            const int m = p.cmeta[min((ct0 + cw + c) * 16 + n, n_col_pad - 1)];
-            const int t = m & 0xFFFF, T = m >> 16;
-            int bits = 0;
+    for (int c = 0; c < CTW; ++c) {
+        const int m = TAPS > 1 ? p.cmeta[min((ct0 + cw + c) * 16 + n, n_col_pad - 1)] : 0;
+        const int t = m & 0xFFFF, T = m >> 16;
 #pragma unroll
-            for (int d = -R::HALO; d <= R::HALO; ++d) bits |= (t + d >= 0 && t + d < T) ? (1 << (d + R::HALO)) : 0;
-            taps[c] = bits;
-        }
+        for (int tap = 0; tap < TAPS; ++tap)
+            at[tap][c] = s_cols + g * R::PLANE + (TAPS == 1 || (unsigned)(t + tap - R::HALO) < (unsigned)T ? (cw + c) * 16 + n + tap : R::ROWS);
     }
     floatx4 acc[RPW][CTW];
 #pragma unroll
@@ -256,25 +268,29 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
 #pragma unroll
         for (int c = 0; c < CTW; ++c) acc[r][c] = b;
     }
+    // A partial sum is added when its successor begins, tile by tile between the products: behind its own last product every addition would
+    // wait for the matrix pipe.  (Pinned there: left to itself the compiler adds all of them at the end, and keeps them in scratch memory.)
+    floatx4 part[PARTS ? RPW : 1][PARTS ? CTW : 1];
+    if constexpr (PARTS) {
+#pragma unroll
+        for (int r = 0; r < RPW; ++r)
+#pragma unroll
+            for (int c = 0; c < CTW; ++c) part[r][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto add_part = [&](int r, int c) __attribute__((always_inline)) {
+        acc[r][c] += part[r][c];
+        asm volatile("" : "+v"(acc[r][c]));
+    };
     stash(0);
     __syncthreads();
-#pragma unroll 1
-    for (int chunk = 0; chunk < R::NCH; ++chunk) {
+    constexpr int CC_AHEAD = cc_ahead<XT>(), NB = CC_AHEAD + 1;
+    auto do_chunk = [&](int chunk, int buf) __attribute__((always_inline)) {      // buf: a constant, so that it is part of a read's offset
         const int next = min(chunk + 1, R::NCH - 1);           // the last chunk requests its own first weights again, and drops them
         if (chunk + 1 < R::NCH) request(chunk + 1);
-        const uint4* buf = s_cols + (chunk & 1) * R::BUF_VECS + g * R::PLANE;
-        constexpr int CC_AHEAD = cc_ahead<XT>(), NB = CC_AHEAD + 1;
-        floatx4 part[PARTS ? RPW : 1][PARTS ? CTW : 1];
         uint4 bv[NB][CTW];
-        int row[CTW];
         auto operands = [&](int i) __attribute__((always_inline)) {
-            const int tap = i / CF;
-            if (i % CF == 0) {
 #pragma unroll
-                for (int c = 0; c < CTW; ++c) row[c] = TAPS == 1 || ((taps[c] >> tap) & 1) ? (cw + c) * 16 + n + tap : R::ROWS;
-            }
-#pragma unroll
-            for (int c = 0; c < CTW; ++c) bv[i % NB][c] = buf[(i % CF) * 4 * R::PLANE + row[c]];
+            for (int c = 0; c < CTW; ++c) bv[i % NB][c] = at[R::tap(i)][c][buf * R::BUF_VECS + R::place(i) * 4 * R::PLANE];
         };
 #pragma unroll
         for (int i = 0; i < CC_AHEAD; ++i) operands(i);
@@ -284,7 +300,8 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
 #pragma unroll
             for (int r = 0; r < RPW; ++r) {
                 af[r] = ring[i % AHEAD][r];
-                ring[i % AHEAD][r] = i + AHEAD < NK ? weight(chunk, i + AHEAD, r) : weight(next, i + AHEAD - NK, r);
+                if (i + AHEAD < NK) ring[i % AHEAD][r] = weight(chunk, i + AHEAD, r);
+                else if constexpr (R::NCH > 1) ring[i % AHEAD][r] = weight(next, i + AHEAD - NK, r);
             }
             if (i + CC_AHEAD < NK) operands(i + CC_AHEAD);
             __builtin_amdgcn_sched_barrier(0);
@@ -292,26 +309,29 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
             for (int c = 0; c < CTW; ++c)
 #pragma unroll
                 for (int r = 0; r < RPW; ++r) {
-                    if constexpr (PARTS) part[r][c] = mfma_frag<XT>(af[r], bv[i % NB][c], i % SUM_OF == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : part[r][c]);
-                    else acc[r][c] = mfma_frag<XT>(af[r], bv[i % NB][c], acc[r][c]);
+                    if constexpr (PARTS) {
+                        if (R::within(i) == 0) add_part(r, c);
+                        part[r][c] = mfma_frag<XT>(af[r], bv[i % NB][c], R::within(i) == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : part[r][c]);
+                    } else acc[r][c] = mfma_frag<XT>(af[r], bv[i % NB][c], acc[r][c]);
                 }
-            if constexpr (PARTS) {
-                if (i % SUM_OF == SUM_OF - 1) {
-#pragma unroll
-                    for (int r = 0; r < RPW; ++r)
-#pragma unroll
-                        for (int c = 0; c < CTW; ++c) acc[r][c] += part[r][c];
-                }
-            }
         }
         if (chunk + 1 < R::NCH) {
-            stash((chunk + 1) & 1);
+            stash(buf ^ 1);
             lds_barrier();
         }
+    };
+#pragma unroll 1
+    for (int chunk = 0; chunk < R::NCH; chunk += R::BUFS) {
+        do_chunk(chunk, 0);
+        if constexpr (R::BUFS == 2) do_chunk(chunk + 1, 1);
     }
 #pragma unroll
     for (int c = 0; c < CTW; ++c) {
         if (ct0 + cw + c >= p.n_ctiles) break;
+        if constexpr (PARTS) {
+#pragma unroll
+            for (int r = 0; r < RPW; ++r) acc[r][c] += part[r][c];
+        }
         const int col = (ct0 + cw + c) * 16 + n;
         const int r_out = EPI == CC_LAST ? p.orow[col] : 0;
 #pragma unroll
@@ -401,9 +421,8 @@ inline hipError_t conv_layer(bool wide, const void* W, const float* b, const voi
     return hipGetLastError();
 }
 
-// Calls of at least this many column tiles take the kernel above.  It is the faster one from about 30 on (two-byte mode, 512 -> 512
-// layers, 75 tiles: 14.5 us in the narrow kernel, 10.7 in this one); the lines lie higher so that calls of a few short windows and a
-// window alone, which the narrow kernel serves, give the same bits up to there: the kernels differ in the order of their sums.
+// Calls of at least this many column tiles take the kernel above (two-byte mode, 512 -> 512 layers, 75 tiles: 14.5 us in the narrow
+// kernel, 10.7 in this one).
 constexpr int PN_WIDE_FROM = 40;
 template <typename XT> constexpr int enc_wide_from() { return sizeof(XT) == 2 ? 40 : 80; }
 

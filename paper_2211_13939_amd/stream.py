@@ -543,7 +543,8 @@ class EncoderAtJoin:
     """Module E for the serving loop (Eq. 1; Sec. 2.2.1: once per request): `enc(i)` for a GpuBackend.  The request's
     id sequences go through tts_encoder_run on the pool's stream and F_enc stays on the device; the pool copies it
     into its own memory when the request is added, so one output buffer serves every join.  `many` does the same for
-    requests that join together, as many per call as the buffer and the encoder take."""
+    requests that join together, as many per call as the buffer and the encoder take: a request's F_enc is the same bits
+    whoever shares its call.  The buffer's rows are whatever a call leaves there."""
 
     JOINS = 8       # requests of full length that the output buffer holds
 

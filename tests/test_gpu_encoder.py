@@ -69,10 +69,10 @@ def test_more_requests_than_mfma_columns_and_long_request():
 
 @pytest.mark.parametrize("bf16", [True, False])
 def test_result_does_not_depend_on_batch_composition(bf16):
-    """Bitwise, among calls that take the same kernels (the convolutions have one kernel for calls below 80 column tiles
-    of tokens - all calls here - and one for larger calls, which differ in summation order only).  The recurrence sums in
-    one order whatever the call: with two-byte weights every request has workgroups of its own, with fp32 weights a unit's
-    sum does not depend on how many workgroups share a direction and how many requests share them."""
+    """Bitwise, whatever the call.  The convolutions and the input projection have one kernel for small calls - all calls here,
+    see the next test - and one for large ones, which sum in one order.  The recurrence does so, too: with two-byte weights
+    every request has workgroups of its own, with fp32 weights a unit's sum does not depend on how many workgroups share a
+    direction and how many requests share them."""
     w = synth.make_encoder_weights(bf16=bf16)
     ids = [synth.encoder_ids(L, 300 + i) for i, L in enumerate((40, 9, 23, 61, 5, 33))]
     enc = binding.Encoder(binding.make_encoder_config(max_tokens=512, max_len=100, bf16=bf16), w)
@@ -86,6 +86,25 @@ def test_result_does_not_depend_on_batch_composition(bf16):
     np.testing.assert_array_equal(four, enc.run(ids)[2])
     np.testing.assert_array_equal(four, enc.run([ids[2], ids[5], ids[4]])[0])
     np.testing.assert_array_equal(four, alone)
+    enc.close()
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_result_does_not_depend_on_the_size_of_the_call(bf16):
+    """Calls of a few column tiles and of more and more of them (both kernels of the convolutions and of the input projection, every
+    number of column tiles per workgroup of the large calls' one): a request's F_enc is, bit for bit, the one it has alone."""
+    w = synth.make_encoder_weights(bf16=bf16)
+    lens = [130, 33, 1, 160, 77, 150] + [int(x) for x in np.random.default_rng(41).integers(1, 300, size=40)]
+    ids = [synth.encoder_ids(L, 3100 + i) for i, L in enumerate(lens)]
+    enc = binding.Encoder(binding.make_encoder_config(max_tokens=8192, max_len=300, bf16=bf16), w)
+    alone = [enc.run([a])[0] for a in ids[:6]]
+    for tiles in (35, 39, 40, 41, 66, 80, 129, 161, 300):
+        n = max(k for k in range(6, len(ids) + 1) if sum(lens[:k]) <= 16 * tiles)
+        last = 16 * tiles - 7 - sum(lens[:n])             # the call ends inside its last tile
+        call = ids[:n] + ([synth.encoder_ids(min(last, 300), 3200 + tiles)] if last > 0 else [])
+        say(f"case encoder, {'bf16' if bf16 else 'fp32'}: {len(call)} requests, {sum(a.shape[1] for a in call) / 16:.1f} column tiles")
+        for want, got in zip(alone, enc.run(call)):
+            np.testing.assert_array_equal(got, want)
     enc.close()
 
 
@@ -231,8 +250,9 @@ def test_largest_batch_bf16():
         worst = max(worst, float(np.abs(got[k] - orc.encoder(W, ids[k])).max()))
     say(f"  max abs err {worst:.3e}, {enc.elapsed_ms() * 1e3:.0f} us")
     assert worst <= TOL_BF16
-    # bit for bit what a smaller call gives that takes the same convolution kernel (from 80 column tiles up)
+    # bit for bit what smaller calls give
     np.testing.assert_array_equal(got[200], enc.run(ids[150:])[50])
+    np.testing.assert_array_equal(got[200], enc.run([ids[200]])[0])
     enc.close()
 
 
@@ -296,7 +316,6 @@ def test_shared_recurrence_of_a_long_request_among_short_ones_fp32(n, at):
     w = synth.make_encoder_weights()
     lens = [1 + (5 * i) % 8 for i in range(n)]
     lens[at] = 300
-    assert sum(lens) <= 79 * 16                # (the convolutions' kernel is that of a call of one request)
     ids = [synth.encoder_ids(L, 2300 + i) for i, L in enumerate(lens)]
     enc = binding.Encoder(binding.make_encoder_config(max_tokens=1280, max_len=300), w)
     say(f"case encoder, fp32: request {at} of {n} has 300 tokens, the others up to 8")
@@ -311,8 +330,8 @@ def test_shared_recurrence_of_a_long_request_among_short_ones_fp32(n, at):
 
 @pytest.mark.parametrize("bf16,lens", [(False, [400, 399, 400, 66]), (False, [1, 640, 640]), (True, [400, 239]), (True, [1, 330, 310, 640, 7])])
 def test_input_projection_of_large_calls(bf16, lens):
-    """Calls on the far side of the line from which the convolutions and the input projection take whole column tiles (40 tiles two-byte,
-    80 fp32), with a whole and a barely begun last tile: the oracle's values for every request."""
+    """Calls on the far side of the lines from which the convolutions and the input projection take whole column tiles, with a whole and
+    a barely begun last tile: the oracle's values for every request."""
     from oracle import oracle as orc
     w = synth.make_encoder_weights(bf16=bf16)
     W = orc.EncoderWeights(w)
@@ -327,7 +346,8 @@ def test_input_projection_of_large_calls(bf16, lens):
 @pytest.mark.parametrize("max_tokens", [64, 100, 400])
 def test_requests_that_join_together_are_encoded_together(weights_fp32, max_tokens):
     """Requests that arrive at one time go through the encoder in as few calls as its token limit and the join's buffer allow
-    (64, 100 and 400 tokens against 45 + 11 + 30 + 1 + 44 + 20), and each one's frames equal those of a join of its own."""
+    (64, 100 and 400 tokens against 45 + 11 + 30 + 1 + 44 + 20), and each one's frames equal those of a join of its own (small calls, fp32;
+    large ones below)."""
     from paper_2211_13939_amd import stream
     lens, steps = [45, 11, 30, 1, 44, 20], [9, 8, 17, 5, 12, 16]
     ids = [synth.encoder_ids(L, 2800 + i) for i, L in enumerate(lens)]
@@ -357,3 +377,25 @@ def test_requests_that_join_together_are_encoded_together(weights_fp32, max_toke
         np.testing.assert_array_equal(a, b)
     assert [n for t, n in calls if not t] == [1] * len(lens)
     assert sum(n for t, n in calls if t) == len(lens) and max(n for t, n in calls if t) == (2 if max_tokens == 64 else 4)
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_large_joins_equal_joins_of_their_own(bf16):
+    """Six requests that join together with 877 tokens, 55 column tiles in one call of the encoder (the kernel of large calls) where each
+    alone has up to 10 (the kernel of small ones): every F_enc is, bit for bit, that of a join of its own."""
+    from paper_2211_13939_amd import stream
+    lens = [150, 130, 160, 143, 150, 144]
+    ids = [synth.encoder_ids(L, 3300 + i) for i, L in enumerate(lens)]
+    enc = binding.Encoder(binding.make_encoder_config(max_tokens=1024, max_len=160, bf16=bf16), synth.make_encoder_weights(bf16=bf16))
+    join = stream.EncoderAtJoin(enc, lambda i: ids[i], 160)
+    say(f"case encoder at join, {'bf16' if bf16 else 'fp32'}: {lens} tokens together and one by one")
+    import torch
+    together, groups = {}, []
+    with torch.cuda.stream(enc.stream):
+        for group, encs in join.many(range(len(lens))):
+            groups.append(len(group))
+            together.update((i, f.cpu().numpy()) for i, f in zip(group, encs))
+        for i in range(len(lens)):
+            np.testing.assert_array_equal(together[i], join(i).cpu().numpy())
+    assert groups == [6]
+    enc.close()

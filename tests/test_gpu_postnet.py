@@ -90,9 +90,9 @@ def test_large_batch_matches_oracle(bf16):
 
 
 def test_very_large_batch_matches_oracle_and_small_batches():
-    """26 windows of 50 frames and a ragged one (1337 columns, 84 tiles: 21 workgroups of columns in the
-    large-batch kernel, the last one partial), bf16.  Against the oracle on every window, and against the same
-    windows in batches of nine (small enough for the other kernel, whose summation order differs)."""
+    """26 windows of 50 frames and a ragged one (1337 columns, 84 tiles: the workgroups of the large-batch kernel's
+    last columns are partial), bf16.  Against the oracle on every window, and against the same
+    windows in batches of nine (small enough for the other kernel)."""
     from oracle import oracle as orc
     ws, bs = synth.make_postnet_weights(bf16=True)
     W = orc.PostnetWeights(ws, bs)
@@ -156,8 +156,7 @@ def test_window_without_full_context_is_rejected_or_exact_at_start():
 
 
 def test_result_does_not_depend_on_batch_composition():
-    """A chunk post-processed alone and in a batch of others: identical bits (every column only sees its own
-    window).  Holds among batches that take the same kernel (below 80 column tiles here)."""
+    """A chunk post-processed alone and in a batch of others: identical bits (every column only sees its own window)."""
     ws, bs = synth.make_postnet_weights(bf16=True)
     rng = np.random.default_rng(8)
     wins = [rng.standard_normal((n, 80)).astype(np.float32) for n in (26, 50, 11, 37, 18)]
@@ -170,6 +169,29 @@ def test_result_does_not_depend_on_batch_composition():
     shuffled = pn.run(wins[::-1], keeps[::-1])[::-1]
     for a, b in zip(together, shuffled):
         np.testing.assert_array_equal(a, b)
+    pn.close()
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_result_does_not_depend_on_the_size_of_the_batch(bf16):
+    """Batches of 3 to 900 column tiles (every kernel of every layer, every number of column tiles per workgroup): a window's frames
+    are, bit for bit, those of the window alone, first, last and in the middle of the batch."""
+    ws, bs = synth.make_postnet_weights(bf16=bf16)
+    rng = np.random.default_rng(43)
+    lens, keeps = [50, 37, 11, 50, 1, 50, 26], [10, 10, 10, 0, 0, 10, 3]
+    n = 290
+    lens = [lens[i % 7] + (13 if i > 100 else 0) for i in range(n)]
+    keeps = [keeps[i % 7] for i in range(n)]
+    wins = [rng.standard_normal((k, 80)).astype(np.float32) for k in lens]
+    pn = binding.Postnet(binding.make_postnet_config(max_columns=16384, bf16=bf16), ws, bs)
+    alone = {}
+    for m in (1, 2, 11, 12, 17, 18, 19, 36, 41, 70, 71, 129, 205, n):
+        say(f"case postnet, {'bf16' if bf16 else 'fp32'}: {m} windows, {sum(lens[:m]) / 16:.1f} column tiles")
+        got = pn.run(wins[:m], keeps[:m])
+        for k in sorted({0, m // 2, max(m - 2, 0), m - 1}):
+            if k not in alone:
+                alone[k] = pn.run([wins[k]], [keeps[k]])[0]
+            np.testing.assert_array_equal(got[k], alone[k])
     pn.close()
 
 
