@@ -390,16 +390,34 @@ inline hipError_t conv_cols(const ColArgs& p, hipStream_t s)
     using V = ColWaves<COUT, TAPS>;
     auto fits = [&](int ct) { return V::GROUPS * ((p.n_ctiles + ct - 1) / ct) <= CC_CUS; };
     if (fits(2)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 2>(p, s);
-    constexpr int MOST = sizeof(XT) == 4 && CIN < 512 ? 4 : V::CT_MOST;       // (fp32, few channels: eight tiles of partial sums spill)
+    constexpr int MOST = sizeof(XT) == 4 && CIN < 512 ? 4 : V::CT_MOST;       // (fp32, few channels: 320 tiles 29 us in fours, 38 in eights; 800: 60, 69)
     if (MOST == 4 || fits(4)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 4>(p, s);
     return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, MOST>(p, s);
 }
 
+// Column tiles of a call from which a layer takes the kernel above (the sums are the same, so every layer has a line of its own).
+// Launches in us, small-call kernel / the kernel above:
+//   two-byte  512 -> 512     20 tiles  8.4 /  8.2,   24  8.8 /  8.4,   36 10.8 /  8.7,   79 16.9 / 10.3
+//             96 -> 512      20        4.2 /  3.8,   36  4.8 /  4.1,   79  6.9 /  5.3
+//             projection     20        5.5 /  5.1,   24  5.2 /  5.5,   28  7.4 /  5.9,   79 13.6 / 10.0
+//             512 -> 80      79        5.3 /  7.4,  100  6.0 /  8.1,  128  8.1 /  8.0,  256 12.3 /  7.9
+//   fp32      512 -> 512     24       22.0 / 23.1,   28 27.7 / 23.3,   40 35.2 / 23.7,   79 65.0 / 41.8
+//             96 -> 512      24        6.2 /  7.8,   28  7.3 /  7.6,   36  9.6 /  8.2,   79 13.0 / 12.9
+//             projection     36       17.0 / 19.9,   79 31.4 / 34.3,  128 48.5 / 60.3,  160 60.2 / 61.2,  200 74.0 / 62.2
+//             512 -> 80      79       16.2 / 38.4,  200 30.2 / 38.5,  256 36.4 / 38.4,  320 48.4 / 38.8
+// (512 -> 80 has five row tiles only: above, a workgroup has all of K in a chain, whatever the size of the call.  The projection in fp32
+// changes sides three times between 28 and 160 tiles with the last wave of its workgroups, by 3 us up to 100 tiles.)
+template <typename XT, int COUT, int TAPS> constexpr int cols_from()
+{
+    constexpr bool TWO_BYTE = sizeof(XT) == 2;
+    return COUT == PN_COUT_LAST ? (TWO_BYTE ? 128 : 260) : TAPS == 1 && !TWO_BYTE ? 160 : 25;
+}
+
 template <typename XT, int CIN, int COUT, int EPI>
-inline hipError_t conv_layer(bool wide, const void* W, const float* b, const void* xin, XT* xout, const int* cmeta, int n_ctiles,
+inline hipError_t conv_layer(const void* W, const float* b, const void* xin, XT* xout, const int* cmeta, int n_ctiles,
                              const float* mel, int n_mel, const int* orow, float* out, hipStream_t s)
 {
-    if (wide) {
+    if (n_ctiles >= cols_from<XT, COUT, PN_TAPS>()) {
         ColArgs p{};
         p.W = (const uint4*)W;
         p.bias = b;
@@ -420,10 +438,5 @@ inline hipError_t conv_layer(bool wide, const void* W, const float* b, const voi
     }
     return hipGetLastError();
 }
-
-// Calls of at least this many column tiles take the kernel above (two-byte mode, 512 -> 512 layers, 75 tiles: 14.5 us in the narrow
-// kernel, 10.7 in this one).
-constexpr int PN_WIDE_FROM = 40;
-template <typename XT> constexpr int enc_wide_from() { return sizeof(XT) == 2 ? 40 : 80; }
 
 }  // namespace tts

@@ -512,7 +512,6 @@ hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const 
 {
     constexpr int C = ENC_DIM;
     const int n_ctiles = (n_col + 15) / 16, n_col_pad = n_ctiles * 16;
-    const bool wide = n_ctiles >= enc_wide_from<XT>();
     XT* x0 = reinterpret_cast<XT*>(d.act[0]);
     XT* x1 = reinterpret_cast<XT*>(d.act[1]);
     EncTables tb;
@@ -520,11 +519,11 @@ hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const 
     hipLaunchKernelGGL((k_enc_embed<XT>), dim3((n_col_pad + 3) / 4), dim3(256), 0, s, tb, staged, n_col, n_col_pad, x0, d.cmeta, d.hx,
                        sizeof(XT) == 2 ? 0 : w.n * 4 * ENC_HID, d.gave_up);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[0], d.conv_b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[1], d.conv_b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(wide, d.conv_w[2], d.conv_b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(d.conv_w[0], d.conv_b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(d.conv_w[1], d.conv_b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(d.conv_w[2], d.conv_b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e != hipSuccess) return e;
-    if (wide) {
+    if (n_ctiles >= cols_from<XT, 2 * ENC_GATES, 1>()) {
         ColArgs p{};
         p.W = (const uint4*)d.w_ih[0];
         p.W1 = (const uint4*)d.w_ih[1];

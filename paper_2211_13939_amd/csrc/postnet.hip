@@ -66,14 +66,13 @@ template <typename XT>
 static hipError_t run_typed(const PostnetPtrs& d, const float* mel, int n_ctiles, float* out, hipStream_t s)
 {
     constexpr int C1 = PN_CIN0, C = PN_CHANNELS, CO = PN_COUT_LAST;
-    const bool wide = n_ctiles >= PN_WIDE_FROM;
     XT* x0 = reinterpret_cast<XT*>(d.act[0]);
     XT* x1 = reinterpret_cast<XT*>(d.act[1]);
-    hipError_t e = conv_layer<XT, C1, C, PN_EPI_TANH>(wide, d.W[0], d.b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(wide, d.W[1], d.b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(wide, d.W[2], d.b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(wide, d.W[3], d.b[3], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, CO, PN_EPI_LAST>(wide, d.W[4], d.b[4], x0, (XT*)nullptr, d.cmeta, n_ctiles, mel, d.n_mel, d.orow, out, s);
+    hipError_t e = conv_layer<XT, C1, C, PN_EPI_TANH>(d.W[0], d.b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(d.W[1], d.b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(d.W[2], d.b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(d.W[3], d.b[3], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, CO, PN_EPI_LAST>(d.W[4], d.b[4], x0, (XT*)nullptr, d.cmeta, n_ctiles, mel, d.n_mel, d.orow, out, s);
     return e;
 }
 

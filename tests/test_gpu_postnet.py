@@ -174,24 +174,30 @@ def test_result_does_not_depend_on_batch_composition():
 
 @pytest.mark.parametrize("bf16", [True, False])
 def test_result_does_not_depend_on_the_size_of_the_batch(bf16):
-    """Batches of 3 to 900 column tiles (every kernel of every layer, every number of column tiles per workgroup): a window's frames
-    are, bit for bit, those of the window alone, first, last and in the middle of the batch."""
+    """Batches of 3 to 700 column tiles, on both sides of every line (where a layer changes its kernel: 25, 128, 260; where the kernel of
+    large calls changes its tiles: 64, 128): a window's frames are, bit for bit, those of the window alone."""
     ws, bs = synth.make_postnet_weights(bf16=bf16)
     rng = np.random.default_rng(43)
-    lens, keeps = [50, 37, 11, 50, 1, 50, 26], [10, 10, 10, 0, 0, 10, 3]
-    n = 290
-    lens = [lens[i % 7] + (13 if i > 100 else 0) for i in range(n)]
-    keeps = [keeps[i % 7] for i in range(n)]
-    wins = [rng.standard_normal((k, 80)).astype(np.float32) for k in lens]
-    pn = binding.Postnet(binding.make_postnet_config(max_columns=16384, bf16=bf16), ws, bs)
+    size = lambda i: (50, 37, 11, 50, 1, 63, 26)[i % 7]
+    keep = lambda i, k: min((10, 10, 10, 0, 0, 10, 3)[i % 7], k - 1)
+    mel = rng.standard_normal((700 * 16, 80)).astype(np.float32)
+    pn = binding.Postnet(binding.make_postnet_config(max_columns=700 * 16, bf16=bf16), ws, bs)
     alone = {}
-    for m in (1, 2, 11, 12, 17, 18, 19, 36, 41, 70, 71, 129, 205, n):
-        say(f"case postnet, {'bf16' if bf16 else 'fp32'}: {m} windows, {sum(lens[:m]) / 16:.1f} column tiles")
-        got = pn.run(wins[:m], keeps[:m])
-        for k in sorted({0, m // 2, max(m - 2, 0), m - 1}):
-            if k not in alone:
-                alone[k] = pn.run([wins[k]], [keeps[k]])[0]
-            np.testing.assert_array_equal(got[k], alone[k])
+    for tiles in (3, 24, 25, 64, 65, 127, 128, 129, 259, 260, 261, 700):
+        wins, keeps, at = [], [], 0
+        while at < 16 * tiles - 5:                         # the last window ends inside the last tile
+            k = min(size(len(wins)), 16 * tiles - 5 - at)
+            keeps.append(keep(len(wins), k))
+            wins.append(mel[at:at + k])
+            at += k
+        say(f"case postnet, {'bf16' if bf16 else 'fp32'}: {len(wins)} windows, {tiles} column tiles")
+        got = pn.run(wins, keeps)
+        n = len(wins)
+        for i in sorted({0, 1, n // 2, n - 2, n - 1} & set(range(n))):
+            key = (i, len(wins[i]))
+            if key not in alone:
+                alone[key] = pn.run([wins[i]], [keeps[i]])[0]
+            np.testing.assert_array_equal(got[i], alone[key])
     pn.close()
 
 
@@ -363,7 +369,7 @@ def test_packing_of_many_short_windows(bf16, n):
 
 @pytest.mark.parametrize("bf16", [False, True])
 def test_column_tiles_of_the_large_batch_kernel(bf16):
-    """Ragged batches on both sides of every line of the rule that gives a workgroup its column tiles (from 40 tiles on; 64 and 128
+    """Ragged batches on both sides of every line of the rule that gives a workgroup its column tiles (from 25 tiles on; 64 and 128
     tiles), with whole and barely begun last tiles: the same windows give the same bits in all of them, and the oracle's values."""
     from oracle import oracle as orc
     ws, bs = synth.make_postnet_weights(bf16=bf16)
