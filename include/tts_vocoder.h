@@ -103,7 +103,8 @@ int tts_vocoder_create(const tts_vocoder_config *cfg, const tts_vocoder_weights 
  *   flags        HOST [n]: TTS_VOCODER_FIRST and / or TTS_VOCODER_LAST.  A chunk without FIRST needs a slot whose
  *                previous chunk went through this object and was not LAST.
  *   d_audio      DEVICE, fp32: the responses back to back; response i has out_samples[i] samples (see the table
- *                at the top; at most 256 * (overlap + n_frames[i])).  The caller provides room for the sum.
+ *                at the top; at most 256 * (overlap + n_frames[i])).  The caller provides room for the sum.  It may
+ *                overlap d_mel: every frame is read before the first sample is written.
  *   out_samples  HOST [n], written before the call returns.
  * Asynchronous on the stream (the host arrays are consumed before the call returns).
  * Errors: TTS_E_INVAL for null pointers, n outside 1 .. max_batch, bad lengths, slots or flags; the state is

@@ -54,7 +54,7 @@ ConvShape post_shape(bool bf) { return shape_of(1, voc_channels(VOC_STAGES - 1),
 struct VocLayout {
     size_t pre_w, pre_b, up_w[VOC_STAGES], up_b[VOC_STAGES];
     size_t res_w[VOC_STAGES][VOC_BLOCKS], res_b[VOC_STAGES][VOC_BLOCKS];
-    size_t post_w, post_b, alpha, beta, m_tail, s_tail, turn, len, x0, y, r[VOC_BLOCKS], total;
+    size_t post_w, post_b, alpha, beta, m_tail, s_tail, kept, turn, len, x0, y, r[VOC_BLOCKS], total;
     size_t state_begin;   // everything from here on is cleared at creation
 };
 
@@ -83,6 +83,7 @@ VocLayout layout_of(const tts_vocoder_config& c)
     l.state_begin = a.off;
     l.m_tail = a.take((size_t)c.max_requests * n_ov * VOC_N_MEL * 4);
     l.s_tail = a.take(2 * (size_t)c.max_requests * n_ov * VOC_HOP * 4);
+    l.kept = a.take((size_t)c.max_batch * n_ov * VOC_N_MEL * 4);
     l.turn = a.take((size_t)c.max_requests * 4);
     l.len = a.take(VOC_MAX_BATCH * 4);
     l.x0 = a.take(frames * VOC_C0 * 4);
@@ -225,6 +226,7 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
     d.m_tail = (float*)(base + lay.m_tail);
     d.s_tail = (float*)(base + lay.s_tail);
     d.s_tail_turn = (size_t)cfg->max_requests * cfg->overlap * VOC_HOP;
+    d.kept = (float*)(base + lay.kept);
     d.turn = (int*)(base + lay.turn);
     d.len = (int*)(base + lay.len);
     d.x0 = (float*)(base + lay.x0);

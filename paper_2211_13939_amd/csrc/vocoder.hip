@@ -221,16 +221,27 @@ __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __res
 // with a previous chunk come from the slot's tail, the others from the caller's chunk, four words at a time (his frames need only
 // be aligned to them).  Publishes the windows' lengths.  (A launch that wrote the windows to memory first took 2.9 us for one
 // window, 4.4 us for 64.)
+// The frames that become the slot's tail(M_pre) are taken here too, by the workgroups of one more column of the grid, so that this
+// launch is the only one to read the caller's frames: his samples, which the last one writes, may lie where they lay.  They wait in
+// `kept`, since other workgroups of this launch still read the old tail.
 template <typename XT>
 __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, const float* __restrict__ d_mel, const float* __restrict__ m_tail,
-                                                          int* __restrict__ len, int* __restrict__ turn, int ov, int window)
+                                                          float* __restrict__ kept, int* __restrict__ len, int* __restrict__ turn, int ov, int window)
 {
     constexpr int CIN = VOC_N_MEL, KS = VOC_K_PRE, TP = vc_tp<XT, CIN, VOC_C0, (KS - 1) / 2, true>();
     __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
     const int w = blockIdx.y, ovw = b.has_prev[w] ? ov : 0, valid = ovw + b.n_frames[w], p0 = blockIdx.x * TP;
-    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
-        len[w] = valid;
-        turn[b.slot[w]] ^= 1;
+    if (blockIdx.x == gridDim.x - 1) {                         // the column that has no tile
+        if (blockIdx.z != 0) return;
+        if (threadIdx.x == 0) {
+            len[w] = valid;
+            turn[b.slot[w]] ^= 1;
+        }
+        if (!b.last[w]) {                                      // at least ov frames here
+            const float* src = d_mel + (size_t)(b.src_row[w] + b.n_frames[w] - ov) * CIN;
+            for (int e = threadIdx.x; e < ov * CIN; e += VC_THREADS) kept[w * ov * CIN + e] = src[e];
+        }
+        return;
     }
     if (p0 >= valid) return;
     const float* mel = d_mel + ((ptrdiff_t)b.src_row[w] - ovw) * CIN;
@@ -247,12 +258,12 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, 
 // it was the request's last.  Each slot has two tails of audio, which calls read and write in turn (the workgroups of a launch come in
 // any order); whose turn it is lies in device memory, where the call's first layer has changed it: a call that was captured goes on
 // with the stream at every replay.
-// (The mel tail is written here because the first layer reads the old one.)  As a launch of its own behind the last layer this took 3.3 us
+// (The mel tail gets its new frames here because the first layer reads the old ones.)  As a launch of its own behind the last layer this took 3.3 us
 // for one window, 4.5 us for 64.
 template <typename XT, bool SHORT>
 __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, const float* __restrict__ alpha, const float* __restrict__ beta,
                                                          float* __restrict__ s_tail, size_t s_tail_turn, const int* __restrict__ turn, float* __restrict__ d_audio,
-                                                         const float* __restrict__ d_mel, float* __restrict__ m_tail, int ov, int window)
+                                                         const float* __restrict__ kept, float* __restrict__ m_tail, int ov, int window)
 {
     constexpr int CIN = voc_channels(VOC_STAGES - 1), KS = VOC_K_POST, TP = vc_tp<XT, CIN, 16, (KS - 1) / 2, SHORT>();
     __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
@@ -260,8 +271,8 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, c
     const bool hp = b.has_prev[w], last = b.last[w];
     const int valid = ((hp ? ov : 0) + nf) * VOC_HOP, p0 = blockIdx.x * TP, N = ov * VOC_HOP;
     if (p0 >= valid) return;
-    if (blockIdx.x == 0 && !last) {                            // nf >= ov here
-        const float* src = d_mel + (size_t)(b.src_row[w] + nf - ov) * VOC_N_MEL;
+    if (blockIdx.x == 0 && !last) {
+        const float* src = kept + w * ov * VOC_N_MEL;
         float* dst = m_tail + (size_t)b.slot[w] * ov * VOC_N_MEL;
         for (int e = threadIdx.x; e < ov * VOC_N_MEL; e += VC_THREADS) dst[e] = src[e];
     }
@@ -665,8 +676,8 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     pre.W = reinterpret_cast<const uint4*>(d.pre_w);
     pre.bias = d.pre_b;
     constexpr int PRE_TP = vc_tp<XT, VOC_N_MEL, VOC_C0, (VOC_K_PRE - 1) / 2, true>();
-    hipLaunchKernelGGL((k_voc_first<XT>), dim3((d.window + PRE_TP - 1) / PRE_TP, b.n, VOC_C0 / 64), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.len,
-                       d.turn, d.overlap, d.window);
+    hipLaunchKernelGGL((k_voc_first<XT>), dim3((d.window + PRE_TP - 1) / PRE_TP + 1, b.n, VOC_C0 / 64), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.kept,
+                       d.len, d.turn, d.overlap, d.window);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = stage_launch<XT, 0>(d, b.n, s);
     if (e == hipSuccess) e = stage_launch<XT, 1>(d, b.n, s);
@@ -681,7 +692,7 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     post.bias = d.post_b;
     auto last = [&](auto kern, int tp) {
         hipLaunchKernelGGL(kern, dim3((d.window * VOC_HOP + tp - 1) / tp, b.n), dim3(VC_THREADS), 0, s, b, post, d.alpha, d.beta, d.s_tail, d.s_tail_turn, d.turn, d_audio,
-                           d_mel, d.m_tail, d.overlap, d.window);
+                           d.kept, d.m_tail, d.overlap, d.window);
     };
     constexpr int CL = voc_channels(VOC_STAGES - 1), LONG_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2>(), SHORT_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2, true>();
     if ((long)((d.window * VOC_HOP + LONG_TP - 1) / LONG_TP) * b.n < VC_SHORT_BELOW) last(k_voc_last<XT, true>, SHORT_TP);

@@ -34,6 +34,7 @@ struct VocoderPtrs {
     float* m_tail;      // [max_requests][overlap][n_mel]   tail(M_pre) of every state slot
     float* s_tail;      // [2][max_requests][overlap * 256] tail(S_pre): a slot's calls read one and write the other in turn
     size_t s_tail_turn; // elements between the two
+    float* kept;        // [max_batch][overlap][n_mel]      last frames of this call's chunks, from its first launch to its last
     int* turn;          // [max_requests]  which of the two the slot's latest call writes (its calls' first launch changes it)
     int* len;           // [max_batch] frames in window i of this call (overlap frames in front included)
     float* x0;          // [max_batch * window][c0]         conv_pre output

@@ -121,6 +121,39 @@ def test_streams_follow_eq3_eq4(overlap):
     voc.close()
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("overlap", [0, 3, 16])
+def test_samples_may_lie_where_the_frames_lay(bf16, overlap):
+    """One buffer for a call's frames and its samples, the samples on top of the frames or beginning a little in front of them: first,
+    middle and last chunks of five requests give the bits that separate buffers give (the frames a slot keeps are read before the
+    first sample is written)."""
+    import torch
+    w = synth.make_vocoder_weights(bf16=bf16)
+    rng = np.random.default_rng(41 + overlap)
+    n, rounds = 5, 4
+    cfg = binding.make_vocoder_config(overlap=overlap, max_chunk=40, max_requests=n, max_batch=n, bf16=bf16)
+    chunks = [[_mel(rng, int(k)) for k in rng.integers(max(overlap, 1), 41, size=n)] for _ in range(rounds)]
+    flags = [(FIRST if r == 0 else 0) | (LAST if r == rounds - 1 else 0) for r in range(rounds)]
+    apart = binding.Vocoder(cfg, w)
+    want = [apart.run(c, list(range(n)), [f] * n) for c, f in zip(chunks, flags)]
+    apart.close()
+    for ahead in (0, 52):                     # floats from the first sample to the first frame
+        say(f"case vocoder, one buffer: overlap {overlap}, {'bf16' if bf16 else 'fp32'}, frames {ahead} floats behind the samples")
+        voc = binding.Vocoder(cfg, w)
+        for c, f, ref in zip(chunks, flags, want):
+            rows = sum(m.shape[0] for m in c)
+            buf = torch.zeros(ahead + (rows + n * overlap) * HOP, device=voc.device)
+            mel = buf[ahead:ahead + rows * 80].view(rows, 80)
+            mel.copy_(torch.from_numpy(np.concatenate(c)))
+            torch.cuda.synchronize()
+            out = voc.run_device(mel, [m.shape[0] for m in c], list(range(n)), [f] * n, buf)
+            torch.cuda.synchronize()
+            got = buf.cpu().numpy()
+            assert out == [x.shape[0] for x in ref]
+            np.testing.assert_array_equal(got[:sum(out)], np.concatenate(ref))
+        voc.close()
+
+
 def test_response_does_not_depend_on_batch_composition():
     w = synth.make_vocoder_weights(bf16=True)
     rng = np.random.default_rng(15)
