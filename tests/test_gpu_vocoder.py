@@ -312,11 +312,12 @@ def test_largest_batch_of_short_chunks():
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("n,window", [(48, 48), (48, 49), (47, 48), (11, 67)])
+@pytest.mark.parametrize("n,window", [(48, 48), (48, 49), (47, 48), (11, 67), (171, 49)])
 def test_windows_around_the_tiles_of_the_residual_blocks(bf16, n, window):
     """Windows whose ends fall next to the ends of tiles and regions (whole windows of up to 48 frames from 48 windows on, tiles
-    with a halo otherwise; 32, 64 and 128 positions a column tile): every response equals, bit for bit, the same chunk's alone,
-    and the oracle's for the shortest, two odd ones and the longest."""
+    with a halo otherwise, the largest of them where there are 1024 workgroups: 171 windows of 49 frames; 32, 64 and 128 positions a
+    column tile): responses equal, bit for bit, the same chunk's alone, and the oracle's for the shortest, an odd one and the two
+    longest."""
     from oracle import oracle as orc
     w = synth.make_vocoder_weights(bf16=bf16)
     rng = np.random.default_rng(29)
