@@ -87,9 +87,10 @@ struct Quad3 {
 //   valid  positions of this window that exist (input side); wbase = first position of the window in the arrays
 //   p0     first position of the tile inside the window
 //   fetch  (position that exists, channel / 4) -> Quad1 or Quad3
+//   seen   (position, channel / 4, the four values): every piece that is staged, among them such as lie outside the window (values of no meaning)
 //   emit   (position, sample): EPI_POST, instead of a store
-template <typename XT, int CIN, int ROWS, int COUT, int KS, int TP, int EPI, bool PRE_ACT, int U, typename FETCH, typename EMIT>
-__device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wbase, int p0, uint4* lds, FETCH fetch, EMIT emit)
+template <typename XT, int CIN, int ROWS, int COUT, int KS, int TP, int EPI, bool PRE_ACT, int U, typename FETCH, typename SEEN, typename EMIT>
+__device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wbase, int p0, uint4* lds, FETCH fetch, SEEN seen, EMIT emit)
 {
     using G = VcGeom<XT, CIN>;
     constexpr int KB = Frag<XT>::KB;
@@ -119,6 +120,7 @@ __device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wba
             const int idx = i0 + i * VC_THREADS + tid, row = idx / C4, c4 = idx - row * C4;
             if (idx >= N_STAGE) break;
             float4 u = v[i].value();
+            seen(p0 - halo + row, c4, u);
             if constexpr (PRE_ACT) { u.x = lrelu(u.x); u.y = lrelu(u.y); u.z = lrelu(u.z); u.w = lrelu(u.w); }
             if ((unsigned)(p0 - halo + row) >= (unsigned)valid) u = make_float4(0.f, 0.f, 0.f, 0.f);
             lds_put4<XT>(lds, ((4 * c4 / G::EPL) * STRIDE + row) * G::EPL + 4 * c4 % G::EPL, u);
@@ -214,16 +216,16 @@ __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __res
         if constexpr (SRC3) return Quad3{quad_at<CIN>(in0, p, c4), quad_at<CIN>(in1, p, c4), quad_at<CIN>(in2, p, c4)};
         else return Quad1{quad_at<CIN>(in0, p, c4)};
     };
-    conv_tile<XT, CIN, ROWS, COUT, KS, TP, EPI, PRE_ACT, U>(a, valid, wbase, p0, lds, fetch, [](int, float) {});
+    conv_tile<XT, CIN, ROWS, COUT, KS, TP, EPI, PRE_ACT, U>(a, valid, wbase, p0, lds, fetch, [](int, int, float4) {}, [](int, float) {});
 }
 
 // The first layer, on the spliced windows [tail(M_pre), M_cur] (Eq. 3 line 1), which exist nowhere else: frames [0, ov) of a window
 // with a previous chunk come from the slot's tail, the others from the caller's chunk, four words at a time (his frames need only
 // be aligned to them).  Publishes the windows' lengths.  (A launch that wrote the windows to memory first took 2.9 us for one
 // window, 4.4 us for 64.)
-// The frames that become the slot's tail(M_pre) are taken here too, by the workgroups of one more column of the grid, so that this
-// launch is the only one to read the caller's frames: his samples, which the last one writes, may lie where they lay.  They wait in
-// `kept`, since other workgroups of this launch still read the old tail.
+// The frames that become the slot's tail(M_pre) are kept aside while they are staged, so that this launch is the only one to read the
+// caller's frames: his samples, which the last one writes, may lie where they lay.  (They wait in `kept`, since other workgroups of this
+// launch still read the old tail.  Read once more by workgroups of their own they cost 0.9 us of a round of one window.)
 template <typename XT>
 __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, const float* __restrict__ d_mel, const float* __restrict__ m_tail,
                                                           float* __restrict__ kept, int* __restrict__ len, int* __restrict__ turn, int ov, int window)
@@ -231,17 +233,9 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, 
     constexpr int CIN = VOC_N_MEL, KS = VOC_K_PRE, TP = vc_tp<XT, CIN, VOC_C0, (KS - 1) / 2, true>();
     __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
     const int w = blockIdx.y, ovw = b.has_prev[w] ? ov : 0, valid = ovw + b.n_frames[w], p0 = blockIdx.x * TP;
-    if (blockIdx.x == gridDim.x - 1) {                         // the column that has no tile
-        if (blockIdx.z != 0) return;
-        if (threadIdx.x == 0) {
-            len[w] = valid;
-            turn[b.slot[w]] ^= 1;
-        }
-        if (!b.last[w]) {                                      // at least ov frames here
-            const float* src = d_mel + (size_t)(b.src_row[w] + b.n_frames[w] - ov) * CIN;
-            for (int e = threadIdx.x; e < ov * CIN; e += VC_THREADS) kept[w * ov * CIN + e] = src[e];
-        }
-        return;
+    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
+        len[w] = valid;
+        turn[b.slot[w]] ^= 1;
     }
     if (p0 >= valid) return;
     const float* mel = d_mel + ((ptrdiff_t)b.src_row[w] - ovw) * CIN;
@@ -250,7 +244,12 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, 
         const float* f = (p < ovw ? tail : mel) + p * CIN + 4 * c4;
         return Quad1{make_float4(f[0], f[1], f[2], f[3])};
     };
-    conv_tile<XT, CIN, VOC_C0, VOC_C0, KS, TP, EPI_PLAIN, false, 1>(a, valid, (size_t)w * window, p0, lds, fetch, [](int, float) {});
+    // the window's last ov frames, all of them the caller's (where the chunk is the request's last they are kept in vain)
+    const int k0 = blockIdx.z == 0 ? max(valid - ov, p0) : valid, k1 = min(valid, p0 + TP);
+    auto keep = [&](int p, int c4, float4 v) __attribute__((always_inline)) {
+        if (p >= k0 && p < k1) *reinterpret_cast<float4*>(kept + ((size_t)w * ov + p - (valid - ov)) * CIN + 4 * c4) = v;
+    };
+    conv_tile<XT, CIN, VOC_C0, VOC_C0, KS, TP, EPI_PLAIN, false, 1>(a, valid, (size_t)w * window, p0, lds, fetch, keep, [](int, float) {});
 }
 
 // The last layer, and what becomes of its samples S_cur: the first ov * 256 of a window with a previous chunk are fused with the
@@ -289,7 +288,7 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, c
     const size_t wbase = (size_t)w * window * VOC_HOP;
     const float *in0 = a.in0 + wbase * CIN, *in1 = a.in1 + wbase * CIN, *in2 = a.in2 + wbase * CIN;
     auto fetch = [&](int p, int c4) __attribute__((always_inline)) { return Quad3{quad_at<CIN>(in0, p, c4), quad_at<CIN>(in1, p, c4), quad_at<CIN>(in2, p, c4)}; };
-    conv_tile<XT, CIN, 16, 1, KS, TP, EPI_POST, true, 1>(a, valid, wbase, p0, lds, fetch, emit);
+    conv_tile<XT, CIN, 16, 1, KS, TP, EPI_POST, true, 1>(a, valid, wbase, p0, lds, fetch, [](int, int, float4) {}, emit);
 }
 
 // ---------------------------------------------------------------------------
@@ -676,7 +675,7 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     pre.W = reinterpret_cast<const uint4*>(d.pre_w);
     pre.bias = d.pre_b;
     constexpr int PRE_TP = vc_tp<XT, VOC_N_MEL, VOC_C0, (VOC_K_PRE - 1) / 2, true>();
-    hipLaunchKernelGGL((k_voc_first<XT>), dim3((d.window + PRE_TP - 1) / PRE_TP + 1, b.n, VOC_C0 / 64), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.kept,
+    hipLaunchKernelGGL((k_voc_first<XT>), dim3((d.window + PRE_TP - 1) / PRE_TP, b.n, VOC_C0 / 64), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.kept,
                        d.len, d.turn, d.overlap, d.window);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = stage_launch<XT, 0>(d, b.n, s);
