@@ -14,28 +14,16 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
          # the first 16 dwords of a kernel's arguments arrive in scalar registers with the wave (gfx950 preloads them):
          # the first loads of a kernel no longer wait for a cold read of the argument block
          "-mllvm", "-amdgpu-kernarg-preload-count=16",
-         # accumulators of the matrix instructions in ordinary vector registers: left to its heuristics the compiler kept them in
-         # the accumulation half of the file in kernels of 256 threads (vocoder.hip) and moved every sum out and in around each
-         # convolution, 15155 moves in that file's assembly against 85 (vocoder, a stream of 64 requests 1.25 -> 1.11 ms, of one
-         # request 322 -> 310 us; the other files had no such moves and their times stay)
+         # accumulators of the matrix instructions in ordinary vector registers.  Left to its heuristics the compiler keeps them in the
+         # accumulation half of the file in the vocoder's up-samplings and its last layer, with 544 moves in and out (none with the
+         # option): a two-byte call of 128 windows of 48 frames 512 -> 509 us, of 256 1049 -> 1040; up to 64 windows, in fp32 and in the
+         # other files, whose kernels hold no such moves either way, the times are the same
          "-mllvm", "-amdgpu-mfma-vgpr-form=1",
          "-Wall", "-Wno-unused-result"]
 
 
 def sources():
     return [os.path.join(CSRC, s) for s in SOURCES]
-
-
-def stale() -> bool:
-    if not os.path.exists(OUT):
-        return True
-    t = os.path.getmtime(OUT)
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)]
-    deps.append(os.path.join(HERE, "..", "include", "tts_pool.h"))
-    deps.append(os.path.join(HERE, "..", "include", "tts_postnet.h"))
-    deps.append(os.path.join(HERE, "..", "include", "tts_vocoder.h"))
-    deps.append(os.path.join(HERE, "..", "include", "tts_encoder.h"))
-    return any(os.path.getmtime(d) > t for d in deps)
 
 
 def build(verbose: bool = False) -> str:

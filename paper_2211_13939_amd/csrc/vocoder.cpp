@@ -164,7 +164,9 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
                       }), bf);
     };
     // a convolution of the residual blocks: where positions are formed in pairs, GEMM row = position of the pair * c_out + channel,
-    // and the second position meets the same taps one further on
+    // and the second position meets the same taps one further on.  The tap that only one of the two positions has is multiplied by a zero weight
+    // for the other one: values that no longer fit the operand type (infinities, beyond 65504 in the two-byte mode) reach one position
+    // further than the convolution's own taps, as NaN, and never another window
     auto put_res = [&](size_t off, int s, int b, const float* src) {
         const ConvShape sh = res_shape(s, b, bf);
         const int c_out = voc_channels(s), taps = voc_block_k(b);

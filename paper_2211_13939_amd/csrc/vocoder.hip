@@ -623,7 +623,18 @@ hipError_t blocks_launch_tp(const VrArgs3& a, const int* len, int rate, int wind
 template <int C, int LEVEL> constexpr int vr_tp() { return LEVEL == 3 ? 8 : ((C >= 32 ? 256 : 512) >> LEVEL) + 8; }
 // With 64 channels (8 positions a frame) the halo of a tile of 128 doubles its work.  A window of up to 384 positions fits a
 // workgroup's registers and LDS and needs none: a CU per window and block, which pays from a few dozen windows on
-// (64 windows: 58 us a launch in tiles of 128, 43 whole).
+// (64 windows: 58 us a launch in tiles of 128, 43 whole).  The rule looks at the configured window; a whole call, us, in tiles with a
+// halo / whole, for windows of that many frames in a configuration of 48:
+//               8            16           24           32           44
+//   two-byte  48 windows  137 /  144   149 /  160   185 /  193   193 /  198   251 /  242
+//             64          154 /  161   160 /  169   230 /  223   240 /  232   308 /  287
+//            128          240 /  243   257 /  257   408 /  376   427 /  396   569 /  509
+//            256          498 /  423   519 /  451   762 /  695   820 /  758  1126 / 1040
+//   fp32      48          620 /  739   618 /  739   904 / 1025   912 / 1032  1233 / 1284
+//             64          735 /  857   730 /  850  1159 / 1211  1165 / 1216  1556 / 1523
+//            128         1219 / 1263  1221 / 1261  2199 / 2005  2213 / 2015  2975 / 2632
+//            256         3196 / 2480  3068 / 2400  4621 / 3934  4615 / 3951  5890 / 5215
+// A call of 48 to 128 short windows would be better off in tiles, by 3 to 11 us (two-byte) or 40 to 120 us (fp32).
 constexpr int VR_WHOLE = 384;
 constexpr int VR_WHOLE_FROM = 48;                // windows from which it is used
 constexpr int VR_SMALL_BELOW = 1024;             // workgroups of the large tiling below which the half tiles are used
