@@ -68,7 +68,7 @@ def test_ragged_batch_of_chunks_matches_oracle(bf16):
 
 @pytest.mark.parametrize("bf16", [False, True])
 def test_large_batch_matches_oracle(bf16):
-    """A batch big enough for the large-batch kernel (84 column tiles): 26 windows of 50 frames (a 40-frame
+    """A batch big enough for the large-batch kernel in every layer but the last (84 column tiles): 26 windows of 50 frames (a 40-frame
     chunk behind 10 frames of context) and one of 31.  A window is its own utterance as far as the oracle
     is concerned: the frames in front of it are zero."""
     from oracle import oracle as orc
@@ -91,8 +91,8 @@ def test_large_batch_matches_oracle(bf16):
 
 def test_very_large_batch_matches_oracle_and_small_batches():
     """26 windows of 50 frames and a ragged one (1337 columns, 84 tiles: the workgroups of the large-batch kernel's
-    last columns are partial), bf16.  Against the oracle on every window, and against the same
-    windows in batches of nine (small enough for the other kernel)."""
+    last columns are partial), bf16.  Against the oracle on every window, and bit for bit against the same
+    windows in batches of seven (22 tiles: small enough for the other kernel)."""
     from oracle import oracle as orc
     ws, bs = synth.make_postnet_weights(bf16=True)
     W = orc.PostnetWeights(ws, bs)
@@ -105,15 +105,15 @@ def test_very_large_batch_matches_oracle_and_small_batches():
     pn = binding.Postnet(binding.make_postnet_config(max_columns=2048, bf16=True), ws, bs)
     got = pn.run(wins, keeps)
     small = []
-    for i in range(0, len(wins), 9):
-        small += pn.run(wins[i:i + 9], keeps[i:i + 9])
+    for i in range(0, len(wins), 7):
+        small += pn.run(wins[i:i + 7], keeps[i:i + 7])
     pn.close()
     scale = max(float(np.abs(r).max()) for r in ref)
     worst = max(float(np.abs(g - r).max()) for g, r in zip(got, ref))
-    between = max(float(np.abs(g - h).max()) for g, h in zip(got, small))
-    say(f"  max abs err {worst:.3e} (largest output {scale:.2f}); against the other kernels {between:.3e}")
+    say(f"  max abs err {worst:.3e} (largest output {scale:.2f})")
     assert worst <= TOL_BF16
-    assert between <= TOL_BF16
+    for g, h in zip(got, small):
+        np.testing.assert_array_equal(g, h)
 
 
 def test_bf16_rounding_points():
