@@ -381,20 +381,6 @@ inline hipError_t conv_cols_ct(const ColArgs& p, hipStream_t s)
     return hipGetLastError();
 }
 
-// Column tiles per workgroup: the fewest that leave no more workgroups than there are compute units, CT_MOST at most (up to there
-// the registers hold the sums and two workgroups share a CU's LDS)
-constexpr int CC_CUS = 256;
-template <typename XT, int CIN, int COUT, int TAPS, int EPI>
-inline hipError_t conv_cols(const ColArgs& p, hipStream_t s)
-{
-    using V = ColWaves<COUT, TAPS>;
-    auto fits = [&](int ct) { return V::GROUPS * ((p.n_ctiles + ct - 1) / ct) <= CC_CUS; };
-    if (fits(2)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 2>(p, s);
-    constexpr int MOST = sizeof(XT) == 4 && CIN < 512 ? 4 : V::CT_MOST;       // (fp32, few channels: 320 tiles 29 us in fours, 38 in eights; 800: 60, 69)
-    if (MOST == 4 || fits(4)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 4>(p, s);
-    return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, MOST>(p, s);
-}
-
 // Column tiles of a call from which a layer takes the kernel above (the sums are the same, so every layer has a line of its own).
 // Launches in us, small-call kernel / the kernel above:
 //   two-byte  512 -> 512     20 tiles  8.4 /  8.2,   24  8.8 /  8.4,   36 10.8 /  8.7,   79 16.9 / 10.3
@@ -411,6 +397,23 @@ template <typename XT, int COUT, int TAPS> constexpr int cols_from()
 {
     constexpr bool TWO_BYTE = sizeof(XT) == 2;
     return COUT == PN_COUT_LAST ? (TWO_BYTE ? 128 : 260) : TAPS == 1 && !TWO_BYTE ? 160 : 25;
+}
+
+// Column tiles per workgroup: the fewest that leave no more workgroups than there are compute units, CT_MOST at most (up to there
+// the registers hold the sums and two workgroups share a CU's LDS)
+constexpr int CC_CUS = 256;
+template <typename XT, int CIN, int COUT, int TAPS, int EPI>
+inline hipError_t conv_cols(const ColArgs& p, hipStream_t s)
+{
+    using V = ColWaves<COUT, TAPS>;
+    auto fits = [&](int ct) { return V::GROUPS * ((p.n_ctiles + ct - 1) / ct) <= CC_CUS; };
+    constexpr int LEAST = cols_from<XT, COUT, TAPS>();         // forms that no call of so many column tiles takes are not built
+    if constexpr (V::GROUPS * ((LEAST + 1) / 2) <= CC_CUS)
+        if (fits(2)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 2>(p, s);
+    constexpr int MOST = sizeof(XT) == 4 && CIN < 512 ? 4 : V::CT_MOST;       // (fp32, few channels: 320 tiles 29 us in fours, 38 in eights; 800: 60, 69)
+    if constexpr (MOST == 4 || V::GROUPS * ((LEAST + 3) / 4) <= CC_CUS)
+        if (MOST == 4 || fits(4)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 4>(p, s);
+    return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, MOST>(p, s);
 }
 
 template <typename XT, int CIN, int COUT, int EPI>
