@@ -393,10 +393,16 @@ inline hipError_t conv_cols_ct(const ColArgs& p, hipStream_t s)
 //             512 -> 80      79       16.2 / 38.4,  200 30.2 / 38.5,  256 36.4 / 38.4,  320 48.4 / 38.8
 // (512 -> 80 has five row tiles only: above, a workgroup has all of K in a chain, whatever the size of the call.  The projection in fp32
 // changes sides three times between 28 and 160 tiles with the last wave of its workgroups, by 3 us up to 100 tiles.)
-template <typename XT, int COUT, int TAPS> constexpr int cols_from()
+// (512 -> 512 and 96 -> 512, two-byte: traced launch by launch, as above, the kernels meet at 20 tiles; queued one behind the other the
+// small-call kernel's layer of 512 channels is the faster one up to 32, where its 32 x n / 2 workgroups are two for every compute unit.  PostNet
+// calls of 25 / 28 / 32 tiles with both lines at 25 45.4 / 46.0 / 46.5 us, at 33 45.0 / 45.6 / 45.6, at 25 and 33 44.8 / 44.8 / 45.5; encoder
+// calls 82.2 / 82.8 / 83.6 with 25, 80.4 / 81.3 / 82.5 with 33.  In fp32, one column tile a workgroup, the 25th tile begins a fourth workgroup.)
+template <typename XT, int CIN, int COUT, int TAPS> constexpr int cols_from()
 {
     constexpr bool TWO_BYTE = sizeof(XT) == 2;
-    return COUT == PN_COUT_LAST ? (TWO_BYTE ? 128 : 260) : TAPS == 1 && !TWO_BYTE ? 160 : 25;
+    if constexpr (TAPS == 1) return TWO_BYTE ? 25 : 160;
+    else if constexpr (COUT == PN_COUT_LAST) return TWO_BYTE ? 128 : 260;
+    else return TWO_BYTE && CIN == 512 ? 33 : 25;
 }
 
 // Column tiles per workgroup: the fewest that leave no more workgroups than there are compute units, CT_MOST at most (up to there
@@ -407,7 +413,7 @@ inline hipError_t conv_cols(const ColArgs& p, hipStream_t s)
 {
     using V = ColWaves<COUT, TAPS>;
     auto fits = [&](int ct) { return V::GROUPS * ((p.n_ctiles + ct - 1) / ct) <= CC_CUS; };
-    constexpr int LEAST = cols_from<XT, COUT, TAPS>();         // forms that no call of so many column tiles takes are not built
+    constexpr int LEAST = cols_from<XT, CIN, COUT, TAPS>();         // forms that no call of so many column tiles takes are not built
     if constexpr (V::GROUPS * ((LEAST + 1) / 2) <= CC_CUS)
         if (fits(2)) return conv_cols_ct<XT, CIN, COUT, TAPS, EPI, 2>(p, s);
     constexpr int MOST = sizeof(XT) == 4 && CIN < 512 ? 4 : V::CT_MOST;       // (fp32, few channels: 320 tiles 29 us in fours, 38 in eights; 800: 60, 69)
@@ -420,7 +426,7 @@ template <typename XT, int CIN, int COUT, int EPI>
 inline hipError_t conv_layer(const void* W, const float* b, const void* xin, XT* xout, const int* cmeta, int n_ctiles,
                              const float* mel, int n_mel, const int* orow, float* out, hipStream_t s)
 {
-    if (n_ctiles >= cols_from<XT, COUT, PN_TAPS>()) {
+    if (n_ctiles >= cols_from<XT, CIN, COUT, PN_TAPS>()) {
         ColArgs p{};
         p.W = (const uint4*)W;
         p.bias = b;

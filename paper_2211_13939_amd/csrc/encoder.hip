@@ -523,7 +523,7 @@ hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const 
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(d.conv_w[1], d.conv_b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(d.conv_w[2], d.conv_b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
     if (e != hipSuccess) return e;
-    if (n_ctiles >= cols_from<XT, 2 * ENC_GATES, 1>()) {
+    if (n_ctiles >= cols_from<XT, C, 2 * ENC_GATES, 1>()) {
         ColArgs p{};
         p.W = (const uint4*)d.w_ih[0];
         p.W1 = (const uint4*)d.w_ih[1];

@@ -331,9 +331,9 @@ def test_shared_recurrence_of_a_long_request_among_short_ones_fp32(n, at):
 @pytest.mark.parametrize("bf16,lens", [(False, [400, 399, 400, 66]), (False, [1, 640, 640]), (False, [640, 640, 640, 640, 1]),
                                        (True, [400, 89]), (True, [400, 239]), (True, [1, 330, 310, 640, 7])])
 def test_input_projection_of_large_calls(bf16, lens):
-    """Calls on the far side of the line from which the convolutions take whole column tiles (25 tiles), and the input projection too
-    (two-byte: 25 tiles; fp32: 160, the call of 161), with two, four and seven of them per workgroup in the projection, a whole and a barely
-    begun last tile: the oracle's values for every request."""
+    """Calls on the far side of the line from which the convolutions (fp32 25 tiles, two-byte 33) or the input projection (two-byte 25 tiles,
+    fp32 160: the calls of 31 and 161) take whole column tiles, with two, four and seven of them per workgroup in the projection, a whole
+    and a barely begun last tile: the oracle's values for every request."""
     from oracle import oracle as orc
     w = synth.make_encoder_weights(bf16=bf16)
     W = orc.EncoderWeights(w)

@@ -174,7 +174,7 @@ def test_result_does_not_depend_on_batch_composition():
 
 @pytest.mark.parametrize("bf16", [True, False])
 def test_result_does_not_depend_on_the_size_of_the_batch(bf16):
-    """Batches of 3 to 700 column tiles, on both sides of every line (where a layer changes its kernel: 25, 128, 260; where the kernel of
+    """Batches of 3 to 700 column tiles, on both sides of every line (where a layer changes its kernel: 25, 33, 128, 260; where the kernel of
     large calls changes its tiles: 64, 128): a window's frames are, bit for bit, those of the window alone."""
     ws, bs = synth.make_postnet_weights(bf16=bf16)
     rng = np.random.default_rng(43)
@@ -183,7 +183,7 @@ def test_result_does_not_depend_on_the_size_of_the_batch(bf16):
     mel = rng.standard_normal((700 * 16, 80)).astype(np.float32)
     pn = binding.Postnet(binding.make_postnet_config(max_columns=700 * 16, bf16=bf16), ws, bs)
     alone = {}
-    for tiles in (3, 24, 25, 64, 65, 127, 128, 129, 259, 260, 261, 700):
+    for tiles in (3, 24, 25, 32, 33, 64, 65, 127, 128, 129, 259, 260, 261, 700):
         wins, keeps, at = [], [], 0
         while at < 16 * tiles - 5:                         # the last window ends inside the last tile
             k = min(size(len(wins)), 16 * tiles - 5 - at)
@@ -369,8 +369,7 @@ def test_packing_of_many_short_windows(bf16, n):
 
 @pytest.mark.parametrize("bf16", [False, True])
 def test_column_tiles_of_the_large_batch_kernel(bf16):
-    """Ragged batches on both sides of every line of the rule that gives a workgroup its column tiles (from 25 tiles on; 64 and 128
-    tiles), with whole and barely begun last tiles: the same windows give the same bits in all of them, and the oracle's values."""
+    """Ragged batches on both sides of every line of the rule that gives a workgroup its column tiles (64 and 128 tiles), with whole and barely begun last tiles: the same windows give the same bits in all of them, and the oracle's values."""
     from oracle import oracle as orc
     ws, bs = synth.make_postnet_weights(bf16=bf16)
     W = orc.PostnetWeights(ws, bs)
