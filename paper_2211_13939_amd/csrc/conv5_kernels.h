@@ -144,7 +144,7 @@ __global__ __launch_bounds__(PN_THREADS) void k_pn_conv(
 // size, whichever kernel a layer of the call takes.  A chunk holds the channel fragments w, w + 8, .. of one partial sum (fp32) or two
 // (two-byte), or, with a few channels, all there are.  The price is 32 additions a wave and partial sum: with one chain over all of k,
 // which differed from the kernel above by 1.4e-4 (two-byte) and was further off 64 bits in fp32 (1.5e-6 .. 1.7e-6 of the PostNet's output
-// against 0.9e-6), a PostNet round of 64 / 256 requests took 66 / 152 us, like this 68 / 155 us; fp32 316 / 1047 us, like this 307 / 1032.
+// against 0.9e-6), a PostNet round of 64 / 256 requests took 68.7 / 163 us, like this 70.0 / 166 us; fp32 316 / 1047 us, like this 307 / 1032.
 template <typename XT> constexpr int cc_ahead() { return sizeof(XT) == 2 ? 2 : 1; }   // k steps between an operand's request and its use
 template <typename XT, int CIN, int TAPS, int CT, int WAVES> struct ColGeom {
     static constexpr int NKF = CIN / Frag<XT>::KB, NKT = TAPS * NKF;
