@@ -1,0 +1,844 @@
+// A segment of decoder steps as ONE launch, for two-byte pools whose running requests lie in the first 16 slots.
+//
+// What bounds a step of so small a pool is a chain: p -> attention LSTM -> query -> energies -> context -> decoder LSTM -> frame
+// -> p.  As launches of its own (k_lsa, k_proj) a step takes 16.8 us at one request, 6 us of it two launch boundaries with the
+// start-up and the first cold round trips behind them, and every launch pulls its share of the 36 MB of weights again.  Here the
+// workgroups stay for the whole segment: each keeps its part of the weights in registers and LDS and its part of the requests'
+// state in registers, and the links of the chain are words handed from workgroup to workgroup through memory.  One such hop takes
+// 0.4 to 0.6 us from store to seen (64 words handed to and fro between two workgroups, on one XCD or on different ones), and a
+// round of polls as long as its bytes at 25 GB/s through a CU: the form is for pools of one tile, and the words are dense.
+//
+// Workgroups (eight waves, one per CU; blockIdx % 8 is the XCD), and what each does in step s:
+//   32 x ATT   32 hidden units of the attention LSTM each: gates from p (K = 256) and the pre-sums, cell, h and the units' rank-32
+//              share of the query out; then, off the chain, the gate pre-sums of step s + 1 from a and h_att
+//   4 x LSA    per request, on one XCD: energies shared among the four, softmax, a quarter of the context's columns each; the
+//              attention weights stay in LDS, the rows of the request's memory (up to 512 positions) in registers
+//   64 x DEC   16 hidden units of the decoder LSTM each: the sums over h_dec and h_att ahead of the chain, those over a on it
+//   6 x ROWS   one row tile of the projection each; 1 x LEAD: frame, prenet, books
+// Every product and every sum is formed in the order of the kernels in kernels.hip, so a request's frames and state are the
+// same bits whichever form a step takes.
+//
+// A word is its own flag: a buffer is filled with EMPTY, a pattern no value is stored as, and a reader polls until none of its
+// words is EMPTY.  Each kind of word has three buffers, step s's is s % 3, and a workgroup empties its words of buffer (s + 1) % 3
+// (ATT: of buffer (s + 2) % 3, at the end of its step) before it stores those of step s (s + 1):
+//   * the readers of step s - 2's words, which lay there, are done: the workgroup has seen words that could not have been made
+//     before all of them were (each role's readers lie on the chain of step s - 1, which led to what it has received in step s);
+//   * a reader of step s + 1 finds them emptied: it has taken this workgroup's words of step s, which were stored after the
+//     emptying had been acknowledged (a poll that the storing wave has waited for lies in between).
+// A launch uses one of two such sets and empties the other one, whole, before it waits for anything: the next launch finds its set
+// empty whatever became of this one.
+// Every wait is bounded; a workgroup whose wait runs out marks the requests that take part in the step as ended and failed,
+// stores nothing more and leaves, and the others' waits then run out in turn.
+#include "kernels.h"
+#include "lsa_tile.h"
+#include "mfma.h"
+
+namespace tts {
+namespace {
+
+constexpr int NT = 512, NW = 8;
+constexpr int KB = Frag<h16_t>::KB;
+constexpr int NK_A = K_ATT / KB, NK_D = K_DEC / KB, NK_P = K_PROJ / KB;    // fragments per row tile: 56, 80, 48
+constexpr int F_H = HID / KB, F_A = ENC / KB, F_P = PRENET / KB;            // fragments of h, a, p: 32, 16, 8
+static_assert(F_H == 4 * NW && F_A == 2 * NW && F_P == NW, "a wave takes four fragments of h, two of a, one of p");
+constexpr int MEL_ROWS = 96;
+
+// one buffer of each kind, in bytes; a fragment is [16 slots][4 groups][8 halves of k], so that one request's share is contiguous
+constexpr int B_FRAG = 1024, B_H = F_H * B_FRAG, B_A = F_A * B_FRAG, B_P = F_P * B_FRAG;
+constexpr int B_QS = QUERY_PARTIALS * ATT * 4, B_Q = SEG_SLOTS * B_QS, B_M = SEG_SLOTS * MEL_ROWS * 4;
+constexpr int O_HA = 0, O_HD = O_HA + 3 * B_H, O_A = O_HD + 3 * B_H, O_P = O_A + 3 * B_A, O_Q = O_P + 3 * B_P, O_M = O_Q + 3 * B_Q, O_E = O_M + 3 * B_M;
+static_assert(O_E == SEG_FIXED_BYTES, "the arena's share");
+constexpr unsigned EMPTY = 0xffffffffu;
+// bit of the buffer instructions' cache policy: sc1 = agent scope (loads look past the caches of CU and XCD, stores write through)
+constexpr int AGENT = 16;
+
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+// this wave's stores so far are acknowledged: stands between the emptying of words and the words of the same step.  Placed where the
+// wave has just waited for loads that it requested after the emptying, it costs nothing.
+__device__ __forceinline__ void stores_done() { vm_in_flight_at_most<0>(); }
+
+struct Words {
+    char* base;
+    int bytes, polls;
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rs() const { return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, BUFFER_RSRC_RAW); }
+    // (the compiler may not take a round of polls for the one before)
+    __device__ __forceinline__ static void again() { asm volatile("" ::: "memory"); }
+    __device__ __forceinline__ u32x4_t look4(int lane_off, int off) const { return __builtin_amdgcn_raw_buffer_load_b128(rs(), lane_off, off, AGENT); }
+    __device__ __forceinline__ unsigned look(int lane_off, int off) const { return __builtin_amdgcn_raw_buffer_load_b32(rs(), lane_off, off, AGENT); }
+    // EMPTY itself is a NaN with all bits set, as a float and as a pair of halves: stored as another NaN
+    __device__ __forceinline__ void put(unsigned v, int lane_off, int off) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b32(v < EMPTY ? v : EMPTY - 1u, rs(), lane_off, off, AGENT);
+    }
+    __device__ __forceinline__ void put4(const floatx4& v, int lane_off, int off) const
+    {
+        u32x4_t u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) u[i] = __float_as_uint(v[i]) < EMPTY ? __float_as_uint(v[i]) : EMPTY - 1u;
+        __builtin_amdgcn_raw_buffer_store_b128(u, rs(), lane_off, off, AGENT);
+    }
+    __device__ __forceinline__ void empty(int lane_off, int off) const { __builtin_amdgcn_raw_buffer_store_b32(EMPTY, rs(), lane_off, off, AGENT); }
+    __device__ __forceinline__ void empty4(int lane_off, int off) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{EMPTY, EMPTY, EMPTY, EMPTY}, rs(), lane_off, off, AGENT);
+    }
+    __device__ __forceinline__ static bool full(const u32x4_t& v) { return max(max(v.x, v.y), max(v.z, v.w)) != EMPTY; }
+
+    // fragments first, first + 8, ... of a B operand (lane = column + 16 * group); zeros where the lane's column takes no part.
+    // False: the wait ran out.
+    // NAP: pause between polls, in units of 64 cycles (waits that are off the chain)
+    template <int N, int NAP = 0>
+    __device__ __forceinline__ bool take(int buf, int first, int lane, bool on, uint4 (&out)[N]) const
+    {
+        const int lane_off = ((lane & 15) * 4 + (lane >> 4)) * 16;
+        u32x4_t w[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) w[n] = u32x4_t{0u, 0u, 0u, 0u};
+        bool in = !on;
+        for (int spin = 0; spin < polls && !in; ++spin) {
+            again();
+#pragma unroll
+            for (int n = 0; n < N; ++n) w[n] = look4(lane_off, buf + (first + 8 * n) * B_FRAG);
+            in = true;
+#pragma unroll
+            for (int n = 0; n < N; ++n) in = in && full(w[n]);
+            if constexpr (NAP > 0) {
+                if (!in) __builtin_amdgcn_s_sleep(NAP);
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < N; ++n) out[n] = make_uint4(w[n].x, w[n].y, w[n].z, w[n].w);
+        return in;
+    }
+
+    // four units of a row tile (lane = column + 16 * unit): row tile q8 of the eight that make up fragment `frag`
+    __device__ __forceinline__ void put_units(int buf, int frag, int q8, int lane, bool on, h16_t h) const
+    {
+        // units 0, 1 and 2, 3 of a column in one word: the lanes of odd units hand theirs to the lanes before them
+        const auto sw = __builtin_amdgcn_permlane16_swap((unsigned)h.bits, (unsigned)h.bits, false, false);
+        if (on && !(lane & 16)) put(sw[0] | sw[1] << 16, unit_off(q8, lane), buf + frag * B_FRAG);
+    }
+    __device__ __forceinline__ static int unit_off(int q8, int lane) { return ((lane & 15) * 4 + (q8 >> 1)) * 16 + (q8 & 1) * 8 + (lane >> 5) * 4; }
+    __device__ __forceinline__ void empty_units(int buf, int frag, int q8, int lane) const
+    {
+        if (!(lane & 16)) empty(unit_off(q8, lane), buf + frag * B_FRAG);
+    }
+};
+
+// x of the lane 16 or 32 away, and of the lanes of a row of 16 at a distance: the sums below add the same pairs as the
+// step's kernels do with shuffles, without a trip through LDS each
+__device__ __forceinline__ float xor16(float v)
+{
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(threadIdx.x & 16 ? sw[0] : sw[1]);
+}
+__device__ __forceinline__ float xor32(float v)
+{
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(threadIdx.x & 32 ? sw[0] : sw[1]);
+}
+template <int N> __device__ __forceinline__ float ror16(float v)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x120 + N, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float wave_sum_fast(float v)
+{
+    v += xor32(v);
+    v += xor16(v);
+    v += ror16<8>(v);      // from here on a row's values repeat every eight, four, two lanes: a rotation meets the lane an xor would
+    v += ror16<4>(v);
+    v += ror16<2>(v);
+    v += ror16<1>(v);
+    return v;
+}
+
+// operands that do not change from step to step stay as they are loaded: without this the compiler keeps their conversions, twice
+// the registers, outside of the loop over the steps
+__device__ __forceinline__ void keep(u32x4_t& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ uint4 as_uint4(const u32x4_t& v) { return make_uint4(v.x, v.y, v.z, v.w); }
+
+__device__ __forceinline__ void cell(const floatx4& g, float& c, float& h)
+{
+    const float gi = sigmoidf_(g[0]), gf = sigmoidf_(g[1]);
+    const float gg = tanhf_(g[2]), go = sigmoidf_(g[3]);
+    c = gf * c + gi * gg;
+    h = go * tanhf_(c);
+}
+
+// the requests that take part in step s end here (thread c < 16 holds slot c's remaining steps)
+__device__ __forceinline__ void give_up(const DevPtrs& d, int s, int rem)
+{
+    if (threadIdx.x < 16 && s < rem) {
+        d.done[threadIdx.x] = 1;
+        d.failed[threadIdx.x] = 1;
+        *d.fault = 1;
+    }
+}
+
+// A barrier at which the waves also learn whether one of them gave up waiting.  `failed` holds the first phase in which one did
+// and phases only grow, so a wave that is late to look does not see the failure of a later phase.
+struct Phases {
+    int* failed;
+    int ph = 0;
+    __device__ __forceinline__ void sync(bool ok)
+    {
+        if (!ok) atomicMin(failed, ph);
+        lds_barrier();
+        ++ph;
+    }
+    __device__ __forceinline__ bool bad() const { return *failed < ph; }
+};
+
+__device__ __forceinline__ int next3(int b) { return b == 2 ? 0 : b + 1; }
+
+// rows 16 mt + 4 g .. + 3 of p: fragment mt / 2, group (mt % 2) * 2 + g / 2, half a group
+__device__ __forceinline__ int p_off(int mt, int col, int g) { return (col * 4 + (mt & 1) * 2 + (g >> 1)) * 16 + (g & 1) * 8; }
+constexpr int ATT_LDS_RT = 2;                               // row tiles whose late fragments lie in LDS: registers hold six
+constexpr int ATT_LATE = 6;                                 // late fragments per wave and row tile: two of a, four of h_att
+constexpr int S_ATT_W = ATT_LDS_RT * ATT_LATE * NW * 1024, S_ATT_RED = NW * 4 * 1024, S_ATT_B = F_P * 1024;
+constexpr int S_ATT = S_ATT_W + S_ATT_RED + S_ATT_B + 32 * 16 * 4;
+constexpr int S_DEC = 3 * NW * 4 * 1024 + NW * 7 * 1024;
+constexpr int S_ROWS = 6 * NW * 1024;
+constexpr int MEL_LD = MEL_ROWS + 8, HID_LD = PRENET + 8;     // halves: an odd number of 16-byte pieces a row
+constexpr int S_LEAD = 16 * (MEL_LD + HID_LD) * 2;
+constexpr int U_PAD = MAX_ENC_LEN + 48;
+constexpr int S_LSA = (NW * ENC + 16 * ATT + 2 * U_PAD + MAX_ENC_LEN + 2 * ATT + 2 * NW) * 4;
+constexpr int S_MAX = S_DEC;
+static_assert(S_ATT <= S_MAX && S_ROWS <= S_MAX && S_LEAD <= S_MAX && S_LSA <= S_MAX && S_MAX + 64 <= 160 * 1024, "the roles' LDS");
+
+// ---------------------------------------------------------------- the attention LSTM and the query
+__device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& x, int cur, int n_slots, int n_steps, int rg, char* lds, Phases ps)
+{
+    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int rt = rg * 8 + wave, unit = rt * 4 + g;
+    uint4* s_w = reinterpret_cast<uint4*>(lds);                                             // [2][6 f][8 waves][64]
+    floatx4 (*red)[4][64] = reinterpret_cast<floatx4 (*)[4][64]>(lds + S_ATT_W);
+    uint4 (*s_b)[64] = reinterpret_cast<uint4 (*)[64]>(lds + S_ATT_W + S_ATT_RED);
+    float (*s_h)[16] = reinterpret_cast<float (*)[16]>(lds + S_ATT_W + S_ATT_RED + S_ATT_B);
+
+    uint4 we[F_P], wl[8 - ATT_LDS_RT][ATT_LATE];
+#pragma unroll
+    for (int f = 0; f < F_P; ++f) we[f] = d.Wa[xfrag(NK_A, rt, f, lane)];
+#pragma unroll
+    for (int r = 0; r < 8 - ATT_LDS_RT; ++r)
+#pragma unroll
+        for (int f = 0; f < ATT_LATE; ++f) wl[r][f] = d.Wa[xfrag(NK_A, rg * 8 + r, wave + 8 * (f + 1), lane)];
+#pragma unroll
+    for (int r = 0; r < ATT_LDS_RT; ++r)
+#pragma unroll
+        for (int f = 0; f < ATT_LATE; ++f)
+            s_w[((r * ATT_LATE + f) * NW + wave) * 64 + lane] = d.Wa[xfrag(NK_A, rg * 8 + 8 - ATT_LDS_RT + r, wave + 8 * (f + 1), lane)];
+    float wq[8];                                            // W_q[16 wave + ..][32 rg + 4 k + ..]
+#pragma unroll
+    for (int k = 0; k < 8; ++k) wq[k] = d.Wq_epi[((size_t)(rg * 8 + k) * 8 + wave) * 64 + lane];
+    const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
+    const floatx4 bias4 = *reinterpret_cast<const floatx4*>(d.ba + unit * 4);
+    floatx4* pre_g = reinterpret_cast<floatx4*>(d.pre_att) + (size_t)rt * 64 + lane;
+    floatx4 pre4 = *pre_g;
+    float c = d.c_att[(size_t)col * HID + unit];
+    uint4 pb[1] = {reinterpret_cast<const uint4*>(d.xatt[cur])[xfrag(NK_A, 0, wave, lane)]};
+    const int q_off = col * B_QS + (16 * wave + 4 * g) * 4;
+
+    int b = 0, b_before = 2, b_next = 1;
+    for (int s = 0; s < n_steps; ++s) {
+        const bool on = s < rem;
+        bool ok = true;
+        if (s > 0) ok = x.take<1>(O_P + b_before * B_P, wave, lane, on, pb);
+        stores_done();
+        s_b[wave][lane] = pb[0];
+        ps.sync(ok);
+        floatx4 g4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int f = 0; f < F_P; ++f) g4 = mfma_frag<h16_t>(we[f], s_b[f][lane], g4);
+        g4 += bias4;
+        g4 += pre4;
+        float c_new = c, hf;
+        cell(g4, c_new, hf);
+        const h16_t h = from_float<h16_t>(hf);
+        s_h[4 * wave + g][col] = on ? to_float(h) : 0.f;
+        if (ps.bad()) return give_up(d, s, rem);
+        x.put_units(O_HA + b * B_H, rg, wave, lane, on, h);
+        lds_barrier();
+        // the units' share of the query: 16 rows per wave
+        {
+            floatx4 part = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < 8; ++k) part = __builtin_amdgcn_mfma_f32_16x16x4f32(wq[k], s_h[4 * k + g][col], part, 0, 0, 0);
+            if (on) x.put4(part, q_off, O_Q + b * B_Q + rg * ATT * 4);
+        }
+        if (on) c = c_new;
+        if (s + 1 == min(rem, n_steps)) {
+            // the request's last step of this segment: its state where the step kernels keep it
+            const int end = cur ^ ((s + 1) & 1);
+            d.c_att[(size_t)col * HID + unit] = c;
+            reinterpret_cast<h16_t*>(d.xatt[end])[xoff<h16_t>(NK_A, col, XA_H + unit)] = h;
+            reinterpret_cast<h16_t*>(d.xdec[end ^ 1])[xoff<h16_t>(NK_D, col, XD_HA + unit)] = h;
+        }
+
+        // off the chain: the next step's gate pre-sums over [a; h_att]
+        uint4 hb[4], ab[2];
+        // (a first: it comes last, so that the larger h_att is asked for once)
+        ok = x.take<2, 16>(O_A + b * B_A, wave, lane, on, ab);
+        ok = x.take<4, 16>(O_HA + b * B_H, wave, lane, on, hb) && ok;
+        // (step s - 1's words, whose buffer is step s + 2's: taken before this step's a was made)
+        x.empty_units(O_HA + b_before * B_H, rg, wave, lane);
+        if (on) x.empty4(q_off, O_Q + b_before * B_Q + rg * ATT * 4);
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (half) lds_barrier();
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const int r = 4 * half + r4;
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int f = 0; f < ATT_LATE; ++f) {
+                    const uint4 w = r < 8 - ATT_LDS_RT ? wl[r < 8 - ATT_LDS_RT ? r : 0][f]
+                                                       : s_w[(((r - (8 - ATT_LDS_RT)) * ATT_LATE + f) * NW + wave) * 64 + lane];
+                    acc = mfma_frag<h16_t>(w, f < 2 ? ab[f < 2 ? f : 0] : hb[f < 2 ? 0 : f - 2], acc);
+                }
+                red[wave][r4][lane] = acc;
+            }
+            if (half) lds_barrier();
+            else ps.sync(ok);
+            if (wave >> 2 == half) {
+                pre4 = red[0][wave & 3][lane];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) pre4 += red[w][wave & 3][lane];
+            }
+        }
+        if (ps.bad()) return give_up(d, s, rem);
+        b_before = b;
+        b = b_next;
+        b_next = next3(b);
+    }
+    *pre_g = pre4;
+}
+
+// ---------------------------------------------------------------- the decoder LSTM
+__device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cur, int n_slots, int n_steps, int j, char* lds, Phases ps)
+{
+    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15;
+    floatx4 (*red_a)[4][64] = reinterpret_cast<floatx4 (*)[4][64]>(lds);
+    floatx4 (*red_hd)[4][64] = red_a + NW;
+    floatx4 (*red_ha)[4][64] = red_hd + NW;
+    uint4* s_w = reinterpret_cast<uint4*>(lds + 3 * NW * 4 * 1024) + wave * 7 * 64 + lane;      // [wave][7][64]: the wave's own
+    uint4 w[4][NK_D / NW];                                  // fragments wave + 8 f: h_att (f = 0 .. 3), a (4, 5), h_dec (6 .. 9)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int f = 0; f < NK_D / NW; ++f)
+            if (r < 3 || f == 0 || f == 4 || f == 5) w[r][f] = d.Wd[xfrag(NK_D, 4 * j + r, wave + 8 * f, lane)];
+#pragma unroll
+    for (int f = 0; f < 7; ++f) s_w[f * 64] = d.Wd[xfrag(NK_D, 4 * j + 3, wave + 8 * (f < 3 ? f + 1 : f + 3), lane)];   // registers hold the others
+    const int er = wave & 3, rt = 4 * j + er, unit = rt * 4 + (lane >> 4);
+    const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
+    const floatx4 bias4 = *reinterpret_cast<const floatx4*>(d.bd + unit * 4);
+    float c = d.c_dec[(size_t)col * HID + unit];
+    uint4 hd[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) hd[f] = reinterpret_cast<const uint4*>(d.xdec[cur])[xfrag(NK_D, 0, XD_HD / KB + wave + 8 * f, lane)];
+
+    int b = 0, b_before = 2, b_next = 1;
+    for (int s = 0; s < n_steps; ++s) {
+        const bool on = s < rem;
+        bool ok = true;
+        // ahead of the chain: the sums over h_dec of the step before and over h_att
+        if (s > 0) ok = x.take<4, 8>(O_HD + b_before * B_H, wave, lane, on, hd);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int f = 0; f < 4; ++f) acc = mfma_frag<h16_t>(r < 3 ? w[r][6 + f] : s_w[(3 + f) * 64], hd[f], acc);
+            red_hd[wave][r][lane] = acc;
+        }
+        uint4 ha[4];
+        ok = x.take<4, 8>(O_HA + b * B_H, wave, lane, on, ha) && ok;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int f = 0; f < 4; ++f) acc = mfma_frag<h16_t>(r < 3 || f == 0 ? w[r][f] : s_w[(f - 1) * 64], ha[f], acc);
+            red_ha[wave][r][lane] = acc;
+        }
+        ps.sync(ok);
+        floatx4 pre4 = red_hd[0][er][lane], pre4b = red_ha[0][er][lane];
+#pragma unroll
+        for (int k = 1; k < NW; ++k) pre4 += red_hd[k][er][lane];
+#pragma unroll
+        for (int k = 1; k < NW; ++k) pre4b += red_ha[k][er][lane];
+        if (ps.bad()) return give_up(d, s, rem);
+
+        if (wave < 4) x.empty_units(O_HD + b_next * B_H, rt >> 3, rt & 7, lane);
+        uint4 ab[2];
+        ok = x.take<2>(O_A + b * B_A, wave, lane, on, ab);
+        stores_done();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+            acc = mfma_frag<h16_t>(w[r][4], ab[0], acc);
+            acc = mfma_frag<h16_t>(w[r][5], ab[1], acc);
+            red_a[wave][r][lane] = acc;
+        }
+        ps.sync(ok);
+        floatx4 g4 = bias4;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) g4 += red_a[k][er][lane];
+        g4 += pre4;
+        g4 += pre4b;
+        float c_new = c, hf;
+        cell(g4, c_new, hf);
+        const h16_t h = from_float<h16_t>(hf);
+        if (ps.bad()) return give_up(d, s, rem);
+        // (waves 4 .. 7 form the same cells and store nothing)
+        x.put_units(O_HD + b * B_H, rt >> 3, rt & 7, lane, on && wave < 4, h);
+        if (on) c = c_new;
+        if (wave < 4 && s + 1 == min(rem, n_steps)) {
+            d.c_dec[(size_t)col * HID + unit] = c;
+            reinterpret_cast<h16_t*>(d.xdec[cur ^ ((s + 1) & 1)])[xoff<h16_t>(NK_D, col, XD_HD + unit)] = h;
+        }
+        b_before = b;
+        b = b_next;
+        b_next = next3(b);
+    }
+}
+
+// ---------------------------------------------------------------- one row tile of the projection
+__device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, int n_slots, int n_steps, int r, char* lds, Phases ps)
+{
+    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15;
+    float (*part)[NW][4][64] = reinterpret_cast<float (*)[NW][4][64]>(lds);    // [sixth of K][wave][element of the accumulator][lane]
+    uint4 w[6];
+#pragma unroll
+    for (int kp = 0; kp < 6; ++kp) w[kp] = reinterpret_cast<const uint4*>(d.Wmel)[((size_t)r * NK_P + kp * NW + wave) * 64 + lane];
+    const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
+    // thread = (element, lane) of the accumulators in the reduction
+    const int el = wave & 3, row = 16 * r + 4 * (lane >> 4) + el, m_off = (col * MEL_ROWS + row) * 4;
+    const float bias = d.bmel[min(row, N_PROJ - 1)];
+    auto product = [&](int kp, const uint4& b) __attribute__((always_inline)) {
+        const floatx4 p = mfma_frag<h16_t>(w[kp], b, floatx4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[kp][wave][i][lane] = p[i];
+    };
+    // a sixth's sum over the waves, rounded to 20 bits of mantissa as the step's kernels hand it over
+    auto sixth = [&](int kp) __attribute__((always_inline)) {
+        float v = kp == 0 ? bias : 0.f;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) v += part[kp][k][el][lane];
+        return __uint_as_float((__float_as_uint(v) + 8u) & ~15u);
+    };
+    int b = 0, b_next = 1;
+    for (int s = 0; s < n_steps; ++s) {
+        const bool on = s < rem;
+        uint4 ab[2], hd[4];
+        bool ok = x.take<2, 8>(O_A + b * B_A, wave, lane, on, ab);
+        if (wave < 4) x.empty(m_off, O_M + b_next * B_M);
+        product(4, ab[0]);
+        product(5, ab[1]);
+        ps.sync(ok);
+        const float v4 = sixth(4), v5 = sixth(5);
+        if (ps.bad()) return give_up(d, s, rem);
+        ok = x.take<4>(O_HD + b * B_H, wave, lane, on, hd);
+        stores_done();
+#pragma unroll
+        for (int kp = 0; kp < 4; ++kp) product(kp, hd[kp]);
+        ps.sync(ok);
+        float v = sixth(0);
+#pragma unroll
+        for (int kp = 1; kp < 4; ++kp) v += sixth(kp);
+        v += v4;
+        v += v5;
+        if (ps.bad()) return give_up(d, s, rem);
+        if (wave < 4 && on && row < N_PROJ) x.put(__float_as_uint(v), m_off, O_M + b * B_M);
+        b = b_next;
+        b_next = next3(b);
+    }
+}
+
+// ---------------------------------------------------------------- frame, prenet, books
+__device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int cur, int n_slots, int n_steps, char* lds, Phases ps)
+{
+    const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63, col = lane & 15, g = lane >> 4;
+    uint16_t (*s_mel)[MEL_LD] = reinterpret_cast<uint16_t (*)[MEL_LD]>(lds);
+    uint16_t (*s_hid)[HID_LD] = reinterpret_cast<uint16_t (*)[HID_LD]>(lds + 16 * MEL_LD * 2);
+    constexpr int NK3 = MEL_ROWS / KB, NK4 = PRENET / KB;
+    uint4 a3[2][NK3], a4[2][NK4];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int mt = wave + m * NW;
+#pragma unroll
+        for (int f = 0; f < NK3; ++f) a3[m][f] = reinterpret_cast<const uint4*>(d.Wp1)[((size_t)mt * NK3 + f) * 64 + lane];
+#pragma unroll
+        for (int f = 0; f < NK4; ++f) a4[m][f] = reinterpret_cast<const uint4*>(d.Wp2)[((size_t)mt * NK4 + f) * 64 + lane];
+    }
+    const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
+    // as a collector of the frame: thread = four rows of one slot
+    constexpr int VEC = MEL_ROWS / 4;
+    const int m_slot = min(tid / VEC, SEG_SLOTS - 1), m_row = tid % VEC * 4;
+    const int m_rem = tid < SEG_SLOTS * VEC && m_row < N_PROJ && m_slot < n_slots && d.live[m_slot] && !d.done[m_slot] ? d.n_steps[m_slot] - d.t[m_slot] : 0;
+    const int m_t0 = d.t[m_slot];
+    // the launches after this one read the half of this pair that belongs to their parity: it must not fall behind
+    const int end_all = cur ^ (n_steps & 1);
+    if (tid == 0 && end_all != cur) d.wg_seq[end_all] = d.wg_seq[cur];
+    int b = 0, b_next = 1;
+    for (int s = 0; s < n_steps; ++s) {
+        const bool on = s < rem, m_on = s < m_rem;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int mt = wave + m * NW;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) x.empty(p_off(mt, col, g) + 4 * i, O_P + b_next * B_P + (mt >> 1) * B_FRAG);
+        }
+        u32x4_t w = {0u, 0u, 0u, 0u};
+        bool in = !m_on;
+        for (int spin = 0; spin < x.polls && !in; ++spin) {
+            Words::again();
+            w = x.look4(tid * 16, O_M + b * B_M);
+            in = m_row == N_MEL ? w.x != EMPTY : Words::full(w);
+        }
+        stores_done();
+        if (m_row == N_MEL || !m_on) w.y = w.z = w.w = 0u;      // no rows beyond the stop row
+        if (tid < SEG_SLOTS * VEC)
+            *reinterpret_cast<uint2*>(&s_mel[m_slot][m_row]) = make_uint2(pack2<h16_t>(__uint_as_float(w.x), __uint_as_float(w.y)),
+                                                                          pack2<h16_t>(__uint_as_float(w.z), __uint_as_float(w.w)));
+        ps.sync(in);
+        {
+            uint4 bm[NK3];
+#pragma unroll
+            for (int f = 0; f < NK3; ++f) bm[f] = *reinterpret_cast<const uint4*>(&s_mel[col][f * KB + g * 8]);
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int f = 0; f < NK3; ++f) acc = mfma_frag<h16_t>(a3[m][f], bm[f], acc);
+                *reinterpret_cast<uint2*>(&s_hid[col][16 * (wave + m * NW) + 4 * g]) =
+                    make_uint2(pack2<h16_t>(fmaxf(acc[0], 0.f), fmaxf(acc[1], 0.f)), pack2<h16_t>(fmaxf(acc[2], 0.f), fmaxf(acc[3], 0.f)));
+            }
+        }
+        if (ps.bad()) return give_up(d, s, rem);
+        lds_barrier();
+        {
+            uint4 bh[NK4];
+#pragma unroll
+            for (int f = 0; f < NK4; ++f) bh[f] = *reinterpret_cast<const uint4*>(&s_hid[col][f * KB + g * 8]);
+            floatx4 acc[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int f = 0; f < NK4; ++f)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) acc[m] = mfma_frag<h16_t>(a4[m][f], bh[f], acc[m]);
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const int mt = wave + m * NW;
+                const unsigned lo = pack2<h16_t>(fmaxf(acc[m][0], 0.f), fmaxf(acc[m][1], 0.f)), hi = pack2<h16_t>(fmaxf(acc[m][2], 0.f), fmaxf(acc[m][3], 0.f));
+                if (s + 1 < min(rem, n_steps)) {
+                    x.put(lo, p_off(mt, col, g), O_P + b * B_P + (mt >> 1) * B_FRAG);
+                    x.put(hi, p_off(mt, col, g) + 4, O_P + b * B_P + (mt >> 1) * B_FRAG);
+                } else if (on) {
+                    h16_t* dst = reinterpret_cast<h16_t*>(d.xatt[cur ^ ((s + 1) & 1)]) + xoff<h16_t>(NK_A, col, XA_P + 16 * mt + 4 * g);
+                    *reinterpret_cast<uint2*>(dst) = make_uint2(lo, hi);
+                }
+            }
+        }
+        // the books, while the others go on
+        if (m_on) {
+            const size_t at = (size_t)m_slot * d.max_steps + m_t0 + s;
+            if (m_row < N_MEL) {
+                *reinterpret_cast<u32x4_t*>(d.mel_ring + at * N_MEL + m_row) = w;
+                *reinterpret_cast<u32x4_t*>(d.m_last + m_slot * N_MEL + m_row) = w;
+            } else {
+                d.stop_ring[at] = __uint_as_float(w.x);
+                d.t[m_slot] = m_t0 + s + 1;
+                if (s + 1 == m_rem) d.done[m_slot] = 1;
+            }
+        }
+        b = b_next;
+        b_next = next3(b);
+    }
+}
+
+// ---------------------------------------------------------------- a quarter of one request's attention
+__device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cur, int n_steps, int slot, int sp, char* lds, Phases ps)
+{
+    constexpr int S = 4, FS = ENC / S, LPR = 64 / S;
+    const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63, jl = lane & 15, g = lane >> 4;
+    float (*s_ctx)[ENC] = reinterpret_cast<float (*)[ENC]>(lds);
+    float (*s_u)[U_PAD] = reinterpret_cast<float (*)[U_PAD]>(lds + NW * ENC * 4);
+    float* s_e = reinterpret_cast<float*>(s_u + 2);
+    float* s_q = s_e + MAX_ENC_LEN;
+    float* s_v = s_q + ATT;
+    float* s_red = s_v + ATT;
+    float (*s_pair)[ATT] = reinterpret_cast<float (*)[ATT]>(s_red + 2 * NW);
+    if (!d.live[slot] || d.done[slot]) return;
+    const int rem = __builtin_amdgcn_readfirstlane(d.n_steps[slot] - d.t[slot]), L = __builtin_amdgcn_readfirstlane(d.L[slot]);
+    const int steps = min(rem, n_steps), ntile = (L + 15) >> 4;
+    const int my_rem = (int)threadIdx.x == slot ? rem : 0;                 // for give_up
+    const int ML = d.max_enc_len;
+    const bf16_t* PMs = reinterpret_cast<const bf16_t*>(d.PM) + (size_t)slot * ML * ATT + 32 * g;
+    LsaTile<h16_t> tile;
+    {
+        const uint4* kf = reinterpret_cast<const uint4*>(d.lsa_kfrag);
+        const uint4* wf = reinterpret_cast<const uint4*>(d.lsa_wfrag);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tile.kA[i >> 1][i & 1] = kf[i * 64 + lane];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) tile.wA[i] = wf[i * 64 + lane];
+    }
+    // the wave's first tile of positions is its only one up to 512 of them: its rows of the processed memory stay in registers
+    u32x4_t pm0[4];
+    {
+        const bf16_t* pm = PMs + (size_t)min((sp + S * wave) * 16 + jl, L - 1) * ATT;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pm0[i] = *reinterpret_cast<const u32x4_t*>(pm + 8 * i);
+    }
+    // and so do the rows of the memory (this workgroup's columns): 16 passes of 32 positions
+    constexpr int NP = 16;
+    const int xw = wave * 4 + lane / LPR;                                  // this lane's position class
+    const bf16_t* Fslot = reinterpret_cast<const bf16_t*>(d.Fmem) + (size_t)slot * ML * ENC;
+    const __amdgpu_buffer_rsrc_t f_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Fslot), 0, L * ENC * 2, BUFFER_RSRC_RAW);
+    const int f_col = (sp * FS + (lane % LPR) * 8) * 2;
+    u32x4_t rows[NP];
+#pragma unroll
+    for (int pp = 0; pp < NP; ++pp) rows[pp] = __builtin_amdgcn_raw_buffer_load_b128(f_rsrc, (pp * 32 + xw) * ENC * 2 + f_col, 0, 0);
+    for (int i = tid; i < ntile * 16 + 32; i += NT) {
+        const bool in = i >= LOC_PAD && i < L + LOC_PAD;
+        const int jc = min(max(i - LOC_PAD, 0), L - 1);
+        s_u[0][i] = in ? d.w_last[cur][(size_t)slot * ML + jc] : 0.f;
+        s_u[1][i] = in ? d.w_acc[cur][(size_t)slot * ML + jc] : 0.f;
+    }
+    if (tid < ATT) s_v[tid] = -2.0f * d.v[tid];
+    if (L + tid < ((L + 31) & ~31)) s_e[L + tid] = 0.f;                    // a pass of 32 positions may end past the last
+    __syncthreads();
+    float vsum = 0.f, bound = 0.f;
+#pragma unroll
+    for (int at = 0; at < 8; ++at) {
+        const float4 vv = *reinterpret_cast<const float4*>(&s_v[32 * g + 4 * at]);
+        vsum += (vv.x + vv.y) + (vv.z + vv.w);
+    }
+    vsum *= -0.5f;
+#pragma unroll
+    for (int at = 0; at < 8; ++at) {
+        const float4 vv = *reinterpret_cast<const float4*>(&s_v[32 * g + 4 * at]);
+        bound += (fabsf(vv.x) + fabsf(vv.y)) + (fabsf(vv.z) + fabsf(vv.w));
+    }
+    bound += __shfl_xor(bound, 16, 64);
+    bound += __shfl_xor(bound, 32, 64);
+    bound *= 0.5f;
+    const bool fast_softmax = bound <= 30.f;
+
+    // this thread's share of the query: four rows of two of its 32 partial products
+    const int q_off = (tid >> 5) * 2 * ATT * 4 + (tid & 31) * 16, b_e = SEG_SLOTS * ML * 4, e_at = O_E + slot * ML * 4;
+    const int k_a = sp * FS + tid, a_off = (slot * 4 + (k_a % KB) / 8) * 16 + (k_a % 8) * 2, a_frag = k_a / KB * B_FRAG;
+    int b = 0, b_next = 1;
+    for (int s = 0; s < steps; ++s) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) keep(pm0[i]);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) keep(rows[i]);
+        for (int tt = sp + S * wave; tt < ntile; tt += S * NW)
+            if (g == 0 && tt * 16 + jl < L) x.empty((tt * 16 + jl) * 4, e_at + b_next * b_e);
+        if (tid < FS && !(tid & 1)) x.empty(a_off, O_A + b_next * B_A + a_frag);
+        // the location features do not wait for the query
+        const uint4 bl0 = tile.loc(s_u[0], s_u[1], min((sp + S * wave) * 16, (ntile - 1) * 16) + jl, g);
+        {
+            u32x4_t w0, w1;
+            bool in = false;
+            for (int spin = 0; spin < x.polls && !in; ++spin) {
+                Words::again();
+                w0 = x.look4(q_off, O_Q + b * B_Q + slot * B_QS);
+                w1 = x.look4(q_off + ATT * 4, O_Q + b * B_Q + slot * B_QS);
+                in = Words::full(w0) && Words::full(w1);
+            }
+            stores_done();
+            floatx4 p;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[i] = __uint_as_float(w0[i]) + __uint_as_float(w1[i]);
+            *reinterpret_cast<floatx4*>(&s_pair[tid >> 5][(tid & 31) * 4]) = p;
+            ps.sync(in);
+        }
+        if (tid < ATT) {
+            float sq[4];
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                sq[h] = s_pair[4 * h][tid];
+#pragma unroll
+                for (int i = 1; i < 4; ++i) sq[h] += s_pair[4 * h + i][tid];
+            }
+            s_q[tid] = (sq[0] + sq[1]) + (sq[2] + sq[3]);
+        }
+        if (ps.bad()) return give_up(d, s, my_rem);
+        lds_barrier();
+        for (int tt = sp + S * wave; tt < ntile; tt += S * NW) {
+            const int j = tt * 16 + jl;
+            const bool first = tt < S * NW;
+            uint4 pmc[4];
+            if (first) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) pmc[i] = as_uint4(pm0[i]);
+            } else {
+                const bf16_t* pm = PMs + (size_t)min(j, L - 1) * ATT;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) pmc[i] = *reinterpret_cast<const uint4*>(pm + 8 * i);
+            }
+            const uint4 bl = first ? bl0 : tile.loc(s_u[0], s_u[1], j, g);
+            float e = vsum;
+#pragma unroll
+            for (int at = 0; at < 8; ++at) {
+                const floatx4 pl = mfma_frag<h16_t>(tile.wA[at], bl, *reinterpret_cast<const floatx4*>(&s_q[32 * g + 4 * at]));
+                const float4 vv = *reinterpret_cast<const float4*>(&s_v[32 * g + 4 * at]);
+                const uint4& u = pmc[at >> 1];
+                const uint32_t w0 = (at & 1) ? u.z : u.x, w1 = (at & 1) ? u.w : u.y;
+                e = fmaf(vv.x, half_one_minus_tanh(pl[0] + bf16_lo(w0)), e);
+                e = fmaf(vv.y, half_one_minus_tanh(pl[1] + bf16_hi(w0)), e);
+                e = fmaf(vv.z, half_one_minus_tanh(pl[2] + bf16_lo(w1)), e);
+                e = fmaf(vv.w, half_one_minus_tanh(pl[3] + bf16_hi(w1)), e);
+            }
+            e += xor16(e);
+            e += xor32(e);
+            if (fast_softmax) e = __expf(e - bound);
+            if (g == 0 && j < L) {
+                s_e[j] = e;
+                x.put(__float_as_uint(e), j * 4, e_at + b * b_e);
+            }
+        }
+        bool ok = true;
+        for (int i = tid; i < L; i += NT) {
+            if ((i >> 4) % S == sp) continue;
+            unsigned w = 0u;
+            bool in = false;
+            for (int spin = 0; spin < x.polls && !in; ++spin) {
+                Words::again();
+                w = x.look(i * 4, e_at + b * b_e);
+                in = w != EMPTY;
+            }
+            ok = ok && in;
+            s_e[i] = __uint_as_float(w);
+        }
+        stores_done();
+        ps.sync(ok);
+        float psum = 0.f;
+        for (int tt = wave; tt < ntile; tt += NW) {
+            const int j = tt * 16 + jl;
+            if (g == 0 && j < L) psum += s_e[j];
+        }
+        psum = wave_sum_fast(psum);
+        if (lane == 0) s_red[NW + wave] = psum;                            // read behind the barrier of the context's sums
+        if (ps.bad()) return give_up(d, s, my_rem);
+        if (!fast_softmax) {
+            float mx = -INFINITY;
+            for (int i = tid; i < L; i += NT) mx = fmaxf(mx, s_e[i]);
+            mx = wave_max(mx);
+            if (lane == 0) s_red[wave] = mx;
+            lds_barrier();
+            mx = s_red[0];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) mx = fmaxf(mx, s_red[w]);
+            float sum = 0.f;
+            for (int i = tid; i < L; i += NT) {
+                const float p = __expf(s_e[i] - mx);
+                s_e[i] = p;
+                sum += p;
+            }
+            sum = wave_sum(sum);
+            if (lane == 0) s_red[NW + wave] = sum;
+            lds_barrier();
+        }
+
+        float acc[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+        auto add = [&](int px, const uint4& r) __attribute__((always_inline)) {
+            const float w = s_e[px];
+            float fv[8];
+            Vec16<bf16_t>::unpack(r, fv);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] = fmaf(w, fv[i], acc[i]);
+        };
+#pragma unroll
+        for (int pp = 0; pp < NP; ++pp) {
+            if (pp * 32 >= L) break;
+            add(pp * 32 + xw, as_uint4(rows[pp]));
+        }
+        for (int x0 = 32 * NP; x0 < L; x0 += 32 * 4) {                     // texts of more than 512 positions: from memory
+            uint4 more[4];
+#pragma unroll
+            for (int pp = 0; pp < 4; ++pp) more[pp] = buffer_load16(f_rsrc, (x0 + pp * 32 + xw) * ENC * 2 + f_col);
+#pragma unroll
+            for (int pp = 0; pp < 4; ++pp)
+                if (x0 + pp * 32 < L) add(x0 + pp * 32 + xw, more[pp]);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s_ctx[wave][lane * 8 + i] = acc[i];
+        lds_barrier();
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sum += s_red[NW + w];
+        const float inv = 1.0f / sum;
+        if (tid < FS) {
+            float c = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+                c += (s_ctx[w][tid] + s_ctx[w][LPR * 8 + tid]) + (s_ctx[w][2 * LPR * 8 + tid] + s_ctx[w][3 * LPR * 8 + tid]);
+            const h16_t a = from_float<h16_t>(c * inv);
+            const unsigned lo = a.bits, hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)lo, 0xB1, 0xf, 0xf, false);      // the neighbour's (lanes 1, 0, 3, 2)
+            if (!(tid & 1)) x.put(lo | hi << 16, a_off, O_A + b * B_A + a_frag);
+            if (s + 1 == steps) {
+                const int end = cur ^ (steps & 1);
+                reinterpret_cast<h16_t*>(d.xatt[end])[xoff<h16_t>(NK_A, slot, XA_A + k_a)] = a;
+                reinterpret_cast<h16_t*>(d.xdec[end ^ 1])[xoff<h16_t>(NK_D, slot, XD_A + k_a)] = a;
+            }
+        }
+        // the new weights: every workgroup of the request keeps all of them
+        for (int i = tid; i < L; i += NT) {
+            const float w = s_e[i] * inv;
+            s_u[0][i + LOC_PAD] = w;
+            s_u[1][i + LOC_PAD] += w;
+        }
+        lds_barrier();
+        b = b_next;
+        b_next = next3(b);
+    }
+    const int end = cur ^ (steps & 1);
+    for (int i = sp + S * tid; i < L; i += S * NT) {
+        d.w_last[end][(size_t)slot * ML + i] = s_u[0][i + LOC_PAD];
+        d.w_acc[end][(size_t)slot * ML + i] = s_u[1][i + LOC_PAD];
+    }
+}
+
+__global__ __launch_bounds__(NT) void k_segment(DevPtrs d, int cur, int n_slots, int n_steps, char* words, char* words_next, int set_bytes)
+{
+    __shared__ __attribute__((aligned(16))) char lds[S_MAX];
+    __shared__ int s_failed;
+    if (threadIdx.x == 0) s_failed = 0x7fffffff;
+    for (int at = (blockIdx.x * NT + threadIdx.x) * 16; at < set_bytes; at += gridDim.x * NT * 16)
+        *reinterpret_cast<u32x4_t*>(words_next + at) = u32x4_t{EMPTY, EMPTY, EMPTY, EMPTY};
+    __syncthreads();
+    const Phases ps = {&s_failed};
+    const Words x = {words, set_bytes, d.wait_polls};
+    const int xcd = blockIdx.x & 7, i = blockIdx.x >> 3;
+    if (i >= 16) {
+        const int slot = ((i - 16) >> 2) * 8 + xcd;
+        if (slot < n_slots) seg_lsa(d, x, cur, n_steps, slot, (i - 16) & 3, lds, ps);
+    } else if (i >= 8) {
+        seg_dec(d, x, cur, n_slots, n_steps, (i - 8) * 8 + xcd, lds, ps);
+    } else if (xcd < 4) {
+        seg_att(d, x, cur, n_slots, n_steps, i * 4 + xcd, lds, ps);
+    } else if (xcd == 4) {
+        if (i < 6) seg_rows(d, x, n_slots, n_steps, i, lds, ps);
+        else if (i == 6) seg_lead(d, x, cur, n_slots, n_steps, lds, ps);
+    }
+}
+
+}  // namespace
+
+hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, hipStream_t s)
+{
+    if (!d.seg_x || n_slots < 1 || n_slots > SEG_SLOTS || n_steps < 1 || (set & ~1) || d.stop_threshold >= 0.f) return hipErrorInvalidValue;
+    const size_t bytes = segment_set_bytes(d.max_enc_len);
+    char* words = static_cast<char*>(d.seg_x);
+    hipLaunchKernelGGL(k_segment, dim3(8 * (16 + 4 * ((n_slots + 7) / 8))), dim3(NT), 0, s, d, cur, n_slots, n_steps, words + set * bytes, words + (set ^ 1) * bytes, (int)bytes);
+    return hipGetLastError();
+}
+
+}  // namespace tts

@@ -71,8 +71,8 @@ namespace {
 struct Layout {
     size_t Wa, Wd, ba, bd, Wq, Wq_epi, qpart, pre_att, pre_dec, pre_dec_b, proj_part, WmemT, lsa_kfrag, lsa_wfrag, v, Wmel, bmel, Wp1, Wp2;
     size_t xatt[2], xdec[2], c_att, c_dec, m_last, w_last[2], w_acc[2], Fmem, PM, mel_ring, stop_ring;
-    size_t L, t, n_steps, done, failed, live, proj_seq, step_seq, lsa_x, hdec_x, p_x, pre_x, wg_seq, stage;
-    size_t total, proj_part_bytes;
+    size_t L, t, n_steps, done, failed, live, proj_seq, step_seq, lsa_x, hdec_x, p_x, pre_x, wg_seq, seg_x, stage;
+    size_t total, proj_part_bytes, seg_bytes;
 };
 
 // Gate pre-sums: the projection kernel needs a handful of CUs, so its launch also contracts what the next step's LSTMs
@@ -158,6 +158,8 @@ Layout make_layout(const tts_config& c)
     l.p_x = a.take((pre_dec_hatt_for(c) ? S / 16 : 0) * (size_t)(PRENET / 32) * 64 * 4 * 8);
     l.pre_x = a.take((pre_dec_hatt_for(c) ? S / 16 : 0) * (size_t)(HID / 4) * 64 * 4 * 8);
     l.wg_seq = a.take(2 * 4);
+    l.seg_x = a.take(pre_dec_hatt_for(c) ? 2 * segment_set_bytes(c.max_enc_len) : 0);
+    l.seg_bytes = a.off - l.seg_x;
     l.stage = a.take(ML * ENC * 4);
     l.total = a.off;
     return l;
@@ -260,6 +262,7 @@ struct tts_pool {
     int stage_regions = 0, stage_frames = 0;
     struct Staged { int64_t id = -1; int first = 0, count = 0; };
     std::vector<Staged> staged;   // per region: which frames of which request it holds (frames never change once made)
+    int seg_set = 0;              // which set of words the next segment's launch uses
     int n_slots_padded = 0;       // slots the arena holds (max_pool rounded up to whole tiles)
     std::vector<int64_t> lost_ids; // requests the device ended early that tts_pool_sync has not reported yet
 };
@@ -417,6 +420,7 @@ extern "C" int tts_pool_create(const tts_config* cfg, const tts_weights* w, void
     d.p_x = pre_dec_hatt_for(*cfg) ? reinterpret_cast<unsigned long long*>(base + l.p_x) : nullptr;
     d.pre_x = pre_dec_hatt_for(*cfg) ? reinterpret_cast<unsigned long long*>(base + l.pre_x) : nullptr;
     d.wg_seq = reinterpret_cast<unsigned*>(base + l.wg_seq);
+    d.seg_x = pre_dec_hatt_for(*cfg) ? base + l.seg_x : nullptr;
     // one pinned word the kernels can reach: a projection leader that gives up on its helpers says so here
     {
         hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&p->h_fault), sizeof(int), hipHostMallocMapped);
@@ -489,6 +493,7 @@ extern "C" int tts_pool_create(const tts_config* cfg, const tts_weights* w, void
         hipError_t e = hipMemset(base + l.L, 0, l.stage - l.L);
         // no word of the projection's hand-over buffer may carry a sequence number a leader could wait for
         if (e == hipSuccess && d.proj_part) e = hipMemset(base + l.proj_part, 0, l.proj_part_bytes);
+        if (e == hipSuccess && d.seg_x) e = hipMemset(base + l.seg_x, 0xff, l.seg_bytes);     // every word empty
         if (e == hipSuccess) e = hipEventCreate(&p->ev0);
         if (e == hipSuccess) e = hipEventCreate(&p->ev1);
         if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -651,6 +656,8 @@ static void shape_for(const tts_pool* p, int span, StepLaunch* sl)
     sl->proj_group = proj_group_for(p->cfg);
     sl->att_lead = 1;
     sl->att_tail = 0;
+    sl->seg_steps = 0;
+    sl->seg_set = 0;
 }
 
 // Step i of `nsteps` consecutive steps of one call: in pools whose last launch can form the next step's attention LSTM
@@ -713,6 +720,33 @@ static int launch_steps(tts_pool* p, int n_active, int nsteps)
     return TTS_OK;
 }
 
+// How many of the next `n` steps run as one launch (segment.hip; 0: they run step by step).  The line is the form's own: one tile
+// of slots, two-byte weights and memory (d.seg_x), frame counts known beforehand.  There it is the faster one at every size, chunks
+// of 40 steps of requests of 165 positions, steps as launches in graphs -> as one launch: 1 request 16.8 -> 10.6 us a step,
+// 4: 17.9 -> 11.8, 8: 18.2 -> 13.7, 12: 18.4 -> 15.9, 16: 18.5 -> 17.4; single steps, back to back: 1 request 28.4 -> 18.5,
+// 16: 28.7 -> 26.4.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other
+// streams gets the compute units at intervals.
+static const int MAX_SEGMENT_STEPS = 64;
+static int segment_steps(const tts_pool* p, int n)
+{
+    if (!p->d.seg_x || !p->cfg.use_graph || p->stop_enabled || p->slot_span > SEG_SLOTS) return 0;
+    int most = 0;
+    for (int sl : p->book->active()) most = std::max(most, p->book->slot(sl).n_steps - p->book->slot(sl).t);
+    return std::min({n, most, MAX_SEGMENT_STEPS});
+}
+static int launch_segment_steps(tts_pool* p, int g)
+{
+    StepLaunch sl;
+    sl.wdtype = p->cfg.weight_dtype;
+    sl.mdtype = p->cfg.memory_dtype;
+    shape_for(p, p->slot_span, &sl);
+    sl.seg_steps = g;
+    sl.seg_set = p->seg_set;
+    HIP_TRY(launch_step(p->d, sl, p->parity, p->stream));
+    p->seg_set ^= 1;
+    return TTS_OK;
+}
+
 static int step_impl(tts_pool* p, int n, int64_t* out_frames, int* out_last_active)
 {
     int64_t frames = 0;
@@ -728,12 +762,15 @@ static int step_impl(tts_pool* p, int n, int64_t* out_frames, int* out_last_acti
         // graphs exist for powers of two up to MAX_GRAPH_STEPS and for one whole chunk (the paper's iteration: a
         // segment of 40 steps as one graph measured 0.05 - 0.2 us per step faster than as graphs of 32 and 8)
         int g = 1;
-        if (p->cfg.use_graph) {
+        const int seg = segment_steps(p, n - i);
+        if (seg > 0) {
+            g = seg;
+        } else if (p->cfg.use_graph) {
             while (g * 2 <= n - i && g * 2 <= MAX_GRAPH_STEPS) g *= 2;
             const int chunk = p->cfg.chunk_frames;
             if (chunk > g && chunk <= n - i && chunk <= MAX_CHUNK_GRAPH_STEPS) g = chunk;
         }
-        rc = launch_steps(p, n_active, g);
+        rc = seg > 0 ? launch_segment_steps(p, g) : launch_steps(p, n_active, g);
         if (rc) return rc;
         for (int k = 0; k < g; ++k) {
             p->parity ^= 1;
