@@ -41,7 +41,8 @@ constexpr int PROJ_GROUP = 6;       // the largest group
 // d.seg_x: two sets, each three buffers of the words a segment's workgroups hand each other: h_att and h_dec (32 fragments of 1 KB),
 // a (16), p (8), the query's partial products, the frame's rows and, per position of the longest text, the energies
 constexpr size_t SEG_FIXED_BYTES = 3 * ((size_t)(32 + 32 + 16 + 8) * 1024 + (size_t)SEG_SLOTS * QUERY_PARTIALS * ATT * 4 + 96 * SEG_SLOTS * 4);
-constexpr size_t segment_set_bytes(int max_enc_len) { return SEG_FIXED_BYTES + (size_t)3 * SEG_SLOTS * max_enc_len * 4; }
+constexpr int segment_energy_bytes(int max_enc_len) { return (max_enc_len + 63) / 64 * 256; }      // per slot: a quarter for each of its workgroups
+constexpr size_t segment_set_bytes(int max_enc_len) { return SEG_FIXED_BYTES + (size_t)3 * SEG_SLOTS * segment_energy_bytes(max_enc_len); }
 
 // One decoder step (paper Eq. 2) for every request whose slot is flagged in d.live.
 // `cur` selects which half of the double-buffered activations is read.

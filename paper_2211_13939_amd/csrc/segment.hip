@@ -43,7 +43,10 @@ constexpr int F_H = HID / KB, F_A = ENC / KB, F_P = PRENET / KB;            // f
 static_assert(F_H == 4 * NW && F_A == 2 * NW && F_P == NW, "a wave takes four fragments of h, two of a, one of p");
 constexpr int MEL_ROWS = 96;
 
-// one buffer of each kind, in bytes; a fragment is [16 slots][4 groups][8 halves of k], so that one request's share is contiguous
+// One buffer of each kind, in bytes.  What one workgroup (for q and p: one wave) stores lies together, a request's share of it in whole
+// 32 to 512 bytes: polls are L2 hits (0.12 us a round of 8 KB) until somebody stores to the line, which the XCD then takes from memory
+// anew, so a line that fills in many small steps is fetched many times.  With words of several workgroups in a line (all in B-operand
+// order, stored as they were made, 4 bytes a lane) a step took 10.6 us at 1 request, 13.7 at 8 and 17.4 at 16; like this 9.7, 10.7, 12.1.
 constexpr int B_FRAG = 1024, B_H = F_H * B_FRAG, B_A = F_A * B_FRAG, B_P = F_P * B_FRAG;
 constexpr int B_QS = QUERY_PARTIALS * ATT * 4, B_Q = SEG_SLOTS * B_QS, B_M = SEG_SLOTS * MEL_ROWS * 4;
 constexpr int O_HA = 0, O_HD = O_HA + 3 * B_H, O_A = O_HD + 3 * B_H, O_P = O_A + 3 * B_A, O_Q = O_P + 3 * B_P, O_M = O_Q + 3 * B_Q, O_E = O_M + 3 * B_M;
@@ -71,6 +74,11 @@ struct Words {
     {
         __builtin_amdgcn_raw_buffer_store_b32(v < EMPTY ? v : EMPTY - 1u, rs(), lane_off, off, AGENT);
     }
+    __device__ __forceinline__ void put2(unsigned a, unsigned b, int lane_off, int off) const
+    {
+        typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{a < EMPTY ? a : EMPTY - 1u, b < EMPTY ? b : EMPTY - 1u}, rs(), lane_off, off, AGENT);
+    }
     __device__ __forceinline__ void put4(const floatx4& v, int lane_off, int off) const
     {
         u32x4_t u;
@@ -85,13 +93,12 @@ struct Words {
     }
     __device__ __forceinline__ static bool full(const u32x4_t& v) { return max(max(v.x, v.y), max(v.z, v.w)) != EMPTY; }
 
-    // fragments first, first + 8, ... of a B operand (lane = column + 16 * group); zeros where the lane's column takes no part.
-    // False: the wait ran out.
+    // Fragments first, first + 8, ... of a B operand (lane = column + 16 * group), STRIDE bytes apart from one to the next, at the
+    // lane's offset in a fragment; zeros where the lane's column takes no part.  False: the wait ran out.
     // NAP: pause between polls, in units of 64 cycles (waits that are off the chain)
-    template <int N, int NAP = 0>
-    __device__ __forceinline__ bool take(int buf, int first, int lane, bool on, uint4 (&out)[N]) const
+    template <int N, int STRIDE, int NAP = 0>
+    __device__ __forceinline__ bool take(int buf, int first, int lane_off, bool on, uint4 (&out)[N]) const
     {
-        const int lane_off = ((lane & 15) * 4 + (lane >> 4)) * 16;
         u32x4_t w[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) w[n] = u32x4_t{0u, 0u, 0u, 0u};
@@ -99,7 +106,7 @@ struct Words {
         for (int spin = 0; spin < polls && !in; ++spin) {
             again();
 #pragma unroll
-            for (int n = 0; n < N; ++n) w[n] = look4(lane_off, buf + (first + 8 * n) * B_FRAG);
+            for (int n = 0; n < N; ++n) w[n] = look4(lane_off, buf + (first + 8 * n) * STRIDE);
             in = true;
 #pragma unroll
             for (int n = 0; n < N; ++n) in = in && full(w[n]);
@@ -111,20 +118,12 @@ struct Words {
         for (int n = 0; n < N; ++n) out[n] = make_uint4(w[n].x, w[n].y, w[n].z, w[n].w);
         return in;
     }
-
-    // four units of a row tile (lane = column + 16 * unit): row tile q8 of the eight that make up fragment `frag`
-    __device__ __forceinline__ void put_units(int buf, int frag, int q8, int lane, bool on, h16_t h) const
-    {
-        // units 0, 1 and 2, 3 of a column in one word: the lanes of odd units hand theirs to the lanes before them
-        const auto sw = __builtin_amdgcn_permlane16_swap((unsigned)h.bits, (unsigned)h.bits, false, false);
-        if (on && !(lane & 16)) put(sw[0] | sw[1] << 16, unit_off(q8, lane), buf + frag * B_FRAG);
-    }
-    __device__ __forceinline__ static int unit_off(int q8, int lane) { return ((lane & 15) * 4 + (q8 >> 1)) * 16 + (q8 & 1) * 8 + (lane >> 5) * 4; }
-    __device__ __forceinline__ void empty_units(int buf, int frag, int q8, int lane) const
-    {
-        if (!(lane & 16)) empty(unit_off(q8, lane), buf + frag * B_FRAG);
-    }
 };
+// a lane's offset in a fragment: of h_att and p ([fragment][slot][32 halves]), of h_dec ([half a fragment][slot][16 halves]: one of the
+// decoder LSTM's workgroups stores half a fragment) and of a ([slot][512 halves])
+__device__ __forceinline__ int off_hp(int col, int g) { return col * 64 + g * 16; }
+__device__ __forceinline__ int off_hd(int col, int g) { return ((g >> 1) * SEG_SLOTS + col) * 32 + (g & 1) * 16; }
+__device__ __forceinline__ int off_a(int col, int g) { return col * (ENC * 2) + g * 16; }
 
 // x of the lane 16 or 32 away, and of the lanes of a row of 16 at a distance: the sums below add the same pairs as the
 // step's kernels do with shuffles, without a trip through LDS each
@@ -192,14 +191,13 @@ struct Phases {
 
 __device__ __forceinline__ int next3(int b) { return b == 2 ? 0 : b + 1; }
 
-// rows 16 mt + 4 g .. + 3 of p: fragment mt / 2, group (mt % 2) * 2 + g / 2, half a group
-__device__ __forceinline__ int p_off(int mt, int col, int g) { return (col * 4 + (mt & 1) * 2 + (g >> 1)) * 16 + (g & 1) * 8; }
 constexpr int ATT_LDS_RT = 2;                               // row tiles whose late fragments lie in LDS: registers hold six
 constexpr int ATT_LATE = 6;                                 // late fragments per wave and row tile: two of a, four of h_att
 constexpr int S_ATT_W = ATT_LDS_RT * ATT_LATE * NW * 1024, S_ATT_RED = NW * 4 * 1024, S_ATT_B = F_P * 1024;
-constexpr int S_ATT = S_ATT_W + S_ATT_RED + S_ATT_B + 32 * 16 * 4;
+constexpr int S_ATT = S_ATT_W + S_ATT_RED + S_ATT_B + 32 * 16 * 4 + 16 * 32 * 2;
 constexpr int S_DEC = 3 * NW * 4 * 1024 + NW * 7 * 1024;
-constexpr int S_ROWS = 6 * NW * 1024;
+constexpr int P_LD = 68;                                    // the reduction reads 4 columns x 16 rows a wave: a bank each
+constexpr int S_ROWS = 6 * NW * 4 * P_LD * 4;
 constexpr int MEL_LD = MEL_ROWS + 8, HID_LD = PRENET + 8;     // halves: an odd number of 16-byte pieces a row
 constexpr int S_LEAD = 16 * (MEL_LD + HID_LD) * 2;
 constexpr int U_PAD = MAX_ENC_LEN + 48;
@@ -216,6 +214,7 @@ __device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& x, int cu
     floatx4 (*red)[4][64] = reinterpret_cast<floatx4 (*)[4][64]>(lds + S_ATT_W);
     uint4 (*s_b)[64] = reinterpret_cast<uint4 (*)[64]>(lds + S_ATT_W + S_ATT_RED);
     float (*s_h)[16] = reinterpret_cast<float (*)[16]>(lds + S_ATT_W + S_ATT_RED + S_ATT_B);
+    h16_t (*s_hh)[32] = reinterpret_cast<h16_t (*)[32]>(s_h + 32);                          // [slot][unit]
 
     uint4 we[F_P], wl[8 - ATT_LDS_RT][ATT_LATE];
 #pragma unroll
@@ -244,7 +243,7 @@ __device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& x, int cu
     for (int s = 0; s < n_steps; ++s) {
         const bool on = s < rem;
         bool ok = true;
-        if (s > 0) ok = x.take<1>(O_P + b_before * B_P, wave, lane, on, pb);
+        if (s > 0) ok = x.take<1, B_FRAG>(O_P + b_before * B_P, wave, off_hp(col, g), on, pb);
         stores_done();
         s_b[wave][lane] = pb[0];
         ps.sync(ok);
@@ -257,8 +256,8 @@ __device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& x, int cu
         cell(g4, c_new, hf);
         const h16_t h = from_float<h16_t>(hf);
         s_h[4 * wave + g][col] = on ? to_float(h) : 0.f;
+        s_hh[col][4 * wave + g] = h;
         if (ps.bad()) return give_up(d, s, rem);
-        x.put_units(O_HA + b * B_H, rg, wave, lane, on, h);
         lds_barrier();
         // the units' share of the query: 16 rows per wave
         {
@@ -266,6 +265,7 @@ __device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& x, int cu
 #pragma unroll
             for (int k = 0; k < 8; ++k) part = __builtin_amdgcn_mfma_f32_16x16x4f32(wq[k], s_h[4 * k + g][col], part, 0, 0, 0);
             if (on) x.put4(part, q_off, O_Q + b * B_Q + rg * ATT * 4);
+            if (wave == 0 && on) x.put4(*reinterpret_cast<const floatx4*>(&s_hh[col][8 * g]), off_hp(col, g), O_HA + b * B_H + rg * B_FRAG);
         }
         if (on) c = c_new;
         if (s + 1 == min(rem, n_steps)) {
@@ -279,10 +279,10 @@ __device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& x, int cu
         // off the chain: the next step's gate pre-sums over [a; h_att]
         uint4 hb[4], ab[2];
         // (a first: it comes last, so that the larger h_att is asked for once)
-        ok = x.take<2, 16>(O_A + b * B_A, wave, lane, on, ab);
-        ok = x.take<4, 16>(O_HA + b * B_H, wave, lane, on, hb) && ok;
+        ok = x.take<2, 64, 16>(O_A + b * B_A, wave, off_a(col, g), on, ab);
+        ok = x.take<4, B_FRAG, 16>(O_HA + b * B_H, wave, off_hp(col, g), on, hb) && ok;
         // (step s - 1's words, whose buffer is step s + 2's: taken before this step's a was made)
-        x.empty_units(O_HA + b_before * B_H, rg, wave, lane);
+        if (wave == 0 && on) x.empty4(off_hp(col, g), O_HA + b_before * B_H + rg * B_FRAG);
         if (on) x.empty4(q_off, O_Q + b_before * B_Q + rg * ATT * 4);
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -318,7 +318,7 @@ __device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& x, int cu
 // ---------------------------------------------------------------- the decoder LSTM
 __device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cur, int n_slots, int n_steps, int j, char* lds, Phases ps)
 {
-    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15;
+    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     floatx4 (*red_a)[4][64] = reinterpret_cast<floatx4 (*)[4][64]>(lds);
     floatx4 (*red_hd)[4][64] = red_a + NW;
     floatx4 (*red_ha)[4][64] = red_hd + NW;
@@ -331,7 +331,7 @@ __device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cu
             if (r < 3 || f == 0 || f == 4 || f == 5) w[r][f] = d.Wd[xfrag(NK_D, 4 * j + r, wave + 8 * f, lane)];
 #pragma unroll
     for (int f = 0; f < 7; ++f) s_w[f * 64] = d.Wd[xfrag(NK_D, 4 * j + 3, wave + 8 * (f < 3 ? f + 1 : f + 3), lane)];   // registers hold the others
-    const int er = wave & 3, rt = 4 * j + er, unit = rt * 4 + (lane >> 4);
+    const int er = wave & 3, rt = 4 * j + er, unit = rt * 4 + g, hd_off = col * 32 + er * 8 + (g >> 1) * 4;
     const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
     const floatx4 bias4 = *reinterpret_cast<const floatx4*>(d.bd + unit * 4);
     float c = d.c_dec[(size_t)col * HID + unit];
@@ -344,7 +344,7 @@ __device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cu
         const bool on = s < rem;
         bool ok = true;
         // ahead of the chain: the sums over h_dec of the step before and over h_att
-        if (s > 0) ok = x.take<4, 8>(O_HD + b_before * B_H, wave, lane, on, hd);
+        if (s > 0) ok = x.take<4, B_FRAG, 8>(O_HD + b_before * B_H, wave, off_hd(col, g), on, hd);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             floatx4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -353,7 +353,7 @@ __device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cu
             red_hd[wave][r][lane] = acc;
         }
         uint4 ha[4];
-        ok = x.take<4, 8>(O_HA + b * B_H, wave, lane, on, ha) && ok;
+        ok = x.take<4, B_FRAG, 8>(O_HA + b * B_H, wave, off_hp(col, g), on, ha) && ok;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             floatx4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -369,9 +369,9 @@ __device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cu
         for (int k = 1; k < NW; ++k) pre4b += red_ha[k][er][lane];
         if (ps.bad()) return give_up(d, s, rem);
 
-        if (wave < 4) x.empty_units(O_HD + b_next * B_H, rt >> 3, rt & 7, lane);
+        if (wave < 4 && on && !(g & 1)) x.empty(hd_off, O_HD + b_next * B_H + j * (B_FRAG / 2));
         uint4 ab[2];
-        ok = x.take<2>(O_A + b * B_A, wave, lane, on, ab);
+        ok = x.take<2, 64>(O_A + b * B_A, wave, off_a(col, g), on, ab);
         stores_done();
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -391,7 +391,11 @@ __device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cu
         const h16_t h = from_float<h16_t>(hf);
         if (ps.bad()) return give_up(d, s, rem);
         // (waves 4 .. 7 form the same cells and store nothing)
-        x.put_units(O_HD + b * B_H, rt >> 3, rt & 7, lane, on && wave < 4, h);
+        {
+            // units 0, 1 and 2, 3 of a column in one word: the lanes of odd units hand theirs to the lanes before them
+            const auto sw = __builtin_amdgcn_permlane16_swap((unsigned)h.bits, (unsigned)h.bits, false, false);
+            if (wave < 4 && on && !(g & 1)) x.put(sw[0] | sw[1] << 16, hd_off, O_HD + b * B_H + j * (B_FRAG / 2));
+        }
         if (on) c = c_new;
         if (wave < 4 && s + 1 == min(rem, n_steps)) {
             d.c_dec[(size_t)col * HID + unit] = c;
@@ -406,14 +410,16 @@ __device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cu
 // ---------------------------------------------------------------- one row tile of the projection
 __device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, int n_slots, int n_steps, int r, char* lds, Phases ps)
 {
-    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15;
-    float (*part)[NW][4][64] = reinterpret_cast<float (*)[NW][4][64]>(lds);    // [sixth of K][wave][element of the accumulator][lane]
+    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    float (*part)[NW][4][P_LD] = reinterpret_cast<float (*)[NW][4][P_LD]>(lds);  // [sixth of K][wave][element of the accumulator][lane]
     uint4 w[6];
 #pragma unroll
     for (int kp = 0; kp < 6; ++kp) w[kp] = reinterpret_cast<const uint4*>(d.Wmel)[((size_t)r * NK_P + kp * NW + wave) * 64 + lane];
     const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
-    // thread = (element, lane) of the accumulators in the reduction
-    const int el = wave & 3, row = 16 * r + 4 * (lane >> 4) + el, m_off = (col * MEL_ROWS + row) * 4;
+    // in the reduction: wave = four columns, thread = one of them and one of 16 rows
+    const int my_col = (4 * wave + g) & 15, row16 = lane & 15, row = 16 * r + row16;
+    const int el = row16 & 3, at = my_col + 16 * (row16 >> 2), m_off = (my_col * 16 + row16) * 4, m_buf = O_M + r * (SEG_SLOTS * 64);
+    const int my_rem = wave < 4 && row < N_PROJ && my_col < n_slots && d.live[my_col] && !d.done[my_col] ? d.n_steps[my_col] - d.t[my_col] : 0;
     const float bias = d.bmel[min(row, N_PROJ - 1)];
     auto product = [&](int kp, const uint4& b) __attribute__((always_inline)) {
         const floatx4 p = mfma_frag<h16_t>(w[kp], b, floatx4{0.f, 0.f, 0.f, 0.f});
@@ -424,21 +430,21 @@ __device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, int n
     auto sixth = [&](int kp) __attribute__((always_inline)) {
         float v = kp == 0 ? bias : 0.f;
 #pragma unroll
-        for (int k = 0; k < NW; ++k) v += part[kp][k][el][lane];
+        for (int k = 0; k < NW; ++k) v += part[kp][k][el][at];
         return __uint_as_float((__float_as_uint(v) + 8u) & ~15u);
     };
     int b = 0, b_next = 1;
     for (int s = 0; s < n_steps; ++s) {
         const bool on = s < rem;
         uint4 ab[2], hd[4];
-        bool ok = x.take<2, 8>(O_A + b * B_A, wave, lane, on, ab);
-        if (wave < 4) x.empty(m_off, O_M + b_next * B_M);
+        bool ok = x.take<2, 64, 8>(O_A + b * B_A, wave, off_a(col, g), on, ab);
+        if (s < my_rem) x.empty(m_off, m_buf + b_next * B_M);
         product(4, ab[0]);
         product(5, ab[1]);
         ps.sync(ok);
         const float v4 = sixth(4), v5 = sixth(5);
         if (ps.bad()) return give_up(d, s, rem);
-        ok = x.take<4>(O_HD + b * B_H, wave, lane, on, hd);
+        ok = x.take<4, B_FRAG>(O_HD + b * B_H, wave, off_hd(col, g), on, hd);
         stores_done();
 #pragma unroll
         for (int kp = 0; kp < 4; ++kp) product(kp, hd[kp]);
@@ -449,7 +455,7 @@ __device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, int n
         v += v4;
         v += v5;
         if (ps.bad()) return give_up(d, s, rem);
-        if (wave < 4 && on && row < N_PROJ) x.put(__float_as_uint(v), m_off, O_M + b * B_M);
+        if (s < my_rem) x.put(__float_as_uint(v), m_off, m_buf + b * B_M);
         b = b_next;
         b_next = next3(b);
     }
@@ -465,7 +471,7 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int c
     uint4 a3[2][NK3], a4[2][NK4];
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
-        const int mt = wave + m * NW;
+        const int mt = 2 * wave + m;
 #pragma unroll
         for (int f = 0; f < NK3; ++f) a3[m][f] = reinterpret_cast<const uint4*>(d.Wp1)[((size_t)mt * NK3 + f) * 64 + lane];
 #pragma unroll
@@ -476,24 +482,19 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int c
     constexpr int VEC = MEL_ROWS / 4;
     const int m_slot = min(tid / VEC, SEG_SLOTS - 1), m_row = tid % VEC * 4;
     const int m_rem = tid < SEG_SLOTS * VEC && m_row < N_PROJ && m_slot < n_slots && d.live[m_slot] && !d.done[m_slot] ? d.n_steps[m_slot] - d.t[m_slot] : 0;
-    const int m_t0 = d.t[m_slot];
+    const int m_t0 = d.t[m_slot], m_off = m_row / 16 * (SEG_SLOTS * 64) + m_slot * 64 + m_row % 16 * 4;     // [row tile][slot][16 rows]
     // the launches after this one read the half of this pair that belongs to their parity: it must not fall behind
     const int end_all = cur ^ (n_steps & 1);
     if (tid == 0 && end_all != cur) d.wg_seq[end_all] = d.wg_seq[cur];
     int b = 0, b_next = 1;
     for (int s = 0; s < n_steps; ++s) {
         const bool on = s < rem, m_on = s < m_rem;
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            const int mt = wave + m * NW;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) x.empty(p_off(mt, col, g) + 4 * i, O_P + b_next * B_P + (mt >> 1) * B_FRAG);
-        }
+        if (on) x.empty4(off_hp(col, g), O_P + b_next * B_P + wave * B_FRAG);
         u32x4_t w = {0u, 0u, 0u, 0u};
         bool in = !m_on;
         for (int spin = 0; spin < x.polls && !in; ++spin) {
             Words::again();
-            w = x.look4(tid * 16, O_M + b * B_M);
+            w = x.look4(m_off, O_M + b * B_M);
             in = m_row == N_MEL ? w.x != EMPTY : Words::full(w);
         }
         stores_done();
@@ -511,7 +512,7 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int c
                 floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int f = 0; f < NK3; ++f) acc = mfma_frag<h16_t>(a3[m][f], bm[f], acc);
-                *reinterpret_cast<uint2*>(&s_hid[col][16 * (wave + m * NW) + 4 * g]) =
+                *reinterpret_cast<uint2*>(&s_hid[col][16 * (2 * wave + m) + 4 * g]) =
                     make_uint2(pack2<h16_t>(fmaxf(acc[0], 0.f), fmaxf(acc[1], 0.f)), pack2<h16_t>(fmaxf(acc[2], 0.f), fmaxf(acc[3], 0.f)));
             }
         }
@@ -530,11 +531,10 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int c
                 for (int m = 0; m < 2; ++m) acc[m] = mfma_frag<h16_t>(a4[m][f], bh[f], acc[m]);
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                const int mt = wave + m * NW;
+                const int mt = 2 * wave + m;
                 const unsigned lo = pack2<h16_t>(fmaxf(acc[m][0], 0.f), fmaxf(acc[m][1], 0.f)), hi = pack2<h16_t>(fmaxf(acc[m][2], 0.f), fmaxf(acc[m][3], 0.f));
                 if (s + 1 < min(rem, n_steps)) {
-                    x.put(lo, p_off(mt, col, g), O_P + b * B_P + (mt >> 1) * B_FRAG);
-                    x.put(hi, p_off(mt, col, g) + 4, O_P + b * B_P + (mt >> 1) * B_FRAG);
+                    x.put2(lo, hi, col * 64 + m * 32 + g * 8, O_P + b * B_P + wave * B_FRAG);
                 } else if (on) {
                     h16_t* dst = reinterpret_cast<h16_t*>(d.xatt[cur ^ ((s + 1) & 1)]) + xoff<h16_t>(NK_A, col, XA_P + 16 * mt + 4 * g);
                     *reinterpret_cast<uint2*>(dst) = make_uint2(lo, hi);
@@ -627,9 +627,12 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
     bound *= 0.5f;
     const bool fast_softmax = bound <= 30.f;
 
+    // the energies of one workgroup's tiles lie together: [4 workgroups][its tiles][16 positions]
+    const int e_slot = segment_energy_bytes(ML);
+    auto e_off = [&](int j) { return (j >> 4 & 3) * (e_slot / 4) + (j >> 6) * 64 + (j & 15) * 4; };
     // this thread's share of the query: four rows of two of its 32 partial products
-    const int q_off = (tid >> 5) * 2 * ATT * 4 + (tid & 31) * 16, b_e = SEG_SLOTS * ML * 4, e_at = O_E + slot * ML * 4;
-    const int k_a = sp * FS + tid, a_off = (slot * 4 + (k_a % KB) / 8) * 16 + (k_a % 8) * 2, a_frag = k_a / KB * B_FRAG;
+    const int q_off = (tid >> 5) * 2 * ATT * 4 + (tid & 31) * 16, b_e = SEG_SLOTS * e_slot, e_at = O_E + slot * e_slot;
+    const int k_a = sp * FS + tid, a_off = slot * (ENC * 2) + k_a * 2;
     int b = 0, b_next = 1;
     for (int s = 0; s < steps; ++s) {
 #pragma unroll
@@ -637,8 +640,8 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
 #pragma unroll
         for (int i = 0; i < NP; ++i) keep(rows[i]);
         for (int tt = sp + S * wave; tt < ntile; tt += S * NW)
-            if (g == 0 && tt * 16 + jl < L) x.empty((tt * 16 + jl) * 4, e_at + b_next * b_e);
-        if (tid < FS && !(tid & 1)) x.empty(a_off, O_A + b_next * B_A + a_frag);
+            if (g == 0 && tt * 16 + jl < L) x.empty(e_off(tt * 16 + jl), e_at + b_next * b_e);
+        if (tid < FS && !(tid & 1)) x.empty(a_off, O_A + b_next * B_A);
         // the location features do not wait for the query
         const uint4 bl0 = tile.loc(s_u[0], s_u[1], min((sp + S * wave) * 16, (ntile - 1) * 16) + jl, g);
         {
@@ -699,7 +702,7 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
             if (fast_softmax) e = __expf(e - bound);
             if (g == 0 && j < L) {
                 s_e[j] = e;
-                x.put(__float_as_uint(e), j * 4, e_at + b * b_e);
+                x.put(__float_as_uint(e), e_off(j), e_at + b * b_e);
             }
         }
         bool ok = true;
@@ -709,7 +712,7 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
             bool in = false;
             for (int spin = 0; spin < x.polls && !in; ++spin) {
                 Words::again();
-                w = x.look(i * 4, e_at + b * b_e);
+                w = x.look(e_off(i), e_at + b * b_e);
                 in = w != EMPTY;
             }
             ok = ok && in;
@@ -782,7 +785,7 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
                 c += (s_ctx[w][tid] + s_ctx[w][LPR * 8 + tid]) + (s_ctx[w][2 * LPR * 8 + tid] + s_ctx[w][3 * LPR * 8 + tid]);
             const h16_t a = from_float<h16_t>(c * inv);
             const unsigned lo = a.bits, hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)lo, 0xB1, 0xf, 0xf, false);      // the neighbour's (lanes 1, 0, 3, 2)
-            if (!(tid & 1)) x.put(lo | hi << 16, a_off, O_A + b * B_A + a_frag);
+            if (!(tid & 1)) x.put(lo | hi << 16, a_off, O_A + b * B_A);
             if (s + 1 == steps) {
                 const int end = cur ^ (steps & 1);
                 reinterpret_cast<h16_t*>(d.xatt[end])[xoff<h16_t>(NK_A, slot, XA_A + k_a)] = a;

@@ -722,9 +722,9 @@ static int launch_steps(tts_pool* p, int n_active, int nsteps)
 
 // How many of the next `n` steps run as one launch (segment.hip; 0: they run step by step).  The line is the form's own: one tile
 // of slots, two-byte weights and memory (d.seg_x), frame counts known beforehand.  There it is the faster one at every size, chunks
-// of 40 steps of requests of 165 positions, steps as launches in graphs -> as one launch: 1 request 16.8 -> 10.6 us a step,
-// 4: 17.9 -> 11.8, 8: 18.2 -> 13.7, 12: 18.4 -> 15.9, 16: 18.5 -> 17.4; single steps, back to back: 1 request 28.4 -> 18.5,
-// 16: 28.7 -> 26.4.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other
+// of 40 steps of requests of 165 positions, steps as launches in graphs -> as one launch: 1 request 16.8 -> 9.7 us a step,
+// 4: 17.9 -> 10.0, 8: 18.2 -> 10.7, 12: 18.4 -> 11.4, 16: 18.5 -> 12.1; single steps, back to back, took 28.4 -> 18.5 (1 request) and
+// 28.7 -> 26.4 us (16) before the words lay as they do now.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other
 // streams gets the compute units at intervals.
 static const int MAX_SEGMENT_STEPS = 64;
 static int segment_steps(const tts_pool* p, int n)
