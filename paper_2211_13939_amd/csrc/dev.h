@@ -23,7 +23,7 @@ constexpr int K_PROJ = HID + ENC;           // 1536: [H_dec; A]
 constexpr int N_PROJ = N_MEL + 1;           // mel rows + stop row
 constexpr int MAX_POOL = 256;
 constexpr int MAX_ENC_LEN = 1024;
-constexpr int SEG_SLOTS = 16;                // slots a segment's launch covers: one pool tile
+constexpr int SEG_SLOTS = 16, SEG_TILES = 3; // a pool tile, and the most of them a segment's launch covers (segment.hip)
 constexpr int MAX_TILES = MAX_POOL / 16;     // a pool tile = 16 consecutive slots = the 16 columns of one MFMA
 // offsets inside the activation rows
 constexpr int XA_P = 0, XA_A = PRENET, XA_H = PRENET + ENC;       // x_att = [p | a | h_att]
@@ -67,6 +67,7 @@ struct DevPtrs {
                           // and writes the other; zero at creation): the stamp of the words in p_x and pre_x
     void* seg_x;          // the words the workgroups of a segment's launch hand each other (segment.hip), all bits set at creation
                           // (null: no step of the pool runs in that form)
+    int seg_slots;        // slots it has room for (whole tiles)
     int* fault;           // pinned host memory: set by a workgroup whose bounded wait for another's words ran out (with `failed` of the slots it froze)
     const void* lsa_kfrag; // location filters as per-lane MFMA A operands (layout depends on WT)
     const void* lsa_wfrag; // W_loc as per-lane MFMA A operands (layout depends on WT)

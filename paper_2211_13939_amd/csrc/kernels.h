@@ -17,9 +17,10 @@ struct StepLaunch {
                     // whose predecessor in the same call formed it already); 0: it does not
     int att_tail;   // 1 (pools with d.p_x only): the step's last launch also forms the attention LSTM of the next step, which then
                     // has att_lead = 0.  The membership and the requests' states must not change between the two steps.
-    int seg_steps;  // > 0: not one step but this many, as one launch (segment.hip): pools with d.seg_x and no stop threshold, n_blocks <= SEG_SLOTS,
+    int seg_steps;  // > 0: not one step but this many, as one launch (segment.hip): pools with d.seg_x and no stop threshold, n_blocks <= SEG_TILES * SEG_SLOTS,
                     // at least one running request takes each of the steps
     int seg_set;    // which of the two sets of d.seg_x it uses: in turn, launch by launch
+    int seg_empty;  // tiles of the other set it has to empty: those that the launch before used
     int pre_gates;  // 2: the projection's launch also forms the next step's gate pre-sums (d.pre_att / d.pre_dec; fp32: n_tiles <= PRESUM_SMALL_TILES),
                     // 1: the attention LSTM's only (pools of more than PRESUM_SMALL_TILES tiles: d.pre_dec is null);
                     // either way the attention LSTM hands the query to the attention kernel as rank-32 partial products (d.qpart)
@@ -38,11 +39,13 @@ constexpr int QUERY_PARTIALS = 32;
 // the 96 x 16 partial sums of all but the first (of all of them, and one more sequence number for the tile's leader, in
 // the fused form of the last kernel: d.hdec_x)
 constexpr int PROJ_GROUP = 6;       // the largest group
-// d.seg_x: two sets, each three buffers of the words a segment's workgroups hand each other: h_att and h_dec (32 fragments of 1 KB),
-// a (16), p (8), the query's partial products, the frame's rows and, per position of the longest text, the energies
+// d.seg_x: two sets, each for every pool tile three buffers of the words a segment's workgroups hand each other: h_att and h_dec
+// (32 fragments of 1 KB), a (16), p (8), the query's partial products, the frame's rows and, per position of the longest text, the energies
 constexpr size_t SEG_FIXED_BYTES = 3 * ((size_t)(32 + 32 + 16 + 8) * 1024 + (size_t)SEG_SLOTS * QUERY_PARTIALS * ATT * 4 + 96 * SEG_SLOTS * 4);
-constexpr int segment_energy_bytes(int max_enc_len) { return (max_enc_len + 63) / 64 * 256; }      // per slot: a quarter for each of its workgroups
-constexpr size_t segment_set_bytes(int max_enc_len) { return SEG_FIXED_BYTES + (size_t)3 * SEG_SLOTS * segment_energy_bytes(max_enc_len); }
+constexpr int segment_energy_bytes(int max_enc_len) { return (max_enc_len + 63) / 64 * 256; }      // per slot: a share for each of its workgroups
+constexpr size_t segment_tile_bytes(int max_enc_len) { return SEG_FIXED_BYTES + (size_t)3 * SEG_SLOTS * segment_energy_bytes(max_enc_len); }
+constexpr int segment_tiles(int max_pool) { return max_pool > SEG_TILES * SEG_SLOTS ? SEG_TILES : (max_pool + SEG_SLOTS - 1) / SEG_SLOTS; }
+constexpr size_t segment_bytes(int max_pool, int max_enc_len) { return 2 * segment_tiles(max_pool) * segment_tile_bytes(max_enc_len); }
 
 // One decoder step (paper Eq. 2) for every request whose slot is flagged in d.live.
 // `cur` selects which half of the double-buffered activations is read.
@@ -50,7 +53,7 @@ constexpr size_t segment_set_bytes(int max_enc_len) { return SEG_FIXED_BYTES + (
 // first kernel and ev[i + 1] after kernel i (per-kernel device times).
 // (Pools with d.hdec_x launch three kernels - the decoder LSTM is part of the last one - and record ev[3] right after ev[2].)
 constexpr int N_STEP_KERNELS = 4;
-hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, hipStream_t s);   // (launch_step's seg_steps)
+hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, hipStream_t s);   // (launch_step's seg_steps)
 hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int cur, hipStream_t s, hipEvent_t* ev = nullptr);
 
 hipError_t launch_set_live(const DevPtrs& d, const LiveArgs& args, hipStream_t s);

@@ -1,20 +1,20 @@
-// A segment of decoder steps as ONE launch, for two-byte pools whose running requests lie in the first 16 slots.
+// A segment of decoder steps as ONE launch, for two-byte pools whose running requests lie in the first SEG_TILES tiles of 16 slots.
 //
 // What bounds a step of so small a pool is a chain: p -> attention LSTM -> query -> energies -> context -> decoder LSTM -> frame
 // -> p.  As launches of its own (k_lsa, k_proj) a step takes 16.8 us at one request, 6 us of it two launch boundaries with the
 // start-up and the first cold round trips behind them, and every launch pulls its share of the 36 MB of weights again.  Here the
 // workgroups stay for the whole segment: each keeps its part of the weights in registers and LDS and its part of the requests'
 // state in registers, and the links of the chain are words handed from workgroup to workgroup through memory.  One such hop takes
-// 0.4 to 0.6 us from store to seen (64 words handed to and fro between two workgroups, on one XCD or on different ones), and a
-// round of polls as long as its bytes at 25 GB/s through a CU: the form is for pools of one tile, and the words are dense.
+// 0.4 to 0.6 us from store to seen (64 words handed to and fro between two workgroups, on one XCD or on different ones).
 //
 // Workgroups (eight waves, one per CU; blockIdx % 8 is the XCD), and what each does in step s:
 //   32 x ATT   32 hidden units of the attention LSTM each: gates from p (K = 256) and the pre-sums, cell, h and the units' rank-32
 //              share of the query out; then, off the chain, the gate pre-sums of step s + 1 from a and h_att
-//   4 x LSA    per request, on one XCD: energies shared among the four, softmax, a quarter of the context's columns each; the
+//   S x LSA    per request, on one XCD: energies shared among the S, softmax, a share of the context's columns each; the
 //              attention weights stay in LDS, the rows of the request's memory (up to 512 positions) in registers
 //   64 x DEC   16 hidden units of the decoder LSTM each: the sums over h_dec and h_att ahead of the chain, those over a on it
-//   6 x ROWS   one row tile of the projection each; 1 x LEAD: frame, prenet, books
+//   per tile: 6 x ROWS   one row tile of the projection each; 1 x LEAD: frame, prenet, books
+// ATT and DEC serve the tiles one after the other; one tile is bound by the chain, three by the work of an ATT.
 // Every product and every sum is formed in the order of the kernels in kernels.hip, so a request's frames and state are the
 // same bits whichever form a step takes.
 //
@@ -64,6 +64,8 @@ __device__ __forceinline__ void stores_done() { vm_in_flight_at_most<0>(); }
 struct Words {
     char* base;
     int bytes, polls;
+    // the words of one pool tile
+    __device__ __forceinline__ Words of(int tile, int tile_bytes) const { return {base + (size_t)tile * tile_bytes, tile_bytes, polls}; }
     __device__ __forceinline__ __amdgpu_buffer_rsrc_t rs() const { return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, BUFFER_RSRC_RAW); }
     // (the compiler may not take a round of polls for the one before)
     __device__ __forceinline__ static void again() { asm volatile("" ::: "memory"); }
@@ -102,7 +104,31 @@ struct Words {
         u32x4_t w[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) w[n] = u32x4_t{0u, 0u, 0u, 0u};
-        bool in = !on;
+        return take_on<N, STRIDE, NAP>(buf, first, lane_off, !on, w, out);
+    }
+    // the first look, asked for ahead: loads return in the order of the requests, those behind a store after its acknowledgement
+    template <int N, int STRIDE>
+    __device__ __forceinline__ void ahead(int buf, int first, int lane_off, u32x4_t (&w)[N]) const
+    {
+        again();
+#pragma unroll
+        for (int n = 0; n < N; ++n) w[n] = look4(lane_off, buf + (first + 8 * n) * STRIDE);
+    }
+    // ... and what is left to be done about it
+    template <int N, int STRIDE, int NAP = 0>
+    __device__ __forceinline__ bool take_rest(int buf, int first, int lane_off, bool on, u32x4_t (&w)[N], uint4 (&out)[N]) const
+    {
+        bool in = true;
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            in = in && full(w[n]);
+            if (!on) w[n] = u32x4_t{0u, 0u, 0u, 0u};
+        }
+        return take_on<N, STRIDE, NAP>(buf, first, lane_off, in || !on, w, out) && polls > 0;
+    }
+    template <int N, int STRIDE, int NAP>
+    __device__ __forceinline__ bool take_on(int buf, int first, int lane_off, bool in, u32x4_t (&w)[N], uint4 (&out)[N]) const
+    {
         for (int spin = 0; spin < polls && !in; ++spin) {
             again();
 #pragma unroll
@@ -165,12 +191,26 @@ __device__ __forceinline__ void cell(const floatx4& g, float& c, float& h)
     h = go * tanhf_(c);
 }
 
-// the requests that take part in step s end here (thread c < 16 holds slot c's remaining steps)
-__device__ __forceinline__ void give_up(const DevPtrs& d, int s, int rem)
+// What a workgroup knows of the requests: the steps each slot still has to take, from the segment's first on (0: no request there).
+struct Pool {
+    int cur, n_steps, n_tiles, tile_bytes;
+    const int* rem;                                         // [n_tiles * 16], in LDS
+};
+// the requests that take part in step s end here
+__device__ __forceinline__ void give_up(const DevPtrs& d, const Pool& pl, int s)
 {
-    if (threadIdx.x < 16 && s < rem) {
+    if ((int)threadIdx.x < pl.n_tiles * 16 && s < pl.rem[threadIdx.x]) {
         d.done[threadIdx.x] = 1;
         d.failed[threadIdx.x] = 1;
+        *d.fault = 1;
+    }
+}
+
+__device__ __forceinline__ void lose_one(const DevPtrs& d, int slot)
+{
+    if (threadIdx.x == 0) {
+        d.done[slot] = 1;
+        d.failed[slot] = 1;
         *d.fault = 1;
     }
 }
@@ -195,7 +235,9 @@ constexpr int ATT_LDS_RT = 2;                               // row tiles whose l
 constexpr int ATT_LATE = 6;                                 // late fragments per wave and row tile: two of a, four of h_att
 constexpr int S_ATT_W = ATT_LDS_RT * ATT_LATE * NW * 1024, S_ATT_RED = NW * 4 * 1024, S_ATT_B = F_P * 1024;
 constexpr int S_ATT = S_ATT_W + S_ATT_RED + S_ATT_B + 32 * 16 * 4 + 16 * 32 * 2;
-constexpr int S_DEC = 3 * NW * 4 * 1024 + NW * 7 * 1024;
+constexpr int S_DEC_RED = 2 * NW * 4 * 1024, S_DEC_W = NW * 7 * 1024;
+constexpr int S_DEC_PRE = SEG_TILES * 2 * 256 * 16, S_DEC_RED2 = NW * 4 * 1024;            // several tiles, one tile: in the same place
+constexpr int S_DEC = S_DEC_RED + S_DEC_W + (S_DEC_PRE > S_DEC_RED2 ? S_DEC_PRE : S_DEC_RED2);
 constexpr int P_LD = 68;                                    // the reduction reads 4 columns x 16 rows a wave: a bank each
 constexpr int S_ROWS = 6 * NW * 4 * P_LD * 4;
 constexpr int MEL_LD = MEL_ROWS + 8, HID_LD = PRENET + 8;     // halves: an odd number of 16-byte pieces a row
@@ -206,9 +248,12 @@ constexpr int S_MAX = S_DEC;
 static_assert(S_ATT <= S_MAX && S_ROWS <= S_MAX && S_LEAD <= S_MAX && S_LSA <= S_MAX && S_MAX + 64 <= 160 * 1024, "the roles' LDS");
 
 // ---------------------------------------------------------------- the attention LSTM and the query
-__device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& x, int cur, int n_slots, int n_steps, int rg, char* lds, Phases ps)
+// MULTI: more tiles than one.  The cells and the pre-sums then live in memory from step to step (each thread's own words of the arrays
+// the step kernels use: requested ahead of the wait for p), else in registers.
+template <bool MULTI>
+__device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& words, const Pool& pl, int rg, char* lds, Phases ps)
 {
-    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4, cur = pl.cur, n_steps = pl.n_steps;
     const int rt = rg * 8 + wave, unit = rt * 4 + g;
     uint4* s_w = reinterpret_cast<uint4*>(lds);                                             // [2][6 f][8 waves][64]
     floatx4 (*red)[4][64] = reinterpret_cast<floatx4 (*)[4][64]>(lds + S_ATT_W);
@@ -231,98 +276,146 @@ __device__ __forceinline__ void seg_att(const DevPtrs& d, const Words& x, int cu
     float wq[8];                                            // W_q[16 wave + ..][32 rg + 4 k + ..]
 #pragma unroll
     for (int k = 0; k < 8; ++k) wq[k] = d.Wq_epi[((size_t)(rg * 8 + k) * 8 + wave) * 64 + lane];
-    const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
     const floatx4 bias4 = *reinterpret_cast<const floatx4*>(d.ba + unit * 4);
     floatx4* pre_g = reinterpret_cast<floatx4*>(d.pre_att) + (size_t)rt * 64 + lane;
-    floatx4 pre4 = *pre_g;
-    float c = d.c_att[(size_t)col * HID + unit];
-    uint4 pb[1] = {reinterpret_cast<const uint4*>(d.xatt[cur])[xfrag(NK_A, 0, wave, lane)]};
+    float* c_g = d.c_att + (size_t)col * HID + unit;
+    constexpr int PRE_TILE = HID / 4 * 64, C_TILE = 16 * HID, NAP = MULTI ? 4 : 16;
+    floatx4 pre4 = pre_g[0];
+    float c = c_g[0];
     const int q_off = col * B_QS + (16 * wave + 4 * g) * 4;
 
     int b = 0, b_before = 2, b_next = 1;
     for (int s = 0; s < n_steps; ++s) {
-        const bool on = s < rem;
-        bool ok = true;
-        if (s > 0) ok = x.take<1, B_FRAG>(O_P + b_before * B_P, wave, off_hp(col, g), on, pb);
-        stores_done();
-        s_b[wave][lane] = pb[0];
-        ps.sync(ok);
-        floatx4 g4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int f = 0; f < F_P; ++f) g4 = mfma_frag<h16_t>(we[f], s_b[f][lane], g4);
-        g4 += bias4;
-        g4 += pre4;
-        float c_new = c, hf;
-        cell(g4, c_new, hf);
-        const h16_t h = from_float<h16_t>(hf);
-        s_h[4 * wave + g][col] = on ? to_float(h) : 0.f;
-        s_hh[col][4 * wave + g] = h;
-        if (ps.bad()) return give_up(d, s, rem);
-        lds_barrier();
-        // the units' share of the query: 16 rows per wave
-        {
-            floatx4 part = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) part = __builtin_amdgcn_mfma_f32_16x16x4f32(wq[k], s_h[4 * k + g][col], part, 0, 0, 0);
-            if (on) x.put4(part, q_off, O_Q + b * B_Q + rg * ATT * 4);
-            if (wave == 0 && on) x.put4(*reinterpret_cast<const floatx4*>(&s_hh[col][8 * g]), off_hp(col, g), O_HA + b * B_H + rg * B_FRAG);
+        // Several tiles: what tile t + 1 needs is asked for while tile t's gates are formed and is there before tile t's words are stored
+        // (loads return in the order of the requests: behind a store they would wait for its acknowledgement).
+        u32x4_t p_next[1];
+        floatx4 pre_next = pre4;
+        float c_next = c;
+        auto ask = [&](int t) __attribute__((always_inline)) {
+            if (s > 0) words.of(t, pl.tile_bytes).ahead<1, B_FRAG>(O_P + b_before * B_P, wave, off_hp(col, g), p_next);
+            else p_next[0] = reinterpret_cast<const u32x4_t*>(d.xatt[cur])[xfrag(NK_A, t, wave, lane)];
+            pre_next = pre_g[t * PRE_TILE];
+            c_next = c_g[t * C_TILE];
+        };
+        if constexpr (MULTI) {
+            ask(0);
+            stores_done();                                  // (and all tiles' emptying, in the step before)
         }
-        if (on) c = c_new;
-        if (s + 1 == min(rem, n_steps)) {
-            // the request's last step of this segment: its state where the step kernels keep it
-            const int end = cur ^ ((s + 1) & 1);
-            d.c_att[(size_t)col * HID + unit] = c;
-            reinterpret_cast<h16_t*>(d.xatt[end])[xoff<h16_t>(NK_A, col, XA_H + unit)] = h;
-            reinterpret_cast<h16_t*>(d.xdec[end ^ 1])[xoff<h16_t>(NK_D, col, XD_HA + unit)] = h;
+        for (int t = 0; t < (MULTI ? pl.n_tiles : 1); ++t) {
+            const Words x = words.of(t, pl.tile_bytes);
+            const int rem = pl.rem[t * 16 + col];
+            const bool on = s < rem;
+            bool ok = true;
+            uint4 pb[1];
+            if constexpr (MULTI) {
+                pre4 = pre_next;
+                c = c_next;
+                if (s > 0) ok = x.take_rest<1, B_FRAG>(O_P + b_before * B_P, wave, off_hp(col, g), on, p_next, pb);
+                else pb[0] = as_uint4(p_next[0]);
+            } else {
+                if (s > 0) ok = x.take<1, B_FRAG>(O_P + b_before * B_P, wave, off_hp(col, g), on, pb);
+                else pb[0] = reinterpret_cast<const uint4*>(d.xatt[cur])[xfrag(NK_A, t, wave, lane)];
+                stores_done();
+            }
+            s_b[wave][lane] = pb[0];
+            ps.sync(ok);
+            if constexpr (MULTI) ask(min(t + 1, pl.n_tiles - 1));
+            floatx4 g4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int f = 0; f < F_P; ++f) g4 = mfma_frag<h16_t>(we[f], s_b[f][lane], g4);
+            g4 += bias4;
+            g4 += pre4;
+            float c_new = c, hf;
+            cell(g4, c_new, hf);
+            const h16_t h = from_float<h16_t>(hf);
+            s_h[4 * wave + g][col] = on ? to_float(h) : 0.f;
+            s_hh[col][4 * wave + g] = h;
+            if (ps.bad()) return give_up(d, pl, s);
+            lds_barrier();
+            // the units' share of the query: 16 rows per wave
+            {
+                floatx4 part = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < 8; ++k) part = __builtin_amdgcn_mfma_f32_16x16x4f32(wq[k], s_h[4 * k + g][col], part, 0, 0, 0);
+                if constexpr (MULTI) stores_done();
+                if (on) x.put4(part, q_off, O_Q + b * B_Q + rg * ATT * 4);
+                if (wave == 0 && on) x.put4(*reinterpret_cast<const floatx4*>(&s_hh[col][8 * g]), off_hp(col, g), O_HA + b * B_H + rg * B_FRAG);
+            }
+            const bool last = s + 1 == min(rem, n_steps);
+            if (on) c = c_new;
+            if (MULTI ? on : last) c_g[t * C_TILE] = c;
+            if (last) {
+                // the request's last step of this segment: its state where the step kernels keep it
+                const int end = cur ^ ((s + 1) & 1);
+                reinterpret_cast<h16_t*>(d.xatt[end])[xoff<h16_t>(NK_A, t * 16 + col, XA_H + unit)] = h;
+                reinterpret_cast<h16_t*>(d.xdec[end ^ 1])[xoff<h16_t>(NK_D, t * 16 + col, XD_HA + unit)] = h;
+            }
         }
 
         // off the chain: the next step's gate pre-sums over [a; h_att]
-        uint4 hb[4], ab[2];
-        // (a first: it comes last, so that the larger h_att is asked for once)
-        ok = x.take<2, 64, 16>(O_A + b * B_A, wave, off_a(col, g), on, ab);
-        ok = x.take<4, B_FRAG, 16>(O_HA + b * B_H, wave, off_hp(col, g), on, hb) && ok;
-        // (step s - 1's words, whose buffer is step s + 2's: taken before this step's a was made)
-        if (wave == 0 && on) x.empty4(off_hp(col, g), O_HA + b_before * B_H + rg * B_FRAG);
-        if (on) x.empty4(q_off, O_Q + b_before * B_Q + rg * ATT * 4);
+        for (int t = 0; t < (MULTI ? pl.n_tiles : 1); ++t) {
+            const Words x = words.of(t, pl.tile_bytes);
+            const bool on = s < pl.rem[t * 16 + col];
+            uint4 hb[4], ab[2];
+            // (a comes last: by then the larger h_att has been asked for once)
+            bool ok;
+            if constexpr (MULTI) {
+                u32x4_t h_look[4];
+                x.ahead<4, B_FRAG>(O_HA + b * B_H, wave, off_hp(col, g), h_look);
+                ok = x.take<2, 64, NAP>(O_A + b * B_A, wave, off_a(col, g), on, ab);
+                ok = x.take_rest<4, B_FRAG, NAP>(O_HA + b * B_H, wave, off_hp(col, g), on, h_look, hb) && ok;
+            } else {
+                ok = x.take<2, 64, NAP>(O_A + b * B_A, wave, off_a(col, g), on, ab);
+                ok = x.take<4, B_FRAG, NAP>(O_HA + b * B_H, wave, off_hp(col, g), on, hb) && ok;
+            }
+            // (step s - 1's words, whose buffer is step s + 2's: taken before this step's a was made)
+            if (wave == 0 && on) x.empty4(off_hp(col, g), O_HA + b_before * B_H + rg * B_FRAG);
+            if (on) x.empty4(q_off, O_Q + b_before * B_Q + rg * ATT * 4);
+            if (MULTI && t > 0) lds_barrier();
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            if (half) lds_barrier();
+            for (int half = 0; half < 2; ++half) {
+                if (half) lds_barrier();
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int r = 4 * half + r4;
-                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const int r = 4 * half + r4;
+                    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int f = 0; f < ATT_LATE; ++f) {
-                    const uint4 w = r < 8 - ATT_LDS_RT ? wl[r < 8 - ATT_LDS_RT ? r : 0][f]
-                                                       : s_w[(((r - (8 - ATT_LDS_RT)) * ATT_LATE + f) * NW + wave) * 64 + lane];
-                    acc = mfma_frag<h16_t>(w, f < 2 ? ab[f < 2 ? f : 0] : hb[f < 2 ? 0 : f - 2], acc);
+                    for (int f = 0; f < ATT_LATE; ++f) {
+                        const uint4 w = r < 8 - ATT_LDS_RT ? wl[r < 8 - ATT_LDS_RT ? r : 0][f]
+                                                           : s_w[(((r - (8 - ATT_LDS_RT)) * ATT_LATE + f) * NW + wave) * 64 + lane];
+                        acc = mfma_frag<h16_t>(w, f < 2 ? ab[f < 2 ? f : 0] : hb[f < 2 ? 0 : f - 2], acc);
+                    }
+                    red[wave][r4][lane] = acc;
                 }
-                red[wave][r4][lane] = acc;
-            }
-            if (half) lds_barrier();
-            else ps.sync(ok);
-            if (wave >> 2 == half) {
-                pre4 = red[0][wave & 3][lane];
+                if (half) lds_barrier();
+                else ps.sync(ok);
+                if (wave >> 2 == half) {
+                    pre4 = red[0][wave & 3][lane];
 #pragma unroll
-                for (int w = 1; w < NW; ++w) pre4 += red[w][wave & 3][lane];
+                    for (int w = 1; w < NW; ++w) pre4 += red[w][wave & 3][lane];
+                }
             }
+            if (ps.bad()) return give_up(d, pl, s);
+            if (MULTI || s + 1 == n_steps) pre_g[t * PRE_TILE] = pre4;
         }
-        if (ps.bad()) return give_up(d, s, rem);
         b_before = b;
         b = b_next;
         b_next = next3(b);
     }
-    *pre_g = pre4;
 }
 
 // ---------------------------------------------------------------- the decoder LSTM
-__device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cur, int n_slots, int n_steps, int j, char* lds, Phases ps)
+template <bool MULTI>
+__device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& words, const Pool& pl, int j, char* lds, Phases ps)
 {
-    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    floatx4 (*red_a)[4][64] = reinterpret_cast<floatx4 (*)[4][64]>(lds);
-    floatx4 (*red_hd)[4][64] = red_a + NW;
-    floatx4 (*red_ha)[4][64] = red_hd + NW;
-    uint4* s_w = reinterpret_cast<uint4*>(lds + 3 * NW * 4 * 1024) + wave * 7 * 64 + lane;      // [wave][7][64]: the wave's own
+    const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4, cur = pl.cur, n_steps = pl.n_steps;
+    // reduction buffers in turn: what was read from one is done when the barrier of the other has been passed (one tile: a third one,
+    // where several tiles keep the sums over h, saves a barrier)
+    floatx4 (*red0)[4][64] = reinterpret_cast<floatx4 (*)[4][64]>(lds);
+    floatx4 (*red1)[4][64] = red0 + NW;
+    floatx4 (*red2)[4][64] = reinterpret_cast<floatx4 (*)[4][64]>(lds + S_DEC_RED + S_DEC_W);
+    uint4* s_w = reinterpret_cast<uint4*>(lds + S_DEC_RED) + wave * 7 * 64 + lane;              // [wave][7][64]: the wave's own
+    floatx4* s_pre = reinterpret_cast<floatx4*>(lds + S_DEC_RED + S_DEC_W) + threadIdx.x;       // [tile][h_dec, h_att][256 threads]
     uint4 w[4][NK_D / NW];                                  // fragments wave + 8 f: h_att (f = 0 .. 3), a (4, 5), h_dec (6 .. 9)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -332,75 +425,136 @@ __device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cu
 #pragma unroll
     for (int f = 0; f < 7; ++f) s_w[f * 64] = d.Wd[xfrag(NK_D, 4 * j + 3, wave + 8 * (f < 3 ? f + 1 : f + 3), lane)];   // registers hold the others
     const int er = wave & 3, rt = 4 * j + er, unit = rt * 4 + g, hd_off = col * 32 + er * 8 + (g >> 1) * 4;
-    const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
     const floatx4 bias4 = *reinterpret_cast<const floatx4*>(d.bd + unit * 4);
-    float c = d.c_dec[(size_t)col * HID + unit];
-    uint4 hd[4];
-#pragma unroll
-    for (int f = 0; f < 4; ++f) hd[f] = reinterpret_cast<const uint4*>(d.xdec[cur])[xfrag(NK_D, 0, XD_HD / KB + wave + 8 * f, lane)];
+    float* c_g = d.c_dec + (size_t)col * HID + unit;
+    constexpr int C_TILE = 16 * HID, NAP = MULTI ? 2 : 8;
+    float c = c_g[0];
 
     int b = 0, b_before = 2, b_next = 1;
     for (int s = 0; s < n_steps; ++s) {
-        const bool on = s < rem;
-        bool ok = true;
-        // ahead of the chain: the sums over h_dec of the step before and over h_att
-        if (s > 0) ok = x.take<4, B_FRAG, 8>(O_HD + b_before * B_H, wave, off_hd(col, g), on, hd);
+        floatx4 pre4, pre4b;
+        // ahead of the chain: the sums over h_dec of the step before (all tiles') and over h_att
+        auto over_hd = [&](int t, floatx4 (*red)[4][64]) __attribute__((always_inline)) {
+            const Words x = words.of(t, pl.tile_bytes);
+            const bool on = s < pl.rem[t * 16 + col];
+            bool ok = true;
+            uint4 hd[4];
+            if (s > 0) {
+                ok = x.take<4, B_FRAG, NAP>(O_HD + b_before * B_H, wave, off_hd(col, g), on, hd);
+            } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+                for (int f = 0; f < 4; ++f) hd[f] = reinterpret_cast<const uint4*>(d.xdec[cur])[xfrag(NK_D, t, XD_HD / KB + wave + 8 * f, lane)];
+            }
 #pragma unroll
-            for (int f = 0; f < 4; ++f) acc = mfma_frag<h16_t>(r < 3 ? w[r][6 + f] : s_w[(3 + f) * 64], hd[f], acc);
-            red_hd[wave][r][lane] = acc;
+            for (int r = 0; r < 4; ++r) {
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int f = 0; f < 4; ++f) acc = mfma_frag<h16_t>(r < 3 ? w[r][6 + f] : s_w[(3 + f) * 64], hd[f], acc);
+                red[wave][r][lane] = acc;
+            }
+            return ok;
+        };
+        auto over_ha = [&](int t, floatx4 (*red)[4][64]) __attribute__((always_inline)) {
+            const Words x = words.of(t, pl.tile_bytes);
+            uint4 ha[4];
+            const bool ok = x.take<4, B_FRAG, NAP>(O_HA + b * B_H, wave, off_hp(col, g), s < pl.rem[t * 16 + col], ha);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int f = 0; f < 4; ++f) acc = mfma_frag<h16_t>(r < 3 || f == 0 ? w[r][f] : s_w[(f - 1) * 64], ha[f], acc);
+                red[wave][r][lane] = acc;
+            }
+            return ok;
+        };
+        auto sum = [&](floatx4 (*red)[4][64]) __attribute__((always_inline)) {
+            floatx4 v = red[0][er][lane];
+#pragma unroll
+            for (int k = 1; k < NW; ++k) v += red[k][er][lane];
+            return v;
+        };
+        if constexpr (MULTI) {
+            for (int i = 0; i < 2 * pl.n_tiles; ++i) {
+                const int t = i < pl.n_tiles ? i : i - pl.n_tiles;
+                floatx4 (*red)[4][64] = i & 1 ? red1 : red0;
+                ps.sync(i < pl.n_tiles ? over_hd(t, red) : over_ha(t, red));
+                const floatx4 v = sum(red);
+                if (ps.bad()) return give_up(d, pl, s);
+                if (wave < 4) s_pre[(2 * t + (i < pl.n_tiles ? 0 : 1)) * 256] = v;
+                // (h_att has come: see the top of the file)
+                if (i >= pl.n_tiles && wave < 4 && !(g & 1) && s < pl.rem[t * 16 + col])
+                    words.of(t, pl.tile_bytes).empty(hd_off, O_HD + b_next * B_H + j * (B_FRAG / 2));
+            }
+        } else {
+            bool ok = over_hd(0, red0);
+            ok = over_ha(0, red1) && ok;
+            ps.sync(ok);
+            pre4 = sum(red0);
+            pre4b = sum(red1);
+            if (ps.bad()) return give_up(d, pl, s);
         }
-        uint4 ha[4];
-        ok = x.take<4, B_FRAG, 8>(O_HA + b * B_H, wave, off_hp(col, g), on, ha) && ok;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int f = 0; f < 4; ++f) acc = mfma_frag<h16_t>(r < 3 || f == 0 ? w[r][f] : s_w[(f - 1) * 64], ha[f], acc);
-            red_ha[wave][r][lane] = acc;
-        }
-        ps.sync(ok);
-        floatx4 pre4 = red_hd[0][er][lane], pre4b = red_ha[0][er][lane];
-#pragma unroll
-        for (int k = 1; k < NW; ++k) pre4 += red_hd[k][er][lane];
-#pragma unroll
-        for (int k = 1; k < NW; ++k) pre4b += red_ha[k][er][lane];
-        if (ps.bad()) return give_up(d, s, rem);
 
-        if (wave < 4 && on && !(g & 1)) x.empty(hd_off, O_HD + b_next * B_H + j * (B_FRAG / 2));
-        uint4 ab[2];
-        ok = x.take<2, 64>(O_A + b * B_A, wave, off_a(col, g), on, ab);
-        stores_done();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mfma_frag<h16_t>(w[r][4], ab[0], acc);
-            acc = mfma_frag<h16_t>(w[r][5], ab[1], acc);
-            red_a[wave][r][lane] = acc;
+        // (several tiles: asked for ahead, as in the attention LSTM)
+        u32x4_t a_next[2];
+        float c_next = c;
+        auto ask = [&](int t) __attribute__((always_inline)) {
+            words.of(t, pl.tile_bytes).ahead<2, 64>(O_A + b * B_A, wave, off_a(col, g), a_next);
+            c_next = c_g[t * C_TILE];
+        };
+        if constexpr (MULTI) {
+            ask(0);
+            stores_done();
         }
-        ps.sync(ok);
-        floatx4 g4 = bias4;
+        for (int t = 0; t < (MULTI ? pl.n_tiles : 1); ++t) {
+            const Words x = words.of(t, pl.tile_bytes);
+            const int rem = pl.rem[t * 16 + col];
+            const bool on = s < rem;
+            floatx4 (*red)[4][64] = !MULTI ? red2 : t & 1 ? red1 : red0;
+            if constexpr (MULTI) c = c_next;
+            else if (wave < 4 && on && !(g & 1)) x.empty(hd_off, O_HD + b_next * B_H + j * (B_FRAG / 2));
+            uint4 ab[2];
+            bool ok;
+            if constexpr (MULTI) {
+                ok = x.take_rest<2, 64>(O_A + b * B_A, wave, off_a(col, g), on, a_next, ab);
+                ask(min(t + 1, pl.n_tiles - 1));
+            } else {
+                ok = x.take<2, 64>(O_A + b * B_A, wave, off_a(col, g), on, ab);
+                stores_done();
+            }
 #pragma unroll
-        for (int k = 0; k < NW; ++k) g4 += red_a[k][er][lane];
-        g4 += pre4;
-        g4 += pre4b;
-        float c_new = c, hf;
-        cell(g4, c_new, hf);
-        const h16_t h = from_float<h16_t>(hf);
-        if (ps.bad()) return give_up(d, s, rem);
-        // (waves 4 .. 7 form the same cells and store nothing)
-        {
+            for (int r = 0; r < 4; ++r) {
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+                acc = mfma_frag<h16_t>(w[r][4], ab[0], acc);
+                acc = mfma_frag<h16_t>(w[r][5], ab[1], acc);
+                red[wave][r][lane] = acc;
+            }
+            ps.sync(ok);
+            floatx4 g4 = bias4;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) g4 += red[k][er][lane];
+            if constexpr (MULTI) {
+                pre4 = s_pre[(2 * t) * 256 - (wave & 4) * 64];
+                pre4b = s_pre[(2 * t + 1) * 256 - (wave & 4) * 64];
+            }
+            g4 += pre4;
+            g4 += pre4b;
+            float c_new = c, hf;
+            cell(g4, c_new, hf);
+            const h16_t h = from_float<h16_t>(hf);
+            if (ps.bad()) return give_up(d, pl, s);
+            // (waves 4 .. 7 form the same cells and store nothing)
             // units 0, 1 and 2, 3 of a column in one word: the lanes of odd units hand theirs to the lanes before them
             const auto sw = __builtin_amdgcn_permlane16_swap((unsigned)h.bits, (unsigned)h.bits, false, false);
+            if constexpr (MULTI) stores_done();
             if (wave < 4 && on && !(g & 1)) x.put(sw[0] | sw[1] << 16, hd_off, O_HD + b * B_H + j * (B_FRAG / 2));
+            const bool last = s + 1 == min(rem, n_steps);
+            if (on) c = c_new;
+            if (wave < 4 && (MULTI ? on : last)) c_g[t * C_TILE] = c;
+            if (wave < 4 && last)
+                reinterpret_cast<h16_t*>(d.xdec[cur ^ ((s + 1) & 1)])[xoff<h16_t>(NK_D, t * 16 + col, XD_HD + unit)] = h;
         }
-        if (on) c = c_new;
-        if (wave < 4 && s + 1 == min(rem, n_steps)) {
-            d.c_dec[(size_t)col * HID + unit] = c;
-            reinterpret_cast<h16_t*>(d.xdec[cur ^ ((s + 1) & 1)])[xoff<h16_t>(NK_D, col, XD_HD + unit)] = h;
-        }
+        // (an odd number of tiles ends on the buffer that the next step begins with; the sums over h above end on the other one)
+        if (MULTI && (pl.n_tiles & 1)) lds_barrier();
         b_before = b;
         b = b_next;
         b_next = next3(b);
@@ -408,18 +562,18 @@ __device__ __forceinline__ void seg_dec(const DevPtrs& d, const Words& x, int cu
 }
 
 // ---------------------------------------------------------------- one row tile of the projection
-__device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, int n_slots, int n_steps, int r, char* lds, Phases ps)
+__device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, const Pool& pl, int tile, int r, char* lds, Phases ps)
 {
     const int wave = wave_id(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     float (*part)[NW][4][P_LD] = reinterpret_cast<float (*)[NW][4][P_LD]>(lds);  // [sixth of K][wave][element of the accumulator][lane]
     uint4 w[6];
 #pragma unroll
     for (int kp = 0; kp < 6; ++kp) w[kp] = reinterpret_cast<const uint4*>(d.Wmel)[((size_t)r * NK_P + kp * NW + wave) * 64 + lane];
-    const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
+    const int rem = pl.rem[tile * 16 + col];
     // in the reduction: wave = four columns, thread = one of them and one of 16 rows
     const int my_col = (4 * wave + g) & 15, row16 = lane & 15, row = 16 * r + row16;
     const int el = row16 & 3, at = my_col + 16 * (row16 >> 2), m_off = (my_col * 16 + row16) * 4, m_buf = O_M + r * (SEG_SLOTS * 64);
-    const int my_rem = wave < 4 && row < N_PROJ && my_col < n_slots && d.live[my_col] && !d.done[my_col] ? d.n_steps[my_col] - d.t[my_col] : 0;
+    const int my_rem = wave < 4 && row < N_PROJ ? pl.rem[tile * 16 + my_col] : 0;
     const float bias = d.bmel[min(row, N_PROJ - 1)];
     auto product = [&](int kp, const uint4& b) __attribute__((always_inline)) {
         const floatx4 p = mfma_frag<h16_t>(w[kp], b, floatx4{0.f, 0.f, 0.f, 0.f});
@@ -434,7 +588,7 @@ __device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, int n
         return __uint_as_float((__float_as_uint(v) + 8u) & ~15u);
     };
     int b = 0, b_next = 1;
-    for (int s = 0; s < n_steps; ++s) {
+    for (int s = 0; s < pl.n_steps; ++s) {
         const bool on = s < rem;
         uint4 ab[2], hd[4];
         bool ok = x.take<2, 64, 8>(O_A + b * B_A, wave, off_a(col, g), on, ab);
@@ -443,7 +597,7 @@ __device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, int n
         product(5, ab[1]);
         ps.sync(ok);
         const float v4 = sixth(4), v5 = sixth(5);
-        if (ps.bad()) return give_up(d, s, rem);
+        if (ps.bad()) return give_up(d, pl, s);
         ok = x.take<4, B_FRAG>(O_HD + b * B_H, wave, off_hd(col, g), on, hd);
         stores_done();
 #pragma unroll
@@ -454,7 +608,7 @@ __device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, int n
         for (int kp = 1; kp < 4; ++kp) v += sixth(kp);
         v += v4;
         v += v5;
-        if (ps.bad()) return give_up(d, s, rem);
+        if (ps.bad()) return give_up(d, pl, s);
         if (s < my_rem) x.put(__float_as_uint(v), m_off, m_buf + b * B_M);
         b = b_next;
         b_next = next3(b);
@@ -462,9 +616,10 @@ __device__ __forceinline__ void seg_rows(const DevPtrs& d, const Words& x, int n
 }
 
 // ---------------------------------------------------------------- frame, prenet, books
-__device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int cur, int n_slots, int n_steps, char* lds, Phases ps)
+__device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, const Pool& pl, int tile, char* lds, Phases ps)
 {
     const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63, col = lane & 15, g = lane >> 4;
+    const int cur = pl.cur, n_steps = pl.n_steps, slot0 = tile * 16;
     uint16_t (*s_mel)[MEL_LD] = reinterpret_cast<uint16_t (*)[MEL_LD]>(lds);
     uint16_t (*s_hid)[HID_LD] = reinterpret_cast<uint16_t (*)[HID_LD]>(lds + 16 * MEL_LD * 2);
     constexpr int NK3 = MEL_ROWS / KB, NK4 = PRENET / KB;
@@ -477,15 +632,15 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int c
 #pragma unroll
         for (int f = 0; f < NK4; ++f) a4[m][f] = reinterpret_cast<const uint4*>(d.Wp2)[((size_t)mt * NK4 + f) * 64 + lane];
     }
-    const int rem = col < n_slots && d.live[col] && !d.done[col] ? d.n_steps[col] - d.t[col] : 0;
+    const int rem = pl.rem[slot0 + col];
     // as a collector of the frame: thread = four rows of one slot
     constexpr int VEC = MEL_ROWS / 4;
     const int m_slot = min(tid / VEC, SEG_SLOTS - 1), m_row = tid % VEC * 4;
-    const int m_rem = tid < SEG_SLOTS * VEC && m_row < N_PROJ && m_slot < n_slots && d.live[m_slot] && !d.done[m_slot] ? d.n_steps[m_slot] - d.t[m_slot] : 0;
-    const int m_t0 = d.t[m_slot], m_off = m_row / 16 * (SEG_SLOTS * 64) + m_slot * 64 + m_row % 16 * 4;     // [row tile][slot][16 rows]
+    const int m_rem = tid < SEG_SLOTS * VEC && m_row < N_PROJ ? pl.rem[slot0 + m_slot] : 0;
+    const int m_t0 = d.t[slot0 + m_slot], m_off = m_row / 16 * (SEG_SLOTS * 64) + m_slot * 64 + m_row % 16 * 4;     // [row tile][slot][16 rows]
     // the launches after this one read the half of this pair that belongs to their parity: it must not fall behind
     const int end_all = cur ^ (n_steps & 1);
-    if (tid == 0 && end_all != cur) d.wg_seq[end_all] = d.wg_seq[cur];
+    if (tile == 0 && tid == 0 && end_all != cur) d.wg_seq[end_all] = d.wg_seq[cur];
     int b = 0, b_next = 1;
     for (int s = 0; s < n_steps; ++s) {
         const bool on = s < rem, m_on = s < m_rem;
@@ -516,7 +671,7 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int c
                     make_uint2(pack2<h16_t>(fmaxf(acc[0], 0.f), fmaxf(acc[1], 0.f)), pack2<h16_t>(fmaxf(acc[2], 0.f), fmaxf(acc[3], 0.f)));
             }
         }
-        if (ps.bad()) return give_up(d, s, rem);
+        if (ps.bad()) return give_up(d, pl, s);
         lds_barrier();
         {
             uint4 bh[NK4];
@@ -536,21 +691,21 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int c
                 if (s + 1 < min(rem, n_steps)) {
                     x.put2(lo, hi, col * 64 + m * 32 + g * 8, O_P + b * B_P + wave * B_FRAG);
                 } else if (on) {
-                    h16_t* dst = reinterpret_cast<h16_t*>(d.xatt[cur ^ ((s + 1) & 1)]) + xoff<h16_t>(NK_A, col, XA_P + 16 * mt + 4 * g);
+                    h16_t* dst = reinterpret_cast<h16_t*>(d.xatt[cur ^ ((s + 1) & 1)]) + xoff<h16_t>(NK_A, slot0 + col, XA_P + 16 * mt + 4 * g);
                     *reinterpret_cast<uint2*>(dst) = make_uint2(lo, hi);
                 }
             }
         }
         // the books, while the others go on
         if (m_on) {
-            const size_t at = (size_t)m_slot * d.max_steps + m_t0 + s;
+            const size_t at = (size_t)(slot0 + m_slot) * d.max_steps + m_t0 + s;
             if (m_row < N_MEL) {
                 *reinterpret_cast<u32x4_t*>(d.mel_ring + at * N_MEL + m_row) = w;
-                *reinterpret_cast<u32x4_t*>(d.m_last + m_slot * N_MEL + m_row) = w;
+                *reinterpret_cast<u32x4_t*>(d.m_last + (slot0 + m_slot) * N_MEL + m_row) = w;
             } else {
                 d.stop_ring[at] = __uint_as_float(w.x);
-                d.t[m_slot] = m_t0 + s + 1;
-                if (s + 1 == m_rem) d.done[m_slot] = 1;
+                d.t[slot0 + m_slot] = m_t0 + s + 1;
+                if (s + 1 == m_rem) d.done[slot0 + m_slot] = 1;
             }
         }
         b = b_next;
@@ -558,10 +713,12 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, int c
     }
 }
 
-// ---------------------------------------------------------------- a quarter of one request's attention
-__device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cur, int n_steps, int slot, int sp, char* lds, Phases ps)
+// ---------------------------------------------------------------- one request's attention, shared by S workgroups
+template <int S>
+__device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, const Pool& pl, int slot, int sp, char* lds, Phases ps)
 {
-    constexpr int S = 4, FS = ENC / S, LPR = 64 / S;
+    constexpr int FS = ENC / S, LPR = 64 / S, NA = 4 / S;                  // columns, lanes per row, position classes per lane
+    const int cur = pl.cur, n_steps = pl.n_steps, in_tile = slot & 15;
     const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63, jl = lane & 15, g = lane >> 4;
     float (*s_ctx)[ENC] = reinterpret_cast<float (*)[ENC]>(lds);
     float (*s_u)[U_PAD] = reinterpret_cast<float (*)[U_PAD]>(lds + NW * ENC * 4);
@@ -570,10 +727,9 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
     float* s_v = s_q + ATT;
     float* s_red = s_v + ATT;
     float (*s_pair)[ATT] = reinterpret_cast<float (*)[ATT]>(s_red + 2 * NW);
-    if (!d.live[slot] || d.done[slot]) return;
-    const int rem = __builtin_amdgcn_readfirstlane(d.n_steps[slot] - d.t[slot]), L = __builtin_amdgcn_readfirstlane(d.L[slot]);
+    const int rem = __builtin_amdgcn_readfirstlane(pl.rem[slot]), L = __builtin_amdgcn_readfirstlane(d.L[slot]);
+    if (rem == 0) return;
     const int steps = min(rem, n_steps), ntile = (L + 15) >> 4;
-    const int my_rem = (int)threadIdx.x == slot ? rem : 0;                 // for give_up
     const int ML = d.max_enc_len;
     const bf16_t* PMs = reinterpret_cast<const bf16_t*>(d.PM) + (size_t)slot * ML * ATT + 32 * g;
     LsaTile<h16_t> tile;
@@ -585,22 +741,26 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
 #pragma unroll
         for (int i = 0; i < 8; ++i) tile.wA[i] = wf[i * 64 + lane];
     }
-    // the wave's first tile of positions is its only one up to 512 of them: its rows of the processed memory stay in registers
-    u32x4_t pm0[4];
-    {
-        const bf16_t* pm = PMs + (size_t)min((sp + S * wave) * 16 + jl, L - 1) * ATT;
+    // the wave's rows of the processed memory stay in registers: of its tiles of positions up to 512 of them
+    constexpr int NPM = S == 4 ? 1 : 2;
+    u32x4_t pm0[NPM][4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) pm0[i] = *reinterpret_cast<const u32x4_t*>(pm + 8 * i);
+    for (int q = 0; q < NPM; ++q) {
+        const bf16_t* pm = PMs + (size_t)min((sp + S * (wave + q * NW)) * 16 + jl, L - 1) * ATT;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pm0[q][i] = *reinterpret_cast<const u32x4_t*>(pm + 8 * i);
     }
-    // and so do the rows of the memory (this workgroup's columns): 16 passes of 32 positions
-    constexpr int NP = 16;
-    const int xw = wave * 4 + lane / LPR;                                  // this lane's position class
+    // and so do the rows of the memory (this workgroup's columns): NP passes of 32 positions
+    constexpr int NP = S == 4 ? 16 : S == 2 ? 10 : 4;
+    const int xw = wave * 4 + lane / LPR * NA;                             // this lane's first position class
     const bf16_t* Fslot = reinterpret_cast<const bf16_t*>(d.Fmem) + (size_t)slot * ML * ENC;
     const __amdgpu_buffer_rsrc_t f_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Fslot), 0, L * ENC * 2, BUFFER_RSRC_RAW);
     const int f_col = (sp * FS + (lane % LPR) * 8) * 2;
-    u32x4_t rows[NP];
+    u32x4_t rows[NP][NA];
 #pragma unroll
-    for (int pp = 0; pp < NP; ++pp) rows[pp] = __builtin_amdgcn_raw_buffer_load_b128(f_rsrc, (pp * 32 + xw) * ENC * 2 + f_col, 0, 0);
+    for (int pp = 0; pp < NP; ++pp)
+#pragma unroll
+        for (int n = 0; n < NA; ++n) rows[pp][n] = __builtin_amdgcn_raw_buffer_load_b128(f_rsrc, (pp * 32 + xw + n) * ENC * 2 + f_col, 0, 0);
     for (int i = tid; i < ntile * 16 + 32; i += NT) {
         const bool in = i >= LOC_PAD && i < L + LOC_PAD;
         const int jc = min(max(i - LOC_PAD, 0), L - 1);
@@ -627,30 +787,32 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
     bound *= 0.5f;
     const bool fast_softmax = bound <= 30.f;
 
-    // the energies of one workgroup's tiles lie together: [4 workgroups][its tiles][16 positions]
+    // the energies of one workgroup's tiles lie together: [workgroup][its tiles][16 positions]
     const int e_slot = segment_energy_bytes(ML);
-    auto e_off = [&](int j) { return (j >> 4 & 3) * (e_slot / 4) + (j >> 6) * 64 + (j & 15) * 4; };
+    auto e_off = [&](int j) { return (j >> 4) % S * (e_slot / S) + (j >> 4) / S * 64 + (j & 15) * 4; };
     // this thread's share of the query: four rows of two of its 32 partial products
-    const int q_off = (tid >> 5) * 2 * ATT * 4 + (tid & 31) * 16, b_e = SEG_SLOTS * e_slot, e_at = O_E + slot * e_slot;
-    const int k_a = sp * FS + tid, a_off = slot * (ENC * 2) + k_a * 2;
+    const int q_off = (tid >> 5) * 2 * ATT * 4 + (tid & 31) * 16, b_e = SEG_SLOTS * e_slot, e_at = O_E + in_tile * e_slot;
+    const int k_a = sp * FS + tid, a_off = in_tile * (ENC * 2) + k_a * 2;
     int b = 0, b_next = 1;
     for (int s = 0; s < steps; ++s) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) keep(pm0[i]);
+        for (int i = 0; i < 4 * NPM; ++i) keep(pm0[i >> 2][i & 3]);
 #pragma unroll
-        for (int i = 0; i < NP; ++i) keep(rows[i]);
+        for (int i = 0; i < NP * NA; ++i) keep(rows[i / NA][i % NA]);
         for (int tt = sp + S * wave; tt < ntile; tt += S * NW)
             if (g == 0 && tt * 16 + jl < L) x.empty(e_off(tt * 16 + jl), e_at + b_next * b_e);
         if (tid < FS && !(tid & 1)) x.empty(a_off, O_A + b_next * B_A);
         // the location features do not wait for the query
-        const uint4 bl0 = tile.loc(s_u[0], s_u[1], min((sp + S * wave) * 16, (ntile - 1) * 16) + jl, g);
+        uint4 bl0[NPM];
+#pragma unroll
+        for (int q = 0; q < NPM; ++q) bl0[q] = tile.loc(s_u[0], s_u[1], min((sp + S * (wave + q * NW)) * 16, (ntile - 1) * 16) + jl, g);
         {
             u32x4_t w0, w1;
             bool in = false;
             for (int spin = 0; spin < x.polls && !in; ++spin) {
                 Words::again();
-                w0 = x.look4(q_off, O_Q + b * B_Q + slot * B_QS);
-                w1 = x.look4(q_off + ATT * 4, O_Q + b * B_Q + slot * B_QS);
+                w0 = x.look4(q_off, O_Q + b * B_Q + in_tile * B_QS);
+                w1 = x.look4(q_off + ATT * 4, O_Q + b * B_Q + in_tile * B_QS);
                 in = Words::full(w0) && Words::full(w1);
             }
             stores_done();
@@ -670,21 +832,10 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
             }
             s_q[tid] = (sq[0] + sq[1]) + (sq[2] + sq[3]);
         }
-        if (ps.bad()) return give_up(d, s, my_rem);
+        if (ps.bad()) return lose_one(d, slot);
         lds_barrier();
-        for (int tt = sp + S * wave; tt < ntile; tt += S * NW) {
+        auto energies = [&](int tt, const uint4 (&pmc)[4], const uint4& bl) __attribute__((always_inline)) {
             const int j = tt * 16 + jl;
-            const bool first = tt < S * NW;
-            uint4 pmc[4];
-            if (first) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) pmc[i] = as_uint4(pm0[i]);
-            } else {
-                const bf16_t* pm = PMs + (size_t)min(j, L - 1) * ATT;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) pmc[i] = *reinterpret_cast<const uint4*>(pm + 8 * i);
-            }
-            const uint4 bl = first ? bl0 : tile.loc(s_u[0], s_u[1], j, g);
             float e = vsum;
 #pragma unroll
             for (int at = 0; at < 8; ++at) {
@@ -704,6 +855,19 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
                 s_e[j] = e;
                 x.put(__float_as_uint(e), e_off(j), e_at + b * b_e);
             }
+        };
+#pragma unroll
+        for (int q = 0; q < NPM; ++q) {
+            const int tt = sp + S * (wave + q * NW);
+            const uint4 pmc[4] = {as_uint4(pm0[q][0]), as_uint4(pm0[q][1]), as_uint4(pm0[q][2]), as_uint4(pm0[q][3])};
+            if (tt < ntile) energies(tt, pmc, bl0[q]);
+        }
+        for (int tt = sp + S * (wave + NPM * NW); tt < ntile; tt += S * NW) {      // texts of more than 512 positions: from memory
+            const bf16_t* pm = PMs + (size_t)min(tt * 16 + jl, L - 1) * ATT;
+            uint4 pmc[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) pmc[i] = *reinterpret_cast<const uint4*>(pm + 8 * i);
+            energies(tt, pmc, tile.loc(s_u[0], s_u[1], tt * 16 + jl, g));
         }
         bool ok = true;
         for (int i = tid; i < L; i += NT) {
@@ -727,7 +891,7 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
         }
         psum = wave_sum_fast(psum);
         if (lane == 0) s_red[NW + wave] = psum;                            // read behind the barrier of the context's sums
-        if (ps.bad()) return give_up(d, s, my_rem);
+        if (ps.bad()) return lose_one(d, slot);
         if (!fast_softmax) {
             float mx = -INFINITY;
             for (int i = tid; i < L; i += NT) mx = fmaxf(mx, s_e[i]);
@@ -748,31 +912,44 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
             lds_barrier();
         }
 
-        float acc[8];
+        float acc[NA][8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-        auto add = [&](int px, const uint4& r) __attribute__((always_inline)) {
+        for (int n = 0; n < NA; ++n)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[n][i] = 0.f;
+        auto add = [&](int n, int px, const uint4& r) __attribute__((always_inline)) {
             const float w = s_e[px];
             float fv[8];
             Vec16<bf16_t>::unpack(r, fv);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] = fmaf(w, fv[i], acc[i]);
+            for (int i = 0; i < 8; ++i) acc[n][i] = fmaf(w, fv[i], acc[n][i]);
         };
 #pragma unroll
         for (int pp = 0; pp < NP; ++pp) {
             if (pp * 32 >= L) break;
-            add(pp * 32 + xw, as_uint4(rows[pp]));
+#pragma unroll
+            for (int n = 0; n < NA; ++n) add(n, pp * 32 + xw + n, as_uint4(rows[pp][n]));
         }
-        for (int x0 = 32 * NP; x0 < L; x0 += 32 * 4) {                     // texts of more than 512 positions: from memory
-            uint4 more[4];
+        for (int x0 = 32 * NP; x0 < L; x0 += 32 * 4 / NA) {                // longer texts: from memory
+            uint4 more[4 / NA][NA];
 #pragma unroll
-            for (int pp = 0; pp < 4; ++pp) more[pp] = buffer_load16(f_rsrc, (x0 + pp * 32 + xw) * ENC * 2 + f_col);
+            for (int pp = 0; pp < 4 / NA; ++pp)
 #pragma unroll
-            for (int pp = 0; pp < 4; ++pp)
-                if (x0 + pp * 32 < L) add(x0 + pp * 32 + xw, more[pp]);
+                for (int n = 0; n < NA; ++n) more[pp][n] = buffer_load16(f_rsrc, (x0 + pp * 32 + xw + n) * ENC * 2 + f_col);
+#pragma unroll
+            for (int pp = 0; pp < 4 / NA; ++pp)
+                if (x0 + pp * 32 < L)
+#pragma unroll
+                    for (int n = 0; n < NA; ++n) add(n, x0 + pp * 32 + xw + n, more[pp][n]);
         }
+        // (classes held by one lane are paired here)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s_ctx[wave][lane * 8 + i] = acc[i];
+        for (int i = 0; i < 8; ++i) {
+            float t = acc[0][i];
+            if constexpr (NA >= 2) t = acc[0][i] + acc[1][i];
+            if constexpr (NA == 4) t = t + (acc[2][i] + acc[3][i]);
+            s_ctx[wave][lane * 8 + i] = t;
+        }
         lds_barrier();
         float sum = 0.f;
 #pragma unroll
@@ -781,8 +958,12 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
         if (tid < FS) {
             float c = 0.f;
 #pragma unroll
-            for (int w = 0; w < NW; ++w)
-                c += (s_ctx[w][tid] + s_ctx[w][LPR * 8 + tid]) + (s_ctx[w][2 * LPR * 8 + tid] + s_ctx[w][3 * LPR * 8 + tid]);
+            for (int w = 0; w < NW; ++w) {
+                float t = s_ctx[w][tid];
+                if constexpr (S >= 2) t += s_ctx[w][LPR * 8 + tid];
+                if constexpr (S == 4) t += s_ctx[w][2 * LPR * 8 + tid] + s_ctx[w][3 * LPR * 8 + tid];
+                c += t;
+            }
             const h16_t a = from_float<h16_t>(c * inv);
             const unsigned lo = a.bits, hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)lo, 0xB1, 0xf, 0xf, false);      // the neighbour's (lanes 1, 0, 3, 2)
             if (!(tid & 1)) x.put(lo | hi << 16, a_off, O_A + b * B_A);
@@ -809,38 +990,62 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, int cu
     }
 }
 
-__global__ __launch_bounds__(NT) void k_segment(DevPtrs d, int cur, int n_slots, int n_steps, char* words, char* words_next, int set_bytes)
+// Which workgroup does what.  Readers of the same words sit together, since an XCD's L2 takes a line that has been stored to from memory
+// once for all of them: ATT and DEC fill XCDs 0 .. 3 in order, LSA and each tile's projection lie on 4 .. 7.  And at least eight CUs of every XCD
+// stay free for work on other streams, whose launches are dealt over all XCDs: with XCDs filled to the last CU a vocoder beside the
+// decoder waited for the end of a segment with each of its launches.  Against DEC and LSA on all XCDs: 1 request 9.9 -> 9.7 us a step,
+// 16: 12.7 -> 11.2; with all of ATT on one XCD and four or two LSA per request of two and three tiles, no CU of four XCDs free: 32 requests
+// 13.8 -> 13.4, 48: 17.7 -> 16.3.
+constexpr int SEG_XCD_WGS = 24;                             // of ATT and DEC on an XCD; LSA, at most 16, and ROWS and LEAD fill the others as far
+template <bool MULTI, int S>
+__global__ __launch_bounds__(NT) void k_segment(DevPtrs d, int cur, int n_slots, int n_steps, char* words, char* words_next, int tile_bytes, int empty_bytes)
 {
     __shared__ __attribute__((aligned(16))) char lds[S_MAX];
-    __shared__ int s_failed;
+    __shared__ int s_failed, s_rem[SEG_TILES * 16];
+    const int n_tiles = (n_slots + 15) / 16;
     if (threadIdx.x == 0) s_failed = 0x7fffffff;
-    for (int at = (blockIdx.x * NT + threadIdx.x) * 16; at < set_bytes; at += gridDim.x * NT * 16)
+    if (threadIdx.x < SEG_TILES * 16) {
+        const int sl = threadIdx.x;
+        s_rem[sl] = sl < n_slots && d.live[sl] && !d.done[sl] ? d.n_steps[sl] - d.t[sl] : 0;
+    }
+    for (int at = (blockIdx.x * NT + threadIdx.x) * 16; at < empty_bytes; at += gridDim.x * NT * 16)
         *reinterpret_cast<u32x4_t*>(words_next + at) = u32x4_t{EMPTY, EMPTY, EMPTY, EMPTY};
     __syncthreads();
     const Phases ps = {&s_failed};
-    const Words x = {words, set_bytes, d.wait_polls};
+    const Pool pl = {cur, n_steps, n_tiles, tile_bytes, s_rem};
+    const Words x = {words, tile_bytes, d.wait_polls};
     const int xcd = blockIdx.x & 7, i = blockIdx.x >> 3;
-    if (i >= 16) {
-        const int slot = ((i - 16) >> 2) * 8 + xcd;
-        if (slot < n_slots) seg_lsa(d, x, cur, n_steps, slot, (i - 16) & 3, lds, ps);
-    } else if (i >= 8) {
-        seg_dec(d, x, cur, n_slots, n_steps, (i - 8) * 8 + xcd, lds, ps);
-    } else if (xcd < 4) {
-        seg_att(d, x, cur, n_slots, n_steps, i * 4 + xcd, lds, ps);
-    } else if (xcd == 4) {
-        if (i < 6) seg_rows(d, x, n_slots, n_steps, i, lds, ps);
-        else if (i == 6) seg_lead(d, x, cur, n_slots, n_steps, lds, ps);
+    if (xcd < 4) {
+        const int k = xcd * SEG_XCD_WGS + i;
+        if (i >= SEG_XCD_WGS) return;
+        if (k < 32) seg_att<MULTI>(d, x, pl, k, lds, ps);
+        else seg_dec<MULTI>(d, x, pl, k - 32, lds, ps);
+    } else if (i < 16) {
+        const int slot = i / S * 4 + xcd - 4;
+        if (slot < n_slots) seg_lsa<S>(d, x.of(slot >> 4, tile_bytes), pl, slot, i % S, lds, ps);
+    } else if (xcd - 4 < n_tiles && i < 23) {
+        const Words w = x.of(xcd - 4, tile_bytes);
+        if (i < 22) seg_rows(d, w, pl, xcd - 4, i - 16, lds, ps);
+        else seg_lead(d, w, pl, xcd - 4, lds, ps);
     }
 }
 
 }  // namespace
 
-hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, hipStream_t s)
+hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, hipStream_t s)
 {
-    if (!d.seg_x || n_slots < 1 || n_slots > SEG_SLOTS || n_steps < 1 || (set & ~1) || d.stop_threshold >= 0.f) return hipErrorInvalidValue;
-    const size_t bytes = segment_set_bytes(d.max_enc_len);
+    const int n_tiles = (n_slots + 15) / 16;
+    if (!d.seg_x || n_slots < 1 || n_slots > d.seg_slots || n_steps < 1 || (set & ~1) || empty_tiles < 0 || empty_tiles * SEG_SLOTS > d.seg_slots || d.stop_threshold >= 0.f)
+        return hipErrorInvalidValue;
+    const size_t tile_bytes = segment_tile_bytes(d.max_enc_len), set_bytes = d.seg_slots / SEG_SLOTS * tile_bytes;
     char* words = static_cast<char*>(d.seg_x);
-    hipLaunchKernelGGL(k_segment, dim3(8 * (16 + 4 * ((n_slots + 7) / 8))), dim3(NT), 0, s, d, cur, n_slots, n_steps, words + set * bytes, words + (set ^ 1) * bytes, (int)bytes);
+    static_assert(4 * SEG_XCD_WGS == 32 + 64 && SEG_TILES <= 4, "ATT and DEC; a projection per XCD");
+    static_assert(16 * 4 >= 4 * SEG_SLOTS && 16 * 4 >= 2 * 2 * SEG_SLOTS && 16 * 4 >= SEG_TILES * SEG_SLOTS, "LSA: four, two or one per slot");
+#define SEG_ARGS dim3(8 * SEG_XCD_WGS), dim3(NT), 0, s, d, cur, n_slots, n_steps, words + set * set_bytes, words + (set ^ 1) * set_bytes, (int)tile_bytes, (int)(empty_tiles * tile_bytes)
+    if (n_tiles == 1) hipLaunchKernelGGL((k_segment<false, 4>), SEG_ARGS);
+    else if (n_tiles == 2) hipLaunchKernelGGL((k_segment<true, 2>), SEG_ARGS);
+    else hipLaunchKernelGGL((k_segment<true, 1>), SEG_ARGS);
+#undef SEG_ARGS
     return hipGetLastError();
 }
 

@@ -158,7 +158,7 @@ Layout make_layout(const tts_config& c)
     l.p_x = a.take((pre_dec_hatt_for(c) ? S / 16 : 0) * (size_t)(PRENET / 32) * 64 * 4 * 8);
     l.pre_x = a.take((pre_dec_hatt_for(c) ? S / 16 : 0) * (size_t)(HID / 4) * 64 * 4 * 8);
     l.wg_seq = a.take(2 * 4);
-    l.seg_x = a.take(pre_dec_hatt_for(c) ? 2 * segment_set_bytes(c.max_enc_len) : 0);
+    l.seg_x = a.take(pre_dec_hatt_for(c) ? segment_bytes(c.max_pool, c.max_enc_len) : 0);
     l.seg_bytes = a.off - l.seg_x;
     l.stage = a.take(ML * ENC * 4);
     l.total = a.off;
@@ -262,7 +262,8 @@ struct tts_pool {
     int stage_regions = 0, stage_frames = 0;
     struct Staged { int64_t id = -1; int first = 0, count = 0; };
     std::vector<Staged> staged;   // per region: which frames of which request it holds (frames never change once made)
-    int seg_set = 0;              // which set of words the next segment's launch uses
+    int seg_set = 0;              // which set of words the next segment's launch uses ...
+    int seg_used = 0;             // ... and how many tiles of the other one the launch before used
     int n_slots_padded = 0;       // slots the arena holds (max_pool rounded up to whole tiles)
     std::vector<int64_t> lost_ids; // requests the device ended early that tts_pool_sync has not reported yet
 };
@@ -421,6 +422,7 @@ extern "C" int tts_pool_create(const tts_config* cfg, const tts_weights* w, void
     d.pre_x = pre_dec_hatt_for(*cfg) ? reinterpret_cast<unsigned long long*>(base + l.pre_x) : nullptr;
     d.wg_seq = reinterpret_cast<unsigned*>(base + l.wg_seq);
     d.seg_x = pre_dec_hatt_for(*cfg) ? base + l.seg_x : nullptr;
+    d.seg_slots = segment_tiles(cfg->max_pool) * SEG_SLOTS;
     // one pinned word the kernels can reach: a projection leader that gives up on its helpers says so here
     {
         hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&p->h_fault), sizeof(int), hipHostMallocMapped);
@@ -658,6 +660,7 @@ static void shape_for(const tts_pool* p, int span, StepLaunch* sl)
     sl->att_tail = 0;
     sl->seg_steps = 0;
     sl->seg_set = 0;
+    sl->seg_empty = 0;
 }
 
 // Step i of `nsteps` consecutive steps of one call: in pools whose last launch can form the next step's attention LSTM
@@ -720,16 +723,16 @@ static int launch_steps(tts_pool* p, int n_active, int nsteps)
     return TTS_OK;
 }
 
-// How many of the next `n` steps run as one launch (segment.hip; 0: they run step by step).  The line is the form's own: one tile
-// of slots, two-byte weights and memory (d.seg_x), frame counts known beforehand.  There it is the faster one at every size, chunks
-// of 40 steps of requests of 165 positions, steps as launches in graphs -> as one launch: 1 request 16.8 -> 9.7 us a step,
-// 4: 17.9 -> 10.0, 8: 18.2 -> 10.7, 12: 18.4 -> 11.4, 16: 18.5 -> 12.1; single steps, back to back, took 28.4 -> 18.5 (1 request) and
-// 28.7 -> 26.4 us (16) before the words lay as they do now.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other
-// streams gets the compute units at intervals.
+// How many of the next `n` steps run as one launch (segment.hip; 0: they run step by step).  The line is the form's own: two-byte weights
+// and memory (d.seg_x), frame counts known beforehand, and the slots up to which it is the faster one.  Chunks of 40 steps of requests
+// of 165 positions, steps as launches in graphs -> as one launch: 1 request 16.8 -> 9.7 us a step, 8: 18.2 -> 10.3, 16: 18.5 -> 11.2,
+// 20: 19.7 -> 13.5, 32: 20.4 -> 13.8, 48: 21.2 -> 17.7; with four tiles, 64 requests, 21.6 -> 21.5.  Single steps, each waited for: 1 request
+// 49 -> 30 us.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other streams that
+// needs every compute unit gets them at intervals.
 static const int MAX_SEGMENT_STEPS = 64;
 static int segment_steps(const tts_pool* p, int n)
 {
-    if (!p->d.seg_x || !p->cfg.use_graph || p->stop_enabled || p->slot_span > SEG_SLOTS) return 0;
+    if (!p->d.seg_x || !p->cfg.use_graph || p->stop_enabled || p->slot_span > p->d.seg_slots) return 0;
     int most = 0;
     for (int sl : p->book->active()) most = std::max(most, p->book->slot(sl).n_steps - p->book->slot(sl).t);
     return std::min({n, most, MAX_SEGMENT_STEPS});
@@ -742,8 +745,10 @@ static int launch_segment_steps(tts_pool* p, int g)
     shape_for(p, p->slot_span, &sl);
     sl.seg_steps = g;
     sl.seg_set = p->seg_set;
+    sl.seg_empty = p->seg_used;
     HIP_TRY(launch_step(p->d, sl, p->parity, p->stream));
     p->seg_set ^= 1;
+    p->seg_used = sl.n_tiles;
     return TTS_OK;
 }
 

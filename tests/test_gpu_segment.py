@@ -1,4 +1,4 @@
-"""Steps as one launch (csrc/segment.hip: two-byte pools whose running requests lie in the first 16 slots) against the same steps
+"""Steps as one launch (csrc/segment.hip: two-byte pools whose running requests lie in the first 48 slots) against the same steps
 as launches of their own (use_graph=False): the same bits, frames and carried state."""
 import numpy as np
 import pytest
@@ -51,18 +51,23 @@ def _same(out, frames):
     ([31 + 40 * i for i in range(8)], [40 - i for i in range(8)], [40]),   # eight slots: one request per XCD
     ([33 + 20 * i for i in range(9)], [12 + i for i in range(9)], [7, 13]),
     ([20 + 9 * i for i in range(16)], [10 + 3 * i for i in range(16)], [20, 35]),
+    ([600, 321, 320, 17] + [30 + 5 * i for i in range(13)], [40] * 17, [1, 39]),   # a second tile: two workgroups a request, 320 positions in registers
+    ([25 + 6 * i for i in range(32)], [8 + i for i in range(32)], [16, 23]),
+    ([300, 129, 128, 257] + [20 + 4 * i for i in range(29)], [5 + i for i in range(33)], [20, 17]),   # a third: one a request, 128 positions
+    ([20 + 5 * i for i in range(48)], [48 - i for i in range(48)], [13, 35]),
 ], ids=lambda v: None)
 def test_segment_equals_steps(lengths, frames, calls, weights_bf16):
     say(f"case: segments of {calls} steps, texts of {lengths}, frames {frames}")
-    _same(_both(weights_bf16, lengths, frames, calls), frames)
+    _same(_both(weights_bf16, lengths, frames, calls, max_pool=16 if len(lengths) <= 16 else 48), frames)
 
 
 def test_segments_between_steps_of_a_larger_pool(weights_bf16):
-    """A 17th request puts the pool's steps beyond one tile; they become segments again when it has ended and the pool is packed."""
-    say("case: 12 requests, ten more for eight steps, segments again")
-    lengths = [20 + 5 * i for i in range(22)]
-    frames = [60] * 12 + [8] * 10
-    _same(_both(weights_bf16, lengths, frames, [15, 8, 37], max_pool=24, max_enc_len=160, later=[1] * 10), frames)
+    """With a 49th request the pool's steps are launches of their own; they become segments again, of fewer tiles, when requests have
+    ended and the pool is packed."""
+    say("case: 12 requests, 40 more for eight steps, ten of them for longer, segments again")
+    lengths = [20 + 2 * i for i in range(52)]
+    frames = [60] * 12 + [20] * 10 + [8] * 30
+    _same(_both(weights_bf16, lengths, frames, [15, 8, 12, 25], max_pool=64, max_enc_len=160, later=[1] * 40), frames)
 
 
 @pytest.mark.parametrize("spoil", [0xFFFFFFFF, 0x7F800000, 0x7FC00000])
