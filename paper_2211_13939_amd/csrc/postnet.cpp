@@ -30,7 +30,7 @@ int c_in_padded(int l) { return l == 0 ? PN_CIN0 : PN_CHANNELS; }
 int c_out_of(int l) { return l == PN_LAYERS - 1 ? PN_COUT_LAST : PN_CHANNELS; }
 
 struct PnLayout {
-    size_t W[PN_LAYERS], b[PN_LAYERS], act[2], cmeta, orow, total;
+    size_t W[PN_LAYERS], b[PN_LAYERS], act[2], cmeta, orow, chain_state, chain, total;
 };
 
 PnLayout layout_of(const tts_postnet_config& c)
@@ -46,6 +46,8 @@ PnLayout layout_of(const tts_postnet_config& c)
     for (int i = 0; i < 2; ++i) l.act[i] = a.take(cols * PN_CHANNELS * ws);
     l.cmeta = a.take(cols * 4);
     l.orow = a.take(cols * 4);
+    l.chain_state = a.take(CHAIN_STATE_BYTES);
+    l.chain = a.take(2 * chain_set_bytes(ws, c.max_columns, PN_LAYERS - 1));
     l.total = a.off;
     return l;
 }
@@ -146,6 +148,7 @@ extern "C" int tts_postnet_create(const tts_postnet_config* cfg, const tts_postn
     }
     if (rc == TTS_OK && hipMemset(base + lay.act[0], 0, lay.total - lay.act[0]) != hipSuccess)
         rc = fail(TTS_E_HIP, "clearing the activation buffers failed");
+    if (rc == TTS_OK && hipMemset(base + lay.chain, 0xff, lay.total - lay.chain) != hipSuccess) rc = fail(TTS_E_HIP, "clearing the words failed");
     if (rc == TTS_OK && (hipEventCreate(&p->ev0) != hipSuccess || hipEventCreate(&p->ev1) != hipSuccess))
         rc = fail(TTS_E_HIP, "hipEventCreate failed");
     if (rc) {
@@ -157,6 +160,9 @@ extern "C" int tts_postnet_create(const tts_postnet_config* cfg, const tts_postn
     p->d.cmeta = (int*)(base + lay.cmeta);
     p->d.orow = (int*)(base + lay.orow);
     p->d.n_mel = cfg->n_mel;
+    p->d.chain_words = base + lay.chain;
+    p->d.chain_state = (int*)(base + lay.chain_state);
+    p->d.chain_set_bytes = (int)chain_set_bytes(bf ? 2 : 4, cfg->max_columns, PN_LAYERS - 1);
     *out = p;
     return TTS_OK;
 }
@@ -179,6 +185,8 @@ static int run_batch(tts_postnet* p, const PostnetPtrs& d, int max_columns, bool
     // the window list travels as kernel arguments, 256 windows at a time; the device expands it into the
     // per-column tables (position inside the window for the zero padding, output row of the column)
     if (timed) HIP_TRY(hipEventRecord(p->ev0, p->stream));
+    // A small call is one launch: the line is the chip's, a workgroup for every compute unit.
+    const bool chain = d.chain_words && n <= PN_META_WINDOWS && n_col <= chain_most_columns(p->cfg.weight_dtype == TTS_DTYPE_BF16 ? 2 : 4);
     int c = 0, r = 0;
     for (int i0 = 0; i0 < n; i0 += PN_META_WINDOWS) {
         PnWindows w;
@@ -192,9 +200,13 @@ static int run_batch(tts_postnet* p, const PostnetPtrs& d, int max_columns, bool
             c += win_len[i];
             r += win_len[i] - keep_from[i];
         }
+        if (chain) {
+            HIP_TRY(launch_postnet_chain(d, p->cfg.weight_dtype, w, d_mel, n_col, d_out, p->stream));
+            break;
+        }
         HIP_TRY(launch_postnet_pack(d, p->cfg.weight_dtype, w, d_mel, n_col, n_pad, i0 == 0, p->stream));
     }
-    HIP_TRY(launch_postnet(d, p->cfg.weight_dtype, d_mel, n_col, d_out, p->stream));
+    if (!chain) HIP_TRY(launch_postnet(d, p->cfg.weight_dtype, d_mel, n_col, d_out, p->stream));
     if (timed) {
         HIP_TRY(hipEventRecord(p->ev1, p->stream));
         p->ev_valid = true;
@@ -219,7 +231,9 @@ extern "C" int tts_postnet_run_static(tts_postnet* p, const float* d_mel, const 
     // the same kernels, their scratch in this GPU's copy of the static array instead of the arena.  A call writes every
     // word of it that it reads (tables and activations of all its column tiles, padding columns included), so nothing
     // has to start at zero and what the previous call left is never seen.
+    // (The words of a call that is one launch do not lend themselves to that: they have to be empty when it begins.)
     PostnetPtrs d = p->d;
+    d.chain_words = nullptr;
     d.act[0] = base;
     d.act[1] = base + PN_STATIC_ACT;
     d.cmeta = reinterpret_cast<int*>(base + 2 * PN_STATIC_ACT);

@@ -12,6 +12,22 @@ constexpr int PN_CIN0 = 96;          // the mel channels padded to whole 64-byte
 constexpr int PN_CHANNELS = 512;
 constexpr int PN_COUT_LAST = 80;
 
+// A call's stack of layers as one launch (conv5_chain.h): CHAIN_GROUPS groups of columns at most, each of one to three times
+// chain_tiles column tiles (what 160 KB of LDS hold); CHAIN_LAYERS: most layers whose outputs the workgroups hand to each other.
+constexpr int CHAIN_GROUPS = 8;
+constexpr int CHAIN_LAYERS = 4;
+constexpr int CHAIN_STATE_BYTES = 32;
+constexpr int chain_tiles(size_t value_bytes) { return value_bytes == 2 ? 2 : 1; }
+constexpr int chain_most_columns(size_t value_bytes) { return CHAIN_GROUPS * 3 * chain_tiles(value_bytes) * 16; }
+constexpr int chain_column_bytes(size_t value_bytes) { return 16 * (int)value_bytes; }      // of one row tile's output
+// one of the two sets of words, for calls of up to `columns` columns: whole groups of any size
+inline size_t chain_set_bytes(size_t value_bytes, long columns, int layers)
+{
+    const long most = chain_most_columns(value_bytes), whole = 3 * chain_tiles(value_bytes) * 16;
+    const long cols = columns >= most ? most : (columns + whole - 1) / whole * whole;
+    return (size_t)(cols < most ? cols : most) * layers * PN_CHANNELS * value_bytes;
+}
+
 struct PostnetPtrs {
     const void* W[PN_LAYERS];   // weight dtype, MFMA A-fragment order, k = tap * C_in(padded) + channel
     const float* b[PN_LAYERS];  // [c_out]
@@ -19,6 +35,9 @@ struct PostnetPtrs {
     int* cmeta;                 // [columns padded to 16] (window length << 16) | index inside the window; 0 for padding
     int* orow;                  // [columns padded to 16] output row of the column, -1 = context or padding
     int n_mel;
+    char* chain_words;          // calls that are one launch (conv5_chain.h): two sets of words, and the words that say which is in use;
+    int* chain_state;           // null: no call is
+    int chain_set_bytes;
 };
 
 // Up to PN_META_WINDOWS windows of one call, as a kernel argument (no host-to-device copy): the device
@@ -36,7 +55,10 @@ struct PnWindows {
 hipError_t launch_postnet_pack(const PostnetPtrs& d, int wdtype, const PnWindows& w, const float* mel, int n_col, int n_col_pad, bool first,
                                hipStream_t s);
 
-// The five layers behind it; out: device fp32 [kept rows][n_mel]
+// All of it as one launch: up to PN_META_WINDOWS windows of at most chain_most_columns columns
+hipError_t launch_postnet_chain(const PostnetPtrs& d, int wdtype, const PnWindows& w, const float* mel, int n_col, float* out, hipStream_t s);
+
+// The five layers behind launch_postnet_pack; out: device fp32 [kept rows][n_mel]
 hipError_t launch_postnet(const PostnetPtrs& d, int wdtype, const float* mel, int n_col, float* out, hipStream_t s);
 
 }  // namespace tts

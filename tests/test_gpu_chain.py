@@ -1,0 +1,72 @@
+"""A small call's convolutions as one launch, whose workgroups hand each other their outputs: the same bits as layer by layer, at the
+edges of column tiles, column groups and of the forms with one, two and three times as many tiles a workgroup; call after call of
+changing sizes (the words of one call are emptied by the next), under capture, and where every wait runs out at once."""
+import numpy as np
+import pytest
+
+from paper_2211_13939_amd import binding, synth
+from tests.helpers import say
+
+pytestmark = pytest.mark.gpu
+
+EDGES = {True: (1, 15, 16, 17, 31, 33, 255, 256, 257, 511, 512, 513, 767, 768, 769), False: (1, 15, 16, 17, 127, 128, 129, 255, 256, 257, 383, 384, 385)}
+
+
+def _windows(columns, rng):
+    wins = []
+    while sum(wins) < columns:
+        wins.append(min(int(rng.integers(1, 60)), columns - sum(wins)))
+    return wins, [int(rng.integers(0, w)) for w in wins]
+
+
+def _postnet(bf16):
+    ws, bs = synth.make_postnet_weights(bf16=bf16)
+    return binding.Postnet(binding.make_postnet_config(max_columns=1024, bf16=bf16), ws, bs)
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_postnet_calls_as_one_launch(bf16):
+    """Against tts_postnet_run_static, whose calls are a launch per layer, twice over: with the words of other sizes before."""
+    import torch
+    rng = np.random.default_rng(71)
+    pn = _postnet(bf16)
+    for columns in EDGES[bf16] + EDGES[bf16][::-2] + (24, 500, 3):
+        wins, keeps = _windows(columns, rng) if columns != 24 else ([1] * 24, [0] * 24)
+        say(f"case postnet as one launch: {columns} columns in {len(wins)} windows, {'bf16' if bf16 else 'fp32'}")
+        with torch.cuda.stream(pn.stream):
+            mel = torch.from_numpy(rng.standard_normal((columns, 80)).astype(np.float32)).cuda()
+            got, want = (torch.full((columns - sum(keeps), 80), float("nan"), device="cuda") for _ in range(2))
+            pn.run_device(mel, wins, keeps, got)
+            pn.run_device(mel, wins, keeps, want, static=True)
+        pn.stream.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
+    pn.close()
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_postnet_call_captured_and_replayed(bf16):
+    """Whose turn the two sets of words are lies on the device: replays, with calls of other sizes between them."""
+    import torch
+    rng = np.random.default_rng(72)
+    pn = _postnet(bf16)
+    wins, keeps = [50, 17, 3], [10, 0, 2]
+    say(f"case postnet as one launch under capture, {'bf16' if bf16 else 'fp32'}")
+    with torch.cuda.stream(pn.stream):
+        mel = torch.zeros((70, 80), device="cuda")
+        got, want, other = (torch.zeros((n, 80), device="cuda") for n in (58, 58, 200))
+        pn.run_device(mel, wins, keeps, got)
+    pn.stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=pn.stream):
+        pn.run_device(mel, wins, keeps, got)
+    for i in range(5):
+        with torch.cuda.stream(pn.stream):
+            mel.copy_(torch.from_numpy(rng.standard_normal((70, 80)).astype(np.float32)))
+            graph.replay()
+            if i % 2:
+                pn.run_device(torch.zeros((200, 80), device="cuda"), [200], [0], other)
+            pn.run_device(mel, wins, keeps, want, static=True)
+        pn.stream.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
+    del graph
+    pn.close()
