@@ -91,7 +91,7 @@ __device__ __forceinline__ void chain_products(uint4 (&a)[NA], const unsigned ch
     uint4 b[AHEAD][CT];
     auto request = [&](int i) __attribute__((always_inline)) {
         const int f = min(wave + i * PN_WAVES, NKT - 1);               // past the last fragment: any operand, the weights are zero
-        const int tap = NKF % PN_WAVES == 0 ? i / (NKF / PN_WAVES) : f / NKF, cf = f - tap * NKF;
+        const int tap = NKF % PN_WAVES == 0 ? i / (NKF < PN_WAVES ? 1 : NKF / PN_WAVES) : f / NKF, cf = f - tap * NKF;
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const int row = (tapmask[c] >> tap) & 1 ? c * 16 + jl + tap : G::ROWS;      // a tap that leaves its window meets zeros

@@ -37,7 +37,7 @@ constexpr int ENC_WAIT_POLLS = DEFAULT_WAIT_POLLS / 64;
 
 struct EncLayout {
     size_t tables[ENC_TABLES], conv_w[ENC_CONVS], conv_b[ENC_CONVS], w_ih[2], w_hh[2], b[2];
-    size_t act[2], cmeta, hx, gave_up, xproj, total;
+    size_t act[2], cmeta, hx, gave_up, xproj, chain_state, chain, total;
     size_t scratch_begin;      // everything from here on is cleared at creation
 };
 
@@ -63,6 +63,8 @@ EncLayout layout_of(const tts_encoder_config& c)
     l.hx = a.take(ws == 4 ? (size_t)2 * ENC_MAX_BATCH * 2 * ENC_HID * 4 : 0);
     l.gave_up = a.take(ws == 4 ? 4 : 0);
     l.xproj = a.take((size_t)2 * c.max_tokens * ENC_GATES * 4);
+    l.chain_state = a.take(CHAIN_STATE_BYTES);
+    l.chain = a.take(2 * chain_set_bytes(ws, c.max_tokens, ENC_CONVS));
     l.total = a.off;
     return l;
 }
@@ -147,6 +149,7 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
     }
     if (rc == TTS_OK && hipMemset(base + lay.scratch_begin, 0, lay.total - lay.scratch_begin) != hipSuccess)
         rc = fail(TTS_E_HIP, "clearing the activation buffers failed");
+    if (rc == TTS_OK && hipMemset(base + lay.chain, 0xff, lay.total - lay.chain) != hipSuccess) rc = fail(TTS_E_HIP, "clearing the words failed");
     const size_t n_tok = cfg->max_tokens;
     for (tts_encoder::Staging& st : e->st) {
         if (rc == TTS_OK && (hipEventCreate(&st.ev0) != hipSuccess || hipEventCreate(&st.ev1) != hipSuccess))
@@ -184,6 +187,9 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
     p.gave_up = (int*)(base + lay.gave_up);
     p.wait_polls = ENC_WAIT_POLLS;
     p.xproj = (float*)(base + lay.xproj);
+    p.chain_words = base + lay.chain;
+    p.chain_state = (int*)(base + lay.chain_state);
+    p.chain_set_bytes = (int)chain_set_bytes(bf ? 2 : 4, cfg->max_tokens, ENC_CONVS);
     p.max_tokens = cfg->max_tokens;
     *out = e;
     return TTS_OK;

@@ -10,7 +10,7 @@
 // are contiguous; the two-byte W_hh has one gate of 16 units per row tile.
 #include "encoder_kernels.h"
 
-#include "conv5_kernels.h"
+#include "conv5_chain.h"
 
 namespace tts {
 namespace {
@@ -70,6 +70,64 @@ __global__ __launch_bounds__(256) void k_enc_xproj(const uint4* __restrict__ W0,
     const int col = ct * 16 + n;
     if (col < n_col) *reinterpret_cast<floatx4*>(Y + ((size_t)dir * max_tokens + col) * ENC_GATES + rt * 16 + 4 * g) = acc;
 }
+
+// The three convolutions and the input projection of a small call as one launch (conv5_chain.h).  A workgroup's share of the projection
+// are four row tiles, two waves each; every sum is the one chain over k that it is above.
+template <typename XT> struct EncChain {
+    static constexpr int LAYERS = ENC_CONVS, CIN = ENC_DIM, EPI = PN_EPI_RELU, EPL = Frag<XT>::EPL, KB = Frag<XT>::KB, NKF = ENC_DIM / KB, LAST = NKF;
+    static constexpr int WG_RTS = 2 * ENC_GATES / 16 / CHAIN_RTS, PER = PN_WAVES / WG_RTS;
+    const uint4* X;
+    const int* cmeta;
+    int n_col, max_tokens;
+    const uint4 *W0, *W1;
+    const float *b0, *b1;
+    float* Y;
+    __device__ __forceinline__ int windows() const { return 0; }
+    __device__ __forceinline__ void meta(int col0, int n, int, int* s_meta, int*) const
+    {
+        if ((int)threadIdx.x < n) s_meta[threadIdx.x] = col0 + (int)threadIdx.x < n_col ? cmeta[col0 + threadIdx.x] : 0;
+    }
+    template <class G> __device__ __forceinline__ void first(int col0, unsigned char* s_x) const
+    {
+        for (int p = threadIdx.x; p < G::ROWS * NKF * 4; p += PN_THREADS) {
+            const int row = p / (NKF * 4), rem = p - row * (NKF * 4), cf = rem >> 2, gg = rem & 3, col = col0 + row;
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (col >= 0 && col < n_col) v = X[xfrag(NKF, col >> 4, cf, (col & 15) + 16 * gg)];
+            *reinterpret_cast<uint4*>(&s_x[chain_at<G>(rem, row)]) = v;
+        }
+    }
+    static constexpr bool HALO = false;
+    __device__ __forceinline__ bool goes_on(int) const { return true; }
+    __device__ __forceinline__ ChainWeights weights(int rt, int wave) const
+    {
+        const int rt_all = rt * WG_RTS + wave % WG_RTS, rw = rt_all % (ENC_GATES / 16);
+        return ChainWeights(rt_all / (ENC_GATES / 16) ? W1 : W0, NKF, rw, 0, 1);
+    }
+    template <class G>
+    __device__ __forceinline__ void fetch(int, int rt, const int*, floatx4& bias, floatx4&) const
+    {
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), rt_all = rt * WG_RTS + wave % WG_RTS, rw = rt_all % (ENC_GATES / 16);
+        bias = *reinterpret_cast<const floatx4*>((rt_all / (ENC_GATES / 16) ? b1 : b0) + rw * 16 + 4 * (threadIdx.x >> 4 & 3));
+    }
+    template <class G, int NA>
+    __device__ __forceinline__ void last(int col0, int rt, const uint4 (&a)[NA], const floatx4& bias, const floatx4&, const unsigned char* s_x, floatx4 (*)[G::CT][64],
+                                         const int (&)[G::CT], const int*) const
+    {
+        constexpr int CT = G::CT;
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, jl = lane & 15, g = lane >> 4;
+        const int rt_all = rt * WG_RTS + wave % WG_RTS, dir = rt_all / (ENC_GATES / 16), rw = rt_all % (ENC_GATES / 16);
+#pragma unroll
+        for (int c0 = 0; c0 < CT; c0 += PER) {
+            const int c = c0 + wave / WG_RTS, col = col0 + c * 16 + jl;
+            if (c >= CT) break;
+            floatx4 acc = bias;
+#pragma unroll
+            for (int i = 0; i < NKF; ++i)
+                acc = mfma_frag<XT>(a[i], *reinterpret_cast<const uint4*>(&s_x[chain_at<G>(i * 4 + g, PN_HALO + c * 16 + jl)]), acc);
+            if (col < n_col) *reinterpret_cast<floatx4*>(Y + ((size_t)dir * max_tokens + col) * ENC_GATES + rw * 16 + 4 * g) = acc;
+        }
+    }
+};
 
 // The recurrence with two-byte weights: one workgroup per direction and REQUEST, the direction's whole matrix (512 KB)
 // resident in its CU, so a step touches no memory beyond the request's precomputed input projection.  A request's steps are a
@@ -507,39 +565,85 @@ void lstm_shared(int G, const EncoderPtrs& d, const PnWindows& w, float* out, hi
                        (const uint4*)d.w_hh[1], d.xproj, d.hx, w, d.max_tokens, out, d.wait_polls, d.gave_up);
 }
 
+// The three convolutions and the input projection, from the embedding in act[0] on: as one launch up to this many tokens.  Us a call, layer
+// by layer -> as one launch, queued one behind the other (and, each waited for); two-byte: 1 request of 60 tokens 77.4 -> 71.6 (102 -> 91),
+// 165: 150.2 -> 149.1 (176 -> 170), 384: 304.6 -> 299.8 (334 -> 325), 5 of 100: 116.3 -> 114.9 (145 -> 140), with six column tiles a
+// workgroup, 7 of 100, 120.1 -> 122.9; fp32: 1 of 60 127.1 -> 120.1 (152 -> 140), 3 of 100 227.7 -> 210.2.
+template <typename XT> constexpr int enc_chain_columns() { return sizeof(XT) == 2 ? chain_most_columns(2) / 3 * 2 : chain_most_columns(4); }
+
+template <typename XT>
+hipError_t front_by_layers(const EncoderPtrs& d, int n_col, hipStream_t s)
+{
+    constexpr int C = ENC_DIM;
+    static_assert(enc_chain_columns<XT>() / 16 + 1 >= cols_from<XT, C, C, PN_TAPS>(), "calls with layers of their own take k_conv_cols");
+    const int n_ctiles = (n_col + 15) / 16;
+    ColArgs p{};
+    p.cmeta = d.cmeta;
+    p.n_ctiles = n_ctiles;
+    hipError_t e = hipSuccess;
+    for (int l = 0; l < ENC_CONVS && e == hipSuccess; ++l) {
+        p.W = (const uint4*)d.conv_w[l];
+        p.bias = d.conv_b[l];
+        p.Xin = (const uint4*)d.act[l & 1];
+        p.Xout = d.act[l & 1 ^ 1];
+        e = conv_cols<XT, C, C, PN_TAPS, CC_RELU>(p, s);
+    }
+    if (e != hipSuccess) return e;
+    const void* x1 = d.act[1];
+    if constexpr (enc_chain_columns<XT>() / 16 + 1 < cols_from<XT, C, 2 * ENC_GATES, 1>())
+        if (n_ctiles < cols_from<XT, C, 2 * ENC_GATES, 1>()) {
+            hipLaunchKernelGGL((k_enc_xproj<XT>), dim3(ENC_GATES / 16 / 4, n_ctiles, 2), dim3(256), 0, s, (const uint4*)d.w_ih[0], (const uint4*)d.w_ih[1],
+                               d.b[0], d.b[1], (const uint4*)x1, n_col, d.max_tokens, d.xproj);
+            return hipGetLastError();
+        }
+    p.W = (const uint4*)d.w_ih[0];
+    p.W1 = (const uint4*)d.w_ih[1];
+    p.bias = d.b[0];
+    p.bias1 = d.b[1];
+    p.Xin = (const uint4*)x1;
+    p.Xout = nullptr;
+    p.out = d.xproj;
+    p.n_col = n_col;
+    p.max_cols = d.max_tokens;
+    return conv_cols<XT, C, 2 * ENC_GATES, 1, CC_XPROJ>(p, s);
+}
+
+template <typename XT>
+hipError_t front_as_one(const EncoderPtrs& d, int n_col, hipStream_t s)
+{
+    EncChain<XT> job;
+    job.X = (const uint4*)d.act[0];
+    job.cmeta = d.cmeta;
+    job.n_col = n_col;
+    job.max_tokens = d.max_tokens;
+    job.W0 = (const uint4*)d.w_ih[0];
+    job.W1 = (const uint4*)d.w_ih[1];
+    job.b0 = d.b[0];
+    job.b1 = d.b[1];
+    job.Y = d.xproj;
+    ChainArgs p{};
+    for (int l = 0; l < ENC_CONVS; ++l) {
+        p.W[l] = (const uint4*)d.conv_w[l];
+        p.b[l] = d.conv_b[l];
+    }
+    p.words = d.chain_words;
+    p.set_bytes = d.chain_set_bytes;
+    p.state = d.chain_state;
+    p.polls = d.wait_polls < CHAIN_POLLS ? d.wait_polls : CHAIN_POLLS;
+    return conv_chain<XT, enc_chain_columns<XT>()>(job, p, n_col, s);
+}
+
 template <typename XT>
 hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const EncStaged& staged, float* out, hipStream_t s)
 {
-    constexpr int C = ENC_DIM;
     const int n_ctiles = (n_col + 15) / 16, n_col_pad = n_ctiles * 16;
     XT* x0 = reinterpret_cast<XT*>(d.act[0]);
-    XT* x1 = reinterpret_cast<XT*>(d.act[1]);
     EncTables tb;
     for (int t = 0; t < ENC_TABLES; ++t) tb.t[t] = d.tables[t];
     hipLaunchKernelGGL((k_enc_embed<XT>), dim3((n_col_pad + 3) / 4), dim3(256), 0, s, tb, staged, n_col, n_col_pad, x0, d.cmeta, d.hx,
                        sizeof(XT) == 2 ? 0 : w.n * 4 * ENC_HID, d.gave_up);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(d.conv_w[0], d.conv_b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(d.conv_w[1], d.conv_b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_RELU>(d.conv_w[2], d.conv_b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e != hipSuccess) return e;
-    if (n_ctiles >= cols_from<XT, C, 2 * ENC_GATES, 1>()) {
-        ColArgs p{};
-        p.W = (const uint4*)d.w_ih[0];
-        p.W1 = (const uint4*)d.w_ih[1];
-        p.bias = d.b[0];
-        p.bias1 = d.b[1];
-        p.Xin = (const uint4*)x1;
-        p.n_ctiles = n_ctiles;
-        p.out = d.xproj;
-        p.n_col = n_col;
-        p.max_cols = d.max_tokens;
-        e = conv_cols<XT, C, 2 * ENC_GATES, 1, CC_XPROJ>(p, s);
-    } else {
-        hipLaunchKernelGGL((k_enc_xproj<XT>), dim3(ENC_GATES / 16 / 4, n_ctiles, 2), dim3(256), 0, s, (const uint4*)d.w_ih[0], (const uint4*)d.w_ih[1],
-                           d.b[0], d.b[1], (const uint4*)x1, n_col, d.max_tokens, d.xproj);
-        e = hipGetLastError();
-    }
+    if (e == hipSuccess) e = n_col <= enc_chain_columns<XT>() ? front_as_one<XT>(d, n_col, s) : front_by_layers<XT>(d, n_col, s);
     if (e != hipSuccess) return e;
     if constexpr (sizeof(XT) == 2) {
         static bool attr_set = false;               // dynamic LDS above 64 KB has to be allowed once

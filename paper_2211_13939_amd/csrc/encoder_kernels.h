@@ -25,6 +25,9 @@ struct EncoderPtrs {
     int* cmeta;                             // per column: (request length << 16) | position inside the request
     uint32_t* hx;                           // fp32: [2][requests][2][ENC_HID] words through which workgroups exchange h
     float* xproj;                           // [2][max_tokens][ENC_GATES]: W_ih x + b of every token, both directions
+    char* chain_words;                      // calls whose convolutions are one launch: as in PostnetPtrs
+    int* chain_state;
+    int chain_set_bytes;
     int max_tokens;
     int n_cu;                               // compute units of the device
     int wait_polls;                         // how often a workgroup polls a partner's word before it gives up

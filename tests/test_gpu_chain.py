@@ -70,3 +70,23 @@ def test_postnet_call_captured_and_replayed(bf16):
         np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
     del graph
     pn.close()
+
+
+@pytest.mark.parametrize("bf16,edges", [(True, (1, 16, 17, 255, 256, 257, 511, 512)), (False, (1, 16, 17, 127, 128, 129, 256, 257, 383, 384))])
+@pytest.mark.parametrize("polls", [None, 0])
+def test_encoder_calls_as_one_launch(bf16, edges, polls):
+    """Against the same requests in a call with one more, long one, which is too large for one launch; polls = 0: nobody waits, the
+    workgroups form what they need themselves."""
+    enc = binding.Encoder(binding.make_encoder_config(max_tokens=1152, max_len=640, bf16=bf16), synth.make_encoder_weights(bf16=bf16))
+    more = synth.encoder_ids(600, 99)
+    for columns in edges:
+        say(f"case encoder as one launch: {columns} tokens, {'bf16' if bf16 else 'fp32'}, polls {polls}")
+        lens = [columns] if columns < 40 else [columns // 3, 1, columns - columns // 3 - 1]
+        ids = [synth.encoder_ids(l, i) for i, l in enumerate(lens)]
+        if polls is not None:
+            enc.set_wait_polls(polls)
+        got = enc.run(ids)
+        want = enc.run(ids + [more])
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(a, b)
+    enc.close()
