@@ -737,7 +737,9 @@ static int segment_steps(const tts_pool* p, int n)
     for (int sl : p->book->active()) most = std::max(most, p->book->slot(sl).n_steps - p->book->slot(sl).t);
     return std::min({n, most, MAX_SEGMENT_STEPS});
 }
-static int launch_segment_steps(tts_pool* p, int g)
+// *taken = false: the stream is being captured.  A replayed segment would find the words of the replay before, so a captured call takes its steps
+// one by one, as it would without segments.
+static int launch_segment_steps(tts_pool* p, int g, bool* taken)
 {
     StepLaunch sl;
     sl.wdtype = p->cfg.weight_dtype;
@@ -746,7 +748,10 @@ static int launch_segment_steps(tts_pool* p, int g)
     sl.seg_steps = g;
     sl.seg_set = p->seg_set;
     sl.seg_empty = p->seg_used;
-    HIP_TRY(launch_step(p->d, sl, p->parity, p->stream));
+    const hipError_t e = launch_step(p->d, sl, p->parity, p->stream);
+    *taken = e != hipErrorStreamCaptureUnsupported;
+    if (!*taken) return TTS_OK;
+    HIP_TRY(e);
     p->seg_set ^= 1;
     p->seg_used = sl.n_tiles;
     return TTS_OK;
@@ -767,16 +772,17 @@ static int step_impl(tts_pool* p, int n, int64_t* out_frames, int* out_last_acti
         // graphs exist for powers of two up to MAX_GRAPH_STEPS and for one whole chunk (the paper's iteration: a
         // segment of 40 steps as one graph measured 0.05 - 0.2 us per step faster than as graphs of 32 and 8)
         int g = 1;
+        bool as_one = false;
         const int seg = segment_steps(p, n - i);
-        if (seg > 0) {
+        if (seg > 0 && (rc = launch_segment_steps(p, seg, &as_one))) return rc;
+        if (as_one) {
             g = seg;
         } else if (p->cfg.use_graph) {
             while (g * 2 <= n - i && g * 2 <= MAX_GRAPH_STEPS) g *= 2;
             const int chunk = p->cfg.chunk_frames;
             if (chunk > g && chunk <= n - i && chunk <= MAX_CHUNK_GRAPH_STEPS) g = chunk;
         }
-        rc = seg > 0 ? launch_segment_steps(p, g) : launch_steps(p, n_active, g);
-        if (rc) return rc;
+        if (!as_one && (rc = launch_steps(p, n_active, g))) return rc;
         for (int k = 0; k < g; ++k) {
             p->parity ^= 1;
             frames += p->book->step(p->parity);
