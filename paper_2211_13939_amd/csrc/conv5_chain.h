@@ -189,8 +189,11 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
         lds_barrier();
         return s_late == 0;
     };
+    // The caller's results may lie where his input lies.  They are written when every block of the first layer has been stored, so a workgroup that
+    // finds its block stored by another one, after it has read the input, keeps its own to itself: it may be made of results.
+    auto stored = [&](int cg, int rt) __attribute__((always_inline)) { return x.look(wave < CT ? (wave * 16 + jl) * G::PIECES * 16 + g * 4 * (int)sizeof(XT) : 0, block(0, cg, rt)); };
     // behind the products: the partial sums meet, and a layer's output goes out as words
-    auto finish = [&](int l, int cg, int rt, const floatx4& bias) __attribute__((always_inline)) {
+    auto finish = [&](int l, int cg, int rt, const floatx4& bias, unsigned there) __attribute__((always_inline)) {
         lds_barrier();
         if (wave >= CT) return;
         floatx4 y = bias;
@@ -198,6 +201,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
         for (int w = 0; w < PN_WAVES; ++w) y += red[w][wave][lane];
         const float y0 = pn_act<JOB::EPI>(y[0]), y1 = pn_act<JOB::EPI>(y[1]), y2 = pn_act<JOB::EPI>(y[2]), y3 = pn_act<JOB::EPI>(y[3]);
         const int at = (wave * 16 + jl) * G::PIECES * 16 + g * 4 * (int)sizeof(XT);
+        if (there != EMPTY) return;
         if constexpr (sizeof(XT) == 2) x.put2(pack2<XT>(y0, y1), pack2<XT>(y2, y3), at, block(l, cg, rt));
         else x.put4(floatx4{y0, y1, y2, y3}, at, block(l, cg, rt));
     };
@@ -232,6 +236,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
                 }
             }
             __syncthreads();
+            const unsigned there = k == 0 ? stored(cg, rt) : EMPTY;
             const ChainWeights W(p.W[k], NKT, rt, wave, PN_WAVES);
             floatx4 acc[CT];
 #pragma unroll
@@ -247,7 +252,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
             if constexpr (G::ON_TOP) lds_barrier();
 #pragma unroll
             for (int c = 0; c < CT; ++c) red[wave][c][lane] = acc[c];
-            finish(k, cg, rt, bias_of(p.b[k], rt));
+            finish(k, cg, rt, bias_of(p.b[k], rt), there);
             __syncthreads();
         }
         columns_of(my_cg, job.windows());
@@ -291,8 +296,10 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
     };
     {
         const ChainWeights W = weights_of(1);
+        Words::again();
+        const unsigned there = stored(my_cg, my_rt);
         chain_products<XT, G, NKF0, NFW0>(a, s_x, tapmask, red, [&](int i) __attribute__((always_inline)) { a[i] = W.at(i); });
-        finish(0, my_cg, my_rt, bias);
+        finish(0, my_cg, my_rt, bias, there);
     }
 #pragma unroll 1
     for (int l = 1; l < LAYERS; ++l) {
@@ -300,7 +307,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
         bias = bias_of(p.b[l], my_rt);
         take(l, true);
         chain_products<XT, G, G::NKF, G::NFW>(a, s_x, tapmask, red, [&](int i) __attribute__((always_inline)) { a[i] = W.at(i); });
-        finish(l, my_cg, my_rt, bias);
+        finish(l, my_cg, my_rt, bias, EMPTY);
     }
     if (job.goes_on(my_rt)) {
         const ChainWeights W = weights_of(LAYERS);
