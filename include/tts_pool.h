@@ -83,7 +83,8 @@ typedef struct {
                           8 x less operand rounding.  max_steps <= 65504 in this mode. */
     int memory_dtype;  /* storage of F_enc and of the processed memory F_enc W_mem^T.
                           TTS_DTYPE_BF16 requires weight_dtype == TTS_DTYPE_BF16. */
-    int use_graph;     /* non-zero: each step is one hipGraph launch */
+    int use_graph;     /* non-zero: steps are queued as hipGraph launches, or, in small pools with two-byte weights and memory,
+                          several of them as one kernel launch (tts_pool_step_n) */
     float stop_threshold; /* a request ends when sigmoid(stop logit) > threshold (Sec. 2.2.1);
                              outside [0,1] = disabled, requests end at their n_steps */
 } tts_config;
@@ -152,7 +153,9 @@ int tts_pool_step(tts_pool *pool, int *out_n_active);
  * for bit, as n calls of tts_pool_step; the steps of one call are queued more
  * tightly (one graph launch for up to a chunk of steps; in pools of at most 64
  * slots with two-byte weights and memory a step that follows another step of
- * the same call is two kernel launches instead of three). */
+ * the same call is two kernel launches instead of three, and while no active
+ * request's slot lies above 48 and there is no stop threshold up to 64 steps
+ * are one kernel launch). */
 int tts_pool_step_n(tts_pool *pool, int n, int64_t *out_frames);
 
 /*

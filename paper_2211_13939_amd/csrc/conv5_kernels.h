@@ -382,6 +382,7 @@ inline hipError_t conv_cols_ct(const ColArgs& p, hipStream_t s)
 }
 
 // Column tiles of a call from which a layer takes the kernel above (the sums are the same, so every layer has a line of its own).
+// (Small calls of the PostNet and the encoder are one launch, conv5_chain.h; the lines below those sizes are for tts_postnet_run_static.)
 // Launches in us, small-call kernel / the kernel above:
 //   two-byte  512 -> 512     20 tiles  8.4 /  8.2,   24  8.8 /  8.4,   36 10.8 /  8.7,   79 16.9 / 10.3
 //             96 -> 512      20        4.2 /  3.8,   36  4.8 /  4.1,   79  6.9 /  5.3
