@@ -336,7 +336,6 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
     }
 }
 
-// Column tiles a workgroup, for calls of up to MOST columns: the fewest of one to three times chain_tiles that leave CHAIN_GROUPS groups at most, a workgroup for every compute unit
 template <typename XT, int CT, class JOB>
 inline hipError_t conv_chain_ct(const JOB& job, ChainArgs& p, int n_col, hipStream_t s)
 {
@@ -349,18 +348,20 @@ inline hipError_t conv_chain_ct(const JOB& job, ChainArgs& p, int n_col, hipStre
         attr_set = true;
     }
     p.groups = (n_col + G::COLS - 1) / G::COLS;
+    if ((long)p.groups * JOB::LAYERS * CHAIN_RTS * G::BLOCK > p.set_bytes) return hipErrorInvalidValue;     // (made for smaller calls)
     hipLaunchKernelGGL(kern, dim3(p.groups * CHAIN_RTS), dim3(PN_THREADS), G::LDS, s, job, p);
     return hipGetLastError();
 }
+// Calls of up to MOST columns; CHAIN_GROUPS groups are a workgroup for every compute unit
 template <typename XT, int MOST, class JOB>
 inline hipError_t conv_chain(const JOB& job, ChainArgs& p, int n_col, hipStream_t s)
 {
     constexpr int UNIT = chain_tiles(sizeof(XT));
-    const int tiles = (n_col + 15) / 16;
-    if (tiles <= CHAIN_GROUPS * UNIT) return conv_chain_ct<XT, UNIT>(job, p, n_col, s);
-    if constexpr (MOST > CHAIN_GROUPS * 2 * UNIT * 16)
-        if (tiles > CHAIN_GROUPS * 2 * UNIT) return conv_chain_ct<XT, 3 * UNIT>(job, p, n_col, s);
-    return conv_chain_ct<XT, 2 * UNIT>(job, p, n_col, s);
+    const int ct = chain_group_tiles(sizeof(XT), n_col);
+    if (ct == UNIT) return conv_chain_ct<XT, UNIT>(job, p, n_col, s);
+    if (ct == 2 * UNIT) return conv_chain_ct<XT, 2 * UNIT>(job, p, n_col, s);
+    if constexpr (MOST > CHAIN_GROUPS * 2 * UNIT * 16) return conv_chain_ct<XT, 3 * UNIT>(job, p, n_col, s);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace tts

@@ -20,12 +20,24 @@ constexpr int CHAIN_STATE_BYTES = 32;
 constexpr int chain_tiles(size_t value_bytes) { return value_bytes == 2 ? 2 : 1; }
 constexpr int chain_most_columns(size_t value_bytes) { return CHAIN_GROUPS * 3 * chain_tiles(value_bytes) * 16; }
 constexpr int chain_column_bytes(size_t value_bytes) { return 16 * (int)value_bytes; }      // of one row tile's output
-// one of the two sets of words, for calls of up to `columns` columns: whole groups of any size
-inline size_t chain_set_bytes(size_t value_bytes, long columns, int layers)
+// column tiles a workgroup of a call: the fewest of one to three times chain_tiles that leave CHAIN_GROUPS groups at most
+constexpr int chain_group_tiles(size_t value_bytes, int columns)
 {
-    const long most = chain_most_columns(value_bytes), whole = 3 * chain_tiles(value_bytes) * 16;
-    const long cols = columns >= most ? most : (columns + whole - 1) / whole * whole;
-    return (size_t)(cols < most ? cols : most) * layers * PN_CHANNELS * value_bytes;
+    const int unit = chain_tiles(value_bytes), tiles = (columns + 15) / 16;
+    return tiles <= CHAIN_GROUPS * unit ? unit : tiles <= CHAIN_GROUPS * 2 * unit ? 2 * unit : 3 * unit;
+}
+// what a call stores: the columns of its groups, whole, of every layer
+constexpr size_t chain_call_bytes(size_t value_bytes, int columns, int layers)
+{
+    const int group = chain_group_tiles(value_bytes, columns) * 16;
+    return (size_t)((columns + group - 1) / group * group) * layers * PN_CHANNELS * value_bytes;
+}
+// One of the two sets of words, for calls of up to `columns` columns: those of the largest.  (A smaller call never stores more: a size of groups
+// is left for the next one when eight of them are full.)
+constexpr size_t chain_set_bytes(size_t value_bytes, long columns, int layers)
+{
+    const int most = chain_most_columns(value_bytes);
+    return chain_call_bytes(value_bytes, columns < most ? (int)columns : most, layers);
 }
 
 struct PostnetPtrs {

@@ -19,9 +19,48 @@ def _windows(columns, rng):
     return wins, [int(rng.integers(0, w)) for w in wins]
 
 
-def _postnet(bf16):
+def _postnet(bf16, max_columns=1024):
     ws, bs = synth.make_postnet_weights(bf16=bf16)
-    return binding.Postnet(binding.make_postnet_config(max_columns=1024, bf16=bf16), ws, bs)
+    return binding.Postnet(binding.make_postnet_config(max_columns=max_columns, bf16=bf16), ws, bs)
+
+
+# capacities whose largest call has more columns in its groups than whole groups of the largest size would
+FULL = [(True, n) for n in (257, 288, 449, 450, 480)] + [(False, n) for n in (129, 144, 225, 240)]
+
+
+@pytest.mark.parametrize("bf16,columns", FULL)
+def test_postnet_made_for_exactly_the_call(bf16, columns):
+    """Several calls in a row: each of the two sets of words in its turn."""
+    import torch
+    rng = np.random.default_rng(columns)
+    pn = _postnet(bf16, max_columns=columns)
+    for call in range(4):
+        wins, keeps = _windows(columns, rng)
+        say(f"case PostNet made for {columns} columns, call {call} of {columns} in {len(wins)} windows, {'bf16' if bf16 else 'fp32'}")
+        with torch.cuda.stream(pn.stream):
+            mel = torch.from_numpy(rng.standard_normal((columns, 80)).astype(np.float32)).cuda()
+            got, want = (torch.full((columns - sum(keeps), 80), float("nan"), device="cuda") for _ in range(2))
+            pn.run_device(mel, wins, keeps, got)
+            pn.run_device(mel, wins, keeps, want, static=True)
+        pn.stream.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
+    pn.close()
+
+
+@pytest.mark.parametrize("bf16,columns", FULL)
+def test_encoder_made_for_exactly_the_call(bf16, columns):
+    """Against the same requests in a larger call of a larger encoder, layer by layer."""
+    weights = synth.make_encoder_weights(bf16=bf16)
+    enc = binding.Encoder(binding.make_encoder_config(max_tokens=columns, max_len=columns, bf16=bf16), weights)
+    large = binding.Encoder(binding.make_encoder_config(max_tokens=1152, max_len=640, bf16=bf16), weights)
+    more = synth.encoder_ids(600, 99)
+    for call, lens in enumerate(([columns], [columns // 3, 1, columns - columns // 3 - 1], [columns // 2, columns - columns // 2])):
+        say(f"case encoder made for {columns} tokens, call {call} of {lens}, {'bf16' if bf16 else 'fp32'}")
+        ids = [synth.encoder_ids(l, 7 * call + i) for i, l in enumerate(lens)]
+        for a, b in zip(enc.run(ids), large.run(ids + [more])):
+            np.testing.assert_array_equal(a, b)
+    enc.close()
+    large.close()
 
 
 @pytest.mark.parametrize("bf16", [True, False])
