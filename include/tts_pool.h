@@ -25,6 +25,16 @@
  * Threading: one owner thread per pool.  All device work is queued on the
  * HIP stream given at create time; calls that hand data back to the host
  * (drain, get_state, sync) wait for that stream.
+ *
+ * Several pools on one GPU, in one process: each may have its own stream and
+ * thread.  Steps that are one launch (tts_pool_step_n) need most of the GPU's
+ * compute units at once, so they begin when the steps that other pools have queued
+ * so far have run, and other pools' steps wait for them in the same way; this
+ * is arranged on the device, and costs a pool whose neighbours are idle nothing
+ * while one thread drives them all (with several threads, an event per call).
+ * Pools of SEVERAL PROCESSES on one GPU do not know of each other: at most one
+ * of them may run such steps at a time, or both may lose requests
+ * (tts_pool_sync); use_graph = 0 keeps a pool from taking them.
  */
 #ifndef TTS_POOL_H
 #define TTS_POOL_H

@@ -20,6 +20,7 @@
 #include "dev.h"
 #include "hostutil.h"
 #include "kernels.h"
+#include "resident.h"
 
 using namespace tts;
 
@@ -241,6 +242,7 @@ struct tts_pool {
     tts_config cfg;
     DevPtrs d;
     hipStream_t stream = nullptr;
+    Resident resident;            // what other pools of the device have to know of this one's launches
     std::unique_ptr<PoolBook> book;
     int parity = 0;               // activation buffer half the next step reads
     long long n_moves = 0;        // requests moved to lower slots since creation
@@ -268,6 +270,13 @@ struct tts_pool {
     std::vector<int64_t> lost_ids; // requests the device ended early that tts_pool_sync has not reported yet
 };
 
+static hipError_t wait_for_stream(tts_pool* p)
+{
+    const hipError_t e = hipStreamSynchronize(p->stream);
+    if (e == hipSuccess) p->resident.queued = GANG_NONE;
+    return e;
+}
+
 // After the stream has been waited for: did a workgroup's bounded wait run out since the last look?  The kernels froze
 // the requests concerned on the device (no frame was stored for them from that step on, every other request went on);
 // here the host's bookkeeping follows: each such request ends after the frames the device holds for it and is marked
@@ -280,7 +289,7 @@ static int absorb_failures(tts_pool* p)
     HIP_TRY(hipMemcpyAsync(failed.data(), p->d.failed, (size_t)n * 4, hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(hipMemcpyAsync(t.data(), p->d.t, (size_t)n * 4, hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(hipMemsetAsync(p->d.failed, 0, (size_t)n * 4, p->stream));
-    HIP_TRY(hipStreamSynchronize(p->stream));
+    HIP_TRY(wait_for_stream(p));
     *p->h_fault = 0;
     for (int sl = 0; sl < n && sl < p->cfg.max_pool; ++sl) {
         if (!failed[sl] || p->book->slot(sl).state == SlotState::Free) continue;
@@ -499,6 +508,7 @@ extern "C" int tts_pool_create(const tts_config* cfg, const tts_weights* w, void
         if (e == hipSuccess) e = hipEventCreate(&p->ev0);
         if (e == hipSuccess) e = hipEventCreate(&p->ev1);
         if (e == hipSuccess) e = hipDeviceSynchronize();
+        if (e == hipSuccess) e = resident_join(p->resident, attr.device, p->stream);
         if (e != hipSuccess) rc = fail(TTS_E_HIP, "pool setup: %s", hipGetErrorString(e));
     }
     if (rc) {
@@ -512,7 +522,8 @@ extern "C" int tts_pool_create(const tts_config* cfg, const tts_weights* w, void
 extern "C" void tts_pool_destroy(tts_pool* p)
 {
     if (!p) return;
-    (void)hipStreamSynchronize(p->stream);
+    (void)wait_for_stream(p);
+    resident_leave(p->resident);
     for (auto& kv : p->graphs) (void)hipGraphExecDestroy(kv.second);
     for (auto g : p->graph_defs) (void)hipGraphDestroy(g);
     if (p->ev0) (void)hipEventDestroy(p->ev0);
@@ -560,7 +571,7 @@ extern "C" int tts_pool_add_requests(tts_pool* p, int n, const float* const* enc
             // buffer on return, so the copy is finished before returning
             if ((rc = flush())) return rc;
             HIP_TRY(hipMemcpyAsync(p->d.stage, enc_out[i], (size_t)L[i] * ENC * 4, hipMemcpyHostToDevice, p->stream));
-            HIP_TRY(hipStreamSynchronize(p->stream));
+            HIP_TRY(wait_for_stream(p));
         }
         ja.F[nb] = on_device ? enc_out[i] : p->d.stage;
         ja.slot[nb] = slot;
@@ -757,11 +768,21 @@ static int launch_segment_steps(tts_pool* p, int g, bool* taken)
     return TTS_OK;
 }
 
+// (by the caller, into a graph of his own)
+static bool being_captured(const tts_pool* p)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (!p->stream || hipStreamIsCapturing(p->stream, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 static int step_impl(tts_pool* p, int n, int64_t* out_frames, int* out_last_active)
 {
     int64_t frames = 0;
     int last = 0;
     if (p->timing) HIP_TRY(hipEventRecord(p->ev0, p->stream));
+    Turn turn(p->resident, being_captured(p));
     int i = 0;
     while (i < n) {
         const int n_active = (int)p->book->active().size();
@@ -774,6 +795,7 @@ static int step_impl(tts_pool* p, int n, int64_t* out_frames, int* out_last_acti
         int g = 1;
         bool as_one = false;
         const int seg = segment_steps(p, n - i);
+        HIP_TRY(turn.before(seg > 0 ? GANG_SEGMENT : GANG_STEPS));
         if (seg > 0 && (rc = launch_segment_steps(p, seg, &as_one))) return rc;
         if (as_one) {
             g = seg;
@@ -834,12 +856,14 @@ extern "C" int tts_pool_kernel_times(tts_pool* p, int n, float* out_us, int cap,
         rc = push_membership(p);
         shape_for(p, p->slot_span, &sl);
     }
+    std::unique_ptr<Turn> turn(new Turn(p->resident, being_captured(p)));
     for (int i = 0; i < n && rc == TTS_OK; ++i) {
         // (a pool that empties on the way: the step before formed an attention LSTM in which no request took part)
         if (p->book->active().empty()) break;
         chain_steps(p, &sl, i, n);
         hipEvent_t* e = &ev[(size_t)i * per];
-        hipError_t he = launch_step(p->d, sl, p->parity, p->stream, e);
+        hipError_t he = turn->before(GANG_STEPS);
+        if (he == hipSuccess) he = launch_step(p->d, sl, p->parity, p->stream, e);
         // an empty interval right after the step: the cost of the event itself
         if (he == hipSuccess) he = hipEventRecord(e[N_STEP_KERNELS + 1], p->stream);
         if (he != hipSuccess) { rc = fail(TTS_E_HIP, "timed step: %s", hipGetErrorString(he)); break; }
@@ -847,13 +871,14 @@ extern "C" int tts_pool_kernel_times(tts_pool* p, int n, float* out_us, int cap,
         p->book->step(p->parity);
         ++done;
     }
+    turn.reset();
     // per kernel: the steps that launched it.  The last kernel is averaged apart for the steps in which it also formed
     // the next step's attention LSTM (all but the last, in pools that do this) and for those in which it did not.
     const bool chained = n > 1 && p->d.p_x != nullptr && CHAIN_ATT_LSTM;
     double acc[N_STEP_KERNELS + 1] = {0}, last_plain = 0;
     int cnt[N_STEP_KERNELS + 1] = {0}, n_plain = 0;
     if (rc == TTS_OK && done > 0) {
-        hipError_t he = hipStreamSynchronize(p->stream);
+        hipError_t he = wait_for_stream(p);
         for (int i = 0; i < done && he == hipSuccess; ++i)
             for (int k = 0; k <= N_STEP_KERNELS && he == hipSuccess; ++k) {
                 float ms = 0.f;
@@ -897,7 +922,7 @@ static int refresh_slot(tts_pool* p, int slot)
     int td[2] = {0, 0};
     HIP_TRY(hipMemcpyAsync(&td[0], p->d.t + slot, 4, hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(hipMemcpyAsync(&td[1], p->d.done + slot, 4, hipMemcpyDeviceToHost, p->stream));
-    HIP_TRY(hipStreamSynchronize(p->stream));
+    HIP_TRY(wait_for_stream(p));
     if (td[1] && td[0] <= p->book->slot(slot).t) p->book->finish_early(slot, td[0]);
     return TTS_OK;
 }
@@ -940,7 +965,7 @@ static int stage_chunks(tts_pool* p, int slot)
     }
     if (n == 0) return TTS_OK;
     hipError_t e = launch_stage_chunks(p->d, sa, n, most, p->d_stage, p->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
+    if (e == hipSuccess) e = wait_for_stream(p);
     if (e == hipSuccess) return TTS_OK;
     forget_staged(p);
     return fail(TTS_E_HIP, "copying chunks to the host: %s", hipGetErrorString(e));
@@ -957,7 +982,7 @@ static int bring_chunk(tts_pool* p, int slot, int first, int count, float* dst, 
     *at = dst;
     const float* src = p->d.mel_ring + ((size_t)slot * p->cfg.max_steps + first) * N_MEL;
     HIP_TRY(hipMemcpyAsync(dst, src, (size_t)count * N_MEL * 4, hipMemcpyDeviceToHost, p->stream));
-    HIP_TRY(hipStreamSynchronize(p->stream));
+    HIP_TRY(wait_for_stream(p));
     return TTS_OK;
 }
 
@@ -973,7 +998,7 @@ extern "C" int tts_pool_drain_chunk(tts_pool* p, int64_t id, float* dst, int* ou
     if (count > 0) {
         // (a caller may take a drain for a wait, also where the chunk is on the host already; on an idle stream it costs 0.2 us)
         const float* at = find_staged(p, slot, first, count);
-        if (at) HIP_TRY(hipStreamSynchronize(p->stream));
+        if (at) HIP_TRY(wait_for_stream(p));
         else if ((rc = bring_chunk(p, slot, first, count, dst, &at))) return rc;
         if (*p->h_fault) {
             // some request was frozen since the last look: if it is this one, the plan above counted frames that were
@@ -1006,7 +1031,7 @@ extern "C" int tts_pool_chunk_window(tts_pool* p, int64_t id, int context, float
     // a request frozen by steps that have already run must not hand out frames it never made (steps still in flight
     // are the caller's to wait for: tts_pool_sync reports what they lost)
     if (*p->h_fault) {
-        HIP_TRY(hipStreamSynchronize(p->stream));
+        HIP_TRY(wait_for_stream(p));
         if ((rc = absorb_failures(p))) return rc;
     }
     int first, count, fin;
@@ -1035,7 +1060,7 @@ extern "C" int tts_pool_get_stop_logits(tts_pool* p, int64_t id, int first, int 
     if (count == 0) return TTS_OK;
     HIP_TRY(hipMemcpyAsync(dst, p->d.stop_ring + (size_t)slot * p->cfg.max_steps + first, (size_t)count * 4,
                            hipMemcpyDeviceToHost, p->stream));
-    HIP_TRY(hipStreamSynchronize(p->stream));
+    HIP_TRY(wait_for_stream(p));
     return TTS_OK;
 }
 
@@ -1054,7 +1079,7 @@ extern "C" int tts_pool_frames(tts_pool* p, int64_t id, int* out_frames, int* ou
     int rc = refresh_slot(p, slot);
     if (rc) return rc;
     if (*p->h_fault) {
-        HIP_TRY(hipStreamSynchronize(p->stream));
+        HIP_TRY(wait_for_stream(p));
         if ((rc = absorb_failures(p))) return rc;
     }
     if (out_frames) *out_frames = p->book->slot(slot).t;
@@ -1070,7 +1095,7 @@ extern "C" long long tts_pool_moves(const tts_pool* p) { return p ? p->n_moves :
 extern "C" int tts_pool_sync(tts_pool* p)
 {
     if (!p) return fail(TTS_E_INVAL, "pool is null");
-    HIP_TRY(hipStreamSynchronize(p->stream));
+    HIP_TRY(wait_for_stream(p));
     int rc = absorb_failures(p);
     return rc ? rc : report_lost(p);
 }
@@ -1082,7 +1107,7 @@ extern "C" int tts_pool_lost(tts_pool* p, int64_t id, int* out_lost)
     if (slot < 0) return fail(TTS_E_NOTFOUND, "no request with id %lld", (long long)id);
     int rc = TTS_OK;
     if (*p->h_fault) {
-        HIP_TRY(hipStreamSynchronize(p->stream));
+        HIP_TRY(wait_for_stream(p));
         if ((rc = absorb_failures(p))) return rc;
     }
     *out_lost = p->book->slot(slot).lost ? 1 : 0;
@@ -1093,7 +1118,7 @@ extern "C" int tts_pool_set_wait_polls(tts_pool* p, int polls)
 {
     if (!p) return fail(TTS_E_INVAL, "pool is null");
     if (polls < 0) return fail(TTS_E_INVAL, "polls = %d is negative", polls);
-    HIP_TRY(hipStreamSynchronize(p->stream));
+    HIP_TRY(wait_for_stream(p));
     p->d.wait_polls = polls;
     // captured graphs hold the old value among their kernel arguments
     for (auto& kv : p->graphs) (void)hipGraphExecDestroy(kv.second);
@@ -1185,7 +1210,7 @@ extern "C" int tts_pool_get_state(tts_pool* p, int64_t id, int which, float* dst
     const float* src = s.n_plain ? s.plain[0] : p->d.stage;
     if (!s.n_plain) HIP_TRY(launch_x_get(p->cfg.weight_dtype, s.x[0], s.xK[0], slot, s.xoff[0], s.n, p->d.stage, p->stream));
     HIP_TRY(hipMemcpyAsync(dst, src, (size_t)s.n * 4, hipMemcpyDeviceToHost, p->stream));
-    HIP_TRY(hipStreamSynchronize(p->stream));
+    HIP_TRY(wait_for_stream(p));
     return TTS_OK;
 }
 
@@ -1209,7 +1234,7 @@ extern "C" int tts_pool_set_state(tts_pool* p, int64_t id, int which, const floa
     // the next step's gate pre-sums were formed from the old state: redo the slot's tile from the half that step reads
     if (pre_gates_for(p->cfg) && (which == TTS_STATE_A || which == TTS_STATE_H_ATT || (which == TTS_STATE_H_DEC && pre_dec_for(p->cfg))))
         HIP_TRY(launch_presum_tile(p->d, p->cfg.weight_dtype, slot >> 4, p->parity, p->stream));
-    HIP_TRY(hipStreamSynchronize(p->stream));
+    HIP_TRY(wait_for_stream(p));
     return TTS_OK;
 }
 

@@ -1,10 +1,13 @@
 // A HIP runtime and the kernels' launch wrappers on host memory, for the host side of the library alone: streams run what is
 // queued at once, except that what a kernel still has to read of pinned memory counts as pending until the host has waited for
 // it.  Any call can be made to fail (fake_fail), and a slot can be frozen as a kernel would that gave up (fake_freeze).
+// What is ordered behind what is followed through streams, events and the host's waits: a segment of steps that is not ordered against another
+// stream's steps, or the other way round, counts (fake_unordered).
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -20,10 +23,41 @@ struct Pending { const void* at; int seq; };
 std::vector<Pending> pending;                   // pinned memory that queued work still reads
 int seq = 0, violations = 0;                    // violations: such memory rewritten or freed
 int freeze_slot = -1, freeze_at = 0;
-struct Event { int seq = 0; };
 
+using Clock = std::map<hipStream_t, int>;       // how much of every stream's work lies before
+struct Event { int seq = 0; Clock clock; };
+struct Launched { hipStream_t stream; int at; bool segment; };
+std::mutex order;
+std::map<hipStream_t, Clock> streams;
+std::vector<Launched> launched;
+int unordered = 0, segments = 0;
+bool busy = false;                              // what hipStreamQuery says
+hipStream_t capturing = nullptr;
+Clock host;                                     // what some thread has waited for has ended
+void merge(Clock& a, const Clock& b)
+{
+    for (const auto& kv : b) a[kv.first] = std::max(a[kv.first], kv.second);
+}
+void ordered(hipStream_t s, bool segment)
+{
+    std::lock_guard<std::mutex> l(order);
+    Clock& c = streams[s];
+    merge(c, host);
+    for (const Launched& x : launched)
+        unordered += x.stream != s && (segment || x.segment) && c[x.stream] < x.at;
+    launched.push_back({s, ++c[s], segment});
+    segments += segment;
+}
+void waited(hipStream_t s)
+{
+    std::lock_guard<std::mutex> l(order);
+    merge(host, streams[s]);
+}
+
+std::mutex book;
 hipError_t call(const char* what)
 {
+    std::lock_guard<std::mutex> l(book);
     ++calls[what];
     auto it = fails.find(what);
     if (it == fails.end() || --it->second.in > 0) return hipSuccess;
@@ -32,6 +66,7 @@ hipError_t call(const char* what)
 }
 void done_up_to(int s)
 {
+    std::lock_guard<std::mutex> l(book);
     pending.erase(std::remove_if(pending.begin(), pending.end(), [&](const Pending& p) { return p.seq <= s; }), pending.end());
 }
 bool is_pending(const void* at)
@@ -43,7 +78,21 @@ bool is_pending(const void* at)
 
 extern "C" {
 void fake_fail(const char* what, int nth, int times) { fails[what] = {nth, times}; }
-void fake_reset() { fails.clear(); freeze_slot = -1; pending.clear(); violations = 0; }
+void fake_reset()
+{
+    fails.clear();
+    freeze_slot = -1;
+    pending.clear();
+    streams.clear();
+    launched.clear();
+    violations = unordered = segments = 0;
+    busy = false;
+    capturing = nullptr;
+}
+void fake_busy(int on) { busy = on; }
+void fake_capture(void* stream) { capturing = (hipStream_t)stream; }
+int fake_unordered() { return unordered; }
+int fake_segments() { return segments; }
 int fake_calls(const char* what) { return calls[what]; }
 int fake_violations() { return violations; }
 void fake_freeze(int slot, int at_frame) { freeze_slot = slot; freeze_at = at_frame; }
@@ -80,18 +129,40 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
     memcpy(d, s, n);
     return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t)
+hipError_t hipStreamSynchronize(hipStream_t s)
 {
     if (hipError_t e = call("hipStreamSynchronize")) return e;
     done_up_to(seq);
+    waited(s);
     return hipSuccess;
 }
+hipError_t hipStreamQuery(hipStream_t s)
+{
+    if (busy) return hipErrorNotReady;
+    waited(s);
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
+{
+    if (hipError_t x = call("hipStreamWaitEvent")) return x;
+    std::lock_guard<std::mutex> l(order);
+    merge(streams[s], reinterpret_cast<Event*>(e)->clock);
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c)
+{
+    *c = s && s == capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = reinterpret_cast<hipEvent_t>(new Event); return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { *e = reinterpret_cast<hipEvent_t>(new Event); return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { delete reinterpret_cast<Event*>(e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t)
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 {
     if (hipError_t x = call("hipEventRecord")) return x;
+    std::lock_guard<std::mutex> l(order);
     reinterpret_cast<Event*>(e)->seq = seq;
+    reinterpret_cast<Event*>(e)->clock = streams[s];
     return hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) { done_up_to(reinterpret_cast<Event*>(e)->seq); return hipSuccess; }
@@ -114,18 +185,20 @@ hipError_t launch_encoder(const EncoderPtrs&, int, const PnWindows&, int, const 
 }
 
 // frame f of a request of n frames: all of its values are 1000 n + f
-hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int, hipStream_t, hipEvent_t*)
+hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int, hipStream_t stream, hipEvent_t*)
 {
-    for (int s = 0; s < cfg.n_blocks; ++s) {
-        if (!d.live[s] || d.done[s]) continue;
-        if (s == freeze_slot && d.t[s] >= freeze_at) {
-            d.failed[s] = d.done[s] = 1;
-            *d.fault = 1;
-            continue;
+    ordered(stream, cfg.seg_steps > 0);
+    for (int k = 0; k < std::max(cfg.seg_steps, 1); ++k)
+        for (int s = 0; s < cfg.n_blocks; ++s) {
+            if (!d.live[s] || d.done[s]) continue;
+            if (s == freeze_slot && d.t[s] >= freeze_at) {
+                d.failed[s] = d.done[s] = 1;
+                *d.fault = 1;
+                continue;
+            }
+            std::fill_n(d.mel_ring + ((size_t)s * d.max_steps + d.t[s]) * N_MEL, N_MEL, 1000.f * d.n_steps[s] + d.t[s]);
+            if (++d.t[s] >= d.n_steps[s]) d.done[s] = 1;
         }
-        std::fill_n(d.mel_ring + ((size_t)s * d.max_steps + d.t[s]) * N_MEL, N_MEL, 1000.f * d.n_steps[s] + d.t[s]);
-        if (++d.t[s] >= d.n_steps[s]) d.done[s] = 1;
-    }
     return hipSuccess;
 }
 hipError_t launch_set_live(const DevPtrs& d, const LiveArgs& a, hipStream_t)

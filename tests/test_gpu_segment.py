@@ -90,3 +90,76 @@ def test_segment_with_a_large_attention_vector(weights_bf16):
     assert np.abs(w["v"]).sum() > 30
     frames = [20, 33]
     _same(_both(w, [70, 600], frames, [33]), frames)
+
+
+def _job(n, weights, max_pool, frames, use_graph=True, seed=0):
+    """A pool of n requests and the frames they give alone on the GPU."""
+    rng = np.random.default_rng(seed)
+    lengths = [int(x) for x in rng.integers(5, 90, size=n)]
+    enc = [synth.round_to_bf16(rng.standard_normal((L, 512)).astype(np.float32)) for L in lengths]
+    wl = synth.small_workload(n, 5, 90, 8, 8, seed=31, bf16=weights["bf16"])
+    make = lambda: make_pool(wl, weights["w"], max_pool=max_pool, max_enc_len=90, max_steps=80, chunk_frames=40, use_graph=use_graph)
+    pool = make()
+    ids = pool.add_requests(enc, [frames] * n)
+    pool.step_n(frames)
+    pool.sync()
+    want = [pool.drain_all(r) for r in ids]
+    pool.close()
+    pool = make()
+    return pool, pool.add_requests(enc, [frames] * n), want
+
+
+@pytest.mark.parametrize("n", [1, 16, 20, 32, 40, 48])
+def test_segments_beside_other_work(n, weights_bf16):
+    """Another stream keeps the compute units busy with products that end by themselves: a segment's workgroups start late, in parts; the
+    frames do not change and no wait runs out."""
+    import torch
+    say(f"case: segments of {n} slots while a second stream runs large matrix products")
+    pool, ids, want = _job(n, dict(w=weights_bf16, bf16=True), 48, 24)
+    side = torch.cuda.Stream(device=pool.device)
+    a = torch.randn(4096, 4096, device=pool.device)
+    with torch.cuda.stream(side):
+        for _ in range(40):
+            a = (a @ a) * 1e-4
+    for k in (4, 1, 7, 12):
+        pool.step_n(k)
+    pool.sync()                      # raises if a wait ran out
+    side.synchronize()
+    for r, w in zip(ids, want):
+        np.testing.assert_array_equal(pool.drain_all(r), w)
+    pool.close()
+
+
+@pytest.mark.parametrize("threads", [False, True])
+def test_segments_of_several_pools(threads, weights_bf16, weights_fp32):
+    """Pools of one and of three tiles, and a fp32 pool whose steps are launches of their own, stepped in turn without a wait, by one
+    thread and by a thread each: the frames of each alone."""
+    import threading
+    say(f"case: three pools, {'a thread each' if threads else 'one thread'}")
+    jobs = [_job(3, dict(w=weights_bf16, bf16=True), 16, 64, seed=1), _job(40, dict(w=weights_bf16, bf16=True), 48, 64, seed=2),
+            _job(5, dict(w=weights_fp32, bf16=False), 16, 64, seed=3)]
+    errors = []
+
+    def drive(pool, counts):
+        try:
+            for k in counts:
+                pool.step_n(k)
+        except BaseException as e:
+            errors.append(e)
+
+    if threads:
+        ts = [threading.Thread(target=drive, args=(job[0], [1, 3] * 16)) for job in jobs]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+    else:
+        for _ in range(16):
+            for job in jobs:
+                drive(job[0], [1, 3])
+    assert not errors
+    for pool, ids, want in jobs:
+        pool.sync()                  # raises if a wait ran out
+        for r, w in zip(ids, want):
+            np.testing.assert_array_equal(pool.drain_all(r), w)
+        pool.close()

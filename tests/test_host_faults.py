@@ -2,7 +2,9 @@
 memory (fake_hip.cpp) in which any call can be made to fail."""
 import ctypes as C
 import os
+import random
 import subprocess
+import threading
 
 import numpy as np
 import pytest
@@ -30,6 +32,7 @@ def lib(tmp_path_factory):
         getattr(L, f).argtypes = [C.c_void_p]
     L.fake_fail.argtypes = [C.c_char_p, C.c_int, C.c_int]
     L.fake_calls.argtypes = [C.c_char_p]
+    L.fake_capture.argtypes = [C.c_void_p]
     return L
 
 
@@ -44,14 +47,15 @@ def _arena(nbytes):
 
 
 class FakePool:
-    def __init__(self, lib, weights, max_pool=4, max_steps=64, chunk=8):
+    def __init__(self, lib, weights, max_pool=4, max_steps=64, chunk=8, stream=1, segments=False):
         self.L, self.chunk = lib, chunk
-        cfg = binding.make_config(synth.DIMS, max_pool=max_pool, max_enc_len=16, max_steps=max_steps, chunk_frames=chunk, use_graph=False)
+        cfg = binding.make_config(synth.DIMS, max_pool=max_pool, max_enc_len=16, max_steps=max_steps, chunk_frames=chunk, use_graph=segments,
+                                  bf16=segments)
         n = int(lib.tts_pool_workspace_bytes(C.byref(cfg)))
         self._arena, at = _arena(n)
         w = binding.TtsWeights(*[weights[k].ctypes.data_as(C.POINTER(C.c_float)) for k in binding.WEIGHT_FIELDS])
         self.h = C.c_void_p()
-        assert lib.tts_pool_create(C.byref(cfg), C.byref(w), at, C.c_size_t(n), C.c_void_p(1), C.byref(self.h)) == 0, lib.tts_last_error()
+        assert lib.tts_pool_create(C.byref(cfg), C.byref(w), at, C.c_size_t(n), C.c_void_p(stream), C.byref(self.h)) == 0, lib.tts_last_error()
 
     def add(self, n_steps):
         enc, rid = np.zeros((3, synth.DIMS["enc_dim"]), np.float32), C.c_int64()
@@ -60,6 +64,9 @@ class FakePool:
 
     def step_n(self, n):
         assert self.L.tts_pool_step_n(self.h, n, None) == 0
+
+    def sync(self):
+        assert self.L.tts_pool_sync(self.h) == 0
 
     def drain(self, rid):
         """(status, first value of every frame, finished)"""
@@ -190,3 +197,127 @@ def test_every_drain_that_hands_out_frames_waits_for_the_stream(lib, weights_fp3
     assert pool.drain(a)[0] == binding.TTS_E_HIP
     assert pool.drain(a) == (0, _frames(24, 16, 8), True)
     pool.close()
+
+
+def test_pools_of_one_thread_that_are_waited_for_cost_each_other_nothing(lib, weights_fp32):
+    """Pools whose steps are segments (two-byte) and one whose steps are launches of their own, each waited for before the next is used:
+    nothing is recorded and nobody waits."""
+    pools = [FakePool(lib, weights_fp32, stream=1, segments=True), FakePool(lib, weights_fp32, stream=2, segments=True),
+             FakePool(lib, weights_fp32, stream=3)]
+    before = [lib.fake_calls(f) for f in (b"hipEventRecord", b"hipStreamWaitEvent")]
+    for k in range(3):
+        for p in pools:
+            rid = p.add(8)
+            p.step_n(8)
+            assert p.drain(rid) == (0, _frames(8, 0, 8), True)
+    assert lib.fake_segments() == 6 and lib.fake_unordered() == 0
+    assert [lib.fake_calls(f) for f in (b"hipEventRecord", b"hipStreamWaitEvent")] == before
+    for p in pools:
+        p.close()
+
+
+@pytest.mark.parametrize("busy", [0, 1])
+def test_segments_of_several_pools_follow_each_other(lib, weights_fp32, busy):
+    """One thread, nobody waited for: a segment is ordered behind the other pools' launches so far, a step behind their segments."""
+    lib.fake_busy(busy)
+    pools = [FakePool(lib, weights_fp32, stream=1, segments=True), FakePool(lib, weights_fp32, stream=2, segments=True),
+             FakePool(lib, weights_fp32, stream=3), FakePool(lib, weights_fp32, stream=2)]
+    r = random.Random(3)
+    for p in pools:
+        for n in (60, 50):
+            p.add(n)
+    for _ in range(80):
+        p = r.choice(pools)
+        p.step_n(r.randrange(1, 4))
+        if r.random() < 0.2:
+            r.choice(pools).sync()
+    us = (C.c_float * 6)()
+    assert lib.tts_pool_kernel_times(pools[2].h, 2, us, 6, None) == 0
+    pools[0].step_n(1)
+    assert lib.fake_segments() > 10 and lib.fake_unordered() == 0
+    for p in pools:
+        p.close()
+
+
+def test_segments_of_pools_of_several_threads_follow_each_other(lib, weights_fp32):
+    """A thread per pool, one of them created while the others step, one thread that ends and hands its pool on."""
+    pools = [FakePool(lib, weights_fp32, stream=1, segments=True, max_steps=4096), FakePool(lib, weights_fp32, stream=2, segments=True, max_steps=4096)]
+    errors = []
+
+    def drive(p, seed, calls):
+        try:
+            r = random.Random(seed)
+            p.add(4000)
+            for _ in range(calls):
+                p.step_n(r.randrange(1, 4))
+                if r.random() < 0.3:
+                    p.sync()
+        except BaseException as e:
+            errors.append(e)
+
+    def late():
+        try:
+            p = FakePool(lib, weights_fp32, stream=3, max_steps=4096)
+            drive(p, 7, 100)
+            p.close()
+        except BaseException as e:
+            errors.append(e)
+
+    lib.fake_busy(1)
+    drive(pools[0], 1, 3)                      # this thread alone, not waited for
+    threads = [threading.Thread(target=drive, args=(pools[0], 2, 200)), threading.Thread(target=drive, args=(pools[1], 3, 200)),
+               threading.Thread(target=late)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    drive(pools[1], 4, 20)
+    assert not errors
+    assert lib.fake_segments() > 100 and lib.fake_unordered() == 0
+    for p in pools:
+        p.close()
+
+
+def test_segment_beside_a_stream_that_is_being_captured(lib, weights_fp32):
+    """A stream that its owner is capturing is left alone, by the same thread and by another one."""
+    a, b = FakePool(lib, weights_fp32, stream=1, segments=True), FakePool(lib, weights_fp32, stream=2, segments=True)
+    a.add(40), b.add(40)
+    a.step_n(2)
+    a.sync()
+    a.step_n(2)
+    lib.fake_busy(1)
+    lib.fake_capture(1)
+    before = [lib.fake_calls(f) for f in (b"hipEventRecord", b"hipStreamWaitEvent", b"hipStreamSynchronize")]
+    b.step_n(2)
+    assert [lib.fake_calls(f) for f in (b"hipEventRecord", b"hipStreamWaitEvent", b"hipStreamSynchronize")] == before
+    t = threading.Thread(target=b.step_n, args=(2,))
+    t.start()
+    t.join()
+    assert lib.fake_calls(b"hipStreamSynchronize") == before[2]
+    lib.fake_capture(None)
+    a.close()
+    b.close()
+
+
+def test_neighbours_event_that_cannot_be_had(lib, weights_fp32):
+    """A wait that cannot be queued: the call says so and steps nothing; an event that cannot be recorded: the stream is waited for."""
+    a, b = FakePool(lib, weights_fp32, stream=1, segments=True), FakePool(lib, weights_fp32, stream=2, segments=True)
+    ra, rb = a.add(8), b.add(8)
+    lib.fake_busy(1)
+    a.step_n(2)
+    lib.fake_fail(b"hipStreamWaitEvent", 1, 1)
+    assert lib.tts_pool_step_n(b.h, 2, None) == binding.TTS_E_HIP
+    n = C.c_int()
+    assert lib.tts_pool_frames(b.h, C.c_int64(rb), C.byref(n), None) == 0 and n.value == 0
+    b.step_n(2)
+    t = threading.Thread(target=a.step_n, args=(2,))
+    t.start()
+    t.join()
+    lib.fake_fail(b"hipEventRecord", 1, 1)
+    b.step_n(2)
+    a.step_n(4)
+    b.step_n(4)
+    assert lib.fake_unordered() == 0
+    assert a.drain(ra) == (0, _frames(8, 0, 8), True) and b.drain(rb) == (0, _frames(8, 0, 8), True)
+    a.close()
+    b.close()
