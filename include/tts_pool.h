@@ -165,7 +165,10 @@ int tts_pool_step(tts_pool *pool, int *out_n_active);
  * slots with two-byte weights and memory a step that follows another step of
  * the same call is two kernel launches instead of three, and while no active
  * request's slot lies above 48 and there is no stop threshold up to 64 steps
- * are one kernel launch). */
+ * are one kernel launch).
+ * On a stream that the caller is capturing the steps go into his graph one by
+ * one.  The pool counts them as taken by this call, so that graph is launched
+ * once, before anything else of the pool. */
 int tts_pool_step_n(tts_pool *pool, int n, int64_t *out_frames);
 
 /*

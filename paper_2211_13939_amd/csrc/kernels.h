@@ -18,7 +18,8 @@ struct StepLaunch {
     int att_tail;   // 1 (pools with d.p_x only): the step's last launch also forms the attention LSTM of the next step, which then
                     // has att_lead = 0.  The membership and the requests' states must not change between the two steps.
     int seg_steps;  // > 0: not one step but this many, as one launch (segment.hip): pools with d.seg_x and no stop threshold, n_blocks <= SEG_TILES * SEG_SLOTS,
-                    // at least one running request takes each of the steps
+                    // at least one running request takes each of the steps, the stream is not being captured (a replay would find the words
+                    // of the replay before)
     int seg_set;    // which of the two sets of d.seg_x it uses: in turn, launch by launch
     int seg_empty;  // tiles of the other set it has to empty: those that the launch before used
     int pre_gates;  // 2: the projection's launch also forms the next step's gate pre-sums (d.pre_att / d.pre_dec; fp32: n_tiles <= PRESUM_SMALL_TILES),

@@ -946,10 +946,6 @@ hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, i
     const int n_tiles = (n_slots + 15) / 16;
     if (!d.seg_x || n_slots < 1 || n_slots > d.seg_slots || n_steps < 1 || (set & ~1) || empty_tiles < 0 || empty_tiles * SEG_SLOTS > d.seg_slots || d.stop_threshold >= 0.f)
         return hipErrorInvalidValue;
-    // which set of words is in use changes from call to call, on the host: a replayed launch would find the words of the replay before
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipError_t e = hipStreamIsCapturing(s, &capture)) return e;
-    if (capture != hipStreamCaptureStatusNone) return hipErrorStreamCaptureUnsupported;
     const size_t tile_bytes = segment_tile_bytes(d.max_enc_len), set_bytes = d.seg_slots / SEG_SLOTS * tile_bytes;
     char* words = static_cast<char*>(d.seg_x);
     static_assert(4 * SEG_XCD_WGS == 32 + 64 && SEG_TILES <= 4, "ATT and DEC; a projection per XCD");

@@ -689,13 +689,12 @@ static void chain_steps(const tts_pool* p, StepLaunch* sl, int i, int nsteps)
 // steps are one hipGraph launch (captured once per (nsteps, pool bucket,
 // parity)); requests that reach their end inside the graph are skipped by the
 // kernels through their device-side done flag.
-static int launch_steps(tts_pool* p, int n_active, int nsteps)
+static int launch_steps(tts_pool* p, int nsteps, bool as_graph)
 {
     StepLaunch sl;
     sl.wdtype = p->cfg.weight_dtype;
     sl.mdtype = p->cfg.memory_dtype;
-    (void)n_active;
-    if (!p->cfg.use_graph) {
+    if (!as_graph) {
         shape_for(p, p->slot_span, &sl);
         for (int i = 0; i < nsteps; ++i) {
             chain_steps(p, &sl, i, nsteps);
@@ -748,9 +747,7 @@ static int segment_steps(const tts_pool* p, int n)
     for (int sl : p->book->active()) most = std::max(most, p->book->slot(sl).n_steps - p->book->slot(sl).t);
     return std::min({n, most, MAX_SEGMENT_STEPS});
 }
-// *taken = false: the stream is being captured.  A replayed segment would find the words of the replay before, so a captured call takes its steps
-// one by one, as it would without segments.
-static int launch_segment_steps(tts_pool* p, int g, bool* taken)
+static int launch_segment_steps(tts_pool* p, int g)
 {
     StepLaunch sl;
     sl.wdtype = p->cfg.weight_dtype;
@@ -759,10 +756,7 @@ static int launch_segment_steps(tts_pool* p, int g, bool* taken)
     sl.seg_steps = g;
     sl.seg_set = p->seg_set;
     sl.seg_empty = p->seg_used;
-    const hipError_t e = launch_step(p->d, sl, p->parity, p->stream);
-    *taken = e != hipErrorStreamCaptureUnsupported;
-    if (!*taken) return TTS_OK;
-    HIP_TRY(e);
+    HIP_TRY(launch_step(p->d, sl, p->parity, p->stream));
     p->seg_set ^= 1;
     p->seg_used = sl.n_tiles;
     return TTS_OK;
@@ -782,7 +776,10 @@ static int step_impl(tts_pool* p, int n, int64_t* out_frames, int* out_last_acti
     int64_t frames = 0;
     int last = 0;
     if (p->timing) HIP_TRY(hipEventRecord(p->ev0, p->stream));
-    Turn turn(p->resident, being_captured(p));
+    // A captured call takes its steps one by one: a graph cannot be captured or launched inside another capture, and which set of words a
+    // segment uses changes with every launch, on the host.
+    const bool captured = being_captured(p);
+    Turn turn(p->resident, captured);
     int i = 0;
     while (i < n) {
         const int n_active = (int)p->book->active().size();
@@ -793,18 +790,17 @@ static int step_impl(tts_pool* p, int n, int64_t* out_frames, int* out_last_acti
         // graphs exist for powers of two up to MAX_GRAPH_STEPS and for one whole chunk (the paper's iteration: a
         // segment of 40 steps as one graph measured 0.05 - 0.2 us per step faster than as graphs of 32 and 8)
         int g = 1;
-        bool as_one = false;
-        const int seg = segment_steps(p, n - i);
+        const int seg = captured ? 0 : segment_steps(p, n - i);
         HIP_TRY(turn.before(seg > 0 ? GANG_SEGMENT : GANG_STEPS));
-        if (seg > 0 && (rc = launch_segment_steps(p, seg, &as_one))) return rc;
-        if (as_one) {
+        const bool as_graph = p->cfg.use_graph && !captured;
+        if (seg > 0) {
             g = seg;
-        } else if (p->cfg.use_graph) {
+        } else if (as_graph) {
             while (g * 2 <= n - i && g * 2 <= MAX_GRAPH_STEPS) g *= 2;
             const int chunk = p->cfg.chunk_frames;
             if (chunk > g && chunk <= n - i && chunk <= MAX_CHUNK_GRAPH_STEPS) g = chunk;
         }
-        if (!as_one && (rc = launch_steps(p, n_active, g))) return rc;
+        if ((rc = seg > 0 ? launch_segment_steps(p, g) : launch_steps(p, g, as_graph))) return rc;
         for (int k = 0; k < g; ++k) {
             p->parity ^= 1;
             frames += p->book->step(p->parity);

@@ -163,3 +163,25 @@ def test_segments_of_several_pools(threads, weights_bf16, weights_fp32):
         for r, w in zip(ids, want):
             np.testing.assert_array_equal(pool.drain_all(r), w)
         pool.close()
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("n", [1, 6, 7])
+def test_captured_steps(n, bf16, weights_bf16, weights_fp32):
+    """A call on a stream that is being captured, its graph launched once, between calls that are not."""
+    import torch
+    say(f"case: {n} steps captured, {'bf16' if bf16 else 'fp32'}")
+    pool, ids, want = _job(3, dict(w=weights_bf16 if bf16 else weights_fp32, bf16=bf16), 16, 40)
+    pool.step_n(5)
+    pool.sync()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=pool.stream):
+        pool.step_n(n)
+    with torch.cuda.stream(pool.stream):
+        graph.replay()
+    pool.step_n(35 - n)
+    pool.sync()
+    for r, w in zip(ids, want):
+        np.testing.assert_array_equal(pool.drain_all(r), w)
+    del graph
+    pool.close()

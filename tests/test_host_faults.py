@@ -299,6 +299,27 @@ def test_segment_beside_a_stream_that_is_being_captured(lib, weights_fp32):
     b.close()
 
 
+def test_captured_call_takes_its_steps_one_by_one(lib, weights_fp32):
+    """(The runtime of this test has no graphs: steps that were captured as a graph would fail the call.)"""
+    a, b = FakePool(lib, weights_fp32, stream=1, segments=True), FakePool(lib, weights_fp32, stream=2, segments=True)
+    ra, rb = a.add(20), b.add(20)
+    a.step_n(2)
+    b.step_n(2)
+    segments, waits = lib.fake_segments(), lib.fake_calls(b"hipStreamWaitEvent")
+    lib.fake_busy(1)
+    lib.fake_capture(1)
+    a.step_n(7)
+    lib.fake_capture(None)
+    assert lib.fake_segments() == segments == 2 and lib.fake_calls(b"hipStreamWaitEvent") == waits
+    a.step_n(11)
+    b.step_n(18)
+    assert lib.fake_segments() == 4
+    for p, r in ((a, ra), (b, rb)):
+        got = [f for _ in range(3) for f in p.drain(r)[1]]
+        assert got == _frames(20, 0, 20)
+        p.close()
+
+
 def test_neighbours_event_that_cannot_be_had(lib, weights_fp32):
     """A wait that cannot be queued: the call says so and steps nothing; an event that cannot be recorded: the stream is waited for."""
     a, b = FakePool(lib, weights_fp32, stream=1, segments=True), FakePool(lib, weights_fp32, stream=2, segments=True)
