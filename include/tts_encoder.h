@@ -86,6 +86,8 @@ int tts_encoder_run(tts_encoder *enc, const int *ids, const int *lens, int n, fl
  * With fp32 weights the workgroups of the recurrence hand h to each other and poll for it at most `polls` times (some
  * milliseconds by default); if other work on the GPU keeps one of them from starting for so long, the call's results are
  * formed again without such hand-overs, bit for bit the same, at about twenty times a step's time.  0 is allowed.
+ * In a call of at most 512 tokens (fp32: 384) it also bounds the waits of the convolutions' one launch, from above (24
+ * polls by default): what has not come by then a workgroup forms itself, bit for bit the same.
  */
 int tts_encoder_set_wait_polls(tts_encoder *enc, int polls);
 

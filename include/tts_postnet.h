@@ -97,6 +97,13 @@ int tts_postnet_run(tts_postnet *pn, const float *d_mel, const int *win_len, con
 int tts_postnet_run_static(tts_postnet *pn, const float *d_mel, const int *win_len, const int *keep_from, int n,
                            float *d_out);
 
+/*
+ * A call of at most 768 frames (fp32: 384) is one launch, whose workgroups hand each other their outputs and poll for them;
+ * what does not come because other work on the GPU keeps a workgroup from starting, those that run form themselves, bit
+ * for bit the same.  They do so after at most `polls` polls (by default after 24, some 20 us).  0 is allowed: nobody waits.
+ */
+int tts_postnet_set_wait_polls(tts_postnet *pn, int polls);
+
 /* Device time of the last tts_postnet_run in milliseconds (HIP events on the stream); waits for the stream. */
 int tts_postnet_elapsed_ms(tts_postnet *pn, float *out_ms);
 

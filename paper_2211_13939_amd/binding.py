@@ -39,7 +39,7 @@ EXPORTS = (
     "tts_book_create", "tts_book_add", "tts_book_step", "tts_book_drain", "tts_book_retire",
     "tts_book_slot", "tts_book_compact", "tts_book_destroy",
     "tts_pool_chunk_window",
-    "tts_postnet_workspace_bytes", "tts_postnet_create", "tts_postnet_run", "tts_postnet_run_static", "tts_postnet_elapsed_ms",
+    "tts_postnet_workspace_bytes", "tts_postnet_create", "tts_postnet_run", "tts_postnet_run_static", "tts_postnet_set_wait_polls", "tts_postnet_elapsed_ms",
     "tts_postnet_destroy",
     "tts_vocoder_workspace_bytes", "tts_vocoder_create", "tts_vocoder_run", "tts_vocoder_elapsed_ms",
     "tts_vocoder_destroy",
@@ -157,6 +157,7 @@ def lib() -> C.CDLL:
                                      C.POINTER(vp)]
     L.tts_postnet_run.argtypes = [vp, vp, _ip, _ip, C.c_int, vp]
     L.tts_postnet_run_static.argtypes = [vp, vp, _ip, _ip, C.c_int, vp]
+    L.tts_postnet_set_wait_polls.argtypes = [vp, C.c_int]
     L.tts_postnet_elapsed_ms.argtypes = [vp, _fp]
     L.tts_postnet_destroy.restype = None
     L.tts_postnet_destroy.argtypes = [vp]
@@ -509,6 +510,9 @@ class Postnet:
             res.append(out[r:r + t - k])
             r += t - k
         return res
+
+    def set_wait_polls(self, polls: int) -> None:
+        _check(lib().tts_postnet_set_wait_polls(self._h, int(polls)))
 
     def elapsed_ms(self) -> float:
         ms = C.c_float()

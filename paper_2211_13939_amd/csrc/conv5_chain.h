@@ -19,7 +19,8 @@
 // waits for: those that do so take the blocks of all layers in turn, from a counter, and form what is not there.  A block waits for blocks
 // in front of it only, which others that run have taken or stored, so somebody always goes on; a block formed twice is stored twice with the same bits.
 // So where the compute units are taken by other work, or by launches like this one on other streams that hold them while they wait, the
-// workgroups that run go on alone, and the others find everything done.
+// workgroups that run go on alone, and the others find everything done.  And should one that has taken a block not get on with it (half a
+// second), a workgroup that waits for it forms every block it needs by itself, layer by layer: then nothing is left to wait for.
 #pragma once
 #include "conv5_kernels.h"
 #include "words.h"
@@ -27,8 +28,8 @@
 namespace tts {
 
 constexpr int CHAIN_RTS = PN_CHANNELS / 16;                // row tiles of an inner layer: workgroups per column group
-constexpr int CHAIN_POLLS = 24;                            // rounds of polls (0.8 us each) before a workgroup helps itself, the first time
-constexpr int CHAIN_POLLS_THEN = 4;                        // ... and after that
+constexpr int CHAIN_POLLS_THEN = 4;                        // CHAIN_POLLS, after the first time
+constexpr int CHAIN_POLLS_LATE = 1 << 20;                  // ... for what others have taken, before it forms that too
 
 template <typename XT, int CT_> struct ChainGeom {
     static constexpr int C = PN_CHANNELS, KB = Frag<XT>::KB, EPL = Frag<XT>::EPL;
@@ -55,7 +56,8 @@ struct ChainArgs {
     int* state;                        // [0] which set is in use, [1] workgroups that are through, [2 + set] KB in use of it,
                                        // [4] blocks taken by workgroups that help themselves
     int groups;                        // column groups
-    int polls;
+    int polls;                         // CHAIN_POLLS or less (1: most take blocks from the counter; 0: nobody waits, every workgroup forms
+                                       // what it needs by itself)
 };
 
 // Where a wave's share of a row tile's weights lies: fragments first, first + step, ...  A fragment's place is a scalar offset, all loads share
@@ -205,16 +207,20 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
         if constexpr (sizeof(XT) == 2) x.put2(pack2<XT>(y0, y1), pack2<XT>(y2, y3), at, block(l, cg, rt));
         else x.put4(floatx4{y0, y1, y2, y3}, at, block(l, cg, rt));
     };
-    // What layer l waits for and is not there, formed here: in few registers, which the layers need, and in its own time
-    auto help = [&](int l) __attribute__((always_inline)) {
-        const int per_layer = p.groups * CHAIN_RTS;
+    // What layer l waits for and is not there, formed here: in few registers, which the layers need, and in its own time.  Blocks from the
+    // counter (one taken is formed, whichever layer it is of); alone: all blocks in front of layer l, one behind the other, from the first
+    // on, so that what a block is made of has been seen or stored by this workgroup
+    auto help = [&](int l, bool alone) __attribute__((always_inline)) {
+        int n_groups = p.groups;
+        asm volatile("" : "+s"(n_groups));         // (none of this is made ahead of the layers)
+        const int per_layer = n_groups * CHAIN_RTS;
 #pragma unroll 1
-        for (int j = 0; j + 1 < l * per_layer;) {
-            if (tid == 0) s_taken = __hip_atomic_fetch_add(p.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int j = -1; j + 1 < l * per_layer;) {
+            if (tid == 0) s_taken = alone ? j + 1 : __hip_atomic_fetch_add(p.state + 4, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
-            j = s_taken;                           // a block taken is formed, whichever layer it is of
+            j = s_taken;
             if (j >= LAYERS * per_layer) break;
-            const int k = j / per_layer, cg = j / CHAIN_RTS % p.groups, rt = j % CHAIN_RTS, NKT = k == 0 ? NKT0 : G::NKT, NKF = NKT / PN_TAPS;
+            const int k = j / per_layer, cg = j / CHAIN_RTS % n_groups, rt = j % CHAIN_RTS, NKT = k == 0 ? NKT0 : G::NKT, NKF = NKT / PN_TAPS;
             Words::again();
             if (__syncthreads_and(wave >= G::SUBS || Words::full(x.look4(lane * 16, block(k, cg, rt) + wave * 1024)))) continue;
             columns_of(cg, job.windows());
@@ -222,20 +228,22 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
             if (k == 0) job.template first<G>(cg * G::COLS - PN_HALO, s_x);
             else {
 #pragma unroll 1
-                for (int i = tid; i < G::ROWS * CHAIN_RTS * G::PIECES; i += PN_THREADS) {      // (all there: seen, or stored here)
+                for (int i = tid; i < G::ROWS * CHAIN_RTS * G::PIECES; i += PN_THREADS) {
                     const int plane = i / G::ROWS, row = i % G::ROWS, c = (cg * G::COLS - PN_HALO) + row;
                     u32x4_t v = {0u, 0u, 0u, 0u};
-                    bool in = c < 0 || c >= p.groups * G::COLS;
+                    bool in = c < 0 || c >= n_groups * G::COLS;
 #pragma unroll 1
-                    for (int spin = 0; spin < 1 << 20 && !in; ++spin) {
+                    for (int spin = 0; spin < CHAIN_POLLS_LATE && !in; ++spin) {
                         Words::again();
                         v = x.look4(block(k - 1, c / G::COLS, plane / G::PIECES) + (c % G::COLS * G::PIECES + plane % G::PIECES) * 16, 0);
                         in = Words::full(v);
                     }
+                    if (!in) s_taken = -1;         // (never alone)
                     *reinterpret_cast<u32x4_t*>(&s_x[chain_at<G>(plane, row)]) = v;
                 }
             }
             __syncthreads();
+            if (s_taken < 0) break;
             const unsigned there = k == 0 ? stored(cg, rt) : EMPTY;
             const ChainWeights W(p.W[k], NKT, rt, wave, PN_WAVES);
             floatx4 acc[CT];
@@ -285,10 +293,18 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
             zero_rows();
         }
         if (__builtin_expect(!stage(l - 1, my_cg, halo, polls), 0)) {
-            help(l);
+            bool in = false;
+            if (p.polls > 0) {
+                help(l, false);
+                if (G::ON_TOP) zero_rows();
+                in = stage(l - 1, my_cg, halo, CHAIN_POLLS_LATE);
+            }
+            if (!in) {
+                help(l, true);
+                if (G::ON_TOP) zero_rows();
+                stage(l - 1, my_cg, halo, CHAIN_POLLS_LATE);
+            }
             polls = min(polls, CHAIN_POLLS_THEN);
-            if (G::ON_TOP) zero_rows();
-            stage(l - 1, my_cg, halo, 1 << 20);
             const ChainWeights mine = weights_of(l);
 #pragma unroll
             for (int i = 0; i < NA; ++i) a[i] = mine.at(i);

@@ -162,6 +162,7 @@ extern "C" int tts_postnet_create(const tts_postnet_config* cfg, const tts_postn
     p->d.n_mel = cfg->n_mel;
     p->d.chain_words = base + lay.chain;
     p->d.chain_state = (int*)(base + lay.chain_state);
+    p->d.wait_polls = CHAIN_POLLS;
     p->d.chain_set_bytes = (int)chain_set_bytes(bf ? 2 : 4, cfg->max_columns, PN_LAYERS - 1);
     *out = p;
     return TTS_OK;
@@ -239,6 +240,14 @@ extern "C" int tts_postnet_run_static(tts_postnet* p, const float* d_mel, const 
     d.cmeta = reinterpret_cast<int*>(base + 2 * PN_STATIC_ACT);
     d.orow = reinterpret_cast<int*>(base + 2 * PN_STATIC_ACT + PN_STATIC_TABLE);
     return run_batch(p, d, TTS_POSTNET_STATIC_MAX_COLUMNS, false, d_mel, win_len, keep_from, n, d_out);
+}
+
+extern "C" int tts_postnet_set_wait_polls(tts_postnet* p, int polls)
+{
+    if (!p) return fail(TTS_E_INVAL, "postnet is null");
+    if (polls < 0) return fail(TTS_E_INVAL, "polls = %d is negative", polls);
+    p->d.wait_polls = polls;
+    return TTS_OK;
 }
 
 extern "C" int tts_postnet_elapsed_ms(tts_postnet* p, float* out_ms)

@@ -165,7 +165,7 @@ hipError_t launch_postnet_chain(const PostnetPtrs& d, int wdtype, const PnWindow
     p.words = d.chain_words;
     p.state = d.chain_state;
     p.set_bytes = d.chain_set_bytes;
-    p.polls = CHAIN_POLLS;
+    p.polls = d.wait_polls < CHAIN_POLLS ? d.wait_polls : CHAIN_POLLS;
     auto go = [&](auto job, auto type) {
         job.w = w;
         job.mel = mel;

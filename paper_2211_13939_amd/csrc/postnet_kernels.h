@@ -17,6 +17,7 @@ constexpr int PN_COUT_LAST = 80;
 constexpr int CHAIN_GROUPS = 8;
 constexpr int CHAIN_LAYERS = 4;
 constexpr int CHAIN_STATE_BYTES = 32;
+constexpr int CHAIN_POLLS = 24;      // rounds of polls (0.8 us each) before a workgroup helps itself, the first time
 constexpr int chain_tiles(size_t value_bytes) { return value_bytes == 2 ? 2 : 1; }
 constexpr int chain_most_columns(size_t value_bytes) { return CHAIN_GROUPS * 3 * chain_tiles(value_bytes) * 16; }
 constexpr int chain_column_bytes(size_t value_bytes) { return 16 * (int)value_bytes; }      // of one row tile's output
@@ -50,6 +51,7 @@ struct PostnetPtrs {
     char* chain_words;          // calls that are one launch (conv5_chain.h): two sets of words, and the words that say which is in use;
     int* chain_state;           // null: no call is
     int chain_set_bytes;
+    int wait_polls;             // ... and how often a workgroup polls for the others' words before it forms them itself
 };
 
 // Up to PN_META_WINDOWS windows of one call, as a kernel argument (no host-to-device copy): the device

@@ -1,6 +1,7 @@
 """A small call's convolutions as one launch, whose workgroups hand each other their outputs: the same bits as layer by layer, at the
 edges of column tiles, column groups and of the forms with one, two and three times as many tiles a workgroup; call after call of
-changing sizes (the words of one call are emptied by the next), under capture, and where every wait runs out at once."""
+changing sizes (the words of one call are emptied by the next), under capture, and where the workgroups wait once or not at all for
+each other and form what they need themselves."""
 import numpy as np
 import pytest
 
@@ -64,14 +65,18 @@ def test_encoder_made_for_exactly_the_call(bf16, columns):
 
 
 @pytest.mark.parametrize("bf16", [True, False])
-def test_postnet_calls_as_one_launch(bf16):
-    """Against tts_postnet_run_static, whose calls are a launch per layer, twice over: with the words of other sizes before."""
+@pytest.mark.parametrize("polls", [None, 1, 0])
+def test_postnet_calls_as_one_launch(polls, bf16):
+    """Against tts_postnet_run_static, whose calls are a launch per layer, twice over: with the words of other sizes before.  polls = 1:
+    most workgroups take what is not there from the counter; 0: every workgroup forms all it needs by itself."""
     import torch
     rng = np.random.default_rng(71)
     pn = _postnet(bf16)
-    for columns in EDGES[bf16] + EDGES[bf16][::-2] + (24, 500, 3):
-        wins, keeps = _windows(columns, rng) if columns not in (24, 500) else ([columns // 4] * 4, [0] * 4)
-        say(f"case postnet as one launch: {columns} columns in {len(wins)} windows, {'bf16' if bf16 else 'fp32'}")
+    if polls is not None:
+        pn.set_wait_polls(polls)
+    for columns in EDGES[bf16] + EDGES[bf16][::-2] + (24, 96, 300, 500, 3):
+        wins, keeps = _windows(columns, rng) if columns not in (24, 96, 300, 500) else ([columns // 4] * 4, [0] * 4)
+        say(f"case postnet as one launch: {columns} columns in {len(wins)} windows, {'bf16' if bf16 else 'fp32'}, polls {polls}")
         with torch.cuda.stream(pn.stream):
             mel = torch.from_numpy(rng.standard_normal((columns, 80)).astype(np.float32)).cuda()
             got, want = (torch.full((columns - sum(keeps), 80), float("nan"), device="cuda") for _ in range(2))
@@ -117,10 +122,9 @@ def test_postnet_call_captured_and_replayed(bf16):
 
 
 @pytest.mark.parametrize("bf16,edges", [(True, (1, 16, 17, 255, 256, 257, 511, 512)), (False, (1, 16, 17, 127, 128, 129, 256, 257, 383, 384))])
-@pytest.mark.parametrize("polls", [None, 0])
+@pytest.mark.parametrize("polls", [None, 1, 0])
 def test_encoder_calls_as_one_launch(bf16, edges, polls):
-    """Against the same requests in a call with one more, long one, which is too large for one launch; polls = 0: nobody waits, the
-    workgroups form what they need themselves."""
+    """Against the same requests in a call with one more, long one, which is too large for one launch; polls as above."""
     enc = binding.Encoder(binding.make_encoder_config(max_tokens=1152, max_len=640, bf16=bf16), synth.make_encoder_weights(bf16=bf16))
     more = synth.encoder_ids(600, 99)
     for columns in edges:
