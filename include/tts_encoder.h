@@ -91,6 +91,9 @@ int tts_encoder_run(tts_encoder *enc, const int *ids, const int *lens, int n, fl
  */
 int tts_encoder_set_wait_polls(tts_encoder *enc, int polls);
 
+/* Calls since creation whose convolutions and input projection were one launch. */
+long long tts_encoder_one_launch_calls(const tts_encoder *enc);
+
 /* Device time of the last tts_encoder_run in milliseconds (HIP events on the stream); waits for the stream. */
 int tts_encoder_elapsed_ms(tts_encoder *enc, float *out_ms);
 

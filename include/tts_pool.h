@@ -225,6 +225,9 @@ int tts_pool_n_active(const tts_pool *pool);
 int tts_pool_span(const tts_pool *pool);
 long long tts_pool_moves(const tts_pool *pool);
 
+/* Launches since creation that were several steps in one, or one step as such a launch (tts_pool_step_n). */
+long long tts_pool_segments(const tts_pool *pool);
+
 /* Wait until everything queued on the pool's stream has run.
  * Workgroups of one launch hand each other words (the projection's partial sums, the attention energies of a
  * request) and wait for them a bounded number of polls.  Should such a wait ever run out (the GPU so oversubscribed by

@@ -104,6 +104,9 @@ int tts_postnet_run_static(tts_postnet *pn, const float *d_mel, const int *win_l
  */
 int tts_postnet_set_wait_polls(tts_postnet *pn, int polls);
 
+/* Calls since creation that were one launch. */
+long long tts_postnet_one_launch_calls(const tts_postnet *pn);
+
 /* Device time of the last tts_postnet_run in milliseconds (HIP events on the stream); waits for the stream. */
 int tts_postnet_elapsed_ms(tts_postnet *pn, float *out_ms);
 

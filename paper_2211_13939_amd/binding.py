@@ -33,17 +33,19 @@ EXPORTS = (
     "tts_pool_workspace_bytes", "tts_pool_create", "tts_pool_add_request", "tts_pool_add_requests", "tts_pool_step",
     "tts_pool_step_n", "tts_pool_drain_chunk", "tts_pool_get_stop_logits", "tts_pool_retire",
     "tts_pool_get_state", "tts_pool_set_state", "tts_pool_frames", "tts_pool_size", "tts_pool_n_active",
-    "tts_pool_span", "tts_pool_moves",
+    "tts_pool_span", "tts_pool_moves", "tts_pool_segments",
     "tts_pool_sync", "tts_pool_lost", "tts_pool_set_wait_polls", "tts_pool_timing", "tts_pool_elapsed_ms", "tts_pool_kernel_times", "tts_pool_destroy",
     "tts_last_error",
     "tts_book_create", "tts_book_add", "tts_book_step", "tts_book_drain", "tts_book_retire",
     "tts_book_slot", "tts_book_compact", "tts_book_destroy",
     "tts_pool_chunk_window",
-    "tts_postnet_workspace_bytes", "tts_postnet_create", "tts_postnet_run", "tts_postnet_run_static", "tts_postnet_set_wait_polls", "tts_postnet_elapsed_ms",
+    "tts_postnet_workspace_bytes", "tts_postnet_create", "tts_postnet_run", "tts_postnet_run_static", "tts_postnet_set_wait_polls",
+    "tts_postnet_one_launch_calls", "tts_postnet_elapsed_ms",
     "tts_postnet_destroy",
     "tts_vocoder_workspace_bytes", "tts_vocoder_create", "tts_vocoder_run", "tts_vocoder_elapsed_ms",
     "tts_vocoder_destroy",
-    "tts_encoder_workspace_bytes", "tts_encoder_create", "tts_encoder_run", "tts_encoder_set_wait_polls", "tts_encoder_elapsed_ms",
+    "tts_encoder_workspace_bytes", "tts_encoder_create", "tts_encoder_run", "tts_encoder_set_wait_polls",
+    "tts_encoder_one_launch_calls", "tts_encoder_elapsed_ms",
     "tts_encoder_destroy",
 )
 
@@ -128,8 +130,9 @@ def lib() -> C.CDLL:
     L.tts_pool_size.argtypes = [vp]
     L.tts_pool_n_active.argtypes = [vp]
     L.tts_pool_span.argtypes = [vp]
-    L.tts_pool_moves.restype = C.c_longlong
-    L.tts_pool_moves.argtypes = [vp]
+    for f in (L.tts_pool_moves, L.tts_pool_segments, L.tts_postnet_one_launch_calls, L.tts_encoder_one_launch_calls):
+        f.restype = C.c_longlong
+        f.argtypes = [vp]
     L.tts_pool_sync.argtypes = [vp]
     L.tts_pool_lost.argtypes = [vp, C.c_int64, _ip]
     L.tts_pool_set_wait_polls.argtypes = [vp, C.c_int]
@@ -334,6 +337,9 @@ class Pool:
     def moves(self) -> int:
         return lib().tts_pool_moves(self._h)
 
+    def segments(self) -> int:
+        return lib().tts_pool_segments(self._h)
+
     def lost(self, rid: int) -> bool:
         """True if the device ended the request early because a step could not be completed for it."""
         v = C.c_int()
@@ -514,6 +520,9 @@ class Postnet:
     def set_wait_polls(self, polls: int) -> None:
         _check(lib().tts_postnet_set_wait_polls(self._h, int(polls)))
 
+    def one_launch_calls(self) -> int:
+        return lib().tts_postnet_one_launch_calls(self._h)
+
     def elapsed_ms(self) -> float:
         ms = C.c_float()
         _check(lib().tts_postnet_elapsed_ms(self._h, C.byref(ms)))
@@ -690,6 +699,9 @@ class Encoder:
 
     def set_wait_polls(self, polls: int) -> None:
         _check(lib().tts_encoder_set_wait_polls(self._h, int(polls)))
+
+    def one_launch_calls(self) -> int:
+        return lib().tts_encoder_one_launch_calls(self._h)
 
     def run(self, ids_list) -> list:
         """Returns F_enc of every request as numpy [L_i, 2 hid]."""

@@ -90,6 +90,7 @@ struct tts_encoder {
         bool used = false;
     } st[2];
     int last = -1;                       // staging buffer of the last call
+    long long n_chained = 0;             // calls with the convolutions as one launch
 };
 
 extern "C" size_t tts_encoder_workspace_bytes(const tts_encoder_config* cfg)
@@ -234,6 +235,7 @@ extern "C" int tts_encoder_run(tts_encoder* e, const int* ids, const int* lens, 
     }
     st.used = true;
     e->last = turn;
+    e->n_chained += n_col <= enc_chain_columns(e->cfg.weight_dtype == TTS_DTYPE_BF16 ? 2 : 4);
     return TTS_OK;
 }
 
@@ -244,6 +246,8 @@ extern "C" int tts_encoder_set_wait_polls(tts_encoder* e, int polls)
     e->d.wait_polls = polls;
     return TTS_OK;
 }
+
+extern "C" long long tts_encoder_one_launch_calls(const tts_encoder* e) { return e ? e->n_chained : 0; }
 
 extern "C" int tts_encoder_elapsed_ms(tts_encoder* e, float* out_ms)
 {

@@ -565,17 +565,11 @@ void lstm_shared(int G, const EncoderPtrs& d, const PnWindows& w, float* out, hi
                        (const uint4*)d.w_hh[1], d.xproj, d.hx, w, d.max_tokens, out, d.wait_polls, d.gave_up);
 }
 
-// The three convolutions and the input projection, from the embedding in act[0] on: as one launch up to this many tokens.  Us a call, layer
-// by layer -> as one launch, queued one behind the other (and, each waited for); two-byte: 1 request of 60 tokens 77.4 -> 71.6 (102 -> 91),
-// 165: 150.2 -> 149.1 (176 -> 170), 384: 304.6 -> 299.8 (334 -> 325), 5 of 100: 116.3 -> 114.9 (145 -> 140), with six column tiles a
-// workgroup, 7 of 100, 120.1 -> 122.9; fp32: 1 of 60 127.1 -> 120.1 (152 -> 140), 3 of 100 227.7 -> 210.2.
-template <typename XT> constexpr int enc_chain_columns() { return sizeof(XT) == 2 ? chain_most_columns(2) / 3 * 2 : chain_most_columns(4); }
-
 template <typename XT>
 hipError_t front_by_layers(const EncoderPtrs& d, int n_col, hipStream_t s)
 {
     constexpr int C = ENC_DIM;
-    static_assert(enc_chain_columns<XT>() / 16 + 1 >= cols_from<XT, C, C, PN_TAPS>(), "calls with layers of their own take k_conv_cols");
+    static_assert(enc_chain_columns(sizeof(XT)) / 16 + 1 >= cols_from<XT, C, C, PN_TAPS>(), "calls with layers of their own take k_conv_cols");
     const int n_ctiles = (n_col + 15) / 16;
     ColArgs p{};
     p.cmeta = d.cmeta;
@@ -590,7 +584,7 @@ hipError_t front_by_layers(const EncoderPtrs& d, int n_col, hipStream_t s)
     }
     if (e != hipSuccess) return e;
     const void* x1 = d.act[1];
-    if constexpr (enc_chain_columns<XT>() / 16 + 1 < cols_from<XT, C, 2 * ENC_GATES, 1>())
+    if constexpr (enc_chain_columns(sizeof(XT)) / 16 + 1 < cols_from<XT, C, 2 * ENC_GATES, 1>())
         if (n_ctiles < cols_from<XT, C, 2 * ENC_GATES, 1>()) {
             hipLaunchKernelGGL((k_enc_xproj<XT>), dim3(ENC_GATES / 16 / 4, n_ctiles, 2), dim3(256), 0, s, (const uint4*)d.w_ih[0], (const uint4*)d.w_ih[1],
                                d.b[0], d.b[1], (const uint4*)x1, n_col, d.max_tokens, d.xproj);
@@ -630,7 +624,7 @@ hipError_t front_as_one(const EncoderPtrs& d, int n_col, hipStream_t s)
     p.set_bytes = d.chain_set_bytes;
     p.state = d.chain_state;
     p.polls = d.wait_polls < CHAIN_POLLS ? d.wait_polls : CHAIN_POLLS;
-    return conv_chain<XT, enc_chain_columns<XT>()>(job, p, n_col, s);
+    return conv_chain<XT, enc_chain_columns(sizeof(XT))>(job, p, n_col, s);
 }
 
 template <typename XT>
@@ -643,7 +637,7 @@ hipError_t run_typed(const EncoderPtrs& d, const PnWindows& w, int n_col, const 
     hipLaunchKernelGGL((k_enc_embed<XT>), dim3((n_col_pad + 3) / 4), dim3(256), 0, s, tb, staged, n_col, n_col_pad, x0, d.cmeta, d.hx,
                        sizeof(XT) == 2 ? 0 : w.n * 4 * ENC_HID, d.gave_up);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = n_col <= enc_chain_columns<XT>() ? front_as_one<XT>(d, n_col, s) : front_by_layers<XT>(d, n_col, s);
+    if (e == hipSuccess) e = n_col <= enc_chain_columns(sizeof(XT)) ? front_as_one<XT>(d, n_col, s) : front_by_layers<XT>(d, n_col, s);
     if (e != hipSuccess) return e;
     if constexpr (sizeof(XT) == 2) {
         static bool attr_set = false;               // dynamic LDS above 64 KB has to be allowed once

@@ -14,6 +14,12 @@ constexpr int ENC_HID = 256;
 constexpr int ENC_GATES = 4 * ENC_HID;      // gate rows per direction
 constexpr int ENC_MAX_BATCH = 256;
 
+// The three convolutions and the input projection, from the embedding in act[0] on, are one launch up to this many tokens.  Us a call, layer
+// by layer -> as one launch, queued one behind the other (and, each waited for); two-byte: 1 request of 60 tokens 77.4 -> 71.6 (102 -> 91),
+// 165: 150.2 -> 149.1 (176 -> 170), 384: 304.6 -> 299.8 (334 -> 325), 5 of 100: 116.3 -> 114.9 (145 -> 140), with six column tiles a
+// workgroup, 7 of 100, 120.1 -> 122.9; fp32: 1 of 60 127.1 -> 120.1 (152 -> 140), 3 of 100 227.7 -> 210.2.
+constexpr int enc_chain_columns(size_t value_bytes) { return value_bytes == 2 ? chain_most_columns(2) / 3 * 2 : chain_most_columns(4); }
+
 struct EncoderPtrs {
     const float* tables[ENC_TABLES];        // fp32 [vocab][dim]
     const void* conv_w[ENC_CONVS];          // weight dtype, A-fragment order, k = tap * dim + channel

@@ -61,6 +61,7 @@ struct tts_postnet {
     hipStream_t stream = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool ev_valid = false;
+    long long n_chained = 0;      // calls that were one launch
 };
 
 // ---- scratch of the entry point that allocates nothing (tts_postnet_run_static): the activations between layers and
@@ -203,6 +204,7 @@ static int run_batch(tts_postnet* p, const PostnetPtrs& d, int max_columns, bool
         }
         if (chain) {
             HIP_TRY(launch_postnet_chain(d, p->cfg.weight_dtype, w, d_mel, n_col, d_out, p->stream));
+            ++p->n_chained;
             break;
         }
         HIP_TRY(launch_postnet_pack(d, p->cfg.weight_dtype, w, d_mel, n_col, n_pad, i0 == 0, p->stream));
@@ -249,6 +251,8 @@ extern "C" int tts_postnet_set_wait_polls(tts_postnet* p, int polls)
     p->d.wait_polls = polls;
     return TTS_OK;
 }
+
+extern "C" long long tts_postnet_one_launch_calls(const tts_postnet* p) { return p ? p->n_chained : 0; }
 
 extern "C" int tts_postnet_elapsed_ms(tts_postnet* p, float* out_ms)
 {

@@ -246,6 +246,7 @@ struct tts_pool {
     std::unique_ptr<PoolBook> book;
     int parity = 0;               // activation buffer half the next step reads
     long long n_moves = 0;        // requests moved to lower slots since creation
+    long long n_segments = 0;     // launches of segments
     int slot_span = 0;            // highest active slot + 1 (as last uploaded): what the per-slot grids must cover
     bool stop_enabled = false;
     bool timing = false;
@@ -759,6 +760,7 @@ static int launch_segment_steps(tts_pool* p, int g)
     HIP_TRY(launch_step(p->d, sl, p->parity, p->stream));
     p->seg_set ^= 1;
     p->seg_used = sl.n_tiles;
+    ++p->n_segments;
     return TTS_OK;
 }
 
@@ -1087,6 +1089,7 @@ extern "C" int tts_pool_size(const tts_pool* p) { return p ? p->book->size() : 0
 extern "C" int tts_pool_n_active(const tts_pool* p) { return p ? (int)p->book->active().size() : 0; }
 extern "C" int tts_pool_span(const tts_pool* p) { return p ? p->book->span() : 0; }
 extern "C" long long tts_pool_moves(const tts_pool* p) { return p ? p->n_moves : 0; }
+extern "C" long long tts_pool_segments(const tts_pool* p) { return p ? p->n_segments : 0; }
 
 extern "C" int tts_pool_sync(tts_pool* p)
 {

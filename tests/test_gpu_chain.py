@@ -45,6 +45,7 @@ def test_postnet_made_for_exactly_the_call(bf16, columns):
             pn.run_device(mel, wins, keeps, want, static=True)
         pn.stream.synchronize()
         np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
+    assert pn.one_launch_calls() == 4
     pn.close()
 
 
@@ -60,6 +61,7 @@ def test_encoder_made_for_exactly_the_call(bf16, columns):
         ids = [synth.encoder_ids(l, 7 * call + i) for i, l in enumerate(lens)]
         for a, b in zip(enc.run(ids), large.run(ids + [more])):
             np.testing.assert_array_equal(a, b)
+    assert enc.one_launch_calls() == 3 and large.one_launch_calls() == 0
     enc.close()
     large.close()
 
@@ -80,7 +82,9 @@ def test_postnet_calls_as_one_launch(polls, bf16):
         with torch.cuda.stream(pn.stream):
             mel = torch.from_numpy(rng.standard_normal((columns, 80)).astype(np.float32)).cuda()
             got, want = (torch.full((columns - sum(keeps), 80), float("nan"), device="cuda") for _ in range(2))
+            before = pn.one_launch_calls()
             pn.run_device(mel, wins, keeps, got)
+            assert pn.one_launch_calls() == before + (columns <= (768 if bf16 else 384))
             pn.run_device(mel, wins, keeps, want, static=True)
         pn.stream.synchronize()
         np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
@@ -133,8 +137,10 @@ def test_encoder_calls_as_one_launch(bf16, edges, polls):
         ids = [synth.encoder_ids(l, i) for i, l in enumerate(lens)]
         if polls is not None:
             enc.set_wait_polls(polls)
+        before = enc.one_launch_calls()
         got = enc.run(ids)
         want = enc.run(ids + [more])
+        assert enc.one_launch_calls() == before + 1
         for a, b in zip(got, want):
             np.testing.assert_array_equal(a, b)
     enc.close()

@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 
 def _both(weights, lengths, frames, calls, max_pool=16, max_enc_len=1024, spoil=None, later=(), forms=(True, False)):
-    """The job in either form: frames of every request and, of those that did not have to be retired on the way, the state."""
+    """The job in either form: frames of every request, its state and its stop logits, and the launches of segments.  A pool without
+    graphs takes every step as launches of its own."""
     wl = synth.small_workload(len(lengths), 5, 90, 8, 8, seed=31, bf16=True)
     out = []
     for use_graph in forms:
@@ -28,13 +29,14 @@ def _both(weights, lengths, frames, calls, max_pool=16, max_enc_len=1024, spoil=
         mel = [pool.drain_all(r) for r in ids]
         state = [{name: pool.get_state(r, name) for name in binding.STATE} for r in ids]
         stop = [pool.stop_logits(r, 0, m.shape[0]) for r, m in zip(ids, mel)]
-        out.append((mel, state, stop))
+        assert (pool.segments() > 0) == use_graph
+        out.append((mel, state, stop, pool.segments()))
         pool.close()
     return out
 
 
 def _same(out, frames):
-    (mel, state, stop), (mel1, state1, stop1) = out
+    (mel, state, stop, _), (mel1, state1, stop1, _) = out
     for i, n in enumerate(frames):
         assert mel[i].shape[0] == n
         np.testing.assert_array_equal(mel[i], mel1[i])
@@ -58,7 +60,9 @@ def _same(out, frames):
 ], ids=lambda v: None)
 def test_segment_equals_steps(lengths, frames, calls, weights_bf16):
     say(f"case: segments of {calls} steps, texts of {lengths}, frames {frames}")
-    _same(_both(weights_bf16, lengths, frames, calls, max_pool=16 if len(lengths) <= 16 else 48), frames)
+    out = _both(weights_bf16, lengths, frames, calls, max_pool=16 if len(lengths) <= 16 else 48)
+    _same(out, frames)
+    assert out[0][3] == len(calls)
 
 
 def test_segments_between_steps_of_a_larger_pool(weights_bf16):
@@ -67,7 +71,9 @@ def test_segments_between_steps_of_a_larger_pool(weights_bf16):
     say("case: 12 requests, 40 more for eight steps, ten of them for longer, segments again")
     lengths = [20 + 2 * i for i in range(52)]
     frames = [60] * 12 + [20] * 10 + [8] * 30
-    _same(_both(weights_bf16, lengths, frames, [15, 8, 12, 25], max_pool=64, max_enc_len=160, later=[1] * 40), frames)
+    out = _both(weights_bf16, lengths, frames, [15, 8, 12, 25], max_pool=64, max_enc_len=160, later=[1] * 40)
+    _same(out, frames)
+    assert out[0][3] == 3
 
 
 @pytest.mark.parametrize("spoil", [0xFFFFFFFF, 0x7F800000, 0x7FC00000])
@@ -76,8 +82,8 @@ def test_segment_with_values_that_are_no_numbers(spoil, weights_bf16):
     keep a reader waiting, and another request must not notice."""
     say(f"case: an encoder output with the bits {spoil:#x} beside an ordinary one")
     frames = [24, 24]
-    (mel, _, _), = _both(weights_bf16, [30, 40], frames, [24], max_enc_len=64, spoil=spoil, forms=(True,))
-    (clean, _, _), = _both(weights_bf16, [30, 40], frames, [24], max_enc_len=64, forms=(True,))
+    (mel, _, _, _), = _both(weights_bf16, [30, 40], frames, [24], max_enc_len=64, spoil=spoil, forms=(True,))
+    (clean, _, _, _), = _both(weights_bf16, [30, 40], frames, [24], max_enc_len=64, forms=(True,))
     assert mel[0].shape == (24, 80) and not np.array_equal(mel[0], clean[0])
     np.testing.assert_array_equal(mel[1], clean[1])
 
@@ -125,6 +131,7 @@ def test_segments_beside_other_work(n, weights_bf16):
         pool.step_n(k)
     pool.sync()                      # raises if a wait ran out
     side.synchronize()
+    assert pool.segments() == 4
     for r, w in zip(ids, want):
         np.testing.assert_array_equal(pool.drain_all(r), w)
     pool.close()
@@ -160,6 +167,7 @@ def test_segments_of_several_pools(threads, weights_bf16, weights_fp32):
     assert not errors
     for pool, ids, want in jobs:
         pool.sync()                  # raises if a wait ran out
+        assert pool.segments() == (32 if len(ids) != 5 else 0)
         for r, w in zip(ids, want):
             np.testing.assert_array_equal(pool.drain_all(r), w)
         pool.close()
@@ -177,6 +185,7 @@ def test_captured_steps(n, bf16, weights_bf16, weights_fp32):
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=pool.stream):
         pool.step_n(n)
+    assert pool.segments() == int(bf16)
     with torch.cuda.stream(pool.stream):
         graph.replay()
     pool.step_n(35 - n)
