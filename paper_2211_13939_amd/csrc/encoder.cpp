@@ -148,9 +148,9 @@ extern "C" int tts_encoder_create(const tts_encoder_config* cfg, const tts_encod
             rc = upload(base + lay.b[d], bp, false);
         }
     }
-    if (rc == TTS_OK && hipMemset(base + lay.scratch_begin, 0, lay.total - lay.scratch_begin) != hipSuccess)
+    if (rc == TTS_OK && fill_now(base + lay.scratch_begin, 0, lay.total - lay.scratch_begin) != hipSuccess)
         rc = fail(TTS_E_HIP, "clearing the activation buffers failed");
-    if (rc == TTS_OK && hipMemset(base + lay.chain, 0xff, lay.total - lay.chain) != hipSuccess) rc = fail(TTS_E_HIP, "clearing the words failed");
+    if (rc == TTS_OK && fill_now(base + lay.chain, 0xff, lay.total - lay.chain) != hipSuccess) rc = fail(TTS_E_HIP, "clearing the words failed");
     const size_t n_tok = cfg->max_tokens;
     for (tts_encoder::Staging& st : e->st) {
         if (rc == TTS_OK && (hipEventCreate(&st.ev0) != hipSuccess || hipEventCreate(&st.ev1) != hipSuccess))

@@ -20,6 +20,13 @@ int fail(int code, const char* fmt, ...);
         if (e_ != hipSuccess) return tts::fail(TTS_E_HIP, "%s: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
+// Fills device memory and waits for it: an object's own stream, which its first call goes to, need not wait for the default stream.
+inline hipError_t fill_now(void* dst, int value, size_t bytes)
+{
+    hipError_t e = hipMemset(dst, value, bytes);
+    return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
+}
+
 // hands out 256-byte aligned offsets into the caller's arena
 struct Carver {
     size_t off = 0;

@@ -147,9 +147,9 @@ extern "C" int tts_postnet_create(const tts_postnet_config* cfg, const tts_postn
         p->d.W[l] = base + lay.W[l];
         p->d.b[l] = (const float*)(base + lay.b[l]);
     }
-    if (rc == TTS_OK && hipMemset(base + lay.act[0], 0, lay.total - lay.act[0]) != hipSuccess)
+    if (rc == TTS_OK && fill_now(base + lay.act[0], 0, lay.total - lay.act[0]) != hipSuccess)
         rc = fail(TTS_E_HIP, "clearing the activation buffers failed");
-    if (rc == TTS_OK && hipMemset(base + lay.chain, 0xff, lay.total - lay.chain) != hipSuccess) rc = fail(TTS_E_HIP, "clearing the words failed");
+    if (rc == TTS_OK && fill_now(base + lay.chain, 0xff, lay.total - lay.chain) != hipSuccess) rc = fail(TTS_E_HIP, "clearing the words failed");
     if (rc == TTS_OK && (hipEventCreate(&p->ev0) != hipSuccess || hipEventCreate(&p->ev1) != hipSuccess))
         rc = fail(TTS_E_HIP, "hipEventCreate failed");
     if (rc) {

@@ -202,7 +202,7 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
         rc = upload(base + lay.alpha, al, false);
         if (rc == TTS_OK) rc = upload(base + lay.beta, be, false);
     }
-    if (rc == TTS_OK && hipMemset(base + lay.state_begin, 0, lay.total - lay.state_begin) != hipSuccess)
+    if (rc == TTS_OK && fill_now(base + lay.state_begin, 0, lay.total - lay.state_begin) != hipSuccess)
         rc = fail(TTS_E_HIP, "clearing the state and activation buffers failed");
     if (rc == TTS_OK && (hipEventCreate(&v->ev0) != hipSuccess || hipEventCreate(&v->ev1) != hipSuccess))
         rc = fail(TTS_E_HIP, "hipEventCreate failed");

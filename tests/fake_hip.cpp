@@ -1,6 +1,7 @@
 // A HIP runtime and the kernels' launch wrappers on host memory, for the host side of the library alone: streams run what is
 // queued at once, except that what a kernel still has to read of pinned memory counts as pending until the host has waited for
 // it.  Any call can be made to fail (fake_fail), and a slot can be frozen as a kernel would that gave up (fake_freeze).
+// A fill of device memory at creation counts as under way until the host has waited (fake_filling).
 // What is ordered behind what is followed through streams, events and the host's waits: a segment of steps that is not ordered against another
 // stream's steps, or the other way round, counts (fake_unordered).
 #include <algorithm>
@@ -13,6 +14,7 @@
 
 #include "../paper_2211_13939_amd/csrc/encoder_kernels.h"
 #include "../paper_2211_13939_amd/csrc/kernels.h"
+#include "../paper_2211_13939_amd/csrc/vocoder_kernels.h"
 
 namespace {
 
@@ -31,6 +33,7 @@ std::mutex order;
 std::map<hipStream_t, Clock> streams;
 std::vector<Launched> launched;
 int unordered = 0, segments = 0;
+bool filling = false;
 bool busy = false;                              // what hipStreamQuery says
 hipStream_t capturing = nullptr;
 Clock host;                                     // what some thread has waited for has ended
@@ -86,9 +89,10 @@ void fake_reset()
     streams.clear();
     launched.clear();
     violations = unordered = segments = 0;
-    busy = false;
+    busy = filling = false;
     capturing = nullptr;
 }
+int fake_filling() { return filling; }
 void fake_busy(int on) { busy = on; }
 void fake_capture(void* stream) { capturing = (hipStream_t)stream; }
 int fake_unordered() { return unordered; }
@@ -106,7 +110,14 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void*)
     return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
-hipError_t hipDeviceSynchronize() { done_up_to(seq); return hipSuccess; }
+hipError_t hipDeviceSynchronize()
+{
+    filling = false;
+    done_up_to(seq);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* s) { *p = const_cast<void*>(s); return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned)
 {
     if (hipError_t e = call("hipHostMalloc")) return e;
@@ -121,7 +132,12 @@ hipError_t hipHostFree(void* p)
     return hipSuccess;
 }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return hipSuccess; }
+hipError_t hipMemset(void* d, int v, size_t n)
+{
+    filling = true;
+    memset(d, v, n);
+    return hipSuccess;
+}
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t)
 {
@@ -132,6 +148,7 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
 hipError_t hipStreamSynchronize(hipStream_t s)
 {
     if (hipError_t e = call("hipStreamSynchronize")) return e;
+    filling = filling && s;
     done_up_to(seq);
     waited(s);
     return hipSuccess;
@@ -183,6 +200,11 @@ hipError_t launch_encoder(const EncoderPtrs&, int, const PnWindows&, int, const 
     pending.push_back({staged.ids, ++seq});     // the first kernel is queued whether or not a later launch fails
     return call("launch_encoder");
 }
+
+hipError_t launch_postnet_pack(const PostnetPtrs&, int, const PnWindows&, const float*, int, int, bool, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_postnet_chain(const PostnetPtrs&, int, const PnWindows&, const float*, int, float*, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_postnet(const PostnetPtrs&, int, const float*, int, float*, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_vocoder(const VocoderPtrs&, int, const VocBatch&, const float*, float*, hipStream_t) { return hipErrorNotSupported; }
 
 // frame f of a request of n frames: all of its values are 1000 n + f
 hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int, hipStream_t stream, hipEvent_t*)

@@ -1,4 +1,4 @@
-"""Error paths of the library's host code, on the CPU: tts_pool.cpp and encoder.cpp compiled against a HIP runtime on host
+"""Error paths and waits of the library's host code, on the CPU: its four translation units compiled against a HIP runtime on host
 memory (fake_hip.cpp) in which any call can be made to fail."""
 import ctypes as C
 import os
@@ -21,13 +21,14 @@ def lib(tmp_path_factory):
     csrc = os.path.join(ROOT, "paper_2211_13939_amd", "csrc")
     # -Bsymbolic: the HIP runtime of this process is not in the way
     subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
-                    "-Wno-unused-result", os.path.join(ROOT, "tests", "fake_hip.cpp"), os.path.join(csrc, "tts_pool.cpp"),
-                    os.path.join(csrc, "encoder.cpp"), "-o", out], check=True)
+                    # (the HIP compiler's own words, in postnet.cpp)
+                    "-Wno-unused-result", "-D__align__(n)=__attribute__((aligned(n)))", "-DHIP_SYMBOL(x)=((const void*)x)", os.path.join(ROOT, "tests", "fake_hip.cpp")]
+                   + [os.path.join(csrc, f) for f in ("tts_pool.cpp", "encoder.cpp", "postnet.cpp", "vocoder.cpp")] + ["-o", out], check=True)
     L = C.CDLL(out)
-    for f in ("tts_pool_workspace_bytes", "tts_encoder_workspace_bytes"):
-        getattr(L, f).restype = C.c_size_t
+    for f in ("pool", "encoder", "postnet", "vocoder"):
+        getattr(L, f"tts_{f}_workspace_bytes").restype = C.c_size_t
     L.tts_last_error.restype = C.c_char_p
-    for f in ("tts_pool_destroy", "tts_encoder_destroy"):
+    for f in ("tts_pool_destroy", "tts_encoder_destroy", "tts_postnet_destroy", "tts_vocoder_destroy"):
         getattr(L, f).restype = None
         getattr(L, f).argtypes = [C.c_void_p]
     L.fake_fail.argtypes = [C.c_char_p, C.c_int, C.c_int]
@@ -342,3 +343,28 @@ def test_neighbours_event_that_cannot_be_had(lib, weights_fp32):
     assert a.drain(ra) == (0, _frames(8, 0, 8), True) and b.drain(rb) == (0, _frames(8, 0, 8), True)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("module", ["pool", "encoder", "postnet", "vocoder"])
+def test_what_an_object_starts_with_is_there_when_it_has_been_made(lib, weights_fp32, module):
+    """The first call goes to the object's own stream, which does not wait for the default stream's fills."""
+    if module == "pool":
+        FakePool(lib, weights_fp32, segments=True).close()
+    elif module == "encoder":
+        FakeEncoder(lib).close()
+    else:
+        if module == "postnet":
+            cfg, w = binding.make_postnet_config(max_columns=64), binding.TtsPostnetWeights()
+        else:
+            cfg, w = binding.make_vocoder_config(overlap=4, max_chunk=8, max_requests=2, max_batch=2), binding.TtsVocoderWeights()
+        zeros = np.zeros(512 * 512 * 16, np.float32)                     # (as large as the largest tensor)
+        at = (C.c_void_p * (C.sizeof(w) // 8)).from_buffer(w)
+        for i in range(len(at)):
+            at[i] = zeros.ctypes.data
+        n = int(getattr(lib, f"tts_{module}_workspace_bytes")(C.byref(cfg)))
+        raw, arena = _arena(n)
+        h = C.c_void_p()
+        create = getattr(lib, f"tts_{module}_create")
+        assert create(C.byref(cfg), C.byref(w), arena, C.c_size_t(n), C.c_void_p(1), C.byref(h)) == 0, lib.tts_last_error()
+        getattr(lib, f"tts_{module}_destroy")(h)
+    assert lib.fake_filling() == 0
