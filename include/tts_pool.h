@@ -234,7 +234,9 @@ long long tts_pool_segments(const tts_pool *pool);
  * other work that a partner is not scheduled for a quarter of a second), the kernels still finish and only the
  * requests whose words were missing are affected: the device stores nothing more for them from that step on (the
  * frames they have are valid and can be drained; they count as finished and hold their slots until retired), every
- * other request in the pool goes on undisturbed.  The first tts_pool_sync after such an incident returns TTS_E_LOST
+ * other request in the pool goes on undisturbed.  Where several steps are one launch (tts_pool_step_n), its workgroups
+ * work for all requests in turn: what one of them misses ends every request that takes part in that step (up to 48),
+ * not those of one tile of 16 or a single one.  The first tts_pool_sync after such an incident returns TTS_E_LOST
  * with the ids in tts_last_error(); tts_pool_lost tells for one request.  Nothing else is needed to go on using the
  * pool.  (A consumer on the device, tts_pool_chunk_window, can only know of steps that have already run: wait with
  * this call before trusting chunks handed over from steps still in flight.) */

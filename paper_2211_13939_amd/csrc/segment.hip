@@ -27,8 +27,11 @@
 //     emptying had been acknowledged (a poll that the storing wave has waited for lies in between).
 // A launch uses one of two such sets and empties the other one, whole, before it waits for anything: the next launch finds its set
 // empty whatever became of this one.
-// Every wait is bounded; a workgroup whose wait runs out marks the requests that take part in the step as ended and failed,
-// stores nothing more and leaves, and the others' waits then run out in turn.
+// Every wait is bounded; a workgroup whose wait runs out marks the requests that take part in the step as ended and failed (LSA: its own, and
+// those that wait for its part of a then mark the others), stores nothing more and leaves, and the others' waits run out in turn.  So one
+// workgroup that other work keeps from starting for the length of a wait ends every request of the step, where the step's launches end one
+// request (k_lsa) or a tile of them (k_proj).  The workgroups of a segment all have to be resident: other pools' launches are kept away
+// (resident.h), work that ends by itself delays them.
 #include "kernels.h"
 #include "lsa_tile.h"
 #include "mfma.h"
@@ -903,8 +906,8 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, const 
 // once for all of them: ATT and DEC fill XCDs 0 .. 3 in order, LSA and each tile's projection lie on 4 .. 7.  And at least eight CUs of every XCD
 // stay free for work on other streams, whose launches are dealt over all XCDs: with XCDs filled to the last CU a vocoder beside the
 // decoder waited for the end of a segment with each of its launches.  Against DEC and LSA on all XCDs: 1 request 9.9 -> 9.7 us a step,
-// 16: 12.7 -> 11.2; with all of ATT on one XCD and four or two LSA per request of two and three tiles, no CU of four XCDs free: 32 requests
-// 13.8 -> 13.4, 48: 17.7 -> 16.3.
+// 16: 12.7 -> 11.2.  Faster but not taken: with all of ATT on one XCD and four or two LSA per request of two and three tiles, which leaves no CU of
+// four XCDs free, 32 requests would take 13.4 us instead of 13.8, 48 of them 16.3 instead of 17.7.
 constexpr int SEG_XCD_WGS = 24;                             // of ATT and DEC on an XCD; LSA, at most 16, and ROWS and LEAD fill the others as far
 template <bool MULTI, int S>
 __global__ __launch_bounds__(NT) void k_segment(DevPtrs d, int cur, int n_slots, int n_steps, char* words, char* words_next, int tile_bytes, int empty_bytes)
