@@ -165,7 +165,8 @@ int tts_pool_step(tts_pool *pool, int *out_n_active);
  * slots with two-byte weights and memory a step that follows another step of
  * the same call is two kernel launches instead of three, and while no active
  * request's slot lies above 48 and there is no stop threshold up to 64 steps
- * are one kernel launch).
+ * are one kernel launch, where that is the faster form: above 16 slots not
+ * for long texts or a step or two).
  * On a stream that the caller is capturing the steps go into his graph one by
  * one.  The pool counts them as taken by this call, so that graph is launched
  * once, before anything else of the pool. */

@@ -734,19 +734,40 @@ static int launch_steps(tts_pool* p, int nsteps, bool as_graph)
     return TTS_OK;
 }
 
+// Fewest steps that are faster as one launch than as launches of their own, for requests in this many tiles of slots whose longest text
+// is `longest` positions (MAX_SEGMENT_STEPS + 1: none are).  A segment's launch begins with all the weights (7 us more than a step's launches),
+// and with more tiles a request has fewer workgroups, which keep fewer of its positions in registers (512, 320, 128) and read the others again at
+// every step.  Us a step of queued calls, all texts of one length, steps as launches in graphs -> as one launch:
+//   17 .. 32 slots   1 step: 320 positions 28.3 -> 28.3, 400 29.2 -> 29.7;   2 steps: 640 26.5 -> 26.4, 704 27.1 -> 27.9;
+//                    3: 768 28.9 -> 26.9;   8: 768 25.0 -> 23.9, 896 26.4 -> 26.6;   40: 896 25.8 -> 25.2, 1024 26.3 -> 27.7
+//   33 .. 48         1: 20 positions 27.5 -> 29.2;   2: 165 24.2 -> 24.0, 256 24.8 -> 25.5;   3: 320 26.6 -> 24.2;   4: 320 23.7 -> 23.0, 336 23.9 -> 24.5;
+//                    8: 352 23.1 -> 22.7, 384 23.4 -> 23.5;   40: 384 22.5 -> 22.0, 400 23.2 -> 23.1, 512 23.3 -> 26.1, 1024 28.4 -> 40.3
+// (one long text among texts of 60 positions: the same lines, within 2 %, but for more than 896 in two tiles, 24.5 -> 22.9 at 1024)
+static const int MAX_SEGMENT_STEPS = 64;
+static int fewest_segment_steps(int tiles, int longest)
+{
+    if (tiles == 1) return 1;
+    if (tiles == 2) return longest <= 320 ? 1 : longest <= 640 ? 2 : longest <= 768 ? 3 : longest <= 896 ? 8 : MAX_SEGMENT_STEPS + 1;
+    return longest <= 160 ? 2 : longest <= 320 ? 3 : longest <= 352 ? 8 : longest <= 384 ? 16 : MAX_SEGMENT_STEPS + 1;
+}
+
 // How many of the next `n` steps run as one launch (segment.hip; 0: they run step by step).  The line is the form's own: two-byte weights
 // and memory (d.seg_x), frame counts known beforehand, and the slots up to which it is the faster one.  Chunks of 40 steps of requests
 // of 165 positions, steps as launches in graphs -> as one launch: 1 request 16.8 -> 9.7 us a step, 8: 18.2 -> 10.3, 16: 18.5 -> 11.2,
 // 20: 19.7 -> 13.5, 32: 20.4 -> 13.8, 48: 21.2 -> 17.7; with four tiles, 64 requests, 21.6 -> 21.5.  Single steps, each waited for: 1 request
 // 49 -> 30 us.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other streams that
 // needs every compute unit gets them at intervals.
-static const int MAX_SEGMENT_STEPS = 64;
 static int segment_steps(const tts_pool* p, int n)
 {
     if (!p->d.seg_x || !p->cfg.use_graph || p->stop_enabled || p->slot_span > p->d.seg_slots) return 0;
-    int most = 0;
-    for (int sl : p->book->active()) most = std::max(most, p->book->slot(sl).n_steps - p->book->slot(sl).t);
-    return std::min({n, most, MAX_SEGMENT_STEPS});
+    int most = 0, longest = 0;
+    for (int sl : p->book->active()) {
+        const SlotInfo& si = p->book->slot(sl);
+        most = std::max(most, si.n_steps - si.t);
+        longest = std::max(longest, si.L);
+    }
+    const int g = std::min({n, most, MAX_SEGMENT_STEPS});
+    return g >= fewest_segment_steps((p->slot_span + 15) / 16, longest) ? g : 0;
 }
 static int launch_segment_steps(tts_pool* p, int g)
 {

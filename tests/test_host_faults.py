@@ -48,9 +48,9 @@ def _arena(nbytes):
 
 
 class FakePool:
-    def __init__(self, lib, weights, max_pool=4, max_steps=64, chunk=8, stream=1, segments=False):
+    def __init__(self, lib, weights, max_pool=4, max_steps=64, chunk=8, stream=1, segments=False, max_enc_len=16):
         self.L, self.chunk = lib, chunk
-        cfg = binding.make_config(synth.DIMS, max_pool=max_pool, max_enc_len=16, max_steps=max_steps, chunk_frames=chunk, use_graph=segments,
+        cfg = binding.make_config(synth.DIMS, max_pool=max_pool, max_enc_len=max_enc_len, max_steps=max_steps, chunk_frames=chunk, use_graph=segments,
                                   bf16=segments)
         n = int(lib.tts_pool_workspace_bytes(C.byref(cfg)))
         self._arena, at = _arena(n)
@@ -58,9 +58,9 @@ class FakePool:
         self.h = C.c_void_p()
         assert lib.tts_pool_create(C.byref(cfg), C.byref(w), at, C.c_size_t(n), C.c_void_p(stream), C.byref(self.h)) == 0, lib.tts_last_error()
 
-    def add(self, n_steps):
-        enc, rid = np.zeros((3, synth.DIMS["enc_dim"]), np.float32), C.c_int64()
-        assert self.L.tts_pool_add_request(self.h, enc.ctypes.data_as(C.c_void_p), 3, n_steps, C.byref(rid)) == 0
+    def add(self, n_steps, length=3):
+        enc, rid = np.zeros((length, synth.DIMS["enc_dim"]), np.float32), C.c_int64()
+        assert self.L.tts_pool_add_request(self.h, enc.ctypes.data_as(C.c_void_p), length, n_steps, C.byref(rid)) == 0
         return rid.value
 
     def step_n(self, n):
@@ -319,6 +319,32 @@ def test_captured_call_takes_its_steps_one_by_one(lib, weights_fp32):
         got = [f for _ in range(3) for f in p.drain(r)[1]]
         assert got == _frames(20, 0, 20)
         p.close()
+
+
+# slots spanned, longest text -> fewest steps of a call that are one launch (None: never)
+FEWEST = [(1, 1024, 1), (16, 1024, 1), (17, 320, 1), (32, 321, 2), (17, 640, 2), (32, 641, 3), (20, 768, 3), (20, 769, 8), (32, 896, 8), (17, 897, None),
+          (32, 1024, None), (33, 160, 2), (48, 161, 3), (33, 320, 3), (48, 321, 8), (48, 352, 8), (33, 353, 16), (48, 384, 16), (33, 385, None),
+          (48, 1024, None)]
+
+
+@pytest.mark.parametrize("slots,longest,fewest", FEWEST)
+def test_steps_are_one_launch_where_that_is_the_faster_form(lib, weights_fp32, slots, longest, fewest):
+    """One text of that length among short ones, in the highest slot.  (Steps as launches of their own would be graphs, which the runtime
+    of this test does not have: such a call fails.)"""
+    pool = FakePool(lib, weights_fp32, max_pool=48, max_steps=200, chunk=40, segments=True, max_enc_len=1024)
+    for k in range(slots - 1):
+        pool.add(200)
+    pool.add(200, longest)
+
+    def as_one(n):
+        before = lib.fake_segments()
+        rc = lib.tts_pool_step_n(pool.h, n, None)
+        assert rc == (0 if lib.fake_segments() > before else binding.TTS_E_HIP)
+        return lib.fake_segments() > before
+
+    assert [as_one(n) for n in range(1, 18)] == [fewest is not None and n >= fewest for n in range(1, 18)]
+    assert as_one(40) == (fewest is not None)
+    pool.close()
 
 
 def test_neighbours_event_that_cannot_be_had(lib, weights_fp32):
