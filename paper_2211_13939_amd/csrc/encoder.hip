@@ -579,7 +579,7 @@ hipError_t front_by_layers(const EncoderPtrs& d, int n_col, hipStream_t s)
         p.W = (const uint4*)d.conv_w[l];
         p.bias = d.conv_b[l];
         p.Xin = (const uint4*)d.act[l & 1];
-        p.Xout = d.act[l & 1 ^ 1];
+        p.Xout = d.act[(l & 1) ^ 1];
         e = conv_cols<XT, C, C, PN_TAPS, CC_RELU>(p, s);
     }
     if (e != hipSuccess) return e;
