@@ -87,7 +87,7 @@ int tts_postnet_run(tts_postnet *pn, const float *d_mel, const int *win_len, con
  * those of tts_postnet_run, but the scratch of the call -- the activations between the layers and the per-column
  * tables -- lives in a static array inside the library instead of the arena: TTS_POSTNET_STATIC_BYTES bytes per GPU
  * that runs it, held until the process ends.  The call allocates nothing (no hipMalloc, no hipFree, no allocating
- * library routine) and records no events (tts_postnet_elapsed_ms does not see it).  A batch may carry at most
+ * library routine) and is not timed (tts_postnet_elapsed_ms does not see it).  A batch may carry at most
  * TTS_POSTNET_STATIC_MAX_COLUMNS frames (context included) whatever max_columns says: more is TTS_E_INVAL.  Every
  * call on a GPU, from any tts_postnet object, uses that GPU's one array: calls that overlap on one GPU (two streams,
  * two threads) race; calls queued on one stream do not.  The device the object was created on must be current.
@@ -107,7 +107,8 @@ int tts_postnet_set_wait_polls(tts_postnet *pn, int polls);
 /* Calls since creation that were one launch. */
 long long tts_postnet_one_launch_calls(const tts_postnet *pn);
 
-/* Device time of the last tts_postnet_run in milliseconds (HIP events on the stream); waits for the stream. */
+/* Device time of the last tts_postnet_run in milliseconds, from the start of its first launch to the end of its last; waits for the stream
+ * (TTS_E_HIP while that is being captured). */
 int tts_postnet_elapsed_ms(tts_postnet *pn, float *out_ms);
 
 void tts_postnet_destroy(tts_postnet *pn);

@@ -113,7 +113,8 @@ int tts_vocoder_create(const tts_vocoder_config *cfg, const tts_vocoder_weights 
 int tts_vocoder_run(tts_vocoder *v, const float *d_mel, const int *n_frames, const int *state_slot, const int *flags,
                     int n, float *d_audio, int *out_samples);
 
-/* Device time of the last tts_vocoder_run in milliseconds (HIP events on the stream); waits for the stream. */
+/* Device time of the last tts_vocoder_run in milliseconds, from the start of its first launch to the end of its last; waits for the stream
+ * (TTS_E_HIP while that is being captured). */
 int tts_vocoder_elapsed_ms(tts_vocoder *v, float *out_ms);
 
 void tts_vocoder_destroy(tts_vocoder *v);

@@ -58,6 +58,7 @@ struct ChainArgs {
     int groups;                        // column groups
     int polls;                         // CHAIN_POLLS or less (1: most take blocks from the counter; 0: nobody waits, every workgroup forms
                                        // what it needs by itself)
+    Stamps stamps;                     // jobs that are a call of their own (TIMED)
 };
 
 // Where a wave's share of a row tile's weights lies: fragments first, first + step, ...  A fragment's place is a scalar offset, all loads share
@@ -134,6 +135,8 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
     constexpr int LAYERS = JOB::LAYERS;
     static_assert(LAYERS <= CHAIN_LAYERS && JOB::CIN <= G::C, "buffers");
     extern __shared__ __attribute__((aligned(16))) unsigned char s_x[];
+    unsigned long long t0 = 0;
+    if constexpr (JOB::TIMED) t0 = p.stamps.now();
     floatx4 (*red)[CT][64] = reinterpret_cast<floatx4 (*)[CT][64]>(s_x + G::RED_AT);
     __shared__ int s_meta[G::COLS], s_row[G::COLS], s_late, s_taken;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, jl = lane & 15, g = lane >> 4;
@@ -348,6 +351,10 @@ __global__ __launch_bounds__(PN_THREADS, 2) void k_conv_chain(JOB job, ChainArgs
             p.state[4] = 0;
             p.state[2 + turn] = p.groups * LAYERS * CHAIN_RTS * G::SUBS;
             p.state[2 + (turn ^ 1)] = 0;
+        }
+        if constexpr (JOB::TIMED) {
+            p.stamps.begin(t0);
+            p.stamps.end();
         }
     }
 }

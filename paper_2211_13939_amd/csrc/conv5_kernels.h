@@ -36,7 +36,7 @@ template <typename XT, int CIN, int COUT, int EPI>
 __global__ __launch_bounds__(PN_THREADS) void k_pn_conv(
     const uint4* __restrict__ Wfrag, const float* __restrict__ bias, const uint4* __restrict__ Xin, XT* __restrict__ Xout,
     const int* __restrict__ cmeta, int n_ctiles, const float* __restrict__ mel, int n_mel, const int* __restrict__ orow,
-    float* __restrict__ out)
+    float* __restrict__ out, Stamps stamps)
 {
     constexpr int KB = Frag<XT>::KB, EPL = Frag<XT>::EPL;
     constexpr int PN_CT = PnCT<XT>::value;
@@ -127,6 +127,7 @@ __global__ __launch_bounds__(PN_THREADS) void k_pn_conv(
             }
         }
     }
+    if (EPI == PN_EPI_LAST && tid == 0) stamps.end();
 }
 
 // The same layer for large batches, and (TAPS = 1) the encoder's input projection: a workgroup owns WR x RPW row tiles and WC x CTW
@@ -193,6 +194,7 @@ struct ColArgs {
     const int* orow;
     float* out;               // CC_LAST: [rows][n_mel]; CC_XPROJ: [2][max_cols][COUT / 2]
     int n_col, max_cols;      // CC_XPROJ
+    Stamps stamps;            // CC_LAST: the call ends here
 };
 
 // grid = (row groups, ceil(column tiles / CT))
@@ -353,6 +355,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void k_conv_cols(ColArgs p)
             }
         }
     }
+    if (EPI == CC_LAST && tid == 0) p.stamps.end();
 }
 
 // 2 x 2 waves of two row tiles each; five waves of one where there are five (the PostNet's last layer); four waves of two row
@@ -425,7 +428,7 @@ inline hipError_t conv_cols(const ColArgs& p, hipStream_t s)
 
 template <typename XT, int CIN, int COUT, int EPI>
 inline hipError_t conv_layer(const void* W, const float* b, const void* xin, XT* xout, const int* cmeta, int n_ctiles,
-                             const float* mel, int n_mel, const int* orow, float* out, hipStream_t s)
+                             const float* mel, int n_mel, const int* orow, float* out, const Stamps& stamps, hipStream_t s)
 {
     if (n_ctiles >= cols_from<XT, CIN, COUT, PN_TAPS>()) {
         ColArgs p{};
@@ -439,12 +442,13 @@ inline hipError_t conv_layer(const void* W, const float* b, const void* xin, XT*
         p.n_mel = n_mel;
         p.orow = orow;
         p.out = out;
+        p.stamps = stamps;
         return conv_cols<XT, CIN, COUT, PN_TAPS, EPI>(p, s);
     } else {
         constexpr int CT = PnCT<XT>::value;
         const dim3 grid(COUT / 16, (n_ctiles + CT - 1) / CT);
         hipLaunchKernelGGL((k_pn_conv<XT, CIN, COUT, EPI>), grid, dim3(PN_THREADS), 0, s, (const uint4*)W, b, (const uint4*)xin,
-                           xout, cmeta, n_ctiles, mel, n_mel, orow, out);
+                           xout, cmeta, n_ctiles, mel, n_mel, orow, out, stamps);
     }
     return hipGetLastError();
 }

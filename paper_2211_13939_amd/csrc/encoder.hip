@@ -74,6 +74,7 @@ __global__ __launch_bounds__(256) void k_enc_xproj(const uint4* __restrict__ W0,
 // The three convolutions and the input projection of a small call as one launch (conv5_chain.h).  A workgroup's share of the projection
 // are four row tiles, two waves each; every sum is the one chain over k that it is above.
 template <typename XT> struct EncChain {
+    static constexpr bool TIMED = false;
     static constexpr int LAYERS = ENC_CONVS, CIN = ENC_DIM, EPI = PN_EPI_RELU, EPL = Frag<XT>::EPL, KB = Frag<XT>::KB, NKF = ENC_DIM / KB, LAST = NKF;
     static constexpr int WG_RTS = 2 * ENC_GATES / 16 / CHAIN_RTS, PER = PN_WAVES / WG_RTS;
     const uint4* X;

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/tts_pool.h"
+#include "stamps.h"
 
 namespace tts {
 
@@ -25,6 +26,20 @@ inline hipError_t fill_now(void* dst, int value, size_t bytes)
 {
     hipError_t e = hipMemset(dst, value, bytes);
     return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
+}
+
+// The call's time from its stamps; the stream is waited for (and therefore not while it is being captured).
+inline int stamps_ms(const Stamps& st, int khz, hipStream_t s, float* out_ms)
+{
+    unsigned long long t[STAMP_BYTES / 8], end = 0;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &capture));
+    if (capture != hipStreamCaptureStatusNone) return fail(TTS_E_HIP, "the stream is being captured");
+    HIP_TRY(hipMemcpyAsync(t, st.at, STAMP_BYTES, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    for (int i = 1; i <= STAMP_ENDS; ++i) end = t[i] > end ? t[i] : end;
+    *out_ms = end > t[0] ? (float)(end - t[0]) / khz : 0.f;
+    return TTS_OK;
 }
 
 // hands out 256-byte aligned offsets into the caller's arena

@@ -30,7 +30,7 @@ int c_in_padded(int l) { return l == 0 ? PN_CIN0 : PN_CHANNELS; }
 int c_out_of(int l) { return l == PN_LAYERS - 1 ? PN_COUT_LAST : PN_CHANNELS; }
 
 struct PnLayout {
-    size_t W[PN_LAYERS], b[PN_LAYERS], act[2], cmeta, orow, chain_state, chain, total;
+    size_t W[PN_LAYERS], b[PN_LAYERS], act[2], cmeta, orow, stamps, chain_state, chain, total;
 };
 
 PnLayout layout_of(const tts_postnet_config& c)
@@ -46,6 +46,7 @@ PnLayout layout_of(const tts_postnet_config& c)
     for (int i = 0; i < 2; ++i) l.act[i] = a.take(cols * PN_CHANNELS * ws);
     l.cmeta = a.take(cols * 4);
     l.orow = a.take(cols * 4);
+    l.stamps = a.take(STAMP_BYTES);
     l.chain_state = a.take(CHAIN_STATE_BYTES);
     l.chain = a.take(2 * chain_set_bytes(ws, c.max_columns, PN_LAYERS - 1));
     l.total = a.off;
@@ -59,8 +60,8 @@ struct tts_postnet {
     PostnetPtrs d;
     int device = -1;              // the device the arena (hence the weights) lives on
     hipStream_t stream = nullptr;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    bool ev_valid = false;
+    int clock_khz = 0;            // of the stamps
+    bool ran = false;
     long long n_chained = 0;      // calls that were one launch
 };
 
@@ -150,8 +151,8 @@ extern "C" int tts_postnet_create(const tts_postnet_config* cfg, const tts_postn
     if (rc == TTS_OK && fill_now(base + lay.act[0], 0, lay.total - lay.act[0]) != hipSuccess)
         rc = fail(TTS_E_HIP, "clearing the activation buffers failed");
     if (rc == TTS_OK && fill_now(base + lay.chain, 0xff, lay.total - lay.chain) != hipSuccess) rc = fail(TTS_E_HIP, "clearing the words failed");
-    if (rc == TTS_OK && (hipEventCreate(&p->ev0) != hipSuccess || hipEventCreate(&p->ev1) != hipSuccess))
-        rc = fail(TTS_E_HIP, "hipEventCreate failed");
+    if (rc == TTS_OK && hipDeviceGetAttribute(&p->clock_khz, hipDeviceAttributeWallClockRate, attr.device) != hipSuccess)
+        rc = fail(TTS_E_HIP, "the rate of the device's clock is not known");
     if (rc) {
         tts_postnet_destroy(p);
         return rc;
@@ -160,6 +161,7 @@ extern "C" int tts_postnet_create(const tts_postnet_config* cfg, const tts_postn
     p->d.act[1] = base + lay.act[1];
     p->d.cmeta = (int*)(base + lay.cmeta);
     p->d.orow = (int*)(base + lay.orow);
+    p->d.stamps.at = (unsigned long long*)(base + lay.stamps);
     p->d.n_mel = cfg->n_mel;
     p->d.chain_words = base + lay.chain;
     p->d.chain_state = (int*)(base + lay.chain_state);
@@ -169,8 +171,8 @@ extern "C" int tts_postnet_create(const tts_postnet_config* cfg, const tts_postn
     return TTS_OK;
 }
 
-// one dynamic batch with the scratch of `d` (the arena's, or the static array's); `timed`: HIP events around it
-static int run_batch(tts_postnet* p, const PostnetPtrs& d, int max_columns, bool timed, const float* d_mel, const int* win_len,
+// one dynamic batch with the scratch of `d` (the arena's, or the static array's)
+static int run_batch(tts_postnet* p, const PostnetPtrs& d, int max_columns, const float* d_mel, const int* win_len,
                      const int* keep_from, int n, float* d_out)
 {
     if (!p || !d_mel || !win_len || !keep_from || !d_out) return fail(TTS_E_INVAL, "null argument");
@@ -186,7 +188,6 @@ static int run_batch(tts_postnet* p, const PostnetPtrs& d, int max_columns, bool
     const int n_col = (int)cols, n_pad = (n_col + 15) / 16 * 16;
     // the window list travels as kernel arguments, 256 windows at a time; the device expands it into the
     // per-column tables (position inside the window for the zero padding, output row of the column)
-    if (timed) HIP_TRY(hipEventRecord(p->ev0, p->stream));
     // A small call is one launch: the line is the chip's, a workgroup for every compute unit.
     const bool chain = d.chain_words && n <= PN_META_WINDOWS && n_col <= chain_most_columns(p->cfg.weight_dtype == TTS_DTYPE_BF16 ? 2 : 4);
     int c = 0, r = 0;
@@ -210,10 +211,6 @@ static int run_batch(tts_postnet* p, const PostnetPtrs& d, int max_columns, bool
         HIP_TRY(launch_postnet_pack(d, p->cfg.weight_dtype, w, d_mel, n_col, n_pad, i0 == 0, p->stream));
     }
     if (!chain) HIP_TRY(launch_postnet(d, p->cfg.weight_dtype, d_mel, n_col, d_out, p->stream));
-    if (timed) {
-        HIP_TRY(hipEventRecord(p->ev1, p->stream));
-        p->ev_valid = true;
-    }
     return TTS_OK;
 }
 
@@ -221,7 +218,9 @@ extern "C" int tts_postnet_run(tts_postnet* p, const float* d_mel, const int* wi
                                float* d_out)
 {
     if (!p) return fail(TTS_E_INVAL, "null argument");
-    return run_batch(p, p->d, p->cfg.max_columns, true, d_mel, win_len, keep_from, n, d_out);
+    const int rc = run_batch(p, p->d, p->cfg.max_columns, d_mel, win_len, keep_from, n, d_out);
+    p->ran = p->ran || rc == TTS_OK;
+    return rc;
 }
 
 extern "C" int tts_postnet_run_static(tts_postnet* p, const float* d_mel, const int* win_len, const int* keep_from, int n,
@@ -237,11 +236,12 @@ extern "C" int tts_postnet_run_static(tts_postnet* p, const float* d_mel, const 
     // (The words of a call that is one launch do not lend themselves to that: they have to be empty when it begins.)
     PostnetPtrs d = p->d;
     d.chain_words = nullptr;
+    d.stamps.at = nullptr;
     d.act[0] = base;
     d.act[1] = base + PN_STATIC_ACT;
     d.cmeta = reinterpret_cast<int*>(base + 2 * PN_STATIC_ACT);
     d.orow = reinterpret_cast<int*>(base + 2 * PN_STATIC_ACT + PN_STATIC_TABLE);
-    return run_batch(p, d, TTS_POSTNET_STATIC_MAX_COLUMNS, false, d_mel, win_len, keep_from, n, d_out);
+    return run_batch(p, d, TTS_POSTNET_STATIC_MAX_COLUMNS, d_mel, win_len, keep_from, n, d_out);
 }
 
 extern "C" int tts_postnet_set_wait_polls(tts_postnet* p, int polls)
@@ -257,16 +257,11 @@ extern "C" long long tts_postnet_one_launch_calls(const tts_postnet* p) { return
 extern "C" int tts_postnet_elapsed_ms(tts_postnet* p, float* out_ms)
 {
     if (!p || !out_ms) return fail(TTS_E_INVAL, "null argument");
-    if (!p->ev_valid) return fail(TTS_E_INVAL, "nothing has run yet");
-    HIP_TRY(hipEventSynchronize(p->ev1));
-    HIP_TRY(hipEventElapsedTime(out_ms, p->ev0, p->ev1));
-    return TTS_OK;
+    if (!p->ran) return fail(TTS_E_INVAL, "nothing has run yet");
+    return stamps_ms(p->d.stamps, p->clock_khz, p->stream, out_ms);
 }
 
 extern "C" void tts_postnet_destroy(tts_postnet* p)
 {
-    if (!p) return;
-    if (p->ev0) (void)hipEventDestroy(p->ev0);
-    if (p->ev1) (void)hipEventDestroy(p->ev1);
     delete p;
 }

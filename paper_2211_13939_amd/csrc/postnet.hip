@@ -13,8 +13,9 @@ namespace tts {
 // (two runs of one side differ by 3 %).
 template <typename XT, int CIN>
 __global__ __launch_bounds__(256) void k_pn_pack(PnWindows w, const float* __restrict__ mel, int n_col, int n_col_pad, int clear_pad,
-                                                 XT* __restrict__ X, int* __restrict__ cmeta, int* __restrict__ orow)
+                                                 XT* __restrict__ X, int* __restrict__ cmeta, int* __restrict__ orow, Stamps stamps)
 {
+    const unsigned long long t0 = stamps.now();
     constexpr int KB = Frag<XT>::KB, EPL = Frag<XT>::EPL, NG = CIN / EPL;
     static_assert(PN_N_MEL % EPL == 0 && CIN % EPL == 0, "a piece is all mel channels or all padding");
     const int i = blockIdx.x, first = blockIdx.y * 256 + threadIdx.x;
@@ -46,6 +47,7 @@ __global__ __launch_bounds__(256) void k_pn_pack(PnWindows w, const float* __res
                 orow[col] = -1;
             }
         }
+    if (clear_pad) stamps.begin(t0);
 }
 
 hipError_t launch_postnet_pack(const PostnetPtrs& d, int wdtype, const PnWindows& w, const float* mel, int n_col, int n_col_pad, bool first,
@@ -55,7 +57,7 @@ hipError_t launch_postnet_pack(const PostnetPtrs& d, int wdtype, const PnWindows
     for (int i = 0; i < w.n; ++i) most = w.len[i] > most ? w.len[i] : most;
     if (w.n < 1 || most < 1) return hipSuccess;
     auto go = [&](auto kern, int per_column, auto* x) {
-        hipLaunchKernelGGL(kern, dim3(w.n, (most * per_column + 255) / 256), dim3(256), 0, s, w, mel, n_col, n_col_pad, first ? 1 : 0, x, d.cmeta, d.orow);
+        hipLaunchKernelGGL(kern, dim3(w.n, (most * per_column + 255) / 256), dim3(256), 0, s, w, mel, n_col, n_col_pad, first ? 1 : 0, x, d.cmeta, d.orow, d.stamps);
     };
     if (wdtype == 0) go(k_pn_pack<float, PN_CIN0>, PN_CIN0 / Frag<float>::EPL, reinterpret_cast<float*>(d.act[0]));
     else go(k_pn_pack<h16_t, PN_CIN0>, PN_CIN0 / Frag<h16_t>::EPL, reinterpret_cast<h16_t*>(d.act[0]));
@@ -68,17 +70,18 @@ static hipError_t run_typed(const PostnetPtrs& d, const float* mel, int n_ctiles
     constexpr int C1 = PN_CIN0, C = PN_CHANNELS, CO = PN_COUT_LAST;
     XT* x0 = reinterpret_cast<XT*>(d.act[0]);
     XT* x1 = reinterpret_cast<XT*>(d.act[1]);
-    hipError_t e = conv_layer<XT, C1, C, PN_EPI_TANH>(d.W[0], d.b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(d.W[1], d.b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(d.W[2], d.b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(d.W[3], d.b[3], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, s);
-    if (e == hipSuccess) e = conv_layer<XT, C, CO, PN_EPI_LAST>(d.W[4], d.b[4], x0, (XT*)nullptr, d.cmeta, n_ctiles, mel, d.n_mel, d.orow, out, s);
+    hipError_t e = conv_layer<XT, C1, C, PN_EPI_TANH>(d.W[0], d.b[0], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, Stamps{}, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(d.W[1], d.b[1], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, Stamps{}, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(d.W[2], d.b[2], x0, x1, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, Stamps{}, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, C, PN_EPI_TANH>(d.W[3], d.b[3], x1, x0, d.cmeta, n_ctiles, nullptr, 0, nullptr, nullptr, Stamps{}, s);
+    if (e == hipSuccess) e = conv_layer<XT, C, CO, PN_EPI_LAST>(d.W[4], d.b[4], x0, (XT*)nullptr, d.cmeta, n_ctiles, mel, d.n_mel, d.orow, out, d.stamps, s);
     return e;
 }
 
 // The whole call as one launch (conv5_chain.h): the first layer reads the caller's frames, four layers' outputs are words, the last one
 // (five row tiles: the workgroups of the others are done before it) writes the chunks' own frames.
 template <typename XT> struct PnChain {
+    static constexpr bool TIMED = true;
     static constexpr int LAYERS = PN_LAYERS - 1, CIN = PN_CIN0, EPI = PN_EPI_TANH, EPL = Frag<XT>::EPL;
     static constexpr int LAST = PN_TAPS * PN_CHANNELS / Frag<XT>::KB / PN_WAVES;
     PnWindows w;
@@ -166,6 +169,7 @@ hipError_t launch_postnet_chain(const PostnetPtrs& d, int wdtype, const PnWindow
     p.state = d.chain_state;
     p.set_bytes = d.chain_set_bytes;
     p.polls = d.wait_polls < CHAIN_POLLS ? d.wait_polls : CHAIN_POLLS;
+    p.stamps = d.stamps;
     auto go = [&](auto job, auto type) {
         job.w = w;
         job.mel = mel;

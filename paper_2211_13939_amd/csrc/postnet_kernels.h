@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "stamps.h"
+
 namespace tts {
 
 constexpr int PN_LAYERS = 5;
@@ -52,6 +54,7 @@ struct PostnetPtrs {
     int* chain_state;           // null: no call is
     int chain_set_bytes;
     int wait_polls;             // ... and how often a workgroup polls for the others' words before it forms them itself
+    Stamps stamps;
 };
 
 // Up to PN_META_WINDOWS windows of one call, as a kernel argument (no host-to-device copy): the device

@@ -54,7 +54,7 @@ ConvShape post_shape(bool bf) { return shape_of(1, voc_channels(VOC_STAGES - 1),
 struct VocLayout {
     size_t pre_w, pre_b, up_w[VOC_STAGES], up_b[VOC_STAGES];
     size_t res_w[VOC_STAGES][VOC_BLOCKS], res_b[VOC_STAGES][VOC_BLOCKS];
-    size_t post_w, post_b, alpha, beta, m_tail, s_tail, kept, turn, len, x0, y, r[VOC_BLOCKS], total;
+    size_t post_w, post_b, alpha, beta, m_tail, s_tail, kept, turn, len, stamps, x0, y, r[VOC_BLOCKS], total;
     size_t state_begin;   // everything from here on is cleared at creation
 };
 
@@ -86,6 +86,7 @@ VocLayout layout_of(const tts_vocoder_config& c)
     l.kept = a.take((size_t)c.max_batch * n_ov * VOC_N_MEL * 4);
     l.turn = a.take((size_t)c.max_requests * 4);
     l.len = a.take(VOC_MAX_BATCH * 4);
+    l.stamps = a.take(STAMP_BYTES);
     l.x0 = a.take(frames * VOC_C0 * 4);
     // positions x channels per frame: 8 * 64, 64 * 32, 128 * 16, 256 * 8 -- at most 2048
     const size_t act = frames * 2048 * 4;
@@ -101,8 +102,8 @@ struct tts_vocoder {
     tts_vocoder_config cfg;
     VocoderPtrs d;
     hipStream_t stream = nullptr;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    bool ev_valid = false;
+    int clock_khz = 0;              // of the stamps
+    bool ran = false;
     std::vector<uint8_t> open;      // per state slot: a chunk went through and was not the last
 };
 
@@ -204,8 +205,8 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
     }
     if (rc == TTS_OK && fill_now(base + lay.state_begin, 0, lay.total - lay.state_begin) != hipSuccess)
         rc = fail(TTS_E_HIP, "clearing the state and activation buffers failed");
-    if (rc == TTS_OK && (hipEventCreate(&v->ev0) != hipSuccess || hipEventCreate(&v->ev1) != hipSuccess))
-        rc = fail(TTS_E_HIP, "hipEventCreate failed");
+    if (rc == TTS_OK && hipDeviceGetAttribute(&v->clock_khz, hipDeviceAttributeWallClockRate, attr.device) != hipSuccess)
+        rc = fail(TTS_E_HIP, "the rate of the device's clock is not known");
     if (rc) {
         tts_vocoder_destroy(v);
         return rc;
@@ -231,6 +232,7 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
     d.kept = (float*)(base + lay.kept);
     d.turn = (int*)(base + lay.turn);
     d.len = (int*)(base + lay.len);
+    d.stamps.at = (unsigned long long*)(base + lay.stamps);
     d.x0 = (float*)(base + lay.x0);
     d.y = (float*)(base + lay.y);
     for (int b = 0; b < VOC_BLOCKS; ++b) {
@@ -279,26 +281,19 @@ extern "C" int tts_vocoder_run(tts_vocoder* v, const float* d_mel, const int* n_
         if (off > 0x7FFFFFFF) return fail(TTS_E_INVAL, "more than 2^31 samples in one call");
     }
     for (int i = 0; i < n; ++i) v->open[state_slot[i]] = (flags[i] & TTS_VOCODER_LAST) ? 0 : 1;
-    HIP_TRY(hipEventRecord(v->ev0, v->stream));
     HIP_TRY(launch_vocoder(v->d, v->cfg.weight_dtype, b, d_mel, d_audio, v->stream));
-    HIP_TRY(hipEventRecord(v->ev1, v->stream));
-    v->ev_valid = true;
+    v->ran = true;
     return TTS_OK;
 }
 
 extern "C" int tts_vocoder_elapsed_ms(tts_vocoder* v, float* out_ms)
 {
     if (!v || !out_ms) return fail(TTS_E_INVAL, "null argument");
-    if (!v->ev_valid) return fail(TTS_E_INVAL, "nothing has run yet");
-    HIP_TRY(hipEventSynchronize(v->ev1));
-    HIP_TRY(hipEventElapsedTime(out_ms, v->ev0, v->ev1));
-    return TTS_OK;
+    if (!v->ran) return fail(TTS_E_INVAL, "nothing has run yet");
+    return stamps_ms(v->d.stamps, v->clock_khz, v->stream, out_ms);
 }
 
 extern "C" void tts_vocoder_destroy(tts_vocoder* v)
 {
-    if (!v) return;
-    if (v->ev0) (void)hipEventDestroy(v->ev0);
-    if (v->ev1) (void)hipEventDestroy(v->ev1);
     delete v;
 }

@@ -228,15 +228,13 @@ __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __res
 // launch still read the old tail.  Read once more by workgroups of their own they cost 0.9 us of a round of one window.)
 template <typename XT>
 __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, const float* __restrict__ d_mel, const float* __restrict__ m_tail,
-                                                          float* __restrict__ kept, int* __restrict__ len, int* __restrict__ turn, int ov, int window)
+                                                          float* __restrict__ kept, int* __restrict__ len, int* __restrict__ turn, int ov, int window,
+                                                          Stamps stamps)
 {
     constexpr int CIN = VOC_N_MEL, KS = VOC_K_PRE, TP = vc_tp<XT, CIN, VOC_C0, (KS - 1) / 2, true>();
     __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
+    const unsigned long long t0 = stamps.now();
     const int w = blockIdx.y, ovw = b.has_prev[w] ? ov : 0, valid = ovw + b.n_frames[w], p0 = blockIdx.x * TP;
-    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
-        len[w] = valid;
-        turn[b.slot[w]] ^= 1;
-    }
     if (p0 >= valid) return;
     const float* mel = d_mel + ((ptrdiff_t)b.src_row[w] - ovw) * CIN;
     const float* tail = m_tail + (size_t)b.slot[w] * ov * CIN;
@@ -250,6 +248,11 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, 
         if (p >= k0 && p < k1) *reinterpret_cast<float4*>(kept + ((size_t)w * ov + p - (valid - ov)) * CIN + 4 * c4) = v;
     };
     conv_tile<XT, CIN, VOC_C0, VOC_C0, KS, TP, EPI_PLAIN, false, 1>(a, valid, (size_t)w * window, p0, lds, fetch, keep, [](int, float) {});
+    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
+        len[w] = valid;
+        turn[b.slot[w]] ^= 1;
+        stamps.begin(t0);
+    }
 }
 
 // The last layer, and what becomes of its samples S_cur: the first ov * 256 of a window with a previous chunk are fused with the
@@ -262,7 +265,7 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, 
 template <typename XT, bool SHORT>
 __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, const float* __restrict__ alpha, const float* __restrict__ beta,
                                                          float* __restrict__ s_tail, size_t s_tail_turn, const int* __restrict__ turn, float* __restrict__ d_audio,
-                                                         const float* __restrict__ kept, float* __restrict__ m_tail, int ov, int window)
+                                                         const float* __restrict__ kept, float* __restrict__ m_tail, int ov, int window, Stamps stamps)
 {
     constexpr int CIN = voc_channels(VOC_STAGES - 1), KS = VOC_K_POST, TP = vc_tp<XT, CIN, 16, (KS - 1) / 2, SHORT>();
     __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
@@ -289,6 +292,7 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, c
     const float *in0 = a.in0 + wbase * CIN, *in1 = a.in1 + wbase * CIN, *in2 = a.in2 + wbase * CIN;
     auto fetch = [&](int p, int c4) __attribute__((always_inline)) { return Quad3{quad_at<CIN>(in0, p, c4), quad_at<CIN>(in1, p, c4), quad_at<CIN>(in2, p, c4)}; };
     conv_tile<XT, CIN, 16, 1, KS, TP, EPI_POST, true, 1>(a, valid, wbase, p0, lds, fetch, [](int, int, float4) {}, emit);
+    if (threadIdx.x == 0) stamps.end();
 }
 
 // ---------------------------------------------------------------------------
@@ -687,7 +691,7 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     pre.bias = d.pre_b;
     constexpr int PRE_TP = vc_tp<XT, VOC_N_MEL, VOC_C0, (VOC_K_PRE - 1) / 2, true>();
     hipLaunchKernelGGL((k_voc_first<XT>), dim3((d.window + PRE_TP - 1) / PRE_TP, b.n, VOC_C0 / 64), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.kept,
-                       d.len, d.turn, d.overlap, d.window);
+                       d.len, d.turn, d.overlap, d.window, d.stamps);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = stage_launch<XT, 0>(d, b.n, s);
     if (e == hipSuccess) e = stage_launch<XT, 1>(d, b.n, s);
@@ -702,7 +706,7 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     post.bias = d.post_b;
     auto last = [&](auto kern, int tp) {
         hipLaunchKernelGGL(kern, dim3((d.window * VOC_HOP + tp - 1) / tp, b.n), dim3(VC_THREADS), 0, s, b, post, d.alpha, d.beta, d.s_tail, d.s_tail_turn, d.turn, d_audio,
-                           d.kept, d.m_tail, d.overlap, d.window);
+                           d.kept, d.m_tail, d.overlap, d.window, d.stamps);
     };
     constexpr int CL = voc_channels(VOC_STAGES - 1), LONG_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2>(), SHORT_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2, true>();
     if ((long)((d.window * VOC_HOP + LONG_TP - 1) / LONG_TP) * b.n < VC_SHORT_BELOW) last(k_voc_last<XT, true>, SHORT_TP);

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "stamps.h"
+
 namespace tts {
 
 constexpr int VOC_STAGES = 4;
@@ -41,6 +43,7 @@ struct VocoderPtrs {
     float* y;           // upsampled activations of the current stage, [positions][channels]
     float* r[VOC_BLOCKS];   // output of every residual block of the current stage
     int overlap, window;    // window = overlap + max_chunk frames: the stride between windows, in frames
+    Stamps stamps;
 };
 
 // The batch as a kernel argument (no host-to-device copy).
