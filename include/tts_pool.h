@@ -166,7 +166,8 @@ int tts_pool_step(tts_pool *pool, int *out_n_active);
  * the same call is two kernel launches instead of three, and while no active
  * request's slot lies above 48 and there is no stop threshold up to 64 steps
  * are one kernel launch, where that is the faster form: above 16 slots not
- * for long texts or a step or two).
+ * for long texts or a step or two; in pools of at most 64 slots with fp32
+ * weights while no active request's slot lies above 16).
  * On a stream that the caller is capturing the steps go into his graph one by
  * one.  The pool counts them as taken by this call, so that graph is launched
  * once, before anything else of the pool. */
@@ -226,8 +227,10 @@ int tts_pool_n_active(const tts_pool *pool);
 int tts_pool_span(const tts_pool *pool);
 long long tts_pool_moves(const tts_pool *pool);
 
-/* Launches since creation that were several steps in one, or one step as such a launch (tts_pool_step_n). */
+/* Launches since creation that were several steps in one, or one step as such a launch (tts_pool_step_n): of a pool with two-byte
+ * weights, and of one with fp32 weights (each 0 for the other). */
 long long tts_pool_segments(const tts_pool *pool);
+long long tts_pool_fp32_segments(const tts_pool *pool);
 
 /* Wait until everything queued on the pool's stream has run.
  * Workgroups of one launch hand each other words (the projection's partial sums, the attention energies of a

@@ -33,7 +33,7 @@ EXPORTS = (
     "tts_pool_workspace_bytes", "tts_pool_create", "tts_pool_add_request", "tts_pool_add_requests", "tts_pool_step",
     "tts_pool_step_n", "tts_pool_drain_chunk", "tts_pool_get_stop_logits", "tts_pool_retire",
     "tts_pool_get_state", "tts_pool_set_state", "tts_pool_frames", "tts_pool_size", "tts_pool_n_active",
-    "tts_pool_span", "tts_pool_moves", "tts_pool_segments",
+    "tts_pool_span", "tts_pool_moves", "tts_pool_segments", "tts_pool_fp32_segments",
     "tts_pool_sync", "tts_pool_lost", "tts_pool_set_wait_polls", "tts_pool_timing", "tts_pool_elapsed_ms", "tts_pool_kernel_times", "tts_pool_destroy",
     "tts_last_error",
     "tts_book_create", "tts_book_add", "tts_book_step", "tts_book_drain", "tts_book_retire",
@@ -130,7 +130,7 @@ def lib() -> C.CDLL:
     L.tts_pool_size.argtypes = [vp]
     L.tts_pool_n_active.argtypes = [vp]
     L.tts_pool_span.argtypes = [vp]
-    for f in (L.tts_pool_moves, L.tts_pool_segments, L.tts_postnet_one_launch_calls, L.tts_encoder_one_launch_calls):
+    for f in (L.tts_pool_moves, L.tts_pool_segments, L.tts_pool_fp32_segments, L.tts_postnet_one_launch_calls, L.tts_encoder_one_launch_calls):
         f.restype = C.c_longlong
         f.argtypes = [vp]
     L.tts_pool_sync.argtypes = [vp]
@@ -339,6 +339,9 @@ class Pool:
 
     def segments(self) -> int:
         return lib().tts_pool_segments(self._h)
+
+    def fp32_segments(self) -> int:
+        return lib().tts_pool_fp32_segments(self._h)
 
     def lost(self, rid: int) -> bool:
         """True if the device ended the request early because a step could not be completed for it."""

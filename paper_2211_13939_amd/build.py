@@ -7,7 +7,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libtts_pool.so")
-SOURCES = ["kernels.hip", "segment.hip", "tts_pool.cpp", "postnet.hip", "postnet.cpp", "vocoder.hip", "vocoder.cpp", "encoder.hip", "encoder.cpp"]
+SOURCES = ["kernels.hip", "segment.hip", "segment32.hip", "tts_pool.cpp", "postnet.hip", "postnet.cpp", "vocoder.hip", "vocoder.cpp", "encoder.hip", "encoder.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

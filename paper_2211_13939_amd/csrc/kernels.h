@@ -46,6 +46,11 @@ constexpr size_t SEG_FIXED_BYTES = 3 * ((size_t)(32 + 32 + 16 + 8) * 1024 + (siz
 constexpr int segment_energy_bytes(int max_enc_len) { return (max_enc_len + 63) / 64 * 256; }      // per slot: a share for each of its workgroups
 constexpr size_t segment_tile_bytes(int max_enc_len) { return SEG_FIXED_BYTES + (size_t)3 * SEG_SLOTS * segment_energy_bytes(max_enc_len); }
 constexpr int segment_tiles(int max_pool) { return max_pool > SEG_TILES * SEG_SLOTS ? SEG_TILES : (max_pool + SEG_SLOTS - 1) / SEG_SLOTS; }
+// fp32 weights and memory (segment32.hip), one tile: h_att and h_dec (64 fragments), a (32), p (16), the attention LSTM's pre-sums, and the rest
+// as above
+constexpr size_t SEG32_FIXED_BYTES =
+    3 * ((size_t)(64 + 64 + 32 + 16 + HID / 4) * 1024 + (size_t)SEG_SLOTS * QUERY_PARTIALS * ATT * 4 + 96 * SEG_SLOTS * 4);
+constexpr size_t segment32_bytes(int max_enc_len) { return SEG32_FIXED_BYTES + (size_t)3 * SEG_SLOTS * segment_energy_bytes(max_enc_len); }
 constexpr size_t segment_bytes(int max_pool, int max_enc_len) { return 2 * segment_tiles(max_pool) * segment_tile_bytes(max_enc_len); }
 
 // One decoder step (paper Eq. 2) for every request whose slot is flagged in d.live.
@@ -55,6 +60,7 @@ constexpr size_t segment_bytes(int max_pool, int max_enc_len) { return 2 * segme
 // (Pools with d.hdec_x launch three kernels - the decoder LSTM is part of the last one - and record ev[3] right after ev[2].)
 constexpr int N_STEP_KERNELS = 4;
 hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, hipStream_t s);   // (launch_step's seg_steps)
+hipError_t launch_segment32(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, hipStream_t s); // (fp32)
 hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int cur, hipStream_t s, hipEvent_t* ev = nullptr);
 
 hipError_t launch_set_live(const DevPtrs& d, const LiveArgs& args, hipStream_t s);

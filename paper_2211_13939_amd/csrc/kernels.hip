@@ -2574,7 +2574,9 @@ static hipError_t step_typed(const DevPtrs& d, int n_req, int n_tiles, int lsa_s
 hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int cur, hipStream_t s, hipEvent_t* ev)
 {
     if (cfg.n_blocks < 1 || cfg.n_tiles < 1) return hipSuccess;
-    if (cfg.seg_steps > 0) return launch_segment(d, cur, cfg.n_blocks, cfg.seg_steps, cfg.seg_set, cfg.seg_empty, s);
+    if (cfg.seg_steps > 0)
+        return cfg.wdtype == 0 ? launch_segment32(d, cur, cfg.n_blocks, cfg.seg_steps, cfg.seg_set, cfg.seg_empty, s)
+                               : launch_segment(d, cur, cfg.n_blocks, cfg.seg_steps, cfg.seg_set, cfg.seg_empty, s);
     if (cfg.pre_gates) {
         if (cfg.n_tiles > MAX_TILES || !d.pre_att || !d.qpart || (cfg.pre_gates == 2) != (d.pre_dec != nullptr)) return hipErrorInvalidValue;
         if (cfg.pre_gates == 1) {

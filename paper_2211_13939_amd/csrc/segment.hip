@@ -35,12 +35,12 @@
 #include "kernels.h"
 #include "lsa_tile.h"
 #include "mfma.h"
+#include "segment_parts.h"
 #include "words.h"
 
 namespace tts {
 namespace {
 
-constexpr int NT = 512, NW = 8;
 constexpr int KB = Frag<h16_t>::KB;
 constexpr int NK_A = K_ATT / KB, NK_D = K_DEC / KB, NK_P = K_PROJ / KB;    // fragments per row tile: 56, 80, 48
 constexpr int F_H = HID / KB, F_A = ENC / KB, F_P = PRENET / KB;            // fragments of h, a, p: 32, 16, 8
@@ -55,93 +55,12 @@ constexpr int B_FRAG = 1024, B_H = F_H * B_FRAG, B_A = F_A * B_FRAG, B_P = F_P *
 constexpr int B_QS = QUERY_PARTIALS * ATT * 4, B_Q = SEG_SLOTS * B_QS, B_M = SEG_SLOTS * MEL_ROWS * 4;
 constexpr int O_HA = 0, O_HD = O_HA + 3 * B_H, O_A = O_HD + 3 * B_H, O_P = O_A + 3 * B_A, O_Q = O_P + 3 * B_P, O_M = O_Q + 3 * B_Q, O_E = O_M + 3 * B_M;
 static_assert(O_E == SEG_FIXED_BYTES, "the arena's share");
-__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
 
 // a lane's offset in a fragment: of h_att and p ([fragment][slot][32 halves]), of h_dec ([half a fragment][slot][16 halves]: one of the
 // decoder LSTM's workgroups stores half a fragment) and of a ([slot][512 halves])
 __device__ __forceinline__ int off_hp(int col, int g) { return col * 64 + g * 16; }
 __device__ __forceinline__ int off_hd(int col, int g) { return ((g >> 1) * SEG_SLOTS + col) * 32 + (g & 1) * 16; }
 __device__ __forceinline__ int off_a(int col, int g) { return col * (ENC * 2) + g * 16; }
-
-// x of the lane 16 or 32 away, and of the lanes of a row of 16 at a distance: the sums below add the same pairs as the
-// step's kernels do with shuffles, without a trip through LDS each
-__device__ __forceinline__ float xor16(float v)
-{
-    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(threadIdx.x & 16 ? sw[0] : sw[1]);
-}
-__device__ __forceinline__ float xor32(float v)
-{
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(threadIdx.x & 32 ? sw[0] : sw[1]);
-}
-template <int N> __device__ __forceinline__ float ror16(float v)
-{
-    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x120 + N, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float wave_sum_fast(float v)
-{
-    v += xor32(v);
-    v += xor16(v);
-    v += ror16<8>(v);      // from here on a row's values repeat every eight, four, two lanes: a rotation meets the lane an xor would
-    v += ror16<4>(v);
-    v += ror16<2>(v);
-    v += ror16<1>(v);
-    return v;
-}
-
-// operands that do not change from step to step stay as they are loaded: without this the compiler keeps their conversions, twice
-// the registers, outside of the loop over the steps
-__device__ __forceinline__ void keep(u32x4_t& v) { asm volatile("" : "+v"(v)); }
-__device__ __forceinline__ uint4 as_uint4(const u32x4_t& v) { return make_uint4(v.x, v.y, v.z, v.w); }
-
-__device__ __forceinline__ void cell(const floatx4& g, float& c, float& h)
-{
-    const float gi = sigmoidf_(g[0]), gf = sigmoidf_(g[1]);
-    const float gg = tanhf_(g[2]), go = sigmoidf_(g[3]);
-    c = gf * c + gi * gg;
-    h = go * tanhf_(c);
-}
-
-// What a workgroup knows of the requests: the steps each slot still has to take, from the segment's first on (0: no request there).
-struct Pool {
-    int cur, n_steps, n_tiles, tile_bytes;
-    const int* rem;                                         // [n_tiles * 16], in LDS
-};
-// the requests that take part in step s end here
-__device__ __forceinline__ void give_up(const DevPtrs& d, const Pool& pl, int s)
-{
-    if ((int)threadIdx.x < pl.n_tiles * 16 && s < pl.rem[threadIdx.x]) {
-        d.done[threadIdx.x] = 1;
-        d.failed[threadIdx.x] = 1;
-        *d.fault = 1;
-    }
-}
-
-__device__ __forceinline__ void lose_one(const DevPtrs& d, int slot)
-{
-    if (threadIdx.x == 0) {
-        d.done[slot] = 1;
-        d.failed[slot] = 1;
-        *d.fault = 1;
-    }
-}
-
-// A barrier at which the waves also learn whether one of them gave up waiting.  `failed` holds the first phase in which one did
-// and phases only grow, so a wave that is late to look does not see the failure of a later phase.
-struct Phases {
-    int* failed;
-    int ph = 0;
-    __device__ __forceinline__ void sync(bool ok)
-    {
-        if (!ok) atomicMin(failed, ph);
-        lds_barrier();
-        ++ph;
-    }
-    __device__ __forceinline__ bool bad() const { return *failed < ph; }
-};
-
-__device__ __forceinline__ int next3(int b) { return b == 2 ? 0 : b + 1; }
 
 constexpr int ATT_LDS_RT = 2;                               // row tiles whose late fragments lie in LDS: registers hold six
 constexpr int ATT_LATE = 6;                                 // late fragments per wave and row tile: two of a, four of h_att

@@ -93,6 +93,8 @@ bool pre_dec_for(const tts_config& c) { return pre_gates_for(c) && (c.max_pool +
 // and its sums over H_att formed beside the attention kernel, in the same launch: that kernel is a chain of waits that
 // leaves a CU's load path idle, and two of its workgroups fit a CU only with two-byte operands and memory
 bool pre_dec_hatt_for(const tts_config& c) { return pre_dec_for(c) && c.weight_dtype == TTS_DTYPE_BF16 && c.memory_dtype == TTS_DTYPE_BF16; }
+// pools whose steps can run as segments, one launch for many: two-byte ones in up to three tiles of slots, fp32 ones (weights and memory) in one
+bool segments32_for(const tts_config& c) { return pre_dec_for(c) && c.weight_dtype == TTS_DTYPE_F32 && c.memory_dtype == TTS_DTYPE_F32; }
 // pools whose last kernel's launch holds the decoder LSTM and hands H_dec to the projection as words: those, and pools of
 // more than 64 slots with two-byte weights
 bool hdec_words_for(const tts_config& c) { return pre_dec_hatt_for(c) || (pre_gates_for(c) && !pre_dec_for(c) && c.weight_dtype == TTS_DTYPE_BF16); }
@@ -159,7 +161,7 @@ Layout make_layout(const tts_config& c)
     l.p_x = a.take((pre_dec_hatt_for(c) ? S / 16 : 0) * (size_t)(PRENET / 32) * 64 * 4 * 8);
     l.pre_x = a.take((pre_dec_hatt_for(c) ? S / 16 : 0) * (size_t)(HID / 4) * 64 * 4 * 8);
     l.wg_seq = a.take(2 * 4);
-    l.seg_x = a.take(pre_dec_hatt_for(c) ? segment_bytes(c.max_pool, c.max_enc_len) : 0);
+    l.seg_x = a.take(pre_dec_hatt_for(c) ? segment_bytes(c.max_pool, c.max_enc_len) : segments32_for(c) ? 2 * segment32_bytes(c.max_enc_len) : 0);
     l.seg_bytes = a.off - l.seg_x;
     l.stage = a.take(ML * ENC * 4);
     l.total = a.off;
@@ -246,7 +248,8 @@ struct tts_pool {
     std::unique_ptr<PoolBook> book;
     int parity = 0;               // activation buffer half the next step reads
     long long n_moves = 0;        // requests moved to lower slots since creation
-    long long n_segments = 0;     // launches of segments
+    long long n_segments = 0;     // launches of segments, of pools with two-byte weights ...
+    long long n_segments32 = 0;   // ... and with fp32 weights
     int slot_span = 0;            // highest active slot + 1 (as last uploaded): what the per-slot grids must cover
     bool stop_enabled = false;
     bool timing = false;
@@ -431,8 +434,8 @@ extern "C" int tts_pool_create(const tts_config* cfg, const tts_weights* w, void
     d.p_x = pre_dec_hatt_for(*cfg) ? reinterpret_cast<unsigned long long*>(base + l.p_x) : nullptr;
     d.pre_x = pre_dec_hatt_for(*cfg) ? reinterpret_cast<unsigned long long*>(base + l.pre_x) : nullptr;
     d.wg_seq = reinterpret_cast<unsigned*>(base + l.wg_seq);
-    d.seg_x = pre_dec_hatt_for(*cfg) ? base + l.seg_x : nullptr;
-    d.seg_slots = segment_tiles(cfg->max_pool) * SEG_SLOTS;
+    d.seg_x = pre_dec_hatt_for(*cfg) || segments32_for(*cfg) ? base + l.seg_x : nullptr;
+    d.seg_slots = segments32_for(*cfg) ? SEG_SLOTS : segment_tiles(cfg->max_pool) * SEG_SLOTS;
     // one pinned word the kernels can reach: a projection leader that gives up on its helpers says so here
     {
         hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&p->h_fault), sizeof(int), hipHostMallocMapped);
@@ -751,11 +754,12 @@ static int fewest_segment_steps(int tiles, int longest)
     return longest <= 160 ? 2 : longest <= 320 ? 3 : longest <= 352 ? 8 : longest <= 384 ? 16 : MAX_SEGMENT_STEPS + 1;
 }
 
-// How many of the next `n` steps run as one launch (segment.hip; 0: they run step by step).  The line is the form's own: two-byte weights
-// and memory (d.seg_x), frame counts known beforehand, and the slots up to which it is the faster one.  Chunks of 40 steps of requests
+// How many of the next `n` steps run as one launch (segment.hip; 0: they run step by step).  The line is the form's own: weights and memory of
+// one width (d.seg_x), frame counts known beforehand, and the slots up to which it is the faster one.  Chunks of 40 steps of requests
 // of 165 positions, steps as launches in graphs -> as one launch: 1 request 16.8 -> 9.7 us a step, 8: 18.2 -> 10.3, 16: 18.5 -> 11.2,
 // 20: 19.7 -> 13.5, 32: 20.4 -> 13.8, 48: 21.2 -> 17.7; with four tiles, 64 requests, 21.6 -> 21.5.  Single steps, each waited for: 1 request
-// 49 -> 30 us.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other streams that
+// 49 -> 30 us.  fp32 pools (segment32.hip) in one tile take it always: calls of 40 steps, 1 request of 60 positions 37.3 -> 14.9 us a step, 16 of 60 38.9 ->
+// 17.0, of 250 39.9 -> 20.7, of 1024 50.3 -> 46.8, 8 of 1024 49.6 -> 28.5; single steps, 16 of 60 44.8 -> 24.4, of 1024 56.8 -> 55.8.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other streams that
 // needs every compute unit gets them at intervals.
 static int segment_steps(const tts_pool* p, int n)
 {
@@ -767,7 +771,7 @@ static int segment_steps(const tts_pool* p, int n)
         longest = std::max(longest, si.L);
     }
     const int g = std::min({n, most, MAX_SEGMENT_STEPS});
-    return g >= fewest_segment_steps((p->slot_span + 15) / 16, longest) ? g : 0;
+    return p->cfg.weight_dtype == TTS_DTYPE_F32 || g >= fewest_segment_steps((p->slot_span + 15) / 16, longest) ? g : 0;
 }
 static int launch_segment_steps(tts_pool* p, int g)
 {
@@ -781,7 +785,7 @@ static int launch_segment_steps(tts_pool* p, int g)
     HIP_TRY(launch_step(p->d, sl, p->parity, p->stream));
     p->seg_set ^= 1;
     p->seg_used = sl.n_tiles;
-    ++p->n_segments;
+    ++(p->cfg.weight_dtype == TTS_DTYPE_BF16 ? p->n_segments : p->n_segments32);
     return TTS_OK;
 }
 
@@ -1111,6 +1115,7 @@ extern "C" int tts_pool_n_active(const tts_pool* p) { return p ? (int)p->book->a
 extern "C" int tts_pool_span(const tts_pool* p) { return p ? p->book->span() : 0; }
 extern "C" long long tts_pool_moves(const tts_pool* p) { return p ? p->n_moves : 0; }
 extern "C" long long tts_pool_segments(const tts_pool* p) { return p ? p->n_segments : 0; }
+extern "C" long long tts_pool_fp32_segments(const tts_pool* p) { return p ? p->n_segments32 : 0; }
 
 extern "C" int tts_pool_sync(tts_pool* p)
 {

@@ -1,0 +1,103 @@
+"""Steps as one launch in fp32 pools (csrc/segment32.hip: the running requests in the first 16 slots) against the same steps as launches
+of their own (use_graph=False): the same bits, frames and carried state."""
+import numpy as np
+import pytest
+
+from paper_2211_13939_amd import binding, synth
+from tests.helpers import make_pool, say
+from tests.test_gpu_segment import _same
+
+pytestmark = pytest.mark.gpu
+
+
+def _both(weights, lengths, frames, calls, max_pool=16, max_enc_len=1024, spoil=None, later=(), forms=(True, False)):
+    wl = synth.small_workload(len(lengths), 5, 90, 8, 8, seed=31)
+    out = []
+    for use_graph in forms:
+        pool = make_pool(wl, weights, max_pool=max_pool, max_enc_len=max_enc_len, max_steps=80, chunk_frames=40, use_graph=use_graph)
+        rng = np.random.default_rng(5)
+        enc = [rng.standard_normal((L, wl.dims["enc_dim"])).astype(np.float32) for L in lengths]
+        if spoil is not None:
+            enc[0].view(np.uint32)[lengths[0] // 2, 3] = spoil
+        n_first = len(lengths) - len(later)
+        ids = pool.add_requests(enc[:n_first], frames[:n_first])
+        for k, n in enumerate(calls):
+            ids += [pool.add_request(enc[n_first + j], frames[n_first + j]) for j, at in enumerate(later) if at == k]
+            pool.step_n(n)
+        pool.sync()
+        mel = [pool.drain_all(r) for r in ids]
+        state = [{name: pool.get_state(r, name) for name in binding.STATE} for r in ids]
+        stop = [pool.stop_logits(r, 0, m.shape[0]) for r, m in zip(ids, mel)]
+        assert (pool.fp32_segments() > 0) == use_graph and pool.segments() == 0
+        out.append((mel, state, stop, pool.fp32_segments()))
+        pool.close()
+    return out
+
+
+@pytest.mark.parametrize("lengths,frames,calls", [
+    ([1], [2], [2]),                                                       # the smallest
+    ([165], [41], [3, 1, 37]),                                             # odd calls, a single step among them
+    ([17, 256, 257], [5, 80, 44], [64, 16]),                               # four workgroups a request keep 256 positions in registers
+    ([513, 512], [9, 12], [12]),                                           # ... and the processed memory of 512
+    ([1024, 16, 1023, 15], [33, 2, 64, 65], [1, 32, 31, 1]),               # the longest texts; ends inside a call and at its end
+    ([31 + 40 * i for i in range(8)], [40 - i for i in range(8)], [40]),   # eight slots, and nine: two workgroups a request
+    ([33 + 20 * i for i in range(9)], [12 + i for i in range(9)], [7, 13]),
+    ([128, 129, 256, 257, 600] + [20 + 9 * i for i in range(11)], [10 + 3 * i for i in range(16)], [20, 35]),   # ... which keep 128 positions
+], ids=lambda v: None)
+def test_segment_equals_steps(lengths, frames, calls, weights_fp32):
+    say(f"case: fp32 segments of {calls} steps, texts of {lengths}, frames {frames}")
+    out = _both(weights_fp32, lengths, frames, calls)
+    _same(out, frames)
+    assert out[0][3] == len(calls)
+
+
+def test_segments_between_steps_of_a_larger_pool(weights_fp32):
+    say("case: 12 fp32 requests, 20 more for eight steps, segments again")
+    lengths, frames = [20 + 4 * i for i in range(32)], [60] * 12 + [8] * 20
+    out = _both(weights_fp32, lengths, frames, [15, 8, 12, 25], max_pool=64, max_enc_len=160, later=[1] * 20)
+    _same(out, frames)
+    assert out[0][3] == 3
+
+
+@pytest.mark.parametrize("spoil", [0xFFFFFFFF, 0x7F800000, 0x7FC00000])
+def test_segment_with_values_that_are_no_numbers(spoil, weights_fp32):
+    """A value with all bits set must not be taken for a word that is missing, and another request must not notice."""
+    say(f"case: an encoder output with the bits {spoil:#x} beside an ordinary one")
+    (mel, _, _, _), = _both(weights_fp32, [30, 40], [24, 24], [24], max_enc_len=64, spoil=spoil, forms=(True,))
+    (clean, _, _, _), = _both(weights_fp32, [30, 40], [24, 24], [24], max_enc_len=64, forms=(True,))
+    assert mel[0].shape == (24, 80) and not np.array_equal(mel[0], clean[0])
+    np.testing.assert_array_equal(mel[1], clean[1])
+
+
+def test_segment_with_a_large_attention_vector(weights_fp32):
+    say("case: attention vector times 40")
+    w = dict(weights_fp32)
+    w["v"] = w["v"] * 40
+    assert np.abs(w["v"]).sum() > 30
+    frames = [20, 33]
+    _same(_both(w, [70, 600], frames, [33]), frames)
+
+
+def test_segments_beside_other_work(weights_fp32):
+    """Another stream keeps the compute units busy with products that end by themselves."""
+    import torch
+    say("case: fp32 segments of 16 slots while a second stream runs large matrix products")
+    wl = synth.small_workload(16, 5, 90, 24, 24, seed=31)
+    out = []
+    for busy in (False, True):
+        pool = make_pool(wl, weights_fp32, max_pool=16, max_enc_len=90, max_steps=24, chunk_frames=24)
+        ids = pool.add_requests([wl.encoder_outputs(i) for i in range(16)], [24] * 16)
+        if busy:
+            side = torch.cuda.Stream(device=pool.device)
+            a = torch.randn(4096, 4096, device=pool.device)
+            with torch.cuda.stream(side):
+                for _ in range(40):
+                    a = (a @ a) * 1e-4
+        for k in (4, 1, 7, 12):
+            pool.step_n(k)
+        pool.sync()                      # raises if a wait ran out
+        assert pool.fp32_segments() == 4
+        out.append([pool.drain_all(r) for r in ids])
+        pool.close()
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
