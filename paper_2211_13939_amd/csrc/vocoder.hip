@@ -331,12 +331,12 @@ struct VrArgs3 { VrArgs b[VOC_BLOCKS]; };
 
 constexpr int VR_LDS_MAX = 160 * 1024;
 
-// The weights stream from L1 / L2 into a ring of registers, VR_AHEAD fragments ahead of the products (6 and 11 ahead: a round of one
-// window 0.6 and 4.5 us longer); the first ones of a convolution are requested before the operand is put in LDS.  (Through LDS, as a
-// first version had them, they were a quarter to a half of its traffic, and a convolution's 88 KB at 64 channels went through the CU in one burst.)  Two operand buffers,
+// The weights stream from L1 / L2 into a ring of registers one or two k steps ahead of the products, and on from one convolution into the next: the
+// first ones of a convolution are requested behind the last products of the one before.  (Through LDS, as a first version had them, they were a
+// quarter to a half of its traffic, and a convolution's 88 KB at 64 channels went through the CU in one burst.  Four steps ahead, with the ring filled
+// anew for every convolution, calls of 16 / 64 / 128 windows of 44 frames took 131 / 274 / 481 us, like this 128 / 269 / 469.)  Two operand buffers,
 // where LDS holds them, so that one barrier per convolution is enough and a wave that is done prepares the next operand
 // while others still read this one.
-constexpr int VR_AHEAD = 4;
 
 template <typename XT, int C, int KS, int TP, bool HALO> struct VrGeom {
     using G = VcGeom<XT, C>;
@@ -349,13 +349,19 @@ template <typename XT, int C, int KS, int TP, bool HALO> struct VrGeom {
     static constexpr int CGROUPS = THREADS / 64 / RGROUPS;
     static constexpr int HALF = (KS - 1) / 2;
     static constexpr int H = HALO ? HALF * 12 : 0;            // sum over d = 1, 3, 5 of (d + 1) * HALF
+    static constexpr int H_MOST = HALO ? (voc_block_k(VOC_BLOCKS - 1) - 1) / 2 * 12 : 0;
     static constexpr int PW = PAIR ? 32 : 16;                 // positions per column tile
-    static constexpr int NCOL = (TP + 2 * H + CGROUPS * PW - 1) / (CGROUPS * PW);       // column tiles per wave
+    static constexpr int NCOL = (TP + 2 * H_MOST + CGROUPS * PW - 1) / (CGROUPS * PW);  // column tiles per wave
     static constexpr int W = CGROUPS * PW * NCOL;             // positions of the region
+    // ... of which so many come out right: TP or a little more with the longest kernel, more with the others, whose halo is shorter.  (With
+    // TP of them in every block, 128 windows of 44 frames 481 us, like this 473)
+    static constexpr int OUT = HALO ? W - 2 * H : TP;
     static constexpr int RT = (PAIR ? 2 * C : C) / 16 / RGROUPS;          // row tiles per wave
     static constexpr int TAPS = PAIR ? KS + 1 : KS;
     static constexpr int NK = TAPS * C / Frag<XT>::KB;
-    static constexpr int AHEAD = NK < VR_AHEAD ? NK : VR_AHEAD;
+    // (ten products a k step are 160 cycles: with two steps ahead there 128 windows 464 -> 472 us, with one where there are fewer products 32
+    // windows 165.8 -> 169.2)
+    static constexpr int AHEAD = RT * NCOL >= 10 || NK == 1 ? 1 : 2;
     // zero rows on each side: the widest tap offset
     static constexpr int PAD = PAIR ? (5 * (HALF + 1) + 1) / 2 : 5 * HALF;
     static constexpr int PLANE = (PAIR ? W / 2 : W) + 2 * PAD;            // rows of a plane
@@ -390,12 +396,12 @@ template <typename R> struct VrWeights {
     }
 };
 template <typename R> using VrRing = uint4[R::AHEAD][R::RT];
-template <typename R> __device__ __forceinline__ void ring_fill(VrRing<R>& ring, const VrWeights<R>& W, int conv)
+template <typename R> __device__ __forceinline__ void ring_fill(VrRing<R>& ring, const VrWeights<R>& W)
 {
 #pragma unroll
     for (int kf = 0; kf < R::AHEAD; ++kf)
 #pragma unroll
-        for (int rt = 0; rt < R::RT; ++rt) ring[kf][rt] = W.at(conv, rt, kf);
+        for (int rt = 0; rt < R::RT; ++rt) ring[kf][rt] = W.at(0, rt, kf);
 }
 
 // acc += W * operand, or bias + W * operand (INIT).  A k step's B fragments are requested before the products of the step before.
@@ -405,7 +411,7 @@ __device__ __forceinline__ void conv_regs(const VrWeights<R>& W, int conv, VrRin
 {
     using G = typename R::G;
     constexpr int NK = R::NK, RT = R::RT, NCOL = R::NCOL, GP = G::GP;
-    const int n = lane & 15, g = lane >> 4;
+    const int n = lane & 15, g = lane >> 4, next = min(conv + 1, 2 * VOC_PAIRS - 1);      // (the last one's request is dropped)
     // this lane's 16 bytes of k in fragment kf: piece 4 kf + g = (tap, channel group)
     auto b_at = [&](int kf) __attribute__((always_inline)) {
         constexpr int STEP = GP < 4 ? 4 / GP : 1;             // taps per fragment
@@ -430,8 +436,10 @@ __device__ __forceinline__ void conv_regs(const VrWeights<R>& W, int conv, VrRin
         uint4 af[RT];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-            af[rt] = ring[kf % R::AHEAD][rt];
-            if (kf + R::AHEAD < NK) ring[kf % R::AHEAD][rt] = W.at(conv, rt, kf + R::AHEAD);
+            constexpr int PHASE = INIT ? 0 : NK % R::AHEAD;
+            uint4& r = ring[(kf + PHASE) % R::AHEAD][rt];
+            af[rt] = r;
+            r = kf + R::AHEAD < NK ? W.at(conv, rt, kf + R::AHEAD) : W.at(next, rt, kf + R::AHEAD - NK);
         }
         if (kf + 1 < NK) request(kf + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -443,9 +451,11 @@ __device__ __forceinline__ void conv_regs(const VrWeights<R>& W, int conv, VrRin
 }
 
 template <typename XT, int C, int KS, int TP, bool HALO>
-__device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t wbase, int p0, uint4* lds)
+__device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t wbase, int tile, uint4* lds)
 {
     using R = VrGeom<XT, C, KS, TP, HALO>;
+    const int p0 = tile * R::OUT;
+    if (p0 >= valid) return;
     using G = typename R::G;
     constexpr int RT = R::RT, NCOL = R::NCOL;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -486,7 +496,7 @@ __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t
                 x[rt][ct] = *reinterpret_cast<const floatx4*>(in + byte_at(p, rt));
             }
     }
-    ring_fill<R>(ring, weights, 0);
+    ring_fill<R>(ring, weights);
     for (int i = tid; i < 2 * VOC_PAIRS * C; i += R::THREADS) lds_bias[i] = a.bias[i];
     // Rows in front of and behind the region, and those of positions outside the window, are zero: nothing but a pair's second
     // position a little past the region's end is ever stored there.
@@ -539,7 +549,6 @@ __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t
         floatx4 t[RT][NCOL], b[RT];
         biases(2 * pair, b);
         conv_regs<XT, R, true>(weights, 2 * pair, ring, d, lds, 0, col0, lane, b, t);
-        ring_fill<R>(ring, weights, 2 * pair + 1);
         if constexpr (!R::TWO) lds_barrier();     // every wave has read the old operand
         __builtin_amdgcn_s_setprio(2);            // vector work goes ahead of the products of the wave it shares a SIMD with
         put(lds1, 1, t, d);
@@ -552,7 +561,6 @@ __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t
         lds_barrier();
         conv_regs<XT, R, false>(weights, 2 * pair + 1, ring, 1, lds1, 1, col0, lane, b, x);
         if (pair + 1 < VOC_PAIRS) {
-            ring_fill<R>(ring, weights, 2 * pair + 2);
             if constexpr (!R::TWO) lds_barrier();
             __builtin_amdgcn_s_setprio(2);
             put(lds, 0, x, 1);
@@ -560,7 +568,7 @@ __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t
             lds_barrier();
         }
     }
-    const int o0 = R::H, o1 = min(R::H + TP, valid - pbase);  // positions of the region that are this tile's output
+    const int o0 = R::H, o1 = min(R::H + R::OUT, valid - pbase);  // positions of the region that are this tile's output
     const int c = column();
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -576,12 +584,11 @@ template <typename XT, int C, int TP, bool HALO>
 __global__ __launch_bounds__((VrGeom<XT, C, 3, TP, HALO>::THREADS), C == 8 ? (sizeof(XT) == 2 ? 4 : 3) : 2) void k_vres(VrArgs3 a3, const int* __restrict__ len, int rate, int window)
 {
     extern __shared__ uint4 lds_dyn[];
-    const int w = blockIdx.y, valid = len[w] * rate, p0 = blockIdx.x * TP;
-    if (p0 >= valid) return;
+    const int w = blockIdx.y, valid = len[w] * rate, tile = blockIdx.x;
     const size_t wbase = (size_t)w * window * rate;
-    if (blockIdx.z == 2) resblock_tile<XT, C, 3, TP, HALO>(a3.b[0], valid, wbase, p0, lds_dyn);
-    else if (blockIdx.z == 1) resblock_tile<XT, C, 7, TP, HALO>(a3.b[1], valid, wbase, p0, lds_dyn);
-    else resblock_tile<XT, C, 11, TP, HALO>(a3.b[2], valid, wbase, p0, lds_dyn);
+    if (blockIdx.z == 2) resblock_tile<XT, C, 3, TP, HALO>(a3.b[0], valid, wbase, tile, lds_dyn);
+    else if (blockIdx.z == 1) resblock_tile<XT, C, 7, TP, HALO>(a3.b[1], valid, wbase, tile, lds_dyn);
+    else resblock_tile<XT, C, 11, TP, HALO>(a3.b[2], valid, wbase, tile, lds_dyn);
 }
 
 // grid = (tiles of a window, windows, row groups).  SHORT: tiles of 64 positions - for the layer that runs at one position
@@ -615,7 +622,8 @@ hipError_t blocks_launch_tp(const VrArgs3& a, const int* len, int rate, int wind
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const dim3 grid(HALO ? (window * rate + TP - 1) / TP : 1, n_windows, VOC_BLOCKS);
+    constexpr int OUT = VrGeom<XT, C, voc_block_k(VOC_BLOCKS - 1), TP, HALO>::OUT;       // (the others have as many tiles or fewer)
+    const dim3 grid(HALO ? (window * rate + OUT - 1) / OUT : 1, n_windows, VOC_BLOCKS);
     hipLaunchKernelGGL(kern, grid, dim3(VrGeom<XT, C, 3, TP, HALO>::THREADS), LDS, s, a, len, rate, window);
     return hipSuccess;
 }
