@@ -54,7 +54,7 @@ ConvShape post_shape(bool bf) { return shape_of(1, voc_channels(VOC_STAGES - 1),
 struct VocLayout {
     size_t pre_w, pre_b, up_w[VOC_STAGES], up_b[VOC_STAGES];
     size_t res_w[VOC_STAGES][VOC_BLOCKS], res_b[VOC_STAGES][VOC_BLOCKS];
-    size_t post_w, post_b, alpha, beta, m_tail, s_tail, kept, turn, len, stamps, x0, y, r[VOC_BLOCKS], total;
+    size_t post_w, post_b, alpha, beta, m_tail, s_tail, kept, turn, len, call, stamps, x0, y, r[VOC_BLOCKS], total;
     size_t state_begin;   // everything from here on is cleared at creation
 };
 
@@ -86,6 +86,7 @@ VocLayout layout_of(const tts_vocoder_config& c)
     l.kept = a.take((size_t)c.max_batch * n_ov * VOC_N_MEL * 4);
     l.turn = a.take((size_t)c.max_requests * 4);
     l.len = a.take(VOC_MAX_BATCH * 4);
+    l.call = a.take(VOC_MAX_BATCH * 16);
     l.stamps = a.take(STAMP_BYTES);
     l.x0 = a.take(frames * VOC_C0 * 4);
     // positions x channels per frame: 8 * 64, 64 * 32, 128 * 16, 256 * 8 -- at most 2048
@@ -232,6 +233,7 @@ extern "C" int tts_vocoder_create(const tts_vocoder_config* cfg, const tts_vocod
     d.kept = (float*)(base + lay.kept);
     d.turn = (int*)(base + lay.turn);
     d.len = (int*)(base + lay.len);
+    d.call = (int4*)(base + lay.call);
     d.stamps.at = (unsigned long long*)(base + lay.stamps);
     d.x0 = (float*)(base + lay.x0);
     d.y = (float*)(base + lay.y);

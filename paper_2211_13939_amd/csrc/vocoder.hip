@@ -89,12 +89,12 @@ struct Quad3 {
 //   fetch  (position that exists, channel / 4) -> Quad1 or Quad3
 //   seen   (position, channel / 4, the four values): every piece that is staged, among them such as lie outside the window (values of no meaning)
 //   emit   (position, sample): EPI_POST, instead of a store
-template <typename XT, int CIN, int ROWS, int COUT, int KS, int TP, int EPI, bool PRE_ACT, int U, typename FETCH, typename SEEN, typename EMIT>
+template <typename XT, int CIN, int ROWS, int COUT, int KS, int TP, int EPI, bool PRE_ACT, int U, int RG, typename FETCH, typename SEEN, typename EMIT>
 __device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wbase, int p0, uint4* lds, FETCH fetch, SEEN seen, EMIT emit)
 {
     using G = VcGeom<XT, CIN>;
     constexpr int KB = Frag<XT>::KB;
-    constexpr int RT = ROWS / 16, RG = RT < 4 ? RT : 4, CT = TP / (16 * VC_WAVES);
+    constexpr int RT = ROWS / 16, CT = TP / (16 * VC_WAVES);
     constexpr int NK = (KS * CIN + KB - 1) / KB;     // K fragments (the weights are zero padded to whole fragments)
     constexpr int NQ = KS * G::GP;                   // 16-byte pieces of k that exist
     constexpr int C4 = CIN / 4;
@@ -102,6 +102,18 @@ __device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wba
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     constexpr int halo = (KS - 1) / 2, nrows = TP + 2 * halo, STRIDE = vc_stride(nrows);
+
+    // The workgroup's share of the output rows: row group blockIdx.z.  Its weights stream from L2 / HBM through a ring of registers, requested
+    // VC_AHEAD k steps before they are used, or, where it has one row tile, all of them here: a window's few dozen positions leave nothing else to
+    // wait behind.
+    const int rt0 = blockIdx.z * RG;
+    const uint4* Wl = a.W + (size_t)rt0 * NK * 64 + lane;
+    constexpr int AHEAD = RG == 1 || NK < VC_AHEAD ? NK : VC_AHEAD;
+    uint4 ring[AHEAD][RG];
+#pragma unroll
+    for (int d = 0; d < AHEAD; ++d)
+#pragma unroll
+        for (int rg = 0; rg < RG; ++rg) ring[d][rg] = Wl[((size_t)rg * NK + d) * 64];
 
     // ---- stage positions [p0 - halo, p0 + TP + halo): activation and operand type applied once per element; a few pieces of every
     // thread are requested together, from clamped positions
@@ -129,22 +141,12 @@ __device__ __forceinline__ void conv_tile(const VcArgs& a, int valid, size_t wba
     __syncthreads();
 
     const int colbase = wave * (TP / VC_WAVES);
-    // The workgroup's share of the output rows: row group blockIdx.z.  Its weights stream from L2 / HBM through a
-    // ring of registers, requested VC_AHEAD k steps before they are used.
     {
-        const int rt0 = blockIdx.z * RG;
         floatx4 acc[RG][CT];
 #pragma unroll
         for (int rg = 0; rg < RG; ++rg)
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) acc[rg][ct] = floatx4{0.f, 0.f, 0.f, 0.f};
-        const uint4* Wl = a.W + (size_t)rt0 * NK * 64 + lane;
-        constexpr int AHEAD = NK < VC_AHEAD ? NK : VC_AHEAD;
-        uint4 ring[AHEAD][RG];
-#pragma unroll
-        for (int d = 0; d < AHEAD; ++d)
-#pragma unroll
-            for (int rg = 0; rg < RG; ++rg) ring[d][rg] = Wl[((size_t)rg * NK + d) * 64];
 #pragma unroll
         for (int kf = 0; kf < NK; ++kf) {
             uint4 af[RG];
@@ -203,7 +205,7 @@ template <int CIN> __device__ __forceinline__ float4 quad_at(const float* window
 }
 
 // grid = (tiles of a window, windows, row groups): one convolution of one kind
-template <typename XT, int CIN, int ROWS, int COUT, int KS, int EPI, bool PRE_ACT, bool SRC3, int U, bool SHORT>
+template <typename XT, int CIN, int ROWS, int COUT, int KS, int EPI, bool PRE_ACT, bool SRC3, int U, bool SHORT, int RG>
 __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __restrict__ len, int rate, int window)
 {
     constexpr int TP = vc_tp<XT, CIN, ROWS, (KS - 1) / 2, SHORT>();
@@ -216,7 +218,7 @@ __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __res
         if constexpr (SRC3) return Quad3{quad_at<CIN>(in0, p, c4), quad_at<CIN>(in1, p, c4), quad_at<CIN>(in2, p, c4)};
         else return Quad1{quad_at<CIN>(in0, p, c4)};
     };
-    conv_tile<XT, CIN, ROWS, COUT, KS, TP, EPI, PRE_ACT, U>(a, valid, wbase, p0, lds, fetch, [](int, int, float4) {}, [](int, float) {});
+    conv_tile<XT, CIN, ROWS, COUT, KS, TP, EPI, PRE_ACT, U, RG>(a, valid, wbase, p0, lds, fetch, [](int, int, float4) {}, [](int, float) {});
 }
 
 // The first layer, on the spliced windows [tail(M_pre), M_cur] (Eq. 3 line 1), which exist nowhere else: frames [0, ov) of a window
@@ -224,11 +226,12 @@ __global__ __launch_bounds__(VC_THREADS) void k_vconv(VcArgs a, const int* __res
 // be aligned to them).  Publishes the windows' lengths.  (A launch that wrote the windows to memory first took 2.9 us for one
 // window, 4.4 us for 64.)
 // The frames that become the slot's tail(M_pre) are kept aside while they are staged, so that this launch is the only one to read the
-// caller's frames: his samples, which the last one writes, may lie where they lay.  (They wait in `kept`, since other workgroups of this
+// caller's frames: his samples, which the last one writes, may lie where they lay.  What the last launch has to know of a window
+// lies in device memory then, in one piece (from a list of windows among its own arguments: 8 windows 95.8 us, like this 94.5).  (They wait in `kept`, since other workgroups of this
 // launch still read the old tail.  Read once more by workgroups of their own they cost 0.9 us of a round of one window.)
-template <typename XT>
+template <typename XT, int RG>
 __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, const float* __restrict__ d_mel, const float* __restrict__ m_tail,
-                                                          float* __restrict__ kept, int* __restrict__ len, int* __restrict__ turn, int ov, int window,
+                                                          float* __restrict__ kept, int* __restrict__ len, int4* __restrict__ call, int* __restrict__ turn, int ov, int window,
                                                           Stamps stamps)
 {
     constexpr int CIN = VOC_N_MEL, KS = VOC_K_PRE, TP = vc_tp<XT, CIN, VOC_C0, (KS - 1) / 2, true>();
@@ -247,10 +250,12 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, 
     auto keep = [&](int p, int c4, float4 v) __attribute__((always_inline)) {
         if (p >= k0 && p < k1) *reinterpret_cast<float4*>(kept + ((size_t)w * ov + p - (valid - ov)) * CIN + 4 * c4) = v;
     };
-    conv_tile<XT, CIN, VOC_C0, VOC_C0, KS, TP, EPI_PLAIN, false, 1>(a, valid, (size_t)w * window, p0, lds, fetch, keep, [](int, float) {});
+    conv_tile<XT, CIN, VOC_C0, VOC_C0, KS, TP, EPI_PLAIN, false, 1, RG>(a, valid, (size_t)w * window, p0, lds, fetch, keep, [](int, float) {});
     if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
+        const int slot = b.slot[w], mine = turn[slot] ^ 1;
         len[w] = valid;
-        turn[b.slot[w]] ^= 1;
+        turn[slot] = mine;
+        call[w] = make_int4(valid, b.out_off[w], slot, mine | (b.has_prev[w] ? VOC_HAS_PREV : 0) | (b.last[w] ? VOC_LAST : 0));
         stamps.begin(t0);
     }
 }
@@ -263,25 +268,26 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_first(VocBatch b, VcArgs a, 
 // (The mel tail gets its new frames here because the first layer reads the old ones.)  As a launch of its own behind the last layer this took 3.3 us
 // for one window, 4.5 us for 64.
 template <typename XT, bool SHORT>
-__global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, const float* __restrict__ alpha, const float* __restrict__ beta,
-                                                         float* __restrict__ s_tail, size_t s_tail_turn, const int* __restrict__ turn, float* __restrict__ d_audio,
+__global__ __launch_bounds__(VC_THREADS) void k_voc_last(VcArgs a, const int4* __restrict__ call, const float* __restrict__ alpha, const float* __restrict__ beta,
+                                                         float* __restrict__ s_tail, size_t s_tail_turn, float* __restrict__ d_audio,
                                                          const float* __restrict__ kept, float* __restrict__ m_tail, int ov, int window, Stamps stamps)
 {
     constexpr int CIN = voc_channels(VOC_STAGES - 1), KS = VOC_K_POST, TP = vc_tp<XT, CIN, 16, (KS - 1) / 2, SHORT>();
     __shared__ uint4 lds[vc_stride(TP + 2 * ((KS - 1) / 2)) * VcGeom<XT, CIN>::GP];
-    const int w = blockIdx.y, nf = b.n_frames[w], mine = turn[b.slot[w]];
-    const bool hp = b.has_prev[w], last = b.last[w];
-    const int valid = ((hp ? ov : 0) + nf) * VOC_HOP, p0 = blockIdx.x * TP, N = ov * VOC_HOP;
+    const int w = blockIdx.y;
+    const int4 c = call[w];
+    const bool hp = c.w & VOC_HAS_PREV, last = c.w & VOC_LAST, mine = c.w & 1;
+    const int valid = c.x * VOC_HOP, p0 = blockIdx.x * TP, N = ov * VOC_HOP;
     if (p0 >= valid) return;
     if (blockIdx.x == 0 && !last) {
         const float* src = kept + w * ov * VOC_N_MEL;
-        float* dst = m_tail + (size_t)b.slot[w] * ov * VOC_N_MEL;
+        float* dst = m_tail + (size_t)c.z * ov * VOC_N_MEL;
         for (int e = threadIdx.x; e < ov * VOC_N_MEL; e += VC_THREADS) dst[e] = src[e];
     }
-    const size_t slot = (size_t)b.slot[w] * N;
+    const size_t slot = (size_t)c.z * N;
     const float* old_tail = s_tail + (mine ? 0 : s_tail_turn) + slot;
     float* new_tail = s_tail + (mine ? s_tail_turn : 0) + slot;
-    float* out = d_audio + b.out_off[w];
+    float* out = d_audio + c.y;
     const int keep = valid - N, n_out = last ? valid : keep;
     auto emit = [&](int i, float v) __attribute__((always_inline)) {
         if (!last && i >= keep) new_tail[i - keep] = v;
@@ -291,7 +297,7 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VocBatch b, VcArgs a, c
     const size_t wbase = (size_t)w * window * VOC_HOP;
     const float *in0 = a.in0 + wbase * CIN, *in1 = a.in1 + wbase * CIN, *in2 = a.in2 + wbase * CIN;
     auto fetch = [&](int p, int c4) __attribute__((always_inline)) { return Quad3{quad_at<CIN>(in0, p, c4), quad_at<CIN>(in1, p, c4), quad_at<CIN>(in2, p, c4)}; };
-    conv_tile<XT, CIN, 16, 1, KS, TP, EPI_POST, true, 1>(a, valid, wbase, p0, lds, fetch, [](int, int, float4) {}, emit);
+    conv_tile<XT, CIN, 16, 1, KS, TP, EPI_POST, true, 1, 1>(a, valid, wbase, p0, lds, fetch, [](int, int, float4) {}, emit);
     if (threadIdx.x == 0) stamps.end();
 }
 
@@ -344,7 +350,10 @@ template <typename XT, int C, int KS, int TP, bool HALO> struct VrGeom {
     // Waves: groups of rows times groups of columns.  Every group of columns fetches the weights of its rows, 16 cycles of the
     // compute unit's L1 a KB: where a region is small they would cost more than the products (64 channels, 128 positions, four
     // groups: 352 KB a convolution of 11 taps, 5600 cycles against 3000), so there the waves share out the rows instead.
-    static constexpr int THREADS = C == 64 ? 512 : 256;
+    // In the smallest regions, which are mostly halo, a wave has all columns of its rows, so that every one is spared the columns that a
+    // convolution's successors do not read any more (TRIM; a call of one window 57.8 -> 56.7 us, fp32, bound by its products, 228 -> 192).
+    static constexpr bool TRIM = C == 64 && TP < 64 && HALO;
+    static constexpr int THREADS = C == 64 && !TRIM ? 512 : 256;
     static constexpr int RGROUPS = C == 64 ? (TP < 128 ? 4 : 2) : C == 32 && TP < 128 ? 2 : 1;
     static constexpr int CGROUPS = THREADS / 64 / RGROUPS;
     static constexpr int HALF = (KS - 1) / 2;
@@ -356,12 +365,18 @@ template <typename XT, int C, int KS, int TP, bool HALO> struct VrGeom {
     // ... of which so many come out right: TP or a little more with the longest kernel, more with the others, whose halo is shorter.  (With
     // TP of them in every block, 128 windows of 44 frames 481 us, like this 473)
     static constexpr int OUT = HALO ? W - 2 * H : TP;
+    // column tiles of convolution i's output that are read again: [first, end)
+    __device__ static constexpr int edge(int i) { return i < 0 ? 0 : edge(i - 1) + HALF * (i & 1 ? 1 : i + 1); }      // i even: dilation i + 1
+    __device__ static constexpr int first(int i) { return TRIM ? edge(i) / 16 : 0; }
+    __device__ static constexpr int end(int i) { return TRIM ? (W - edge(i) + 15) / 16 : NCOL; }
+    static_assert(!TRIM || (CGROUPS == 1 && !PAIR), "a wave's columns are the region's");
     static constexpr int RT = (PAIR ? 2 * C : C) / 16 / RGROUPS;          // row tiles per wave
     static constexpr int TAPS = PAIR ? KS + 1 : KS;
     static constexpr int NK = TAPS * C / Frag<XT>::KB;
     // (ten products a k step are 160 cycles: with two steps ahead there 128 windows 464 -> 472 us, with one where there are fewer products 32
     // windows 165.8 -> 169.2)
-    static constexpr int AHEAD = RT * NCOL >= 10 || NK == 1 ? 1 : 2;
+    static constexpr int AHEAD = TRIM ? 2 : RT * NCOL >= 10 || NK == 1 ? 1 : 2;
+    static_assert(2 * NK % AHEAD == 0, "two convolutions go round the ring in whole turns");
     // zero rows on each side: the widest tap offset
     static constexpr int PAD = PAIR ? (5 * (HALF + 1) + 1) / 2 : 5 * HALF;
     static constexpr int PLANE = (PAIR ? W / 2 : W) + 2 * PAD;            // rows of a plane
@@ -395,6 +410,10 @@ template <typename R> struct VrWeights {
         return make_uint4(v.x, v.y, v.z, v.w);
     }
 };
+template <int N> struct Int {
+    static constexpr int value = N;
+    __device__ constexpr operator int() const { return N; }
+};
 template <typename R> using VrRing = uint4[R::AHEAD][R::RT];
 template <typename R> __device__ __forceinline__ void ring_fill(VrRing<R>& ring, const VrWeights<R>& W)
 {
@@ -404,8 +423,9 @@ template <typename R> __device__ __forceinline__ void ring_fill(VrRing<R>& ring,
         for (int rt = 0; rt < R::RT; ++rt) ring[kf][rt] = W.at(0, rt, kf);
 }
 
-// acc += W * operand, or bias + W * operand (INIT).  A k step's B fragments are requested before the products of the step before.
-template <typename XT, typename R, bool INIT>
+// acc += W * operand, or bias + W * operand (INIT), for the wave's column tiles CT0 .. CT1 - 1.  A k step's B fragments are requested before the
+// products of the step before.
+template <typename XT, typename R, bool INIT, int CT0, int CT1>
 __device__ __forceinline__ void conv_regs(const VrWeights<R>& W, int conv, VrRing<R>& ring, int dil, const uint4* lds, int buf, int col0, int lane,
                                           const floatx4 (&bias)[R::RT], floatx4 (&acc)[R::RT][R::NCOL])
 {
@@ -428,7 +448,7 @@ __device__ __forceinline__ void conv_regs(const VrWeights<R>& W, int conv, VrRin
     auto request = [&](int kf) __attribute__((always_inline)) {
         const uint4* bl = lds + b_at(kf);
 #pragma unroll
-        for (int ct = 0; ct < NCOL; ++ct) bv[kf & 1][ct] = bl[ct * 16];
+        for (int ct = CT0; ct < CT1; ++ct) bv[kf & 1][ct] = bl[ct * 16];
     };
     request(0);
 #pragma unroll
@@ -444,7 +464,7 @@ __device__ __forceinline__ void conv_regs(const VrWeights<R>& W, int conv, VrRin
         if (kf + 1 < NK) request(kf + 1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ct = 0; ct < NCOL; ++ct)
+        for (int ct = CT0; ct < CT1; ++ct)
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) acc[rt][ct] = mfma_frag<XT>(af[rt], bv[kf & 1][ct], INIT && kf == 0 ? bias[rt] : acc[rt][ct]);
     }
@@ -515,8 +535,8 @@ __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t
             zero_rows(plane, 0, R::PAD + (R::PAIR ? (r0 - pl + 1) >> 1 : r0));
             zero_rows(plane, R::PAD + (R::PAIR ? (r1 - pl + 1) >> 1 : r1), R::PLANE);
         }
-    // operand of the next convolution: lrelu, operand type, positions of the window only; v in the layout of pairs d apart
-    auto put = [&](uint4* at, int buf, const floatx4 (&v)[RT][NCOL], int d) __attribute__((always_inline)) {
+    // operand of the next convolution: lrelu, operand type, positions of the window only; v in the layout of pairs d apart; column tiles as above
+    auto put = [&](uint4* at, int buf, const floatx4 (&v)[RT][NCOL], int d, auto ct0, auto ct1) __attribute__((always_inline)) {
         const int c = column();
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
@@ -528,11 +548,11 @@ __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t
             };
             if (edge) {
 #pragma unroll
-                for (int ct = 0; ct < NCOL; ++ct)
+                for (int ct = ct0; ct < ct1; ++ct)
                     if ((unsigned)(pbase + pos(c, rt, ct, d)) < (unsigned)valid) store(ct);
             } else {
 #pragma unroll
-                for (int ct = 0; ct < NCOL; ++ct) store(ct);
+                for (int ct = ct0; ct < ct1; ++ct) store(ct);
             }
         }
     };
@@ -541,32 +561,41 @@ __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t
         for (int rt = 0; rt < RT; ++rt) v[rt] = *reinterpret_cast<const floatx4*>(lds_bias + conv * C + chan(rt));
     };
     uint4* const lds1 = lds + (R::TWO ? R::OPERAND_VECS : 0);
-    put(lds, 0, x, 1);
+    put(lds, 0, x, 1, Int<0>{}, Int<NCOL>{});
     lds_barrier();
-#pragma unroll 1
-    for (int pair = 0; pair < VOC_PAIRS; ++pair) {
+    auto do_pair = [&](int pair, auto trim) __attribute__((always_inline)) {       // trim: the pair's number where its columns depend on it
+        constexpr int P = decltype(trim)::value, A0 = R::first(2 * P), A1 = R::end(2 * P), B0 = R::first(2 * P + 1), B1 = R::end(2 * P + 1);
         const int d = 2 * pair + 1;
         floatx4 t[RT][NCOL], b[RT];
         biases(2 * pair, b);
-        conv_regs<XT, R, true>(weights, 2 * pair, ring, d, lds, 0, col0, lane, b, t);
+        conv_regs<XT, R, true, A0, A1>(weights, 2 * pair, ring, d, lds, 0, col0, lane, b, t);
         if constexpr (!R::TWO) lds_barrier();     // every wave has read the old operand
         __builtin_amdgcn_s_setprio(2);            // vector work goes ahead of the products of the wave it shares a SIMD with
-        put(lds1, 1, t, d);
+        put(lds1, 1, t, d, Int<A0>{}, Int<A1>{});
         __builtin_amdgcn_s_setprio(0);
         biases(2 * pair + 1, b);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int ct = 0; ct < NCOL; ++ct) x[rt][ct] += b[rt];
+            for (int ct = B0; ct < B1; ++ct) x[rt][ct] += b[rt];
         lds_barrier();
-        conv_regs<XT, R, false>(weights, 2 * pair + 1, ring, 1, lds1, 1, col0, lane, b, x);
+        conv_regs<XT, R, false, B0, B1>(weights, 2 * pair + 1, ring, 1, lds1, 1, col0, lane, b, x);
         if (pair + 1 < VOC_PAIRS) {
             if constexpr (!R::TWO) lds_barrier();
             __builtin_amdgcn_s_setprio(2);
-            put(lds, 0, x, 1);
+            put(lds, 0, x, 1, Int<B0>{}, Int<B1>{});
             __builtin_amdgcn_s_setprio(0);
             lds_barrier();
         }
+    };
+    if constexpr (R::TRIM) {
+        static_assert(VOC_PAIRS == 3, "the pairs one by one");
+        do_pair(0, Int<0>{});
+        do_pair(1, Int<1>{});
+        do_pair(2, Int<2>{});
+    } else {
+#pragma unroll 1
+        for (int pair = 0; pair < VOC_PAIRS; ++pair) do_pair(pair, Int<0>{});
     }
     const int o0 = R::H, o1 = min(R::H + R::OUT, valid - pbase);  // positions of the region that are this tile's output
     const int c = column();
@@ -595,6 +624,9 @@ __global__ __launch_bounds__((VrGeom<XT, C, 3, TP, HALO>::THREADS), C == 8 ? (si
 // per frame, where a window is a few dozen positions long, and for every layer of a batch so small that the large tiles
 // would leave most of the chip idle (an output's sum does not depend on the tile it falls in).
 constexpr int VC_SHORT_BELOW = 512;              // workgroups of the large tiling below which the short one is used
+// Row tiles per workgroup: four, or one where that is at most a workgroup for every compute unit: all its weights are on their way then before the
+// positions are staged (calls of 1 / 4 / 8 windows 62.3 / 81.6 / 99.7 -> 57.7 / 77.7 / 95.8 us; fp32 242.7 / 347 / 418 -> 228.7 / 336 / 405).
+constexpr int VC_FEW = 256;
 template <typename XT, int CIN, int ROWS, int COUT, int KS, int EPI, bool PRE_ACT, bool SRC3, int U, bool SHORT>
 void conv_launch(const VcArgs& a, const int* len, int rate, int window, int n_windows, hipStream_t s)
 {
@@ -607,7 +639,12 @@ void conv_launch(const VcArgs& a, const int* len, int rate, int window, int n_wi
             return;
         }
     }
-    hipLaunchKernelGGL((k_vconv<XT, CIN, ROWS, COUT, KS, EPI, PRE_ACT, SRC3, U, SHORT>), grid, dim3(VC_THREADS), 0, s, a, len, rate, window);
+    if constexpr (SHORT && RG > 1)
+        if ((long)grid.x * grid.y * RT <= VC_FEW) {
+            hipLaunchKernelGGL((k_vconv<XT, CIN, ROWS, COUT, KS, EPI, PRE_ACT, SRC3, U, SHORT, 1>), dim3(grid.x, grid.y, RT), dim3(VC_THREADS), 0, s, a, len, rate, window);
+            return;
+        }
+    hipLaunchKernelGGL((k_vconv<XT, CIN, ROWS, COUT, KS, EPI, PRE_ACT, SRC3, U, SHORT, RG>), grid, dim3(VC_THREADS), 0, s, a, len, rate, window);
 }
 
 template <typename XT, int C, int TP, bool HALO>
@@ -698,8 +735,12 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     pre.W = reinterpret_cast<const uint4*>(d.pre_w);
     pre.bias = d.pre_b;
     constexpr int PRE_TP = vc_tp<XT, VOC_N_MEL, VOC_C0, (VOC_K_PRE - 1) / 2, true>();
-    hipLaunchKernelGGL((k_voc_first<XT>), dim3((d.window + PRE_TP - 1) / PRE_TP, b.n, VOC_C0 / 64), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.kept,
-                       d.len, d.turn, d.overlap, d.window, d.stamps);
+    const int pre_tiles = (d.window + PRE_TP - 1) / PRE_TP;
+    auto first = [&](auto kern, int row_groups) {
+        hipLaunchKernelGGL(kern, dim3(pre_tiles, b.n, row_groups), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.kept, d.len, d.call, d.turn, d.overlap, d.window, d.stamps);
+    };
+    if ((long)pre_tiles * b.n * (VOC_C0 / 16) <= VC_FEW) first(k_voc_first<XT, 1>, VOC_C0 / 16);
+    else first(k_voc_first<XT, 4>, VOC_C0 / 64);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = stage_launch<XT, 0>(d, b.n, s);
     if (e == hipSuccess) e = stage_launch<XT, 1>(d, b.n, s);
@@ -713,7 +754,7 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     post.W = reinterpret_cast<const uint4*>(d.post_w);
     post.bias = d.post_b;
     auto last = [&](auto kern, int tp) {
-        hipLaunchKernelGGL(kern, dim3((d.window * VOC_HOP + tp - 1) / tp, b.n), dim3(VC_THREADS), 0, s, b, post, d.alpha, d.beta, d.s_tail, d.s_tail_turn, d.turn, d_audio,
+        hipLaunchKernelGGL(kern, dim3((d.window * VOC_HOP + tp - 1) / tp, b.n), dim3(VC_THREADS), 0, s, post, d.call, d.alpha, d.beta, d.s_tail, d.s_tail_turn, d_audio,
                            d.kept, d.m_tail, d.overlap, d.window, d.stamps);
     };
     constexpr int CL = voc_channels(VOC_STAGES - 1), LONG_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2>(), SHORT_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2, true>();

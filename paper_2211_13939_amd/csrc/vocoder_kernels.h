@@ -25,6 +25,8 @@ constexpr int voc_channels(int s) { return VOC_C0 >> (s + 1); }              // 
 constexpr bool voc_paired(int channels) { return channels <= 16; }
 constexpr int voc_cum_rate(int s) { return s == 0 ? 8 : (s == 1 ? 64 : (s == 2 ? 128 : 256)); }   // positions per frame after stage s
 
+constexpr int VOC_HAS_PREV = 2, VOC_LAST = 4;
+
 struct VocoderPtrs {
     // weights in MFMA A-fragment order (weight dtype), k = tap * C_in + channel; biases fp32
     const void* pre_w;  const float* pre_b;
@@ -39,6 +41,7 @@ struct VocoderPtrs {
     float* kept;        // [max_batch][overlap][n_mel]      last frames of this call's chunks, from its first launch to its last
     int* turn;          // [max_requests]  which of the two the slot's latest call writes (its calls' first launch changes it)
     int* len;           // [max_batch] frames in window i of this call (overlap frames in front included)
+    int4* call;         // [max_batch] of window i: its frames, its first sample in the response, its state slot, the bits below and (bit 0) whose turn it is
     float* x0;          // [max_batch * window][c0]         conv_pre output
     float* y;           // upsampled activations of the current stage, [positions][channels]
     float* r[VOC_BLOCKS];   // output of every residual block of the current stage
