@@ -204,6 +204,14 @@ int tts_pool_get_stop_logits(tts_pool *pool, int64_t id, int first, int count, f
  * immediately", Sec. 2.2.2); also allowed for an unfinished request.  Frees its slot. */
 int tts_pool_retire(tts_pool *pool, int64_t id);
 
+/*
+ * The same for `n` (1 .. 256) different requests with one launch: their windows lie back to back in d_dst, in the order of `ids` (room for
+ * n * (context + chunk_frames) * n_mel floats; a request without a chunk that is ready has none there), and the three arrays of n say of
+ * each what tts_pool_chunk_window says.  On an error nothing was handed out.
+ */
+int tts_pool_chunk_windows(tts_pool *pool, int n, const int64_t *ids, int context, float *d_dst, int *out_context,
+                           int *out_frames, int *out_finished);
+
 /* Copy one carried state of request `id` to HOST `dst` (fp32, `cap` elements of
  * room); *out_n receives the element count.  Waits for the stream. */
 int tts_pool_get_state(tts_pool *pool, int64_t id, int which, float *dst, int cap, int *out_n);

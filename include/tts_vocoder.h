@@ -102,7 +102,7 @@ int tts_vocoder_create(const tts_vocoder_config *cfg, const tts_vocoder_weights 
  *                tail(S_pre) of its request between calls (Eq. 4 is applied by this call).
  *   flags        HOST [n]: TTS_VOCODER_FIRST and / or TTS_VOCODER_LAST.  A chunk without FIRST needs a slot whose
  *                previous chunk went through this object and was not LAST.
- *   d_audio      DEVICE, fp32: the responses back to back; response i has out_samples[i] samples (see the table
+ *   d_audio      DEVICE (or pinned host memory that the device can write), fp32: the responses back to back; response i has out_samples[i] samples (see the table
  *                at the top; at most 256 * (overlap + n_frames[i])).  The caller provides room for the sum.  It may
  *                overlap d_mel: every frame is read before the first sample is written.
  *   out_samples  HOST [n], written before the call returns.

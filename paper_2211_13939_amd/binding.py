@@ -38,7 +38,7 @@ EXPORTS = (
     "tts_last_error",
     "tts_book_create", "tts_book_add", "tts_book_step", "tts_book_drain", "tts_book_retire",
     "tts_book_slot", "tts_book_compact", "tts_book_destroy",
-    "tts_pool_chunk_window",
+    "tts_pool_chunk_window", "tts_pool_chunk_windows",
     "tts_postnet_workspace_bytes", "tts_postnet_create", "tts_postnet_run", "tts_postnet_run_static", "tts_postnet_set_wait_polls",
     "tts_postnet_one_launch_calls", "tts_postnet_elapsed_ms",
     "tts_postnet_destroy",
@@ -154,6 +154,7 @@ def lib() -> C.CDLL:
     L.tts_book_destroy.restype = None
     L.tts_book_destroy.argtypes = [vp]
     L.tts_pool_chunk_window.argtypes = [vp, C.c_int64, C.c_int, vp, _ip, _ip, _ip]
+    L.tts_pool_chunk_windows.argtypes = [vp, C.c_int, C.POINTER(C.c_int64), C.c_int, vp, _ip, _ip, _ip]
     L.tts_postnet_workspace_bytes.restype = C.c_size_t
     L.tts_postnet_workspace_bytes.argtypes = [C.POINTER(TtsPostnetConfig)]
     L.tts_postnet_create.argtypes = [C.POINTER(TtsPostnetConfig), C.POINTER(TtsPostnetWeights), vp, C.c_size_t, vp,
@@ -394,6 +395,16 @@ class Pool:
                                            C.byref(n), C.byref(fin)))
         return c.value, n.value, bool(fin.value)
 
+    def chunk_windows(self, rids, context: int, d_dst) -> list:
+        """chunk_window for several requests with one launch, their windows back to back in d_dst
+        ([>= len(rids) * (context + chunk), n_mel]): [(context frames, chunk frames, finished)] of each."""
+        n = len(rids)
+        assert d_dst.is_cuda and d_dst.dtype == self._torch.float32 and d_dst.is_contiguous()
+        assert d_dst.numel() >= n * (context + self.chunk) * self.n_mel
+        ids, out = (C.c_int64 * n)(*rids), [(C.c_int * n)() for _ in range(3)]
+        _check(lib().tts_pool_chunk_windows(self._h, n, ids, int(context), C.c_void_p(d_dst.data_ptr()), *out))
+        return [(c, k, bool(f)) for c, k, f in zip(*out)]
+
     def close(self) -> None:
         if getattr(self, "_h", None):
             lib().tts_pool_destroy(self._h)
@@ -598,7 +609,7 @@ class Vocoder:
         fl = np.ascontiguousarray(flags, np.int32)
         n = int(nf.shape[0])
         assert sl.shape[0] == n and fl.shape[0] == n
-        assert d_mel.is_cuda and d_audio.is_cuda and d_mel.is_contiguous() and d_audio.is_contiguous()
+        assert d_mel.is_cuda and (d_audio.is_cuda or d_audio.is_pinned()) and d_mel.is_contiguous() and d_audio.is_contiguous()
         assert d_mel.dtype == self._torch.float32 and d_audio.dtype == self._torch.float32
         assert d_mel.numel() >= int(nf.sum()) * self.cfg.n_mel
         assert d_audio.numel() >= int((nf + self.cfg.overlap).sum()) * VOCODER_HOP

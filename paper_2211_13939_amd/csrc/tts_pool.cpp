@@ -1071,6 +1071,54 @@ extern "C" int tts_pool_chunk_window(tts_pool* p, int64_t id, int context, float
     return TTS_OK;
 }
 
+// One launch for all of them: a copy each took 4.8 us of the stream's time, so much as the module behind it for a chunk.
+extern "C" int tts_pool_chunk_windows(tts_pool* p, int n, const int64_t* ids, int context, float* d_dst, int* out_context,
+                                      int* out_frames, int* out_finished)
+{
+    if (!p || !ids || !d_dst || !out_context || !out_frames || !out_finished) return fail(TTS_E_INVAL, "null argument");
+    if (n < 1 || n > MAX_POOL) return fail(TTS_E_INVAL, "n = %d requests, 1 .. %d per call", n, MAX_POOL);
+    if (context < 0) return fail(TTS_E_INVAL, "context = %d", context);
+    int slots[MAX_POOL];
+    for (int i = 0; i < n; ++i) {
+        slots[i] = p->book->find(ids[i]);
+        if (slots[i] < 0) return fail(TTS_E_NOTFOUND, "no request with id %lld", (long long)ids[i]);
+        for (int k = 0; k < i; ++k)
+            if (slots[k] == slots[i]) return fail(TTS_E_INVAL, "request %lld appears twice", (long long)ids[i]);
+    }
+    int rc;
+    for (int i = 0; i < n; ++i)
+        if ((rc = refresh_slot(p, slots[i]))) return rc;
+    if (*p->h_fault) {                       // (as for one window)
+        HIP_TRY(wait_for_stream(p));
+        if ((rc = absorb_failures(p))) return rc;
+    }
+    StageArgs sa;
+    int m = 0, most = 0, rows = 0, counts[MAX_POOL];
+    for (int i = 0; i < n; ++i) {
+        int first;
+        p->book->drain_plan(slots[i], &first, &counts[i], &out_finished[i]);
+        out_context[i] = counts[i] > 0 ? std::min(first, context) : 0;
+        out_frames[i] = counts[i];
+        if (counts[i] == 0) continue;
+        sa.row[m] = slots[i] * p->cfg.max_steps + first - out_context[i];
+        sa.frames[m] = out_context[i] + counts[i];
+        sa.to[m] = rows;
+        rows += sa.frames[m];
+        most = std::max(most, sa.frames[m]);
+        ++m;
+    }
+    if (m > 1 && (uintptr_t)d_dst % 16 == 0) {
+        HIP_TRY(launch_stage_chunks(p->d, sa, m, most, d_dst, p->stream));
+    } else {
+        for (int i = 0; i < m; ++i)
+            HIP_TRY(hipMemcpyAsync(d_dst + (size_t)sa.to[i] * N_MEL, p->d.mel_ring + (size_t)sa.row[i] * N_MEL, (size_t)sa.frames[i] * N_MEL * 4,
+                                   hipMemcpyDeviceToDevice, p->stream));
+    }
+    for (int i = 0; i < n; ++i)
+        if (counts[i] > 0) p->book->drain_commit(slots[i], counts[i]);
+    return TTS_OK;
+}
+
 extern "C" int tts_pool_get_stop_logits(tts_pool* p, int64_t id, int first, int count, float* dst)
 {
     if (!p || !dst) return fail(TTS_E_INVAL, "null argument");

@@ -360,7 +360,6 @@ class GpuPostnetBackend(GpuBackend):
             assert vocoder.cfg.max_requests >= cap_v and vocoder.cfg.max_batch >= cap_v and vocoder.cfg.max_chunk >= chunk
             self._free_slots = list(range(cap_v))[::-1]
             hop = 256
-            self._d_audio = torch.empty(cap_v * (chunk + vocoder.cfg.overlap) * hop, dtype=torch.float32, device=pool.device)
             self._h_audio = torch.empty(cap_v * (chunk + vocoder.cfg.overlap) * hop, dtype=torch.float32).pin_memory()
         cap = int(pool.cfg.max_pool)
         self._d_in = torch.empty((cap * (chunk + context), pool.n_mel), dtype=torch.float32, device=pool.device)
@@ -372,11 +371,20 @@ class GpuPostnetBackend(GpuBackend):
                          d_out=self._d_out if first else torch.empty_like(self._d_out),
                          h_out=self._h_out if first else torch.empty_like(self._h_out).pin_memory(), ev=None)
                 if vocoder is not None:
-                    d["d_audio"] = self._d_audio if first else torch.empty_like(self._d_audio)
                     d["h_audio"] = self._h_audio if first else torch.empty_like(self._h_audio).pin_memory()
                 return d
             self._sets = [one_set(i == 0) for i in range(self.N_SETS)]
             self._next_set = 0
+
+    def _windows(self, d_in, ended):
+        """The chunks that are ready, with their context, out of the pool's ring into d_in with one launch: (id, what the loop knows of it,
+        context frames, frames, finished) of every request that may have one."""
+        ready = [(rid, s) for rid, s in self.live.items()
+                 if (s["done"] - s["drained"] >= self.chunk or s["done"] == s["total"]) and rid not in ended]
+        del ready[d_in.shape[0] // (self.chunk + self.context):]
+        if not ready:
+            return []
+        return [(rid, s, *w) for (rid, s), w in zip(ready, self.pool.chunk_windows([rid for rid, _ in ready], self.context, d_in))]
 
     # ---- the overlapped form
     def _harvest(self):
@@ -413,21 +421,16 @@ class GpuPostnetBackend(GpuBackend):
         self.pool.step_n(k)
         for s in self.live.values():
             s["done"] = min(s["total"], s["done"] + k)
-        fin_ids, span = [], self.chunk + self.context
+        fin_ids = []
         while True:                         # a request that ends may hand out a full chunk and then its rest
             st = self._sets[self._next_set]
             if st["ev"] is not None:
                 st["ev"].synchronize()      # the round that used this set last (N_SETS rounds ago) is through
-            lens, keeps, row, out_rows, items, voc, handed = [], [], 0, 0, [], [], []
-            for rid, s in self.live.items():
-                ready = s["done"] - s["drained"] >= self.chunk or s["done"] == s["total"]
-                if not ready or rid in fin_ids or row + span > st["d_in"].shape[0]:
-                    continue
-                c, n, fin = self.pool.chunk_window(rid, self.context, st["d_in"][row:])
+            lens, keeps, out_rows, items, voc, handed = [], [], 0, [], [], []
+            for rid, s, c, n, fin in self._windows(st["d_in"], fin_ids):
                 if n:
                     lens.append(c + n)
                     keeps.append(c)
-                    row += c + n
                     items.append((s["index"], bool(fin)))
                     handed.append((s["index"], s["drained"], out_rows, n))
                     if self.vocoder is not None:
@@ -451,9 +454,7 @@ class GpuPostnetBackend(GpuBackend):
             with torch.cuda.stream(side):
                 if self.vocoder is not None:
                     rnd["n_out"] = self.vocoder.run_device(st["d_out"], [v[0] for v in voc], [v[1] for v in voc],
-                                                           [v[2] for v in voc], st["d_audio"])
-                    total = sum(rnd["n_out"])
-                    st["h_audio"][:total].copy_(st["d_audio"][:total], non_blocking=True)
+                                                           [v[2] for v in voc], st["h_audio"])
                 if self.vocoder is None or self.on_chunk is not None:
                     st["h_out"][:out_rows].copy_(st["d_out"][:out_rows], non_blocking=True)
                 st["ev"] = torch.cuda.Event()
@@ -478,18 +479,12 @@ class GpuPostnetBackend(GpuBackend):
         for s in self.live.values():
             s["done"] = min(s["total"], s["done"] + k)
         chunk_ids, fin_ids = [], []
-        span = self.chunk + self.context
         while True:                         # a request that ends may hand out a full chunk and then its rest
-            lens, keeps, row, out_rows, handed, voc = [], [], 0, 0, [], []
-            for rid, s in self.live.items():
-                ready = s["done"] - s["drained"] >= self.chunk or s["done"] == s["total"]
-                if not ready or rid in fin_ids or row + span > self._d_in.shape[0]:
-                    continue
-                c, n, fin = self.pool.chunk_window(rid, self.context, self._d_in[row:])
+            lens, keeps, out_rows, handed, voc = [], [], 0, [], []
+            for rid, s, c, n, fin in self._windows(self._d_in, fin_ids):
                 if n:
                     lens.append(c + n)
                     keeps.append(c)
-                    row += c + n
                     handed.append((s["index"], s["drained"], out_rows, n))
                     if self.vocoder is not None:
                         if "vslot" not in s:
@@ -510,11 +505,9 @@ class GpuPostnetBackend(GpuBackend):
                 break
             self.postnet.run_device(self._d_in, lens, keeps, self._d_out)
             if self.vocoder is not None:
+                # (straight to the host: as a copy behind it the samples took 17 us of a round of one request)
                 n_out = self.vocoder.run_device(self._d_out, [v[0] for v in voc], [v[1] for v in voc], [v[2] for v in voc],
-                                                self._d_audio)
-                total = sum(n_out)
-                with self.pool._torch.cuda.stream(self.pool.stream):
-                    self._h_audio[:total].copy_(self._d_audio[:total], non_blocking=True)
+                                                self._h_audio)
                 if self.on_audio is not None:
                     self.pool.sync()
                     host, at = self._h_audio.numpy(), 0
