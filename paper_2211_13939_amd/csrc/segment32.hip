@@ -1,19 +1,23 @@
 // A segment of decoder steps as ONE launch for pools with fp32 weights and memory whose running requests lie in the first 16 slots: the
 // counterpart of segment.hip, which says how such a launch works (words, their three buffers, the two sets, the bounded waits) and why it pays.
 //
-// As launches of its own (four, kernels.hip) a step of 16 requests takes 38.9 us, like this 17.0 (1 request: 37.3, 14.9): 15 of them one leader's prenet and the gate pre-sums behind it,
-// 10 the attention, 14 the two LSTMs, each with its start-up, a cold trip and its share of 73 MB of weights.  Twice the bytes of the two-byte
-// form and an eighth of its matrix rate (256 FLOP a cycle and compute unit; the products of a step are 10 us of 96 units) ask for another
-// split of the work:
+// As launches of its own (four, kernels.hip) a step takes 38.9 us at 16 requests of 60 positions and 37.3 at one: 15 of them one leader's prenet and
+// the gate pre-sums behind it, 10 the attention, 14 the two LSTMs, each with its start-up, a cold trip and its share of 73 MB of weights.  Like this
+// 16.9 and 14.9; 16 requests of 250 positions 39.9 -> 19.5.  Twice the bytes of the two-byte form and an eighth of its matrix rate (256 FLOP a cycle
+// and compute unit; the products of a step are 10 us of 96 units) ask for another split of the work:
 //   32 x ATT    32 hidden units of the attention LSTM each: gates from p (K = 256) and the pre-sums (words), cell, h, rank-32 share of the query
 //  128 x GATES  8 hidden units of the decoder LSTM and of the attention LSTM's pre-sums each.  In a step: the decoder's sums over h_att (while the
 //               attention works), over a (on the chain), cell, h_dec out; then, off the chain, the attention LSTM's pre-sums of the next step over
 //               [a; h_att], and the decoder's over h_dec.  The decoder's weights live in registers and LDS (328 KB), the pre-sums' (196 KB)
 //               stream from L2: 16 such workgroups an XCD, 3 MB of its 4.
-//   S x LSA     per request; S = 4 up to 8 slots, 2 above
+//   S x LSA     per request; S = 4 up to 8 slots, 2 above; 448 and 224 positions of its memory stay in registers and LDS (with 256 and 128, in
+//               registers alone, 16 requests of 165 / 250 positions 19.2 / 20.7 us a step, like this 18.8 / 19.5)
 //    6 x ROWS   one row tile of the projection each
 //    4 x LEAD   frame and the prenet's first layer each, a quarter of its second: a chain of 64 matrix instructions a row tile, four row tiles
 //               side by side on the SIMDs (one workgroup for all of it: 3.4 us); the first one keeps the books
+// The chain of a step at 16 requests of 60 positions, us from p's arrival: query stored 2.5 (1.7 of them products: 64 matrix instructions in a
+// chain a row tile, two a SIMD), taken 3.6, energies stored 5.8, taken 6.3, context stored 7.0, taken 8.8, h_dec stored 10.3, taken 11.9, frame's sums stored
+// 13.2, taken 14.2, prenet stored 16.7, taken 17.6.  (Pauses between the polls change nothing.)
 // Every sum is formed in the order of the kernels in kernels.hip: the same bits whichever form a step takes.
 #include "kernels.h"
 #include "lsa_tile.h"
@@ -75,8 +79,11 @@ constexpr int MEL_LD = MEL_ROWS + 4, HID_LD = PRENET + 4;     // an odd number o
 constexpr int S_LEAD = 16 * (MEL_LD + HID_LD) * 4;
 constexpr int U_PAD = MAX_ENC_LEN + 48;
 constexpr int S_LSA = (NW * ENC + 16 * ATT + 2 * U_PAD + MAX_ENC_LEN + 2 * ATT + 2 * NW + 32 * 64 + 8 * 64 * 4) * 4;
-constexpr int S_MAX = S_GATES;
-static_assert(S_ATT <= S_MAX && S_ROWS <= S_MAX && S_LEAD <= S_MAX && S_LSA <= S_MAX && S_MAX + 128 <= 160 * 1024, "the roles' LDS");
+// Beside what it needs LDS holds the rows of so many positions of a request's memory that the workgroup's columns of them are 96 KB.
+constexpr int S_ROWS_KEPT = 96 * 1024, S_MAX = S_LSA + S_ROWS_KEPT;
+constexpr int lsa_lds_passes(int split) { return S_ROWS_KEPT / (32 * ENC * 4 / split); }
+static_assert(lsa_lds_passes(2) == 3 && lsa_lds_passes(4) == 6, "224 and 448 positions with those in registers");
+static_assert(S_ATT <= S_MAX && S_GATES <= S_MAX && S_ROWS <= S_MAX && S_LEAD <= S_MAX && S_LSA % 16 == 0 && S_MAX + 128 <= 160 * 1024, "the roles' LDS");
 
 // ---------------------------------------------------------------- the attention LSTM and the query
 __device__ __forceinline__ void att(const DevPtrs& d, const Words& x, const Pool& pl, int rg, char* lds, Phases ps)
@@ -457,8 +464,8 @@ __device__ __forceinline__ void lsa(const DevPtrs& d, const Words& x, const Pool
     u32x4_t pm0[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) pm0[i] = *reinterpret_cast<const u32x4_t*>(PMs + (size_t)min((sp + S * wave) * 16 + jl, L - 1) * ATT + 4 * i);
-    // and so do rows of the memory (this workgroup's columns): NP passes of 32 positions
-    constexpr int NP = S == 4 ? 8 : 4;
+    // and so do rows of the memory (this workgroup's columns), NP passes of 32 positions; NL more lie in LDS
+    constexpr int NP = S == 4 ? 8 : 4, NL = lsa_lds_passes(S);
     const int xw = wave * 4 + lane / LPR * NA;                             // this lane's first position class
     const float* Fslot = reinterpret_cast<const float*>(d.Fmem) + (size_t)slot * ML * ENC;
     const __amdgpu_buffer_rsrc_t f_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Fslot), 0, L * ENC * 4, BUFFER_RSRC_RAW);
@@ -470,6 +477,11 @@ __device__ __forceinline__ void lsa(const DevPtrs& d, const Words& x, const Pool
         for (int n = 0; n < NA; ++n)
 #pragma unroll
             for (int v = 0; v < 2; ++v) mem[pp][n][v] = __builtin_amdgcn_raw_buffer_load_b128(f_rsrc, (pp * 32 + xw + n) * ENC * 4 + f_col + 16 * v, 0, 0);
+    u32x4_t* const s_mem = reinterpret_cast<u32x4_t*>(s_w + 8 * 64) + tid;       // [pass][class][half a row][thread]: the thread's own
+    for (int pp = 0; pp < NL && (NP + pp) * 32 < L; ++pp)
+#pragma unroll
+        for (int i = 0; i < 2 * NA; ++i)
+            s_mem[(pp * 2 * NA + i) * NT] = __builtin_amdgcn_raw_buffer_load_b128(f_rsrc, ((NP + pp) * 32 + xw + (i >> 1)) * ENC * 4 + f_col + 16 * (i & 1), 0, 0);
     for (int i = tid; i < ntile * 16 + 32; i += NT) {
         const bool in = i >= LOC_PAD && i < L + LOC_PAD;
         const int jc = min(max(i - LOC_PAD, 0), L - 1);
@@ -658,8 +670,15 @@ __device__ __forceinline__ void lsa(const DevPtrs& d, const Words& x, const Pool
 #pragma unroll
             for (int n = 0; n < NA; ++n) add(n, pp * 32 + xw + n, mem[pp][n]);
         }
+#pragma unroll 1
+        for (int pp = NP; pp < NP + NL && pp * 32 < L; ++pp)
+#pragma unroll
+            for (int n = 0; n < NA; ++n) {
+                const u32x4_t r[2] = {s_mem[((pp - NP) * 2 * NA + 2 * n) * NT], s_mem[((pp - NP) * 2 * NA + 2 * n + 1) * NT]};
+                add(n, pp * 32 + xw + n, r);
+            }
         constexpr int MORE = 4 / NA;
-        for (int x0 = 32 * NP; x0 < L; x0 += 32 * MORE) {                  // longer texts: from memory
+        for (int x0 = 32 * (NP + NL); x0 < L; x0 += 32 * MORE) {                  // longer texts: from memory
             u32x4_t more[MORE][NA][2];
 #pragma unroll
             for (int pp = 0; pp < MORE; ++pp)

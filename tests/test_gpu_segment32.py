@@ -38,11 +38,12 @@ def _both(weights, lengths, frames, calls, max_pool=16, max_enc_len=1024, spoil=
     ([1], [2], [2]),                                                       # the smallest
     ([165], [41], [3, 1, 37]),                                             # odd calls, a single step among them
     ([17, 256, 257], [5, 80, 44], [64, 16]),                               # four workgroups a request keep 256 positions in registers
-    ([513, 512], [9, 12], [12]),                                           # ... and the processed memory of 512
+    ([448, 449], [12, 9], [12]),                                           # ... and up to 448 in LDS
+    ([513, 512], [9, 12], [12]),                                           # ... and the processed memory of 512 in registers
     ([1024, 16, 1023, 15], [33, 2, 64, 65], [1, 32, 31, 1]),               # the longest texts; ends inside a call and at its end
     ([31 + 40 * i for i in range(8)], [40 - i for i in range(8)], [40]),   # eight slots, and nine: two workgroups a request
     ([33 + 20 * i for i in range(9)], [12 + i for i in range(9)], [7, 13]),
-    ([128, 129, 256, 257, 600] + [20 + 9 * i for i in range(11)], [10 + 3 * i for i in range(16)], [20, 35]),   # ... which keep 128 positions
+    ([128, 129, 256, 257, 600, 224, 225] + [20 + 9 * i for i in range(9)], [10 + 3 * i for i in range(16)], [20, 35]),   # ... which keep 128 and 224
 ], ids=lambda v: None)
 def test_segment_equals_steps(lengths, frames, calls, weights_fp32):
     say(f"case: fp32 segments of {calls} steps, texts of {lengths}, frames {frames}")
