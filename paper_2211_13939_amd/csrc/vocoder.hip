@@ -623,10 +623,12 @@ __global__ __launch_bounds__((VrGeom<XT, C, 3, TP, HALO>::THREADS), C == 8 ? (si
 // grid = (tiles of a window, windows, row groups).  SHORT: tiles of 64 positions - for the layer that runs at one position
 // per frame, where a window is a few dozen positions long, and for every layer of a batch so small that the large tiles
 // would leave most of the chip idle (an output's sum does not depend on the tile it falls in).
-constexpr int VC_SHORT_BELOW = 512;              // workgroups of the large tiling below which the short one is used
-// Row tiles per workgroup: four, or one where that is at most a workgroup for every compute unit: all its weights are on their way then before the
-// positions are staged (calls of 1 / 4 / 8 windows 62.3 / 81.6 / 99.7 -> 57.7 / 77.7 / 95.8 us; fp32 242.7 / 347 / 418 -> 228.7 / 336 / 405).
-constexpr int VC_FEW = 256;
+// (Calls of 48 / 64 / 128 windows with the line at 512 workgroups 226 / 270.3 / 480.9 us, at 1024 220 / 266.4 / 479.7, at 2048 220 / 266 / 475.)
+constexpr int VC_SHORT_BELOW = 2048;             // workgroups of the large tiling below which the short one is used
+// Row tiles per workgroup: four, or one where that is at most two workgroups for every compute unit: all its weights are on their way then before the
+// positions are staged (calls of 1 / 4 / 8 windows 62.3 / 81.6 / 99.7 -> 57.7 / 77.7 / 95.8 us; fp32 242.7 / 347 / 418 -> 228.7 / 336 / 405; with the
+// line at one workgroup 4 / 16 / 40 windows take 1 / 1 / 2 us longer).
+constexpr int VC_FEW = 512;
 template <typename XT, int CIN, int ROWS, int COUT, int KS, int EPI, bool PRE_ACT, bool SRC3, int U, bool SHORT>
 void conv_launch(const VcArgs& a, const int* len, int rate, int window, int n_windows, hipStream_t s)
 {
@@ -686,9 +688,16 @@ template <int C, int LEVEL> constexpr int vr_tp() { return LEVEL == 3 ? 8 : ((C 
 // A call of 48 to 128 short windows would be better off in tiles, by 3 to 11 us (two-byte) or 40 to 120 us (fp32).
 constexpr int VR_WHOLE = 384;
 constexpr int VR_WHOLE_FROM = 48;                // windows from which it is used
-constexpr int VR_SMALL_BELOW = 1024;             // workgroups of the large tiling below which the half tiles are used
-constexpr int VR_TINY_BELOW = 128;               // ... and the quarter tiles
-constexpr int VR_LEAST_UPTO = 320;               // most workgroups of the smallest regions
+// Workgroups of the large tiling below which the half tiles are used, and the quarter tiles (fp32 with 64 channels, bound by products, sooner), and the
+// most workgroups of the smallest regions.  Us a call, windows of 44 frames:
+//   half tiles      below 1024: 24 / 28 windows 149.2 / 159.2, fp32 733.6 / 806.5;   below 700: 146.0 / 157.1, 706.8 / 762.2;   below 850: 149.4 / 157.3
+//   quarter tiles   below 128, fp32: 24 / 28 windows 706.8 / 762.2, 32 820.7;   below 256 (64 channels): 647.0 / 704.1, 816.3; two-byte, below 192: 24 windows
+//                   144.7 of 146.0, 28 161.9 of 157.1
+//   smallest        up to 320: 3 / 4 windows 72.9 / 76.8, fp32 319 / 336, 5 / 6 / 8 343 / 355 / 406;   up to 800: 70.6 / 73.6, 226 / 242, 314 / 344;   up to 1100:
+//                   8 windows 94.1 -> 100.6, fp32 406 -> 397;   up to 1600, fp32: 10 / 12 windows 425 / 470 -> 461 / 543
+constexpr int VR_SMALL_BELOW = 700;
+template <typename XT, int C> constexpr int vr_tiny_below() { return sizeof(XT) == 4 && C == 64 ? 256 : 128; }
+template <typename XT> constexpr int vr_least_upto() { return sizeof(XT) == 4 ? 1100 : 800; }
 
 template <typename XT, int C>
 hipError_t blocks_launch(const VrArgs3& a, const int* len, int rate, int window, int n_windows, hipStream_t s)
@@ -696,12 +705,12 @@ hipError_t blocks_launch(const VrArgs3& a, const int* len, int rate, int window,
     if constexpr (C == 64)
         if (window * rate <= VR_WHOLE && n_windows >= VR_WHOLE_FROM) return blocks_launch_tp<XT, C, VR_WHOLE, false>(a, len, rate, window, n_windows, s);
     if constexpr (C == 64)
-        if ((long)((window * rate + vr_tp<C, 3>() - 1) / vr_tp<C, 3>()) * n_windows * VOC_BLOCKS <= VR_LEAST_UPTO)
+        if ((long)((window * rate + vr_tp<C, 3>() - 1) / vr_tp<C, 3>()) * n_windows * VOC_BLOCKS <= vr_least_upto<XT>())
             return blocks_launch_tp<XT, C, vr_tp<C, 3>(), true>(a, len, rate, window, n_windows, s);
     const long wgs = (long)((window * rate + vr_tp<C, 0>() - 1) / vr_tp<C, 0>()) * n_windows * VOC_BLOCKS;
-    return wgs < VR_TINY_BELOW    ? blocks_launch_tp<XT, C, vr_tp<C, 2>(), true>(a, len, rate, window, n_windows, s)
-           : wgs < VR_SMALL_BELOW ? blocks_launch_tp<XT, C, vr_tp<C, 1>(), true>(a, len, rate, window, n_windows, s)
-                                  : blocks_launch_tp<XT, C, vr_tp<C, 0>(), true>(a, len, rate, window, n_windows, s);
+    return wgs < vr_tiny_below<XT, C>() ? blocks_launch_tp<XT, C, vr_tp<C, 2>(), true>(a, len, rate, window, n_windows, s)
+           : wgs < VR_SMALL_BELOW       ? blocks_launch_tp<XT, C, vr_tp<C, 1>(), true>(a, len, rate, window, n_windows, s)
+                                        : blocks_launch_tp<XT, C, vr_tp<C, 0>(), true>(a, len, rate, window, n_windows, s);
 }
 
 template <typename XT, int S>
