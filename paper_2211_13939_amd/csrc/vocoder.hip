@@ -12,6 +12,8 @@
 // bytes of channels.  The weights are stored in A-fragment order and stream from L2.
 // Windows of different requests lie at a fixed stride; positions outside a window's own length read as zero, which
 // is the zero padding of every layer.
+#include <algorithm>
+
 #include "vocoder_kernels.h"
 
 #include "mfma.h"
@@ -620,6 +622,11 @@ __global__ __launch_bounds__((VrGeom<XT, C, 3, TP, HALO>::THREADS), C == 8 ? (si
     else resblock_tile<XT, C, 11, TP, HALO>(a3.b[2], valid, wbase, tile, lds_dyn);
 }
 
+// What a call asks of every launch: its windows and the frames of the longest one.
+struct Load {
+    int n, longest;
+};
+
 // grid = (tiles of a window, windows, row groups).  SHORT: tiles of 64 positions - for the layer that runs at one position
 // per frame, where a window is a few dozen positions long, and for every layer of a batch so small that the large tiles
 // would leave most of the chip idle (an output's sum does not depend on the tile it falls in).
@@ -630,14 +637,14 @@ constexpr int VC_SHORT_BELOW = 2048;             // workgroups of the large tili
 // line at one workgroup 4 / 16 / 40 windows take 1 / 1 / 2 us longer).
 constexpr int VC_FEW = 512;
 template <typename XT, int CIN, int ROWS, int COUT, int KS, int EPI, bool PRE_ACT, bool SRC3, int U, bool SHORT>
-void conv_launch(const VcArgs& a, const int* len, int rate, int window, int n_windows, hipStream_t s)
+void conv_launch(const VcArgs& a, const int* len, int rate, int window, Load c, hipStream_t s)
 {
     constexpr int TP = vc_tp<XT, CIN, ROWS, (KS - 1) / 2, SHORT>();
     constexpr int RT = ROWS / 16, RG = RT < 4 ? RT : 4;
-    const dim3 grid((window * rate + TP - 1) / TP, n_windows, RT / RG);
+    const dim3 grid((c.longest * rate + TP - 1) / TP, c.n, RT / RG);
     if constexpr (!SHORT) {
         if ((long)grid.x * grid.y * grid.z < VC_SHORT_BELOW) {
-            conv_launch<XT, CIN, ROWS, COUT, KS, EPI, PRE_ACT, SRC3, U, true>(a, len, rate, window, n_windows, s);
+            conv_launch<XT, CIN, ROWS, COUT, KS, EPI, PRE_ACT, SRC3, U, true>(a, len, rate, window, c, s);
             return;
         }
     }
@@ -650,7 +657,7 @@ void conv_launch(const VcArgs& a, const int* len, int rate, int window, int n_wi
 }
 
 template <typename XT, int C, int TP, bool HALO>
-hipError_t blocks_launch_tp(const VrArgs3& a, const int* len, int rate, int window, int n_windows, hipStream_t s)
+hipError_t blocks_launch_tp(const VrArgs3& a, const int* len, int rate, int window, Load c, hipStream_t s)
 {
     constexpr int L3 = VrGeom<XT, C, 3, TP, HALO>::BYTES, L7 = VrGeom<XT, C, 7, TP, HALO>::BYTES, L11 = VrGeom<XT, C, 11, TP, HALO>::BYTES;
     constexpr int LDS = L3 > L7 ? (L3 > L11 ? L3 : L11) : (L7 > L11 ? L7 : L11);      // the three kernels share a launch
@@ -662,7 +669,7 @@ hipError_t blocks_launch_tp(const VrArgs3& a, const int* len, int rate, int wind
         attr_set = true;
     }
     constexpr int OUT = VrGeom<XT, C, voc_block_k(VOC_BLOCKS - 1), TP, HALO>::OUT;       // (the others have as many tiles or fewer)
-    const dim3 grid(HALO ? (window * rate + OUT - 1) / OUT : 1, n_windows, VOC_BLOCKS);
+    const dim3 grid(HALO ? (c.longest * rate + OUT - 1) / OUT : 1, c.n, VOC_BLOCKS);
     hipLaunchKernelGGL(kern, grid, dim3(VrGeom<XT, C, 3, TP, HALO>::THREADS), LDS, s, a, len, rate, window);
     return hipSuccess;
 }
@@ -672,49 +679,40 @@ hipError_t blocks_launch_tp(const VrArgs3& a, const int* len, int rate, int wind
 // column tiles.  With 64 channels, where a window is a few hundred positions and a region's products are the longest, a
 // request alone takes the smallest region there is.
 template <int C, int LEVEL> constexpr int vr_tp() { return LEVEL == 3 ? 8 : ((C >= 32 ? 256 : 512) >> LEVEL) + 8; }
-// With 64 channels (8 positions a frame) the halo of a tile of 128 doubles its work.  A window of up to 384 positions fits a
-// workgroup's registers and LDS and needs none: a CU per window and block, which pays from a few dozen windows on
-// (64 windows: 58 us a launch in tiles of 128, 43 whole).  The rule looks at the configured window; a whole call, us, in tiles with a
-// halo / whole, for windows of that many frames in a configuration of 48:
-//               8            16           24           32           44
-//   two-byte  48 windows  137 /  144   149 /  160   185 /  193   193 /  198   251 /  242
-//             64          154 /  161   160 /  169   230 /  223   240 /  232   308 /  287
-//            128          240 /  243   257 /  257   408 /  376   427 /  396   569 /  509
-//            256          498 /  423   519 /  451   762 /  695   820 /  758  1126 / 1040
-//   fp32      48          620 /  739   618 /  739   904 / 1025   912 / 1032  1233 / 1284
-//             64          735 /  857   730 /  850  1159 / 1211  1165 / 1216  1556 / 1523
-//            128         1219 / 1263  1221 / 1261  2199 / 2005  2213 / 2015  2975 / 2632
-//            256         3196 / 2480  3068 / 2400  4621 / 3934  4615 / 3951  5890 / 5215
-// A call of 48 to 128 short windows would be better off in tiles, by 3 to 11 us (two-byte) or 40 to 120 us (fp32).
+// With 64 channels (8 positions a frame) the halo of a tile of 128 doubles its work.  A window of up to 384 positions fits a workgroup's
+// registers and LDS whole and needs none: a CU per window and block, which pays where there are enough of them, unless half a tile holds the window.
+//
+// All lines below look at the call's longest window, whatever the configuration allows: `large` counts positions in large tiles, the others their own
+// workgroups.  (By the configured window, 48 frames: calls of 4 / 16 / 64 / 128 windows of 16 frames 68.0 / 84.9 / 157.8 / 219 us, like this 57.0 / 77.6 /
+// 133 / 188; fp32 320 / 358 / 777 / 1125 -> 195 / 294 / 588 / 988; of 32 frames 73.0 / 106.8 / 206 / 343 -> 66.0 / 102.9 / 197 / 325.)
+// Us a call of n windows of 44 frames unless said otherwise, on one side of each line and on the other:
+//   whole       tiles / whole: 40, 48, 64, 96 windows 195 / 198, 222 / 220, 273 / 265, 383 / 361, of 32 frames 48, 64, 96: 163 / 171, 199 / 198, 277 / 260; fp32 48, 64:
+//               1125 / 1186, 1461 / 1424, of 32 frames 64, 96: 1037 / 1043, 1398 / 1355; of 16 frames half a tile holds them: 96 windows 159 / 168, fp32 740 / 856
+//   smallest    next larger / smallest: 3, 4 windows 73 / 71, 77 / 74, 5, 8: 84 / 84, 94 / 101 (beyond the line); fp32 4, 8: 336 / 242, 406 / 397, 10, 12: 425 / 461, 470 / 543
+//   quarter     half / quarter: 24, 28 windows 146 / 145, 157 / 162; fp32 24, 32, 40: 707 / 647, 821 / 816, 956 / 1007
+//   half        large / half: 24, 28 windows 146.0 / 149.2, 157.1 / 159.2; fp32 707 / 734, 762 / 806
 constexpr int VR_WHOLE = 384;
-constexpr int VR_WHOLE_FROM = 48;                // windows from which it is used
-// Workgroups of the large tiling below which the half tiles are used, and the quarter tiles (fp32 with 64 channels, bound by products, sooner), and the
-// most workgroups of the smallest regions.  Us a call, windows of 44 frames:
-//   half tiles      below 1024: 24 / 28 windows 149.2 / 159.2, fp32 733.6 / 806.5;   below 700: 146.0 / 157.1, 706.8 / 762.2;   below 850: 149.4 / 157.3
-//   quarter tiles   below 128, fp32: 24 / 28 windows 706.8 / 762.2, 32 820.7;   below 256 (64 channels): 647.0 / 704.1, 816.3; two-byte, below 192: 24 windows
-//                   144.7 of 146.0, 28 161.9 of 157.1
-//   smallest        up to 320: 3 / 4 windows 72.9 / 76.8, fp32 319 / 336, 5 / 6 / 8 343 / 355 / 406;   up to 800: 70.6 / 73.6, 226 / 242, 314 / 344;   up to 1100:
-//                   8 windows 94.1 -> 100.6, fp32 406 -> 397;   up to 1600, fp32: 10 / 12 windows 425 / 470 -> 461 / 543
+template <typename XT> constexpr int vr_whole_from() { return sizeof(XT) == 4 ? 224 : 192; }
 constexpr int VR_SMALL_BELOW = 700;
-template <typename XT, int C> constexpr int vr_tiny_below() { return sizeof(XT) == 4 && C == 64 ? 256 : 128; }
+template <typename XT, int C> constexpr int vr_tiny_upto() { return C != 64 ? 470 : sizeof(XT) == 4 ? 576 : 360; }
 template <typename XT> constexpr int vr_least_upto() { return sizeof(XT) == 4 ? 1100 : 800; }
 
 template <typename XT, int C>
-hipError_t blocks_launch(const VrArgs3& a, const int* len, int rate, int window, int n_windows, hipStream_t s)
+hipError_t blocks_launch(const VrArgs3& a, const int* len, int rate, int window, Load c, hipStream_t s)
 {
-    if constexpr (C == 64)
-        if (window * rate <= VR_WHOLE && n_windows >= VR_WHOLE_FROM) return blocks_launch_tp<XT, C, VR_WHOLE, false>(a, len, rate, window, n_windows, s);
-    if constexpr (C == 64)
-        if ((long)((window * rate + vr_tp<C, 3>() - 1) / vr_tp<C, 3>()) * n_windows * VOC_BLOCKS <= vr_least_upto<XT>())
-            return blocks_launch_tp<XT, C, vr_tp<C, 3>(), true>(a, len, rate, window, n_windows, s);
-    const long wgs = (long)((window * rate + vr_tp<C, 0>() - 1) / vr_tp<C, 0>()) * n_windows * VOC_BLOCKS;
-    return wgs < vr_tiny_below<XT, C>() ? blocks_launch_tp<XT, C, vr_tp<C, 2>(), true>(a, len, rate, window, n_windows, s)
-           : wgs < VR_SMALL_BELOW       ? blocks_launch_tp<XT, C, vr_tp<C, 1>(), true>(a, len, rate, window, n_windows, s)
-                                        : blocks_launch_tp<XT, C, vr_tp<C, 0>(), true>(a, len, rate, window, n_windows, s);
+    const long positions = (long)c.longest * rate, regions = (long)c.n * VOC_BLOCKS, large = positions * regions / vr_tp<C, 0>();
+    auto tiles = [&](int tp) { return (positions + tp - 1) / tp * regions; };
+    if constexpr (C == 64) {
+        if (positions <= VR_WHOLE && positions > vr_tp<C, 1>() && large >= vr_whole_from<XT>()) return blocks_launch_tp<XT, C, VR_WHOLE, false>(a, len, rate, window, c, s);
+        if (tiles(vr_tp<C, 3>()) <= vr_least_upto<XT>()) return blocks_launch_tp<XT, C, vr_tp<C, 3>(), true>(a, len, rate, window, c, s);
+    }
+    if (tiles(vr_tp<C, 2>()) <= vr_tiny_upto<XT, C>()) return blocks_launch_tp<XT, C, vr_tp<C, 2>(), true>(a, len, rate, window, c, s);
+    return large < VR_SMALL_BELOW ? blocks_launch_tp<XT, C, vr_tp<C, 1>(), true>(a, len, rate, window, c, s)
+                                  : blocks_launch_tp<XT, C, vr_tp<C, 0>(), true>(a, len, rate, window, c, s);
 }
 
 template <typename XT, int S>
-hipError_t stage_launch(const VocoderPtrs& d, int n_windows, hipStream_t s)
+hipError_t stage_launch(const VocoderPtrs& d, Load c, hipStream_t s)
 {
     constexpr int CIN = VOC_C0 >> S, C = CIN / 2, U = voc_rate(S);
     constexpr int rate_in = S == 0 ? 1 : voc_cum_rate(S - 1), rate = voc_cum_rate(S);
@@ -725,7 +723,7 @@ hipError_t stage_launch(const VocoderPtrs& d, int n_windows, hipStream_t s)
     up.out = d.y;
     up.W = reinterpret_cast<const uint4*>(d.up_w[S]);
     up.bias = d.up_b[S];
-    conv_launch<XT, CIN, U * C, C, 3, EPI_UP, true, (S > 0), U, (S == 0)>(up, d.len, rate_in, d.window, n_windows, s);
+    conv_launch<XT, CIN, U * C, C, 3, EPI_UP, true, (S > 0), U, (S == 0)>(up, d.len, rate_in, d.window, c, s);
     VrArgs3 rb{};
     for (int b = 0; b < VOC_BLOCKS; ++b) {
         rb.b[b].in = d.y;
@@ -733,28 +731,30 @@ hipError_t stage_launch(const VocoderPtrs& d, int n_windows, hipStream_t s)
         rb.b[b].W = reinterpret_cast<const uint4*>(d.res_w[S][b]);
         rb.b[b].bias = d.res_b[S][b];
     }
-    return blocks_launch<XT, C>(rb, d.len, rate, d.window, n_windows, s);
+    return blocks_launch<XT, C>(rb, d.len, rate, d.window, c, s);
 }
 
 template <typename XT>
 hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d_mel, float* d_audio, hipStream_t s)
 {
+    Load c{b.n, 0};
+    for (int w = 0; w < b.n; ++w) c.longest = std::max(c.longest, (b.has_prev[w] ? d.overlap : 0) + b.n_frames[w]);
     VcArgs pre{};
     pre.out = d.x0;
     pre.W = reinterpret_cast<const uint4*>(d.pre_w);
     pre.bias = d.pre_b;
     constexpr int PRE_TP = vc_tp<XT, VOC_N_MEL, VOC_C0, (VOC_K_PRE - 1) / 2, true>();
-    const int pre_tiles = (d.window + PRE_TP - 1) / PRE_TP;
+    const int pre_tiles = (c.longest + PRE_TP - 1) / PRE_TP;
     auto first = [&](auto kern, int row_groups) {
         hipLaunchKernelGGL(kern, dim3(pre_tiles, b.n, row_groups), dim3(VC_THREADS), 0, s, b, pre, d_mel, d.m_tail, d.kept, d.len, d.call, d.turn, d.overlap, d.window, d.stamps);
     };
     if ((long)pre_tiles * b.n * (VOC_C0 / 16) <= VC_FEW) first(k_voc_first<XT, 1>, VOC_C0 / 16);
     else first(k_voc_first<XT, 4>, VOC_C0 / 64);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = stage_launch<XT, 0>(d, b.n, s);
-    if (e == hipSuccess) e = stage_launch<XT, 1>(d, b.n, s);
-    if (e == hipSuccess) e = stage_launch<XT, 2>(d, b.n, s);
-    if (e == hipSuccess) e = stage_launch<XT, 3>(d, b.n, s);
+    if (e == hipSuccess) e = stage_launch<XT, 0>(d, c, s);
+    if (e == hipSuccess) e = stage_launch<XT, 1>(d, c, s);
+    if (e == hipSuccess) e = stage_launch<XT, 2>(d, c, s);
+    if (e == hipSuccess) e = stage_launch<XT, 3>(d, c, s);
     if (e != hipSuccess) return e;
     VcArgs post{};
     post.in0 = d.r[0];
@@ -763,11 +763,11 @@ hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d
     post.W = reinterpret_cast<const uint4*>(d.post_w);
     post.bias = d.post_b;
     auto last = [&](auto kern, int tp) {
-        hipLaunchKernelGGL(kern, dim3((d.window * VOC_HOP + tp - 1) / tp, b.n), dim3(VC_THREADS), 0, s, post, d.call, d.alpha, d.beta, d.s_tail, d.s_tail_turn, d_audio,
+        hipLaunchKernelGGL(kern, dim3((c.longest * VOC_HOP + tp - 1) / tp, b.n), dim3(VC_THREADS), 0, s, post, d.call, d.alpha, d.beta, d.s_tail, d.s_tail_turn, d_audio,
                            d.kept, d.m_tail, d.overlap, d.window, d.stamps);
     };
     constexpr int CL = voc_channels(VOC_STAGES - 1), LONG_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2>(), SHORT_TP = vc_tp<XT, CL, 16, (VOC_K_POST - 1) / 2, true>();
-    if ((long)((d.window * VOC_HOP + LONG_TP - 1) / LONG_TP) * b.n < VC_SHORT_BELOW) last(k_voc_last<XT, true>, SHORT_TP);
+    if ((long)((c.longest * VOC_HOP + LONG_TP - 1) / LONG_TP) * b.n < VC_SHORT_BELOW) last(k_voc_last<XT, true>, SHORT_TP);
     else last(k_voc_last<XT, false>, LONG_TP);
     return hipGetLastError();
 }
