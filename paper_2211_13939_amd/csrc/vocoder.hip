@@ -322,8 +322,8 @@ __global__ __launch_bounds__(VC_THREADS) void k_voc_last(VcArgs a, const int4* _
 // The operand buffer holds even and odd positions in planes of their own, so the columns of a tap are still consecutive
 // rows: 2 P + m d lies in plane m & 1 at row P + (m d - (m & 1)) / 2.
 //
-// Measured (two-byte mode, windows of 48 frames, one launch): 1 window, 64 / 32 / 16 / 8 channels 34.0 / 13.9 / 9.5 / 9.0 us -> 16.4 / 11.0 /
-// 8.4 / 5.7; 64 windows 93.4 / 107 / 70.4 / 119 -> 43.0 / 92 / 67 / 41.  With 32 channels the matrix pipes are busy 36 % of the time and
+// Measured (two-byte mode, windows of 48 frames, one launch): 1 window, 64 / 32 / 16 / 8 channels 34.0 / 13.9 / 9.5 / 9.0 us -> 14.9 / 10.9 /
+// 7.8 / 5.4; 64 windows 93.4 / 107 / 70.4 / 119 -> 43.6 / 92 / 59 / 40.  With 32 channels the matrix pipes are busy 36 % of the time and
 // the vector units 30 %: a product takes 17 cycles, a vector instruction beside it two to four more, whichever wave of the SIMD it
 // is of, and a value costs two and a half of them (leaky ReLU, conversion, store).  One workgroup for a stage's three blocks, with
 // their mean stored for the next layer, took as long (352 against 353 us a round of 64); two tiles in a workgroup of eight waves
