@@ -107,6 +107,17 @@ struct LiveArgs {
     uint32_t bits[MAX_POOL / 32];
 };
 
+// How many steps the request in each slot still has to take when a segment's launch begins (0: no running request): the host's count
+// (kernel argument).
+struct SegmentLeft {
+    int steps[SEG_TILES * SEG_SLOTS];
+};
+
+// What every workgroup of that launch goes by, read when it starts, which may be when others are steps ahead: nothing in it is written by the
+// launch but `failed`, and that only for a request that is lost anyway.  (Not from n_steps - t and `done`, which the launch's own leader keeps:
+// a workgroup that the leader's first step does not wait for could find that step counted.)
+__host__ __device__ inline int segment_left(const DevPtrs& d, const SegmentLeft& left, int slot) { return d.failed[slot] ? 0 : left.steps[slot]; }
+
 // one launch's worth of chunks on their way to the host (kernel argument): chunk i = frames[i] rows from row row[i] of the mel
 // ring, to row to[i] of the pinned staging buffer
 struct StageArgs {

@@ -22,6 +22,7 @@ struct StepLaunch {
                     // of the replay before)
     int seg_set;    // which of the two sets of d.seg_x it uses: in turn, launch by launch
     int seg_empty;  // tiles of the other set it has to empty: those that the launch before used
+    SegmentLeft seg_left; // by slot
     int pre_gates;  // 2: the projection's launch also forms the next step's gate pre-sums (d.pre_att / d.pre_dec; fp32: n_tiles <= PRESUM_SMALL_TILES),
                     // 1: the attention LSTM's only (pools of more than PRESUM_SMALL_TILES tiles: d.pre_dec is null);
                     // either way the attention LSTM hands the query to the attention kernel as rank-32 partial products (d.qpart)
@@ -59,8 +60,8 @@ constexpr size_t segment_bytes(int max_pool, int max_enc_len) { return 2 * segme
 // first kernel and ev[i + 1] after kernel i (per-kernel device times).
 // (Pools with d.hdec_x launch three kernels - the decoder LSTM is part of the last one - and record ev[3] right after ev[2].)
 constexpr int N_STEP_KERNELS = 4;
-hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, hipStream_t s);   // (launch_step's seg_steps)
-hipError_t launch_segment32(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, hipStream_t s); // (fp32)
+hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, const SegmentLeft& left, hipStream_t s);   // (launch_step's seg_steps)
+hipError_t launch_segment32(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, const SegmentLeft& left, hipStream_t s); // (fp32)
 hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int cur, hipStream_t s, hipEvent_t* ev = nullptr);
 
 hipError_t launch_set_live(const DevPtrs& d, const LiveArgs& args, hipStream_t s);

@@ -2575,8 +2575,8 @@ hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int cur, hipStre
 {
     if (cfg.n_blocks < 1 || cfg.n_tiles < 1) return hipSuccess;
     if (cfg.seg_steps > 0)
-        return cfg.wdtype == 0 ? launch_segment32(d, cur, cfg.n_blocks, cfg.seg_steps, cfg.seg_set, cfg.seg_empty, s)
-                               : launch_segment(d, cur, cfg.n_blocks, cfg.seg_steps, cfg.seg_set, cfg.seg_empty, s);
+        return cfg.wdtype == 0 ? launch_segment32(d, cur, cfg.n_blocks, cfg.seg_steps, cfg.seg_set, cfg.seg_empty, cfg.seg_left, s)
+                               : launch_segment(d, cur, cfg.n_blocks, cfg.seg_steps, cfg.seg_set, cfg.seg_empty, cfg.seg_left, s);
     if (cfg.pre_gates) {
         if (cfg.n_tiles > MAX_TILES || !d.pre_att || !d.qpart || (cfg.pre_gates == 2) != (d.pre_dec != nullptr)) return hipErrorInvalidValue;
         if (cfg.pre_gates == 1) {

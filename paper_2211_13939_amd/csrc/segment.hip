@@ -468,7 +468,7 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, const
     constexpr int VEC = MEL_ROWS / 4;
     const int m_slot = min(tid / VEC, SEG_SLOTS - 1), m_row = tid % VEC * 4;
     const int m_rem = tid < SEG_SLOTS * VEC && m_row < N_PROJ ? pl.rem[slot0 + m_slot] : 0;
-    const int m_t0 = d.t[slot0 + m_slot], m_off = m_row / 16 * (SEG_SLOTS * 64) + m_slot * 64 + m_row % 16 * 4;     // [row tile][slot][16 rows]
+    const int m_t0 = d.n_steps[slot0 + m_slot] - m_rem, m_off = m_row / 16 * (SEG_SLOTS * 64) + m_slot * 64 + m_row % 16 * 4;     // [row tile][slot][16 rows]
     // the launches after this one read the half of this pair that belongs to their parity: it must not fall behind
     const int end_all = cur ^ (n_steps & 1);
     if (tile == 0 && tid == 0 && end_all != cur) d.wg_seq[end_all] = d.wg_seq[cur];
@@ -535,6 +535,7 @@ __device__ __forceinline__ void seg_lead(const DevPtrs& d, const Words& x, const
                 *reinterpret_cast<u32x4_t*>(d.m_last + (slot0 + m_slot) * N_MEL + m_row) = w;
             } else {
                 d.stop_ring[at] = __uint_as_float(w.x);
+                // (no workgroup of this launch reads these two)
                 d.t[slot0 + m_slot] = m_t0 + s + 1;
                 if (s + 1 == m_rem) d.done[slot0 + m_slot] = 1;
             }
@@ -829,7 +830,7 @@ __device__ __forceinline__ void seg_lsa(const DevPtrs& d, const Words& x, const 
 // four XCDs free, 32 requests would take 13.4 us instead of 13.8, 48 of them 16.3 instead of 17.7.
 constexpr int SEG_XCD_WGS = 24;                             // of ATT and DEC on an XCD; LSA, at most 16, and ROWS and LEAD fill the others as far
 template <bool MULTI, int S>
-__global__ __launch_bounds__(NT) void k_segment(DevPtrs d, int cur, int n_slots, int n_steps, char* words, char* words_next, int tile_bytes, int empty_bytes)
+__global__ __launch_bounds__(NT) void k_segment(DevPtrs d, int cur, int n_slots, int n_steps, char* words, char* words_next, int tile_bytes, int empty_bytes, SegmentLeft left)
 {
     __shared__ __attribute__((aligned(16))) char lds[S_MAX];
     __shared__ int s_failed, s_rem[SEG_TILES * 16];
@@ -837,7 +838,7 @@ __global__ __launch_bounds__(NT) void k_segment(DevPtrs d, int cur, int n_slots,
     if (threadIdx.x == 0) s_failed = 0x7fffffff;
     if (threadIdx.x < SEG_TILES * 16) {
         const int sl = threadIdx.x;
-        s_rem[sl] = sl < n_slots && d.live[sl] && !d.done[sl] ? d.n_steps[sl] - d.t[sl] : 0;
+        s_rem[sl] = sl < n_slots ? segment_left(d, left, sl) : 0;
     }
     for (int at = (blockIdx.x * NT + threadIdx.x) * 16; at < empty_bytes; at += gridDim.x * NT * 16)
         *reinterpret_cast<u32x4_t*>(words_next + at) = u32x4_t{EMPTY, EMPTY, EMPTY, EMPTY};
@@ -863,7 +864,7 @@ __global__ __launch_bounds__(NT) void k_segment(DevPtrs d, int cur, int n_slots,
 
 }  // namespace
 
-hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, hipStream_t s)
+hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, const SegmentLeft& left, hipStream_t s)
 {
     const int n_tiles = (n_slots + 15) / 16;
     if (!d.seg_x || n_slots < 1 || n_slots > d.seg_slots || n_steps < 1 || (set & ~1) || empty_tiles < 0 || empty_tiles * SEG_SLOTS > d.seg_slots || d.stop_threshold >= 0.f)
@@ -872,7 +873,7 @@ hipError_t launch_segment(const DevPtrs& d, int cur, int n_slots, int n_steps, i
     char* words = static_cast<char*>(d.seg_x);
     static_assert(4 * SEG_XCD_WGS == 32 + 64 && SEG_TILES <= 4, "ATT and DEC; a projection per XCD");
     static_assert(16 * 4 >= 4 * SEG_SLOTS && 16 * 4 >= 2 * 2 * SEG_SLOTS && 16 * 4 >= SEG_TILES * SEG_SLOTS, "LSA: four, two or one per slot");
-#define SEG_ARGS dim3(8 * SEG_XCD_WGS), dim3(NT), 0, s, d, cur, n_slots, n_steps, words + set * set_bytes, words + (set ^ 1) * set_bytes, (int)tile_bytes, (int)(empty_tiles * tile_bytes)
+#define SEG_ARGS dim3(8 * SEG_XCD_WGS), dim3(NT), 0, s, d, cur, n_slots, n_steps, words + set * set_bytes, words + (set ^ 1) * set_bytes, (int)tile_bytes, (int)(empty_tiles * tile_bytes), left
     if (n_tiles == 1) hipLaunchKernelGGL((k_segment<false, 4>), SEG_ARGS);
     else if (n_tiles == 2) hipLaunchKernelGGL((k_segment<true, 2>), SEG_ARGS);
     else hipLaunchKernelGGL((k_segment<true, 1>), SEG_ARGS);

@@ -374,7 +374,7 @@ __device__ __forceinline__ void lead(const DevPtrs& d, const Words& x, const Poo
     constexpr int VEC = MEL_ROWS / 4;
     const int m_slot = min(tid / VEC, SEG_SLOTS - 1), m_row = tid % VEC * 4;
     const int m_rem = tid < SEG_SLOTS * VEC && m_row < N_PROJ ? pl.rem[m_slot] : 0;
-    const int m_t0 = d.t[m_slot], m_off = m_row / 16 * (SEG_SLOTS * 64) + m_slot * 64 + m_row % 16 * 4;     // [row tile][slot][16 rows]
+    const int m_t0 = d.n_steps[m_slot] - m_rem, m_off = m_row / 16 * (SEG_SLOTS * 64) + m_slot * 64 + m_row % 16 * 4;     // [row tile][slot][16 rows]
     int b = 0, b_next = 1;
     for (int s = 0; s < n_steps; ++s) {
         const bool on = s < rem, m_on = s < m_rem;
@@ -424,6 +424,7 @@ __device__ __forceinline__ void lead(const DevPtrs& d, const Words& x, const Poo
                 *reinterpret_cast<u32x4_t*>(d.m_last + m_slot * N_MEL + m_row) = w;
             } else {
                 d.stop_ring[at] = __uint_as_float(w.x);
+                // (no workgroup of this launch reads these two: another LEAD may start after several steps)
                 d.t[m_slot] = m_t0 + s + 1;
                 if (s + 1 == m_rem) d.done[m_slot] = 1;
             }
@@ -741,14 +742,14 @@ __device__ __forceinline__ void lsa(const DevPtrs& d, const Words& x, const Pool
 // ATT.  Five CUs or more of every XCD stay free for work on other streams.
 constexpr int WGS = 27;                                     // on an XCD
 template <int S>
-__global__ __launch_bounds__(NT) void k_segment32(DevPtrs d, int cur, int n_slots, int n_steps, char* words, char* words_next, int bytes, int empty_bytes)
+__global__ __launch_bounds__(NT) void k_segment32(DevPtrs d, int cur, int n_slots, int n_steps, char* words, char* words_next, int bytes, int empty_bytes, SegmentLeft left)
 {
     __shared__ __attribute__((aligned(16))) char lds[S_MAX];
     __shared__ int s_failed, s_rem[SEG_SLOTS];
     if (threadIdx.x == 0) s_failed = 0x7fffffff;
     if (threadIdx.x < SEG_SLOTS) {
         const int sl = threadIdx.x;
-        s_rem[sl] = sl < n_slots && d.live[sl] && !d.done[sl] ? d.n_steps[sl] - d.t[sl] : 0;
+        s_rem[sl] = sl < n_slots ? segment_left(d, left, sl) : 0;
     }
     for (int at = (blockIdx.x * NT + threadIdx.x) * 16; at < empty_bytes; at += gridDim.x * NT * 16)
         *reinterpret_cast<u32x4_t*>(words_next + at) = u32x4_t{EMPTY, EMPTY, EMPTY, EMPTY};
@@ -773,7 +774,7 @@ __global__ __launch_bounds__(NT) void k_segment32(DevPtrs d, int cur, int n_slot
 
 }  // namespace
 
-hipError_t launch_segment32(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, hipStream_t s)
+hipError_t launch_segment32(const DevPtrs& d, int cur, int n_slots, int n_steps, int set, int empty_tiles, const SegmentLeft& left, hipStream_t s)
 {
     if (!d.seg_x || n_slots < 1 || n_slots > SEG_SLOTS || n_steps < 1 || (set & ~1) || (empty_tiles & ~1) || d.stop_threshold >= 0.f) return hipErrorInvalidValue;
     const size_t bytes = segment32_bytes(d.max_enc_len);
@@ -781,7 +782,7 @@ hipError_t launch_segment32(const DevPtrs& d, int cur, int n_slots, int n_steps,
     static_assert(HID / 8 == GATES && GATES / 8 + 8 + 3 == WGS && 4 * 8 >= 2 * SEG_SLOTS, "eight units a GATES; ATT, LSA and the projection beside them");
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(8 * WGS), dim3(NT), 0, s, d, cur, n_slots, n_steps, words + set * bytes, words + (set ^ 1) * bytes, (int)bytes,
-                           (int)(empty_tiles * bytes));
+                           (int)(empty_tiles * bytes), left);
     };
     if (n_slots <= 8) go(k_segment32<4>);
     else go(k_segment32<2>);

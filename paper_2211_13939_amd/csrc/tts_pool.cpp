@@ -782,6 +782,8 @@ static int launch_segment_steps(tts_pool* p, int g)
     sl.seg_steps = g;
     sl.seg_set = p->seg_set;
     sl.seg_empty = p->seg_used;
+    std::fill(std::begin(sl.seg_left.steps), std::end(sl.seg_left.steps), 0);
+    for (int slot : p->book->active()) sl.seg_left.steps[slot] = p->book->slot(slot).n_steps - p->book->slot(slot).t;
     HIP_TRY(launch_step(p->d, sl, p->parity, p->stream));
     p->seg_set ^= 1;
     p->seg_used = sl.n_tiles;

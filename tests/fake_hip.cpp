@@ -4,6 +4,8 @@
 // A fill of device memory at creation counts as under way until the host has waited (fake_filling).
 // What is ordered behind what is followed through streams, events and the host's waits: a segment of steps that is not ordered against another
 // stream's steps, or the other way round, counts (fake_unordered).
+// A segment's workgroups may start late: what they go by is looked at before the segment and again behind each of its steps, and must be the same,
+// and right, for every request that was not lost on the way (fake_stale).
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
@@ -32,7 +34,7 @@ struct Launched { hipStream_t stream; int at; bool segment; };
 std::mutex order;
 std::map<hipStream_t, Clock> streams;
 std::vector<Launched> launched;
-int unordered = 0, segments = 0;
+int unordered = 0, segments = 0, stale = 0;
 bool filling = false;
 bool busy = false;                              // what hipStreamQuery says
 hipStream_t capturing = nullptr;
@@ -88,7 +90,7 @@ void fake_reset()
     pending.clear();
     streams.clear();
     launched.clear();
-    violations = unordered = segments = 0;
+    violations = unordered = segments = stale = 0;
     busy = filling = false;
     capturing = nullptr;
 }
@@ -97,6 +99,7 @@ void fake_busy(int on) { busy = on; }
 void fake_capture(void* stream) { capturing = (hipStream_t)stream; }
 int fake_unordered() { return unordered; }
 int fake_segments() { return segments; }
+int fake_stale() { return stale; }
 int fake_calls(const char* what) { return calls[what]; }
 int fake_violations() { return violations; }
 void fake_freeze(int slot, int at_frame) { freeze_slot = slot; freeze_at = at_frame; }
@@ -210,7 +213,13 @@ hipError_t launch_vocoder(const VocoderPtrs&, int, const VocBatch&, const float*
 hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int, hipStream_t stream, hipEvent_t*)
 {
     ordered(stream, cfg.seg_steps > 0);
-    for (int k = 0; k < std::max(cfg.seg_steps, 1); ++k)
+    std::vector<int> left(cfg.seg_steps > 0 ? cfg.n_blocks : 0);
+    for (int s = 0; s < (int)left.size(); ++s) left[s] = d.live[s] && !d.done[s] ? d.n_steps[s] - d.t[s] : 0;
+    auto look = [&] {
+        for (int s = 0; s < (int)left.size(); ++s) stale += !d.failed[s] && segment_left(d, cfg.seg_left, s) != left[s];
+    };
+    look();
+    for (int k = 0; k < std::max(cfg.seg_steps, 1); ++k) {
         for (int s = 0; s < cfg.n_blocks; ++s) {
             if (!d.live[s] || d.done[s]) continue;
             if (s == freeze_slot && d.t[s] >= freeze_at) {
@@ -221,6 +230,8 @@ hipError_t launch_step(const DevPtrs& d, const StepLaunch& cfg, int, hipStream_t
             std::fill_n(d.mel_ring + ((size_t)s * d.max_steps + d.t[s]) * N_MEL, N_MEL, 1000.f * d.n_steps[s] + d.t[s]);
             if (++d.t[s] >= d.n_steps[s]) d.done[s] = 1;
         }
+        look();
+    }
     return hipSuccess;
 }
 hipError_t launch_set_live(const DevPtrs& d, const LiveArgs& a, hipStream_t)
@@ -246,7 +257,16 @@ hipError_t launch_stage_chunks(const DevPtrs& d, const StageArgs& sa, int n, int
         memcpy(dst + (size_t)sa.to[i] * N_MEL, d.mel_ring + (size_t)sa.row[i] * N_MEL, (size_t)sa.frames[i] * N_MEL * 4);
     return hipSuccess;
 }
-hipError_t launch_move_slots(const DevPtrs&, int, int, const MoveArgs&, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_move_slots(const DevPtrs& d, int, int, const MoveArgs& mv, int n, hipStream_t)
+{
+    for (int i = 0; i < n; ++i) {
+        const int from = mv.from[i], to = mv.to[i];
+        for (int* a : {d.L, d.t, d.n_steps, d.done, d.failed}) a[to] = a[from];
+        d.failed[from] = 0;
+        std::copy_n(d.mel_ring + (size_t)from * d.max_steps * N_MEL, (size_t)d.max_steps * N_MEL, d.mel_ring + (size_t)to * d.max_steps * N_MEL);
+    }
+    return hipSuccess;
+}
 hipError_t launch_presum_tile(const DevPtrs&, int, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_prenet_slot(const DevPtrs&, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_x_get(int, const void*, int, int, int, int, float*, hipStream_t) { return hipErrorNotSupported; }

@@ -48,10 +48,10 @@ def _arena(nbytes):
 
 
 class FakePool:
-    def __init__(self, lib, weights, max_pool=4, max_steps=64, chunk=8, stream=1, segments=False, max_enc_len=16):
+    def __init__(self, lib, weights, max_pool=4, max_steps=64, chunk=8, stream=1, segments=False, max_enc_len=16, bf16=None):
         self.L, self.chunk = lib, chunk
         cfg = binding.make_config(synth.DIMS, max_pool=max_pool, max_enc_len=max_enc_len, max_steps=max_steps, chunk_frames=chunk, use_graph=segments,
-                                  bf16=segments)
+                                  bf16=segments if bf16 is None else bf16)
         n = int(lib.tts_pool_workspace_bytes(C.byref(cfg)))
         self._arena, at = _arena(n)
         w = binding.TtsWeights(*[weights[k].ctypes.data_as(C.POINTER(C.c_float)) for k in binding.WEIGHT_FIELDS])
@@ -319,6 +319,37 @@ def test_captured_call_takes_its_steps_one_by_one(lib, weights_fp32):
         got = [f for _ in range(3) for f in p.drain(r)[1]]
         assert got == _frames(20, 0, 20)
         p.close()
+
+
+@pytest.mark.parametrize("bf16,slots", [(False, 16), (True, 16), (True, 48)])
+def test_what_a_segment_goes_by_does_not_change_while_it_runs(lib, weights_fp32, bf16, slots):
+    """Requests that end with a segment's first step, inside it, with its last step and behind it, that leave, that move to lower slots, that
+    are lost: a workgroup that starts steps after the others counts the same steps as they do."""
+    pool = FakePool(lib, weights_fp32, max_pool=slots, max_steps=80, segments=True, bf16=bf16)
+    rids = [pool.add(n) for n in ([1, 2, 3, 7, 8, 9, 40, 41, 64, 80] * 5)[:slots]]
+    ninth = rids[9]
+    for k, n in enumerate((2, 6, 2, 6, 24, 30, 64)):
+        pool.step_n(n)
+        assert lib.fake_stale() == 0, k
+        if k in (2, 4):                                   # of those that have ended half leave, and others come
+            n_done = 0
+            for rid in list(rids):
+                got, done = C.c_int(), C.c_int()
+                assert lib.tts_pool_frames(pool.h, C.c_int64(rid), C.byref(got), C.byref(done)) == 0
+                n_done += done.value and rid != ninth
+                if done.value and rid != ninth and n_done % 2:
+                    assert lib.tts_pool_retire(pool.h, C.c_int64(rid)) == 0
+                    rids.remove(rid)
+            rids += [pool.add(n) for n in (2, 30, 31)]
+        if k == 3:
+            lib.fake_freeze(9, 20)                        # (of 80 frames, there from the beginning)
+    assert lib.fake_segments() == 7
+    lost = C.c_int()
+    assert lib.tts_pool_sync(pool.h) == binding.TTS_E_LOST
+    assert lib.tts_pool_lost(pool.h, C.c_int64(ninth), C.byref(lost)) == 0 and lost.value
+    if slots > 16:
+        assert lib.tts_pool_moves(pool.h) > 0
+    pool.close()
 
 
 # slots spanned, longest text -> fewest steps of a call that are one launch (None: never)
