@@ -292,8 +292,8 @@ static int absorb_failures(tts_pool* p)
     std::vector<int> failed(n), t(n);
     HIP_TRY(hipMemcpyAsync(failed.data(), p->d.failed, (size_t)n * 4, hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(hipMemcpyAsync(t.data(), p->d.t, (size_t)n * 4, hipMemcpyDeviceToHost, p->stream));
-    HIP_TRY(hipMemsetAsync(p->d.failed, 0, (size_t)n * 4, p->stream));
     HIP_TRY(wait_for_stream(p));
+    HIP_TRY(hipMemsetAsync(p->d.failed, 0, (size_t)n * 4, p->stream));        // not before the marks are here
     *p->h_fault = 0;
     for (int sl = 0; sl < n && sl < p->cfg.max_pool; ++sl) {
         if (!failed[sl] || p->book->slot(sl).state == SlotState::Free) continue;

@@ -157,6 +157,18 @@ def test_drain_whose_bookkeeping_fails_leaves_no_chunk_behind_that_was_never_mad
     pool.close()
 
 
+def test_what_the_device_lost_is_not_forgotten_by_a_wait_that_fails(lib, weights_fp32):
+    """Slot 1 is frozen after 5 frames of 8.  The wait for the device's marks fails: the next call still finds them."""
+    pool = FakePool(lib, weights_fp32)
+    a, b = pool.add(24), pool.add(23)
+    lib.fake_freeze(1, 5)
+    pool.step_n(8)
+    lib.fake_fail(b"hipStreamSynchronize", 2, 1)          # (the first wait is the chunks')
+    assert pool.drain(a)[0] == binding.TTS_E_HIP
+    assert pool.drain(b) == (0, _frames(23, 0, 5), True)
+    pool.close()
+
+
 @pytest.mark.parametrize("times", [1, 2])
 def test_pool_without_pinned_memory_for_its_chunks(lib, weights_fp32, times):
     """Where the pinned staging buffer cannot be had (the second pinned allocation; the first is the status word), the pool makes
