@@ -102,3 +102,33 @@ def test_segments_beside_other_work(weights_fp32):
         pool.close()
     for a, b in zip(*out):
         np.testing.assert_array_equal(a, b)
+
+
+def test_requests_that_end_on_their_way_beside_other_work(weights_fp32):
+    """As above, and every segment has requests that end inside it: what the workgroups count is all there is to end them.  (When a workgroup
+    starts is the scheduler's: that a late one counts the same steps is tests/test_host_faults.py's.)"""
+    import torch
+    say("case: fp32 segments of 16 slots that requests end in while a second stream runs large matrix products")
+    wl = synth.small_workload(16, 5, 90, 24, 24, seed=31)
+    frames = [2, 3, 4, 5, 6, 8, 11, 12, 13, 14, 20, 23, 24, 24, 24, 24]
+    out = []
+    for busy in (False, True):
+        pool = make_pool(wl, weights_fp32, max_pool=16, max_enc_len=90, max_steps=24, chunk_frames=24)
+        ids = pool.add_requests([wl.encoder_outputs(i) for i in range(16)], frames)
+        if busy:
+            side = torch.cuda.Stream(device=pool.device)
+            a = torch.randn(4096, 4096, device=pool.device)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                for _ in range(40):
+                    a = (a @ a) * 1e-4
+        for k in (4, 1, 7, 12):
+            pool.step_n(k)
+        pool.sync()                      # raises if a wait ran out
+        assert pool.fp32_segments() == 4
+        out.append([pool.drain_all(r) for r in ids])
+        assert [m.shape[0] for m in out[-1]] == frames
+        pool.close()
+        torch.cuda.synchronize()
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
