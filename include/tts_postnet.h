@@ -108,7 +108,7 @@ int tts_postnet_set_wait_polls(tts_postnet *pn, int polls);
 long long tts_postnet_one_launch_calls(const tts_postnet *pn);
 
 /* Device time of the last tts_postnet_run in milliseconds, from the start of its first launch to the end of its last; waits for the stream
- * (TTS_E_HIP while that is being captured). */
+ * (TTS_E_HIP while that is being captured).  Of a call that was captured it is the time of its graph's latest launch (TTS_E_INVAL before the first). */
 int tts_postnet_elapsed_ms(tts_postnet *pn, float *out_ms);
 
 void tts_postnet_destroy(tts_postnet *pn);

@@ -114,7 +114,7 @@ int tts_vocoder_run(tts_vocoder *v, const float *d_mel, const int *n_frames, con
                     int n, float *d_audio, int *out_samples);
 
 /* Device time of the last tts_vocoder_run in milliseconds, from the start of its first launch to the end of its last; waits for the stream
- * (TTS_E_HIP while that is being captured). */
+ * (TTS_E_HIP while that is being captured).  Of a call that was captured it is the time of its graph's latest launch (TTS_E_INVAL before the first). */
 int tts_vocoder_elapsed_ms(tts_vocoder *v, float *out_ms);
 
 void tts_vocoder_destroy(tts_vocoder *v);

@@ -28,15 +28,31 @@ inline hipError_t fill_now(void* dst, int value, size_t bytes)
     return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
 }
 
-// The call's time from its stamps; the stream is waited for (and therefore not while it is being captured).
-inline int stamps_ms(const Stamps& st, int khz, hipStream_t s, float* out_ms)
+// (by the caller, into a graph of his own; the default stream never is)
+inline bool being_captured(hipStream_t s)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (!s || hipStreamIsCapturing(s, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
+// A module's latest call that was queued.
+struct TimedCall {
+    unsigned long long number = 0;      // 0: none
+    bool captured = false;              // into a graph, and runs when that is launched
+};
+
+// The call's time from its stamps; the stream is waited for (and therefore not while it is being captured).  Stamps of another call than the
+// latest are those of a graph that was launched behind it, unless the latest is itself one that waits for its graph's launch: that has no time yet.
+inline int stamps_ms(const Stamps& st, const TimedCall& latest, int khz, hipStream_t s, float* out_ms)
 {
     unsigned long long t[STAMP_BYTES / 8], end = 0;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing(s, &capture));
-    if (capture != hipStreamCaptureStatusNone) return fail(TTS_E_HIP, "the stream is being captured");
+    if (!latest.number) return fail(TTS_E_INVAL, "nothing has run yet");
+    if (being_captured(s)) return fail(TTS_E_HIP, "the stream is being captured");
     HIP_TRY(hipMemcpyAsync(t, st.at, STAMP_BYTES, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    if (latest.captured && t[STAMP_CALL] != latest.number) return fail(TTS_E_INVAL, "the last call was captured and has not run yet");
     for (int i = 1; i <= STAMP_ENDS; ++i) end = t[i] > end ? t[i] : end;
     *out_ms = end > t[0] ? (float)(end - t[0]) / khz : 0.f;
     return TTS_OK;

@@ -61,7 +61,7 @@ struct tts_postnet {
     int device = -1;              // the device the arena (hence the weights) lives on
     hipStream_t stream = nullptr;
     int clock_khz = 0;            // of the stamps
-    bool ran = false;
+    TimedCall latest;             // of tts_postnet_run
     long long n_chained = 0;      // calls that were one launch
 };
 
@@ -218,8 +218,10 @@ extern "C" int tts_postnet_run(tts_postnet* p, const float* d_mel, const int* wi
                                float* d_out)
 {
     if (!p) return fail(TTS_E_INVAL, "null argument");
+    const bool captured = being_captured(p->stream);
+    ++p->d.stamps.call;
     const int rc = run_batch(p, p->d, p->cfg.max_columns, d_mel, win_len, keep_from, n, d_out);
-    p->ran = p->ran || rc == TTS_OK;
+    if (rc == TTS_OK) p->latest = {p->d.stamps.call, captured};
     return rc;
 }
 
@@ -257,8 +259,7 @@ extern "C" long long tts_postnet_one_launch_calls(const tts_postnet* p) { return
 extern "C" int tts_postnet_elapsed_ms(tts_postnet* p, float* out_ms)
 {
     if (!p || !out_ms) return fail(TTS_E_INVAL, "null argument");
-    if (!p->ran) return fail(TTS_E_INVAL, "nothing has run yet");
-    return stamps_ms(p->d.stamps, p->clock_khz, p->stream, out_ms);
+    return stamps_ms(p->d.stamps, p->latest, p->clock_khz, p->stream, out_ms);
 }
 
 extern "C" void tts_postnet_destroy(tts_postnet* p)

@@ -9,16 +9,21 @@ namespace tts {
 
 // Workgroups of the last launch share the end stamps by their number, those of an XCD (dealt by the number's last three bits) a part of them: what
 // two of them store to one place is not much apart, and the latest of all is the call's end.  Nothing has to be cleared: the clock only grows.
-constexpr int STAMP_ENDS = 256, STAMP_BYTES = (1 + STAMP_ENDS) * 8;
+// Behind them lies the number of the call that they are of: a call that was only captured has none of its own yet.
+constexpr int STAMP_ENDS = 256, STAMP_CALL = 1 + STAMP_ENDS, STAMP_BYTES = (STAMP_CALL + 1) * 8;
 
 struct Stamps {
-    unsigned long long* at;      // [0] the call's start, [1 ..] ends; null: the call is not timed
+    unsigned long long* at;      // [0] the call's start, [1 ..] ends, [STAMP_CALL] its number; null: the call is not timed
+    unsigned long long call;     // ... from 1 on
 #ifdef __HIPCC__
     // The start is read first and stored last: a store ahead of a wave's loads would hold them up until it is acknowledged.
     __device__ __forceinline__ unsigned long long now() const { return at ? wall_clock64() : 0; }
     __device__ __forceinline__ void begin(unsigned long long when) const
     {
-        if (at && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0) at[0] = when;
+        if (at && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0) {
+            at[0] = when;
+            at[STAMP_CALL] = call;
+        }
     }
     // by a thread of the workgroup that is through
     __device__ __forceinline__ void end() const

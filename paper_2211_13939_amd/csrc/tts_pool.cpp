@@ -791,15 +791,6 @@ static int launch_segment_steps(tts_pool* p, int g)
     return TTS_OK;
 }
 
-// (by the caller, into a graph of his own)
-static bool being_captured(const tts_pool* p)
-{
-    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    if (!p->stream || hipStreamIsCapturing(p->stream, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return false;
-}
-
 static int step_impl(tts_pool* p, int n, int64_t* out_frames, int* out_last_active)
 {
     int64_t frames = 0;
@@ -807,7 +798,7 @@ static int step_impl(tts_pool* p, int n, int64_t* out_frames, int* out_last_acti
     if (p->timing) HIP_TRY(hipEventRecord(p->ev0, p->stream));
     // A captured call takes its steps one by one: a graph cannot be captured or launched inside another capture, and which set of words a
     // segment uses changes with every launch, on the host.
-    const bool captured = being_captured(p);
+    const bool captured = being_captured(p->stream);
     Turn turn(p->resident, captured);
     int i = 0;
     while (i < n) {
@@ -881,7 +872,7 @@ extern "C" int tts_pool_kernel_times(tts_pool* p, int n, float* out_us, int cap,
         rc = push_membership(p);
         shape_for(p, p->slot_span, &sl);
     }
-    std::unique_ptr<Turn> turn(new Turn(p->resident, being_captured(p)));
+    std::unique_ptr<Turn> turn(new Turn(p->resident, being_captured(p->stream)));
     for (int i = 0; i < n && rc == TTS_OK; ++i) {
         // (a pool that empties on the way: the step before formed an attention LSTM in which no request took part)
         if (p->book->active().empty()) break;

@@ -104,7 +104,7 @@ struct tts_vocoder {
     VocoderPtrs d;
     hipStream_t stream = nullptr;
     int clock_khz = 0;              // of the stamps
-    bool ran = false;
+    TimedCall latest;
     std::vector<uint8_t> open;      // per state slot: a chunk went through and was not the last
 };
 
@@ -282,17 +282,18 @@ extern "C" int tts_vocoder_run(tts_vocoder* v, const float* d_mel, const int* n_
         off += emit;
         if (off > 0x7FFFFFFF) return fail(TTS_E_INVAL, "more than 2^31 samples in one call");
     }
+    const bool captured = being_captured(v->stream);
+    ++v->d.stamps.call;
     for (int i = 0; i < n; ++i) v->open[state_slot[i]] = (flags[i] & TTS_VOCODER_LAST) ? 0 : 1;
     HIP_TRY(launch_vocoder(v->d, v->cfg.weight_dtype, b, d_mel, d_audio, v->stream));
-    v->ran = true;
+    v->latest = {v->d.stamps.call, captured};
     return TTS_OK;
 }
 
 extern "C" int tts_vocoder_elapsed_ms(tts_vocoder* v, float* out_ms)
 {
     if (!v || !out_ms) return fail(TTS_E_INVAL, "null argument");
-    if (!v->ran) return fail(TTS_E_INVAL, "nothing has run yet");
-    return stamps_ms(v->d.stamps, v->clock_khz, v->stream, out_ms);
+    return stamps_ms(v->d.stamps, v->latest, v->clock_khz, v->stream, out_ms);
 }
 
 extern "C" void tts_vocoder_destroy(tts_vocoder* v)

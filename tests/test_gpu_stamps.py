@@ -67,3 +67,44 @@ def test_vocoder_call(bf16, requests):
     if requests > 1:
         assert _check(voc, lambda: voc.run_device(mel, [3], [0], whole[:1], audio), torch) < long
     voc.close()
+
+
+@pytest.mark.parametrize("module", ["postnet of 3 windows", "postnet of 60 windows", "vocoder"])
+def test_a_call_that_was_only_captured_has_no_time(module):
+    """Neither that of a call before it nor none at all; its graph's launches have theirs, and a call behind them has its own."""
+    import torch
+    say(f"case captured calls, {module}")
+    n = 60 if "60" in module else 3
+    if module == "vocoder":
+        obj = binding.Vocoder(binding.make_vocoder_config(overlap=8, max_chunk=40, max_requests=n, max_batch=n, bf16=True), synth.make_vocoder_weights(bf16=True))
+    else:
+        obj = binding.Postnet(binding.make_postnet_config(max_columns=n * 50, bf16=True), *synth.make_postnet_weights(bf16=True))
+    with torch.cuda.stream(obj.stream):
+        mel = torch.randn(n * 50, 80, device="cuda")
+        out = torch.zeros(n * 48 * binding.VOCODER_HOP, device="cuda")
+    whole = [binding.VOCODER_FIRST | binding.VOCODER_LAST] * n
+
+    def call(k):
+        if module == "vocoder":
+            obj.run_device(mel, [40] * k, list(range(k)), whole[:k], out)
+        else:
+            obj.run_device(mel, [50] * k, [10] * k, out)
+
+    for before in (False, True):
+        if before:
+            call(1)
+            assert obj.elapsed_ms() > 0
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=obj.stream):
+            call(n)
+        with pytest.raises(binding.TtsError) as e:
+            obj.elapsed_ms()
+        assert e.value.code == binding.TTS_E_INVAL
+        for _ in range(2):
+            with torch.cuda.stream(obj.stream):
+                graph.replay()
+            assert obj.elapsed_ms() > 0
+    call(1)
+    assert obj.elapsed_ms() > 0
+    torch.cuda.synchronize()
+    obj.close()
