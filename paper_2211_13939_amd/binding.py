@@ -602,8 +602,9 @@ class Vocoder:
         self._h = h
 
     def run_device(self, d_mel, n_frames, state_slot, flags, d_audio) -> list:
-        """d_mel: CUDA fp32 [sum n_frames, n_mel] (the chunks back to back); d_audio: CUDA fp32 with room for
-        256 * (overlap + n_frames[i]) samples per chunk.  Queued on the stream; returns the responses' lengths."""
+        """d_mel: CUDA fp32 [sum n_frames, n_mel] (the chunks back to back); d_audio: CUDA fp32 (or pinned host memory) with room for
+        256 * (overlap + n_frames[i]) samples per chunk.  Queued on the stream; returns the responses' lengths.  Both tensors are the
+        caller's to keep until the stream has come this far, pinned memory whichever stream it is used on."""
         nf = np.ascontiguousarray(n_frames, np.int32)
         sl = np.ascontiguousarray(state_slot, np.int32)
         fl = np.ascontiguousarray(flags, np.int32)

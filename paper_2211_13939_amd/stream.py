@@ -376,6 +376,15 @@ class GpuPostnetBackend(GpuBackend):
             self._sets = [one_set(i == 0) for i in range(self.N_SETS)]
             self._next_set = 0
 
+    def __del__(self):
+        # The vocoder's kernels store to pinned memory themselves: torch's allocator, which would hand it out again at once, knows of
+        # no use that it has to wait for, as it does behind a copy of its own.
+        try:
+            if self.vocoder is not None:
+                self.vocoder.stream.synchronize()
+        except Exception:
+            pass
+
     def _windows(self, d_in, ended):
         """The chunks that are ready, with their context, out of the pool's ring into d_in with one launch: (id, what the loop knows of it,
         context frames, frames, finished) of every request that may have one."""

@@ -79,3 +79,35 @@ def test_samples_to_pinned_memory(bf16, requests):
     assert n == requests * 40 * binding.VOCODER_HOP
     np.testing.assert_array_equal(host[:n].numpy(), dev[:n].cpu().numpy())
     voc.close()
+
+
+def test_buffers_of_a_loop_that_is_dropped_with_a_round_on_its_way(weights_fp32):
+    """The vocoder stores a round's samples to pinned memory: nobody else is given that memory before it has."""
+    import gc
+    import torch
+    from paper_2211_13939_amd import stream
+    say("case: an overlapped loop that is dropped while its vocoder round is queued")
+    wl = synth.small_workload(2, 10, 50, 24, 24, seed=53)
+    pool = make_pool(wl, weights_fp32, chunk_frames=12, max_pool=2)
+    side = torch.cuda.Stream(device=pool.device)
+    pn = binding.Postnet(binding.make_postnet_config(max_columns=2 * (12 + CTX)), *synth.make_postnet_weights(), stream=side)
+    voc = binding.Vocoder(binding.make_vocoder_config(overlap=4, max_chunk=12, max_requests=2, max_batch=2), synth.make_vocoder_weights(), stream=side)
+    be = stream.GpuPostnetBackend(pool, pn, lambda i: wl.encoder_outputs(i), wl.n_steps, 12, CTX, vocoder=voc, on_audio=lambda i, a: None, overlap=True)
+    for i in range(2):
+        be.add(i)
+    with torch.cuda.stream(side):
+        a = torch.ones(8192, 8192, device="cuda")
+        for _ in range(20):
+            a = (a @ a) * 1e-4
+    be.run(12)
+    assert be.pending() and not side.query()
+    size, mine = be._sets[0]["h_audio"].numel(), {st["h_audio"].data_ptr() for st in be._sets}
+    del be
+    gc.collect()
+    others = [torch.empty(size, pin_memory=True) for _ in range(6)]
+    done = side.query()
+    assert done or not mine & {t.data_ptr() for t in others}
+    torch.cuda.synchronize()
+    voc.close()
+    pn.close()
+    pool.close()
