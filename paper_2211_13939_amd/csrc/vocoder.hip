@@ -335,7 +335,10 @@ struct VrArgs {
     const uint4* W;                          // the six convolutions one after the other, [2 pair + {0: dilated, 1: plain}]
     const float* bias;                       // [2 * VOC_PAIRS][C]
 };
-struct VrArgs3 { VrArgs b[VOC_BLOCKS]; };
+struct VrArgs3 {
+    VrArgs b[VOC_BLOCKS];
+    VocLeast least;                  // the smallest regions
+};
 
 constexpr int VR_LDS_MAX = 160 * 1024;
 
@@ -610,15 +613,18 @@ __device__ __forceinline__ void resblock_tile(const VrArgs& a, int valid, size_t
         }
 }
 
-// The three residual blocks (kernels 3, 7, 11) of a stage: grid = (tiles, windows, 3), the longest first.
+// The three residual blocks (kernels 3, 7, 11) of a stage: grid = (tiles, windows, 3), the longest first.  The smallest regions: one dimension, the
+// regions of all windows (VocLeast).
 template <typename XT, int C, int TP, bool HALO>
 __global__ __launch_bounds__((VrGeom<XT, C, 3, TP, HALO>::THREADS), C == 8 ? (sizeof(XT) == 2 ? 4 : 3) : 2) void k_vres(VrArgs3 a3, const int* __restrict__ len, int rate, int window)
 {
     extern __shared__ uint4 lds_dyn[];
-    const int w = blockIdx.y, valid = len[w] * rate, tile = blockIdx.x;
+    int w = blockIdx.y, block = VOC_BLOCKS - 1 - blockIdx.z, tile = blockIdx.x;
+    if constexpr (VrGeom<XT, C, 3, TP, HALO>::TRIM) block = a3.least.block(blockIdx.x, &w, &tile);
+    const int valid = len[w] * rate;
     const size_t wbase = (size_t)w * window * rate;
-    if (blockIdx.z == 2) resblock_tile<XT, C, 3, TP, HALO>(a3.b[0], valid, wbase, tile, lds_dyn);
-    else if (blockIdx.z == 1) resblock_tile<XT, C, 7, TP, HALO>(a3.b[1], valid, wbase, tile, lds_dyn);
+    if (block == 0) resblock_tile<XT, C, 3, TP, HALO>(a3.b[0], valid, wbase, tile, lds_dyn);
+    else if (block == 1) resblock_tile<XT, C, 7, TP, HALO>(a3.b[1], valid, wbase, tile, lds_dyn);
     else resblock_tile<XT, C, 11, TP, HALO>(a3.b[2], valid, wbase, tile, lds_dyn);
 }
 
@@ -669,8 +675,14 @@ hipError_t blocks_launch_tp(const VrArgs3& a, const int* len, int rate, int wind
         attr_set = true;
     }
     constexpr int OUT = VrGeom<XT, C, voc_block_k(VOC_BLOCKS - 1), TP, HALO>::OUT;       // (the others have as many tiles or fewer)
-    const dim3 grid(HALO ? (c.longest * rate + OUT - 1) / OUT : 1, c.n, VOC_BLOCKS);
-    hipLaunchKernelGGL(kern, grid, dim3(VrGeom<XT, C, 3, TP, HALO>::THREADS), LDS, s, a, len, rate, window);
+    dim3 grid(HALO ? (c.longest * rate + OUT - 1) / OUT : 1, c.n, VOC_BLOCKS);
+    VrArgs3 args = a;
+    if constexpr (VrGeom<XT, C, 3, TP, HALO>::TRIM) {
+        static_assert(VrGeom<XT, C, 3, TP, HALO>::OUT == voc_least_out(0) && VrGeom<XT, C, 7, TP, HALO>::OUT == voc_least_out(1) && OUT == voc_least_out(2), "what comes out right");
+        args.least = voc_least(c.n, c.longest * rate);
+        grid = dim3(args.least.all());
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(VrGeom<XT, C, 3, TP, HALO>::THREADS), LDS, s, args, len, rate, window);
     return hipSuccess;
 }
 
@@ -688,7 +700,7 @@ template <int C, int LEVEL> constexpr int vr_tp() { return LEVEL == 3 ? 8 : ((C 
 // Us a call of n windows of 44 frames unless said otherwise, on one side of each line and on the other:
 //   whole       tiles / whole: 40, 48, 64, 96 windows 195 / 198, 222 / 220, 273 / 265, 383 / 361, of 32 frames 48, 64, 96: 163 / 171, 199 / 198, 277 / 260; fp32 48, 64:
 //               1125 / 1186, 1461 / 1424, of 32 frames 64, 96: 1037 / 1043, 1398 / 1355; of 16 frames half a tile holds them: 96 windows 159 / 168, fp32 740 / 856
-//   smallest    next larger / smallest: 3, 4 windows 73 / 71, 77 / 74, 5, 8: 84 / 84, 94 / 101 (beyond the line); fp32 4, 8: 336 / 242, 406 / 397, 10, 12: 425 / 461, 470 / 543
+//   smallest    next larger / smallest: 3, 4 windows 77 / 72, 80 / 76, 5, 8: 89 / 87, 98 / 100 (beyond the line); fp32 4, 8: 337 / 244, 409 / 400, 10, 12: 428 / 439, 472 / 546
 //   quarter     half / quarter: 24, 28 windows 146 / 145, 157 / 162; fp32 24, 32, 40: 707 / 647, 821 / 816, 956 / 1007
 //   half        large / half: 24, 28 windows 146.0 / 149.2, 157.1 / 159.2; fp32 707 / 734, 762 / 806
 constexpr int VR_WHOLE = 384;

@@ -27,6 +27,33 @@ constexpr int voc_cum_rate(int s) { return s == 0 ? 8 : (s == 1 ? 64 : (s == 2 ?
 
 constexpr int VOC_HAS_PREV = 2, VOC_LAST = 4;
 
+// The smallest regions of the residual blocks with 64 channels: what a block's halo leaves of 128 positions comes out right, so a block with a
+// shorter kernel has fewer regions.  A launch has a workgroup for every region that a window may have and no more, the longest kernel's first.  (With as many
+// for every block, those without a region were every window's same ones, and an XCD gets every eighth workgroup: where a window has 8 or 16
+// regions, of 8 or 16 frames, two XCDs had all of the shorter kernels'.  fp32, 40 windows of 8 frames / 20 of 16 / 6 of 32:
+// 476 / 470 / 326 us a call, like this 392 / 384 / 248; two-byte, 1 / 4 of 48: 54.3 / 78.6 -> 54.1 / 76.8.)
+constexpr int VOC_LEAST = 128;
+constexpr int voc_least_out(int b) { return VOC_LEAST - 12 * (voc_block_k(b) - 1); }
+struct VocLeast {
+    int windows, n[VOC_BLOCKS];                                 // regions of a window
+    __host__ __device__ int all() const { return windows * (n[0] + n[1] + n[2]); }
+    // workgroup i's block, window and region
+    __host__ __device__ int block(int i, int* window, int* tile) const
+    {
+        int b = VOC_BLOCKS - 1;
+        for (; b > 0 && i >= windows * n[b]; --b) i -= windows * n[b];
+        *window = i / n[b];
+        *tile = i - *window * n[b];
+        return b;
+    }
+};
+inline VocLeast voc_least(int windows, int positions)
+{
+    VocLeast l{windows, {}};
+    for (int b = 0; b < VOC_BLOCKS; ++b) l.n[b] = (positions + voc_least_out(b) - 1) / voc_least_out(b);
+    return l;
+}
+
 struct VocoderPtrs {
     // weights in MFMA A-fragment order (weight dtype), k = tap * C_in + channel; biases fp32
     const void* pre_w;  const float* pre_b;
