@@ -701,12 +701,13 @@ template <int C, int LEVEL> constexpr int vr_tp() { return LEVEL == 3 ? 8 : ((C 
 //   whole       tiles / whole: 40, 48, 64, 96 windows 195 / 198, 222 / 220, 273 / 265, 383 / 361, of 32 frames 48, 64, 96: 163 / 171, 199 / 198, 277 / 260; fp32 48, 64:
 //               1125 / 1186, 1461 / 1424, of 32 frames 64, 96: 1037 / 1043, 1398 / 1355; of 16 frames half a tile holds them: 96 windows 159 / 168, fp32 740 / 856
 //   smallest    next larger / smallest: 3, 4 windows 77 / 72, 80 / 76, 5, 8: 89 / 87, 98 / 100 (beyond the line); fp32 4, 8: 337 / 244, 409 / 400, 10, 12: 428 / 439, 472 / 546
-//   quarter     half / quarter: 24, 28 windows 146 / 145, 157 / 162; fp32 24, 32, 40: 707 / 647, 821 / 816, 956 / 1007
+//   quarter     half / quarter: 24, 28 windows 148 / 146, 159 / 163; fp32 24, 32, 36: 709 / 651, 826 / 821, 892 / 948; of 48 frames 28, 32: 780 / 776, 844 / 902;
+//               of 68 frames 20, 24: 787 / 781, 895 / 954
 //   half        large / half: 24, 28 windows 146.0 / 149.2, 157.1 / 159.2; fp32 707 / 734, 762 / 806
 constexpr int VR_WHOLE = 384;
 template <typename XT> constexpr int vr_whole_from() { return sizeof(XT) == 4 ? 224 : 192; }
 constexpr int VR_SMALL_BELOW = 700;
-template <typename XT, int C> constexpr int vr_tiny_upto() { return C != 64 ? 470 : sizeof(XT) == 4 ? 576 : 360; }
+template <typename XT, int C> constexpr int vr_tiny_upto() { return C != 64 ? 470 : sizeof(XT) == 4 ? 512 : 360; }
 template <typename XT> constexpr int vr_least_upto() { return sizeof(XT) == 4 ? 1100 : 800; }
 
 template <typename XT, int C>
