@@ -628,9 +628,9 @@ __global__ __launch_bounds__((VrGeom<XT, C, 3, TP, HALO>::THREADS), C == 8 ? (si
     else resblock_tile<XT, C, 11, TP, HALO>(a3.b[2], valid, wbase, tile, lds_dyn);
 }
 
-// What a call asks of every launch: its windows and the frames of the longest one.
+// What a call asks of every launch: its windows, the frames of the longest one and of all.
 struct Load {
-    int n, longest;
+    int n, longest, frames;
 };
 
 // grid = (tiles of a window, windows, row groups).  SHORT: tiles of 64 positions - for the layer that runs at one position
@@ -702,12 +702,13 @@ template <int C, int LEVEL> constexpr int vr_tp() { return LEVEL == 3 ? 8 : ((C 
 //               1125 / 1186, 1461 / 1424, of 32 frames 64, 96: 1037 / 1043, 1398 / 1355; of 16 frames half a tile holds them: 96 windows 159 / 168, fp32 740 / 856
 //   smallest    next larger / smallest: 3, 4 windows 77 / 72, 80 / 76, 5, 8: 89 / 87, 98 / 100 (beyond the line); fp32 4, 8: 337 / 244, 409 / 400, 10, 12: 428 / 439, 472 / 546
 //   quarter     half / quarter: 24, 28 windows 148 / 146, 159 / 163; fp32 24, 32, 36: 709 / 651, 826 / 821, 892 / 948; of 48 frames 28, 32: 780 / 776, 844 / 902;
-//               of 68 frames 20, 24: 787 / 781, 895 / 954
+//               of 68 frames 20, 24: 787 / 781, 895 / 954 (beyond VR_TINY_FULL); 4 fp32 windows of up to 400 frames, which have quarters without work, 653 / 592
 //   half        large / half: 24, 28 windows 146.0 / 149.2, 157.1 / 159.2; fp32 707 / 734, 762 / 806
 constexpr int VR_WHOLE = 384;
 template <typename XT> constexpr int vr_whole_from() { return sizeof(XT) == 4 ? 224 : 192; }
 constexpr int VR_SMALL_BELOW = 700;
-template <typename XT, int C> constexpr int vr_tiny_upto() { return C != 64 ? 470 : sizeof(XT) == 4 ? 512 : 360; }
+template <typename XT, int C> constexpr int vr_tiny_upto() { return C != 64 ? 470 : sizeof(XT) == 4 ? 576 : 360; }
+constexpr int VR_TINY_FULL = 490;                // quarters' worth of positions, of all windows together
 template <typename XT> constexpr int vr_least_upto() { return sizeof(XT) == 4 ? 1100 : 800; }
 
 template <typename XT, int C>
@@ -719,7 +720,7 @@ hipError_t blocks_launch(const VrArgs3& a, const int* len, int rate, int window,
         if (positions <= VR_WHOLE && positions > vr_tp<C, 1>() && large >= vr_whole_from<XT>()) return blocks_launch_tp<XT, C, VR_WHOLE, false>(a, len, rate, window, c, s);
         if (tiles(vr_tp<C, 3>()) <= vr_least_upto<XT>()) return blocks_launch_tp<XT, C, vr_tp<C, 3>(), true>(a, len, rate, window, c, s);
     }
-    if (tiles(vr_tp<C, 2>()) <= vr_tiny_upto<XT, C>()) return blocks_launch_tp<XT, C, vr_tp<C, 2>(), true>(a, len, rate, window, c, s);
+    if (tiles(vr_tp<C, 2>()) <= vr_tiny_upto<XT, C>() && (long)c.frames * rate * VOC_BLOCKS / vr_tp<C, 2>() <= VR_TINY_FULL) return blocks_launch_tp<XT, C, vr_tp<C, 2>(), true>(a, len, rate, window, c, s);
     return large < VR_SMALL_BELOW ? blocks_launch_tp<XT, C, vr_tp<C, 1>(), true>(a, len, rate, window, c, s)
                                   : blocks_launch_tp<XT, C, vr_tp<C, 0>(), true>(a, len, rate, window, c, s);
 }
@@ -750,8 +751,12 @@ hipError_t stage_launch(const VocoderPtrs& d, Load c, hipStream_t s)
 template <typename XT>
 hipError_t vocoder_typed(const VocoderPtrs& d, const VocBatch& b, const float* d_mel, float* d_audio, hipStream_t s)
 {
-    Load c{b.n, 0};
-    for (int w = 0; w < b.n; ++w) c.longest = std::max(c.longest, (b.has_prev[w] ? d.overlap : 0) + b.n_frames[w]);
+    Load c{b.n, 0, 0};
+    for (int w = 0; w < b.n; ++w) {
+        const int f = (b.has_prev[w] ? d.overlap : 0) + b.n_frames[w];
+        c.longest = std::max(c.longest, f);
+        c.frames += f;
+    }
     VcArgs pre{};
     pre.out = d.x0;
     pre.W = reinterpret_cast<const uint4*>(d.pre_w);
