@@ -197,20 +197,20 @@ int tts_pool_drain_chunk(tts_pool *pool, int64_t id, float *dst, int *out_frames
 int tts_pool_chunk_window(tts_pool *pool, int64_t id, int context, float *d_dst, int *out_context, int *out_frames,
                           int *out_finished);
 
+/*
+ * tts_pool_chunk_window for `n` (1 .. 256) different requests with one launch: their windows lie back to back in d_dst, in
+ * the order of `ids` (room for n * (context + chunk_frames) * n_mel floats; a request without a chunk that is ready has none
+ * there), and the three arrays of n say of each what that call says.  On an error nothing was handed out.
+ */
+int tts_pool_chunk_windows(tts_pool *pool, int n, const int64_t *ids, int context, float *d_dst, int *out_context,
+                           int *out_frames, int *out_finished);
+
 /* Stop logits of frames [first, first+count) of request `id` into HOST `dst`; waits for the stream. */
 int tts_pool_get_stop_logits(tts_pool *pool, int64_t id, int first, int count, float *dst);
 
 /* Remove a request ("if a request completes, its item is removed from the pool
  * immediately", Sec. 2.2.2); also allowed for an unfinished request.  Frees its slot. */
 int tts_pool_retire(tts_pool *pool, int64_t id);
-
-/*
- * The same for `n` (1 .. 256) different requests with one launch: their windows lie back to back in d_dst, in the order of `ids` (room for
- * n * (context + chunk_frames) * n_mel floats; a request without a chunk that is ready has none there), and the three arrays of n say of
- * each what tts_pool_chunk_window says.  On an error nothing was handed out.
- */
-int tts_pool_chunk_windows(tts_pool *pool, int n, const int64_t *ids, int context, float *d_dst, int *out_context,
-                           int *out_frames, int *out_finished);
 
 /* Copy one carried state of request `id` to HOST `dst` (fp32, `cap` elements of
  * room); *out_n receives the element count.  Waits for the stream. */
