@@ -1,7 +1,7 @@
 // Which pools of this process may launch beside which.
 //
-// The workgroups of a segment's launch (segment.hip) wait for each other and take a compute unit each, 24 of the 32 of an XCD, until the segment
-// ends.  Two such launches on one device, or one beside another pool's step launches, whose workgroups wait for each other too, could
+// The workgroups of a segment's launch (segment.hip) wait for each other and take a compute unit each, 24 of the 32 of an XCD (fp32: up to 27), until the
+// segment ends.  Two such launches on one device, or one beside another pool's step launches, whose workgroups wait for each other too, could
 // each get a part of their workgroups started and wait for the rest until the bound of the waits ends the requests of both.  So on one
 // device a segment's launch begins when the other pools' launches so far have ended, and a step's when the other pools' segments have;
 // steps of several pools run beside each other (a step's launches leave room for another's workgroups on a compute unit).

@@ -759,7 +759,8 @@ static int fewest_segment_steps(int tiles, int longest)
 // of 165 positions, steps as launches in graphs -> as one launch: 1 request 16.8 -> 9.7 us a step, 8: 18.2 -> 10.3, 16: 18.5 -> 11.2,
 // 20: 19.7 -> 13.5, 32: 20.4 -> 13.8, 48: 21.2 -> 17.7; with four tiles, 64 requests, 21.6 -> 21.5.  Single steps, each waited for: 1 request
 // 49 -> 30 us.  fp32 pools (segment32.hip) in one tile take it always: calls of 40 steps, 1 request of 60 positions 37.3 -> 14.9 us a step, 16 of 60 38.9 ->
-// 16.9, of 250 39.9 -> 19.5, of 1024 50.3 -> 46.8, 8 of 1024 49.6 -> 28.5; single steps, 16 of 60 44.8 -> 24.4, of 1024 56.8 -> 55.8.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other streams that
+// 16.9, of 250 39.9 -> 19.5, of 1024 50.7 -> 44.1, 8 of 1024 49.8 -> 27.6; single steps, 16 of 60 44.8 -> 24.4, of 1024 59.0 -> 58.7, each waited
+// for 70.3 -> 67.7.  At most MAX_SEGMENT_STEPS a launch (beyond, the start of a launch no longer shows), so that work on other streams that
 // needs every compute unit gets them at intervals.
 static int segment_steps(const tts_pool* p, int n)
 {

@@ -695,11 +695,11 @@ template <int C, int LEVEL> constexpr int vr_tp() { return LEVEL == 3 ? 8 : ((C 
 // registers and LDS whole and needs none: a CU per window and block, which pays where there are enough of them, unless half a tile holds the window.
 //
 // All lines below look at the call's longest window, whatever the configuration allows: `large` counts positions in large tiles, the others their own
-// workgroups.  (By the configured window, 48 frames: calls of 4 / 16 / 64 / 128 windows of 16 frames 68.0 / 84.9 / 157.8 / 219 us, like this 57.0 / 77.6 /
-// 133 / 188; fp32 320 / 358 / 777 / 1125 -> 195 / 294 / 588 / 988; of 32 frames 73.0 / 106.8 / 206 / 343 -> 66.0 / 102.9 / 197 / 325.)
+// workgroups.  (By the configured window, 44 frames: calls of 4 / 16 / 64 / 128 windows of 12 frames 62.6 / 85.9 / 152 / 204 us, like this 58.5 / 79.1 /
+// 135 / 189; fp32 225 / 357 / 781 / 1100 -> 197 / 250 / 584 / 881; of 28 frames 66.7 / 107 / 202 / 330 -> 64.1 / 105 / 198 / 327, fp32 229 / 457 / 1095 / 1743 -> 222 / 428 / 934 / 1689.)
 // Us a call of n windows of 44 frames unless said otherwise, on one side of each line and on the other:
-//   whole       tiles / whole: 40, 48, 64, 96 windows 195 / 198, 222 / 220, 273 / 265, 383 / 361, of 32 frames 48, 64, 96: 163 / 171, 199 / 198, 277 / 260; fp32 48, 64:
-//               1125 / 1186, 1461 / 1424, of 32 frames 64, 96: 1037 / 1043, 1398 / 1355; of 16 frames half a tile holds them: 96 windows 159 / 168, fp32 740 / 856
+//   whole       tiles / whole: 40, 48, 64, 96 windows 195 / 198, 221 / 219, 270 / 263, 377 / 357, of 28 frames 48, 64, 96: 164 / 172, 198 / 199, 275 / 257; fp32 48, 64:
+//               1138 / 1198, 1475 / 1435, of 28 frames 64, 96: 933 / 1050, 1400 / 1366; of 12 frames half a tile holds them: 96 windows 159 / 169, fp32 800 / 864
 //   smallest    next larger / smallest: 3, 4 windows 77 / 72, 80 / 76, 5, 8: 89 / 87, 98 / 100 (beyond the line); fp32 4, 8: 337 / 244, 409 / 400, 10, 12: 428 / 439, 472 / 546
 //   quarter     half / quarter: 24, 28 windows 148 / 146, 159 / 163; fp32 24, 32, 36: 709 / 651, 826 / 821, 892 / 948; of 48 frames 28, 32: 780 / 776, 844 / 902;
 //               of 68 frames 20, 24: 787 / 781, 895 / 954 (beyond VR_TINY_FULL); 4 fp32 windows of up to 400 frames, which have quarters without work, 653 / 592
